@@ -185,35 +185,77 @@ bool is_device_memory(const void *p)
 }
 
 // Routing of a single batch computed on the spot (no cache, or a schedule the cache has no plan for).
-__global__ void route_batch_kernel(const int32_t *__restrict__ ids, int64_t n, const uint8_t *__restrict__ is_local, const int32_t *__restrict__ row_of,
-                                   const SlotRec *__restrict__ slot_pairs /* see slot_lookup; NULL: no cache */, int64_t *__restrict__ entry, unsigned long long *__restrict__ counts /* local, hit, miss */)
+//
+// Bound by its scattered reads (is_local, row_of and a slot-map record per listed ID), so a thread takes ROUTE_PER_THREAD
+// IDs and has the reads of all of them in flight at once.  The counts go through LDS to two adds per workgroup, spread
+// over ROUTE_COUNT_SLOTS pairs of counters which the host adds up: three adds per wave to the same three addresses queued
+// up behind each other at 11 ns apiece and were nine tenths of the kernel (a batch of 1.2 M rows of 512 bytes: routing
+// 615 us, now under 20; the whole call 852 -> 243 us, its gather 227).  Misses are not counted: they are the rows that are
+// neither local nor cached.
+constexpr int ROUTE_THREADS = 256;
+constexpr int ROUTE_PER_THREAD = 4;
+constexpr int ROUTE_TILE = ROUTE_THREADS * ROUTE_PER_THREAD;
+constexpr int ROUTE_COUNT_SLOTS = 16;
+constexpr size_t ROUTE_COUNT_BYTES = 2 * ROUTE_COUNT_SLOTS * sizeof(unsigned long long);      // local, hit per slot
+
+// entry == NULL: the counts alone.  counts == NULL: the entries alone.
+__global__ void __launch_bounds__(ROUTE_THREADS) route_batch_kernel(const int32_t *__restrict__ ids, int64_t n, const uint8_t *__restrict__ is_local,
+                                                                    const int32_t *__restrict__ row_of,
+                                                                    const SlotRec *__restrict__ slot_pairs /* see slot_lookup; NULL: no cache */,
+                                                                    int64_t *__restrict__ entry, unsigned long long *__restrict__ counts)
 {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t tag = -1;
-    if (j < n) {
-        const int32_t v = ids[j];
-        int64_t row;
-        if (is_local[v]) { tag = TAG_LOCAL; row = row_of[v]; }
-        else {
-            const int32_t slot = slot_pairs ? slot_lookup(slot_pairs, (uint32_t)v) : -1;
-            if (slot >= 0) { tag = TAG_CACHE; row = slot; }
-            else { tag = TAG_REMOTE; row = row_of[v]; }
-        }
-        entry[j] = make_entry(tag, row);
+    __shared__ unsigned int red[2][ROUTE_THREADS / 64];
+    const int64_t j0 = (int64_t)blockIdx.x * ROUTE_TILE + threadIdx.x;
+    int32_t v[ROUTE_PER_THREAD], row[ROUTE_PER_THREAD], slot[ROUTE_PER_THREAD];
+    uint8_t local[ROUTE_PER_THREAD];
+#pragma unroll
+    for (int k = 0; k < ROUTE_PER_THREAD; ++k) v[k] = ids[min(j0 + k * ROUTE_THREADS, n - 1)];        // (past the end: the last ID again, not used)
+#pragma unroll
+    for (int k = 0; k < ROUTE_PER_THREAD; ++k) local[k] = is_local[v[k]];
+#pragma unroll
+    for (int k = 0; k < ROUTE_PER_THREAD; ++k) slot[k] = slot_pairs ? slot_lookup(slot_pairs, (uint32_t)v[k]) : -1;
+    if (entry)
+#pragma unroll
+        for (int k = 0; k < ROUTE_PER_THREAD; ++k) row[k] = row_of[v[k]];
+    unsigned int n_local = 0, n_hit = 0;                       // of the wave
+#pragma unroll
+    for (int k = 0; k < ROUTE_PER_THREAD; ++k) {
+        const int64_t j = j0 + k * ROUTE_THREADS;
+        const bool is_loc = local[k] != 0, is_hit = !is_loc && slot[k] >= 0;
+        if (entry && j < n) entry[j] = make_entry(is_loc ? TAG_LOCAL : is_hit ? TAG_CACHE : TAG_REMOTE, is_hit ? slot[k] : row[k]);
+        n_local += (unsigned int)__popcll(__ballot(is_loc && j < n));
+        n_hit += (unsigned int)__popcll(__ballot(is_hit && j < n));
     }
-    const unsigned long long ml = __ballot(tag == TAG_LOCAL), mh = __ballot(tag == TAG_CACHE), mm = __ballot(tag == TAG_REMOTE);
-    if ((threadIdx.x & 63) == 0) {
-        if (ml) atomicAdd(&counts[0], (unsigned long long)__popcll(ml));
-        if (mh) atomicAdd(&counts[1], (unsigned long long)__popcll(mh));
-        if (mm) atomicAdd(&counts[2], (unsigned long long)__popcll(mm));
+    if (!counts) return;
+    if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = n_local; red[1][threadIdx.x >> 6] = n_hit; }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned int c = 0;
+        for (int w = 0; w < ROUTE_THREADS / 64; ++w) c += red[threadIdx.x][w];
+        if (c) atomicAdd(&counts[2 * (blockIdx.x % ROUTE_COUNT_SLOTS) + threadIdx.x], (unsigned long long)c);
     }
 }
 
+static void launch_route(const int32_t *ids, int64_t n, const rg_features *f, const SlotRec *slot_pairs, int64_t *entry, unsigned long long *counts, hipStream_t st)
+{
+    if (n <= 0) return;
+    hipLaunchKernelGGL(route_batch_kernel, dim3((unsigned)((n + ROUTE_TILE - 1) / ROUTE_TILE)), dim3(ROUTE_THREADS), 0, st, ids, n, f->is_local, f->row_of,
+                       slot_pairs, entry, counts);
+}
+
+static void sum_route_counts(const unsigned long long *counts /* host, [2 * ROUTE_COUNT_SLOTS] */, int64_t n_rows, rg_gather_stats *stats)
+{
+    uint64_t local = 0, hit = 0;
+    for (int s = 0; s < ROUTE_COUNT_SLOTS; ++s) { local += counts[2 * s]; hit += counts[2 * s + 1]; }
+    stats->n_rows = (uint64_t)n_rows; stats->n_local = local; stats->n_hit = hit; stats->n_miss = (uint64_t)n_rows - local - hit;
+}
+
 // ---------------------------------------------------------------- the entry point that allocates nothing
-// Its scratch -- the three counters and one routing entry per row of the batch -- lives in the library's image: one
+// Its scratch -- the counters and one routing entry per row of the batch -- lives in the library's image: one
 // copy per GPU, at an address of that GPU's own, which the host asks for once per device.  The array's name is only a
 // stand-in on the host; kernels and copies get the pointer kept here.
 constexpr uint64_t NOALLOC_HEAD_BYTES = 256;                       // the counters, in front of the entries
+static_assert(ROUTE_COUNT_BYTES <= NOALLOC_HEAD_BYTES, "the counters fit in front of the entries");
 static __device__ __align__(256) unsigned char scratch[NOALLOC_HEAD_BYTES + RG_NOALLOC_MAX_ROWS * sizeof(int64_t)];
 
 constexpr int MAX_DEVICES = 64;
@@ -240,7 +282,7 @@ static rg_status scratch_of_current_device(unsigned char **out)
 // (a fill kernel, not hipMemsetAsync: the call may be recorded into a graph)
 __global__ void clear_counts_kernel(unsigned long long *__restrict__ counts)
 {
-    if (threadIdx.x < 3) counts[threadIdx.x] = 0ull;
+    if (threadIdx.x < 2 * ROUTE_COUNT_SLOTS) counts[threadIdx.x] = 0ull;
 }
 
 }  // namespace rg
@@ -278,19 +320,18 @@ extern "C" rg_status rg_gather_batch_noalloc(const rg_schedule *s, const rg_cach
     hipStream_t st = as_stream(stream);
     RowSources src{(const uint8_t *)f->local_rows, f->local_stride, c ? (const uint8_t *)c->rows : (const uint8_t *)f->local_rows,
                    c ? c->stride : f->local_stride, (const uint8_t *)f->remote_rows, f->remote_stride};
-    hipLaunchKernelGGL(clear_counts_kernel, dim3(1), dim3(64), 0, st, counts);
+    if (stats) hipLaunchKernelGGL(clear_counts_kernel, dim3(1), dim3(64), 0, st, counts);
     if (m > 0) {
-        hipLaunchKernelGGL(route_batch_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, h.ids + off, m, f->is_local, f->row_of,
-                           c ? c->slot_pairs : nullptr, entry, counts);
+        launch_route(h.ids + off, m, f, c ? c->slot_pairs : nullptr, entry, stats ? counts : nullptr, st);
         RG_HIP(hipGetLastError());
         RG_TRY(launch_gather(entry, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, -1));      // (group -1: no event timers, they are created on demand)
     }
     RG_HIP(hipGetLastError());
     if (stats) {
-        unsigned long long hc[3] = {0, 0, 0};
+        unsigned long long hc[2 * ROUTE_COUNT_SLOTS];
         RG_HIP(hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, st));
         RG_HIP(hipStreamSynchronize(st));
-        stats->n_rows = (uint64_t)m; stats->n_local = hc[0]; stats->n_hit = hc[1]; stats->n_miss = hc[2];
+        sum_route_counts(hc, m, stats);
     }
     return RG_OK;
 }
@@ -349,27 +390,27 @@ extern "C" rg_status rg_gather_batch(const rg_schedule *s, const rg_cache *c, co
         return RG_OK;
     }
 
-    // No prepared plan: classify this batch now, copy every row on `stream`, wait for the counts.
+    // No prepared plan: classify this batch now, copy every row on `stream`, wait for both.
     Arena tmp(s->arena.allocator(), st);     // scratch from the allocator the schedule was built with
     int64_t *entry = nullptr;
-    unsigned long long *counts = nullptr;
+    unsigned long long *counts = nullptr, hc[2 * ROUTE_COUNT_SLOTS] = {};
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)m, &entry));
-    RG_TRY(tmp.dev_n<unsigned long long>(3, &counts));
-    RG_HIP(hipMemsetAsync(counts, 0, 3 * sizeof(unsigned long long), st));
+    if (stats) {
+        RG_TRY(tmp.dev(ROUTE_COUNT_BYTES, (void **)&counts));
+        RG_HIP(hipMemsetAsync(counts, 0, ROUTE_COUNT_BYTES, st));
+    }
     if (m > 0) {
         {
             ScopedTimer tm(KG_PLAN, st);
-            hipLaunchKernelGGL(route_batch_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, h.ids + off, m, f->is_local, f->row_of,
-                               c ? c->slot_pairs : nullptr, entry, counts);
+            launch_route(h.ids + off, m, f, c ? c->slot_pairs : nullptr, entry, counts, st);
         }
         RG_HIP(hipGetLastError());
         RG_TRY(launch_gather(entry, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
     }
-    unsigned long long hc[3] = {0, 0, 0};
-    RG_HIP(hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, st));
+    if (stats) RG_HIP(hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, st));
     RG_HIP(hipStreamSynchronize(st));
     tmp.drained();
-    if (stats) { stats->n_rows = (uint64_t)m; stats->n_local = hc[0]; stats->n_hit = hc[1]; stats->n_miss = hc[2]; }
+    if (stats) sum_route_counts(hc, m, stats);
     return RG_OK;
 }
 
@@ -464,22 +505,19 @@ extern "C" rg_status rg_classify_batch(const rg_schedule *s, const rg_cache *c, 
     const int64_t off = h.off_host[batch], m = h.off_host[batch + 1] - off;
     hipStream_t st = as_stream(stream);
     Arena tmp(s->arena.allocator(), st);     // scratch from the allocator the schedule was built with
-    int64_t *entry = nullptr;
     unsigned long long *counts = nullptr;
-    RG_TRY(tmp.dev_n<int64_t>((uint64_t)m, &entry));
-    RG_TRY(tmp.dev_n<unsigned long long>(3, &counts));
-    RG_HIP(hipMemsetAsync(counts, 0, 3 * sizeof(unsigned long long), st));
+    RG_TRY(tmp.dev(ROUTE_COUNT_BYTES, (void **)&counts));
+    RG_HIP(hipMemsetAsync(counts, 0, ROUTE_COUNT_BYTES, st));
     if (m > 0) {
         ScopedTimer tm(KG_PLAN, st);
-        hipLaunchKernelGGL(route_batch_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, h.ids + off, m, f->is_local, f->row_of,
-                           c ? c->slot_pairs : nullptr, entry, counts);
+        launch_route(h.ids + off, m, f, c ? c->slot_pairs : nullptr, nullptr, counts, st);
     }
-    unsigned long long hc[3] = {0, 0, 0};
+    unsigned long long hc[2 * ROUTE_COUNT_SLOTS] = {};
     hipError_t e1 = hipGetLastError();
     hipError_t e2 = hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, st);
     hipError_t e3 = hipStreamSynchronize(st);                    // also before `tmp` is released
     if (e3 == hipSuccess) tmp.drained();
     if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) { set_error("rg_classify_batch: HIP call failed"); return RG_EHIP; }
-    stats->n_rows = (uint64_t)m; stats->n_local = hc[0]; stats->n_hit = hc[1]; stats->n_miss = hc[2];
+    sum_route_counts(hc, m, stats);
     return RG_OK;
 }
