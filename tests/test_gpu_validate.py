@@ -1,0 +1,63 @@
+"""rg_graph_validate's count against a count row by row in numpy: sizes around the vectors, waves and tiles of the flat
+pass, indices at every 4-byte phase, IDs and rows damaged in every way the check names."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rg():
+    from paper_2509_05207_amd import binding
+    binding.lib()
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return binding
+
+
+def count_row_by_row(indptr, indices):
+    n, bad = indptr.size - 1, 0
+    for v in range(n):
+        b, e = int(indptr[v]), int(indptr[v + 1])
+        if e < b or (v == 0 and b != 0):
+            bad += 1
+            continue
+        for j in range(b, e):
+            u = int(indices[j])
+            if u < 0 or u >= n or (j > b and indices[j - 1] >= u):
+                bad += 1
+    return bad
+
+
+def check(rg, indptr, indices, phase):
+    pad = torch.zeros(indices.size + phase, dtype=torch.int32, device="cuda")
+    pad[phase:] = torch.from_numpy(indices).cuda()
+    assert rg.rg_graph_validate(torch.from_numpy(indptr).cuda(), pad[phase:]) == count_row_by_row(indptr, indices)
+
+
+@pytest.mark.parametrize("edges", [0, 1, 3, 4, 5, 7, 255, 256, 257, 1023, 1025, 4099, 20_011])
+@pytest.mark.parametrize("phase", [0, 1, 2, 3])
+def test_violations_are_counted_at_every_size_and_phase(rg, edges, phase):
+    rng = np.random.default_rng(7 * edges + phase)
+    n = 500
+    cuts = np.sort(rng.integers(0, edges + 1, size=n - 1))
+    indptr = np.concatenate([[0], cuts, [edges]]).astype(np.int64)                 # empty rows among them
+    rows = [np.sort(rng.choice(n, size=int(d), replace=d > n)) for d in np.diff(indptr)]
+    indices = np.concatenate(rows).astype(np.int32) if edges else np.zeros(0, np.int32)
+    check(rg, indptr, indices, phase)
+    if edges:
+        hit = rng.integers(0, edges, size=1 + edges // 50)
+        indices[hit] = rng.choice(np.array([-1, n, n + 5, 0, n - 1, -2**31, 2**31 - 1], np.int64), size=hit.size).astype(np.int32)
+        check(rg, indptr, indices, phase)
+
+
+def test_rows_out_of_order_are_counted_row_by_row(rg):
+    rng = np.random.default_rng(3)
+    n, deg = 3000, 8
+    indptr = np.arange(0, deg * n + 1, deg).astype(np.int64)
+    indices = np.sort(rng.integers(0, n, size=(n, deg)), axis=1).astype(np.int32).ravel()
+    for damage in ({5: 5 * deg - 11}, {0: 3}, {n // 2: 0, 17: 19 * deg}, {n: 0}):
+        bad = indptr.copy()
+        for k, x in damage.items():
+            bad[k] = x
+        check(rg, bad, indices, 0)
