@@ -162,43 +162,58 @@ __global__ void __launch_bounds__(TOPK_THREADS) digit_histogram8_kernel(const ui
         if (h[k]) atomicAdd(&mine[k], (unsigned long long)h[k]);
 }
 
-// One workgroup of DIGIT_BINS threads: sum the copies of each bin (and clear them for the next pass), then one thread
-// walks the bins from the top until `want` is covered.
+// One workgroup of DIGIT_BINS threads: sum the copies of each bin (and clear them for the next pass), then find the bin
+// from the top in which `want` is covered.  Bound by the latency of its loads and of whatever runs in one thread: the
+// copies are read eight at a time and the bins above each bin added up by a scan (bins walked by one thread, copies
+// read one after the other: 15-20 us; so: under 5).
 __global__ void __launch_bounds__(DIGIT_BINS) choose_digit_kernel(SelectState *__restrict__ stp, unsigned long long *__restrict__ bins_copies, int shift,
                                                                   int first_pass, uint64_t K)
 {
-    __shared__ unsigned long long bins[DIGIT_BINS];
-    {
-        unsigned long long sum = 0;
-        for (int cpy = 0; cpy < BIN_COPIES; ++cpy) {
-            sum += bins_copies[(size_t)cpy * DIGIT_BINS + threadIdx.x];
-            bins_copies[(size_t)cpy * DIGIT_BINS + threadIdx.x] = 0;
-        }
-        bins[threadIdx.x] = sum;
+    __shared__ unsigned long long wave_sum[DIGIT_BINS / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int bin = DIGIT_BINS - 1 - (int)threadIdx.x;                 // thread 0 has the top bin
+    unsigned long long mine = 0;
+    for (int c0 = 0; c0 < BIN_COPIES; c0 += 8) {
+        unsigned long long x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = bins_copies[(size_t)(c0 + u) * DIGIT_BINS + bin];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { mine += x[u]; bins_copies[(size_t)(c0 + u) * DIGIT_BINS + bin] = 0; }
     }
+    unsigned long long incl = mine;                                    // of this bin and the bins above it
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned long long y = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += y;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    SelectState st = *stp;
-    if (first_pass) {
-        uint64_t tot = 0;
-        for (int k = 0; k < DIGIT_BINS; ++k) tot += bins[k];
-        st.n_candidates = tot;
-        st.want = K;
-        if (K >= tot) { st.take_all = 1; st.t = 0; st.r = 0; st.k_eff = tot; }
-        else st.k_eff = K;
+    unsigned long long total = 0;
+    for (int w = 0; w < DIGIT_BINS / 64; ++w) {
+        if (w < wave) incl += wave_sum[w];
+        total += wave_sum[w];
     }
-    if (!st.take_all) {
-        uint64_t above = 0;
-        int d = DIGIT_BINS - 1;
-        for (; d > 0; --d) {
-            if (above + bins[d] >= st.want) break;
-            above += bins[d];
+    const SelectState was = *stp;
+    __syncthreads();                                                   // everyone has read the state before one thread writes it
+    const uint64_t want = first_pass ? K : was.want;
+    const bool all = first_pass ? K >= total : was.take_all != 0;
+    if (all) {
+        if (first_pass && threadIdx.x == 0) {
+            SelectState st = was;
+            st.n_candidates = total; st.want = K; st.take_all = 1; st.t = 0; st.r = 0; st.k_eff = total;
+            *stp = st;
         }
-        st.want -= above;                         // still to take inside digit d
-        st.prefix |= (uint32_t)d << shift;
-        st.prefix_mask |= (uint32_t)(DIGIT_BINS - 1) << shift;
-        if (shift == 0) { st.t = st.prefix; st.r = st.want; }
+        return;
     }
+    // the bin in which the count from the top first reaches `want`; the last one if none does
+    const unsigned long long above = incl - mine;
+    const bool chosen = bin > 0 ? above + mine >= want && (threadIdx.x == 0 || above < want) : above < want || threadIdx.x == 0;
+    if (!chosen) return;
+    SelectState st = was;
+    if (first_pass) { st.n_candidates = total; st.k_eff = K; }
+    st.want = want - above;                                            // still to take inside this digit
+    st.prefix |= (uint32_t)bin << shift;
+    st.prefix_mask |= (uint32_t)(DIGIT_BINS - 1) << shift;
+    if (shift == 0) { st.t = st.prefix; st.r = st.want; }
     *stp = st;
 }
 
@@ -424,88 +439,104 @@ struct RouteSources {
     const int32_t *row_of;
     const SlotRec *slot_pairs;       // see slot_lookup
 };
-__device__ __forceinline__ int64_t route_of(const RouteSources &r, int64_t v)
-{
-    const SlotRec p = r.slot_pairs[v >> 5];
-    const uint32_t bit = 1u << (v & 31);
-    if (p.z & bit) return make_entry(TAG_LOCAL, r.row_of[v]);
-    if (p.x & bit) return make_entry(TAG_CACHE, (int64_t)(p.y + __popc(p.x & (bit - 1))));
-    return make_entry(TAG_REMOTE, r.row_of[v]);
-}
-
-// entry[j] = route_of(ids[j]) for every listed input node, which of them are misses (one bit each, in position order:
-// a wave's ballot is the 64-bit word of its 64 consecutive positions), the misses of every tile of PLAN_TILE
-// positions, and per-batch counts of local rows and cache hits.  A block covers one tile and adds its counts once
-// when it lies inside one batch (nearly always), else position by position.
+// entry[j] = where ids[j] is served from, for every listed input node, which of them are misses and which are local (one
+// bit each, in position order: a wave's ballot is the 64-bit word of its 64 consecutive positions), and how many of
+// either each tile of PLAN_TILE positions holds.  Nothing is added up per batch here: the tiles of a batch run at the
+// same time, and two adds per tile to the batch's counters queued up behind each other (an epoch of 80 M input nodes in
+// 196 batches: 712 us with the adds, 494 with tiles of 1,024 positions without them, 441 so; 111 M nodes, 4.2 M input
+// nodes: 253 -> 122).  The kernel waits for its dependent reads (ID, slot-map record, row), so each kind
+// is asked for by all of a thread's positions before the first answer is used.
 constexpr int PLAN_THREADS = 256;
-constexpr int PLAN_PER_THREAD = 4;
+constexpr int PLAN_PER_THREAD = 8;
 constexpr int PLAN_TILE = PLAN_THREADS * PLAN_PER_THREAD;
-constexpr int PLAN_TILE_WORDS = PLAN_TILE / 64;          // miss-bit words per tile
+constexpr int PLAN_TILE_WORDS = PLAN_TILE / 64;          // bit words per tile
 
-__global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__restrict__ ids, int64_t n, const int64_t *__restrict__ batch_off, uint32_t n_batches,
-                                                            RouteSources rs,
-                                                            int64_t *__restrict__ entry, unsigned long long *__restrict__ miss_bits /* [tiles * PLAN_TILE_WORDS] */,
-                                                            int32_t *__restrict__ tile_miss /* [tiles] */,
-                                                            unsigned long long *__restrict__ counts /* [n_batches][2]: local, hit */)
+__global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__restrict__ ids, int64_t n, RouteSources rs, int64_t *__restrict__ entry,
+                                                            unsigned long long *__restrict__ miss_bits /* [tiles * PLAN_TILE_WORDS] */,
+                                                            unsigned long long *__restrict__ local_bits /* the same */,
+                                                            int32_t *__restrict__ tile_miss /* [tiles] */, int32_t *__restrict__ tile_local /* [tiles] */)
 {
-    __shared__ unsigned int red[3][PLAN_THREADS / 64];
+    __shared__ int red[2][PLAN_THREADS / 64];
     const int64_t tile0 = (int64_t)blockIdx.x * PLAN_TILE;
-    const int64_t tile_last = (tile0 + PLAN_TILE <= n ? tile0 + PLAN_TILE : n) - 1;
-    const uint32_t b_first = batch_of_pos(batch_off, n_batches, tile0);
-    const bool one_batch = batch_off[b_first + 1] > tile_last;                 // block-uniform
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned int n_local = 0, n_hit = 0, n_miss = 0;                           // n_miss: of the wave (the same in all its lanes)
+    uint32_t v[PLAN_PER_THREAD];
+    SlotRec rec[PLAN_PER_THREAD];
+    int32_t row[PLAN_PER_THREAD];
+#pragma unroll
+    for (int k = 0; k < PLAN_PER_THREAD; ++k) v[k] = (uint32_t)ids[min(tile0 + (int64_t)k * PLAN_THREADS + threadIdx.x, n - 1)];      // (past the end: the last ID again, not used)
+#pragma unroll
+    for (int k = 0; k < PLAN_PER_THREAD; ++k) rec[k] = rs.slot_pairs[v[k] >> 5];
+#pragma unroll
+    for (int k = 0; k < PLAN_PER_THREAD; ++k) {
+        const uint32_t bit = 1u << (v[k] & 31);
+        // a cached row is at its rank, the others at row_of
+        row[k] = (rec[k].x & ~rec[k].z & bit) ? (int32_t)(rec[k].y + __popc(rec[k].x & (bit - 1))) : rs.row_of[v[k]];
+    }
+    int n_local = 0, n_miss = 0;                           // of the wave
 #pragma unroll
     for (int k = 0; k < PLAN_PER_THREAD; ++k) {
         const int64_t j = tile0 + (int64_t)k * PLAN_THREADS + threadIdx.x;
-        int64_t tag = -1;
-        if (j < n) {
-            const int64_t e = route_of(rs, ids[j]);
-            tag = entry_tag(e);
-            entry[j] = e;
-            if (one_batch) { n_local += tag == TAG_LOCAL; n_hit += tag == TAG_CACHE; }
-            else if (tag != TAG_REMOTE) {
-                const uint32_t b = batch_of_pos(batch_off, n_batches, j);
-                atomicAdd(&counts[2 * (uint64_t)b + (tag == TAG_CACHE ? 1 : 0)], 1ull);
-            }
+        const uint32_t bit = 1u << (v[k] & 31);
+        const bool local = (rec[k].z & bit) != 0, cached = !local && (rec[k].x & bit) != 0;
+        if (j < n) __builtin_nontemporal_store(make_entry(local ? TAG_LOCAL : cached ? TAG_CACHE : TAG_REMOTE, row[k]), entry + j);
+        const unsigned long long ml = __ballot(j < n && local), mm = __ballot(j < n && !local && !cached);
+        if (lane == 0) {
+            const uint64_t word = (uint64_t)blockIdx.x * PLAN_TILE_WORDS + k * (PLAN_THREADS / 64) + wave;
+            miss_bits[word] = mm;
+            local_bits[word] = ml;
         }
-        const unsigned long long m = __ballot(tag == TAG_REMOTE);
-        if (lane == 0) miss_bits[(uint64_t)blockIdx.x * PLAN_TILE_WORDS + k * (PLAN_THREADS / 64) + wave] = m;
-        n_miss += (unsigned int)__popcll(m);
+        n_local += __popcll(ml);
+        n_miss += __popcll(mm);
     }
-    for (int o = 32; o > 0; o >>= 1) { n_local += __shfl_down(n_local, o, 64); n_hit += __shfl_down(n_hit, o, 64); }
-    if (lane == 0) { red[0][wave] = n_local; red[1][wave] = n_hit; red[2][wave] = n_miss; }
+    if (lane == 0) { red[0][wave] = n_miss; red[1][wave] = n_local; }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned int a = 0, h = 0, m = 0;
-        for (int w = 0; w < PLAN_THREADS / 64; ++w) { a += red[0][w]; h += red[1][w]; m += red[2][w]; }
-        tile_miss[blockIdx.x] = (int32_t)m;
-        if (one_batch) {
-            if (a) atomicAdd(&counts[2 * (uint64_t)b_first], (unsigned long long)a);
-            if (h) atomicAdd(&counts[2 * (uint64_t)b_first + 1], (unsigned long long)h);
-        }
+    if (threadIdx.x < 2) {
+        int c = 0;
+        for (int w = 0; w < PLAN_THREADS / 64; ++w) c += red[threadIdx.x][w];
+        (threadIdx.x == 0 ? tile_miss : tile_local)[blockIdx.x] = c;
     }
 }
 
-// Misses in front of position pos: those of the tiles in front of its tile (tile_scan) and of the words and bits in front of it inside the tile.
-__device__ __forceinline__ int64_t misses_before(const unsigned long long *__restrict__ miss_bits, const int64_t *__restrict__ tile_scan, int64_t pos)
+// Set bits among positions [lo, hi), counted by a wave (the sum is the lanes' together).
+__device__ __forceinline__ int64_t lane_bits_between(const unsigned long long *__restrict__ bits, int64_t lo, int64_t hi, int lane)
 {
-    const int64_t tile = pos / PLAN_TILE, word = pos >> 6;
-    int64_t cnt = tile_scan[tile];
-    for (int64_t w = tile * PLAN_TILE_WORDS; w < word; ++w) cnt += __popcll(miss_bits[w]);
-    const int bit = (int)(pos & 63);
-    if (bit) cnt += __popcll(miss_bits[word] & ((1ull << bit) - 1ull));
+    int64_t cnt = 0;
+    for (int64_t w = (lo >> 6) + lane; (w << 6) < hi; w += 64) {
+        unsigned long long m = bits[w];
+        if ((w << 6) < lo) m &= ~0ull << (lo & 63);
+        if (hi - (w << 6) < 64) m &= (1ull << (hi & 63)) - 1ull;
+        cnt += __popcll(m);
+    }
     return cnt;
 }
 
-// miss_off[b] = misses in front of batch b's first position (miss_off[n_batches] = all of them)
-__global__ void miss_offsets_kernel(const unsigned long long *__restrict__ miss_bits, const int64_t *__restrict__ tile_scan, int64_t n, int64_t n_tiles,
-                                    const int64_t *__restrict__ batch_off, uint32_t n_batches, int64_t *__restrict__ miss_off)
+// One wave per batch (and one for the end).  miss_off[b] = misses in front of batch b's first position: those of the
+// tiles in front of its tile (tile_scan) and of the positions in front of it inside the tile; n_local[b] = its local
+// rows: the whole tiles between its ends, and the bits of the tiles it begins and ends in.
+__global__ void __launch_bounds__(64) batch_counts_kernel(const unsigned long long *__restrict__ miss_bits, const unsigned long long *__restrict__ local_bits,
+                                                          const int64_t *__restrict__ tile_scan, const int32_t *__restrict__ tile_local, int64_t n, int64_t n_tiles,
+                                                          const int64_t *__restrict__ batch_off, uint32_t n_batches, int64_t *__restrict__ miss_off,
+                                                          int64_t *__restrict__ n_local)
 {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b > n_batches) return;
-    const int64_t pos = batch_off[b];
-    miss_off[b] = pos >= n ? tile_scan[n_tiles] : misses_before(miss_bits, tile_scan, pos);
+    const uint32_t b = blockIdx.x;
+    const int lane = threadIdx.x;
+    const int64_t lo = batch_off[b], t_lo = lo / PLAN_TILE;
+    int64_t before = lo < n ? lane_bits_between(miss_bits, t_lo * PLAN_TILE, lo, lane) : 0;
+    int64_t local = 0;
+    if (b < n_batches) {
+        const int64_t hi = batch_off[b + 1], t_hi = hi / PLAN_TILE;
+        if (t_lo == t_hi) local = lane_bits_between(local_bits, lo, hi, lane);
+        else {
+            local = lane_bits_between(local_bits, lo, (t_lo + 1) * PLAN_TILE, lane);
+            for (int64_t t = t_lo + 1 + lane; t < t_hi; t += 64) local += tile_local[t];
+            local += lane_bits_between(local_bits, t_hi * PLAN_TILE, hi, lane);
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) { before += __shfl_down(before, o, 64); local += __shfl_down(local, o, 64); }
+    if (lane == 0) {
+        miss_off[b] = lo < n ? tile_scan[t_lo] + before : tile_scan[n_tiles];
+        if (b < n_batches) n_local[b] = local;
+    }
 }
 
 // miss_rows[rank of the miss] = its position within its batch, for every miss.  A workgroup takes one tile: every
@@ -553,29 +584,28 @@ rg_status build_plan(const rg_schedule *s, const RouteSources &rs, Arena &keep, 
     if (beta == 0) { RG_TRY(keep.dev_n<int32_t>(0, &plan->miss_rows)); return RG_OK; }
 
     const int64_t n_tiles = (n + PLAN_TILE - 1) / PLAN_TILE, n_words = n_tiles * PLAN_TILE_WORDS;
-    unsigned long long *miss_bits = nullptr;
-    int32_t *tile_miss = nullptr;
-    int64_t *tile_scan = nullptr, *miss_off_dev = nullptr;
-    unsigned long long *counts = nullptr;
+    unsigned long long *miss_bits = nullptr, *local_bits = nullptr;
+    int32_t *tile_miss = nullptr, *tile_local = nullptr;
+    int64_t *tile_scan = nullptr, *miss_off_dev = nullptr, *n_local_dev = nullptr;
     RG_TRY(tmp.dev_n<unsigned long long>((uint64_t)std::max<int64_t>(n_words, 1), &miss_bits));
+    RG_TRY(tmp.dev_n<unsigned long long>((uint64_t)std::max<int64_t>(n_words, 1), &local_bits));
     RG_TRY(tmp.dev_n<int32_t>((uint64_t)std::max<int64_t>(n_tiles, 1), &tile_miss));
+    RG_TRY(tmp.dev_n<int32_t>((uint64_t)std::max<int64_t>(n_tiles, 1), &tile_local));
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_tiles + 1, &tile_scan));
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)beta + 1, &miss_off_dev));
-    RG_TRY(tmp.dev_n<unsigned long long>(2 * (uint64_t)beta, &counts));
-    RG_HIP(hipMemsetAsync(counts, 0, 2 * (uint64_t)beta * sizeof(unsigned long long), st));
+    RG_TRY(tmp.dev_n<int64_t>((uint64_t)beta, &n_local_dev));
     {
         ScopedTimer tm(KG_PLAN, st);
         if (n > 0)
-            hipLaunchKernelGGL(plan_kernel, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, h.off_dev, beta,
-                               rs, plan->entry, miss_bits, tile_miss, counts);
+            hipLaunchKernelGGL(plan_kernel, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, plan->entry, miss_bits, local_bits, tile_miss, tile_local);
         RG_TRY(scan_i32_to_i64(tile_miss, tile_scan, n_tiles, tmp, st));
-        hipLaunchKernelGGL(miss_offsets_kernel, dim3((beta + 1 + 255) / 256), dim3(256), 0, st, miss_bits, tile_scan, n, n_tiles, h.off_dev, beta, miss_off_dev);
+        hipLaunchKernelGGL(batch_counts_kernel, dim3(beta + 1), dim3(64), 0, st, miss_bits, local_bits, tile_scan, tile_local, n, n_tiles, h.off_dev, beta, miss_off_dev, n_local_dev);
     }
-    std::vector<unsigned long long> hc(2 * (size_t)beta);
+    std::vector<int64_t> n_local(beta);
     {
         Readback rb(st);
         RG_TRY(rb.add(plan->miss_off.data(), miss_off_dev, ((size_t)beta + 1) * sizeof(int64_t)));
-        RG_TRY(rb.add(hc.data(), counts, hc.size() * sizeof(unsigned long long)));
+        RG_TRY(rb.add(n_local.data(), n_local_dev, (size_t)beta * sizeof(int64_t)));
         RG_TRY(rb.wait());
     }
     const int64_t n_miss = plan->miss_off[beta];
@@ -588,12 +618,11 @@ rg_status build_plan(const rg_schedule *s, const RouteSources &rs, Arena &keep, 
     for (uint32_t b = 0; b < beta; ++b) {
         rg_gather_stats &g = plan->stats[b];
         g.n_rows = (uint64_t)(h.off_host[b + 1] - h.off_host[b]);
-        g.n_local = hc[2 * (size_t)b];
-        g.n_hit = hc[2 * (size_t)b + 1];
+        g.n_local = (uint64_t)n_local[b];
         g.n_miss = (uint64_t)(plan->miss_off[b + 1] - plan->miss_off[b]);
+        g.n_hit = g.n_rows - g.n_local - g.n_miss;
     }
-    RG_HIP(hipStreamSynchronize(st));
-    return RG_OK;
+    return RG_OK;                 // (the caller waits for the stream before `tmp` goes back)
 }
 
 // The tally as uint32_t[n_nodes] for rg_cache_view: the array itself, or -- where the build counted in bytes -- a

@@ -1,0 +1,46 @@
+"""A cache's plans where batches and the plan kernel's tiles of 2,048 positions meet: batches that begin and end inside a
+tile, on its edge, span several, are many to a tile; counts and rows against numpy."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rg():
+    from paper_2509_05207_amd import binding
+    binding.lib()
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return binding
+
+
+@pytest.mark.parametrize("n_train,batch", [(1, 1), (300, 7), (2047, 2047), (2048, 2048), (2049, 2048), (4096, 64), (6145, 2049), (10_000, 5000), (30_000, 4096)])
+@pytest.mark.parametrize("K", [0, 900, 60_000])
+def test_counts_and_rows_of_every_batch(rg, n_train, batch, K):
+    rng = np.random.default_rng(n_train + K)
+    n = 60_000
+    d = "cuda"
+    indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
+    train = torch.from_numpy(rng.permutation(n)[:n_train].astype(np.int32)).to(d)
+    scheds = [rg.rg_build_schedule(indptr, indices, train, batch, [], 5, 0, e) for e in (0, 1)]
+    is_local = (rng.random(n) < 0.25).astype(np.uint8)
+    row_of = np.where(is_local, np.cumsum(is_local) - 1, np.cumsum(1 - is_local) - 1).astype(np.int32)
+    table = rng.integers(0, 2**31, size=(n, 4)).astype(np.int32)
+    remote = torch.from_numpy(table[is_local == 0]).pin_memory()          # misses go through the miss lists
+    feat = rg.make_features(torch.from_numpy(is_local).to(d), torch.from_numpy(row_of).to(d), torch.from_numpy(table[is_local == 1]).to(d), remote, 16)
+    cache = rg.rg_build_cache(scheds, feat, K)
+    cached = np.zeros(n, bool)
+    cached[rg.rg_cache_view(cache, n)["cache_ids"].cpu().numpy()] = True
+    for s in scheds:
+        ids, _, off = rg.rg_schedule_frontier(s, 0)
+        ids = ids.cpu().numpy()
+        want = []
+        for b in range(s.n_batches):
+            v = ids[off[b]:off[b + 1]]
+            local, hit = int(is_local[v].sum()), int((cached[v] & (is_local[v] == 0)).sum())
+            want.append(dict(n_rows=v.size, n_local=local, n_hit=hit, n_miss=v.size - local - hit))
+        out = torch.full((n_train, 4), -7, dtype=torch.int32, device=d)
+        assert rg.rg_gather_batches(s, cache, feat, 0, s.n_batches, out) == want
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), table[ids])
