@@ -186,6 +186,34 @@ __device__ __forceinline__ uint32_t kth_key_threshold(const uint32_t (&k)[E], co
     return lo + (uint32_t)((((uint64_t)1) << (bit + 1)) - 1u);
 }
 
+// How many IDs of a row a guessed cut lets through on average.  Keys are uniform 32-bit words, so about lambda of the
+// row's keys lie at or below lambda / len of the key range; the guess decides only how much work is done, never the
+// result: if fewer than f keys turn up (a Poisson count: one row in 600 to 900 for fan-outs of 5 to 25), the exact
+// procedure runs.  Every candidate is an append and widens the final cut, so the guess is as low as the misses allow:
+// with f + 4 sqrt(f) + 8 a row is missed once in 10^5 but three candidates in ten are superfluous.
+__device__ __forceinline__ float guessed_candidates(int f) { return (float)f + 3.0f * __fsqrt_rn((float)f) + 3.0f; }
+// The cut itself, its lower half all ones (see key32_open); share <= 0.5.
+__device__ __forceinline__ uint32_t guessed_cut_of(float share) { return (uint32_t)(share * 4294967296.0f) | 0xFFFFu; }
+
+// The f smallest keys among cnt candidates buf[0 .. cnt) (row order; f <= cnt <= 64, one per lane), none above `upper`,
+// written to out in row order and marked.  The IDs go from the candidate's lane straight to their place: the
+// row's registers, or the buffer, are not passed over again.
+template <int MARK>
+__device__ __forceinline__ void emit_candidates(const uint32_t *buf, int cnt, int f, uint32_t lo, uint32_t hi, uint32_t upper, int lane,
+                                                int32_t *__restrict__ out, const ReachedOfBatch &reached_b)
+{
+    cnt = uni(cnt); f = uni(f); lo = uni(lo); hi = uni(hi);
+    const uint32_t u = lane < cnt ? buf[lane] : 0u;
+    const uint32_t k[1] = {key32(lo, hi, u)};
+    const unsigned long long vm[1] = {low_lanes(cnt)};
+    const uint32_t cut = uni(kth_key_threshold<1>(k, vm, f, cnt, uni(upper)));       // (may be the end of its bracket: no candidate lies between upper and it)
+    const unsigned long long m = ballot64(k[0] <= cut) & vm[0];
+    if (my_bit(m)) {
+        out[lanes_below(m, lane)] = (int32_t)u;
+        mark_reached<MARK>(reached_b, u);
+    }
+}
+
 // Row of f < len <= 64 * E IDs held in registers (u[e] of lane l is row[e * 64 + l]),
 // sampled and written to out in row order.  buf: scratch of at least 64 entries (used when E > 1).
 template <int E, int MARK>
@@ -198,18 +226,14 @@ __device__ __forceinline__ void sample_registers(const uint32_t (&u)[E], int len
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         vm[e] = low_lanes(len - e * 64);
-        k[e] = key32(lo, hi, u[e]);
+        k[e] = key32_open(lo, hi, u[e]);
     }
-    uint32_t cut = 0;
-    bool have_cut = false;
     if (E > 1) {
-        // As for long rows, a cut guessed from the key distribution first: about lambda of the row's keys lie below
-        // lambda / len.  If between f and 64 do, the threshold is searched among those alone, one key per lane and
-        // from the guessed cut's leading bit down, instead of among all E registers from bit 31; the f smallest keys of the
-        // row are among them, so the result is the same.  Otherwise (or for rows too short to guess) the search below.
-        const float lambda = (float)f + 4.0f * __fsqrt_rn((float)f) + 8.0f;
-        if (uni(lambda * 2.0f <= (float)len)) {
-            const uint32_t guessed = uni((uint32_t)(lambda / (float)len * 4294967296.0f));
+        // As for long rows, a cut guessed from the key distribution first.  If between f and 64 IDs pass, they are
+        // listed one per lane and the threshold is searched among those alone, from the guessed cut's leading bit down.
+        const float lambda = guessed_candidates(f);
+        if (uni(lambda * 2.0f <= (float)len && lambda <= 56.0f)) {          // (a larger fan-out lets more than 64 through as a rule)
+            const uint32_t guessed = uni(guessed_cut_of(lambda / (float)len));
             unsigned long long m[E];
             int total = 0;
 #pragma unroll
@@ -221,20 +245,19 @@ __device__ __forceinline__ void sample_registers(const uint32_t (&u)[E], int len
                 int base = 0;
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    if (my_bit(m[e])) buf[base + lanes_below(m[e], lane)] = k[e];
+                    if (my_bit(m[e])) buf[base + lanes_below(m[e], lane)] = u[e];
                     base += __popcll(m[e]);
                 }
                 __syncthreads();
-                const uint32_t ck[1] = {lane < total ? buf[lane] : 0u};
-                const unsigned long long cvm[1] = {low_lanes(total)};
-                cut = kth_key_threshold<1>(ck, cvm, f, total, guessed);
-                if (cut > guessed) cut = guessed;      // (the search may answer with the end of its bracket: keys above the guess are no candidates)
-                have_cut = true;
+                emit_candidates<MARK>(buf, total, f, lo, hi, guessed, lane, out, reached_b);
                 __syncthreads();      // the scratch is free again
+                return;
             }
         }
     }
-    if (!have_cut) cut = kth_key_threshold<E>(k, vm, f, len);
+#pragma unroll
+    for (int e = 0; e < E; ++e) k[e] ^= k[e] >> 16;
+    const uint32_t cut = kth_key_threshold<E>(k, vm, f, len);
     int base = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -413,7 +436,7 @@ __device__ __forceinline__ void stream_block(const u32x4 &blk, int count, int f,
     append_block<CAP, MAYBE_OPEN>(u, k, vm, f, lo, hi, lane, buf, s);
 }
 
-// A full block while a cut is in force, the common outcomes only: no candidate, or candidates that fit the buffer.
+// A full block while a cut whose lower half is all ones is in force, the common outcomes only: no candidate, or candidates that fit the buffer.
 // Returns false, with nothing done, when they do not fit; the caller then takes the block through append_block.
 template <int CAP>
 __device__ __forceinline__ bool stream_full_block_fast(const u32x4 &blk, uint32_t lo, uint32_t hi, int lane, uint32_t *buf, Stream &s)
@@ -423,7 +446,7 @@ __device__ __forceinline__ bool stream_full_block_fast(const u32x4 &blk, uint32_
     s.cnt = uni(s.cnt);
     unsigned long long m[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) m[e] = ballot64(key32(lo, hi, u[e]) <= cut);
+    for (int e = 0; e < 4; ++e) m[e] = ballot64(key32_open(lo, hi, u[e]) <= cut);
     const unsigned long long any = m[0] | m[1] | m[2] | m[3];
     if (any == 0ull) return true;
     const int total = __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]);
@@ -445,14 +468,14 @@ __device__ __forceinline__ bool stream_full_block_fast(const u32x4 &blk, uint32_
     return true;
 }
 
-// Row of len > 256 IDs streamed once; on return buf[0..f) is the sample in row order.  The IDs in
+// Row of len > 256 IDs streamed once, its sample written to out in row order and marked.  The IDs in
 // front of the first 128-byte boundary go first (one per lane); from there on the row is read in
 // blocks of 1 KB, one aligned 16-byte load per lane, so no two loads of a wave share a cache line,
 // and the next block's load is in flight while the current block's keys are computed.
 // first = row[lane] and blk0 = row_ahead(row, len, lane), loaded by the caller.
-template <int CAP>
+template <int CAP, int MARK>
 __device__ __forceinline__ void sample_long_row(const int32_t *__restrict__ row, int len, uint32_t first, int f, uint32_t lo, uint32_t hi, int lane,
-                                                uint32_t *buf, const u32x4 &blk0)
+                                                uint32_t *buf, const u32x4 &blk0, int32_t *__restrict__ out, const ReachedOfBatch &reached_b)
 {
     len = uni(len); f = uni(f); lo = uni(lo); hi = uni(hi);
     const int head = uni(row_head(row, len));
@@ -460,14 +483,13 @@ __device__ __forceinline__ void sample_long_row(const int32_t *__restrict__ row,
     const int rem = len - head;                                  // > 0: len > 256 and head < 32
     const int n_blocks = (rem + 255) >> 8;
     const uint32_t head_u = lane < head ? first : 0u;          // the head is part of the row's leading 64 IDs, which the caller holds
-    // First attempt with a guessed cut.  Keys are uniform 32-bit words, so about lambda = f + 4 sqrt(f) + 8 of the
-    // row's keys fall below lambda / len: streaming with that cut from the start collects the few IDs that can be in
-    // the sample and skips the first cut and the prunes of the exact procedure.  The guess never changes the result:
-    // every ID with a key up to the cut is kept, so if at least f turn up, the f smallest keys of the row are among
-    // them; if fewer do (once in thousands of rows), the row is streamed again with the exact procedure.
-    const float lambda = (float)f + 4.0f * __fsqrt_rn((float)f) + 8.0f;
+    // First attempt with a guessed cut (see guessed_candidates): streaming with it from the start collects the few IDs
+    // that can be in the sample and skips the first cut and the prunes of the exact procedure.  Every ID with a key up to
+    // the cut is kept, so if at least f turn up, the f smallest keys of the row are among them; if fewer do, the row is
+    // streamed again with the exact procedure.
+    const float lambda = guessed_candidates(f);
     const bool can_guess = uni(lambda * 4.0f <= (float)len);
-    const uint32_t guessed_cut = (uint32_t)(fminf(lambda / (float)len, 0.5f) * 4294967296.0f);
+    const uint32_t guessed_cut = guessed_cut_of(fminf(lambda / (float)len, 0.5f));
     Stream s{0, true, 0u};
     const int first_attempt = uni(can_guess ? 0 : 1);
   for (int attempt = first_attempt; attempt < 2; attempt = uni(attempt + 1)) {
@@ -558,11 +580,18 @@ __device__ __forceinline__ void sample_long_row(const int32_t *__restrict__ row,
     __syncthreads();
     if (s.cnt >= f) break;                                       // (always, in the exact attempt: len > f)
   }
-    if (s.cnt > f) {
-        const uint32_t upper = s.open ? 0xFFFFFFFFu : s.cut;
-        if (CAP > 64 && s.cnt <= 64) (void)prune_buffer<64>(buf, s.cnt, f, lo, hi, lane, upper);     // the usual case after a guessed cut: one ID per lane
-        else (void)prune_buffer<CAP>(buf, s.cnt, f, lo, hi, lane, upper);
+    const uint32_t upper = s.open ? 0xFFFFFFFFu : s.cut;
+    if (s.cnt <= 64) {                                           // the usual case after a guessed cut: one ID per lane
+        emit_candidates<MARK>(buf, s.cnt, f, lo, hi, upper, lane, out, reached_b);
+    } else {
+        if (s.cnt > f) (void)prune_buffer<CAP>(buf, s.cnt, f, lo, hi, lane, upper);
+        for (int j = lane; j < f; j += 64) {
+            const uint32_t u = buf[j];
+            out[j] = (int32_t)u;
+            mark_reached<MARK>(reached_b, u);
+        }
     }
+    __syncthreads();      // the buffer is reused by the wave's next row
 }
 
 // SAMPLE of a row of len > f IDs into out (row order), marking the sampled IDs as MARK says.
@@ -578,13 +607,7 @@ __device__ __forceinline__ void sample_row(const int32_t *__restrict__ row, int 
         const uint32_t u[4] = {first, ahead.x, ahead.y, ahead.z};
         sample_registers<4, MARK>(u, len, f, lo, hi, lane, buf, out, reached_b);
     } else {
-        sample_long_row<CAP>(row, len, first, f, lo, hi, lane, buf, ahead);
-        for (int j = lane; j < f; j += 64) {
-            const uint32_t u = buf[j];
-            out[j] = (int32_t)u;
-            mark_reached<MARK>(reached_b, u);
-        }
-        __syncthreads();      // the buffer is reused by the wave's next row
+        sample_long_row<CAP, MARK>(row, len, first, f, lo, hi, lane, buf, ahead, out, reached_b);
     }
 }
 
