@@ -109,7 +109,10 @@ typedef struct rg_cache rg_cache;
  * mark with byte stores, 2 in the others); RAPIDGNN_GROUP_TILES=1 / 0 forces /
  * forbids handing out the pieces of rows above 16,384 IDs grouped by the piece
  * they read, so that batches that share a row meet in the caches (default: from
- * 16,384 pieces on).  The result is the same in every case.  The maps are drawn from a pool of blocks known to be
+ * 16,384 pieces on); RAPIDGNN_HUB_ROWS=<IDs> makes rows of at least so many IDs
+ * (and more than 16,384) be sampled from the keys' side, without being read
+ * (default: behind the first hop of epochs of 8 batches and more, from a length
+ * computed from the fan-out and n_nodes).  The result is the same in every case.  The maps are drawn from a pool of blocks known to be
  * all-zero and handed back to it after the build has cleared what it touched;
  * RAPIDGNN_CHECK_ZERO_MAPS=1 makes every build verify that on the device first.
  */

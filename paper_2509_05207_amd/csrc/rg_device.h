@@ -46,6 +46,24 @@ __device__ __forceinline__ uint32_t key32(uint32_t lo, uint32_t hi, uint32_t u)
     return x ^ (x >> 16);
 }
 
+// The neighbour ID whose key is x: key32 undone step by step (an odd multiplier's inverse modulo 2^32 by Newton's
+// iteration, which doubles the right low bits each time).
+constexpr uint32_t inverse32(uint32_t a)
+{
+    uint32_t y = a;                                // right in the low 3 bits: a * a = 1 modulo 8
+    for (int k = 0; k < 4; ++k) y *= 2u - a * y;
+    return y;
+}
+static_assert(inverse32(HG32) * HG32 == 1u && inverse32(HA32) * HA32 == 1u && inverse32(HB32) * HB32 == 1u, "");
+__device__ __forceinline__ uint32_t key32_inverse(uint32_t lo, uint32_t hi, uint32_t x)
+{
+    x ^= x >> 16; x *= inverse32(HB32);
+    x ^= (x >> 15) ^ (x >> 30); x *= inverse32(HA32);
+    x -= hi;
+    x ^= x >> 16; x *= inverse32(HG32);
+    return x ^ lo;
+}
+
 // ---------------------------------------------------------------- drawn positions (the O(f) sampler)
 // Position p_t of draw t among the deg > f slots of a row, for a node state s; p_0, p_1, ... are distinct.
 //   deg <= 64: selection without replacement.  Draw k takes r_k = floor(u_k * (deg - k)), u_k the top 32 bits of

@@ -41,6 +41,8 @@
 
 #include <algorithm>
 #include <atomic>
+#include <climits>
+#include <cmath>
 #include <cstdlib>
 
 namespace rg {
@@ -62,6 +64,67 @@ struct NodeRecs {
     uint64_t *state;      // S_v = combine(combine(S_{e,i}, hop + 1), v)
 };
 
+// ---------------------------------------------------------------- hub rows: found by node_records_kernel
+// The longest rows are not read at all (see hub_sample_kernel): each distinct one gets an entry in a small hash table
+// keyed by node, with room for a table of its IDs, and every frontier position that holds one becomes a job.
+constexpr int HUB_SLOTS = 4096;                 // distinct hub rows; a row that finds no place is sampled in tiles
+constexpr int HUB_PROBES = 64;
+constexpr uint32_t HUB_MAX_JOBS = 1u << 18;
+constexpr uint32_t HUB_MAX_FANOUT = 448;
+struct HubRow {
+    int64_t begin;
+    unsigned long long first;                   // its first bucket
+    int32_t deg;
+    int32_t shift;                              // bucket of ID u: u >> shift
+    int32_t damaged;                            // not strictly ascending inside [0, n_nodes): the table does not hold
+    int32_t pad;
+};
+struct HubJob { int64_t i; int32_t slot; int32_t pad; };
+struct HubCounts { unsigned long long buckets; uint32_t n_jobs, n_rows; };
+// A bucket: the IDs of 2^shift consecutive ones that the row holds, as their low bits, in order; HUB_EMPTY behind them.  A
+// bucket that is full may have had no room for all.
+constexpr int HUB_BUCKET = 16;
+constexpr uint32_t HUB_EMPTY = 0xFFFFu;
+constexpr int HUB_MAX_SHIFT = 15;               // low bits stay below HUB_EMPTY
+struct alignas(32) HubBucket { uint16_t id[HUB_BUCKET]; };
+struct HubTable {
+    int32_t min_deg;                            // rows from this length on; INT32_MAX: none
+    int32_t *keys;                              // [HUB_SLOTS], -1 = free
+    HubRow *rows;                               // [HUB_SLOTS]
+    int32_t *list;                              // [HUB_SLOTS]: the slots in use
+    HubJob *jobs;
+    uint32_t max_jobs;
+    HubCounts *counts;
+};
+// Makes frontier position i, node v, a hub job; false: no place left.
+__device__ __forceinline__ bool add_hub_job(const HubTable &h, int64_t i, int32_t v, int64_t begin, int64_t deg, int64_t n_nodes)
+{
+    uint32_t slot = ((uint32_t)v * 0x9E3779B1u) >> 20;
+    static_assert(HUB_SLOTS == 1 << 12, "twelve bits of hash");
+    bool found = false;
+    for (int t = 0; t < HUB_PROBES && !found; ++t) {
+        int32_t have = h.keys[slot];
+        if (have != v && have == -1) {
+            have = atomicCAS(&h.keys[slot], -1, v);
+            if (have == -1) {                   // this thread's: the row is described once
+                int32_t shift = 0;
+                while (shift < HUB_MAX_SHIFT && (n_nodes >> shift) > deg / 4) ++shift;         // 4 to 8 IDs per bucket on average
+                const int64_t buckets = ((n_nodes - 1) >> shift) + 1;
+                h.rows[slot] = HubRow{begin, atomicAdd(&h.counts->buckets, (unsigned long long)buckets), (int32_t)deg, shift, 0, 0};
+                h.list[atomicAdd(&h.counts->n_rows, 1u)] = (int32_t)slot;
+                have = v;
+            }
+        }
+        if (have == v) found = true;
+        else slot = (slot + 1) & (HUB_SLOTS - 1);
+    }
+    if (!found) return false;
+    const uint32_t j = atomicAdd(&h.counts->n_jobs, 1u);
+    if (j >= h.max_jobs) return false;
+    h.jobs[j] = HubJob{i, (int32_t)slot, 0};
+    return true;
+}
+
 // Also adds up, over the frontier, what the hop will read of the adjacency: [0] the sum of the degrees (in IDs),
 // [1] the part of it in rows of up to BIG_ROW IDs (the rows that are not sampled as tiles), [2] the number of rows of
 // 1 .. SHORT_ROW IDs and [3] the IDs in them.  The sums are spread over DEG_SUM_SLOTS sets of four counters,
@@ -73,7 +136,7 @@ constexpr int SHORT_ROW = 64;            // rows of up to this many IDs are samp
 __global__ void __launch_bounds__(256) node_records_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ frontier, int64_t n,
                                                            const int64_t *__restrict__ batch_off, uint32_t n_batches, const uint64_t *__restrict__ batch_seed,
                                                            uint32_t hop, uint32_t fanout, NodeRecs r, int32_t *__restrict__ cnt, int32_t *__restrict__ tiles,
-                                                           int64_t n_nodes, unsigned long long *__restrict__ total)
+                                                           int64_t n_nodes, unsigned long long *__restrict__ total, HubTable hubs)
 {
     __shared__ unsigned long long part[DEG_SUMS][4];
     unsigned long long acc[DEG_SUMS] = {0, 0, 0, 0};
@@ -89,7 +152,7 @@ __global__ void __launch_bounds__(256) node_records_kernel(const int64_t *__rest
         r.batch[i] = b;
         r.state[i] = combine(combine(batch_seed[b], (uint64_t)hop + 1u), (uint64_t)(uint32_t)v);
         cnt[i] = (int32_t)(deg < (int64_t)fanout ? deg : (int64_t)fanout);
-        tiles[i] = (int32_t)tiles_of(deg);
+        tiles[i] = hubs.keys && deg >= hubs.min_deg && add_hub_job(hubs, i, v, b0, deg, n_nodes) ? 0 : (int32_t)tiles_of(deg);
         acc[0] += (unsigned long long)deg;
         if (deg <= (int64_t)BIG_ROW) acc[1] += (unsigned long long)deg;
         if (deg > 0 && deg <= (int64_t)SHORT_ROW) { acc[2] += 1; acc[3] += (unsigned long long)deg; }
@@ -993,6 +1056,190 @@ __global__ void __launch_bounds__(64) sample_merge_kernel(HopArgs a)
 }
 
 
+// ---------------------------------------------------------------- hub rows: sampled from the keys' side
+// A row of d IDs holds about lambda keys up to the cut lambda / d * 2^32.  Reading the row finds them with d keys; but
+// key32 is a bijection, so they are found as well by taking the key values 0, 1, 2, ... up to the cut, undoing each
+// (key32_inverse) and asking whether the row holds the ID that comes out.  That is lambda / d * 2^32 values, of which only
+// the share n_nodes / 2^32 are IDs at all and have to be looked up: the longer the row the fewer, and fewer than d from
+// d = sqrt(lambda * 2^32) on.  A row of 6.7 M IDs takes 14,000 values instead of 6.7 M keys. 
+// On 111 M nodes and 405 M edges in 147 batches, fan-out 10 behind 15, the sampling launches took 4.5 ms, nine tenths of
+// it vector instructions; with the rows from 450,000 IDs on taken out: 1.66 ms, and 0.26 for the key values, 0.17 for the
+// tables, 0.05 to clear them.  (A directory of positions into the row in place of the tables cost 0.09 to build but three
+// dependent reads per lookup: 0.38 ms for the key values.)
+// Results are those of reading the row: all IDs with a key in the range come out, the f smallest keys are taken.
+//
+// Lookup: a table per distinct row, a bucket of sixteen 16-bit entries for every 2^shift consecutive IDs, so that one
+// 32-byte read settles nearly every ID (a search of the whole row where a full bucket does not hold it); built by one
+// pass over the row.  Rows are shared by most batches, so the pass is paid once for many jobs.  The IDs to look up are
+// collected per wave and looked up 64 at a time: only one value in 40 (of 10^8 nodes) needs it.
+__global__ void __launch_bounds__(256) hub_table_kernel(const int32_t *__restrict__ indices, int64_t n_nodes, HubTable h, HubBucket *__restrict__ buckets)
+{
+    const int32_t slot = h.list[blockIdx.y];
+    const HubRow r = h.rows[slot];
+    const int32_t *row = indices + r.begin;
+    HubBucket *mine = buckets + r.first;
+    const uint32_t n = (uint32_t)n_nodes;
+    bool damaged = false;
+    const int lane = threadIdx.x & 63;
+    // A wave takes 64 consecutive IDs; an ID's place in its bucket is its distance from the lane its bucket starts in, and
+    // for the bucket the wave starts in the middle of, also from the up to sixteen IDs in front of the wave.
+    for (int64_t base = (int64_t)blockIdx.x * 256 + (threadIdx.x & ~63u); base < r.deg; base += (int64_t)gridDim.x * 256) {
+        const int64_t i = base + lane;
+        const bool in = i < r.deg;
+        const uint32_t u = in ? (uint32_t)row[i] : 0xFFFFFFFFu, before = in && i > 0 ? (uint32_t)row[i - 1] : 0u;
+        const int64_t behind = base - 1 - lane;                  // lanes 0 .. 15: the IDs in front of the wave, nearest first
+        const uint32_t back = lane < HUB_BUCKET && behind >= 0 ? (uint32_t)row[behind] : 0xFFFFFFFFu;
+        const uint32_t b = u >> r.shift, b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+        const unsigned long long not_mine = ~__ballot(lane < HUB_BUCKET && behind >= 0 && back >> r.shift == b0);
+        const int carried = __ffsll((long long)not_mine) - 1;    // how many of them, without a gap, are in the first lane's bucket
+        const unsigned long long starts = __ballot(in && (i == 0 || before >> r.shift != b)) & (lane == 63 ? ~0ull : (2ull << lane) - 1ull);
+        const int rank = starts ? lane - (63 - __clzll((long long)starts)) : lane + carried;
+        if (!in) continue;
+        if (u >= n || (i > 0 && before >= u)) damaged = true;
+        else if (rank < HUB_BUCKET) mine[b].id[rank] = (uint16_t)(u & ((1u << r.shift) - 1u));
+    }
+    if (damaged) h.rows[slot].damaged = 1;
+}
+
+// Whether the row (ascending) holds u < n_nodes.
+__device__ __forceinline__ bool hub_holds(const HubBucket *__restrict__ mine, const HubRow &r, const int32_t *__restrict__ row, uint32_t u)
+{
+    const uint4 *p = reinterpret_cast<const uint4 *>(mine + (u >> r.shift));
+    const uint4 x = p[0], y = p[1];
+    const uint32_t want = (u & ((1u << r.shift) - 1u)) * 0x00010001u;
+    const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    uint32_t any = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t d = w[k] ^ want;                          // a 16-bit half that is zero: found
+        any |= (d - 0x00010001u) & ~d & 0x80008000u;
+    }
+    if (any) return true;
+    if (y.w >> 16 == HUB_EMPTY) return false;
+    int32_t lo = 0, hi = r.deg;
+    while (lo < hi) {                                            // the first position whose ID is not below u
+        const int32_t m = lo + ((hi - lo) >> 1);
+        if ((uint32_t)row[m] < u) lo = m + 1; else hi = m;
+    }
+    return lo < r.deg && (uint32_t)row[lo] == u;
+}
+
+struct HubArgs {
+    const int32_t *indices;
+    int64_t n_nodes;
+    HubTable h;
+    const HubBucket *buckets;
+    uint32_t n_jobs;
+    NodeRecs rec;
+    uint32_t fanout;
+    const int64_t *samp_off; int32_t *samp_nbr;
+    ReachedMaps reached;
+};
+
+constexpr int HUB_THREADS = 256;
+constexpr int HUB_WAVES = HUB_THREADS / 64;
+constexpr int HUB_HITS = 1024;                  // the guess lets 515 through at the largest fan-out; 19 KB of LDS, so that eight workgroups of a compute unit wait for their lookups together
+constexpr int HUB_QUEUE = 64 + 4 * 64;          // a wave's IDs waiting to be looked up: fewer than 64 left over, and a step's four per lane
+
+template <int MARK>
+__global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
+{
+    __shared__ uint32_t hit_key[HUB_HITS], hit_id[HUB_HITS], hit_at[HUB_HITS];      // hit_at: the row order (the ID itself where the row ascends)
+    __shared__ uint8_t hit_taken[HUB_HITS];
+    __shared__ uint32_t queue[HUB_WAVES][HUB_QUEUE];                                // keys of IDs below n_nodes
+    __shared__ uint32_t n_hits;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int f = (int)a.fanout;
+    const uint32_t n = (uint32_t)a.n_nodes;
+    for (uint32_t j = blockIdx.x; j < a.n_jobs; j += gridDim.x) {
+        const HubJob job = a.h.jobs[j];
+        const HubRow r = a.h.rows[job.slot];
+        const int32_t *row = a.indices + r.begin;
+        const HubBucket *mine = a.buckets + r.first;
+        const uint64_t S = a.rec.state[job.i];
+        const uint32_t lo = uni((uint32_t)S), hi = uni((uint32_t)(S >> 32));
+        uint64_t from = 0, to = (uint64_t)(guessed_candidates(f) / (float)r.deg * 4294967296.0f) + 1;     // key values [from, to)
+        uint32_t kept = 0;                                       // hits with keys below `from` (fewer than f)
+        for (;;) {
+            if (to > ((uint64_t)1 << 32)) to = (uint64_t)1 << 32;
+            __syncthreads();                                     // the hits of the job before, or of the round before, have been read
+            if (threadIdx.x == 0) n_hits = kept;
+            __syncthreads();
+            auto add_hit = [&](uint32_t key, uint32_t id, uint32_t at) {
+                const uint32_t k = atomicAdd(&n_hits, 1u);
+                if (k < HUB_HITS) { hit_key[k] = key; hit_id[k] = id; hit_at[k] = at; }
+            };
+            if (!r.damaged) {
+                int waiting = 0;                                 // in this wave's queue (the same in all its lanes)
+                auto look_up = [&](int count) {                  // the queue's last `count` <= 64 entries
+                    if (lane < count) {
+                        const uint32_t key = queue[wave][waiting - count + lane], u = key32_inverse(lo, hi, key);
+                        if (hub_holds(mine, r, row, u)) add_hit(key, u, u);
+                    }
+                    waiting -= count;
+                };
+                for (uint64_t base = from + (uint64_t)wave * 256; base < to; base += HUB_THREADS * 4) {
+                    const uint32_t left = (uint32_t)(to - base < 256 ? to - base : 256);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t at = (uint32_t)(64 * e + lane), key = (uint32_t)base + at;
+                        const unsigned long long m = ballot64(key32_inverse(lo, hi, key) < n && at < left);
+                        if (my_bit(m)) queue[wave][waiting + lanes_below(m, lane)] = key;
+                        waiting += __popcll(m);
+                    }
+                    waiting = uni(waiting);
+                    __builtin_amdgcn_wave_barrier();             // (one wave's LDS operations are done in order)
+                    while (waiting >= 64) look_up(64);
+                }
+                if (waiting > 0) look_up(waiting);
+            } else {
+                for (int32_t p = threadIdx.x; p < r.deg; p += HUB_THREADS) {         // a row that is not in order: read as it is
+                    const uint32_t u = (uint32_t)row[p], key = key32(lo, hi, u);
+                    if (key >= from && key < to) add_hit(key, u, (uint32_t)p);
+                }
+            }
+            __syncthreads();
+            const uint32_t found = n_hits;
+            if (found > HUB_HITS && to - from > 1) { to = from + (to - from) / 2; continue; }        // too many for the list: a smaller range (the hits kept so far stay)
+            if (found >= (uint32_t)f || to == ((uint64_t)1 << 32)) break;
+            kept = found;
+            const uint64_t step = 2 * (to - from);               // too few: the next key values, twice as many
+            from = to;
+            to += step;
+        }
+        // the f smallest keys, in row order
+        const int c = n_hits < HUB_HITS ? (int)n_hits : HUB_HITS;
+        for (int k = threadIdx.x; k < c; k += HUB_THREADS) {
+            const uint32_t key = hit_key[k], at = hit_at[k];
+            int smaller = 0;
+            for (int q = 0; q < c; ++q) smaller += hit_key[q] < key || (hit_key[q] == key && hit_at[q] < at) ? 1 : 0;
+            hit_taken[k] = smaller < f ? 1 : 0;
+        }
+        __syncthreads();
+        int32_t *out = a.samp_nbr + a.samp_off[job.i];
+        const ReachedOfBatch reached_b = reached_of<MARK>(a.reached, a.rec.batch[job.i]);
+        for (int k = threadIdx.x; k < c; k += HUB_THREADS) {
+            if (!hit_taken[k]) continue;
+            const uint32_t at = hit_at[k];
+            int in_front = 0;
+            for (int q = 0; q < c; ++q) in_front += hit_taken[q] && hit_at[q] < at ? 1 : 0;
+            out[in_front] = (int32_t)hit_id[k];
+            mark_reached<MARK>(reached_b, hit_id[k]);
+        }
+    }
+}
+
+// From which length on a row is sampled from the keys' side: where its key values cost what its IDs would.  A value costs
+// about 1.6 times what an ID does (twice the arithmetic, no read), and the share of values that are IDs one more
+// scattered read each.  Measured around the line it gives for the graph above (450,000), sampling altogether: from
+// 350,000 2.2 ms, 450,000 2.09, 600,000 2.12, 800,000 2.20, none 4.5.
+static double hub_line(int64_t n_nodes, uint32_t fanout)
+{
+    const double f = (double)fanout, lambda = f + 3.0 * std::sqrt(f) + 3.0;
+    const double per_value = 1.6 + 20.0 * (double)n_nodes / 4294967296.0;
+    return std::sqrt(per_value * lambda * 4294967296.0);
+}
+
 struct ShortArgs {
     const int32_t *indices;
     int64_t n_frontier;
@@ -1119,10 +1366,29 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     unsigned long long sum_parts[DEG_SUMS * DEG_SUM_SLOTS];
     RG_TRY(tmp.dev_n<unsigned long long>(DEG_SUMS * DEG_SUM_SLOTS, &sum_deg_dev));
     RG_HIP(hipMemsetAsync(sum_deg_dev, 0, sizeof(sum_parts), st));
+    // Hub rows (see hub_sample_kernel): where the directory of a row is shared by the batches of an epoch -- behind the seeds,
+    // which hold a node once.
+    HubTable hubs{INT32_MAX, nullptr, nullptr, nullptr, nullptr, 0, nullptr};
+    HubCounts hub_counts{0, 0, 0};
+    {
+        double line = hop > 0 && beta >= 8 ? hub_line(g->n_nodes, fanout) : 2147483647.0;
+        if (const char *force = getenv("RAPIDGNN_HUB_ROWS")) line = std::max(atof(force), 4.0 * RG_MAX_FANOUT);      // same results either way; for tests and tuning
+        if (sampler == RG_SAMPLER_KEYS && fanout > 0 && fanout <= HUB_MAX_FANOUT && line <= (double)g->n_nodes) {
+            hubs.min_deg = std::max((int32_t)std::min(line, 2147483647.0), BIG_ROW + 1);
+            hubs.max_jobs = (uint32_t)std::min<int64_t>(n_cur, HUB_MAX_JOBS);
+            RG_TRY(tmp.dev_n<int32_t>(HUB_SLOTS, &hubs.keys));
+            RG_TRY(tmp.dev_n<HubRow>(HUB_SLOTS, &hubs.rows));
+            RG_TRY(tmp.dev_n<int32_t>(HUB_SLOTS, &hubs.list));
+            RG_TRY(tmp.dev_n<HubJob>(hubs.max_jobs, &hubs.jobs));
+            RG_TRY(tmp.dev_n<HubCounts>(1, &hubs.counts));
+            RG_HIP(hipMemsetAsync(hubs.keys, 0xFF, HUB_SLOTS * sizeof(int32_t), st));
+            RG_HIP(hipMemsetAsync(hubs.counts, 0, sizeof(HubCounts), st));
+        }
+    }
     {
         ScopedTimer tm(KG_OFFSETS, st);
         hipLaunchKernelGGL(node_records_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((n_cur + 255) / 256, (int64_t)n_cu * 64))), dim3(256), 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta,
-                           batch_seed, hop, fanout, rec, cnt, tiles, (int64_t)g->n_nodes, sum_deg_dev);
+                           batch_seed, hop, fanout, rec, cnt, tiles, (int64_t)g->n_nodes, sum_deg_dev, hubs);
         RG_TRY(scan_i32_to_i64(cnt, cur.samp_off, n_cur, tmp, st));
         RG_TRY(scan_i32_to_i64(tiles, tile_off, n_cur, tmp, st));
     }
@@ -1134,6 +1400,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         RG_TRY(rb.add(sum_parts, sum_deg_dev, sizeof(sum_parts)));
         RG_TRY(rb.add(&cur.n_samples, cur.samp_off + n_cur, sizeof(int64_t)));
         RG_TRY(rb.add(&n_tiles, tile_off + n_cur, sizeof(int64_t)));
+        if (hubs.counts) RG_TRY(rb.add(&hub_counts, hubs.counts, sizeof(hub_counts)));
         if (also_read_dev) RG_TRY(rb.add(also_read_host, also_read_dev, sizeof(unsigned long long)));     // a value the caller wants behind the same wait
         RG_TRY(rb.wait());
         for (int k = 0; k < DEG_SUM_SLOTS; ++k)
@@ -1229,6 +1496,22 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         const unsigned merge_grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_tiles + merge_span - 1) / merge_span, (int64_t)n_cu * 64));
         HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_mode != 0 ? SHORT_ROW : 0, short_mode == 2 ? 1 : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile_off, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work};
         ScopedTimer tm(KG_SAMPLER, st);
+        if (const uint32_t n_jobs = std::min(hub_counts.n_jobs, hubs.max_jobs)) {
+            HubBucket *buckets = nullptr;
+            RG_TRY(tmp.dev_n<HubBucket>(hub_counts.buckets, &buckets));
+            RG_HIP(hipMemsetAsync(buckets, 0xFF, hub_counts.buckets * sizeof(HubBucket), st));
+            const uint32_t per_row = std::max<uint32_t>(64, std::min<uint32_t>(1024, 64u * (uint32_t)n_cu / hub_counts.n_rows));       // few rows, long ones: the workgroups of the chip shared out among them
+            hipLaunchKernelGGL(hub_table_kernel, dim3(per_row, hub_counts.n_rows), dim3(256), 0, st, g->indices, g->n_nodes, hubs, buckets);
+            const HubArgs ha{g->indices, g->n_nodes, hubs, buckets, n_jobs, rec, fanout, cur.samp_off, cur.samp_nbr, reached};
+            const dim3 grid(std::min<uint32_t>(n_jobs, (uint32_t)n_cu * 64)), block(HUB_THREADS);
+            switch (mark) {
+            case MARK_BYTES_ALL: hipLaunchKernelGGL(hub_sample_kernel<MARK_BYTES_ALL>, grid, block, 0, st, ha); break;
+            case MARK_BITS_ALL: hipLaunchKernelGGL(hub_sample_kernel<MARK_BITS_ALL>, grid, block, 0, st, ha); break;
+            case MARK_BYTES: hipLaunchKernelGGL(hub_sample_kernel<MARK_BYTES>, grid, block, 0, st, ha); break;
+            default: hipLaunchKernelGGL(hub_sample_kernel<MARK_BITS>, grid, block, 0, st, ha); break;
+            }
+            RG_HIP(hipGetLastError());
+        }
         // worth it where a group is long work: rows of a thousand IDs on average, tiles aside (short rows finish a
         // group of 64 in no time, and four times the requests to the work counter then cost more than the tail does;
         // measured: Medium, 2,500 IDs per row, 4 % faster; large_sparse and partition_share, a few hundred, 1-8 % slower)
