@@ -1412,7 +1412,9 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     // large part of the hop's traffic (rows mostly no longer than the fan-out: one mark per ID read), and costs a
     // little where long rows are scanned for a few samples (measured: at one mark per 20 IDs read nothing is gained,
     // at one per 10 the hop is a quarter faster).  Threshold: one mark per 14 IDs read.
-    const unsigned long long sum_deg = sums[0];
+    // The positions sampler reads no more IDs than it draws, so its marks are always most of its traffic (233 k nodes, 29 M
+    // draws: its two launches 1231 us with atomic marks, 704 with byte stores).
+    const unsigned long long sum_deg = sampler == RG_SAMPLER_POSITIONS ? (unsigned long long)cur.n_samples : sums[0];
     const bool use_bytes = can_bytes && (prefer_bytes >= 0 ? prefer_bytes != 0 : (unsigned long long)cur.n_samples * 14ull >= sum_deg);
     if (use_bytes && !maps.bytes) {
         const uint64_t map_bytes = maps.words_per_batch * 32 * (uint64_t)beta;
@@ -1422,7 +1424,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     // A hop that marks many times more IDs than the maps have groups reaches nearly every group: the per-mark flag
     // store (a third of the hop's scattered stores) is replaced by setting every flag once.
     const uint64_t flag_bytes = maps.words_per_batch / 8 * (uint64_t)beta;
-    const bool all_flags = sampler == RG_SAMPLER_KEYS && fanout > 0 && fanout + 64 <= 256 && (uint64_t)cur.n_samples >= 16 * flag_bytes;
+    const bool all_flags = (sampler == RG_SAMPLER_POSITIONS || fanout + 64 <= 256) && fanout > 0 && (uint64_t)cur.n_samples >= 16 * flag_bytes;
     if (all_flags) RG_HIP(hipMemsetAsync(maps.flags, 1, flag_bytes, st));
     const ReachedMaps reached{use_bytes ? (void *)maps.bytes : (void *)maps.words, maps.flags, maps.words_per_batch, (!use_bytes && maps.paired) ? 1u : 0u};
     tmp.free_one(cnt);
@@ -1433,12 +1435,12 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
             ScopedTimer tm(KG_SAMPLER, st);
             const int64_t per_round = fanout >= (uint32_t)POS_THREADS ? 1 : POS_THREADS / fanout;
             const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_cur + per_round - 1) / per_round, (int64_t)n_cu * 64));
-            if (use_bytes)
-                hipLaunchKernelGGL(sample_positions_kernel<MARK_BYTES>, dim3(grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, cur.samp_off,
-                                   cur.samp_nbr, reached);
-            else
-                hipLaunchKernelGGL(sample_positions_kernel<MARK_BITS>, dim3(grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, cur.samp_off,
-                                   cur.samp_nbr, reached);
+#define RG_POSITIONS(M) hipLaunchKernelGGL(sample_positions_kernel<M>, dim3(grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, cur.samp_off, cur.samp_nbr, reached)
+            if (use_bytes && all_flags) RG_POSITIONS(MARK_BYTES_ALL);
+            else if (use_bytes) RG_POSITIONS(MARK_BYTES);
+            else if (all_flags) RG_POSITIONS(MARK_BITS_ALL);
+            else RG_POSITIONS(MARK_BITS);
+#undef RG_POSITIONS
             RG_HIP(hipGetLastError());
         }
         return RG_OK;

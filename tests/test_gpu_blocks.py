@@ -1,0 +1,59 @@
+"""Computation blocks where the workgroup map changes shape: numbers of batches around the eight XCDs, groups of batches of
+every size, batches with few edges and none; and the O(f) sampler's marks in every form; against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rg():
+    from paper_2509_05207_amd import binding
+    binding.lib()
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return binding
+
+
+def graph(rng, n, most):
+    deg = rng.integers(0, most + 1, size=n)
+    deg[rng.random(n) < 0.2] = 0
+    indptr = np.zeros(n + 1, np.int64)
+    rows = []
+    for v in range(n):
+        r = np.unique(rng.integers(0, n, size=deg[v]))
+        rows.append(r.astype(np.int32))
+        indptr[v + 1] = indptr[v] + r.size
+    return indptr, np.concatenate(rows)
+
+
+@pytest.mark.parametrize("n_batches", [1, 7, 8, 9, 17])
+@pytest.mark.parametrize("group", [1, 3, 8, 100])
+def test_blocks_of_every_group(rg, orc, n_batches, group):
+    rng = np.random.default_rng(n_batches)
+    n, batch = 3000, 40
+    indptr, indices = graph(rng, n, 12)
+    train = rng.permutation(n)[: n_batches * batch - 3].astype(np.int32)
+    o = orc.Schedule(indptr, indices, train, batch, [5, 1, 3], 1, 0, 0)
+    s = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), batch, [5, 1, 3], 1, 0, 0)
+    rg.rg_schedule_build_blocks(s, workspace_limit_bytes=4 * n * group)
+    for hop in range(3):
+        assert np.array_equal(rg.rg_schedule_block(s, hop).cpu().numpy(), o.block(hop)), hop
+
+
+@pytest.mark.parametrize("byte_maps", ["0", "1", None])
+@pytest.mark.parametrize("fanout", [[2, 3], [40, 40], [255, 2], [256, 3], [300, 1]])
+def test_positions_sampler_in_every_marking(rg, orc, byte_maps, fanout, monkeypatch):
+    if byte_maps is not None:
+        monkeypatch.setenv("RAPIDGNN_BYTE_MAPS", byte_maps)
+    rng = np.random.default_rng(len(fanout) + fanout[0])
+    n = 2000
+    indptr, indices = graph(rng, n, 700)
+    train = rng.permutation(n)[:500].astype(np.int32)
+    o = orc.Schedule(indptr, indices, train, 60, fanout, 1, 0, 0, sampler="positions")
+    s = rg.rg_build_schedule_with(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), 60, fanout, 1, 0, 0,
+                                  sampler=rg.RG_SAMPLER_POSITIONS)
+    for hop in range(3):
+        assert np.array_equal(rg.rg_schedule_frontier(s, hop)[0].cpu().numpy(), o.frontier(hop)[0]), hop
+    for hop in range(2):
+        assert np.array_equal(rg.rg_schedule_samples(s, hop)[1].cpu().numpy(), o.samples(hop)[1]), hop
