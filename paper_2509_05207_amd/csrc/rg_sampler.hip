@@ -133,39 +133,173 @@ __device__ __forceinline__ bool add_hub_job(const HubTable &h, int64_t i, int32_
 constexpr int DEG_SUM_SLOTS = 64;
 constexpr int DEG_SUMS = 4;
 constexpr int SHORT_ROW = 64;            // rows of up to this many IDs are sampled four at a time, sixteen lanes each
-__global__ void __launch_bounds__(256) node_records_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ frontier, int64_t n,
-                                                           const int64_t *__restrict__ batch_off, uint32_t n_batches, const uint64_t *__restrict__ batch_seed,
-                                                           uint32_t hop, uint32_t fanout, NodeRecs r, int32_t *__restrict__ cnt, int32_t *__restrict__ tiles,
-                                                           int64_t n_nodes, unsigned long long *__restrict__ total, HubTable hubs)
+
+// Bound by its bytes (a random 16-byte read of indptr and 28 bytes written per node), so a workgroup takes NODE_CHUNK
+// consecutive positions, whose batch and hop stream it looks up once, and a thread has four nodes' reads in flight.
+// How many IDs each node will sample and how many tile jobs its row makes go into one word, count[i] = samples |
+// tiles << 12, and the chunk's sums of both into chunk_sum (tiles in the upper half): two prefix sums over the nodes
+// become one scan of the chunks and one pass (24.8 M nodes of an epoch's three hops, with their prefix sums: 980 us as two
+// separate scans, 600 so).
+constexpr int NODE_THREADS = 256;
+constexpr int NODE_PER_THREAD = 4;
+constexpr int NODE_CHUNK = NODE_THREADS * NODE_PER_THREAD;
+constexpr uint32_t COUNT_BITS = 12;      // samples: at most RG_MAX_FANOUT; tiles: at most 2^31 / TILE_PIECE = 2^15
+static_assert(RG_MAX_FANOUT < (1u << COUNT_BITS) && (((uint64_t)1 << 31) / TILE_PIECE) < (1u << (32 - COUNT_BITS)), "");
+__device__ __forceinline__ uint32_t samples_of(uint32_t count) { return count & ((1u << COUNT_BITS) - 1u); }
+__device__ __forceinline__ uint32_t tiles_in(uint32_t count) { return count >> COUNT_BITS; }
+
+__global__ void __launch_bounds__(NODE_THREADS) node_records_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ frontier, int64_t n,
+                                                                    const int64_t *__restrict__ batch_off, uint32_t n_batches, const uint64_t *__restrict__ batch_seed,
+                                                                    uint32_t hop, uint32_t fanout, NodeRecs r, uint32_t *__restrict__ count,
+                                                                    unsigned long long *__restrict__ chunk_sum, int64_t n_nodes,
+                                                                    unsigned long long *__restrict__ total, HubTable hubs)
 {
-    __shared__ unsigned long long part[DEG_SUMS][4];
-    unsigned long long acc[DEG_SUMS] = {0, 0, 0, 0};
-    // (a bounded grid, each workgroup striding over the frontier: the sums cost two atomics per workgroup)
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t v = frontier[i];
-        const bool known = v >= 0 && (int64_t)v < n_nodes;      // (a seed out of range is refused by the host at the hop's readback; until then it has no row)
-        const int64_t b0 = known ? indptr[v] : 0;
-        const int64_t deg = known ? indptr[v + 1] - b0 : 0;
-        const uint32_t b = batch_of(batch_off, n_batches, i);
-        r.row_begin[i] = b0;
-        r.deg[i] = (int32_t)deg;
-        r.batch[i] = b;
-        r.state[i] = combine(combine(batch_seed[b], (uint64_t)hop + 1u), (uint64_t)(uint32_t)v);
-        cnt[i] = (int32_t)(deg < (int64_t)fanout ? deg : (int64_t)fanout);
-        tiles[i] = hubs.keys && deg >= hubs.min_deg && add_hub_job(hubs, i, v, b0, deg, n_nodes) ? 0 : (int32_t)tiles_of(deg);
-        acc[0] += (unsigned long long)deg;
-        if (deg <= (int64_t)BIG_ROW) acc[1] += (unsigned long long)deg;
-        if (deg > 0 && deg <= (int64_t)SHORT_ROW) { acc[2] += 1; acc[3] += (unsigned long long)deg; }
+    __shared__ unsigned long long part[DEG_SUMS + 1][NODE_THREADS / 64];
+    unsigned long long acc[DEG_SUMS + 1] = {0, 0, 0, 0, 0};       // see above; and the chunk's sums
+    const int64_t base = (int64_t)blockIdx.x * NODE_CHUNK;
+    int32_t v[NODE_PER_THREAD];
+    int64_t b0[NODE_PER_THREAD], deg[NODE_PER_THREAD];
+#pragma unroll
+    for (int k = 0; k < NODE_PER_THREAD; ++k) {
+        const int64_t i = base + k * NODE_THREADS + threadIdx.x;
+        v[k] = i < n ? frontier[i] : -1;
     }
 #pragma unroll
-    for (int k = 0; k < DEG_SUMS; ++k) {
+    for (int k = 0; k < NODE_PER_THREAD; ++k) {
+        const bool known = v[k] >= 0 && (int64_t)v[k] < n_nodes;      // (a seed out of range is refused by the host at the hop's readback; until then it has no row)
+        b0[k] = known ? indptr[v[k]] : 0;
+        deg[k] = known ? indptr[v[k] + 1] : 0;
+    }
+    const uint32_t b_first = batch_of(batch_off, n_batches, base);
+    const int64_t first_end = batch_off[b_first + 1];
+    const uint64_t first_stream = combine(batch_seed[b_first], (uint64_t)hop + 1u);
+#pragma unroll
+    for (int k = 0; k < NODE_PER_THREAD; ++k) {
+        const int64_t i = base + k * NODE_THREADS + threadIdx.x;
+        if (i >= n) continue;
+        const int64_t d = deg[k] > b0[k] ? deg[k] - b0[k] : 0;
+        uint32_t b = b_first;
+        uint64_t stream = first_stream;
+        if (i >= first_end) {
+            b = batch_of(batch_off, n_batches, i);
+            stream = combine(batch_seed[b], (uint64_t)hop + 1u);
+        }
+        r.row_begin[i] = b0[k];
+        r.deg[i] = (int32_t)d;
+        r.batch[i] = b;
+        r.state[i] = combine(stream, (uint64_t)(uint32_t)v[k]);
+        const uint32_t samples = (uint32_t)(d < (int64_t)fanout ? d : (int64_t)fanout);
+        const uint32_t tiles = hubs.keys && d >= hubs.min_deg && add_hub_job(hubs, i, v[k], b0[k], d, n_nodes) ? 0u : (uint32_t)tiles_of(d);
+        count[i] = samples | tiles << COUNT_BITS;
+        acc[0] += (unsigned long long)d;
+        if (d <= (int64_t)BIG_ROW) acc[1] += (unsigned long long)d;
+        if (d > 0 && d <= (int64_t)SHORT_ROW) { acc[2] += 1; acc[3] += (unsigned long long)d; }
+        acc[DEG_SUMS] += (unsigned long long)samples | (unsigned long long)tiles << 32;
+    }
+#pragma unroll
+    for (int k = 0; k <= DEG_SUMS; ++k) {
         for (int o = 32; o > 0; o >>= 1) acc[k] += __shfl_down(acc[k], o, 64);
         if ((threadIdx.x & 63) == 0) part[k][threadIdx.x >> 6] = acc[k];
     }
     __syncthreads();
-    if (threadIdx.x < DEG_SUMS) {
+    if (threadIdx.x <= DEG_SUMS) {
         const unsigned long long a = part[threadIdx.x][0] + part[threadIdx.x][1] + part[threadIdx.x][2] + part[threadIdx.x][3];
-        if (a) atomicAdd(total + DEG_SUMS * (blockIdx.x % DEG_SUM_SLOTS) + threadIdx.x, a);
+        if (threadIdx.x == DEG_SUMS) chunk_sum[blockIdx.x] = a;
+        else if (a) atomicAdd(total + DEG_SUMS * (blockIdx.x % DEG_SUM_SLOTS) + threadIdx.x, a);
+    }
+}
+
+// One workgroup: chunk_sum -> exclusive prefix sums of both halves, samples and tiles in front of each chunk, with the
+// totals behind the last; the total of the samples also to *samp_end.
+constexpr int CHUNK_SCAN_THREADS = 1024;
+constexpr int CHUNK_SCAN_PER_THREAD = 8;
+__global__ void __launch_bounds__(CHUNK_SCAN_THREADS) scan_chunks_kernel(const unsigned long long *__restrict__ chunk_sum, int64_t n_chunks,
+                                                                         int64_t *__restrict__ samp_base, int64_t *__restrict__ tile_base, int64_t *__restrict__ samp_end)
+{
+    __shared__ int64_t wave_sum[2][CHUNK_SCAN_THREADS / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int64_t carry[2] = {0, 0};
+    for (int64_t c0 = 0; c0 < n_chunks; c0 += CHUNK_SCAN_THREADS * CHUNK_SCAN_PER_THREAD) {
+        const int64_t first = c0 + (int64_t)threadIdx.x * CHUNK_SCAN_PER_THREAD;
+        unsigned long long x[CHUNK_SCAN_PER_THREAD];
+        int64_t mine[2] = {0, 0};
+#pragma unroll
+        for (int k = 0; k < CHUNK_SCAN_PER_THREAD; ++k) x[k] = first + k < n_chunks ? chunk_sum[first + k] : 0ull;
+#pragma unroll
+        for (int k = 0; k < CHUNK_SCAN_PER_THREAD; ++k) { mine[0] += (int64_t)(uint32_t)x[k]; mine[1] += (int64_t)(x[k] >> 32); }
+        int64_t run[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            int64_t incl = mine[h];
+            for (int d = 1; d < 64; d <<= 1) {
+                const int64_t y = __shfl_up(incl, d, 64);
+                if (lane >= d) incl += y;
+            }
+            if (lane == 63) wave_sum[h][wave] = incl;
+            run[h] = carry[h] + incl - mine[h];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            for (int w = 0; w < CHUNK_SCAN_THREADS / 64; ++w) {
+                if (w < wave) run[h] += wave_sum[h][w];
+                carry[h] += wave_sum[h][w];
+            }
+        __syncthreads();                                         // before the next round's sums
+#pragma unroll
+        for (int k = 0; k < CHUNK_SCAN_PER_THREAD; ++k) {
+            if (first + k < n_chunks) { samp_base[first + k] = run[0]; tile_base[first + k] = run[1]; }
+            run[0] += (int64_t)(uint32_t)x[k];
+            run[1] += (int64_t)(x[k] >> 32);
+        }
+    }
+    if (threadIdx.x == 0) { samp_base[n_chunks] = carry[0]; tile_base[n_chunks] = carry[1]; *samp_end = carry[0]; }
+}
+
+// A chunk's exclusive prefix sum of x, one value per thread (the sums of a chunk fit 32 bits).
+__device__ __forceinline__ uint32_t chunk_exclusive_scan(uint32_t x)
+{
+    __shared__ uint32_t wave_sum[NODE_THREADS / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t incl = x;
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += y;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += wave_sum[w];
+    return incl - x;
+}
+
+__device__ __forceinline__ void load_counts(const uint32_t *__restrict__ count, int64_t first, int64_t n, uint32_t (&c)[NODE_PER_THREAD])
+{
+    static_assert(NODE_PER_THREAD == 4, "one 16-byte load");
+    if (first + 4 <= n) {
+        const uint4 x = *reinterpret_cast<const uint4 *>(count + first);
+        c[0] = x.x; c[1] = x.y; c[2] = x.z; c[3] = x.w;
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = first + k < n ? count[first + k] : 0u;
+}
+
+// samp_off[i] for the nodes of a chunk; a thread takes four consecutive ones.
+__global__ void __launch_bounds__(NODE_THREADS) sample_offsets_kernel(const uint32_t *__restrict__ count, int64_t n, const int64_t *__restrict__ samp_base,
+                                                                      int64_t *__restrict__ samp_off)
+{
+    const int64_t first = (int64_t)blockIdx.x * NODE_CHUNK + (int64_t)threadIdx.x * NODE_PER_THREAD;
+    uint32_t c[NODE_PER_THREAD];
+    load_counts(count, first, n, c);
+    const uint32_t s0 = samples_of(c[0]), s1 = s0 + samples_of(c[1]), s2 = s1 + samples_of(c[2]), s3 = s2 + samples_of(c[3]);
+    const int64_t at = samp_base[blockIdx.x] + (int64_t)chunk_exclusive_scan(s3);
+    if (first + 4 <= n) {
+        *reinterpret_cast<longlong2 *>(samp_off + first) = make_longlong2(at, at + s0);
+        *reinterpret_cast<longlong2 *>(samp_off + first + 2) = make_longlong2(at + s1, at + s2);
+    } else {
+        if (first < n) samp_off[first] = at;
+        if (first + 1 < n) samp_off[first + 1] = at + s0;
+        if (first + 2 < n) samp_off[first + 2] = at + s1;
     }
 }
 
@@ -816,33 +950,38 @@ __device__ __forceinline__ int short_row_slot(bool mine, int deg, int lane)
     return at;
 }
 
-// Per tile job j: the frontier position i whose row it belongs to (tile_off[i] <= j < tile_off[i + 1]), where its piece of
-// the row starts in `indices`, how long it is (near-equal pieces, each longer than 2 * RG_MAX_FANOUT) and the node's
-// stream S_v.  Written by the nodes that have tiles, so that a wave finds everything about its piece in one round of
-// loads instead of a search through tile_off and a second round for the node's record.
+// Per tile job j: the frontier position whose row it belongs to, which of the row's tiles it is, where its piece of the
+// row starts in `indices`, how long it is (near-equal pieces, each longer than 2 * RG_MAX_FANOUT) and the node's
+// stream S_v: a wave finds everything about its piece in one round of loads.
 struct TileRecs {
     int64_t *node;
+    int32_t *t;
     int64_t *begin;
     int32_t *len;
     uint64_t *state;
 };
-// One thread per tile job: its node is the frontier position i with tile_off[i] <= j < tile_off[i + 1].
-__global__ void tile_records_kernel(const int64_t *__restrict__ tile_off, const int64_t *__restrict__ row_begin, const int32_t *__restrict__ deg,
-                                    const uint64_t *__restrict__ state, int64_t n, int64_t n_tiles, TileRecs r)
+// The tile jobs of a chunk's nodes, in frontier order.
+__global__ void __launch_bounds__(NODE_THREADS) tile_nodes_kernel(const uint32_t *__restrict__ count, int64_t n, const int64_t *__restrict__ tile_base, TileRecs r)
+{
+    const int64_t base = tile_base[blockIdx.x];
+    if (tile_base[blockIdx.x + 1] == base) return;
+    const int64_t first = (int64_t)blockIdx.x * NODE_CHUNK + (int64_t)threadIdx.x * NODE_PER_THREAD;
+    uint32_t c[NODE_PER_THREAD];
+    load_counts(count, first, n, c);
+    int64_t j = base + (int64_t)chunk_exclusive_scan(tiles_in(c[0]) + tiles_in(c[1]) + tiles_in(c[2]) + tiles_in(c[3]));
+#pragma unroll
+    for (int k = 0; k < NODE_PER_THREAD; ++k)
+        for (uint32_t t = 0; t < tiles_in(c[k]); ++t, ++j) { r.node[j] = first + k; r.t[j] = (int32_t)t; }
+}
+// One thread per tile job.
+__global__ void tile_records_kernel(const int64_t *__restrict__ row_begin, const int32_t *__restrict__ deg, const uint64_t *__restrict__ state, int64_t n_tiles, TileRecs r)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n_tiles) return;
-    int64_t lo = 0, hi = n;                    // invariant: tile_off[lo] <= j < tile_off[hi]   (tile_off[0] = 0, tile_off[n] = n_tiles)
-    while (hi - lo > 1) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (tile_off[mid] <= j) lo = mid; else hi = mid;
-    }
-    const int64_t i = lo;
+    const int64_t i = r.node[j], t = r.t[j];
     const int64_t d = deg[i];
-    const int64_t T = tiles_of(d);            // the count tile_off was summed from
-    const int64_t t = j - tile_off[i];
+    const int64_t T = tiles_of(d);
     const int64_t first_pos = t * d / T, last_pos = (t + 1) * d / T;
-    r.node[j] = i;
     r.begin[j] = row_begin[i] + first_pos;
     r.len[j] = (int32_t)(last_pos - first_pos);
     r.state[j] = state[i];
@@ -881,7 +1020,7 @@ struct HopArgs {
     NodeRecs rec;
     uint32_t fanout;
     const int64_t *samp_off; int32_t *samp_nbr;
-    const int64_t *tile_off; TileRecs tile; int64_t n_tiles; int32_t *tile_out;      // tile j writes tile_out[j * fanout ..)
+    TileRecs tile; int64_t n_tiles; int32_t *tile_out;      // tile j writes tile_out[j * fanout ..)
     int merge_span;                                                    // tiles a wave of sample_merge_kernel looks at per round
     const int32_t *tile_order;                                         // the k-th tile job to hand out, or NULL: job k
     ReachedMaps reached;
@@ -1033,8 +1172,7 @@ __global__ void __launch_bounds__(64) sample_merge_kernel(HopArgs a)
     for (int64_t base = (int64_t)blockIdx.x * span; base < a.n_tiles; base += (int64_t)gridDim.x * span) {
         int64_t i_lane = -1;
         if (lane < span && base + lane < a.n_tiles) {
-            const int64_t i = a.tile.node[base + lane];
-            if (a.tile_off[i] == base + lane) i_lane = i;
+            if (a.tile.t[base + lane] == 0) i_lane = a.tile.node[base + lane];
         }
         unsigned long long firsts = ballot64(i_lane >= 0);
         while (firsts != 0ull) {
@@ -1042,7 +1180,7 @@ __global__ void __launch_bounds__(64) sample_merge_kernel(HopArgs a)
             firsts &= firsts - 1ull;
             const int64_t i = bcast64(i_lane, l);
             const int64_t w = base + l;
-            const int64_t T = a.tile_off[i + 1] - w;
+            const int64_t T = tiles_of(a.rec.deg[i]);
             const uint32_t b = a.rec.batch[i];
             const uint64_t S = a.rec.state[i];
             const int32_t *row = a.tile_out + w * f;
@@ -1351,12 +1489,15 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
                      hipStream_t st, const unsigned long long *also_read_dev, unsigned long long *also_read_host)
 {
     const int64_t n_cur = cur.off_host[beta];
-    int32_t *cnt = nullptr, *tiles = nullptr;
-    int64_t *tile_off = nullptr;
+    const int64_t n_chunks = (n_cur + NODE_CHUNK - 1) / NODE_CHUNK;
+    uint32_t *count = nullptr;
+    unsigned long long *chunk_sum = nullptr;
+    int64_t *samp_base = nullptr, *tile_base = nullptr;
     NodeRecs rec{nullptr, nullptr, nullptr, nullptr};
-    RG_TRY(tmp.dev_n<int32_t>((uint64_t)n_cur, &cnt));
-    RG_TRY(tmp.dev_n<int32_t>((uint64_t)n_cur, &tiles));
-    RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_cur + 1, &tile_off));
+    RG_TRY(tmp.dev_n<uint32_t>((uint64_t)n_cur, &count));
+    RG_TRY(tmp.dev_n<unsigned long long>((uint64_t)n_chunks, &chunk_sum));
+    RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_chunks + 1, &samp_base));
+    RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_chunks + 1, &tile_base));
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_cur, &rec.row_begin));
     RG_TRY(tmp.dev_n<int32_t>((uint64_t)n_cur, &rec.deg));
     RG_TRY(tmp.dev_n<uint32_t>((uint64_t)n_cur, &rec.batch));
@@ -1387,10 +1528,11 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     }
     {
         ScopedTimer tm(KG_OFFSETS, st);
-        hipLaunchKernelGGL(node_records_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((n_cur + 255) / 256, (int64_t)n_cu * 64))), dim3(256), 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta,
-                           batch_seed, hop, fanout, rec, cnt, tiles, (int64_t)g->n_nodes, sum_deg_dev, hubs);
-        RG_TRY(scan_i32_to_i64(cnt, cur.samp_off, n_cur, tmp, st));
-        RG_TRY(scan_i32_to_i64(tiles, tile_off, n_cur, tmp, st));
+        hipLaunchKernelGGL(node_records_kernel, dim3((unsigned)n_chunks), dim3(NODE_THREADS), 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta,
+                           batch_seed, hop, fanout, rec, count, chunk_sum, (int64_t)g->n_nodes, sum_deg_dev, hubs);
+        hipLaunchKernelGGL(scan_chunks_kernel, dim3(1), dim3(CHUNK_SCAN_THREADS), 0, st, chunk_sum, n_chunks, samp_base, tile_base, cur.samp_off + n_cur);
+        hipLaunchKernelGGL(sample_offsets_kernel, dim3((unsigned)n_chunks), dim3(NODE_THREADS), 0, st, count, n_cur, samp_base, cur.samp_off);
+        RG_HIP(hipGetLastError());
     }
     int64_t n_tiles = 0;
     // (the byte-marking kernels exist for fan-outs up to 192: the two smaller candidate buffers)
@@ -1399,7 +1541,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         Readback rb(st);
         RG_TRY(rb.add(sum_parts, sum_deg_dev, sizeof(sum_parts)));
         RG_TRY(rb.add(&cur.n_samples, cur.samp_off + n_cur, sizeof(int64_t)));
-        RG_TRY(rb.add(&n_tiles, tile_off + n_cur, sizeof(int64_t)));
+        RG_TRY(rb.add(&n_tiles, tile_base + n_chunks, sizeof(int64_t)));
         if (hubs.counts) RG_TRY(rb.add(&hub_counts, hubs.counts, sizeof(hub_counts)));
         if (also_read_dev) RG_TRY(rb.add(also_read_host, also_read_dev, sizeof(unsigned long long)));     // a value the caller wants behind the same wait
         RG_TRY(rb.wait());
@@ -1427,8 +1569,6 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     const bool all_flags = (sampler == RG_SAMPLER_POSITIONS || fanout + 64 <= 256) && fanout > 0 && (uint64_t)cur.n_samples >= 16 * flag_bytes;
     if (all_flags) RG_HIP(hipMemsetAsync(maps.flags, 1, flag_bytes, st));
     const ReachedMaps reached{use_bytes ? (void *)maps.bytes : (void *)maps.words, maps.flags, maps.words_per_batch, (!use_bytes && maps.paired) ? 1u : 0u};
-    tmp.free_one(cnt);
-    tmp.free_one(tiles);
     RG_TRY(keep.dev_n<int32_t>((uint64_t)cur.n_samples, &cur.samp_nbr));
     if (sampler == RG_SAMPLER_POSITIONS) {
         if (fanout > 0 && n_cur > 0) {
@@ -1447,15 +1587,17 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     }
     if (fanout == 0) n_tiles = 0;             // nothing is drawn; every sample is empty
     int32_t *tile_out = nullptr;
-    TileRecs tile{nullptr, nullptr, nullptr, nullptr};
+    TileRecs tile{nullptr, nullptr, nullptr, nullptr, nullptr};
     RG_TRY(tmp.dev_n<int32_t>((uint64_t)n_tiles * fanout, &tile_out));
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_tiles, &tile.node));
+    RG_TRY(tmp.dev_n<int32_t>((uint64_t)n_tiles, &tile.t));
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_tiles, &tile.begin));
     RG_TRY(tmp.dev_n<int32_t>((uint64_t)n_tiles, &tile.len));
     RG_TRY(tmp.dev_n<uint64_t>((uint64_t)n_tiles, &tile.state));
     if (n_tiles > 0) {
         ScopedTimer tm(KG_OFFSETS, st);
-        hipLaunchKernelGGL(tile_records_kernel, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, st, tile_off, rec.row_begin, rec.deg, rec.state, n_cur, n_tiles, tile);
+        hipLaunchKernelGGL(tile_nodes_kernel, dim3((unsigned)n_chunks), dim3(NODE_THREADS), 0, st, count, n_cur, tile_base, tile);
+        hipLaunchKernelGGL(tile_records_kernel, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, st, rec.row_begin, rec.deg, rec.state, n_tiles, tile);
     }
     int32_t *tile_order = nullptr;
     bool group_tiles = n_tiles >= (int64_t)n_cu * 64 && n_tiles <= 0x7FFFFFFF;     // fewer jobs than two rounds of the resident waves: nothing to bring together
@@ -1496,7 +1638,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         int merge_span = 64;                              // tiles per look of a merging wave: 64 if that still occupies the chip's waves
         while (merge_span > 1 && n_tiles / merge_span < (int64_t)n_cu * 32) merge_span >>= 1;
         const unsigned merge_grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_tiles + merge_span - 1) / merge_span, (int64_t)n_cu * 64));
-        HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_mode != 0 ? SHORT_ROW : 0, short_mode == 2 ? 1 : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile_off, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work};
+        HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_mode != 0 ? SHORT_ROW : 0, short_mode == 2 ? 1 : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work};
         ScopedTimer tm(KG_SAMPLER, st);
         if (const uint32_t n_jobs = std::min(hub_counts.n_jobs, hubs.max_jobs)) {
             HubBucket *buckets = nullptr;
