@@ -1,0 +1,38 @@
+"""Frontiers written through LDS and group by group (more than 4,096 new IDs in a wave's 16,384), for both forms of the
+reached map: batches that reach a little, about a quarter and most of the graph, at sizes around a wave's and a
+workgroup's span; against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rg():
+    from paper_2509_05207_amd import binding
+    binding.lib()
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return binding
+
+
+@pytest.mark.parametrize("byte_maps", ["0", "1"])
+@pytest.mark.parametrize("n", [300, 16_383, 16_385, 65_537, 140_001])
+@pytest.mark.parametrize("share", [0.02, 0.29, 2.0])
+def test_new_ids_of_every_density(rg, orc, n, share, byte_maps, monkeypatch):
+    monkeypatch.setenv("RAPIDGNN_BYTE_MAPS", byte_maps)
+    rng = np.random.default_rng(n)
+    deg = 20
+    indices = np.sort((rng.integers(0, n, size=(n, 1)) + np.arange(deg) * (n // deg) + rng.integers(0, n // deg, size=(n, deg))) % n, axis=1)
+    keep = np.concatenate([np.ones((n, 1), bool), np.diff(indices, axis=1) > 0], axis=1)
+    indptr = np.zeros(n + 1, np.int64)
+    indptr[1:] = np.cumsum(keep.sum(axis=1))
+    indices = indices[keep].astype(np.int32)
+    batch = max(1, int(n * share / 16))
+    train = rng.permutation(n)[: min(n, 3 * batch - 1)].astype(np.int32)
+    o = orc.Schedule(indptr, indices, train, batch, [16, 2], 3, 0, 0, n_threads=4)
+    s = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), batch, [16, 2], 3, 0, 0)
+    for hop in range(3):
+        ids, off = o.frontier(hop)
+        gids, _, goff = rg.rg_schedule_frontier(s, hop)
+        assert np.array_equal(goff, off) and np.array_equal(gids.cpu().numpy(), ids), hop
