@@ -97,16 +97,13 @@ typedef struct rg_cache rg_cache;
  *   fanout       host, [L]; L <= RG_MAX_HOPS, fanout[l] <= RG_MAX_FANOUT; L may be 0
  *   a            allocator or NULL
  *   out          receives the handle
- * Scratch, for the duration of the call: a bitmap of n_batches * n_nodes bits and
- * a map of the IDs a hop reaches, n_batches * n_nodes bytes if that is at most
- * 2 GiB (marks are then plain stores), else as many bits (marks are atomic ORs).
+ * Scratch, for the duration of the call: two bitmaps of n_batches * n_nodes bits
+ * (the IDs a batch has seen, and the IDs a hop reaches).
  * Environment: RAPIDGNN_SPARSE_FRONTIER=1 / 0 forces / forbids the frontier
  * passes tuned for graphs of 10^7 nodes and more (default: chosen from
- * n_nodes); RAPIDGNN_BYTE_MAPS=1 / 0 forces / forbids the byte form of the
- * reached map (never used together with those passes); RAPIDGNN_SHORT_ROWS=0 / 1 / 2
- * makes rows of up to 64 IDs be sampled one per wave / four at a time by a kernel
- * of their own / four at a time inside the main kernel (default: 1 in hops that
- * mark with byte stores, 2 in the others); RAPIDGNN_GROUP_TILES=1 / 0 forces /
+ * n_nodes; sampling kernels then mark what they reach themselves, else a pass
+ * over the samples does); RAPIDGNN_SHORT_ROWS=0 makes rows of up to 64 IDs be
+ * sampled one per wave instead of four; RAPIDGNN_GROUP_TILES=1 / 0 forces /
  * forbids handing out the pieces of rows above 16,384 IDs grouped by the piece
  * they read, so that batches that share a row meet in the caches (default: from
  * 16,384 pieces on); RAPIDGNN_HUB_ROWS=<IDs> makes rows of at least so many IDs

@@ -133,59 +133,40 @@ __device__ __forceinline__ uint32_t batch_of(const int64_t *__restrict__ off, ui
 }
 
 // ---------------------------------------------------------------- reached-ID maps
-// Every sampled ID is marked in the batch's `reached` map; which of the reached IDs are new to the batch is decided
-// afterwards, group by group, against the batch's `seen` bitmap.  The map comes in two forms.  As a byte per node ID,
-// where a mark is a plain store of 1: nothing is read, nothing is atomic, and the memory system takes three to five
-// times as many of them per second as of the other form -- but the map is eight times as large and its scattered
-// stores reach memory as whole lines.  As a bit per node ID, where a mark is an atomic OR without return value.  The
-// wave waits for neither; a hop uses the form that suits its traffic (see sample_hop).  Beside the map there is one
-// flag byte per 256 IDs: the frontier passes read the flags and touch only the flagged groups, which on a graph of
-// 10^8 nodes is a few per cent of the map.
-// What a kernel does with a sampled ID (a template argument).  MARK_BYTES_ALL, MARK_BITS_ALL: the same forms without
-// the flag store, for a hop that reaches nearly every group anyway; its caller sets every flag instead.
-constexpr int MARK_NONE = 0, MARK_BITS = 1, MARK_BYTES = 2, MARK_BYTES_ALL = 3, MARK_BITS_ALL = 4;
-struct ReachedForms {             // host side: the forms a schedule build holds
-    uint32_t *words;              // [n_batches * words_per_batch]
-    uint8_t *bytes;               // [n_batches * words_per_batch * 32]; NULL until the first hop that wants it
-    uint8_t *flags;               // [n_batches * words_per_batch / 8]
-    uint64_t words_per_batch;     // a multiple of 8
-    bool bytes_allowed;           // the byte form is small enough to be worth having
-    bool paired;                  // `words` holds a 64-byte record per group of 256 IDs: the group's eight words of `reached`,
-                                  // then its eight words of `seen` (see paired_word)
-};
-struct ReachedMaps {              // the form one hop marks
-    void *map;
-    uint8_t *flags;
-    uint64_t words_per_batch;
-    uint32_t paired;              // 1: the bit form in paired records
-};
-struct ReachedOfBatch {
-    void *map;
-    uint8_t *flags;
-    uint32_t paired;
-};
+// Every sampled ID is marked in the batch's `reached` bitmap; which of the reached IDs are new to the batch is decided
+// afterwards, group by group, against the batch's `seen` bitmap.  Beside the map there is one flag byte per 256 IDs: the
+// frontier passes read the flags and touch only the flagged groups, which on a graph of 10^8 nodes is a few per cent of
+// the map.  Where a batch's bitmap is small enough to be put together in LDS piece by piece, a pass over the hop's samples
+// writes it (mark_pass_kernel) and the sampling kernels mark nothing; on larger graphs they mark each ID as they write it,
+// by an atomic OR without return value which the wave does not wait for.
+constexpr int MARK_NONE = 0, MARK_BITS = 1;      // what a kernel does with a sampled ID (a template argument)
 // On graphs of 10^8 nodes a batch touches a few per cent of its groups, so the frontier passes read a group's words
 // of `reached` and of `seen` from two unrelated places each time.  Paired, both lie in one 64-byte record: word w of
 // a map that would hold both arrays apart is word paired_word(w) of the records (`seen`: eight words further on).
+// Graphs whose maps are paired are the ones whose sampling kernels mark.
+struct ReachedMaps {
+    uint32_t *words;              // [n_batches * words_per_batch]; paired: 64-byte records, the group's words of `reached` in front
+    uint8_t *flags;               // [n_batches * words_per_batch / 8]
+    uint64_t words_per_batch;     // a multiple of 8
+    bool paired;
+};
+struct ReachedOfBatch {
+    uint32_t *words;
+    uint8_t *flags;
+};
 __host__ __device__ __forceinline__ uint64_t paired_word(uint64_t w) { return ((w >> 3) << 4) | (w & 7); }
 template <int MARK>
 __device__ __forceinline__ ReachedOfBatch reached_of(const ReachedMaps &m, uint32_t batch)
 {
-    const uint64_t step = (MARK == MARK_BYTES || MARK == MARK_BYTES_ALL) ? m.words_per_batch << 5 : m.words_per_batch << (2 + m.paired);       // bytes per batch
-    return ReachedOfBatch{static_cast<uint8_t *>(m.map) + (uint64_t)batch * step, m.flags + (uint64_t)batch * (m.words_per_batch >> 3), m.paired};
+    if (MARK == MARK_NONE) return ReachedOfBatch{nullptr, nullptr};
+    return ReachedOfBatch{m.words + (uint64_t)batch * (m.words_per_batch << 1), m.flags + (uint64_t)batch * (m.words_per_batch >> 3)};
 }
 template <int MARK>
 __device__ __forceinline__ void mark_reached(const ReachedOfBatch &r, uint32_t u)
 {
     if (MARK == MARK_NONE) return;
-    if (MARK == MARK_BYTES_ALL) { static_cast<uint8_t *>(r.map)[u] = 1; return; }
-    if (MARK == MARK_BYTES) static_cast<uint8_t *>(r.map)[u] = 1;
-    else {
-        const uint32_t w = u >> 5;
-        (void)__hip_atomic_fetch_or(static_cast<uint32_t *>(r.map) + (r.paired ? (((w >> 3) << 4) | (w & 7)) : w), 1u << (u & 31), __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (MARK != MARK_BITS_ALL) r.flags[u >> 8] = 1;
+    (void)__hip_atomic_fetch_or(r.words + paired_word(u >> 5), 1u << (u & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    r.flags[u >> 8] = 1;
 }
 
 }  // namespace rg

@@ -34,8 +34,9 @@
 //    Tiles are dealt out by workgroup index and done before the groups of
 //    nodes, which the waves then take from a counter as they become free.
 //
-// No step sorts anything.  While a wave writes a sample it also marks the
-// batch's reached-ID bitmaps, so frontier dedup costs no extra pass.
+// No step sorts anything.  What a batch has reached is marked in its bitmap by
+// a pass over the samples (mark_pass_kernel), or, on graphs whose bitmaps are
+// too large for that, by the sampling waves as they write the samples.
 #include "rg_internal.h"
 #include "rg_device.h"
 
@@ -1015,8 +1016,7 @@ struct HopArgs {
     const int32_t *indices;
     const int32_t *frontier; int64_t n_frontier;
     int64_t n_full_groups, n_units;                                    // set by launch_hop: see there
-    int min_deg;                                                       // rows of up to this many IDs are not sampled one per wave ...
-    int short_inline;                                                  // ... but four at a time: 1 = by sample_kernel<.., true>, a group's short rows first; 0 = by sample_short_kernel
+    int min_deg;                                                       // rows of up to this many IDs are not sampled one per wave but four at a time, a group's short rows first (sample_kernel<.., true>); 0: none are
     NodeRecs rec;
     uint32_t fanout;
     const int64_t *samp_off; int32_t *samp_nbr;
@@ -1378,44 +1378,6 @@ static double hub_line(int64_t n_nodes, uint32_t fanout)
     return std::sqrt(per_value * lambda * 4294967296.0);
 }
 
-struct ShortArgs {
-    const int32_t *indices;
-    int64_t n_frontier;
-    NodeRecs rec;
-    uint32_t fanout;
-    const int64_t *samp_off; int32_t *samp_nbr;
-    ReachedMaps reached;
-};
-
-template <int MARK>
-__global__ void __launch_bounds__(64) sample_short_kernel(ShortArgs a)
-{
-    __shared__ ShortRec recs[64];
-    const int lane = threadIdx.x;
-    const int64_t n_groups = (a.n_frontier + 63) >> 6;
-    for (int64_t w = blockIdx.x; w < n_groups; w += gridDim.x) {
-        const int64_t i_lane = (w << 6) + lane;
-        const int deg_lane = i_lane < a.n_frontier ? a.rec.deg[i_lane] : 0;
-        const bool mine = deg_lane > 0 && deg_lane <= SHORT_ROW;
-        const int count = __popcll(ballot64(mine));
-        if (count == 0) continue;
-        const int at = short_row_slot(mine, deg_lane, lane);
-        __syncthreads();                                            // the previous group's records have been read by every lane
-        if (mine) recs[at] = ShortRec{a.rec.row_begin[i_lane], a.samp_off[i_lane], a.rec.state[i_lane], deg_lane, a.rec.batch[i_lane]};
-        __syncthreads();
-        sample_short_rows<MARK>(recs, count, a.indices, (int)a.fanout, a.samp_nbr, a.reached, lane);
-    }
-}
-
-template <int MARK>
-static rg_status launch_short(const ShortArgs &a, int n_cu, hipStream_t st)
-{
-    const int64_t n_groups = (a.n_frontier + 63) >> 6;
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_groups, (int64_t)n_cu * 32));
-    hipLaunchKernelGGL((sample_short_kernel<MARK>), dim3(grid), dim3(64), 0, st, a);
-    return RG_OK;
-}
-
 // Every workgroup of the sampling launch must be resident from the start (tiles are dealt out by workgroup index), so
 // the grid is what the chip holds of this kernel, or the amount of work if that is less.
 template <int CAP, int MARK>
@@ -1423,7 +1385,7 @@ static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, 
 {
     HopArgs a = args;
     static std::atomic<int> asked[2] = {{0}, {0}};      // the same answer every time; asked once (schedules may be built from several threads)
-    const int which = a.short_inline ? 1 : 0;
+    const int which = a.min_deg > 0 ? 1 : 0;
     int per_cu = asked[which].load(std::memory_order_relaxed);
     if (per_cu == 0) {
         int v = 0;
@@ -1478,14 +1440,84 @@ __global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int
     }
 }
 
+// ---------------------------------------------------------------- the samples marked in the reached bitmaps
+// Bound by reading the samples once per piece of the bitmap.  A workgroup puts MARK_WORDS words of one batch's bitmap
+// together in LDS from all of the batch's samples, or a part of them, and writes them and the flags of the groups that
+// hold bits: nothing scattered leaves the compute unit.  Marked one by one from the sampling kernels, the memory system takes 25 G
+// atomic ORs or 88 G byte stores a second and the kernels carry the address arithmetic.   233 k nodes, 29 M samples: 0.05 ms; 2.45 M nodes, 167 M samples:
+// 0.54, and the launches that marked bytes themselves 3.9 -> 2.2 ms; 146 M samples in three hops: 0.32, launches that marked
+// bits 10.6 -> 9.6.
+// The pieces of a batch run on one XCD (workgroup g runs on XCD g mod 8) at about the same time and share the reads.
+constexpr int MARK_THREADS = 1024;
+constexpr int MARK_WORDS = 16384;                        // 64 KB of LDS, 524,288 IDs: two workgroups per compute unit
+constexpr int MARK_XCDS = 8;
+constexpr int MARK_IN_FLIGHT = 8;
+constexpr int64_t MARK_PART = 1 << 18;                   // samples per part, at least, where there are too few pieces to fill the chip
+
+__global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *__restrict__ samp_nbr, const int64_t *__restrict__ samp_off, const int64_t *__restrict__ batch_off,
+                                                                 uint32_t n_batches, uint32_t pieces, uint32_t parts, uint32_t piece_words, ReachedMaps m)
+{
+    extern __shared__ uint32_t bits[];                   // [piece_words]
+    const uint32_t r = blockIdx.x / MARK_XCDS, per_batch = pieces * parts;
+    const uint32_t b = r / per_batch * MARK_XCDS + blockIdx.x % MARK_XCDS;
+    if (b >= n_batches) return;
+    const uint32_t piece = r % per_batch % pieces, part = r % per_batch / pieces;
+    for (uint32_t w = threadIdx.x; w < piece_words; w += MARK_THREADS) bits[w] = 0u;
+    __syncthreads();
+    const int64_t first = samp_off[batch_off[b]], n = samp_off[batch_off[b + 1]] - first;
+    const int64_t lo = first + n * part / parts, hi = first + n * (part + 1) / parts;
+    const uint32_t id0 = piece * piece_words * 32u, n_ids = piece_words * 32u;
+    for (int64_t j0 = lo + threadIdx.x; j0 < hi; j0 += MARK_IN_FLIGHT * MARK_THREADS) {
+        uint32_t u[MARK_IN_FLIGHT];
+#pragma unroll
+        for (int q = 0; q < MARK_IN_FLIGHT; ++q) u[q] = (uint32_t)samp_nbr[min(j0 + q * MARK_THREADS, hi - 1)] - id0;      // (past the end: the last sample again)
+#pragma unroll
+        for (int q = 0; q < MARK_IN_FLIGHT; ++q)
+            if (u[q] < n_ids) atomicOr(&bits[u[q] >> 5], 1u << (u[q] & 31));
+    }
+    __syncthreads();
+    // a thread per group of eight words: written where it holds bits (the map is clear otherwise), its flag set
+    const uint64_t word0 = (uint64_t)piece * piece_words;
+    uint32_t *map = m.words + (uint64_t)b * m.words_per_batch + word0;
+    uint8_t *flags = m.flags + (((uint64_t)b * m.words_per_batch + word0) >> 3);
+    const uint32_t n_groups = (uint32_t)(min((uint64_t)piece_words, m.words_per_batch - word0) >> 3);
+    for (uint32_t g = threadIdx.x; g < n_groups; g += MARK_THREADS) {
+        const uint4 x = *reinterpret_cast<const uint4 *>(bits + 8 * g), y = *reinterpret_cast<const uint4 *>(bits + 8 * g + 4);
+        if ((x.x | x.y | x.z | x.w | y.x | y.y | y.z | y.w) == 0u) continue;
+        if (parts == 1) {
+            *reinterpret_cast<uint4 *>(map + 8 * g) = x;
+            *reinterpret_cast<uint4 *>(map + 8 * g + 4) = y;
+        } else {
+            const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (w[k]) (void)__hip_atomic_fetch_or(map + 8 * g + k, w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        flags[g] = 1;
+    }
+}
+
+static rg_status launch_mark_pass(const HopData &cur, uint32_t beta, const ReachedMaps &m, int n_cu, hipStream_t st)
+{
+    if (cur.n_samples == 0) return RG_OK;
+    const uint32_t piece_words = (uint32_t)std::min<uint64_t>(MARK_WORDS, m.words_per_batch);          // (both multiples of eight)
+    const uint32_t pieces = (uint32_t)((m.words_per_batch + piece_words - 1) / piece_words);
+    // a few batches of many samples are read in parts, whose bits are ORed into the map
+    const uint64_t units = (uint64_t)pieces * beta;
+    const uint32_t parts = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(cur.n_samples / beta / MARK_PART, n_cu / (int64_t)units));
+    const uint64_t grid = (uint64_t)(beta + MARK_XCDS - 1) / MARK_XCDS * MARK_XCDS * pieces * parts;
+    if (grid > 0x7FFFFFFFull) { set_error("rg_build_schedule: %llu pieces of bitmaps in one hop", (unsigned long long)grid); return RG_ERANGE; }
+    hipLaunchKernelGGL(mark_pass_kernel, dim3((unsigned)grid), dim3(MARK_THREADS), piece_words * sizeof(uint32_t), st, cur.samp_nbr, cur.samp_off, cur.off_dev, beta, pieces,
+                       parts, piece_words, m);
+    RG_HIP(hipGetLastError());
+    return RG_OK;
+}
+
 // Samples hop `hop` of every batch: fills cur.samp_off / samp_nbr / n_samples and marks the reached-ID bitmaps.
 // also_read_dev (or NULL): one more device value copied to *also_read_host behind the hop's own readback; if it
 // comes back non-zero the hop stops there (the caller is about to refuse its input).
-// Where `maps` allows the reached map's byte form, the hop marks into whichever form suits it (see below; the byte
-// map is allocated, clear, by the first hop that wants it) and *marked_bytes says which, so that the frontier pass
-// reads the right one.
 rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint64_t *batch_seed, uint32_t hop, uint32_t fanout,
-                     uint32_t sampler, ReachedForms &maps, int prefer_bytes, bool *marked_bytes, Arena &keep, Arena &tmp, int n_cu,
+                     uint32_t sampler, const ReachedMaps &reached, Arena &keep, Arena &tmp, int n_cu,
                      hipStream_t st, const unsigned long long *also_read_dev, unsigned long long *also_read_host)
 {
     const int64_t n_cur = cur.off_host[beta];
@@ -1535,8 +1567,6 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         RG_HIP(hipGetLastError());
     }
     int64_t n_tiles = 0;
-    // (the byte-marking kernels exist for fan-outs up to 192: the two smaller candidate buffers)
-    const bool can_bytes = maps.bytes_allowed && (sampler == RG_SAMPLER_POSITIONS || fanout + 64 <= 256);
     {
         Readback rb(st);
         RG_TRY(rb.add(sum_parts, sum_deg_dev, sizeof(sum_parts)));
@@ -1549,26 +1579,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
             for (int q = 0; q < DEG_SUMS; ++q) sums[q] += sum_parts[DEG_SUMS * k + q];
         if (also_read_dev && *also_read_host != 0) return RG_OK;        // the caller refuses the build: nothing more to launch
     }
-    // Which form of the reached map this hop marks.  A byte store is several times cheaper than an atomic OR, but the
-    // byte map is 8 times the size and its scattered stores reach memory as whole lines; that pays where marks are a
-    // large part of the hop's traffic (rows mostly no longer than the fan-out: one mark per ID read), and costs a
-    // little where long rows are scanned for a few samples (measured: at one mark per 20 IDs read nothing is gained,
-    // at one per 10 the hop is a quarter faster).  Threshold: one mark per 14 IDs read.
-    // The positions sampler reads no more IDs than it draws, so its marks are always most of its traffic (233 k nodes, 29 M
-    // draws: its two launches 1231 us with atomic marks, 704 with byte stores).
-    const unsigned long long sum_deg = sampler == RG_SAMPLER_POSITIONS ? (unsigned long long)cur.n_samples : sums[0];
-    const bool use_bytes = can_bytes && (prefer_bytes >= 0 ? prefer_bytes != 0 : (unsigned long long)cur.n_samples * 14ull >= sum_deg);
-    if (use_bytes && !maps.bytes) {
-        const uint64_t map_bytes = maps.words_per_batch * 32 * (uint64_t)beta;
-        RG_TRY(tmp.dev_zeroed(map_bytes, (void **)&maps.bytes, st));       // (the caller hands it back as all-zero: the frontier passes clear what a hop marks)
-    }
-    *marked_bytes = use_bytes;
-    // A hop that marks many times more IDs than the maps have groups reaches nearly every group: the per-mark flag
-    // store (a third of the hop's scattered stores) is replaced by setting every flag once.
-    const uint64_t flag_bytes = maps.words_per_batch / 8 * (uint64_t)beta;
-    const bool all_flags = (sampler == RG_SAMPLER_POSITIONS || fanout + 64 <= 256) && fanout > 0 && (uint64_t)cur.n_samples >= 16 * flag_bytes;
-    if (all_flags) RG_HIP(hipMemsetAsync(maps.flags, 1, flag_bytes, st));
-    const ReachedMaps reached{use_bytes ? (void *)maps.bytes : (void *)maps.words, maps.flags, maps.words_per_batch, (!use_bytes && maps.paired) ? 1u : 0u};
+    const bool inline_marks = reached.paired;
     RG_TRY(keep.dev_n<int32_t>((uint64_t)cur.n_samples, &cur.samp_nbr));
     if (sampler == RG_SAMPLER_POSITIONS) {
         if (fanout > 0 && n_cur > 0) {
@@ -1576,12 +1587,11 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
             const int64_t per_round = fanout >= (uint32_t)POS_THREADS ? 1 : POS_THREADS / fanout;
             const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_cur + per_round - 1) / per_round, (int64_t)n_cu * 64));
 #define RG_POSITIONS(M) hipLaunchKernelGGL(sample_positions_kernel<M>, dim3(grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, cur.samp_off, cur.samp_nbr, reached)
-            if (use_bytes && all_flags) RG_POSITIONS(MARK_BYTES_ALL);
-            else if (use_bytes) RG_POSITIONS(MARK_BYTES);
-            else if (all_flags) RG_POSITIONS(MARK_BITS_ALL);
-            else RG_POSITIONS(MARK_BITS);
+            if (inline_marks) RG_POSITIONS(MARK_BITS);
+            else RG_POSITIONS(MARK_NONE);
 #undef RG_POSITIONS
             RG_HIP(hipGetLastError());
+            if (!inline_marks) RG_TRY(launch_mark_pass(cur, beta, reached, n_cu, st));
         }
         return RG_OK;
     }
@@ -1622,23 +1632,19 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     }
 
     if (fanout > 0 && n_cur > 0) {
-        // Rows of up to SHORT_ROW IDs are sampled four at a time wherever a frontier has any: by a kernel of their own
-        // where the hop marks with plain byte stores, inside the other kernel (each group's short rows first) where marks are
-        // atomic ORs -- a kernel of nothing but short rows is then bound by the rate of those atomics (large_sparse: 58 M of
-        // them in 2.6 ms, 22 G/s), while between the streaming of long rows they cost next to nothing.  Same samples in
-        // every case; RAPIDGNN_SHORT_ROWS = 0 / 1 / 2 forces one row per wave / the kernel of their own / the inline form.
-        int short_mode = sums[2] == 0 ? 0 : use_bytes ? 1 : 2;
-        if (const char *force = getenv("RAPIDGNN_SHORT_ROWS")) short_mode = force[0] == '1' ? 1 : force[0] == '2' ? 2 : 0;
-        const bool short_rows_apart = short_mode == 1;
+        // Rows of up to SHORT_ROW IDs are sampled four at a time wherever a frontier has any (in a kernel of their own instead:
+        // 2.45 M nodes, fan-outs 15,10,5 10.2 ms against 9.6, fan-outs 50,50 2.20 against 2.10).  Same samples either way;
+        // RAPIDGNN_SHORT_ROWS = 0 forces one row per wave.
+        bool short_rows = sums[2] != 0;
+        if (const char *force = getenv("RAPIDGNN_SHORT_ROWS")) short_rows = force[0] != '0';
         const uint32_t need = fanout + 64;
-        const int mark = need > 256 ? MARK_BITS : all_flags && use_bytes ? MARK_BYTES_ALL : all_flags ? MARK_BITS_ALL : use_bytes ? MARK_BYTES : MARK_BITS;
         unsigned long long *next_work = nullptr;
         RG_TRY(tmp.dev_n<unsigned long long>(1, &next_work));
         RG_HIP(hipMemsetAsync(next_work, 0, sizeof(unsigned long long), st));
         int merge_span = 64;                              // tiles per look of a merging wave: 64 if that still occupies the chip's waves
         while (merge_span > 1 && n_tiles / merge_span < (int64_t)n_cu * 32) merge_span >>= 1;
         const unsigned merge_grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_tiles + merge_span - 1) / merge_span, (int64_t)n_cu * 64));
-        HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_mode != 0 ? SHORT_ROW : 0, short_mode == 2 ? 1 : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work};
+        HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_rows ? SHORT_ROW : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work};
         ScopedTimer tm(KG_SAMPLER, st);
         if (const uint32_t n_jobs = std::min(hub_counts.n_jobs, hubs.max_jobs)) {
             HubBucket *buckets = nullptr;
@@ -1648,46 +1654,30 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
             hipLaunchKernelGGL(hub_table_kernel, dim3(per_row, hub_counts.n_rows), dim3(256), 0, st, g->indices, g->n_nodes, hubs, buckets);
             const HubArgs ha{g->indices, g->n_nodes, hubs, buckets, n_jobs, rec, fanout, cur.samp_off, cur.samp_nbr, reached};
             const dim3 grid(std::min<uint32_t>(n_jobs, (uint32_t)n_cu * 64)), block(HUB_THREADS);
-            switch (mark) {
-            case MARK_BYTES_ALL: hipLaunchKernelGGL(hub_sample_kernel<MARK_BYTES_ALL>, grid, block, 0, st, ha); break;
-            case MARK_BITS_ALL: hipLaunchKernelGGL(hub_sample_kernel<MARK_BITS_ALL>, grid, block, 0, st, ha); break;
-            case MARK_BYTES: hipLaunchKernelGGL(hub_sample_kernel<MARK_BYTES>, grid, block, 0, st, ha); break;
-            default: hipLaunchKernelGGL(hub_sample_kernel<MARK_BITS>, grid, block, 0, st, ha); break;
-            }
+            if (inline_marks) hipLaunchKernelGGL(hub_sample_kernel<MARK_BITS>, grid, block, 0, st, ha);
+            else hipLaunchKernelGGL(hub_sample_kernel<MARK_NONE>, grid, block, 0, st, ha);
             RG_HIP(hipGetLastError());
         }
         // worth it where a group is long work: rows of a thousand IDs on average, tiles aside (short rows finish a
         // group of 64 in no time, and four times the requests to the work counter then cost more than the tail does;
         // measured: Medium, 2,500 IDs per row, 4 % faster; large_sparse and partition_share, a few hundred, 1-8 % slower)
-        const unsigned long long ids_here = sums[1] - (short_mode != 0 ? sums[3] : 0), rows_here = (unsigned long long)n_cur - (short_mode != 0 ? sums[2] : 0);
+        const unsigned long long ids_here = sums[1] - (short_rows ? sums[3] : 0), rows_here = (unsigned long long)n_cur - (short_rows ? sums[2] : 0);
         const bool fine_tail = ids_here >= 1024ull * rows_here;
         // a frontier that does not give every resident wave a group of 64 (the seed hop) is split finer from rows of 256 IDs on
         const bool fine_if_few = ids_here >= 256ull * rows_here;
-        if (need <= 128) {
-            if (all_flags && use_bytes) RG_TRY((launch_hop<128, MARK_BYTES_ALL>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-            else if (all_flags) RG_TRY((launch_hop<128, MARK_BITS_ALL>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-            else if (use_bytes) RG_TRY((launch_hop<128, MARK_BYTES>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-            else RG_TRY((launch_hop<128, MARK_BITS>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-        } else if (need <= 256) {
-            if (all_flags && use_bytes) RG_TRY((launch_hop<256, MARK_BYTES_ALL>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-            else if (all_flags) RG_TRY((launch_hop<256, MARK_BITS_ALL>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-            else if (use_bytes) RG_TRY((launch_hop<256, MARK_BYTES>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-            else RG_TRY((launch_hop<256, MARK_BITS>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-        }
-        else if (need <= 512) RG_TRY((launch_hop<512, MARK_BITS>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-        else if (need <= 1024) RG_TRY((launch_hop<1024, MARK_BITS>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
-        else RG_TRY((launch_hop<2048, MARK_BITS>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));
+#define RG_HOP(CAP)                                                                                                   \
+    do {                                                                                                              \
+        if (inline_marks) RG_TRY((launch_hop<CAP, MARK_BITS>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));      \
+        else RG_TRY((launch_hop<CAP, MARK_NONE>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));                   \
+    } while (0)
+        if (need <= 128) RG_HOP(128);
+        else if (need <= 256) RG_HOP(256);
+        else if (need <= 512) RG_HOP(512);
+        else if (need <= 1024) RG_HOP(1024);
+        else RG_HOP(2048);
+#undef RG_HOP
         RG_HIP(hipGetLastError());
-        if (short_rows_apart) {
-            const ShortArgs sa{g->indices, n_cur, rec, fanout, cur.samp_off, cur.samp_nbr, reached};
-            switch (mark) {
-            case MARK_BYTES_ALL: RG_TRY(launch_short<MARK_BYTES_ALL>(sa, n_cu, st)); break;
-            case MARK_BITS_ALL: RG_TRY(launch_short<MARK_BITS_ALL>(sa, n_cu, st)); break;
-            case MARK_BYTES: RG_TRY(launch_short<MARK_BYTES>(sa, n_cu, st)); break;
-            default: RG_TRY(launch_short<MARK_BITS>(sa, n_cu, st)); break;
-            }
-            RG_HIP(hipGetLastError());
-        }
+        if (!inline_marks) RG_TRY(launch_mark_pass(cur, beta, reached, n_cu, st));
     }
     return RG_OK;
 }

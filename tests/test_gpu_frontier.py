@@ -36,3 +36,20 @@ def test_new_ids_of_every_density(rg, orc, n, share, byte_maps, monkeypatch):
         ids, off = o.frontier(hop)
         gids, _, goff = rg.rg_schedule_frontier(s, hop)
         assert np.array_equal(goff, off) and np.array_equal(gids.cpu().numpy(), ids), hop
+
+
+@pytest.mark.parametrize("n", [524_287, 524_289, 1_100_000])
+@pytest.mark.parametrize("n_train,batch", [(40_000, 40_000), (41_000, 20_480), (300, 20)])
+def test_marks_in_pieces_and_parts(rg, orc, n, n_train, batch):
+    """Bitmaps of one to three pieces of 524,288 IDs; batches whose samples are marked in several parts, and in one."""
+    rng = np.random.default_rng(n + n_train)
+    deg = 18
+    step = n // deg
+    indices = ((np.arange(deg) * step)[None, :] + rng.integers(0, step, size=(n, deg))).astype(np.int32)       # ascending: one ID per stretch
+    indptr = np.arange(0, n * deg + 1, deg, dtype=np.int64)
+    train = rng.permutation(n)[:n_train].astype(np.int32)
+    o = orc.Schedule(indptr, indices.ravel(), train, batch, [16], 3, 0, 0, n_threads=4)
+    s = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices.ravel()).cuda(), torch.from_numpy(train).cuda(), batch, [16], 3, 0, 0)
+    ids, off = o.frontier(1)
+    gids, _, goff = rg.rg_schedule_frontier(s, 1)
+    assert np.array_equal(goff, off) and np.array_equal(gids.cpu().numpy(), ids)
