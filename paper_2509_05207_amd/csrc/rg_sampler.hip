@@ -1445,11 +1445,11 @@ __global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int
 // together in LDS from all of the batch's samples, or a part of them, and writes them and the flags of the groups that
 // hold bits: nothing scattered leaves the compute unit.  Marked one by one from the sampling kernels, the memory system takes 25 G
 // atomic ORs or 88 G byte stores a second and the kernels carry the address arithmetic.   233 k nodes, 29 M samples: 0.05 ms; 2.45 M nodes, 167 M samples:
-// 0.54, and the launches that marked bytes themselves 3.9 -> 2.2 ms; 146 M samples in three hops: 0.32, launches that marked
+// 0.43, and the launches that marked bytes themselves 3.9 -> 2.2 ms; 146 M samples in three hops: 0.32, launches that marked
 // bits 10.6 -> 9.6.
 // The pieces of a batch run on one XCD (workgroup g runs on XCD g mod 8) at about the same time and share the reads.
 constexpr int MARK_THREADS = 1024;
-constexpr int MARK_WORDS = 16384;                        // 64 KB of LDS, 524,288 IDs: two workgroups per compute unit
+constexpr int MARK_WORDS = 32768;                        // 128 KB of LDS, 1,048,576 IDs: every piece reads all samples of its batch, so few large ones (of 64 KB: 0.54 ms for the 167 M below, so 0.43)
 constexpr int MARK_XCDS = 8;
 constexpr int MARK_IN_FLIGHT = 8;
 constexpr int64_t MARK_PART = 1 << 18;                   // samples per part, at least, where there are too few pieces to fill the chip
@@ -1507,6 +1507,7 @@ static rg_status launch_mark_pass(const HopData &cur, uint32_t beta, const Reach
     const uint32_t parts = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(cur.n_samples / beta / MARK_PART, n_cu / (int64_t)units));
     const uint64_t grid = (uint64_t)(beta + MARK_XCDS - 1) / MARK_XCDS * MARK_XCDS * pieces * parts;
     if (grid > 0x7FFFFFFFull) { set_error("rg_build_schedule: %llu pieces of bitmaps in one hop", (unsigned long long)grid); return RG_ERANGE; }
+    RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(mark_pass_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, MARK_WORDS * (int)sizeof(uint32_t)));
     hipLaunchKernelGGL(mark_pass_kernel, dim3((unsigned)grid), dim3(MARK_THREADS), piece_words * sizeof(uint32_t), st, cur.samp_nbr, cur.samp_off, cur.off_dev, beta, pieces,
                        parts, piece_words, m);
     RG_HIP(hipGetLastError());

@@ -38,10 +38,10 @@ def test_new_ids_of_every_density(rg, orc, n, share, byte_maps, monkeypatch):
         assert np.array_equal(goff, off) and np.array_equal(gids.cpu().numpy(), ids), hop
 
 
-@pytest.mark.parametrize("n", [524_287, 524_289, 1_100_000])
+@pytest.mark.parametrize("n", [1_048_575, 1_048_577, 2_200_000])
 @pytest.mark.parametrize("n_train,batch", [(40_000, 40_000), (41_000, 20_480), (300, 20)])
 def test_marks_in_pieces_and_parts(rg, orc, n, n_train, batch):
-    """Bitmaps of one to three pieces of 524,288 IDs; batches whose samples are marked in several parts, and in one."""
+    """Bitmaps of one to three pieces of 1,048,576 IDs; batches whose samples are marked in several parts, and in one."""
     rng = np.random.default_rng(n + n_train)
     deg = 18
     step = n // deg
