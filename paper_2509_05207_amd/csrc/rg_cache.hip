@@ -434,11 +434,34 @@ __device__ __forceinline__ uint32_t batch_of_pos(const int64_t *__restrict__ off
 }
 
 // Where a request for v's feature row is served from: (tag << 62) | row.  One record of the slot map says whether v
-// is local and whether (and where) it is cached; row_of is read for the others only.
+// is local and whether (and where) it is cached; row_of is read for the others only, and not even for those where the
+// tables hold the nodes' rows in the order of their IDs: row_of is then a rank, which the record gives too.
 struct RouteSources {
     const int32_t *row_of;
     const SlotRec *slot_pairs;       // see slot_lookup
+    const uint32_t *not_ranks;       // dev: 0 = row_of[v] is the number of local (of remote) IDs in front of v, for every v; NULL: not known
 };
+
+// local_cnt[r] = local IDs among record r's 32
+__global__ void local_counts_kernel(const SlotRec *__restrict__ recs, int64_t n_recs, int32_t *__restrict__ local_cnt)
+{
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < n_recs) local_cnt[r] = __popc(recs[r].z);
+}
+// The records' w, and whether row_of is what they make of it: *not_ranks = 1 if any node's differs.
+__global__ void row_ranks_kernel(SlotRec *recs, int64_t n, const int64_t *__restrict__ local_off, const int32_t *__restrict__ row_of, uint32_t *__restrict__ not_ranks)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    bool differs = false;
+    if (v < n) {
+        const uint32_t z = recs[v >> 5].z, bit = 1u << (v & 31);
+        const int64_t in_front = local_off[v >> 5], local = in_front + __popc(z & (bit - 1));
+        differs = row_of[v] != ((z & bit) ? local : v - local);
+        if ((v & 31) == 0) recs[v >> 5].w = (uint32_t)in_front;
+    }
+    if (__ballot(differs) != 0ull && (threadIdx.x & 63) == 0) *not_ranks = 1u;
+}
+
 // entry[j] = where ids[j] is served from, for every listed input node, which of them are misses and which are local (one
 // bit each, in position order: a wave's ballot is the 64-bit word of its 64 consecutive positions), and how many of
 // either each tile of PLAN_TILE positions holds.  Nothing is added up per batch here: the tiles of a batch run at the
@@ -459,6 +482,7 @@ __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__res
     __shared__ int red[2][PLAN_THREADS / 64];
     const int64_t tile0 = (int64_t)blockIdx.x * PLAN_TILE;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool ranks = rs.not_ranks && *rs.not_ranks == 0u;
     uint32_t v[PLAN_PER_THREAD];
     SlotRec rec[PLAN_PER_THREAD];
     int32_t row[PLAN_PER_THREAD];
@@ -469,8 +493,12 @@ __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__res
 #pragma unroll
     for (int k = 0; k < PLAN_PER_THREAD; ++k) {
         const uint32_t bit = 1u << (v[k] & 31);
-        // a cached row is at its rank, the others at row_of
-        row[k] = (rec[k].x & ~rec[k].z & bit) ? (int32_t)(rec[k].y + __popc(rec[k].x & (bit - 1))) : rs.row_of[v[k]];
+        // a cached row is at its rank among the cached IDs, the others at row_of
+        if (rec[k].x & ~rec[k].z & bit) row[k] = (int32_t)(rec[k].y + __popc(rec[k].x & (bit - 1)));
+        else if (ranks) {
+            const uint32_t local = rec[k].w + __popc(rec[k].z & (bit - 1));
+            row[k] = (int32_t)((rec[k].z & bit) ? local : v[k] - local);
+        } else row[k] = rs.row_of[v[k]];
     }
     int n_local = 0, n_miss = 0;                           // of the wave
 #pragma unroll
@@ -801,7 +829,29 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
 
     // ---- a5/a9: plans, miss lists and counts for every batch of every epoch
     c->plans.resize(n_epochs);
-    const RouteSources rs{f->row_of, c->slot_pairs};
+    RouteSources rs{f->row_of, c->slot_pairs, nullptr};
+    // Reading row_of is two thirds of what a plan over many input nodes moves (a batch's IDs touch nearly every line of it),
+    // so it is first checked, in one pass, for being the ranks that the slot map knows anyway.  The pass reads row_of
+    // once; worth it from eight input nodes per node on (two epochs of 80 M input nodes on 2.45 M nodes: their plans
+    // 882 us, 494 so, and 20 for the check; a graph with fewer input nodes than nodes would pay more than it saves).
+    int64_t n_inputs = 0;
+    for (uint32_t e = 0; e < n_epochs; ++e) n_inputs += epochs[e]->n_batches ? epochs[e]->hop[epochs[e]->L].off_host[epochs[e]->n_batches] : 0;
+    if (n > 0 && n_inputs >= 8 * n) {
+        const int64_t n_recs = (n + 31) / 32;
+        int32_t *local_cnt = nullptr;
+        int64_t *local_off = nullptr;
+        uint32_t *not_ranks = nullptr;
+        RG_TRY(tmp.dev_n<int32_t>((uint64_t)n_recs, &local_cnt));
+        RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_recs + 1, &local_off));
+        RG_TRY(tmp.dev_n<uint32_t>(1, &not_ranks));
+        ScopedTimer tm(KG_PLAN, st);
+        RG_HIP(hipMemsetAsync(not_ranks, 0, sizeof(uint32_t), st));
+        hipLaunchKernelGGL(local_counts_kernel, dim3((unsigned)((n_recs + 255) / 256)), dim3(256), 0, st, c->slot_pairs, n_recs, local_cnt);
+        RG_TRY(scan_i32_to_i64(local_cnt, local_off, n_recs, tmp, st));
+        hipLaunchKernelGGL(row_ranks_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, c->slot_pairs, n, local_off, f->row_of, not_ranks);
+        RG_HIP(hipGetLastError());
+        rs.not_ranks = not_ranks;
+    }
     for (uint32_t e = 0; e < n_epochs; ++e) RG_TRY(build_plan(epochs[e], rs, c->arena, tmp, st, &c->plans[e]));
     if (forked.side) RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));
     RG_HIP(hipStreamSynchronize(st));

@@ -154,7 +154,8 @@ __host__ __device__ inline int64_t make_entry(int64_t tag, int64_t row) { return
 // ---------------------------------------------------------------- slot of a cached node
 // Slot j of the cache table holds the j-th smallest cached ID, so a node's slot is its rank among the cached IDs.
 // The cache keeps that as one record per 32 node IDs -- x: which of them are cached, y: how many cached IDs lie in
-// front of the 32, z: which of them are local (the caller's is_local as bits), w: unused -- half a byte per node
+// front of the 32, z: which of them are local (the caller's is_local as bits), w: how many local IDs lie in front of the
+// 32 (written only where a plan wants it, see row_ranks_kernel) -- half a byte per node
 // instead of the four of a dense slot_of array plus the byte of is_local (55 MB against 555 MB on a graph of 10^8
 // nodes, so lookups meet cached lines and the select pass has next to nothing to write).
 typedef uint4 SlotRec;

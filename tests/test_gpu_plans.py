@@ -44,3 +44,36 @@ def test_counts_and_rows_of_every_batch(rg, n_train, batch, K):
         assert rg.rg_gather_batches(s, cache, feat, 0, s.n_batches, out) == want
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy(), table[ids])
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 1000, 4096])
+@pytest.mark.parametrize("order", ["ranks", "last two swapped", "shuffled", "all local", "all remote"])
+def test_rows_whatever_order_the_tables_are_in(rg, n, order):
+    """Ten epochs over all nodes, so that the plans look whether row_of is the ranks the slot map knows: where it is, where
+    it is but for two nodes, and where it is any order."""
+    rng = np.random.default_rng(n)
+    d = "cuda"
+    indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
+    scheds = [rg.rg_build_schedule(indptr, indices, torch.arange(n, dtype=torch.int32, device=d), 700, [], 5, 0, e) for e in range(10)]
+    is_local = (rng.random(n) < {"all local": 2.0, "all remote": -1.0}.get(order, 0.4)).astype(np.uint8)
+    rows = {}
+    row_of = np.zeros(n, np.int32)
+    for side in (0, 1):
+        nodes = np.flatnonzero(is_local == side)
+        at = np.arange(nodes.size)
+        if order == "shuffled":
+            at = rng.permutation(nodes.size)
+        elif order == "last two swapped" and side == 0 and nodes.size > 1:
+            at[-2:] = at[-2:][::-1]
+        row_of[nodes] = at
+        t = np.zeros((max(nodes.size, 1), 4), np.int32)
+        t[at] = np.stack([nodes, nodes * 3, nodes ^ 5, -nodes], axis=1)
+        rows[side] = torch.from_numpy(t).to(d)
+    feat = rg.make_features(torch.from_numpy(is_local).to(d), torch.from_numpy(row_of).to(d), rows[1], rows[0], 16)
+    cache = rg.rg_build_cache(scheds, feat, n // 5)
+    for s in scheds[::4]:
+        ids = rg.rg_schedule_frontier(s, 0)[0].cpu().numpy()
+        out = torch.full((n, 4), -7, dtype=torch.int32, device=d)
+        rg.rg_gather_batches(s, cache, feat, 0, s.n_batches, out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), np.stack([ids, ids * 3, ids ^ 5, -ids], axis=1))
