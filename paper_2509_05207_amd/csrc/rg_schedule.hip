@@ -24,15 +24,16 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
                      const unsigned long long *also_read_dev, unsigned long long *also_read_host);
 
 // ---------------------------------------------------------------- a1/a2: seeds, shuffle keys
-__global__ void batch_seeds_kernel(uint64_t s0, uint32_t worker, uint32_t epoch, uint32_t n_batches, uint64_t *__restrict__ seeds)
+// (S_{e,i} = combine(combine(combine(mix64(s0 ^ G), w), e), i): the part in front of i is the same for all batches and
+// comes from the host, as does the shuffle's P_e)
+static uint64_t worker_stream(uint64_t s0, uint32_t worker) { return combine(mix64(s0 ^ HG64), worker); }
+static uint64_t epoch_stream(uint64_t s0, uint32_t worker, uint32_t epoch) { return combine(worker_stream(s0, worker), epoch); }
+static uint64_t shuffle_stream(uint64_t s0, uint32_t worker, uint32_t epoch) { return combine(worker_stream(s0, worker), ((uint64_t)1 << 32) + epoch); }
+
+__global__ void batch_seeds_kernel(uint64_t epoch_state, uint32_t n_batches, uint64_t *__restrict__ seeds)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_batches) return;
-    uint64_t h = mix64(s0 ^ HG64);
-    h = combine(h, worker);
-    h = combine(h, epoch);
-    h = combine(h, i);
-    seeds[i] = h;
+    if (i < n_batches) seeds[i] = combine(epoch_state, i);
 }
 
 // Shuffle: train position t gets key combine(P_e, t); the epoch's order is ascending (key, t).
@@ -49,32 +50,38 @@ __device__ __forceinline__ bool kp_less(const KeyPos &a, const KeyPos &b)
     return a.key < b.key || (a.key == b.key && a.pos < b.pos);
 }
 
-__device__ __forceinline__ uint64_t shuffle_key(uint64_t s0, uint32_t worker, uint32_t epoch, uint64_t t)
-{
-    uint64_t P = mix64(s0 ^ HG64);
-    P = combine(P, worker);
-    P = combine(P, ((uint64_t)1 << 32) + epoch);
-    return combine(P, t);
-}
 __device__ __forceinline__ uint32_t bucket_of_key(uint64_t key, uint32_t bucket_bits) { return bucket_bits ? (uint32_t)(key >> (64u - bucket_bits)) : 0u; }
 
-__global__ void shuffle_count_kernel(uint64_t s0, uint32_t worker, uint32_t epoch, uint64_t T, uint32_t bucket_bits, int32_t *__restrict__ bucket_cnt)
+// Counts the buckets; the count in front of a position's own is its place in its bucket (in whatever order the adds
+// arrive; the ranks below do not depend on it), so the scatter needs no adds of its own.
+// The same threads check the precondition on train_nodes: *n_bad += the IDs outside [0, n_nodes) and the IDs that
+// occurred before (`once`: a bit per node ID, clear on entry).  Until the host has seen the count (at the build's
+// first readback), the kernels that index by a seed's value skip values out of range.  (Bound by the atomics' answers, so
+// both of a thread's are in flight at once.  300,000 positions: count, scatter and check 60 us as kernels of their own with a
+// key from the first word on and adds in both, 40 so.)
+__global__ void shuffle_count_kernel(uint64_t P, uint64_t T, uint32_t bucket_bits, int32_t *__restrict__ bucket_cnt, int32_t *__restrict__ place,
+                                     const int32_t *__restrict__ train, int64_t n_nodes, uint32_t *__restrict__ once, unsigned long long *__restrict__ n_bad)
 {
     const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < T) atomicAdd(&bucket_cnt[bucket_of_key(shuffle_key(s0, worker, epoch, t), bucket_bits)], 1);
+    bool bad = false;
+    if (t < T) {
+        const int64_t v = train[t];
+        const int32_t at = atomicAdd(&bucket_cnt[bucket_of_key(combine(P, t), bucket_bits)], 1);
+        if (v < 0 || v >= n_nodes) bad = true;
+        else bad = (atomicOr(&once[v >> 5], 1u << (v & 31)) >> (v & 31)) & 1u;
+        place[t] = at;
+    }
+    const unsigned long long m = __ballot(bad);
+    if (m != 0ull && (threadIdx.x & 63) == 0) atomicAdd(n_bad, (unsigned long long)__popcll(m));
 }
 
-// bucket_cnt is counted down again, so every slot of a bucket is handed out once; the order inside a bucket is
-// whatever the atomics give, the ranks below do not depend on it.
-__global__ void shuffle_scatter_kernel(uint64_t s0, uint32_t worker, uint32_t epoch, uint64_t T, uint32_t bucket_bits,
-                                       const int64_t *__restrict__ bucket_off, int32_t *__restrict__ bucket_cnt, KeyPos *__restrict__ kp)
+__global__ void shuffle_scatter_kernel(uint64_t P, uint64_t T, uint32_t bucket_bits, const int64_t *__restrict__ bucket_off, const int32_t *__restrict__ place,
+                                       KeyPos *__restrict__ kp)
 {
     const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= T) return;
-    const uint64_t key = shuffle_key(s0, worker, epoch, t);
-    const uint32_t b = bucket_of_key(key, bucket_bits);
-    const int32_t left = atomicSub(&bucket_cnt[b], 1);                 // count .. 1
-    kp[bucket_off[b] + left - 1] = KeyPos{key, t};
+    const uint64_t key = combine(P, t);
+    kp[bucket_off[bucket_of_key(key, bucket_bits)] + place[t]] = KeyPos{key, t};
 }
 
 constexpr int RANK_THREADS = 256;
@@ -101,23 +108,6 @@ __global__ void __launch_bounds__(RANK_THREADS) shuffle_rank_kernel(const KeyPos
         }
         if (have) seeds[first + rank] = train[mine.pos];
     }
-}
-
-// The precondition on train_nodes, checked on the device: *n_bad += the IDs outside [0, n_nodes) and the IDs that
-// occurred before (`once`: a bit per node ID, clear on entry).  Until the host has seen the count (at the build's
-// first readback), the kernels that index by a seed's value skip values out of range.
-__global__ void check_train_kernel(const int32_t *__restrict__ train, uint64_t T, int64_t n_nodes, uint32_t *__restrict__ once,
-                                   unsigned long long *__restrict__ n_bad)
-{
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool bad = false;
-    if (t < T) {
-        const int64_t v = train[t];
-        if (v < 0 || v >= n_nodes) bad = true;
-        else bad = (atomicOr(&once[v >> 5], 1u << (v & 31)) >> (v & 31)) & 1u;
-    }
-    const unsigned long long m = __ballot(bad);
-    if (m != 0ull && (threadIdx.x & 63) == 0) atomicAdd(n_bad, (unsigned long long)__popcll(m));
 }
 
 // paired: `seen` points at the first group's `seen` half of the paired records (see paired_word)
@@ -576,7 +566,7 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
     // ---- a1: batch seeds
     uint64_t *batch_seed = nullptr;
     RG_TRY(tmp.dev_n<uint64_t>(beta ? beta : 1, &batch_seed));
-    if (beta) hipLaunchKernelGGL(batch_seeds_kernel, dim3((beta + 255) / 256), dim3(256), 0, st, s0, worker, epoch, beta, batch_seed);
+    if (beta) hipLaunchKernelGGL(batch_seeds_kernel, dim3((beta + 255) / 256), dim3(256), 0, st, epoch_stream(s0, worker, epoch), beta, batch_seed);
 
     // ---- a2: shuffle and cut into batches
     HopData &h0 = s->hop[0];
@@ -585,39 +575,35 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
     h0.off_host.resize((size_t)beta + 1);
     for (uint32_t b = 0; b <= beta; ++b) h0.off_host[b] = (int64_t)std::min<uint64_t>((uint64_t)b * B, T);
     RG_HIP(hipMemcpyAsync(h0.off_dev, h0.off_host.data(), ((size_t)beta + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
+    // cleared together: the count of bad train nodes, the bit per node of the check, the shuffle's bucket counts
+    uint32_t bucket_bits = 0;                  // about a hundred positions per bucket, a power of two of buckets
+    while (bucket_bits < 20 && ((uint64_t)128 << bucket_bits) < T) ++bucket_bits;
+    const uint64_t n_buckets = (uint64_t)1 << bucket_bits, once_words = ((uint64_t)g->n_nodes + 31) / 32;
     unsigned long long *n_bad_train = nullptr, n_bad_host = 0;
-    RG_TRY(tmp.dev_n<unsigned long long>(1, &n_bad_train));
-    RG_HIP(hipMemsetAsync(n_bad_train, 0, sizeof(unsigned long long), st));
-    if (T > 0) {
-        uint32_t *once = nullptr;
-        const uint64_t once_words = ((uint64_t)g->n_nodes + 31) / 32;
-        RG_TRY(tmp.dev_n<uint32_t>(once_words, &once));
-        RG_HIP(hipMemsetAsync(once, 0, once_words * sizeof(uint32_t), st));
-        hipLaunchKernelGGL(check_train_kernel, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, st, train, T, (int64_t)g->n_nodes, once, n_bad_train);
-    }
+    const uint64_t cleared_bytes = sizeof(unsigned long long) + (n_buckets + once_words) * sizeof(uint32_t);
+    RG_TRY(tmp.dev(cleared_bytes, (void **)&n_bad_train));
+    RG_HIP(hipMemsetAsync(n_bad_train, 0, cleared_bytes, st));
+    int32_t *bucket_cnt = reinterpret_cast<int32_t *>(n_bad_train + 1);
+    uint32_t *once = reinterpret_cast<uint32_t *>(bucket_cnt + n_buckets);
     auto refuse_bad_train = [&]() -> rg_status {
         if (n_bad_host == 0) return RG_OK;
         set_error("rg_build_schedule: %llu of the %llu train nodes are outside [0, n_nodes) or repeated", n_bad_host, (unsigned long long)T);
         return RG_EINVAL;
     };
     if (T > 0) {
-        // about a hundred positions per bucket, a power of two of buckets
-        uint32_t bucket_bits = 0;
-        while (bucket_bits < 20 && ((uint64_t)128 << bucket_bits) < T) ++bucket_bits;
-        const uint64_t n_buckets = (uint64_t)1 << bucket_bits;
         KeyPos *kp = nullptr;
-        int32_t *bucket_cnt = nullptr;
+        int32_t *place = nullptr;
         int64_t *bucket_off = nullptr;
         RG_TRY(tmp.dev_n<KeyPos>(T, &kp));
-        RG_TRY(tmp.dev_n<int32_t>(n_buckets, &bucket_cnt));
+        RG_TRY(tmp.dev_n<int32_t>(T, &place));
         RG_TRY(tmp.dev_n<int64_t>(n_buckets + 1, &bucket_off));
-        RG_HIP(hipMemsetAsync(bucket_cnt, 0, n_buckets * sizeof(int32_t), st));
         {
             ScopedTimer tm(KG_SORT, st);
             const unsigned blocks = (unsigned)((T + 255) / 256);
-            hipLaunchKernelGGL(shuffle_count_kernel, dim3(blocks), dim3(256), 0, st, s0, worker, epoch, T, bucket_bits, bucket_cnt);
+            const uint64_t P = shuffle_stream(s0, worker, epoch);
+            hipLaunchKernelGGL(shuffle_count_kernel, dim3(blocks), dim3(256), 0, st, P, T, bucket_bits, bucket_cnt, place, train, (int64_t)g->n_nodes, once, n_bad_train);
             RG_TRY(scan_i32_to_i64(bucket_cnt, bucket_off, (int64_t)n_buckets, tmp, st));
-            hipLaunchKernelGGL(shuffle_scatter_kernel, dim3(blocks), dim3(256), 0, st, s0, worker, epoch, T, bucket_bits, bucket_off, bucket_cnt, kp);
+            hipLaunchKernelGGL(shuffle_scatter_kernel, dim3(blocks), dim3(256), 0, st, P, T, bucket_bits, bucket_off, place, kp);
             hipLaunchKernelGGL(shuffle_rank_kernel, dim3((unsigned)n_buckets), dim3(RANK_THREADS), 0, st, kp, bucket_off, train, h0.ids);
         }
         RG_HIP(hipGetLastError());
