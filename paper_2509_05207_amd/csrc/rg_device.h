@@ -136,14 +136,14 @@ __device__ __forceinline__ uint32_t batch_of(const int64_t *__restrict__ off, ui
 // Every sampled ID is marked in the batch's `reached` bitmap; which of the reached IDs are new to the batch is decided
 // afterwards, group by group, against the batch's `seen` bitmap.  Beside the map there is one flag byte per 256 IDs: the
 // frontier passes read the flags and touch only the flagged groups, which on a graph of 10^8 nodes is a few per cent of
-// the map.  Where a batch's bitmap is small enough to be put together in LDS piece by piece, a pass over the hop's samples
-// writes it (mark_pass_kernel) and the sampling kernels mark nothing; on larger graphs they mark each ID as they write it,
-// by an atomic OR without return value which the wave does not wait for.
+// the map.  Where a hop's samples are dense enough in the bitmaps, a pass over them puts the bitmaps together in LDS piece
+// by piece (mark_pass_kernel) and the sampling kernels mark nothing; elsewhere they mark each ID as they write it, by an
+// atomic OR without return value which the wave does not wait for.
 constexpr int MARK_NONE = 0, MARK_BITS = 1;      // what a kernel does with a sampled ID (a template argument)
 // On graphs of 10^8 nodes a batch touches a few per cent of its groups, so the frontier passes read a group's words
 // of `reached` and of `seen` from two unrelated places each time.  Paired, both lie in one 64-byte record: word w of
 // a map that would hold both arrays apart is word paired_word(w) of the records (`seen`: eight words further on).
-// Graphs whose maps are paired are the ones whose sampling kernels mark.
+// Where maps are paired the sampling kernels always mark.
 struct ReachedMaps {
     uint32_t *words;              // [n_batches * words_per_batch]; paired: 64-byte records, the group's words of `reached` in front
     uint8_t *flags;               // [n_batches * words_per_batch / 8]
@@ -153,19 +153,22 @@ struct ReachedMaps {
 struct ReachedOfBatch {
     uint32_t *words;
     uint8_t *flags;
+    uint32_t paired;
 };
 __host__ __device__ __forceinline__ uint64_t paired_word(uint64_t w) { return ((w >> 3) << 4) | (w & 7); }
 template <int MARK>
 __device__ __forceinline__ ReachedOfBatch reached_of(const ReachedMaps &m, uint32_t batch)
 {
-    if (MARK == MARK_NONE) return ReachedOfBatch{nullptr, nullptr};
-    return ReachedOfBatch{m.words + (uint64_t)batch * (m.words_per_batch << 1), m.flags + (uint64_t)batch * (m.words_per_batch >> 3)};
+    if (MARK == MARK_NONE) return ReachedOfBatch{nullptr, nullptr, 0};
+    const uint32_t paired = m.paired ? 1u : 0u;
+    return ReachedOfBatch{m.words + (uint64_t)batch * (m.words_per_batch << paired), m.flags + (uint64_t)batch * (m.words_per_batch >> 3), paired};
 }
 template <int MARK>
 __device__ __forceinline__ void mark_reached(const ReachedOfBatch &r, uint32_t u)
 {
     if (MARK == MARK_NONE) return;
-    (void)__hip_atomic_fetch_or(r.words + paired_word(u >> 5), 1u << (u & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t w = u >> 5;
+    (void)__hip_atomic_fetch_or(r.words + (r.paired ? (((w >> 3) << 4) | (w & 7)) : w), 1u << (u & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     r.flags[u >> 8] = 1;
 }
 

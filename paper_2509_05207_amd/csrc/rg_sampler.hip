@@ -1201,7 +1201,7 @@ __global__ void __launch_bounds__(64) sample_merge_kernel(HopArgs a)
 // the share n_nodes / 2^32 are IDs at all and have to be looked up: the longer the row the fewer, and fewer than d from
 // d = sqrt(lambda * 2^32) on.  A row of 6.7 M IDs takes 14,000 values instead of 6.7 M keys. 
 // On 111 M nodes and 405 M edges in 147 batches, fan-out 10 behind 15, the sampling launches took 4.5 ms, nine tenths of
-// it vector instructions; with the rows from 450,000 IDs on taken out: 1.66 ms, and 0.26 for the key values, 0.17 for the
+// it vector instructions; with the rows from 450,000 IDs on taken out (half the length the rule takes): 1.66 ms, and 0.26 for the key values, 0.17 for the
 // tables, 0.05 to clear them.  (A directory of positions into the row in place of the tables cost 0.09 to build but three
 // dependent reads per lookup: 0.38 ms for the key values.)
 // Results are those of reading the row: all IDs with a key in the range come out, the f smallest keys are taken.
@@ -1266,7 +1266,7 @@ struct HubArgs {
     const int32_t *indices;
     int64_t n_nodes;
     HubTable h;
-    const HubBucket *buckets;
+    const HubBucket *buckets;                   // NULL: no tables, every row is read
     uint32_t n_jobs;
     NodeRecs rec;
     uint32_t fanout;
@@ -1293,7 +1293,7 @@ __global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
         const HubJob job = a.h.jobs[j];
         const HubRow r = a.h.rows[job.slot];
         const int32_t *row = a.indices + r.begin;
-        const HubBucket *mine = a.buckets + r.first;
+        const HubBucket *mine = a.buckets ? a.buckets + r.first : nullptr;
         const uint64_t S = a.rec.state[job.i];
         const uint32_t lo = uni((uint32_t)S), hi = uni((uint32_t)(S >> 32));
         uint64_t from = 0, to = (uint64_t)(guessed_candidates(f) / (float)r.deg * 4294967296.0f) + 1;     // key values [from, to)
@@ -1307,7 +1307,7 @@ __global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
                 const uint32_t k = atomicAdd(&n_hits, 1u);
                 if (k < HUB_HITS) { hit_key[k] = key; hit_id[k] = id; hit_at[k] = at; }
             };
-            if (!r.damaged) {
+            if (!r.damaged && a.buckets) {
                 int waiting = 0;                                 // in this wave's queue (the same in all its lanes)
                 auto look_up = [&](int count) {                  // the queue's last `count` <= 64 entries
                     if (lane < count) {
@@ -1331,7 +1331,7 @@ __global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
                 }
                 if (waiting > 0) look_up(waiting);
             } else {
-                for (int32_t p = threadIdx.x; p < r.deg; p += HUB_THREADS) {         // a row that is not in order: read as it is
+                for (int64_t p = threadIdx.x; p < r.deg; p += HUB_THREADS) {         // a row that is not in order, or without a table: read as it is
                     const uint32_t u = (uint32_t)row[p], key = key32(lo, hi, u);
                     if (key >= from && key < to) add_hit(key, u, (uint32_t)p);
                 }
@@ -1367,15 +1367,16 @@ __global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
     }
 }
 
-// From which length on a row is sampled from the keys' side: where its key values cost what its IDs would.  A value costs
-// about 1.6 times what an ID does (twice the arithmetic, no read), and the share of values that are IDs one more
-// scattered read each.  Measured around the line it gives for the graph above (450,000), sampling altogether: from
-// 350,000 2.2 ms, 450,000 2.09, 600,000 2.12, 800,000 2.20, none 4.5.
+// From which length on a row is sampled from the keys' side: twice the length at which its key values cost what its IDs
+// would.  A value costs about 1.6 times what an ID does (twice the arithmetic, no read), and the share of values that are
+// IDs one more scattered read each.  At the even length nothing is won and a few jobs do not fill the chip: 15 M nodes,
+// 176 batches, sampled from 520,000 IDs on (the even length) 770 us for the schedule, 699 without.  On the
+// graph above (even length 450,000), sampling altogether: from 350,000 2.2 ms, 450,000 2.09, 600,000 2.12, 800,000 2.20, none 4.5.
 static double hub_line(int64_t n_nodes, uint32_t fanout)
 {
     const double f = (double)fanout, lambda = f + 3.0 * std::sqrt(f) + 3.0;
     const double per_value = 1.6 + 20.0 * (double)n_nodes / 4294967296.0;
-    return std::sqrt(per_value * lambda * 4294967296.0);
+    return 2.0 * std::sqrt(per_value * lambda * 4294967296.0);
 }
 
 // Every workgroup of the sampling launch must be resident from the start (tiles are dealt out by workgroup index), so
@@ -1452,6 +1453,7 @@ constexpr int MARK_THREADS = 1024;
 constexpr int MARK_WORDS = 32768;                        // 128 KB of LDS, 1,048,576 IDs: every piece reads all samples of its batch, so few large ones (of 64 KB: 0.54 ms for the 167 M below, so 0.43)
 constexpr int MARK_XCDS = 8;
 constexpr int MARK_IN_FLIGHT = 8;
+constexpr uint64_t MARK_SPARSE = 512;                    // see sample_hop
 constexpr int64_t MARK_PART = 1 << 18;                   // samples per part, at least, where there are too few pieces to fill the chip
 
 __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *__restrict__ samp_nbr, const int64_t *__restrict__ samp_off, const int64_t *__restrict__ batch_off,
@@ -1580,7 +1582,10 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
             for (int q = 0; q < DEG_SUMS; ++q) sums[q] += sum_parts[DEG_SUMS * k + q];
         if (also_read_dev && *also_read_host != 0) return RG_OK;        // the caller refuses the build: nothing more to launch
     }
-    const bool inline_marks = reached.paired;
+    // The mark pass clears and looks through every word of every batch's bitmap, some 5 us per 128 KB of LDS and compute
+    // unit; marks from the sampling kernels take 40 ps each where they do not hide behind the reads.  So the pass from one
+    // sample per MARK_SPARSE IDs of bitmap on (where both cost the same it is about one per 2,048).
+    const bool inline_marks = reached.paired || (uint64_t)cur.n_samples * MARK_SPARSE < reached.words_per_batch * 32 * (uint64_t)beta;
     RG_TRY(keep.dev_n<int32_t>((uint64_t)cur.n_samples, &cur.samp_nbr));
     if (sampler == RG_SAMPLER_POSITIONS) {
         if (fanout > 0 && n_cur > 0) {
@@ -1648,11 +1653,13 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_rows ? SHORT_ROW : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work};
         ScopedTimer tm(KG_SAMPLER, st);
         if (const uint32_t n_jobs = std::min(hub_counts.n_jobs, hubs.max_jobs)) {
+            // (no memory for the tables: the rows are read instead, as rows out of order are; the build needs no more than it did)
             HubBucket *buckets = nullptr;
-            RG_TRY(tmp.dev_n<HubBucket>(hub_counts.buckets, &buckets));
-            RG_HIP(hipMemsetAsync(buckets, 0xFF, hub_counts.buckets * sizeof(HubBucket), st));
+            const bool tables = tmp.dev_n<HubBucket>(hub_counts.buckets, &buckets) == RG_OK;
+            if (!tables) buckets = nullptr;
+            if (tables) RG_HIP(hipMemsetAsync(buckets, 0xFF, hub_counts.buckets * sizeof(HubBucket), st));
             const uint32_t per_row = std::max<uint32_t>(64, std::min<uint32_t>(1024, 64u * (uint32_t)n_cu / hub_counts.n_rows));       // few rows, long ones: the workgroups of the chip shared out among them
-            hipLaunchKernelGGL(hub_table_kernel, dim3(per_row, hub_counts.n_rows), dim3(256), 0, st, g->indices, g->n_nodes, hubs, buckets);
+            if (tables) hipLaunchKernelGGL(hub_table_kernel, dim3(per_row, hub_counts.n_rows), dim3(256), 0, st, g->indices, g->n_nodes, hubs, buckets);
             const HubArgs ha{g->indices, g->n_nodes, hubs, buckets, n_jobs, rec, fanout, cur.samp_off, cur.samp_nbr, reached};
             const dim3 grid(std::min<uint32_t>(n_jobs, (uint32_t)n_cu * 64)), block(HUB_THREADS);
             if (inline_marks) hipLaunchKernelGGL(hub_sample_kernel<MARK_BITS>, grid, block, 0, st, ha);

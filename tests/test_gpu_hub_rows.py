@@ -38,9 +38,10 @@ def hub_graph(rng, n, hub_deg, shuffled=()):
     return indptr, indices, hubs
 
 
-def check(rg, orc, indptr, indices, train, batch, fanout):
+def check(rg, orc, indptr, indices, train, batch, fanout, allocator=None):
     o = orc.Schedule(indptr, indices, train, batch, fanout, 5, 1, 2, n_threads=8)
-    g = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), batch, fanout, 5, 1, 2)
+    g = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), batch, fanout, 5, 1, 2,
+                             allocator=allocator)
     assert g.n_batches == o.n_batches
     for hop in range(o.L + 1):
         ids, off = o.frontier(hop)
@@ -70,3 +71,14 @@ def test_hub_rows_without_being_forced(rg, orc, sparse, monkeypatch):
     indptr, indices, hubs = hub_graph(rng, n, [899_999, 880_000, 300_000, 500_000, 600_000])
     train = rng.permutation(n)[:800].astype(np.int32)
     check(rg, orc, indptr, indices, train, 64, [3, 2, 5])
+
+
+def test_hub_rows_without_memory_for_their_tables(rg, orc, monkeypatch):
+    monkeypatch.setenv("RAPIDGNN_HUB_ROWS", "16385")
+    rng = np.random.default_rng(4)
+    n = 200_000
+    indptr, indices, hubs = hub_graph(rng, n, [150_000, 199_999, 180_000])
+    train = np.unique(np.concatenate([hubs, rng.permutation(n)[:100]])).astype(np.int32)
+    a = rg.TorchAllocator(limit_bytes=1 << 20)
+    check(rg, orc, indptr, indices, train, 64, [12, 4], allocator=a.struct)
+    assert a.n_refused == 2                                  # the tables of either hop, nothing else
