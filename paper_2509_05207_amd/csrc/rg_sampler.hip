@@ -388,8 +388,12 @@ __device__ __forceinline__ uint32_t kth_key_threshold(const uint32_t (&k)[E], co
 // row's keys lie at or below lambda / len of the key range; the guess decides only how much work is done, never the
 // result: if fewer than f keys turn up (a Poisson count: one row in 600 to 900 for fan-outs of 5 to 25), the exact
 // procedure runs.  Every candidate is an append and widens the final cut, so the guess is as low as the misses allow:
-// with f + 4 sqrt(f) + 8 a row is missed once in 10^5 but three candidates in ten are superfluous.
+// with f + 4 sqrt(f) + 8 a row is missed once in 10^5 but three candidates in ten are superfluous.  A missed row is streamed twice
+// by its wave.  For the pieces of long rows that is the tail of the launch (they run a wave each, in one round or a few), and eight
+// more candidates are nothing to 16,384 IDs: they get the safe guess.  A share of 15 M nodes, 177 batches of 163 seeds, fan-outs
+// 15, 10: the schedule 669 us with the low guess for all rows, 579 so; eight batches of 32 on 32 M nodes: 401 and 318.
 __device__ __forceinline__ float guessed_candidates(int f) { return (float)f + 3.0f * __fsqrt_rn((float)f) + 3.0f; }
+__device__ __forceinline__ float safely_guessed_candidates(int f) { return (float)f + 4.0f * __fsqrt_rn((float)f) + 8.0f; }
 // The cut itself, its lower half all ones (see key32_open); share <= 0.5.
 __device__ __forceinline__ uint32_t guessed_cut_of(float share) { return (uint32_t)(share * 4294967296.0f) | 0xFFFFu; }
 
@@ -685,7 +689,7 @@ __device__ __forceinline__ void sample_long_row(const int32_t *__restrict__ row,
     // that can be in the sample and skips the first cut and the prunes of the exact procedure.  Every ID with a key up to
     // the cut is kept, so if at least f turn up, the f smallest keys of the row are among them; if fewer do, the row is
     // streamed again with the exact procedure.
-    const float lambda = guessed_candidates(f);
+    const float lambda = len > BIG_ROW ? safely_guessed_candidates(f) : guessed_candidates(f);
     const bool can_guess = uni(lambda * 4.0f <= (float)len);
     const uint32_t guessed_cut = guessed_cut_of(fminf(lambda / (float)len, 0.5f));
     Stream s{0, true, 0u};
