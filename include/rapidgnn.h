@@ -108,8 +108,14 @@ typedef struct rg_cache rg_cache;
  * they read, so that batches that share a row meet in the caches (default: from
  * 16,384 pieces on); RAPIDGNN_HUB_ROWS=<IDs> makes rows of at least so many IDs
  * (and more than 16,384) be sampled from the keys' side, without being read
- * (default: behind the first hop of epochs of 8 batches and more, from a length
- * computed from the fan-out and n_nodes).  The result is the same in every case.  The maps are drawn from a pool of blocks known to be
+ * (default: behind the first hop of epochs of 16 batches and more, from a length
+ * computed from the fan-out and n_nodes, where a hop's frontiers hold at least 24
+ * such pieces per compute unit; never a hop with such a row out of order);
+ * RAPIDGNN_HUB_RANGE=<factor> changes how many key values are looked through first
+ * (for tests).  The result is the same in every case.
+ * Further scratch that a hop sampled so takes only if it is there: tables of up to
+ * 8 bytes per ID of the distinct rows.
+ * The bitmaps are drawn from a pool of blocks known to be
  * all-zero and handed back to it after the build has cleared what it touched;
  * RAPIDGNN_CHECK_ZERO_MAPS=1 makes every build verify that on the device first.
  */

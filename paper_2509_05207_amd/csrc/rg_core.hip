@@ -48,7 +48,8 @@ struct BlockCache {
 
     // zeroed: prefer a block that is known to hold nothing but zero bytes (*was_zero says whether one was found;
     // otherwise the caller clears what it got).  A request that finds no ordinary block takes a zeroed one.
-    void *take(uint64_t bytes, hipError_t *err, bool zeroed = false, bool *was_zero = nullptr)
+    // spare: the caller can do without; nothing is given back to the driver for it.
+    void *take(uint64_t bytes, hipError_t *err, bool zeroed = false, bool *was_zero = nullptr, bool spare = false)
     {
         int dev = 0;
         (void)hipGetDevice(&dev);
@@ -75,7 +76,7 @@ struct BlockCache {
         }
         void *p = nullptr;
         hipError_t e = hipMalloc(&p, want);
-        if (e != hipSuccess) {                       // release what waits for its readers, give the cache back to the driver, try once more
+        if (e != hipSuccess && !spare) {             // release what waits for its readers, give the cache back to the driver, try once more
             (void)hipGetLastError();
             reap_retired(true);
             trim();
@@ -244,6 +245,18 @@ rg_status Arena::dev(uint64_t bytes, void **out)
     in_use_ += want;
     *out = p;
     return RG_OK;
+}
+
+bool Arena::dev_spare(uint64_t bytes, void **out)
+{
+    const uint64_t want = bytes ? bytes : 256;
+    hipError_t e = hipSuccess;
+    void *p = custom_ ? a_.alloc(want, 1, a_.ctx) : g_blocks.take(want, &e, false, nullptr, true);
+    if (!p) return false;
+    items_.push_back({p, 1, want});
+    in_use_ += want;
+    *out = p;
+    return true;
 }
 
 rg_status Arena::dev_zeroed(uint64_t bytes, void **out, hipStream_t st)

@@ -54,6 +54,8 @@ class Arena {
     rg_status dev(uint64_t bytes, void **out);
     rg_status pinned(uint64_t bytes, void **out);
     template <typename T> rg_status dev_n(uint64_t n, T **out) { return dev(n * sizeof(T), (void **)out); }
+    // Device memory the caller can do without: false, and nothing else done to find it or said about it, where there is none.
+    bool dev_spare(uint64_t bytes, void **out);
     // Device memory that holds zero bytes: a block that an earlier call handed back as all-zero (free_zeroed), or a
     // fresh one cleared on `st`.  The big per-batch bitmaps of a schedule build come and go this way, so that an
     // epoch clears only the parts the epoch before it touched instead of gigabytes.

@@ -66,22 +66,20 @@ struct NodeRecs {
 };
 
 // ---------------------------------------------------------------- hub rows: found by node_records_kernel
-// The longest rows are not read at all (see hub_sample_kernel): each distinct one gets an entry in a small hash table
-// keyed by node, with room for a table of its IDs, and every frontier position that holds one becomes a job.
+// The longest rows may be sampled without being read (see hub_sample_kernel): each distinct one gets an entry in a small
+// hash table keyed by node, and the frontier positions that hold one are flagged in their count word.  Whether they become
+// jobs of that kernel or tile jobs like every other long row is decided by the host once it knows how many there are.
 constexpr int HUB_SLOTS = 4096;                 // distinct hub rows; a row that finds no place is sampled in tiles
 constexpr int HUB_PROBES = 64;
-constexpr uint32_t HUB_MAX_JOBS = 1u << 18;
 constexpr uint32_t HUB_MAX_FANOUT = 448;
 struct HubRow {
     int64_t begin;
     unsigned long long first;                   // its first bucket
     int32_t deg;
     int32_t shift;                              // bucket of ID u: u >> shift
-    int32_t damaged;                            // not strictly ascending inside [0, n_nodes): the table does not hold
-    int32_t pad;
 };
 struct HubJob { int64_t i; int32_t slot; int32_t pad; };
-struct HubCounts { unsigned long long buckets; uint32_t n_jobs, n_rows; };
+struct HubCounts { unsigned long long buckets; uint32_t n_rows, n_jobs, damaged, pad; };       // damaged: a row that is not strictly ascending inside [0, n_nodes), for which its table does not hold
 // A bucket: the IDs of 2^shift consecutive ones that the row holds, as their low bits, in order; HUB_EMPTY behind them.  A
 // bucket that is full may have had no room for all.
 constexpr int HUB_BUCKET = 16;
@@ -90,73 +88,79 @@ constexpr int HUB_MAX_SHIFT = 15;               // low bits stay below HUB_EMPTY
 struct alignas(32) HubBucket { uint16_t id[HUB_BUCKET]; };
 struct HubTable {
     int32_t min_deg;                            // rows from this length on; INT32_MAX: none
-    int32_t *keys;                              // [HUB_SLOTS], -1 = free
+    HubCounts *counts;                          // clear on entry, as are the keys
+    uint32_t *keys;                             // [HUB_SLOTS]: node + 1, 0 = free
     HubRow *rows;                               // [HUB_SLOTS]
     int32_t *list;                              // [HUB_SLOTS]: the slots in use
-    HubJob *jobs;
-    uint32_t max_jobs;
-    HubCounts *counts;
 };
-// Makes frontier position i, node v, a hub job; false: no place left.
-__device__ __forceinline__ bool add_hub_job(const HubTable &h, int64_t i, int32_t v, int64_t begin, int64_t deg, int64_t n_nodes)
+__device__ __forceinline__ uint32_t first_hub_slot(uint32_t v)
 {
-    uint32_t slot = ((uint32_t)v * 0x9E3779B1u) >> 20;
     static_assert(HUB_SLOTS == 1 << 12, "twelve bits of hash");
-    bool found = false;
-    for (int t = 0; t < HUB_PROBES && !found; ++t) {
-        int32_t have = h.keys[slot];
-        if (have != v && have == -1) {
-            have = atomicCAS(&h.keys[slot], -1, v);
-            if (have == -1) {                   // this thread's: the row is described once
+    return (v * 0x9E3779B1u) >> 20;
+}
+// Gives node v's row an entry, if it has none yet; false: no place left.
+__device__ __forceinline__ bool add_hub_row(const HubTable &h, uint32_t v, int64_t begin, int64_t deg, int64_t n_nodes)
+{
+    uint32_t slot = first_hub_slot(v);
+    for (int t = 0; t < HUB_PROBES; ++t) {
+        uint32_t have = h.keys[slot];
+        if (have == 0u) {
+            have = atomicCAS(&h.keys[slot], 0u, v + 1u);
+            if (have == 0u) {                   // this thread's: the row is described once
                 int32_t shift = 0;
                 while (shift < HUB_MAX_SHIFT && (n_nodes >> shift) > deg / 4) ++shift;         // 4 to 8 IDs per bucket on average
                 const int64_t buckets = ((n_nodes - 1) >> shift) + 1;
-                h.rows[slot] = HubRow{begin, atomicAdd(&h.counts->buckets, (unsigned long long)buckets), (int32_t)deg, shift, 0, 0};
+                h.rows[slot] = HubRow{begin, atomicAdd(&h.counts->buckets, (unsigned long long)buckets), (int32_t)deg, shift};
                 h.list[atomicAdd(&h.counts->n_rows, 1u)] = (int32_t)slot;
-                have = v;
+                return true;
             }
         }
-        if (have == v) found = true;
-        else slot = (slot + 1) & (HUB_SLOTS - 1);
+        if (have == v + 1u) return true;
+        slot = (slot + 1) & (HUB_SLOTS - 1);
     }
-    if (!found) return false;
-    const uint32_t j = atomicAdd(&h.counts->n_jobs, 1u);
-    if (j >= h.max_jobs) return false;
-    h.jobs[j] = HubJob{i, (int32_t)slot, 0};
-    return true;
+    return false;
 }
 
 // Also adds up, over the frontier, what the hop will read of the adjacency: [0] the sum of the degrees (in IDs),
 // [1] the part of it in rows of up to BIG_ROW IDs (the rows that are not sampled as tiles), [2] the number of rows of
-// 1 .. SHORT_ROW IDs and [3] the IDs in them.  The sums are spread over DEG_SUM_SLOTS sets of four counters,
-// total[4 * slot + k], which the host adds up: thousands of workgroups adding to one address would queue up behind
-// each other.
+// 1 .. SHORT_ROW IDs and [3] the IDs in them; of flagged hub rows, [4] how many and [5] how many tiles they make.  The
+// sums are spread over DEG_SUM_SLOTS sets of counters, total[DEG_SUMS * slot + k], which the host adds up: thousands of
+// workgroups adding to one address would queue up behind each other.
 constexpr int DEG_SUM_SLOTS = 64;
-constexpr int DEG_SUMS = 4;
+constexpr int DEG_SUMS = 6;
 constexpr int SHORT_ROW = 64;            // rows of up to this many IDs are sampled four at a time, sixteen lanes each
 
 // Bound by its bytes (a random 16-byte read of indptr and 28 bytes written per node), so a workgroup takes NODE_CHUNK
 // consecutive positions, whose batch and hop stream it looks up once, and a thread has four nodes' reads in flight.
-// How many IDs each node will sample and how many tile jobs its row makes go into one word, count[i] = samples |
-// tiles << 12, and the chunk's sums of both into chunk_sum (tiles in the upper half): two prefix sums over the nodes
-// become one scan of the chunks and one pass (24.8 M nodes of an epoch's three hops, with their prefix sums: 980 us as two
-// separate scans, 600 so).
+// How many IDs each node will sample, how many tile jobs its row makes and whether it is a hub row go into one word,
+// count[i] = samples | tiles << 12 | hub << 31, and the chunk's sums of samples and tiles into chunk_sum (tiles in the
+// upper half; those of hub rows apart, into chunk_hub): two prefix sums over the nodes become one scan of the chunks and
+// one pass (24.8 M nodes of an epoch's three hops, with their prefix sums: 980 us as two separate scans, 600 so).
+// HUBS: rows from hubs.min_deg on are looked for (an instantiation of its own, with two sums more).
 constexpr int NODE_THREADS = 256;
 constexpr int NODE_PER_THREAD = 4;
 constexpr int NODE_CHUNK = NODE_THREADS * NODE_PER_THREAD;
 constexpr uint32_t COUNT_BITS = 12;      // samples: at most RG_MAX_FANOUT; tiles: at most 2^31 / TILE_PIECE = 2^15
-static_assert(RG_MAX_FANOUT < (1u << COUNT_BITS) && (((uint64_t)1 << 31) / TILE_PIECE) < (1u << (32 - COUNT_BITS)), "");
+constexpr uint32_t HUB_FLAG = 1u << 31;
+static_assert(RG_MAX_FANOUT < (1u << COUNT_BITS) && (((uint64_t)1 << 31) / TILE_PIECE) < (1u << (31 - COUNT_BITS)), "");
 __device__ __forceinline__ uint32_t samples_of(uint32_t count) { return count & ((1u << COUNT_BITS) - 1u); }
-__device__ __forceinline__ uint32_t tiles_in(uint32_t count) { return count >> COUNT_BITS; }
+// The tile jobs of a node's row among those of the rows asked for.
+enum { TILES_OF_ROWS = 1, TILES_OF_HUB_ROWS = 2 };
+__device__ __forceinline__ uint32_t tiles_in(uint32_t count, int which)
+{
+    return (which & ((count & HUB_FLAG) ? TILES_OF_HUB_ROWS : TILES_OF_ROWS)) ? (count & ~HUB_FLAG) >> COUNT_BITS : 0u;
+}
 
+template <bool HUBS>
 __global__ void __launch_bounds__(NODE_THREADS) node_records_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ frontier, int64_t n,
                                                                     const int64_t *__restrict__ batch_off, uint32_t n_batches, const uint64_t *__restrict__ batch_seed,
                                                                     uint32_t hop, uint32_t fanout, NodeRecs r, uint32_t *__restrict__ count,
-                                                                    unsigned long long *__restrict__ chunk_sum, int64_t n_nodes,
+                                                                    unsigned long long *__restrict__ chunk_sum, uint32_t *__restrict__ chunk_hub /* HUBS */, int64_t n_nodes,
                                                                     unsigned long long *__restrict__ total, HubTable hubs)
 {
-    __shared__ unsigned long long part[DEG_SUMS + 1][NODE_THREADS / 64];
-    unsigned long long acc[DEG_SUMS + 1] = {0, 0, 0, 0, 0};       // see above; and the chunk's sums
+    constexpr int SUMS = HUBS ? DEG_SUMS : DEG_SUMS - 2;
+    __shared__ unsigned long long part[SUMS + 1][NODE_THREADS / 64];
+    unsigned long long acc[SUMS + 1] = {};       // see above; and the chunk's sums
     const int64_t base = (int64_t)blockIdx.x * NODE_CHUNK;
     int32_t v[NODE_PER_THREAD];
     int64_t b0[NODE_PER_THREAD], deg[NODE_PER_THREAD];
@@ -190,31 +194,34 @@ __global__ void __launch_bounds__(NODE_THREADS) node_records_kernel(const int64_
         r.batch[i] = b;
         r.state[i] = combine(stream, (uint64_t)(uint32_t)v[k]);
         const uint32_t samples = (uint32_t)(d < (int64_t)fanout ? d : (int64_t)fanout);
-        const uint32_t tiles = hubs.keys && d >= hubs.min_deg && add_hub_job(hubs, i, v[k], b0[k], d, n_nodes) ? 0u : (uint32_t)tiles_of(d);
-        count[i] = samples | tiles << COUNT_BITS;
+        const uint32_t tiles = (uint32_t)tiles_of(d);
+        const bool hub = HUBS && d >= hubs.min_deg && add_hub_row(hubs, (uint32_t)v[k], b0[k], d, n_nodes);
+        count[i] = samples | tiles << COUNT_BITS | (hub ? HUB_FLAG : 0u);
         acc[0] += (unsigned long long)d;
         if (d <= (int64_t)BIG_ROW) acc[1] += (unsigned long long)d;
         if (d > 0 && d <= (int64_t)SHORT_ROW) { acc[2] += 1; acc[3] += (unsigned long long)d; }
-        acc[DEG_SUMS] += (unsigned long long)samples | (unsigned long long)tiles << 32;
+        if (HUBS && hub) { acc[4 % SUMS] += 1; acc[5 % SUMS] += tiles; }
+        acc[SUMS] += (unsigned long long)samples | (unsigned long long)(hub ? 0u : tiles) << 32;
     }
 #pragma unroll
-    for (int k = 0; k <= DEG_SUMS; ++k) {
+    for (int k = 0; k <= SUMS; ++k) {
         for (int o = 32; o > 0; o >>= 1) acc[k] += __shfl_down(acc[k], o, 64);
         if ((threadIdx.x & 63) == 0) part[k][threadIdx.x >> 6] = acc[k];
     }
     __syncthreads();
-    if (threadIdx.x <= DEG_SUMS) {
+    if (threadIdx.x <= SUMS) {
         const unsigned long long a = part[threadIdx.x][0] + part[threadIdx.x][1] + part[threadIdx.x][2] + part[threadIdx.x][3];
-        if (threadIdx.x == DEG_SUMS) chunk_sum[blockIdx.x] = a;
+        if (HUBS && threadIdx.x == 5) chunk_hub[blockIdx.x] = (uint32_t)a;
+        if (threadIdx.x == SUMS) chunk_sum[blockIdx.x] = a;
         else if (a) atomicAdd(total + DEG_SUMS * (blockIdx.x % DEG_SUM_SLOTS) + threadIdx.x, a);
     }
 }
 
 // One workgroup: chunk_sum -> exclusive prefix sums of both halves, samples and tiles in front of each chunk, with the
-// totals behind the last; the total of the samples also to *samp_end.
+// totals behind the last; the total of the samples also to *samp_end.  chunk_hub (or NULL): tiles that count with the others.
 constexpr int CHUNK_SCAN_THREADS = 1024;
 constexpr int CHUNK_SCAN_PER_THREAD = 8;
-__global__ void __launch_bounds__(CHUNK_SCAN_THREADS) scan_chunks_kernel(const unsigned long long *__restrict__ chunk_sum, int64_t n_chunks,
+__global__ void __launch_bounds__(CHUNK_SCAN_THREADS) scan_chunks_kernel(const unsigned long long *__restrict__ chunk_sum, const uint32_t *__restrict__ chunk_hub, int64_t n_chunks,
                                                                          int64_t *__restrict__ samp_base, int64_t *__restrict__ tile_base, int64_t *__restrict__ samp_end)
 {
     __shared__ int64_t wave_sum[2][CHUNK_SCAN_THREADS / 64];
@@ -225,7 +232,7 @@ __global__ void __launch_bounds__(CHUNK_SCAN_THREADS) scan_chunks_kernel(const u
         unsigned long long x[CHUNK_SCAN_PER_THREAD];
         int64_t mine[2] = {0, 0};
 #pragma unroll
-        for (int k = 0; k < CHUNK_SCAN_PER_THREAD; ++k) x[k] = first + k < n_chunks ? chunk_sum[first + k] : 0ull;
+        for (int k = 0; k < CHUNK_SCAN_PER_THREAD; ++k) x[k] = first + k < n_chunks ? chunk_sum[first + k] + (chunk_hub ? (unsigned long long)chunk_hub[first + k] << 32 : 0ull) : 0ull;
 #pragma unroll
         for (int k = 0; k < CHUNK_SCAN_PER_THREAD; ++k) { mine[0] += (int64_t)(uint32_t)x[k]; mine[1] += (int64_t)(x[k] >> 32); }
         int64_t run[2];
@@ -965,18 +972,20 @@ struct TileRecs {
     int32_t *len;
     uint64_t *state;
 };
-// The tile jobs of a chunk's nodes, in frontier order.
-__global__ void __launch_bounds__(NODE_THREADS) tile_nodes_kernel(const uint32_t *__restrict__ count, int64_t n, const int64_t *__restrict__ tile_base, TileRecs r)
+// The tile jobs of a chunk's nodes, in frontier order; which: see tiles_in.
+__global__ void __launch_bounds__(NODE_THREADS) tile_nodes_kernel(const uint32_t *__restrict__ count, int64_t n, const int64_t *__restrict__ tile_base, int which, TileRecs r)
 {
     const int64_t base = tile_base[blockIdx.x];
     if (tile_base[blockIdx.x + 1] == base) return;
     const int64_t first = (int64_t)blockIdx.x * NODE_CHUNK + (int64_t)threadIdx.x * NODE_PER_THREAD;
-    uint32_t c[NODE_PER_THREAD];
+    uint32_t c[NODE_PER_THREAD], tiles[NODE_PER_THREAD];
     load_counts(count, first, n, c);
-    int64_t j = base + (int64_t)chunk_exclusive_scan(tiles_in(c[0]) + tiles_in(c[1]) + tiles_in(c[2]) + tiles_in(c[3]));
+#pragma unroll
+    for (int k = 0; k < NODE_PER_THREAD; ++k) tiles[k] = tiles_in(c[k], which);
+    int64_t j = base + (int64_t)chunk_exclusive_scan(tiles[0] + tiles[1] + tiles[2] + tiles[3]);
 #pragma unroll
     for (int k = 0; k < NODE_PER_THREAD; ++k)
-        for (uint32_t t = 0; t < tiles_in(c[k]); ++t, ++j) { r.node[j] = first + k; r.t[j] = (int32_t)t; }
+        for (uint32_t t = 0; t < tiles[k]; ++t, ++j) { r.node[j] = first + k; r.t[j] = (int32_t)t; }
 }
 // One thread per tile job.
 __global__ void tile_records_kernel(const int64_t *__restrict__ row_begin, const int32_t *__restrict__ deg, const uint64_t *__restrict__ state, int64_t n_tiles, TileRecs r)
@@ -1240,7 +1249,26 @@ __global__ void __launch_bounds__(256) hub_table_kernel(const int32_t *__restric
         if (u >= n || (i > 0 && before >= u)) damaged = true;
         else if (rank < HUB_BUCKET) mine[b].id[rank] = (uint16_t)(u & ((1u << r.shift) - 1u));
     }
-    if (damaged) h.rows[slot].damaged = 1;
+    if (damaged) h.counts->damaged = 1u;
+}
+
+// A job for every frontier position that holds a hub row, in whatever order they arrive (a job's samples go to the
+// position's own place).
+__global__ void __launch_bounds__(NODE_THREADS) hub_jobs_kernel(const uint32_t *__restrict__ count, const int32_t *__restrict__ frontier, int64_t n,
+                                                                const uint32_t *__restrict__ chunk_hub, HubTable h, HubJob *__restrict__ jobs)
+{
+    if (chunk_hub[blockIdx.x] == 0u) return;
+    const int64_t first = (int64_t)blockIdx.x * NODE_CHUNK + (int64_t)threadIdx.x * NODE_PER_THREAD;
+    uint32_t c[NODE_PER_THREAD];
+    load_counts(count, first, n, c);
+#pragma unroll
+    for (int k = 0; k < NODE_PER_THREAD; ++k) {
+        if (!(c[k] & HUB_FLAG)) continue;
+        const uint32_t v = (uint32_t)frontier[first + k];
+        uint32_t slot = first_hub_slot(v);
+        for (int t = 0; t < HUB_PROBES && h.keys[slot] != v + 1u; ++t) slot = (slot + 1) & (HUB_SLOTS - 1);
+        jobs[atomicAdd(&h.counts->n_jobs, 1u)] = HubJob{first + k, (int32_t)slot, 0};
+    }
 }
 
 // Whether the row (ascending) holds u < n_nodes.
@@ -1269,9 +1297,11 @@ __device__ __forceinline__ bool hub_holds(const HubBucket *__restrict__ mine, co
 struct HubArgs {
     const int32_t *indices;
     int64_t n_nodes;
-    HubTable h;
-    const HubBucket *buckets;                   // NULL: no tables, every row is read
+    const HubRow *rows;
+    const HubBucket *buckets;
+    const HubJob *jobs;
     uint32_t n_jobs;
+    float first_range;                          // of the guessed range of key values, how much is looked through first (1; for tests)
     NodeRecs rec;
     uint32_t fanout;
     const int64_t *samp_off; int32_t *samp_nbr;
@@ -1280,13 +1310,13 @@ struct HubArgs {
 
 constexpr int HUB_THREADS = 256;
 constexpr int HUB_WAVES = HUB_THREADS / 64;
-constexpr int HUB_HITS = 1024;                  // the guess lets 515 through at the largest fan-out; 19 KB of LDS, so that eight workgroups of a compute unit wait for their lookups together
+constexpr int HUB_HITS = 1024;                  // the guess lets 515 through at the largest fan-out; 15 KB of LDS, so that eight workgroups of a compute unit wait for their lookups together
 constexpr int HUB_QUEUE = 64 + 4 * 64;          // a wave's IDs waiting to be looked up: fewer than 64 left over, and a step's four per lane
 
 template <int MARK>
 __global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
 {
-    __shared__ uint32_t hit_key[HUB_HITS], hit_id[HUB_HITS], hit_at[HUB_HITS];      // hit_at: the row order (the ID itself where the row ascends)
+    __shared__ uint32_t hit_key[HUB_HITS], hit_id[HUB_HITS];
     __shared__ uint8_t hit_taken[HUB_HITS];
     __shared__ uint32_t queue[HUB_WAVES][HUB_QUEUE];                                // keys of IDs below n_nodes
     __shared__ uint32_t n_hits;
@@ -1294,67 +1324,59 @@ __global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
     const int f = (int)a.fanout;
     const uint32_t n = (uint32_t)a.n_nodes;
     for (uint32_t j = blockIdx.x; j < a.n_jobs; j += gridDim.x) {
-        const HubJob job = a.h.jobs[j];
-        const HubRow r = a.h.rows[job.slot];
+        const HubJob job = a.jobs[j];
+        const HubRow r = a.rows[job.slot];
         const int32_t *row = a.indices + r.begin;
-        const HubBucket *mine = a.buckets ? a.buckets + r.first : nullptr;
+        const HubBucket *mine = a.buckets + r.first;
         const uint64_t S = a.rec.state[job.i];
         const uint32_t lo = uni((uint32_t)S), hi = uni((uint32_t)(S >> 32));
-        uint64_t from = 0, to = (uint64_t)(guessed_candidates(f) / (float)r.deg * 4294967296.0f) + 1;     // key values [from, to)
+        uint64_t from = 0, to = (uint64_t)fminf(guessed_candidates(f) / (float)r.deg * a.first_range * 4294967296.0f, 4294967296.0f) + 1;     // key values [from, to)
         uint32_t kept = 0;                                       // hits with keys below `from` (fewer than f)
         for (;;) {
             if (to > ((uint64_t)1 << 32)) to = (uint64_t)1 << 32;
             __syncthreads();                                     // the hits of the job before, or of the round before, have been read
             if (threadIdx.x == 0) n_hits = kept;
             __syncthreads();
-            auto add_hit = [&](uint32_t key, uint32_t id, uint32_t at) {
-                const uint32_t k = atomicAdd(&n_hits, 1u);
-                if (k < HUB_HITS) { hit_key[k] = key; hit_id[k] = id; hit_at[k] = at; }
+            int waiting = 0;                                     // in this wave's queue (the same in all its lanes)
+            auto look_up = [&](int count) {                      // the queue's last `count` <= 64 entries
+                if (lane < count) {
+                    const uint32_t key = queue[wave][waiting - count + lane], u = key32_inverse(lo, hi, key);
+                    if (hub_holds(mine, r, row, u)) {
+                        const uint32_t k = atomicAdd(&n_hits, 1u);
+                        if (k < HUB_HITS) { hit_key[k] = key; hit_id[k] = u; }
+                    }
+                }
+                waiting -= count;
             };
-            if (!r.damaged && a.buckets) {
-                int waiting = 0;                                 // in this wave's queue (the same in all its lanes)
-                auto look_up = [&](int count) {                  // the queue's last `count` <= 64 entries
-                    if (lane < count) {
-                        const uint32_t key = queue[wave][waiting - count + lane], u = key32_inverse(lo, hi, key);
-                        if (hub_holds(mine, r, row, u)) add_hit(key, u, u);
-                    }
-                    waiting -= count;
-                };
-                for (uint64_t base = from + (uint64_t)wave * 256; base < to; base += HUB_THREADS * 4) {
-                    const uint32_t left = (uint32_t)(to - base < 256 ? to - base : 256);
+            for (uint64_t base = from + (uint64_t)wave * 256; base < to; base += HUB_THREADS * 4) {
+                const uint32_t left = (uint32_t)(to - base < 256 ? to - base : 256);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t at = (uint32_t)(64 * e + lane), key = (uint32_t)base + at;
-                        const unsigned long long m = ballot64(key32_inverse(lo, hi, key) < n && at < left);
-                        if (my_bit(m)) queue[wave][waiting + lanes_below(m, lane)] = key;
-                        waiting += __popcll(m);
-                    }
-                    waiting = uni(waiting);
-                    __builtin_amdgcn_wave_barrier();             // (one wave's LDS operations are done in order)
-                    while (waiting >= 64) look_up(64);
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t at = (uint32_t)(64 * e + lane), key = (uint32_t)base + at;
+                    const unsigned long long m = ballot64(key32_inverse(lo, hi, key) < n && at < left);
+                    if (my_bit(m)) queue[wave][waiting + lanes_below(m, lane)] = key;
+                    waiting += __popcll(m);
                 }
-                if (waiting > 0) look_up(waiting);
-            } else {
-                for (int64_t p = threadIdx.x; p < r.deg; p += HUB_THREADS) {         // a row that is not in order, or without a table: read as it is
-                    const uint32_t u = (uint32_t)row[p], key = key32(lo, hi, u);
-                    if (key >= from && key < to) add_hit(key, u, (uint32_t)p);
-                }
+                waiting = uni(waiting);
+                __builtin_amdgcn_wave_barrier();                 // (one wave's LDS operations are done in order)
+                while (waiting >= 64) look_up(64);
             }
+            if (waiting > 0) look_up(waiting);
             __syncthreads();
             const uint32_t found = n_hits;
-            if (found > HUB_HITS && to - from > 1) { to = from + (to - from) / 2; continue; }        // too many for the list: a smaller range (the hits kept so far stay)
+            if (found > HUB_HITS) { to = from + (to - from) / 2; continue; }        // too many for the list: a smaller range (the hits kept so far stay; a single key value is one hit at most)
             if (found >= (uint32_t)f || to == ((uint64_t)1 << 32)) break;
             kept = found;
             const uint64_t step = 2 * (to - from);               // too few: the next key values, twice as many
             from = to;
             to += step;
         }
-        // the f smallest keys, in row order
-        const int c = n_hits < HUB_HITS ? (int)n_hits : HUB_HITS;
+        // the f smallest keys, in row order: the row ascends, so in the order of the IDs
+        const int c = (int)n_hits;
         for (int k = threadIdx.x; k < c; k += HUB_THREADS) {
-            const uint32_t key = hit_key[k], at = hit_at[k];
+            const uint32_t key = hit_key[k];
             int smaller = 0;
-            for (int q = 0; q < c; ++q) smaller += hit_key[q] < key || (hit_key[q] == key && hit_at[q] < at) ? 1 : 0;
+            for (int q = 0; q < c; ++q) smaller += hit_key[q] < key ? 1 : 0;
             hit_taken[k] = smaller < f ? 1 : 0;
         }
         __syncthreads();
@@ -1362,11 +1384,11 @@ __global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
         const ReachedOfBatch reached_b = reached_of<MARK>(a.reached, a.rec.batch[job.i]);
         for (int k = threadIdx.x; k < c; k += HUB_THREADS) {
             if (!hit_taken[k]) continue;
-            const uint32_t at = hit_at[k];
+            const uint32_t id = hit_id[k];
             int in_front = 0;
-            for (int q = 0; q < c; ++q) in_front += hit_taken[q] && hit_at[q] < at ? 1 : 0;
-            out[in_front] = (int32_t)hit_id[k];
-            mark_reached<MARK>(reached_b, hit_id[k]);
+            for (int q = 0; q < c; ++q) in_front += hit_taken[q] && hit_id[q] < id ? 1 : 0;
+            out[in_front] = (int32_t)id;
+            mark_reached<MARK>(reached_b, id);
         }
     }
 }
@@ -1382,6 +1404,15 @@ static double hub_line(int64_t n_nodes, uint32_t fanout)
     const double per_value = 1.6 + 20.0 * (double)n_nodes / 4294967296.0;
     return 2.0 * std::sqrt(per_value * lambda * 4294967296.0);
 }
+
+// How many tile jobs the hub rows must make, per compute unit, to be worth their tables: clearing and building those and a
+// wait for the rows' order cost 70 to 130 us (2 to 28 M distinct IDs), a tile job 17 ns.  Shares of 15 to 100 M nodes,
+// schedule with hub jobs against without: 387 to 3,480 tiles 31 to 129 us slower, 4,215 14 faster, 5,600 87, 6,525 40,
+// 7,654 67, 10,578 96, 21,835 289, 68,334 1,040.
+constexpr int HUB_TILES_PER_CU = 24;
+// Epochs of fewer batches seldom hold so many (the 100 M nodes, 15 batches of 2,048 seeds: 6,525), and looking for them costs
+// some 10 us a hop.
+constexpr uint32_t HUB_BATCHES = 16;
 
 // Every workgroup of the sampling launch must be resident from the start (tiles are dealt out by workgroup index), so
 // the grid is what the chip holds of this kernel, or the amount of work if that is less.
@@ -1529,7 +1560,18 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
 {
     const int64_t n_cur = cur.off_host[beta];
     const int64_t n_chunks = (n_cur + NODE_CHUNK - 1) / NODE_CHUNK;
-    uint32_t *count = nullptr;
+    // Hub rows (see hub_sample_kernel): where the table of a row is shared by the batches of an epoch -- behind the seeds,
+    // which hold a node once.
+    HubTable hubs{INT32_MAX, nullptr, nullptr, nullptr, nullptr};
+    const char *forced_line = getenv("RAPIDGNN_HUB_ROWS");                            // same results either way; for tests and tuning
+    {
+        double line = hop > 0 && beta >= HUB_BATCHES ? hub_line(g->n_nodes, fanout) : 2147483647.0;
+        if (forced_line) line = std::max(atof(forced_line), 4.0 * RG_MAX_FANOUT);
+        if (sampler == RG_SAMPLER_KEYS && fanout > 0 && fanout <= HUB_MAX_FANOUT && line <= (double)g->n_nodes)
+            hubs.min_deg = std::max((int32_t)std::min(line, 2147483647.0), BIG_ROW + 1);
+    }
+    const bool look_for_hubs = hubs.min_deg != INT32_MAX;
+    uint32_t *count = nullptr, *chunk_hub = nullptr;
     unsigned long long *chunk_sum = nullptr;
     int64_t *samp_base = nullptr, *tile_base = nullptr;
     NodeRecs rec{nullptr, nullptr, nullptr, nullptr};
@@ -1542,44 +1584,39 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     RG_TRY(tmp.dev_n<uint32_t>((uint64_t)n_cur, &rec.batch));
     RG_TRY(tmp.dev_n<uint64_t>((uint64_t)n_cur, &rec.state));
     RG_TRY(keep.dev_n<int64_t>((uint64_t)n_cur + 1, &cur.samp_off));
-    unsigned long long sums[DEG_SUMS] = {0, 0, 0, 0}, *sum_deg_dev = nullptr;       // see node_records_kernel
+    unsigned long long sums[DEG_SUMS] = {}, *sum_deg_dev = nullptr;       // see node_records_kernel
     unsigned long long sum_parts[DEG_SUMS * DEG_SUM_SLOTS];
-    RG_TRY(tmp.dev_n<unsigned long long>(DEG_SUMS * DEG_SUM_SLOTS, &sum_deg_dev));
-    RG_HIP(hipMemsetAsync(sum_deg_dev, 0, sizeof(sum_parts), st));
-    // Hub rows (see hub_sample_kernel): where the directory of a row is shared by the batches of an epoch -- behind the seeds,
-    // which hold a node once.
-    HubTable hubs{INT32_MAX, nullptr, nullptr, nullptr, nullptr, 0, nullptr};
-    HubCounts hub_counts{0, 0, 0};
-    {
-        double line = hop > 0 && beta >= 8 ? hub_line(g->n_nodes, fanout) : 2147483647.0;
-        if (const char *force = getenv("RAPIDGNN_HUB_ROWS")) line = std::max(atof(force), 4.0 * RG_MAX_FANOUT);      // same results either way; for tests and tuning
-        if (sampler == RG_SAMPLER_KEYS && fanout > 0 && fanout <= HUB_MAX_FANOUT && line <= (double)g->n_nodes) {
-            hubs.min_deg = std::max((int32_t)std::min(line, 2147483647.0), BIG_ROW + 1);
-            hubs.max_jobs = (uint32_t)std::min<int64_t>(n_cur, HUB_MAX_JOBS);
-            RG_TRY(tmp.dev_n<int32_t>(HUB_SLOTS, &hubs.keys));
-            RG_TRY(tmp.dev_n<HubRow>(HUB_SLOTS, &hubs.rows));
-            RG_TRY(tmp.dev_n<int32_t>(HUB_SLOTS, &hubs.list));
-            RG_TRY(tmp.dev_n<HubJob>(hubs.max_jobs, &hubs.jobs));
-            RG_TRY(tmp.dev_n<HubCounts>(1, &hubs.counts));
-            RG_HIP(hipMemsetAsync(hubs.keys, 0xFF, HUB_SLOTS * sizeof(int32_t), st));
-            RG_HIP(hipMemsetAsync(hubs.counts, 0, sizeof(HubCounts), st));
-        }
+    const size_t hub_cleared = look_for_hubs ? sizeof(HubCounts) + HUB_SLOTS * sizeof(uint32_t) : 0;      // behind the sums, cleared with them
+    RG_TRY(tmp.dev(sizeof(sum_parts) + hub_cleared, (void **)&sum_deg_dev));
+    RG_HIP(hipMemsetAsync(sum_deg_dev, 0, sizeof(sum_parts) + hub_cleared, st));
+    if (look_for_hubs) {
+        hubs.counts = reinterpret_cast<HubCounts *>(sum_deg_dev + DEG_SUMS * DEG_SUM_SLOTS);
+        hubs.keys = reinterpret_cast<uint32_t *>(hubs.counts + 1);
+        RG_TRY(tmp.dev(HUB_SLOTS * (sizeof(HubRow) + sizeof(int32_t)), (void **)&hubs.rows));
+        hubs.list = reinterpret_cast<int32_t *>(hubs.rows + HUB_SLOTS);
+        RG_TRY(tmp.dev_n<uint32_t>((uint64_t)n_chunks, &chunk_hub));
     }
     {
         ScopedTimer tm(KG_OFFSETS, st);
-        hipLaunchKernelGGL(node_records_kernel, dim3((unsigned)n_chunks), dim3(NODE_THREADS), 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta,
-                           batch_seed, hop, fanout, rec, count, chunk_sum, (int64_t)g->n_nodes, sum_deg_dev, hubs);
-        hipLaunchKernelGGL(scan_chunks_kernel, dim3(1), dim3(CHUNK_SCAN_THREADS), 0, st, chunk_sum, n_chunks, samp_base, tile_base, cur.samp_off + n_cur);
-        hipLaunchKernelGGL(sample_offsets_kernel, dim3((unsigned)n_chunks), dim3(NODE_THREADS), 0, st, count, n_cur, samp_base, cur.samp_off);
+        const dim3 grid((unsigned)n_chunks), block(NODE_THREADS);
+        if (look_for_hubs)
+            hipLaunchKernelGGL(node_records_kernel<true>, grid, block, 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta, batch_seed, hop, fanout, rec, count, chunk_sum,
+                               chunk_hub, (int64_t)g->n_nodes, sum_deg_dev, hubs);
+        else
+            hipLaunchKernelGGL(node_records_kernel<false>, grid, block, 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta, batch_seed, hop, fanout, rec, count, chunk_sum,
+                               chunk_hub, (int64_t)g->n_nodes, sum_deg_dev, hubs);
+        hipLaunchKernelGGL(scan_chunks_kernel, dim3(1), dim3(CHUNK_SCAN_THREADS), 0, st, chunk_sum, (const uint32_t *)nullptr, n_chunks, samp_base, tile_base, cur.samp_off + n_cur);
+        hipLaunchKernelGGL(sample_offsets_kernel, grid, block, 0, st, count, n_cur, samp_base, cur.samp_off);
         RG_HIP(hipGetLastError());
     }
-    int64_t n_tiles = 0;
+    int64_t n_tiles = 0;                          // of the rows that are no hub rows, at first
+    HubCounts hub_counts{};
     {
         Readback rb(st);
         RG_TRY(rb.add(sum_parts, sum_deg_dev, sizeof(sum_parts)));
         RG_TRY(rb.add(&cur.n_samples, cur.samp_off + n_cur, sizeof(int64_t)));
         RG_TRY(rb.add(&n_tiles, tile_base + n_chunks, sizeof(int64_t)));
-        if (hubs.counts) RG_TRY(rb.add(&hub_counts, hubs.counts, sizeof(hub_counts)));
+        if (look_for_hubs) RG_TRY(rb.add(&hub_counts, hubs.counts, sizeof(hub_counts)));
         if (also_read_dev) RG_TRY(rb.add(also_read_host, also_read_dev, sizeof(unsigned long long)));     // a value the caller wants behind the same wait
         RG_TRY(rb.wait());
         for (int k = 0; k < DEG_SUM_SLOTS; ++k)
@@ -1605,6 +1642,34 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         }
         return RG_OK;
     }
+    // The hub rows: as jobs of hub_sample_kernel where that saves more than it costs, the tables and jobs find memory and the
+    // rows turn out to be in order; else as tile jobs like the other long rows.
+    const uint64_t n_hub_jobs = sums[4], n_hub_tiles = sums[5];
+    HubBucket *buckets = nullptr;
+    HubJob *jobs = nullptr;
+    bool hub_jobs = n_hub_jobs > 0 && n_hub_jobs <= 0x7FFFFFFFull && (forced_line || n_hub_tiles >= (uint64_t)HUB_TILES_PER_CU * n_cu) &&
+                    tmp.dev_spare(hub_counts.buckets * sizeof(HubBucket), (void **)&buckets) && tmp.dev_spare(n_hub_jobs * sizeof(HubJob), (void **)&jobs);
+    if (hub_jobs) {
+        {
+            ScopedTimer tm(KG_SAMPLER, st);
+            RG_HIP(hipMemsetAsync(buckets, 0xFF, hub_counts.buckets * sizeof(HubBucket), st));
+            const uint32_t per_row = std::max<uint32_t>(64, std::min<uint32_t>(1024, 64u * (uint32_t)n_cu / hub_counts.n_rows));       // few rows, long ones: the workgroups of the chip shared out among them
+            hipLaunchKernelGGL(hub_table_kernel, dim3(per_row, hub_counts.n_rows), dim3(256), 0, st, g->indices, g->n_nodes, hubs, buckets);
+            hipLaunchKernelGGL(hub_jobs_kernel, dim3((unsigned)n_chunks), dim3(NODE_THREADS), 0, st, count, cur.ids, n_cur, chunk_hub, hubs, jobs);
+            RG_HIP(hipGetLastError());
+        }
+        Readback rb(st);
+        RG_TRY(rb.add(&hub_counts, hubs.counts, sizeof(hub_counts)));
+        RG_TRY(rb.wait());
+        hub_jobs = hub_counts.damaged == 0;
+    }
+    if (!hub_jobs && n_hub_jobs > 0) {        // the tiles in front of each chunk once more, with those of the hub rows
+        tmp.free_one(buckets);                // (the host has waited for what read them)
+        tmp.free_one(jobs);
+        n_tiles += (int64_t)n_hub_tiles;
+        ScopedTimer tm(KG_OFFSETS, st);
+        hipLaunchKernelGGL(scan_chunks_kernel, dim3(1), dim3(CHUNK_SCAN_THREADS), 0, st, chunk_sum, chunk_hub, n_chunks, samp_base, tile_base, cur.samp_off + n_cur);
+    }
     if (fanout == 0) n_tiles = 0;             // nothing is drawn; every sample is empty
     int32_t *tile_out = nullptr;
     TileRecs tile{nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -1616,7 +1681,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     RG_TRY(tmp.dev_n<uint64_t>((uint64_t)n_tiles, &tile.state));
     if (n_tiles > 0) {
         ScopedTimer tm(KG_OFFSETS, st);
-        hipLaunchKernelGGL(tile_nodes_kernel, dim3((unsigned)n_chunks), dim3(NODE_THREADS), 0, st, count, n_cur, tile_base, tile);
+        hipLaunchKernelGGL(tile_nodes_kernel, dim3((unsigned)n_chunks), dim3(NODE_THREADS), 0, st, count, n_cur, tile_base, hub_jobs ? TILES_OF_ROWS : TILES_OF_ROWS | TILES_OF_HUB_ROWS, tile);
         hipLaunchKernelGGL(tile_records_kernel, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, st, rec.row_begin, rec.deg, rec.state, n_tiles, tile);
     }
     int32_t *tile_order = nullptr;
@@ -1656,16 +1721,10 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         const unsigned merge_grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_tiles + merge_span - 1) / merge_span, (int64_t)n_cu * 64));
         HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_rows ? SHORT_ROW : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work};
         ScopedTimer tm(KG_SAMPLER, st);
-        if (const uint32_t n_jobs = std::min(hub_counts.n_jobs, hubs.max_jobs)) {
-            // (no memory for the tables: the rows are read instead, as rows out of order are; the build needs no more than it did)
-            HubBucket *buckets = nullptr;
-            const bool tables = tmp.dev_n<HubBucket>(hub_counts.buckets, &buckets) == RG_OK;
-            if (!tables) buckets = nullptr;
-            if (tables) RG_HIP(hipMemsetAsync(buckets, 0xFF, hub_counts.buckets * sizeof(HubBucket), st));
-            const uint32_t per_row = std::max<uint32_t>(64, std::min<uint32_t>(1024, 64u * (uint32_t)n_cu / hub_counts.n_rows));       // few rows, long ones: the workgroups of the chip shared out among them
-            if (tables) hipLaunchKernelGGL(hub_table_kernel, dim3(per_row, hub_counts.n_rows), dim3(256), 0, st, g->indices, g->n_nodes, hubs, buckets);
-            const HubArgs ha{g->indices, g->n_nodes, hubs, buckets, n_jobs, rec, fanout, cur.samp_off, cur.samp_nbr, reached};
-            const dim3 grid(std::min<uint32_t>(n_jobs, (uint32_t)n_cu * 64)), block(HUB_THREADS);
+        if (hub_jobs) {
+            const char *range = getenv("RAPIDGNN_HUB_RANGE");                         // same results either way; for tests
+            const HubArgs ha{g->indices, g->n_nodes, hubs.rows, buckets, jobs, (uint32_t)n_hub_jobs, range ? std::max((float)atof(range), 0.0f) : 1.0f, rec, fanout, cur.samp_off, cur.samp_nbr, reached};
+            const dim3 grid(std::min<uint32_t>((uint32_t)n_hub_jobs, (uint32_t)n_cu * 64)), block(HUB_THREADS);
             if (inline_marks) hipLaunchKernelGGL(hub_sample_kernel<MARK_BITS>, grid, block, 0, st, ha);
             else hipLaunchKernelGGL(hub_sample_kernel<MARK_NONE>, grid, block, 0, st, ha);
             RG_HIP(hipGetLastError());

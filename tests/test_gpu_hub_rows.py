@@ -1,9 +1,12 @@
 """Hub rows sampled from the keys' side (key values undone and looked up) against the oracle, which reads the rows: rows
-at the shortest length the path takes and below it, fan-outs to the largest it takes and above, rows that are not in
-order, and a graph where the path is taken without being forced."""
+at the shortest length the path takes and below it, fan-outs to the largest it takes and above, first ranges of key values
+that hold too few and too many; and where rows go to the tile jobs instead: out of order, without memory for their tables,
+too few of them."""
 import numpy as np
 import pytest
 import torch
+
+from recording_allocator import RecordingAllocator
 
 pytestmark = pytest.mark.gpu
 
@@ -53,24 +56,63 @@ def check(rg, orc, indptr, indices, train, batch, fanout, allocator=None):
         assert np.array_equal(gso.cpu().numpy(), so) and np.array_equal(gnb.cpu().numpy(), nb), f"samples {hop}"
 
 
+HUB_DEGREES = [16384, 16385, 20011, 65536, 131073, 199_999, 30_000, 150_000]
+
+
+@pytest.mark.parametrize("shuffled", [(), (6, 7)])
 @pytest.mark.parametrize("fanout", [[1, 1], [12, 4], [60, 20], [200, 3], [448], [449]])
-def test_hub_rows_equal_the_oracle(rg, orc, fanout, monkeypatch):
+def test_hub_rows_equal_the_oracle(rg, orc, fanout, shuffled, monkeypatch):
+    """Every row in order: all from 16,385 IDs on are sampled from the keys' side.  Two that are not: the hop's rows are read."""
     monkeypatch.setenv("RAPIDGNN_HUB_ROWS", "16385")
     rng = np.random.default_rng(sum(fanout))
     n = 200_000
-    indptr, indices, hubs = hub_graph(rng, n, [16384, 16385, 20011, 65536, 131073, 199_999, 30_000, 150_000], shuffled=(6, 7))
+    indptr, indices, hubs = hub_graph(rng, n, HUB_DEGREES, shuffled)
     train = np.unique(np.concatenate([hubs, rng.permutation(n)[:300]])).astype(np.int32)
     check(rg, orc, indptr, indices, train, 64, fanout)
 
 
+@pytest.mark.parametrize("first_range", ["0.01", "0.4", "9"])
+@pytest.mark.parametrize("fanout", [[5, 2], [200, 3]])
+def test_first_ranges_that_hold_too_few_or_too_many(rg, orc, fanout, first_range, monkeypatch):
+    """Of the guessed range of key values, a hundredth, less than half and nine times as much: rounds that go on behind what they
+    looked through, and (fan-out 200: 245 expected, 1,024 in the list) ones that start again with half of it."""
+    monkeypatch.setenv("RAPIDGNN_HUB_ROWS", "16385")
+    monkeypatch.setenv("RAPIDGNN_HUB_RANGE", first_range)
+    rng = np.random.default_rng(sum(fanout))
+    n = 200_000
+    indptr, indices, hubs = hub_graph(rng, n, HUB_DEGREES)
+    train = np.unique(np.concatenate([hubs, rng.permutation(n)[:300]])).astype(np.int32)
+    check(rg, orc, indptr, indices, train, 64, fanout)
+
+
+def requested_bytes(rg, monkeypatch, *args, hub_rows=None):
+    if hub_rows:
+        monkeypatch.setenv("RAPIDGNN_HUB_ROWS", hub_rows)
+    else:
+        monkeypatch.delenv("RAPIDGNN_HUB_ROWS", raising=False)
+    a = RecordingAllocator(rg)
+    check(rg, *args, allocator=a.struct)
+    return a.requested
+
+
 @pytest.mark.parametrize("sparse", ["0", "1"])
-def test_hub_rows_without_being_forced(rg, orc, sparse, monkeypatch):
+@pytest.mark.parametrize("n_train,worth_it", [(800, False), (64 * 110, True)])
+def test_hub_rows_without_being_forced(rg, orc, n_train, worth_it, sparse, monkeypatch):
+    """13 batches that share five hub rows make 806 tile jobs of them in a hop, 110 batches 6,820: only those are worth tables
+    (24 tile jobs per compute unit, 256 of them), which the device memory asked for shows."""
     monkeypatch.setenv("RAPIDGNN_SPARSE_FRONTIER", sparse)
     rng = np.random.default_rng(11)
     n = 900_000
-    indptr, indices, hubs = hub_graph(rng, n, [899_999, 880_000, 300_000, 500_000, 600_000])
-    train = rng.permutation(n)[:800].astype(np.int32)
-    check(rg, orc, indptr, indices, train, 64, [3, 2, 5])
+    indptr, indices, hubs = hub_graph(rng, n, [899_999, 880_000, 700_000, 800_000, 600_000])
+    train = rng.permutation(n)[:n_train].astype(np.int32)
+    args = (orc, indptr, indices, train, 64, [3, 2, 5])
+    by_rule = requested_bytes(rg, monkeypatch, *args)
+    never = requested_bytes(rg, monkeypatch, *args, hub_rows="2e9")
+    tables = 5 * 32 * n // 8                                  # per hop: five rows, a bucket of 32 bytes per eight IDs
+    if worth_it:
+        assert by_rule > never + tables
+    else:
+        assert by_rule < never + tables / 10
 
 
 def test_hub_rows_without_memory_for_their_tables(rg, orc, monkeypatch):
