@@ -1552,11 +1552,13 @@ static rg_status launch_mark_pass(const HopData &cur, uint32_t beta, const Reach
 }
 
 // Samples hop `hop` of every batch: fills cur.samp_off / samp_nbr / n_samples and marks the reached-ID bitmaps.
+// tmp: scratch of this hop alone.  hubs_allowed: hub rows may be looked for, *looked_for_hubs: they were, which takes
+// memory that the hop can do without.
 // also_read_dev (or NULL): one more device value copied to *also_read_host behind the hop's own readback; if it
 // comes back non-zero the hop stops there (the caller is about to refuse its input).
 rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint64_t *batch_seed, uint32_t hop, uint32_t fanout,
                      uint32_t sampler, const ReachedMaps &reached, Arena &keep, Arena &tmp, int n_cu,
-                     hipStream_t st, const unsigned long long *also_read_dev, unsigned long long *also_read_host)
+                     hipStream_t st, bool hubs_allowed, bool *looked_for_hubs, const unsigned long long *also_read_dev, unsigned long long *also_read_host)
 {
     const int64_t n_cur = cur.off_host[beta];
     const int64_t n_chunks = (n_cur + NODE_CHUNK - 1) / NODE_CHUNK;
@@ -1564,13 +1566,13 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     // which hold a node once.
     HubTable hubs{INT32_MAX, nullptr, nullptr, nullptr, nullptr};
     const char *forced_line = getenv("RAPIDGNN_HUB_ROWS");                            // same results either way; for tests and tuning
-    {
+    if (hubs_allowed) {
         double line = hop > 0 && beta >= HUB_BATCHES ? hub_line(g->n_nodes, fanout) : 2147483647.0;
         if (forced_line) line = std::max(atof(forced_line), 4.0 * RG_MAX_FANOUT);
         if (sampler == RG_SAMPLER_KEYS && fanout > 0 && fanout <= HUB_MAX_FANOUT && line <= (double)g->n_nodes)
             hubs.min_deg = std::max((int32_t)std::min(line, 2147483647.0), BIG_ROW + 1);
     }
-    const bool look_for_hubs = hubs.min_deg != INT32_MAX;
+    const bool look_for_hubs = *looked_for_hubs = hubs.min_deg != INT32_MAX;
     uint32_t *count = nullptr, *chunk_hub = nullptr;
     unsigned long long *chunk_sum = nullptr;
     int64_t *samp_base = nullptr, *tile_base = nullptr;

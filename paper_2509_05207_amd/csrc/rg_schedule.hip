@@ -20,7 +20,7 @@
 namespace rg {
 
 rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint64_t *batch_seed, uint32_t hop, uint32_t fanout, uint32_t sampler,
-                     const ReachedMaps &reached, Arena &keep, Arena &tmp, int n_cu, hipStream_t st,
+                     const ReachedMaps &reached, Arena &keep, Arena &tmp, int n_cu, hipStream_t st, bool hubs_allowed, bool *looked_for_hubs,
                      const unsigned long long *also_read_dev, unsigned long long *also_read_host);
 
 // ---------------------------------------------------------------- a1/a2: seeds, shuffle keys
@@ -687,28 +687,41 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
         HopData &nxt = s->hop[l + 1];
         const int64_t n_cur = cur.off_host[beta];
 
-        // a3: the samples of this hop; sampled IDs are marked in `reached` as they are written
-        RG_TRY(sample_hop(g, cur, beta, batch_seed, l, fanout[l], sampler, reached, s->arena, tmp, n_cu, st,
-                          l == 0 ? n_bad_train : nullptr, &n_bad_host));
-        if (l == 0) RG_TRY(refuse_bad_train());
+        // The hop up to the sizes of the next frontier.  Its scratch goes back behind the wait for those.
+        auto sample_and_count = [&](bool hubs_allowed, bool *looked_for_hubs) -> rg_status {
+            Arena hop_tmp(a, st);
+            // a3: the samples of this hop; sampled IDs are marked in `reached`
+            RG_TRY(sample_hop(g, cur, beta, batch_seed, l, fanout[l], sampler, reached, s->arena, hop_tmp, n_cu, st, hubs_allowed, looked_for_hubs,
+                              l == 0 ? n_bad_train : nullptr, &n_bad_host));
+            if (l == 0) RG_TRY(refuse_bad_train());
 
-        // a4: fresh IDs per (batch, chunk) -> positions -> next frontier
-        RG_TRY(s->arena.dev_n<int64_t>((uint64_t)beta + 1, &nxt.off_dev));
-        {
-            ScopedTimer tm(KG_FRONTIER, st);
-            if (sparse_maps)
-                hipLaunchKernelGGL(fresh_count_sparse_kernel, dim3(chunks, beta), dim3(FR_THREADS), 0, st, reached_words, reached_flags, seen, wpb, chunks, fresh_cnt);
-            else
-                hipLaunchKernelGGL(fresh_count_kernel, dim3(chunks, beta), dim3(FR_THREADS), 0, st, reached_words, reached_flags, seen, wpb, chunks, fresh_cnt);
-            RG_TRY(scan_i32_to_i64(fresh_cnt, fresh_scan, (int64_t)n_cells, tmp, st));
-            hipLaunchKernelGGL(next_offsets_kernel, dim3((beta + 1 + 255) / 256), dim3(256), 0, st, cur.off_dev, fresh_scan, beta, chunks, nxt.off_dev);
-        }
-        nxt.off_host.resize((size_t)beta + 1);
-        {
+            // a4: fresh IDs per (batch, chunk) -> positions -> next frontier
+            RG_TRY(s->arena.dev_n<int64_t>((uint64_t)beta + 1, &nxt.off_dev));
+            {
+                ScopedTimer tm(KG_FRONTIER, st);
+                if (sparse_maps)
+                    hipLaunchKernelGGL(fresh_count_sparse_kernel, dim3(chunks, beta), dim3(FR_THREADS), 0, st, reached_words, reached_flags, seen, wpb, chunks, fresh_cnt);
+                else
+                    hipLaunchKernelGGL(fresh_count_kernel, dim3(chunks, beta), dim3(FR_THREADS), 0, st, reached_words, reached_flags, seen, wpb, chunks, fresh_cnt);
+                RG_TRY(scan_i32_to_i64(fresh_cnt, fresh_scan, (int64_t)n_cells, hop_tmp, st));
+                hipLaunchKernelGGL(next_offsets_kernel, dim3((beta + 1 + 255) / 256), dim3(256), 0, st, cur.off_dev, fresh_scan, beta, chunks, nxt.off_dev);
+            }
+            nxt.off_host.resize((size_t)beta + 1);
             Readback rb(st);
             RG_TRY(rb.add(nxt.off_host.data(), nxt.off_dev, ((size_t)beta + 1) * sizeof(int64_t)));
             RG_TRY(rb.wait());
+            hop_tmp.drained();
+            return RG_OK;
+        };
+        bool looked_for_hubs = false;
+        rg_status rc = sample_and_count(true, &looked_for_hubs);
+        if (rc == RG_ENOMEM && looked_for_hubs) {
+            // Perhaps for want of what the hub rows took: once more without (the marks of the first try are marked again).
+            for (void *p : {(void *)cur.samp_off, (void *)cur.samp_nbr, (void *)nxt.off_dev}) s->arena.free_one(p);
+            cur.samp_off = nullptr; cur.samp_nbr = nullptr; nxt.off_dev = nullptr;
+            rc = sample_and_count(false, &looked_for_hubs);
         }
+        RG_TRY(rc);
         const int64_t n_next = nxt.off_host[beta];
         RG_TRY(s->arena.dev_n<int32_t>((uint64_t)n_next, &nxt.ids));
         {

@@ -124,3 +124,25 @@ def test_hub_rows_without_memory_for_their_tables(rg, orc, monkeypatch):
     a = rg.TorchAllocator(limit_bytes=1 << 20)
     check(rg, orc, indptr, indices, train, 64, [12, 4], allocator=a.struct)
     assert a.n_refused == 2                                  # the tables of either hop, nothing else
+
+
+@pytest.mark.parametrize("fanout", [[12, 4], [3, 2, 2]])
+def test_hub_rows_take_no_memory_that_the_build_needs(rg, orc, fanout, monkeypatch):
+    """An allocator with just what the build takes without tables suffices; and where there is more, one hop's tables are
+    the most that is ever held."""
+    rng = np.random.default_rng(4)
+    n = 200_000
+    indptr, indices, hubs = hub_graph(rng, n, [150_000, 199_999, 180_000, 190_000])
+    train = np.unique(np.concatenate([hubs, rng.permutation(n)[:100]])).astype(np.int32)
+    args = (rg, orc, indptr, indices, train, 64, fanout)
+    monkeypatch.setenv("RAPIDGNN_HUB_ROWS", "2e9")
+    without = RecordingAllocator(rg)
+    check(*args, allocator=without.struct)
+    monkeypatch.setenv("RAPIDGNN_HUB_ROWS", "16385")
+    tight = RecordingAllocator(rg, total_bytes=without.peak)
+    check(*args, allocator=tight.struct)
+    assert tight.n_refused > 0 and tight.peak <= without.peak
+    free = RecordingAllocator(rg)
+    check(*args, allocator=free.struct)
+    tables = 4 * 32 * n // 8                                 # four rows, a bucket of 32 bytes per eight IDs
+    assert tables / 2 < free.peak - without.peak < tables + (1 << 19)
