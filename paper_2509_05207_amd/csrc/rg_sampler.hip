@@ -1480,10 +1480,11 @@ __global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int
 // Bound by reading the samples once per piece of the bitmap.  A workgroup puts MARK_WORDS words of one batch's bitmap
 // together in LDS from all of the batch's samples, or a part of them, and writes them and the flags of the groups that
 // hold bits: nothing scattered leaves the compute unit.  Marked one by one from the sampling kernels, the memory system takes 25 G
-// atomic ORs or 88 G byte stores a second and the kernels carry the address arithmetic.   233 k nodes, 29 M samples: 0.05 ms; 2.45 M nodes, 167 M samples:
+// atomic ORs or 88 G byte stores a second and the kernels carry the address arithmetic.  233 k nodes, 29 M samples: 0.05 ms; 2.45 M nodes, 167 M samples:
 // 0.43, and the launches that marked bytes themselves 3.9 -> 2.2 ms; 146 M samples in three hops: 0.32, launches that marked
 // bits 10.6 -> 9.6.
-// The pieces of a batch run on one XCD (workgroup g runs on XCD g mod 8) at about the same time and share the reads.
+// The pieces of a batch run on one XCD (workgroup g runs on XCD g mod 8) at about the same time and share the reads; the
+// batches left over from whole eights are dealt out over all XCDs, or one batch would have an eighth of the chip.
 constexpr int MARK_THREADS = 1024;
 constexpr int MARK_WORDS = 32768;                        // 128 KB of LDS, 1,048,576 IDs: every piece reads all samples of its batch, so few large ones (of 64 KB: 0.54 ms for the 167 M below, so 0.43)
 constexpr int MARK_XCDS = 8;
@@ -1495,10 +1496,18 @@ __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *
                                                                  uint32_t n_batches, uint32_t pieces, uint32_t parts, uint32_t piece_words, ReachedMaps m)
 {
     extern __shared__ uint32_t bits[];                   // [piece_words]
-    const uint32_t r = blockIdx.x / MARK_XCDS, per_batch = pieces * parts;
-    const uint32_t b = r / per_batch * MARK_XCDS + blockIdx.x % MARK_XCDS;
-    if (b >= n_batches) return;
-    const uint32_t piece = r % per_batch % pieces, part = r % per_batch / pieces;
+    const uint32_t per_batch = pieces * parts, whole = n_batches / MARK_XCDS * MARK_XCDS, rest = n_batches - whole;
+    uint32_t b, at;                                      // the batch, and which of its workgroups
+    if (blockIdx.x < whole * per_batch) {
+        const uint32_t r = blockIdx.x / MARK_XCDS;
+        b = r / per_batch * MARK_XCDS + blockIdx.x % MARK_XCDS;
+        at = r % per_batch;
+    } else {
+        const uint32_t r = blockIdx.x - whole * per_batch;
+        b = whole + r % rest;
+        at = r / rest;
+    }
+    const uint32_t piece = at % pieces, part = at / pieces;
     for (uint32_t w = threadIdx.x; w < piece_words; w += MARK_THREADS) bits[w] = 0u;
     __syncthreads();
     const int64_t first = samp_off[batch_off[b]], n = samp_off[batch_off[b + 1]] - first;
@@ -1542,7 +1551,7 @@ static rg_status launch_mark_pass(const HopData &cur, uint32_t beta, const Reach
     // a few batches of many samples are read in parts, whose bits are ORed into the map
     const uint64_t units = (uint64_t)pieces * beta;
     const uint32_t parts = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(cur.n_samples / beta / MARK_PART, n_cu / (int64_t)units));
-    const uint64_t grid = (uint64_t)(beta + MARK_XCDS - 1) / MARK_XCDS * MARK_XCDS * pieces * parts;
+    const uint64_t grid = (uint64_t)beta * pieces * parts;
     if (grid > 0x7FFFFFFFull) { set_error("rg_build_schedule: %llu pieces of bitmaps in one hop", (unsigned long long)grid); return RG_ERANGE; }
     RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(mark_pass_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, MARK_WORDS * (int)sizeof(uint32_t)));
     hipLaunchKernelGGL(mark_pass_kernel, dim3((unsigned)grid), dim3(MARK_THREADS), piece_words * sizeof(uint32_t), st, cur.samp_nbr, cur.samp_off, cur.off_dev, beta, pieces,
