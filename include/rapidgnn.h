@@ -101,8 +101,11 @@ typedef struct rg_cache rg_cache;
  * (the IDs a batch has seen, and the IDs a hop reaches).
  * Environment: RAPIDGNN_SPARSE_FRONTIER=1 / 0 forces / forbids the frontier
  * passes tuned for graphs of 10^7 nodes and more (default: chosen from
- * n_nodes; sampling kernels then mark what they reach themselves, else a pass
- * over the samples does); RAPIDGNN_SHORT_ROWS=0 makes rows of up to 64 IDs be
+ * n_nodes; the sampling kernels then mark what they reach themselves);
+ * RAPIDGNN_MARK_PASS=1 / 0 forces / forbids marking what a hop of any other build
+ * reaches by a pass over its samples instead (default: from one sample per 512 IDs
+ * of the batches' bitmaps on);
+ * RAPIDGNN_SHORT_ROWS=0 makes rows of up to 64 IDs be
  * sampled one per wave instead of four; RAPIDGNN_GROUP_TILES=1 / 0 forces /
  * forbids handing out the pieces of rows above 16,384 IDs grouped by the piece
  * they read, so that batches that share a row meet in the caches (default: from

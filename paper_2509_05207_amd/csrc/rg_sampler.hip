@@ -1637,7 +1637,8 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     // The mark pass clears and looks through every word of every batch's bitmap, some 5 us per 128 KB of LDS and compute
     // unit; marks from the sampling kernels take 40 ps each where they do not hide behind the reads.  So the pass from one
     // sample per MARK_SPARSE IDs of bitmap on (where both cost the same it is about one per 2,048).
-    const bool inline_marks = reached.paired || (uint64_t)cur.n_samples * MARK_SPARSE < reached.words_per_batch * 32 * (uint64_t)beta;
+    bool inline_marks = reached.paired || (uint64_t)cur.n_samples * MARK_SPARSE < reached.words_per_batch * 32 * (uint64_t)beta;
+    if (const char *force = getenv("RAPIDGNN_MARK_PASS"); force && !reached.paired) inline_marks = force[0] == '0';       // same results either way; for tests and tuning
     RG_TRY(keep.dev_n<int32_t>((uint64_t)cur.n_samples, &cur.samp_nbr));
     if (sampler == RG_SAMPLER_POSITIONS) {
         if (fanout > 0 && n_cur > 0) {

@@ -1,5 +1,5 @@
 """Computation blocks where the workgroup map changes shape: numbers of batches around the eight XCDs, groups of batches of
-every size, batches with few edges and none; and the O(f) sampler's marks in every form; against the oracle."""
+every size, batches with few edges and none; and the O(f) sampler's samples marked in every way; against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -41,11 +41,11 @@ def test_blocks_of_every_group(rg, orc, n_batches, group):
         assert np.array_equal(rg.rg_schedule_block(s, hop).cpu().numpy(), o.block(hop)), hop
 
 
-@pytest.mark.parametrize("byte_maps", ["0", "1", None])
+@pytest.mark.parametrize("mark_pass", ["0", "1", None])
 @pytest.mark.parametrize("fanout", [[2, 3], [40, 40], [255, 2], [256, 3], [300, 1]])
-def test_positions_sampler_in_every_marking(rg, orc, byte_maps, fanout, monkeypatch):
-    if byte_maps is not None:
-        monkeypatch.setenv("RAPIDGNN_BYTE_MAPS", byte_maps)
+def test_positions_sampler_in_every_marking(rg, orc, mark_pass, fanout, monkeypatch):
+    if mark_pass is not None:
+        monkeypatch.setenv("RAPIDGNN_MARK_PASS", mark_pass)
     rng = np.random.default_rng(len(fanout) + fanout[0])
     n = 2000
     indptr, indices = graph(rng, n, 700)

@@ -1,5 +1,5 @@
-"""Frontiers written through LDS and group by group (more than 4,096 new IDs in a wave's 16,384), for both forms of the
-reached map: batches that reach a little, about a quarter and most of the graph, at sizes around a wave's and a
+"""Frontiers written through LDS and group by group (more than 4,096 new IDs in a wave's 16,384), for both ways of marking
+what was reached: batches that reach a little, about a quarter and most of the graph, at sizes around a wave's and a
 workgroup's span; against the oracle."""
 import numpy as np
 import pytest
@@ -16,11 +16,11 @@ def rg():
     return binding
 
 
-@pytest.mark.parametrize("byte_maps", ["0", "1"])
+@pytest.mark.parametrize("mark_pass", ["0", "1"])
 @pytest.mark.parametrize("n", [300, 16_383, 16_385, 65_537, 140_001])
 @pytest.mark.parametrize("share", [0.02, 0.29, 2.0])
-def test_new_ids_of_every_density(rg, orc, n, share, byte_maps, monkeypatch):
-    monkeypatch.setenv("RAPIDGNN_BYTE_MAPS", byte_maps)
+def test_new_ids_of_every_density(rg, orc, n, share, mark_pass, monkeypatch):
+    monkeypatch.setenv("RAPIDGNN_MARK_PASS", mark_pass)
     rng = np.random.default_rng(n)
     deg = 20
     indices = np.sort((rng.integers(0, n, size=(n, 1)) + np.arange(deg) * (n // deg) + rng.integers(0, n // deg, size=(n, deg))) % n, axis=1)
@@ -39,9 +39,12 @@ def test_new_ids_of_every_density(rg, orc, n, share, byte_maps, monkeypatch):
 
 
 @pytest.mark.parametrize("n", [1_048_575, 1_048_577, 2_200_000])
-@pytest.mark.parametrize("n_train,batch", [(40_000, 40_000), (41_000, 20_480), (300, 20)])
-def test_marks_in_pieces_and_parts(rg, orc, n, n_train, batch):
-    """Bitmaps of one to three pieces of 1,048,576 IDs; batches whose samples are marked in several parts, and in one."""
+@pytest.mark.parametrize("n_train,batch", [(40_000, 40_000), (41_000, 20_480), (300, 20), (360, 20), (180, 20)])
+@pytest.mark.parametrize("mark_pass", ["1", "0"])
+def test_marks_in_pieces_and_parts(rg, orc, n, n_train, batch, mark_pass, monkeypatch):
+    """Bitmaps of one to three pieces of 1,048,576 IDs; batches whose samples are marked in several parts, and in one; one,
+    two, fifteen, eighteen and nine batches, of which the pass sends whole eights to an XCD each."""
+    monkeypatch.setenv("RAPIDGNN_MARK_PASS", mark_pass)
     rng = np.random.default_rng(n + n_train)
     deg = 18
     step = n // deg

@@ -59,11 +59,13 @@ def check(rg, orc, indptr, indices, train, batch, fanout, allocator=None):
 HUB_DEGREES = [16384, 16385, 20011, 65536, 131073, 199_999, 30_000, 150_000]
 
 
-@pytest.mark.parametrize("shuffled", [(), (6, 7)])
+@pytest.mark.parametrize("shuffled,mark_pass", [((), "1"), ((), "0"), ((6, 7), "1")])
 @pytest.mark.parametrize("fanout", [[1, 1], [12, 4], [60, 20], [200, 3], [448], [449]])
-def test_hub_rows_equal_the_oracle(rg, orc, fanout, shuffled, monkeypatch):
-    """Every row in order: all from 16,385 IDs on are sampled from the keys' side.  Two that are not: the hop's rows are read."""
+def test_hub_rows_equal_the_oracle(rg, orc, fanout, shuffled, mark_pass, monkeypatch):
+    """Every row in order: all from 16,385 IDs on are sampled from the keys' side, and marked by the pass or as they are
+    sampled.  Two that are not in order: the hop's rows are read."""
     monkeypatch.setenv("RAPIDGNN_HUB_ROWS", "16385")
+    monkeypatch.setenv("RAPIDGNN_MARK_PASS", mark_pass)
     rng = np.random.default_rng(sum(fanout))
     n = 200_000
     indptr, indices, hubs = hub_graph(rng, n, HUB_DEGREES, shuffled)

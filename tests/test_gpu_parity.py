@@ -510,12 +510,10 @@ def test_both_frontier_variants_give_the_same_schedule(case, rg, force, monkeypa
 @pytest.mark.parametrize("force", ["1", "0"])
 @pytest.mark.parametrize("sampler", ["keys", "positions"])
 @pytest.mark.parametrize("fanout", [None, (300, 3)])
-def test_both_forms_of_the_reached_map_give_the_same_schedule(case, rg, orc, force, sampler, fanout, monkeypatch):
-    """Marks as plain byte stores into a byte per ID, and as atomic ORs into a bit per ID (what graphs too large for
-    the byte form get), each forced; both samplers mark through the same call.  With fan-outs (300, 3) and the byte
-    form forced, the key sampler's first hop still marks bits (its byte-marking kernels stop at a fan-out of 192)
-    and its second hop bytes: both forms within one build."""
-    monkeypatch.setenv("RAPIDGNN_BYTE_MAPS", force)
+def test_both_ways_of_marking_give_the_same_schedule(case, rg, orc, force, sampler, fanout, monkeypatch):
+    """What a hop reaches marked by a pass over its samples, and by the sampling kernels as they write them, each forced; with
+    the workload's own fan-outs and with one beyond the smaller candidate buffers."""
+    monkeypatch.setenv("RAPIDGNN_MARK_PASS", force)
     w = case.w
     fan = list(fanout) if fanout else list(w.cfg.fanout)
     code = rg.RG_SAMPLER_KEYS if sampler == "keys" else rg.RG_SAMPLER_POSITIONS

@@ -60,17 +60,13 @@ SHAPES = [
 
 
 @pytest.mark.parametrize("shape", range(len(SHAPES)))
-@pytest.mark.parametrize("sampler,maps", [("keys", "auto"), ("keys", "bytes"), ("keys", "bits"), ("keys", "one_row_per_wave"), ("keys", "four_short_rows_per_wave"), ("keys", "four_short_rows_inline"),
-                                          ("positions", "auto")])
-def test_random_shape(rg, orc, shape, sampler, maps, monkeypatch):
-    if maps in ("bytes", "bits"):                        # the form of the reached-ID map, forced (chosen per hop otherwise)
-        monkeypatch.setenv("RAPIDGNN_BYTE_MAPS", "1" if maps == "bytes" else "0")
-    if maps == "one_row_per_wave":                       # without the kernel that samples four short rows at a time ...
+@pytest.mark.parametrize("sampler,form", [("keys", "auto"), ("keys", "marked_by_the_pass"), ("keys", "marked_as_sampled"), ("keys", "one_row_per_wave"),
+                                          ("positions", "marked_by_the_pass"), ("positions", "marked_as_sampled")])
+def test_random_shape(rg, orc, shape, sampler, form, monkeypatch):
+    if form.startswith("marked"):                        # how the reached-ID maps are written, forced (chosen per hop otherwise)
+        monkeypatch.setenv("RAPIDGNN_MARK_PASS", "1" if form == "marked_by_the_pass" else "0")
+    if form == "one_row_per_wave":                       # without sampling four short rows at a time
         monkeypatch.setenv("RAPIDGNN_SHORT_ROWS", "0")
-    if maps == "four_short_rows_per_wave":               # ... with it in every hop (by default: in hops that mark with byte stores) ...
-        monkeypatch.setenv("RAPIDGNN_SHORT_ROWS", "1")
-    if maps == "four_short_rows_inline":                 # ... and with the same done inside the other kernel (by default: in hops that mark with atomic ORs)
-        monkeypatch.setenv("RAPIDGNN_SHORT_ROWS", "2")
     n, classes, fanout, batch, n_train = SHAPES[shape]
     rng = np.random.default_rng(4000 + shape)
     indptr, indices = random_graph(rng, n, classes)
@@ -94,12 +90,13 @@ def test_random_shape(rg, orc, shape, sampler, maps, monkeypatch):
         assert np.array_equal(gnb.cpu().numpy(), nb), f"sampled neighbours differ at hop {hop}"
 
 
-@pytest.mark.parametrize("group_tiles", ["1", "0"])
-def test_rows_of_several_tiles(rg, orc, group_tiles, monkeypatch):
+@pytest.mark.parametrize("group_tiles,mark_pass", [("1", "1"), ("0", "1"), ("0", "0")])
+def test_rows_of_several_tiles(rg, orc, group_tiles, mark_pass, monkeypatch):
     """Hub rows on both sides of the tiling threshold and of the tile length, up to three tiles, as seeds and as
     neighbours of many short rows, so that every batch samples them in every hop; with the tile jobs handed out
-    grouped by the piece they read, and in frontier order."""
+    grouped by the piece they read, and in frontier order, their samples marked by the pass and by the merging kernel."""
     monkeypatch.setenv("RAPIDGNN_GROUP_TILES", group_tiles)
+    monkeypatch.setenv("RAPIDGNN_MARK_PASS", mark_pass)
     rng = np.random.default_rng(77)
     n = 200_000
     hub_deg = [16384, 16385, 40000, 65535, 65536, 65537, 70000, 131072, 131073, 150000, 196608, 199999]
