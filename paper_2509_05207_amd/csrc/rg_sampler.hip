@@ -1489,7 +1489,7 @@ constexpr int MARK_THREADS = 1024;
 constexpr int MARK_WORDS = 32768;                        // 128 KB of LDS, 1,048,576 IDs: every piece reads all samples of its batch, so few large ones (of 64 KB: 0.54 ms for the 167 M below, so 0.43)
 constexpr int MARK_XCDS = 8;
 constexpr int MARK_IN_FLIGHT = 8;
-constexpr uint64_t MARK_SPARSE = 512;                    // see sample_hop
+constexpr uint64_t MARK_SPARSE = 512, MARK_MANY = 1 << 21, MARK_CROWD = 96;      // see sample_hop
 constexpr int64_t MARK_PART = 1 << 18;                   // samples per part, at least, where there are too few pieces to fill the chip
 
 __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *__restrict__ samp_nbr, const int64_t *__restrict__ samp_off, const int64_t *__restrict__ batch_off,
@@ -1634,10 +1634,17 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
             for (int q = 0; q < DEG_SUMS; ++q) sums[q] += sum_parts[DEG_SUMS * k + q];
         if (also_read_dev && *also_read_host != 0) return RG_OK;        // the caller refuses the build: nothing more to launch
     }
-    // The mark pass clears and looks through every word of every batch's bitmap, some 5 us per 128 KB of LDS and compute
-    // unit; marks from the sampling kernels take 40 ps each where they do not hide behind the reads.  So the pass from one
-    // sample per MARK_SPARSE IDs of bitmap on (where both cost the same it is about one per 2,048).
-    bool inline_marks = reached.paired || (uint64_t)cur.n_samples * MARK_SPARSE < reached.words_per_batch * 32 * (uint64_t)beta;
+    // By a pass or by the sampling kernels themselves.  The pass clears and looks through the words of every batch's bitmap,
+    // some 6 us per 128 KB of LDS and compute unit and 8 us for itself; an atomic OR costs 40 ps where nothing hides it, next
+    // to nothing while rows are read, and more where many meet on a word.  So the pass
+    //  - from one sample per MARK_SPARSE IDs of bitmap on: 2.45 M nodes, one hop, fan-out 30, marked by the kernels / by the
+    //    pass: keys sampler one per 2,848 445 / 525 us, 1,424 1,076 / 1,094, 712 810 / 787, 356 587 / 539 (positions sampler
+    //    958 / 1,077, 702 / 778, 498 / 541; two hops, one per 148 in the second, 997 / 920);
+    //  - there, from MARK_MANY samples on or MARK_CROWD per word: sampling one batch, fan-outs 50,50, 2.45 M nodes, 512 seeds
+    //    (1 M samples in the second hop) 185 / 230 us, 4,096 seeds 407 / 344, 15,000 seeds 934 / 583; 30,000 nodes, 4,096
+    //    seeds 154 / 106.
+    const uint64_t mark_words = reached.words_per_batch * (uint64_t)beta, n_marks = (uint64_t)cur.n_samples;
+    bool inline_marks = reached.paired || n_marks * MARK_SPARSE < mark_words * 32 || (n_marks < MARK_MANY && n_marks < mark_words * MARK_CROWD);
     if (const char *force = getenv("RAPIDGNN_MARK_PASS"); force && !reached.paired) inline_marks = force[0] == '0';       // same results either way; for tests and tuning
     RG_TRY(keep.dev_n<int32_t>((uint64_t)cur.n_samples, &cur.samp_nbr));
     if (sampler == RG_SAMPLER_POSITIONS) {
