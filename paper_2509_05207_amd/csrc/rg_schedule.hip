@@ -236,12 +236,17 @@ __global__ void __launch_bounds__(PREFIX_THREADS) copy_prefix_kernel(const int32
 constexpr int EMIT_WINDOW = 4096;          // IDs of a wave (of 16,384) that go through LDS, as 16-bit offsets: 32 KB per workgroup
 // Writes the fresh IDs of (batch, chunk) in ascending order behind the batch's old frontier, adds
 // the reached IDs to `seen` and clears `reached` for the next hop.
+// THROUGH_LDS: not where a wave has fewer than EMIT_FEW new IDs on average.  Its 32 KB leave five workgroups on a compute unit
+// instead of eight, and cells that are empty or nearly so are nothing but waiting (frontier passes with / without, 2.45 M
+// nodes: 0.3 and 1.4 per wave 503 / 367 us, 2 and 10 157 / 142, 12 and 59 103 / 101, 59 and 252 71 / 71, 83 to 1,900 108 / 128).
+constexpr uint64_t EMIT_FEW = 64;
+template <bool THROUGH_LDS>
 __global__ void __launch_bounds__(FR_THREADS) fresh_emit_kernel(uint32_t *__restrict__ reached, uint8_t *__restrict__ flags, uint32_t *__restrict__ seen,
                                                                 uint8_t *__restrict__ seen_flags, uint64_t words_per_batch, uint32_t chunks, const int64_t *__restrict__ fresh_scan,
                                                                 const int64_t *__restrict__ cur_off, int32_t *__restrict__ next)
 {
     __shared__ int wave_tot[FR_THREADS / 64];
-    __shared__ uint16_t window[FR_THREADS / 64][EMIT_WINDOW];
+    __shared__ uint16_t window[THROUGH_LDS ? FR_THREADS / 64 : 1][THROUGH_LDS ? EMIT_WINDOW : 1];
     const uint32_t c = blockIdx.x, b = blockIdx.y;
     const int64_t scan_here = fresh_scan[(uint64_t)b * chunks + c];
     const bool any_fresh = fresh_scan[(uint64_t)b * chunks + c + 1] != scan_here;      // block-uniform
@@ -280,6 +285,13 @@ __global__ void __launch_bounds__(FR_THREADS) fresh_emit_kernel(uint32_t *__rest
     int before = incl - n;
     for (int k = 0; k < wave; ++k) before += wave_tot[k];
     // next_off[b] + |U_l of b| + scan - scan(b, 0)  ==  cur_off[b + 1] + scan
+    if (!THROUGH_LDS) {
+        int64_t pos = cur_off[b + 1] + scan_here + before;
+#pragma unroll
+        for (int k = 0; k < FR_WORDS_PER_THREAD; ++k)
+            for (uint32_t x = w[k]; x; x &= x - 1) next[pos++] = (int32_t)((uint32_t)((w0 + k) << 5) + __ffs((int)x) - 1);
+        return;
+    }
     // Each lane writing its own group's IDs, every store of the wave would go to 64 places (85 M IDs of three hops 423 us,
     // 61 M of two 394).  Up to EMIT_WINDOW IDs of a wave are put in order in LDS first and written from there 64 at a time;
     // more are written group by group, a group's bits as lane masks (so: 175 and 192; with the groups alone 376 and 222).
@@ -729,8 +741,10 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
             hipLaunchKernelGGL(copy_prefix_kernel, dim3((unsigned)((n_cur + PREFIX_CHUNK - 1) / PREFIX_CHUNK)), dim3(PREFIX_THREADS), 0, st, cur.ids, cur.off_dev, nxt.off_dev, beta, n_cur, nxt.ids);
             if (sparse_maps)
                 hipLaunchKernelGGL(fresh_emit_sparse_kernel, dim3(chunks, beta), dim3(FR_THREADS), 0, st, reached_words, reached_flags, seen, seen_flags, wpb, chunks, fresh_scan, cur.off_dev, nxt.ids, l + 1 < L ? 1 : 0);
+            else if ((uint64_t)(n_next - n_cur) < EMIT_FEW * n_cells * (FR_THREADS / 64))
+                hipLaunchKernelGGL(fresh_emit_kernel<false>, dim3(chunks, beta), dim3(FR_THREADS), 0, st, reached_words, reached_flags, seen, seen_flags, wpb, chunks, fresh_scan, cur.off_dev, nxt.ids);
             else
-                hipLaunchKernelGGL(fresh_emit_kernel, dim3(chunks, beta), dim3(FR_THREADS), 0, st, reached_words, reached_flags, seen, seen_flags, wpb, chunks, fresh_scan, cur.off_dev, nxt.ids);
+                hipLaunchKernelGGL(fresh_emit_kernel<true>, dim3(chunks, beta), dim3(FR_THREADS), 0, st, reached_words, reached_flags, seen, seen_flags, wpb, chunks, fresh_scan, cur.off_dev, nxt.ids);
         }
         RG_HIP(hipGetLastError());
     }
