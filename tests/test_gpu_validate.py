@@ -51,9 +51,12 @@ def test_violations_are_counted_at_every_size_and_phase(rg, edges, phase):
         check(rg, indptr, indices, phase)
 
 
-def test_rows_out_of_order_are_counted_row_by_row(rg):
+@pytest.mark.parametrize("n", [3000, 16_384, 16_385])
+def test_rows_out_of_order_are_counted_row_by_row(rg, n):
+    """Up to 16 workgroups of four rows per compute unit (256 of them) the rows are counted behind the first look at indptr
+    without a word from the host, beyond on its request."""
     rng = np.random.default_rng(3)
-    n, deg = 3000, 8
+    deg = 8
     indptr = np.arange(0, deg * n + 1, deg).astype(np.int64)
     indices = np.sort(rng.integers(0, n, size=(n, deg)), axis=1).astype(np.int32).ravel()
     for damage in ({5: 5 * deg - 11}, {0: 3}, {n // 2: 0, 17: 19 * deg}, {n: 0}):
