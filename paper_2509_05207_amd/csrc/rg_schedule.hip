@@ -604,10 +604,9 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
     };
     if (T > 0) {
         KeyPos *kp = nullptr;
-        int32_t *place = nullptr;
+        int32_t *place = h0.ids;               // (the seeds are written by the last of the three kernels, the places read by the one before)
         int64_t *bucket_off = nullptr;
         RG_TRY(tmp.dev_n<KeyPos>(T, &kp));
-        RG_TRY(tmp.dev_n<int32_t>(T, &place));
         RG_TRY(tmp.dev_n<int64_t>(n_buckets + 1, &bucket_off));
         {
             ScopedTimer tm(KG_SORT, st);
