@@ -222,8 +222,10 @@ typedef struct rg_features {
  * cache keeps a map from node to slot (half a byte per node: which IDs are
  * cached and local, and ranks) and the tally: 1 byte per node where the given
  * epochs have at most 255 batches together (no frequency can then exceed 255),
- * else 4.  Environment: RAPIDGNN_NARROW_TALLY=0 forbids the byte form (same
- * results either way).  The fill of the table runs on a stream the library
+ * else 4.  Environment: RAPIDGNN_NARROW_TALLY=0 forbids the byte form;
+ * RAPIDGNN_ROW_RANKS=1 / 0 makes the plans look whether row_of numbers the local
+ * and the remote nodes in the order of their IDs, in which case they need not read
+ * it, / not look (default: from eight listed input nodes per node of the graph on).  Same results either way.  The fill of the table runs on a stream the library
  * owns, beside the routing work on `stream`; the call returns after both.
  */
 rg_status rg_build_cache(const rg_schedule *const *epochs, uint32_t n_epochs, const rg_features *f,

@@ -442,6 +442,10 @@ struct RouteSources {
     const uint32_t *not_ranks;       // dev: 0 = row_of[v] is the number of local (of remote) IDs in front of v, for every v; NULL: not known
 };
 
+// Reading row_of is two thirds of what a plan over many input nodes moves (a batch's IDs touch nearly every line of it), so it
+// is first checked, in one pass, for being the ranks that the slot map knows anyway.  The pass reads row_of once;
+// worth it from RANK_INPUTS_PER_NODE input nodes per node on.
+constexpr int64_t RANK_INPUTS_PER_NODE = 8;
 // local_cnt[r] = local IDs among record r's 32
 __global__ void local_counts_kernel(const SlotRec *__restrict__ recs, int64_t n_recs, int32_t *__restrict__ local_cnt)
 {
@@ -462,9 +466,9 @@ __global__ void row_ranks_kernel(SlotRec *recs, int64_t n, const int64_t *__rest
     if (__ballot(differs) != 0ull && (threadIdx.x & 63) == 0) *not_ranks = 1u;
 }
 
-// entry[j] = where ids[j] is served from, for every listed input node, which of them are misses and which are local (one
-// bit each, in position order: a wave's ballot is the 64-bit word of its 64 consecutive positions), and how many of
-// either each tile of PLAN_TILE positions holds.  Nothing is added up per batch here: the tiles of a batch run at the
+// entry[j] = where ids[j] is served from, for every listed input node, which of them are misses (one
+// bit each, in position order: a wave's ballot is the 64-bit word of its 64 consecutive positions), and how many misses and
+// how many local rows each tile of PLAN_TILE positions holds.  Nothing is added up per batch here: the tiles of a batch run at the
 // same time, and two adds per tile to the batch's counters queued up behind each other (an epoch of 80 M input nodes in
 // 196 batches: 712 us with the adds, 494 with tiles of 1,024 positions without them, 441 so; 111 M nodes, 4.2 M input
 // nodes: 253 -> 122).  The kernel waits for its dependent reads (ID, slot-map record, row), so each kind
@@ -476,7 +480,6 @@ constexpr int PLAN_TILE_WORDS = PLAN_TILE / 64;          // bit words per tile
 
 __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__restrict__ ids, int64_t n, RouteSources rs, int64_t *__restrict__ entry,
                                                             unsigned long long *__restrict__ miss_bits /* [tiles * PLAN_TILE_WORDS] */,
-                                                            unsigned long long *__restrict__ local_bits /* the same */,
                                                             int32_t *__restrict__ tile_miss /* [tiles] */, int32_t *__restrict__ tile_local /* [tiles] */)
 {
     __shared__ int red[2][PLAN_THREADS / 64];
@@ -508,11 +511,7 @@ __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__res
         const bool local = (rec[k].z & bit) != 0, cached = !local && (rec[k].x & bit) != 0;
         if (j < n) __builtin_nontemporal_store(make_entry(local ? TAG_LOCAL : cached ? TAG_CACHE : TAG_REMOTE, row[k]), entry + j);
         const unsigned long long ml = __ballot(j < n && local), mm = __ballot(j < n && !local && !cached);
-        if (lane == 0) {
-            const uint64_t word = (uint64_t)blockIdx.x * PLAN_TILE_WORDS + k * (PLAN_THREADS / 64) + wave;
-            miss_bits[word] = mm;
-            local_bits[word] = ml;
-        }
+        if (lane == 0) miss_bits[(uint64_t)blockIdx.x * PLAN_TILE_WORDS + k * (PLAN_THREADS / 64) + wave] = mm;
         n_local += __popcll(ml);
         n_miss += __popcll(mm);
     }
@@ -538,32 +537,50 @@ __device__ __forceinline__ int64_t lane_bits_between(const unsigned long long *_
     return cnt;
 }
 
-// One wave per batch (and one for the end).  miss_off[b] = misses in front of batch b's first position: those of the
-// tiles in front of its tile (tile_scan) and of the positions in front of it inside the tile; n_local[b] = its local
-// rows: the whole tiles between its ends, and the bits of the tiles it begins and ends in.
-__global__ void __launch_bounds__(64) batch_counts_kernel(const unsigned long long *__restrict__ miss_bits, const unsigned long long *__restrict__ local_bits,
-                                                          const int64_t *__restrict__ tile_scan, const int32_t *__restrict__ tile_local, int64_t n, int64_t n_tiles,
-                                                          const int64_t *__restrict__ batch_off, uint32_t n_batches, int64_t *__restrict__ miss_off,
-                                                          int64_t *__restrict__ n_local)
+// Entries among positions [lo, hi) that are local, counted by a workgroup (the sum is the threads' together).
+constexpr int COUNT_THREADS = 256;
+constexpr int COUNT_IN_FLIGHT = PLAN_TILE / COUNT_THREADS;
+__device__ __forceinline__ int64_t thread_local_rows_between(const int64_t *__restrict__ entry, int64_t lo, int64_t hi)      // (within one tile)
 {
+    int64_t e[COUNT_IN_FLIGHT], cnt = 0;
+#pragma unroll
+    for (int k = 0; k < COUNT_IN_FLIGHT; ++k) {
+        const int64_t j = lo + k * COUNT_THREADS + threadIdx.x;
+        e[k] = j < hi ? entry[j] : make_entry(TAG_REMOTE, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < COUNT_IN_FLIGHT; ++k) cnt += entry_tag(e[k]) == TAG_LOCAL ? 1 : 0;
+    return cnt;
+}
+
+// One workgroup per batch (and one for the end).  miss_off[b] = misses in front of batch b's first position: those of the
+// tiles in front of its tile (tile_scan) and of the positions in front of it inside the tile; n_local[b] = its local
+// rows: the whole tiles between its ends, and the entries of the tiles it begins and ends in.
+__global__ void __launch_bounds__(COUNT_THREADS) batch_counts_kernel(const unsigned long long *__restrict__ miss_bits, const int64_t *__restrict__ entry,
+                                                                     const int64_t *__restrict__ tile_scan, const int32_t *__restrict__ tile_local, int64_t n, int64_t n_tiles,
+                                                                     const int64_t *__restrict__ batch_off, uint32_t n_batches, int64_t *__restrict__ miss_off,
+                                                                     int64_t *__restrict__ n_local)
+{
+    __shared__ int64_t part[COUNT_THREADS / 64];
     const uint32_t b = blockIdx.x;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t lo = batch_off[b], t_lo = lo / PLAN_TILE;
-    int64_t before = lo < n ? lane_bits_between(miss_bits, t_lo * PLAN_TILE, lo, lane) : 0;
+    int64_t before = lo < n && wave == 0 ? lane_bits_between(miss_bits, t_lo * PLAN_TILE, lo, lane) : 0;
     int64_t local = 0;
     if (b < n_batches) {
         const int64_t hi = batch_off[b + 1], t_hi = hi / PLAN_TILE;
-        if (t_lo == t_hi) local = lane_bits_between(local_bits, lo, hi, lane);
+        if (t_lo == t_hi) local = thread_local_rows_between(entry, lo, hi);
         else {
-            local = lane_bits_between(local_bits, lo, (t_lo + 1) * PLAN_TILE, lane);
-            for (int64_t t = t_lo + 1 + lane; t < t_hi; t += 64) local += tile_local[t];
-            local += lane_bits_between(local_bits, t_hi * PLAN_TILE, hi, lane);
+            local = thread_local_rows_between(entry, lo, (t_lo + 1) * PLAN_TILE) + thread_local_rows_between(entry, t_hi * PLAN_TILE, hi);
+            for (int64_t t = t_lo + 1 + threadIdx.x; t < t_hi; t += COUNT_THREADS) local += tile_local[t];
         }
     }
     for (int o = 32; o > 0; o >>= 1) { before += __shfl_down(before, o, 64); local += __shfl_down(local, o, 64); }
-    if (lane == 0) {
+    if (lane == 0) part[wave] = local;
+    __syncthreads();
+    if (threadIdx.x == 0) {
         miss_off[b] = lo < n ? tile_scan[t_lo] + before : tile_scan[n_tiles];
-        if (b < n_batches) n_local[b] = local;
+        if (b < n_batches) n_local[b] = part[0] + part[1] + part[2] + part[3];
     }
 }
 
@@ -600,7 +617,28 @@ __global__ void __launch_bounds__(256) miss_list_kernel(const unsigned long long
 
 // Routing entries, miss lists and counts of one schedule.  What the
 // plan keeps lives in `keep`; scratch in `tmp`.
-rg_status build_plan(const rg_schedule *s, const RouteSources &rs, Arena &keep, Arena &tmp, hipStream_t st, Plan *plan)
+// Whether row_of is ranks (see RouteSources): asked once, in the entries of the first plan that has room for it before they are
+// written, so that it takes no memory of its own.
+struct RankCheck {
+    SlotRec *recs;
+    int64_t n_nodes;
+    uint32_t *not_ranks;             // dev
+    bool pending;
+};
+static rg_status check_row_ranks(const RankCheck &c, const int32_t *row_of, void *room, Arena &tmp, hipStream_t st)
+{
+    const int64_t n_recs = (c.n_nodes + 31) / 32;
+    int64_t *local_off = static_cast<int64_t *>(room);
+    int32_t *local_cnt = reinterpret_cast<int32_t *>(local_off + n_recs + 1);
+    RG_HIP(hipMemsetAsync(c.not_ranks, 0, sizeof(uint32_t), st));
+    hipLaunchKernelGGL(local_counts_kernel, dim3((unsigned)((n_recs + 255) / 256)), dim3(256), 0, st, c.recs, n_recs, local_cnt);
+    RG_TRY(scan_i32_to_i64(local_cnt, local_off, n_recs, tmp, st));
+    hipLaunchKernelGGL(row_ranks_kernel, dim3((unsigned)((c.n_nodes + 255) / 256)), dim3(256), 0, st, c.recs, c.n_nodes, local_off, row_of, c.not_ranks);
+    RG_HIP(hipGetLastError());
+    return RG_OK;
+}
+
+rg_status build_plan(const rg_schedule *s, RouteSources &rs, RankCheck &check, Arena &keep, Arena &tmp, hipStream_t st, Plan *plan)
 {
     const uint32_t beta = s->n_batches;
     const HopData &h = s->hop[s->L];
@@ -612,11 +650,10 @@ rg_status build_plan(const rg_schedule *s, const RouteSources &rs, Arena &keep, 
     if (beta == 0) { RG_TRY(keep.dev_n<int32_t>(0, &plan->miss_rows)); return RG_OK; }
 
     const int64_t n_tiles = (n + PLAN_TILE - 1) / PLAN_TILE, n_words = n_tiles * PLAN_TILE_WORDS;
-    unsigned long long *miss_bits = nullptr, *local_bits = nullptr;
+    unsigned long long *miss_bits = nullptr;
     int32_t *tile_miss = nullptr, *tile_local = nullptr;
     int64_t *tile_scan = nullptr, *miss_off_dev = nullptr, *n_local_dev = nullptr;
     RG_TRY(tmp.dev_n<unsigned long long>((uint64_t)std::max<int64_t>(n_words, 1), &miss_bits));
-    RG_TRY(tmp.dev_n<unsigned long long>((uint64_t)std::max<int64_t>(n_words, 1), &local_bits));
     RG_TRY(tmp.dev_n<int32_t>((uint64_t)std::max<int64_t>(n_tiles, 1), &tile_miss));
     RG_TRY(tmp.dev_n<int32_t>((uint64_t)std::max<int64_t>(n_tiles, 1), &tile_local));
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_tiles + 1, &tile_scan));
@@ -624,10 +661,15 @@ rg_status build_plan(const rg_schedule *s, const RouteSources &rs, Arena &keep, 
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)beta, &n_local_dev));
     {
         ScopedTimer tm(KG_PLAN, st);
+        if (check.pending && (uint64_t)n * sizeof(int64_t) >= (uint64_t)((check.n_nodes + 31) / 32 + 1) * (sizeof(int64_t) + sizeof(int32_t))) {
+            RG_TRY(check_row_ranks(check, rs.row_of, plan->entry, tmp, st));
+            rs.not_ranks = check.not_ranks;
+            check.pending = false;
+        }
         if (n > 0)
-            hipLaunchKernelGGL(plan_kernel, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, plan->entry, miss_bits, local_bits, tile_miss, tile_local);
+            hipLaunchKernelGGL(plan_kernel, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, plan->entry, miss_bits, tile_miss, tile_local);
         RG_TRY(scan_i32_to_i64(tile_miss, tile_scan, n_tiles, tmp, st));
-        hipLaunchKernelGGL(batch_counts_kernel, dim3(beta + 1), dim3(64), 0, st, miss_bits, local_bits, tile_scan, tile_local, n, n_tiles, h.off_dev, beta, miss_off_dev, n_local_dev);
+        hipLaunchKernelGGL(batch_counts_kernel, dim3(beta + 1), dim3(COUNT_THREADS), 0, st, miss_bits, plan->entry, tile_scan, tile_local, n, n_tiles, h.off_dev, beta, miss_off_dev, n_local_dev);
     }
     std::vector<int64_t> n_local(beta);
     {
@@ -830,29 +872,12 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
     // ---- a5/a9: plans, miss lists and counts for every batch of every epoch
     c->plans.resize(n_epochs);
     RouteSources rs{f->row_of, c->slot_pairs, nullptr};
-    // Reading row_of is two thirds of what a plan over many input nodes moves (a batch's IDs touch nearly every line of it),
-    // so it is first checked, in one pass, for being the ranks that the slot map knows anyway.  The pass reads row_of
-    // once; worth it from eight input nodes per node on (two epochs of 80 M input nodes on 2.45 M nodes: their plans
-    // 882 us, 494 so, and 20 for the check; a graph with fewer input nodes than nodes would pay more than it saves).
     int64_t n_inputs = 0;
     for (uint32_t e = 0; e < n_epochs; ++e) n_inputs += epochs[e]->n_batches ? epochs[e]->hop[epochs[e]->L].off_host[epochs[e]->n_batches] : 0;
-    if (n > 0 && n_inputs >= 8 * n) {
-        const int64_t n_recs = (n + 31) / 32;
-        int32_t *local_cnt = nullptr;
-        int64_t *local_off = nullptr;
-        uint32_t *not_ranks = nullptr;
-        RG_TRY(tmp.dev_n<int32_t>((uint64_t)n_recs, &local_cnt));
-        RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_recs + 1, &local_off));
-        RG_TRY(tmp.dev_n<uint32_t>(1, &not_ranks));
-        ScopedTimer tm(KG_PLAN, st);
-        RG_HIP(hipMemsetAsync(not_ranks, 0, sizeof(uint32_t), st));
-        hipLaunchKernelGGL(local_counts_kernel, dim3((unsigned)((n_recs + 255) / 256)), dim3(256), 0, st, c->slot_pairs, n_recs, local_cnt);
-        RG_TRY(scan_i32_to_i64(local_cnt, local_off, n_recs, tmp, st));
-        hipLaunchKernelGGL(row_ranks_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, c->slot_pairs, n, local_off, f->row_of, not_ranks);
-        RG_HIP(hipGetLastError());
-        rs.not_ranks = not_ranks;
-    }
-    for (uint32_t e = 0; e < n_epochs; ++e) RG_TRY(build_plan(epochs[e], rs, c->arena, tmp, st, &c->plans[e]));
+    bool look_for_ranks = n_inputs >= RANK_INPUTS_PER_NODE * n;
+    if (const char *force = getenv("RAPIDGNN_ROW_RANKS")) look_for_ranks = force[0] == '1';      // same results either way; for tests and tuning
+    RankCheck check{c->slot_pairs, n, reinterpret_cast<uint32_t *>(bins), look_for_ranks && n > 0};       // (the digits have been chosen)
+    for (uint32_t e = 0; e < n_epochs; ++e) RG_TRY(build_plan(epochs[e], rs, check, c->arena, tmp, st, &c->plans[e]));
     if (forked.side) RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));
     RG_HIP(hipStreamSynchronize(st));
     if (forked.side) { RG_HIP(hipStreamSynchronize(forked.side)); forked.side = nullptr; }

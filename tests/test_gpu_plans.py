@@ -48,9 +48,11 @@ def test_counts_and_rows_of_every_batch(rg, n_train, batch, K):
 
 @pytest.mark.parametrize("n", [1, 31, 33, 1000, 4096])
 @pytest.mark.parametrize("order", ["ranks", "last two swapped", "shuffled", "all local", "all remote"])
-def test_rows_whatever_order_the_tables_are_in(rg, n, order):
-    """Ten epochs over all nodes, so that the plans look whether row_of is the ranks the slot map knows: where it is, where
-    it is but for two nodes, and where it is any order."""
+@pytest.mark.parametrize("look", ["1", "0"])
+def test_rows_whatever_order_the_tables_are_in(rg, n, order, look, monkeypatch):
+    """Ten epochs over all nodes whose plans look whether row_of is the ranks the slot map knows -- where it is, where it is
+    but for two nodes, and where it is any order -- and plans that do not look."""
+    monkeypatch.setenv("RAPIDGNN_ROW_RANKS", look)
     rng = np.random.default_rng(n)
     d = "cuda"
     indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)

@@ -1,4 +1,5 @@
 """Device memory that builds take beside what they hand out, against what their lists need."""
+import numpy as np
 import pytest
 import torch
 
@@ -23,3 +24,24 @@ def test_scratch_of_the_shuffle(rg):
     s = rg.rg_build_schedule(indptr, indices, torch.arange(n, dtype=torch.int32, device=d), 100_000, [], 5, 0, 0, allocator=a.struct)
     assert a.peak < 20 * n + 12 * n // 64 + n // 8 + (1 << 18)
     del s
+
+
+@pytest.mark.parametrize("look", ["1", "0"])
+def test_scratch_of_a_plan(rg, look, monkeypatch):
+    """Beside its entries (8 bytes a position) and its list of misses (4 a miss), a plan takes a bit per position and 16 bytes per
+    2,048 of them while it is made; looking whether row_of is ranks takes nothing (1/64 of the 4 M positions are 0.06 MB)."""
+    monkeypatch.setenv("RAPIDGNN_ROW_RANKS", look)
+    rng = np.random.default_rng(1)
+    n, d = 4_000_000, "cuda"
+    indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
+    s = rg.rg_build_schedule(indptr, indices, torch.arange(n, dtype=torch.int32, device=d), 100_000, [], 5, 0, 0)
+    is_local = (rng.random(n) < 0.99).astype(np.uint8)
+    row_of = np.where(is_local, np.cumsum(is_local) - 1, np.cumsum(1 - is_local) - 1).astype(np.int32)
+    table = torch.zeros((n, 4), dtype=torch.int32, device=d)
+    feat = rg.make_features(torch.from_numpy(is_local).to(d), torch.from_numpy(row_of).to(d), table, table, 16)
+    a = RecordingAllocator(rg)
+    c = rg.rg_build_cache([s], feat, 0, allocator=a.struct)
+    n_miss = int((is_local == 0).sum())
+    assert a.live < 8 * n + 4 * n_miss + n + n // 2 + (1 << 18)              # entries, misses; the tally's byte and the slot map's half per node
+    assert a.peak - a.live < n // 8 + n // 64 + (1 << 18)
+    del c
