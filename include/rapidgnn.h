@@ -225,7 +225,8 @@ typedef struct rg_features {
  * else 4.  Environment: RAPIDGNN_NARROW_TALLY=0 forbids the byte form;
  * RAPIDGNN_ROW_RANKS=1 / 0 makes the plans look whether row_of numbers the local
  * and the remote nodes in the order of their IDs, in which case they need not read
- * it, / not look (default: from eight listed input nodes per node of the graph on).  Same results either way.  The fill of the table runs on a stream the library
+ * it, / not look (default: from 2^24 listed input nodes on, if they are eight per
+ * node of the graph).  Same results either way.  The fill of the table runs on a stream the library
  * owns, beside the routing work on `stream`; the call returns after both.
  */
 rg_status rg_build_cache(const rg_schedule *const *epochs, uint32_t n_epochs, const rg_features *f,

@@ -443,9 +443,12 @@ struct RouteSources {
 };
 
 // Reading row_of is two thirds of what a plan over many input nodes moves (a batch's IDs touch nearly every line of it), so it
-// is first checked, in one pass, for being the ranks that the slot map knows anyway.  The pass reads row_of once;
-// worth it from RANK_INPUTS_PER_NODE input nodes per node on.
+// is first checked, in one pass, for being the ranks that the slot map knows anyway.  The pass reads row_of once and is a few
+// launches: 8 to 16 us where there is little to save, so it wants RANK_INPUTS_PER_NODE input nodes per node, and RANK_INPUTS
+// (plans that read row_of / that know the ranks: 0.6 M inputs on 30,000 nodes 120 / 131 us, 8.5 M on 1 M 161 / 171, 17 M on
+// 1 M 266 / 243, 42 M on 1 M 475 / 376, 28 M on 233,000 281 / 281, 84 M on 233,000 876 / 793).
 constexpr int64_t RANK_INPUTS_PER_NODE = 8;
+constexpr int64_t RANK_INPUTS = 1 << 24;
 // local_cnt[r] = local IDs among record r's 32
 __global__ void local_counts_kernel(const SlotRec *__restrict__ recs, int64_t n_recs, int32_t *__restrict__ local_cnt)
 {
@@ -874,7 +877,7 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
     RouteSources rs{f->row_of, c->slot_pairs, nullptr};
     int64_t n_inputs = 0;
     for (uint32_t e = 0; e < n_epochs; ++e) n_inputs += epochs[e]->n_batches ? epochs[e]->hop[epochs[e]->L].off_host[epochs[e]->n_batches] : 0;
-    bool look_for_ranks = n_inputs >= RANK_INPUTS_PER_NODE * n;
+    bool look_for_ranks = n_inputs >= RANK_INPUTS_PER_NODE * n && n_inputs >= RANK_INPUTS;
     if (const char *force = getenv("RAPIDGNN_ROW_RANKS")) look_for_ranks = force[0] == '1';      // same results either way; for tests and tuning
     RankCheck check{c->slot_pairs, n, reinterpret_cast<uint32_t *>(bins), look_for_ranks && n > 0};       // (the digits have been chosen)
     for (uint32_t e = 0; e < n_epochs; ++e) RG_TRY(build_plan(epochs[e], rs, check, c->arena, tmp, st, &c->plans[e]));
