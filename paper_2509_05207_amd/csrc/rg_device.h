@@ -132,6 +132,15 @@ __device__ __forceinline__ uint32_t batch_of(const int64_t *__restrict__ off, ui
     return lo;
 }
 
+// What a wave's lanes have written to LDS before is what they read behind it, and what they have read before is not yet
+// overwritten: for memory that one wave has to itself, where no barrier of the workgroup stands between.  The hardware takes a
+// wave's LDS operations in order; the fence keeps the compiler to it and costs no instruction.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------- reached-ID maps
 // Every sampled ID is marked in the batch's `reached` bitmap; which of the reached IDs are new to the batch is decided
 // afterwards, group by group, against the batch's `seen` bitmap.  Beside the map there is one flag byte per 256 IDs: the

@@ -1358,8 +1358,9 @@ __global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
                     waiting += __popcll(m);
                 }
                 waiting = uni(waiting);
-                __builtin_amdgcn_wave_barrier();                 // (one wave's LDS operations are done in order)
+                wave_lds_order();
                 while (waiting >= 64) look_up(64);
+                wave_lds_order();
             }
             if (waiting > 0) look_up(waiting);
             __syncthreads();

@@ -304,7 +304,7 @@ __global__ void __launch_bounds__(FR_THREADS) fresh_emit_kernel(uint32_t *__rest
 #pragma unroll
         for (int k = 0; k < FR_WORDS_PER_THREAD; ++k)
             for (uint32_t x = w[k]; x; x &= x - 1) window[wave][at++] = (uint16_t)(lane * (FR_WORDS_PER_THREAD * 32) + k * 32 + __ffs((int)x) - 1);
-        __builtin_amdgcn_wave_barrier();                         // (the wave's own window: its LDS operations are done in order)
+        wave_lds_order();
         for (int j = lane; j < wave_n; j += 64) next[wave_pos + j] = wave_id0 + window[wave][j];
         return;
     }
