@@ -12,7 +12,7 @@ Prints ONE JSON line.
                   starts, the library's event timers OFF
   roofline        the kernel group with the most device time, from a second pass of the same steps with the
                   library's per-launch HIP event timers ON (they cost a little, so they stay out of `value`); for the
-                  sampler the bound it sits closer to: HBM by the bytes that moved, or the vector unit's integer rate
+                  sampler by the bytes that moved
   pcie_inclusive  the same steps with the remote feature table in pinned host memory -- the configuration's own
                   placement: VectorPull and every miss cross the host link (reported, never `value`)
   cpu_baseline    the CPU oracle on a bounded prefix of the epoch, per call, on one thread and on all cores
@@ -45,17 +45,19 @@ def log(*a):
 
 
 def algorithmic_bytes(rg, sched, indptr, fanout):
-    """Per hop: (frontier nodes, sum of degrees, sampled edges, algorithmic bytes of the sampler launch).
-    Per frontier node: 16 B of indptr, 4 B frontier ID, 8 B sample offset, 4 B per row entry read,
-    4 B per sampled neighbour written."""
+    """Per hop: frontier nodes, the row entries of all of them and of the distinct ones, sampled edges, and the algorithmic
+    bytes of its sampling (accounting.sampler_traffic_bytes)."""
     out = []
     for hop, f in enumerate(fanout):
         ids, _, off = rg.rg_schedule_frontier(sched, hop)
         v = ids.long()
         deg = indptr[v + 1] - indptr[v]
         n, sdeg = int(ids.numel()), int(deg.sum().item())
+        held = torch.zeros(indptr.numel() - 1, dtype=torch.bool, device=indptr.device)
+        held[v] = True
+        distinct = int((indptr[1:] - indptr[:-1])[held].sum().item())
         samp = int(torch.clamp(deg, max=f).sum().item())
-        out.append(dict(nodes=n, sum_deg=sdeg, sampled=samp, bytes=n * (16 + 4 + 8) + 4 * sdeg + 4 * samp))
+        out.append(dict(nodes=n, sum_deg=sdeg, distinct=distinct, sampled=samp, bytes=accounting.sampler_traffic_bytes(n, distinct, samp)))
     return out
 
 
@@ -398,7 +400,6 @@ def measure(rg, name, args, full):
     gath_gbps, gath_frac = group_rate(gath_ms, gath_bytes)
     samp_launches = max(1, prof["sampler"]["launches"] // steps)
     gath_launches = max(1, (prof["gather"]["launches"] + prof["gather_miss"]["launches"]) // steps)
-    scanned = sum(h["sum_deg"] for h in hops)
     result = {
         "value": value, "unit": "sampled edges/s", "steps": steps, "warmup": warmup, "ms_per_step": ms_per_step,
         "ms_per_step_with_event_timers": dt_prof / steps * 1e3,
@@ -410,10 +411,8 @@ def measure(rg, name, args, full):
                    "K_eff": int(k_eff)},
         "sampler": {"kernel": "sample_kernel", "edges_per_s_kernel": sampled_edges / (samp_ms * 1e-3) if samp_ms else None, "GBps": samp_gbps,
                     "frac_hbm": samp_frac, "ms_per_step": samp_ms, "launches_per_step": samp_launches,
-                    "algorithmic_bytes_per_step": samp_bytes, "scanned_row_entries": scanned,
-                    "int_ops_per_step": accounting.sampler_int_ops(scanned),
-                    "TOPps": accounting.sampler_int_ops(scanned) / (samp_ms * 1e-3) / 1e12 if samp_ms else None,
-                    "frac_alu": accounting.sampler_int_ops(scanned) / (samp_ms * 1e-3) / 1e12 / accounting.INT32_VECTOR_PEAK_TOPS if samp_ms else None},
+                    "algorithmic_bytes_per_step": samp_bytes, "row_entries_of_frontiers": sum(h["sum_deg"] for h in hops),
+                    "row_entries_of_distinct_nodes": sum(h["distinct"] for h in hops)},
         "gather": {"kernel": "gather_rows_kernel", "GBps": gath_gbps, "frac_hbm": gath_frac, "ms_per_step": gath_ms,
                    "launches_per_step": gath_launches, "algorithmic_bytes_per_step": gath_bytes,
                    "delivered_GBps": rows_per_epoch * W.row_bytes / (gath_ms * 1e-3) / 1e9 if gath_ms else None},
@@ -445,24 +444,18 @@ def measure(rg, name, args, full):
         roof["traffic_source"] = ("stored: separate rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command "
                                   "(profiles/measured_traffic.json), not read in this run")
     if key == "sampler":
-        # The sampler reads a hub's row once per batch that holds the hub, and hands those reads out so that they meet in
-        # the caches: its HBM traffic can then be a fraction of its algorithmic bytes, and its algorithmic bytes per
-        # second can pass the HBM peak.  Whichever of its two bounds it sits closer to is the one reported: HBM by the
-        # bytes that really moved (the stored counter figure; the algorithmic bytes where none is stored), or the vector
-        # unit's integer rate by the operations the keys need.
-        hbm_bytes = g.get("traffic_per_step", g["algorithmic_bytes_per_step"])
-        frac_hbm_moved = hbm_bytes / (g["ms_per_step"] * 1e-3) / 1e9 / HBM_PEAK_GBPS
-        roof["hbm"] = {"algorithmic_GBps": g["GBps"], "algorithmic_frac": g["frac_hbm"], "moved_GBps": frac_hbm_moved * HBM_PEAK_GBPS,
-                       "moved_frac": frac_hbm_moved}
-        if g["frac_alu"] > frac_hbm_moved:
-            roof.update(bound="alu", achieved=g["TOPps"], peak=accounting.INT32_VECTOR_PEAK_TOPS, unit="TOP/s", frac=g["frac_alu"],
-                        int_ops_per_launch=g["int_ops_per_step"] / launches, int_ops_per_step=g["int_ops_per_step"],
-                        int_ops_per_scanned_row_entry=accounting.SAMPLER_INT_OPS_PER_ENTRY)
+        # Its algorithmic bytes count every distinct row of a hop once.  What moves is more (a row is read once per batch
+        # that holds its node, less what the caches serve) or less (the longest rows are looked up, not read), so the
+        # rate reported is that of the bytes that moved, where they have been counted.  No share of the vector unit's
+        # rate is given: how many keys a launch computes is decided inside the library.
+        roof["algorithmic_GBps"], roof["algorithmic_frac"] = g["GBps"], g["frac_hbm"]
+        if "traffic_per_step" in g:
+            roof["achieved"], roof["frac"] = group_rate(g["ms_per_step"], g["traffic_per_step"])
     copy_gbps = device_copy_gbps()
     roof["device_copy_GBps"] = copy_gbps                       # a 1 GiB device-to-device copy on this machine, read + write
     roof["algorithmic_GBps_over_device_copy"] = g["GBps"] / copy_gbps
     log(f"[bench] plain device-to-device copy of 1 GiB: {copy_gbps:.0f} GB/s read+write; {roof['kernel']} reaches {g['GBps']:.0f} GB/s of algorithmic bytes"
-        + (f", {roof['achieved']:.1f} of {roof['peak']:.1f} TOP/s of integer arithmetic" if roof["bound"] == "alu" else ""))
+        + f", {roof['achieved']:.0f} GB/s of the bytes reported")
     result["roofline"] = roof
     result["access_stats"] = access_stats
 

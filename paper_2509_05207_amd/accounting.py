@@ -38,13 +38,8 @@ def gather_group(n_batches: int, rows_per_epoch: int, stride_bytes: int) -> int:
     return g
 
 
-# The sampler's arithmetic per scanned row entry: ten 32-bit integer operations for the key of a neighbour ID (an XOR,
-# three multiplies, three shifts, two XORs and one add folded into them as the instruction set allows) and one compare
-# against the running cut.  The vector unit's peak for such operations: 256 compute units x 64 lanes x 2.4 GHz, one
-# operation per lane and cycle (no fused multiply-add or packed forms apply to 32-bit integer multiplies and XORs).
-SAMPLER_INT_OPS_PER_ENTRY = 11
-INT32_VECTOR_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
-
-
-def sampler_int_ops(scanned_row_entries: int) -> int:
-    return SAMPLER_INT_OPS_PER_ENTRY * int(scanned_row_entries)
+def sampler_traffic_bytes(n_nodes: int, distinct_row_entries: int, n_sampled: int) -> int:
+    """Algorithmic bytes of one hop of the row-ranking sampler: per frontier node 16 bytes of indptr, a 4-byte ID and an
+    8-byte sample offset; every distinct row read once, 4 bytes an entry, however many batches hold its node; 4 bytes per
+    sampled neighbour written."""
+    return n_nodes * (16 + 4 + 8) + 4 * distinct_row_entries + 4 * n_sampled
