@@ -145,7 +145,7 @@ __device__ __forceinline__ void wave_lds_order()
 // Every sampled ID is marked in the batch's `reached` bitmap; which of the reached IDs are new to the batch is decided
 // afterwards, group by group, against the batch's `seen` bitmap.  Beside the map there is one flag byte per 256 IDs: the
 // frontier passes read the flags and touch only the flagged groups, which on a graph of 10^8 nodes is a few per cent of
-// the map.  Where a hop's samples are dense enough in the bitmaps, a pass over them puts the bitmaps together in LDS piece
+// the map.  Where a hop's samples are many and dense in the bitmaps, a pass over them puts the bitmaps together in LDS piece
 // by piece (mark_pass_kernel) and the sampling kernels mark nothing; elsewhere they mark each ID as they write it, by an
 // atomic OR without return value which the wave does not wait for.
 constexpr int MARK_NONE = 0, MARK_BITS = 1;      // what a kernel does with a sampled ID (a template argument)

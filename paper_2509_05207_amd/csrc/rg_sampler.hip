@@ -34,9 +34,12 @@
 //    Tiles are dealt out by workgroup index and done before the groups of
 //    nodes, which the waves then take from a counter as they become free.
 //
+//  - the very longest rows, where a hop holds many of them, are not read but
+//    sampled from the keys' side (hub_sample_kernel).
+//
 // No step sorts anything.  What a batch has reached is marked in its bitmap by
-// a pass over the samples (mark_pass_kernel), or, on graphs whose bitmaps are
-// too large for that, by the sampling waves as they write the samples.
+// a pass over the samples (mark_pass_kernel) where they are many and dense in
+// the bitmaps, else by the sampling waves as they write them.
 #include "rg_internal.h"
 #include "rg_device.h"
 

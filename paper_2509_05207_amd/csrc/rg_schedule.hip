@@ -117,7 +117,7 @@ __global__ void mark_seeds_kernel(const int32_t *__restrict__ seeds, uint64_t T,
     const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= T) return;
     const uint32_t v = (uint32_t)seeds[t];
-    if ((int64_t)v >= n_nodes) return;          // (refused by the host as soon as it has read check_train_kernel's count)
+    if ((int64_t)v >= n_nodes) return;          // (refused by the host as soon as it has read shuffle_count_kernel's count)
     const uint64_t word = (t / batch_size) * words_per_batch + (v >> 5);
     atomicOr(&seen[paired ? paired_word(word) : word], 1u << (v & 31));
     if (seen_flags) seen_flags[word >> 3] = 1;          // (NULL in the large-graph form: see clear_listed_seen_kernel)
