@@ -470,8 +470,8 @@ __global__ void row_ranks_kernel(SlotRec *recs, int64_t n, const int64_t *__rest
 }
 
 // entry[j] = where ids[j] is served from, for every listed input node, which of them are misses (one
-// bit each, in position order: a wave's ballot is the 64-bit word of its 64 consecutive positions), and how many misses and
-// how many local rows each tile of PLAN_TILE positions holds.  Nothing is added up per batch here: the tiles of a batch run at the
+// bit each, in position order: a wave's ballot is the 64-bit word of its 64 consecutive positions), how many misses each tile
+// of PLAN_TILE positions holds and how many local rows each PLAN_GROUP of them.  Nothing is added up per batch here: the tiles of a batch run at the
 // same time, and two adds per tile to the batch's counters queued up behind each other (an epoch of 80 M input nodes in
 // 196 batches: 712 us with the adds, 494 with tiles of 1,024 positions without them, 441 so; 111 M nodes, 4.2 M input
 // nodes: 253 -> 122).  The kernel waits for its dependent reads (ID, slot-map record, row), so each kind
@@ -480,12 +480,14 @@ constexpr int PLAN_THREADS = 256;
 constexpr int PLAN_PER_THREAD = 8;
 constexpr int PLAN_TILE = PLAN_THREADS * PLAN_PER_THREAD;
 constexpr int PLAN_TILE_WORDS = PLAN_TILE / 64;          // bit words per tile
+constexpr int PLAN_GROUP = 2 * PLAN_THREADS;             // positions to a count of local rows
+constexpr int PLAN_TILE_GROUPS = PLAN_TILE / PLAN_GROUP;
 
 __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__restrict__ ids, int64_t n, RouteSources rs, int64_t *__restrict__ entry,
                                                             unsigned long long *__restrict__ miss_bits /* [tiles * PLAN_TILE_WORDS] */,
-                                                            int32_t *__restrict__ tile_miss /* [tiles] */, int32_t *__restrict__ tile_local /* [tiles] */)
+                                                            int32_t *__restrict__ tile_miss /* [tiles] */, uint16_t *__restrict__ group_local /* [tiles * PLAN_TILE_GROUPS] */)
 {
-    __shared__ int red[2][PLAN_THREADS / 64];
+    __shared__ int red[1 + PLAN_TILE_GROUPS][PLAN_THREADS / 64];
     const int64_t tile0 = (int64_t)blockIdx.x * PLAN_TILE;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool ranks = rs.not_ranks && *rs.not_ranks == 0u;
@@ -506,7 +508,7 @@ __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__res
             row[k] = (int32_t)((rec[k].z & bit) ? local : v[k] - local);
         } else row[k] = rs.row_of[v[k]];
     }
-    int n_local = 0, n_miss = 0;                           // of the wave
+    int n_local[PLAN_TILE_GROUPS] = {}, n_miss = 0;        // of the wave
 #pragma unroll
     for (int k = 0; k < PLAN_PER_THREAD; ++k) {
         const int64_t j = tile0 + (int64_t)k * PLAN_THREADS + threadIdx.x;
@@ -515,15 +517,20 @@ __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__res
         if (j < n) __builtin_nontemporal_store(make_entry(local ? TAG_LOCAL : cached ? TAG_CACHE : TAG_REMOTE, row[k]), entry + j);
         const unsigned long long ml = __ballot(j < n && local), mm = __ballot(j < n && !local && !cached);
         if (lane == 0) miss_bits[(uint64_t)blockIdx.x * PLAN_TILE_WORDS + k * (PLAN_THREADS / 64) + wave] = mm;
-        n_local += __popcll(ml);
+        n_local[k / 2] += __popcll(ml);
         n_miss += __popcll(mm);
     }
-    if (lane == 0) { red[0][wave] = n_miss; red[1][wave] = n_local; }
+    if (lane == 0) {
+        red[0][wave] = n_miss;
+#pragma unroll
+        for (int q = 0; q < PLAN_TILE_GROUPS; ++q) red[1 + q][wave] = n_local[q];
+    }
     __syncthreads();
-    if (threadIdx.x < 2) {
+    if (threadIdx.x <= PLAN_TILE_GROUPS) {
         int c = 0;
         for (int w = 0; w < PLAN_THREADS / 64; ++w) c += red[threadIdx.x][w];
-        (threadIdx.x == 0 ? tile_miss : tile_local)[blockIdx.x] = c;
+        if (threadIdx.x == 0) tile_miss[blockIdx.x] = c;
+        else group_local[(uint64_t)blockIdx.x * PLAN_TILE_GROUPS + threadIdx.x - 1] = (uint16_t)c;
     }
 }
 
@@ -540,49 +547,41 @@ __device__ __forceinline__ int64_t lane_bits_between(const unsigned long long *_
     return cnt;
 }
 
-// Entries among positions [lo, hi) that are local, counted by a workgroup (the sum is the threads' together).
-constexpr int COUNT_THREADS = 256;
-constexpr int COUNT_IN_FLIGHT = PLAN_TILE / COUNT_THREADS;
-__device__ __forceinline__ int64_t thread_local_rows_between(const int64_t *__restrict__ entry, int64_t lo, int64_t hi)      // (within one tile)
-{
-    int64_t e[COUNT_IN_FLIGHT], cnt = 0;
-#pragma unroll
-    for (int k = 0; k < COUNT_IN_FLIGHT; ++k) {
-        const int64_t j = lo + k * COUNT_THREADS + threadIdx.x;
-        e[k] = j < hi ? entry[j] : make_entry(TAG_REMOTE, 0);
-    }
-#pragma unroll
-    for (int k = 0; k < COUNT_IN_FLIGHT; ++k) cnt += entry_tag(e[k]) == TAG_LOCAL ? 1 : 0;
-    return cnt;
-}
-
 // One workgroup per batch (and one for the end).  miss_off[b] = misses in front of batch b's first position: those of the
 // tiles in front of its tile (tile_scan) and of the positions in front of it inside the tile; n_local[b] = its local
-// rows: the whole tiles between its ends, and the entries of the tiles it begins and ends in.
+// rows: those of the whole groups between its ends, and the entries in front of and behind them.  Bound by its dependent
+// reads, of which there are two: the batch's ends, then everything else at once (a plan of 500,000 entries in 145 batches 5.2 us; with
+// whole tiles counted and the entries of the end tiles read, 10.0).
+constexpr int COUNT_THREADS = 256;
+constexpr int COUNT_IN_FLIGHT = PLAN_GROUP / COUNT_THREADS;
 __global__ void __launch_bounds__(COUNT_THREADS) batch_counts_kernel(const unsigned long long *__restrict__ miss_bits, const int64_t *__restrict__ entry,
-                                                                     const int64_t *__restrict__ tile_scan, const int32_t *__restrict__ tile_local, int64_t n, int64_t n_tiles,
+                                                                     const int64_t *__restrict__ tile_scan, const uint16_t *__restrict__ group_local, int64_t n, int64_t n_tiles,
                                                                      const int64_t *__restrict__ batch_off, uint32_t n_batches, int64_t *__restrict__ miss_off,
                                                                      int64_t *__restrict__ n_local)
 {
     __shared__ int64_t part[COUNT_THREADS / 64];
     const uint32_t b = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t lo = batch_off[b], t_lo = lo / PLAN_TILE;
-    int64_t before = lo < n && wave == 0 ? lane_bits_between(miss_bits, t_lo * PLAN_TILE, lo, lane) : 0;
-    int64_t local = 0;
-    if (b < n_batches) {
-        const int64_t hi = batch_off[b + 1], t_hi = hi / PLAN_TILE;
-        if (t_lo == t_hi) local = thread_local_rows_between(entry, lo, hi);
-        else {
-            local = thread_local_rows_between(entry, lo, (t_lo + 1) * PLAN_TILE) + thread_local_rows_between(entry, t_hi * PLAN_TILE, hi);
-            for (int64_t t = t_lo + 1 + threadIdx.x; t < t_hi; t += COUNT_THREADS) local += tile_local[t];
-        }
+    const int64_t lo = batch_off[b], hi = batch_off[min(b + 1, n_batches)];      // (the end: no positions)
+    const int64_t g_lo = (lo + PLAN_GROUP - 1) / PLAN_GROUP, g_hi = hi / PLAN_GROUP;      // whole groups [g_lo, g_hi), if any
+    const int64_t front_end = g_lo <= g_hi ? g_lo * PLAN_GROUP : hi, back = g_lo <= g_hi ? g_hi * PLAN_GROUP : hi;
+    int64_t e[2 * COUNT_IN_FLIGHT], local = 0;
+#pragma unroll
+    for (int k = 0; k < COUNT_IN_FLIGHT; ++k) {
+        const int64_t j = lo + k * COUNT_THREADS + threadIdx.x, i = back + k * COUNT_THREADS + threadIdx.x;
+        e[2 * k] = j < front_end ? entry[j] : make_entry(TAG_REMOTE, 0);
+        e[2 * k + 1] = i < hi ? entry[i] : make_entry(TAG_REMOTE, 0);
     }
+    for (int64_t g = g_lo + threadIdx.x; g < g_hi; g += COUNT_THREADS) local += group_local[g];
+    int64_t before = lo < n && wave == 0 ? lane_bits_between(miss_bits, lo / PLAN_TILE * PLAN_TILE, lo, lane) : 0;
+    const int64_t scan_here = tile_scan[lo < n ? lo / PLAN_TILE : n_tiles];
+#pragma unroll
+    for (int k = 0; k < 2 * COUNT_IN_FLIGHT; ++k) local += entry_tag(e[k]) == TAG_LOCAL ? 1 : 0;
     for (int o = 32; o > 0; o >>= 1) { before += __shfl_down(before, o, 64); local += __shfl_down(local, o, 64); }
     if (lane == 0) part[wave] = local;
     __syncthreads();
     if (threadIdx.x == 0) {
-        miss_off[b] = lo < n ? tile_scan[t_lo] + before : tile_scan[n_tiles];
+        miss_off[b] = scan_here + before;
         if (b < n_batches) n_local[b] = part[0] + part[1] + part[2] + part[3];
     }
 }
@@ -654,11 +653,12 @@ rg_status build_plan(const rg_schedule *s, RouteSources &rs, RankCheck &check, A
 
     const int64_t n_tiles = (n + PLAN_TILE - 1) / PLAN_TILE, n_words = n_tiles * PLAN_TILE_WORDS;
     unsigned long long *miss_bits = nullptr;
-    int32_t *tile_miss = nullptr, *tile_local = nullptr;
+    int32_t *tile_miss = nullptr;
+    uint16_t *group_local = nullptr;
     int64_t *tile_scan = nullptr, *miss_off_dev = nullptr, *n_local_dev = nullptr;
     RG_TRY(tmp.dev_n<unsigned long long>((uint64_t)std::max<int64_t>(n_words, 1), &miss_bits));
     RG_TRY(tmp.dev_n<int32_t>((uint64_t)std::max<int64_t>(n_tiles, 1), &tile_miss));
-    RG_TRY(tmp.dev_n<int32_t>((uint64_t)std::max<int64_t>(n_tiles, 1), &tile_local));
+    RG_TRY(tmp.dev_n<uint16_t>((uint64_t)std::max<int64_t>(n_tiles, 1) * PLAN_TILE_GROUPS, &group_local));
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_tiles + 1, &tile_scan));
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)beta + 1, &miss_off_dev));
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)beta, &n_local_dev));
@@ -670,9 +670,9 @@ rg_status build_plan(const rg_schedule *s, RouteSources &rs, RankCheck &check, A
             check.pending = false;
         }
         if (n > 0)
-            hipLaunchKernelGGL(plan_kernel, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, plan->entry, miss_bits, tile_miss, tile_local);
+            hipLaunchKernelGGL(plan_kernel, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, plan->entry, miss_bits, tile_miss, group_local);
         RG_TRY(scan_i32_to_i64(tile_miss, tile_scan, n_tiles, tmp, st));
-        hipLaunchKernelGGL(batch_counts_kernel, dim3(beta + 1), dim3(COUNT_THREADS), 0, st, miss_bits, plan->entry, tile_scan, tile_local, n, n_tiles, h.off_dev, beta, miss_off_dev, n_local_dev);
+        hipLaunchKernelGGL(batch_counts_kernel, dim3(beta + 1), dim3(COUNT_THREADS), 0, st, miss_bits, plan->entry, tile_scan, group_local, n, n_tiles, h.off_dev, beta, miss_off_dev, n_local_dev);
     }
     std::vector<int64_t> n_local(beta);
     {

@@ -28,7 +28,7 @@ def test_scratch_of_the_shuffle(rg):
 
 @pytest.mark.parametrize("look", ["1", "0"])
 def test_scratch_of_a_plan(rg, look, monkeypatch):
-    """Beside its entries (8 bytes a position) and its list of misses (4 a miss), a plan takes a bit per position and 16 bytes per
+    """Beside its entries (8 bytes a position) and its list of misses (4 a miss), a plan takes a bit per position and 20 bytes per
     2,048 of them while it is made; looking whether row_of is ranks takes nothing (1/64 of the 4 M positions are 0.06 MB)."""
     monkeypatch.setenv("RAPIDGNN_ROW_RANKS", look)
     rng = np.random.default_rng(1)
