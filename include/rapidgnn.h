@@ -234,7 +234,7 @@ rg_status rg_build_cache(const rg_schedule *const *epochs, uint32_t n_epochs, co
 
 /* Views of the cache: K_eff, the cached ids (dev, ascending), freq (dev,
  * [n_nodes]), slot_of (dev, [n_nodes], -1 = not cached), the table and its row
- * stride (the bytes of the table behind a row are zero).  Any output pointer may be NULL.  The cache itself keeps slot_of as
+ * stride.  Any output pointer may be NULL.  The cache itself keeps slot_of as
  * a rank map and, where it could, the tally in bytes: the first call that asks
  * for slot_of (for freq) makes the array (4 bytes per node from the cache's
  * allocator, one kernel, waited for); calls that pass NULL for both never pay

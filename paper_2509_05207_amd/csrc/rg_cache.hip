@@ -739,14 +739,6 @@ rg_status cache_slot_view(const rg_cache *cc, const int32_t **out)
     return RG_OK;
 }
 
-// The last 16 bytes of every row, in front of the fill: what a row leaves of them (the stride is its bytes rounded up to 16) is
-// then zero and not what the memory held, so that a table is the same bytes whenever it is built.
-__global__ void clear_row_ends_kernel(uint8_t *__restrict__ rows, uint64_t n_rows, uint64_t stride)
-{
-    const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < n_rows) *reinterpret_cast<uint4 *>(rows + (r + 1) * stride - 16) = make_uint4(0, 0, 0, 0);
-}
-
 static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_epochs, const rg_features *f, uint64_t K,
                                   const rg_allocator *a, hipStream_t st, rg_cache *c)
 {
@@ -876,11 +868,6 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
         forked.side = side;
         RowSources src{(const uint8_t *)f->local_rows, f->local_stride, (const uint8_t *)c->rows, c->stride,
                        (const uint8_t *)f->remote_rows, f->remote_stride};
-        if (c->stride > f->row_bytes) {
-            ScopedTimer tm(KG_FILL, side);
-            hipLaunchKernelGGL(clear_row_ends_kernel, dim3((unsigned)((c->K_eff + 255) / 256)), dim3(256), 0, side, (uint8_t *)c->rows, (uint64_t)c->K_eff, c->stride);
-            RG_HIP(hipGetLastError());
-        }
         RG_TRY(launch_gather(fill_entries, (int64_t)c->K_eff, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)c->rows, c->stride, side, KG_FILL));
         RG_HIP(hipEventRecord(c->ev_join, side));
     }

@@ -4,10 +4,9 @@ import torch
 
 class RecordingAllocator:
     """live, peak: device bytes handed out, now and at most; requested: their sum over all requests.  total_bytes: a request that
-    would take `live` above it is refused (NULL to the library), as an allocator that has run out would.  fill: the byte that device
-    memory holds when it is handed out."""
+    would take `live` above it is refused (NULL to the library), as an allocator that has run out would."""
 
-    def __init__(self, rg, total_bytes=None, fill=None):
+    def __init__(self, rg, total_bytes=None):
         self.blocks, self.live, self.peak, self.requested, self.n_refused = {}, 0, 0, 0, 0
 
         def alloc(nbytes, kind, _ctx):
@@ -16,9 +15,6 @@ class RecordingAllocator:
                 self.n_refused += 1
                 return None
             t = torch.empty(n, dtype=torch.uint8, device="cuda") if kind == 1 else torch.empty(n, dtype=torch.uint8, pin_memory=True)
-            if kind == 1 and fill is not None:
-                t.fill_(fill)
-                torch.cuda.synchronize()
             self.blocks[t.data_ptr()] = (t, n if kind == 1 else 0)
             if kind == 1:
                 self.live += n

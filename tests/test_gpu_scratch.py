@@ -1,4 +1,4 @@
-"""Device memory that builds take beside what they hand out, against what their lists need; and what they leave in it."""
+"""Device memory that builds take beside what they hand out, against what their lists need."""
 import numpy as np
 import pytest
 import torch
@@ -45,19 +45,3 @@ def test_scratch_of_a_plan(rg, look, monkeypatch):
     assert a.live < 8 * n + 4 * n_miss + n + n // 2 + (1 << 18)              # entries, misses; the tally's byte and the slot map's half per node
     assert a.peak - a.live < n // 8 + n // 64 + (1 << 18)
     del c
-
-
-@pytest.mark.parametrize("row_bytes", [1, 15, 16, 38, 100, 112])
-def test_table_bytes_do_not_depend_on_the_memory_they_are_in(rg, row_bytes):
-    rng = np.random.default_rng(row_bytes)
-    n, d = 5000, "cuda"
-    indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
-    s = rg.rg_build_schedule(indptr, indices, torch.from_numpy(rng.permutation(n)[:3000].astype(np.int32)).to(d), 700, [], 5, 0, 0)
-    table = torch.from_numpy(rng.integers(1, 255, size=(n, row_bytes)).astype(np.uint8)).to(d)
-    feat = rg.make_features(torch.zeros(n, dtype=torch.uint8, device=d), torch.arange(n, dtype=torch.int32, device=d), table[:1].clone(), table, row_bytes)
-    a = RecordingAllocator(rg, fill=0xA5)
-    c = rg.rg_build_cache([s], feat, 2000, allocator=a.struct)
-    v = rg.rg_cache_view(c, n)
-    want = torch.zeros((2000, (row_bytes + 15) // 16 * 16), dtype=torch.uint8, device=d)
-    want[:, :row_bytes] = table[v["cache_ids"].long()]
-    assert torch.equal(v["rows"].view(torch.uint8).reshape(want.shape), want)
