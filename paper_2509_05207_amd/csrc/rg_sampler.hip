@@ -127,8 +127,8 @@ __device__ __forceinline__ bool add_hub_row(const HubTable &h, uint32_t v, int64
 // Also adds up, over the frontier, what the hop will read of the adjacency: [0] the sum of the degrees (in IDs),
 // [1] the part of it in rows of up to BIG_ROW IDs (the rows that are not sampled as tiles), [2] the number of rows of
 // 1 .. SHORT_ROW IDs and [3] the IDs in them; of flagged hub rows, [4] how many and [5] how many tiles they make.  The
-// sums are spread over DEG_SUM_SLOTS sets of counters, total[DEG_SUMS * slot + k], which the host adds up: thousands of
-// workgroups adding to one address would queue up behind each other.
+// sums (the first four where no hub rows are looked for) are spread over DEG_SUM_SLOTS sets of counters, total[number of
+// sums * slot + k], which the host adds up: thousands of workgroups adding to one address would queue up behind each other.
 constexpr int DEG_SUM_SLOTS = 64;
 constexpr int DEG_SUMS = 6;
 constexpr int SHORT_ROW = 64;            // rows of up to this many IDs are sampled four at a time, sixteen lanes each
@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(NODE_THREADS) node_records_kernel(const int64_
         const unsigned long long a = part[threadIdx.x][0] + part[threadIdx.x][1] + part[threadIdx.x][2] + part[threadIdx.x][3];
         if (HUBS && threadIdx.x == 5) chunk_hub[blockIdx.x] = (uint32_t)a;
         if (threadIdx.x == SUMS) chunk_sum[blockIdx.x] = a;
-        else if (a) atomicAdd(total + DEG_SUMS * (blockIdx.x % DEG_SUM_SLOTS) + threadIdx.x, a);
+        else if (a) atomicAdd(total + SUMS * (blockIdx.x % DEG_SUM_SLOTS) + threadIdx.x, a);
     }
 }
 
@@ -1493,7 +1493,8 @@ constexpr int MARK_THREADS = 1024;
 constexpr int MARK_WORDS = 32768;                        // 128 KB of LDS, 1,048,576 IDs: every piece reads all samples of its batch, so few large ones (of 64 KB: 0.54 ms for the 167 M below, so 0.43)
 constexpr int MARK_XCDS = 8;
 constexpr int MARK_IN_FLIGHT = 8;
-constexpr uint64_t MARK_SPARSE = 512, MARK_MANY = 1 << 21, MARK_CROWD = 96;      // see sample_hop
+constexpr uint64_t MARK_SPARSE = 512, MARK_MANY = 1 << 21, MARK_CROWD = 64;      // see marks_want_a_pass
+constexpr uint64_t MARK_PASS = 320 << 10, MARK_ROUND = 240 << 10;
 constexpr int64_t MARK_PART = 1 << 18;                   // samples per part, at least, where there are too few pieces to fill the chip
 
 __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *__restrict__ samp_nbr, const int64_t *__restrict__ samp_off, const int64_t *__restrict__ batch_off,
@@ -1547,10 +1548,32 @@ __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *
     }
 }
 
+static uint32_t mark_piece_words(const ReachedMaps &m) { return (uint32_t)std::min<uint64_t>(MARK_WORDS, m.words_per_batch); }      // (both multiples of eight)
+
+// By a pass or by the sampling kernels themselves.  The pass clears and looks through the words of every batch's bitmap, some
+// 6 us per 128 KB of LDS and compute unit, and 8 us for itself, more where a few workgroups have all the samples; an atomic OR
+// costs 25 to 40 ps where little hides it, next to nothing while rows are read, and more where many meet on a word.  So the pass
+//  - from one sample per MARK_SPARSE IDs of bitmap on: 2.45 M nodes, one hop, fan-out 30, marked by the kernels / by the
+//    pass: keys sampler one per 2,848 445 / 525 us, 1,424 1,076 / 1,094, 712 810 / 787, 356 587 / 539 (positions sampler
+//    958 / 1,077, 702 / 778, 498 / 541; two hops, one per 148 in the second, 997 / 920);
+//  - there, from MARK_MANY samples on, or MARK_CROWD per word (sampling of one batch, fan-outs 50,50, 2.45 M nodes, 512 seeds
+//    (1 M samples in the second hop) 185 / 230 us, 4,096 seeds 407 / 344, 15,000 seeds 934 / 583; 30,000 nodes, 4,096 seeds
+//    154 / 106; ten batches on 40,000 nodes, 1.2 M samples, 91 per word, 287 / 280);
+//  - and where its workgroups are a quarter of the compute units and more, from as many samples on as cost what it does: MARK_PASS
+//    and MARK_ROUND per round of full workgroups (113 batches on 76,000 nodes, 115,000 and 1 M samples, 393 / 384 us).
+static bool marks_want_a_pass(const ReachedMaps &m, uint32_t beta, uint64_t n_marks, int n_cu)
+{
+    const uint64_t words = m.words_per_batch * (uint64_t)beta, piece_words = mark_piece_words(m);
+    if (n_marks * MARK_SPARSE < words * 32) return false;
+    if (n_marks >= MARK_MANY || n_marks >= words * MARK_CROWD) return true;
+    const uint64_t units = (m.words_per_batch + piece_words - 1) / piece_words * beta, cus = (uint64_t)n_cu;
+    return units * 4 >= cus && n_marks >= MARK_PASS + MARK_ROUND * ((units + cus - 1) / cus) * piece_words / MARK_WORDS;
+}
+
 static rg_status launch_mark_pass(const HopData &cur, uint32_t beta, const ReachedMaps &m, int n_cu, hipStream_t st)
 {
     if (cur.n_samples == 0) return RG_OK;
-    const uint32_t piece_words = (uint32_t)std::min<uint64_t>(MARK_WORDS, m.words_per_batch);          // (both multiples of eight)
+    const uint32_t piece_words = mark_piece_words(m);
     const uint32_t pieces = (uint32_t)((m.words_per_batch + piece_words - 1) / piece_words);
     // a few batches of many samples are read in parts, whose bits are ORed into the map
     const uint64_t units = (uint64_t)pieces * beta;
@@ -1601,9 +1624,11 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     RG_TRY(keep.dev_n<int64_t>((uint64_t)n_cur + 1, &cur.samp_off));
     unsigned long long sums[DEG_SUMS] = {}, *sum_deg_dev = nullptr;       // see node_records_kernel
     unsigned long long sum_parts[DEG_SUMS * DEG_SUM_SLOTS];
+    const int n_sums = look_for_hubs ? DEG_SUMS : DEG_SUMS - 2;
+    const size_t sum_bytes = (size_t)n_sums * DEG_SUM_SLOTS * sizeof(unsigned long long);
     const size_t hub_cleared = look_for_hubs ? sizeof(HubCounts) + HUB_SLOTS * sizeof(uint32_t) : 0;      // behind the sums, cleared with them
-    RG_TRY(tmp.dev(sizeof(sum_parts) + hub_cleared, (void **)&sum_deg_dev));
-    RG_HIP(hipMemsetAsync(sum_deg_dev, 0, sizeof(sum_parts) + hub_cleared, st));
+    RG_TRY(tmp.dev(sum_bytes + hub_cleared, (void **)&sum_deg_dev));
+    RG_HIP(hipMemsetAsync(sum_deg_dev, 0, sum_bytes + hub_cleared, st));
     if (look_for_hubs) {
         hubs.counts = reinterpret_cast<HubCounts *>(sum_deg_dev + DEG_SUMS * DEG_SUM_SLOTS);
         hubs.keys = reinterpret_cast<uint32_t *>(hubs.counts + 1);
@@ -1628,27 +1653,17 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     HubCounts hub_counts{};
     {
         Readback rb(st);
-        RG_TRY(rb.add(sum_parts, sum_deg_dev, sizeof(sum_parts)));
+        RG_TRY(rb.add(sum_parts, sum_deg_dev, sum_bytes));
         RG_TRY(rb.add(&cur.n_samples, cur.samp_off + n_cur, sizeof(int64_t)));
         RG_TRY(rb.add(&n_tiles, tile_base + n_chunks, sizeof(int64_t)));
         if (look_for_hubs) RG_TRY(rb.add(&hub_counts, hubs.counts, sizeof(hub_counts)));
         if (also_read_dev) RG_TRY(rb.add(also_read_host, also_read_dev, sizeof(unsigned long long)));     // a value the caller wants behind the same wait
         RG_TRY(rb.wait());
         for (int k = 0; k < DEG_SUM_SLOTS; ++k)
-            for (int q = 0; q < DEG_SUMS; ++q) sums[q] += sum_parts[DEG_SUMS * k + q];
+            for (int q = 0; q < n_sums; ++q) sums[q] += sum_parts[n_sums * k + q];
         if (also_read_dev && *also_read_host != 0) return RG_OK;        // the caller refuses the build: nothing more to launch
     }
-    // By a pass or by the sampling kernels themselves.  The pass clears and looks through the words of every batch's bitmap,
-    // some 6 us per 128 KB of LDS and compute unit and 8 us for itself; an atomic OR costs 40 ps where nothing hides it, next
-    // to nothing while rows are read, and more where many meet on a word.  So the pass
-    //  - from one sample per MARK_SPARSE IDs of bitmap on: 2.45 M nodes, one hop, fan-out 30, marked by the kernels / by the
-    //    pass: keys sampler one per 2,848 445 / 525 us, 1,424 1,076 / 1,094, 712 810 / 787, 356 587 / 539 (positions sampler
-    //    958 / 1,077, 702 / 778, 498 / 541; two hops, one per 148 in the second, 997 / 920);
-    //  - there, from MARK_MANY samples on or MARK_CROWD per word: sampling one batch, fan-outs 50,50, 2.45 M nodes, 512 seeds
-    //    (1 M samples in the second hop) 185 / 230 us, 4,096 seeds 407 / 344, 15,000 seeds 934 / 583; 30,000 nodes, 4,096
-    //    seeds 154 / 106.
-    const uint64_t mark_words = reached.words_per_batch * (uint64_t)beta, n_marks = (uint64_t)cur.n_samples;
-    bool inline_marks = reached.paired || n_marks * MARK_SPARSE < mark_words * 32 || (n_marks < MARK_MANY && n_marks < mark_words * MARK_CROWD);
+    bool inline_marks = reached.paired || !marks_want_a_pass(reached, beta, (uint64_t)cur.n_samples, n_cu);
     if (const char *force = getenv("RAPIDGNN_MARK_PASS"); force && !reached.paired) inline_marks = force[0] == '0';       // same results either way; for tests and tuning
     RG_TRY(keep.dev_n<int32_t>((uint64_t)cur.n_samples, &cur.samp_nbr));
     if (sampler == RG_SAMPLER_POSITIONS) {
