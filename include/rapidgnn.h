@@ -104,7 +104,8 @@ typedef struct rg_cache rg_cache;
  * n_nodes; the sampling kernels then mark what they reach themselves);
  * RAPIDGNN_MARK_PASS=1 / 0 forces / forbids marking what a hop of any other build
  * reaches by a pass over its samples instead (default: from one sample per 512 IDs
- * of the batches' bitmaps, if there are 2,097,152 samples or three per ID);
+ * of the batches' bitmaps, if there are 2,097,152 samples, two per ID, or as many
+ * as cost what the pass does);
  * RAPIDGNN_SHORT_ROWS=0 makes rows of up to 64 IDs be
  * sampled one per wave instead of four; RAPIDGNN_GROUP_TILES=1 / 0 forces /
  * forbids handing out the pieces of rows above 16,384 IDs grouped by the piece
