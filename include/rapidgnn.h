@@ -107,7 +107,7 @@ typedef struct rg_cache rg_cache;
  * of the batches' bitmaps, if there are 2,097,152 samples, two per ID, or as many
  * as cost what the pass does);
  * RAPIDGNN_SHORT_ROWS=0 makes rows of up to 64 IDs be
- * sampled one per wave instead of four; RAPIDGNN_GROUP_TILES=1 / 0 forces /
+ * copied one per wave instead of four at fan-outs above 64; RAPIDGNN_GROUP_TILES=1 / 0 forces /
  * forbids handing out the pieces of rows above 16,384 IDs grouped by the piece
  * they read, so that batches that share a row meet in the caches (default: from
  * 16,384 pieces on); RAPIDGNN_HUB_ROWS=<IDs> makes rows of at least so many IDs
@@ -115,8 +115,9 @@ typedef struct rg_cache rg_cache;
  * (default: behind the first hop of epochs of 16 batches and more, from a length
  * computed from the fan-out and n_nodes, where a hop's frontiers hold at least 24
  * such pieces per compute unit; never a hop with such a row out of order);
- * RAPIDGNN_HUB_RANGE=<factor> changes how many key values are looked through first
- * (for tests).  The result is the same in every case.
+ * RAPIDGNN_HUB_RANGE=<factor> changes how many key values are looked through first,
+ * RAPIDGNN_GUESS_SCALE=<factor> how many IDs of a row its first cut is to let
+ * through at fan-outs up to 64 (both for tests).  The result is the same in every case.
  * Further scratch that a hop sampled so takes only if it is there: tables of up to
  * 8 bytes per ID of the distinct rows.
  * The bitmaps are drawn from a pool of blocks known to be

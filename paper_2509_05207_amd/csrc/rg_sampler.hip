@@ -14,6 +14,14 @@
 // node's first 64 neighbour IDs already in flight while the current node is
 // sampled.
 //
+// Fan-outs up to 64 (sample_rows_kernel):
+//
+//  - rows of up to 64 IDs: four at a time, sixteen lanes each (sample_short_rows).
+//  - longer rows are streamed once against a cut guessed from the key distribution, what passes is listed in LDS in row
+//    order, and the f smallest keys of that list are the sample.
+//
+// Larger fan-outs (sample_kernel), and the concatenated results of a long row's tiles (sample_merge_kernel):
+//
 //  - deg <= f: the row is the sample; it is copied.
 //  - deg <= 256: the row sits in registers (1 or 4 IDs per lane).  A threshold
 //    that exactly f keys do not exceed is found by bisection on ballots, and the
@@ -26,6 +34,9 @@
 //    overflow it is pruned to the f smallest keys with the same search and an
 //    in-place ordered compaction, which also tightens the cut.  What is left
 //    after the last block is the sample.
+//
+// At any fan-out:
+//
 //  - rows longer than BIG_ROW are cut into T near-equal tiles, each sampled by
 //    its own wave into scratch (f IDs per tile, row order); a second small
 //    launch samples the concatenation of a row's tile results, which is the
@@ -33,7 +44,6 @@
 //    each tile.  This bounds the work of one wave whatever the degree skew.
 //    Tiles are dealt out by workgroup index and done before the groups of
 //    nodes, which the waves then take from a counter as they become free.
-//
 //  - the very longest rows, where a hop holds many of them, are not read but
 //    sampled from the keys' side (hub_sample_kernel).
 //
@@ -857,34 +867,94 @@ __device__ __forceinline__ int count_smaller16(uint32_t k)
     return cnt;
 }
 
-// This lane's row's sixteen bits of a lane mask, counted.
-__device__ __forceinline__ int popc_of_my_row(unsigned long long m, int lane) { return __popc((uint32_t)(m >> (lane & 48)) & 0xFFFFu); }
-
-// For each row of sixteen lanes on its own: the largest key value `cut` such that exactly f of the row's keys do not
-// exceed it.  k[e], e < E: the row's keys, a missing one stands as 0xFFFFFFFF; deg (> f in the rows that search, same
-// in all lanes of a row): how many there are; rows with searching == false ride along and get an arbitrary answer.
-// Bit by bit from the top, as kth_key_threshold does for a whole wave: the f-th smallest key stays inside
-// [lo, lo + 2^(bit+1)), and a row is done as soon as exactly f keys lie below the bracket's upper end -- for keys
-// spread over 32 bits after about log2(deg) + 2 steps; the loop ends when every row is done.
-template <int E>
-__device__ __forceinline__ uint32_t kth_key_threshold_rows(const uint32_t (&k)[4], int f, int deg, bool searching, int lane)
+// The sum of x over the lane's row of sixteen lanes, in all of them.
+__device__ __forceinline__ int sum16(int x)
 {
-    uint32_t lo = 0, cut = 0xFFFFFFFFu;
-    int below_hi = deg;
-    bool done = !searching;
-    for (int bit = 31; bit >= 0; --bit) {
-        if (ballot64(!done) == 0ull) break;
-        const uint32_t t = lo | (1u << bit);
-        int c = 0;
+    x += (int)rotate16<8>((uint32_t)x);
+    x += (int)rotate16<4>((uint32_t)x);
+    x += (int)rotate16<2>((uint32_t)x);
+    x += (int)rotate16<1>((uint32_t)x);
+    return x;
+}
+// The sum of x over the lanes of the row up to and with this one, byte by byte (no byte may overflow).
+template <int N> __device__ __forceinline__ uint32_t from_left16(uint32_t x)      // the value N lanes to the left in the row of sixteen; 0 past its start
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x110 + N, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t prefix16(uint32_t x)
+{
+    x += from_left16<1>(x);
+    x += from_left16<2>(x);
+    x += from_left16<4>(x);
+    x += from_left16<8>(x);
+    return x;
+}
+__device__ __forceinline__ uint32_t last_of16(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x15F, 0xF, 0xF, false); }      // lane 15's value of the row of sixteen
+
+// Four rows' IDs, one row per sixteen lanes: lane l16 of a row holds IDs l16, l16 + 16, ... in u[0 .. E), n of them in the
+// row (same in its lanes).  The min(n, f) with the smallest keys go to `out` in order and are marked.  All 64 lanes call it.
+// One ID per lane is decided by rank (see count_smaller16); more by halving the range of key values until exactly f keys
+// lie below, all four rows side by side and in vector instructions alone: with counts taken from lane masks on the scalar
+// unit instead, that unit, which a compute unit's four SIMDs share, was busier than the vector units (84 % against 79 % of its issue
+// slots, 22 M rows of 340 IDs on average at fan-out 5).
+template <int E, int MARK>
+__device__ __forceinline__ void emit_rows(const uint32_t (&u)[E], int n, int f, uint32_t lo, uint32_t hi, int l16, int32_t *__restrict__ out,
+                                          const ReachedOfBatch &reached_b)
+{
+    bool sel[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) c += popc_of_my_row(ballot64(k[e] < t), lane);
-        if (!done) {
-            if (c >= f) below_hi = c; else lo = t;
-            cut = lo | ((1u << bit) - 1u);
-            done = below_hi == f;
+    for (int e = 0; e < E; ++e) sel[e] = l16 + 16 * e < n;
+    const bool search = n > f;
+    if (ballot64(search) != 0ull) {
+        uint32_t k[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) k[e] = sel[e] ? key32(lo, hi, u[e]) : 0xFFFFFFFFu;       // (a missing key's stand-in is below nothing)
+        if (E == 1) {
+            const int smaller = count_smaller16(k[0]);
+            if (search) sel[0] = sel[0] && smaller < f;
+        } else {
+            uint32_t from = 0, to = 0xFFFFFFFFu, t = to >> 1;     // fewer than f keys lie below `from`, at least f at or below `to`
+            for (int step = 0; step < 34; ++step) {              // (distinct keys are told apart in 32 steps; repeated IDs of a damaged row never)
+                int c = 0;
+#pragma unroll
+                for (int e = 0; e < E; ++e) c += k[e] <= t ? 1 : 0;
+                c = sum16(c);
+                if (ballot64(search && c != f) == 0ull) break;
+                const bool few = c < f;
+                if (c <= f) from = t + (few ? 1u : 0u);
+                if (!few) to = t;                                // (exactly f: this row's t stays as it is)
+                t = from + ((to - from) >> 1);
+            }
+            if (search) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) sel[e] = sel[e] && k[e] <= t;
+            }
         }
     }
-    return cut;
+    // an ID's place is the number of selected ones in front of it: those of the lanes to the left in its own step of sixteen,
+    // from a prefix sum of four steps' flags packed in a word, and all of the steps before
+    const uint32_t keep = (uint32_t)(search ? f : n);
+    uint32_t in_front = 0;                                       // of the words before, in every byte
+#pragma unroll
+    for (int w = 0; w < (E + 3) / 4; ++w) {
+        uint32_t x = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (4 * w + q < E) x |= sel[4 * w + q] ? 1u << (8 * q) : 0u;
+        const uint32_t incl = prefix16(x), all = last_of16(incl);
+        const uint32_t place = incl - x + all * 0x01010100u + in_front;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = 4 * w + q;
+            if (e >= E) break;
+            const uint32_t at = (place >> (8 * q)) & 0xFFu;
+            if (sel[e] && at < keep) {                           // (at < keep but for repeated IDs)
+                out[at] = (int32_t)u[e];
+                mark_reached<MARK>(reached_b, u[e]);
+            }
+        }
+        if (E > 4) in_front += ((all * 0x01010101u) >> 24) * 0x01010101u;
+    }
 }
 
 // The listed short rows (recs[0 .. count), shortest first; LDS) sampled four per round.  All 64 lanes call it.
@@ -907,43 +977,13 @@ __device__ __forceinline__ void sample_short_rows(const ShortRec *recs, int coun
     fetch(0, r, u);
     for (int it = 0; it < n_it; ++it) {
         if (it + 1 < n_it) fetch(it + 1, r_next, u_next);
-        const int deg = r.deg;
-        bool sel[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sel[e] = l16 + 16 * e < deg;
-        const bool searching = deg > f;
-        if (ballot64(searching) != 0ull) {                       // some row of the round is longer than the fan-out
-            const uint32_t slo = (uint32_t)r.state, shi = (uint32_t)(r.state >> 32);
-            uint32_t k[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) k[e] = sel[e] ? key32(slo, shi, u[e]) : 0xFFFFFFFFu;     // (a missing key's stand-in is never counted as smaller than anything)
-            if (ballot64(searching && deg > 16) == 0ull) {       // one key per lane: by rank
-                const int smaller = count_smaller16(k[0]);
-                if (searching) sel[0] = sel[0] && smaller < f;
-            } else {
-                uint32_t cut;
-                if (ballot64(searching && deg > 48) != 0ull) cut = kth_key_threshold_rows<4>(k, f, deg, searching, lane);
-                else if (ballot64(searching && deg > 32) != 0ull) cut = kth_key_threshold_rows<3>(k, f, deg, searching, lane);
-                else cut = kth_key_threshold_rows<2>(k, f, deg, searching, lane);
-                if (searching) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) sel[e] = sel[e] && k[e] <= cut;
-                }
-            }
-        }
-        // row order is ID 0 .. 15 (e = 0), 16 .. 31 (e = 1), ...: a selected ID's place is the number of selected IDs before it
         const ReachedOfBatch reached_b = reached_of<MARK>(reached, r.batch);
         int32_t *out = samp_nbr + r.out;
-        int base = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t m16 = (uint32_t)(ballot64(sel[e]) >> (lane & 48)) & 0xFFFFu;       // the selected lanes of this lane's row
-            if (sel[e]) {
-                out[base + __popc(m16 & ((1u << l16) - 1u))] = (int32_t)u[e];
-                mark_reached<MARK>(reached_b, u[e]);
-            }
-            base += __popc(m16);
-        }
+        const uint32_t lo = (uint32_t)r.state, hi = (uint32_t)(r.state >> 32);
+        const uint32_t u1[1] = {u[0]}, u2[2] = {u[0], u[1]};
+        if (ballot64(r.deg > 32) != 0ull) emit_rows<4, MARK>(u, r.deg, f, lo, hi, l16, out, reached_b);
+        else if (ballot64(r.deg > 16) != 0ull) emit_rows<2, MARK>(u2, r.deg, f, lo, hi, l16, out, reached_b);
+        else emit_rows<1, MARK>(u1, r.deg, f, lo, hi, l16, out, reached_b);
         r = r_next;
 #pragma unroll
         for (int e = 0; e < 4; ++e) u[e] = u_next[e];
@@ -1041,6 +1081,7 @@ struct HopArgs {
     const int32_t *tile_order;                                         // the k-th tile job to hand out, or NULL: job k
     ReachedMaps reached;
     unsigned long long *next_work;                                     // work items are handed out in order through this counter
+    float guess_scale;                                                 // of the candidates a row's first cut is to let through (1; for tests: sample_rows_kernel)
 };
 
 // The next unclaimed work item (lane 0 asks, every lane gets the answer).
@@ -1170,6 +1211,316 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CAP <= 
                 sample_row<CAP, MARK>(row, cdeg, cfirst, cahead, f, (uint32_t)S, (uint32_t)(S >> 32), lane, buf, out, reached_b);
             }
         }
+    }
+}
+
+// ---------------------------------------------------------------- fan-outs up to 64
+// The same work for fan-outs of at most ROWS_FANOUT.  Bound by the vector units' integer rate, and next to it by the scalar
+// unit, which a compute unit's four SIMDs share and which takes one instruction per SIMD and four cycles, as the vector units do.
+// sample_kernel issues as many of the one as of the other, both pipes were four fifths busy, and no more than 1.9 instructions
+// per SIMD and four cycles come through, whatever their kind; so here instructions are what is saved: no tests inside a chunk's
+// inner blocks, no cases at a block's load, no copies between the two chunks' registers, one compare per step of the last cut.
+// Per block of 256 IDs, everything a row costs included (233,000 nodes, rows of 13 blocks, fan-outs 25, 10): 57 vector and 59 scalar
+// instructions before, 49 and 36 so; the launches 3.65 -> 3.1 ms (2.45 M nodes: 15, 10, 5 9.6 -> 7.7, 50, 50 2.09 -> 1.6).
+//
+// A row's IDs are streamed once against a guessed cut (a key and its compare are nine vector
+// instructions per ID), what passes, a few dozen IDs, is listed in LDS in row order, and the f smallest keys of the list are
+// the sample.  If fewer than f IDs pass, or more than fit, the row is streamed again with another cut (retry_row).
+//
+// A row is read in blocks of 256 IDs, 16 bytes per lane.  Rows above MID_ROW IDs are read from the last 128-byte boundary in
+// front of them (`skip` IDs early, which do not count), so that no two loads share a line; lanes of the last block that would read past the row
+// read its last 16 bytes instead, and only the IDs that no other lane has count.  Blocks come in chunks of ROWS_CHUNK; while one is
+// looked through the next one of the row, or the first one of the next row, is on its way.
+constexpr int ROWS_FANOUT = 64;
+constexpr int ROWS_ROOM = 128;           // candidates of one row
+constexpr int ROWS_CHUNK = 2;
+constexpr int MID_ROW = 256;
+
+typedef u32x4 u32x4_dword_aligned __attribute__((aligned(4)));
+
+struct StreamedRow {
+    const int32_t *from;                 // where block 0 starts: `skip` IDs in front of the row
+    int skip, len, n_blocks;
+};
+
+// Block j; lanes past the row's last four IDs hold those.
+__device__ __forceinline__ u32x4 load_row_block(const StreamedRow &r, int j, int lane)
+{
+    const uint32_t at = min(1024u * (uint32_t)j + 16u * (uint32_t)lane, 4u * (uint32_t)(r.skip + r.len - 4));
+    return *reinterpret_cast<const u32x4_dword_aligned *>(reinterpret_cast<const char *>(r.from) + at);
+}
+
+__device__ __forceinline__ int places(unsigned long long m, int first)      // first + the number of set bits of m below this lane's
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)first));
+}
+
+// Appends the IDs of a block whose key is not above `cut` to cand[cnt ..), in row order, unless they do not fit; cnt counts on
+// in any case.  OPEN: the cut's lower half is all ones (see key32_open).  EDGE: the first or the last block of its row, of which
+// not all IDs count; p: the position in the row that the lane's first ID should have (in front of the row: negative).
+// The empty asm statements keep the branches that lanes take apart from those that the wave takes, so that cnt stays in a
+// scalar register and the two ways of writing are not folded into one.
+template <bool OPEN, bool EDGE>
+__device__ __forceinline__ void take_block(const u32x4 &blk, int p, int last_four, uint32_t lo, uint32_t hi, uint32_t cut, uint32_t *cand, int &cnt)
+{
+    const uint32_t u[4] = {blk.x, blk.y, blk.z, blk.w};
+    unsigned long long m[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = ballot64((OPEN ? key32_open(lo, hi, u[e]) : key32(lo, hi, u[e])) <= cut);
+    if (EDGE) {
+        const int first = max(p, 0) - min(p, last_four);         // from which of the lane's four IDs on they count
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m[e] &= ballot64(first <= e);
+    }
+    const unsigned long long m01 = m[0] | m[1], m012 = m01 | m[2], any = m012 | m[3];
+    if (any == 0ull) return;
+    if (__builtin_expect(((m[0] & m[1]) | (m01 & m[2]) | (m012 & m[3])) == 0ull, 1)) {      // no lane holds two candidates: lane order is row order
+        const int before = cnt;
+        cnt += __popcll(any);
+        if (cnt <= ROWS_ROOM) {
+            uint32_t v = my_bit(m[2]) ? u[2] : u[3];
+            v = my_bit(m[1]) ? u[1] : v;
+            v = my_bit(m[0]) ? u[0] : v;
+            const int at = places(any, before);
+            if (my_bit(any)) cand[at] = v;
+            asm volatile("; one each");
+        }
+    } else {
+        const int before = cnt;
+        cnt += __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]);
+        if (cnt <= ROWS_ROOM) {
+            int at = places(m[3], places(m[2], places(m[1], places(m[0], before))));
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (my_bit(m[e])) cand[at++] = u[e];
+            asm volatile("; several");
+        }
+    }
+}
+
+// The row again, with finished keys, until between f and ROWS_ROOM IDs pass: the cut is moved by what the count says is missing
+// or too much, inside what the tries so far leave.  Returns how many, and the cut.  (Only a row that repeats IDs can have no
+// such cut; its first f IDs stand for it then.)
+__device__ __forceinline__ int retry_row(const StreamedRow &r, int f, uint32_t lo, uint32_t hi, int cnt, uint32_t *cut_io, int lane, uint32_t *cand)
+{
+    uint32_t cut = *cut_io;
+    uint64_t low = 0, high = (uint64_t)1 << 32;                  // cuts below `low` let too few through, from `high` on too many
+    const float spare = 2.0f * __fsqrt_rn((float)f) + 4.0f;
+    for (int t = 0; t < 48 && (cnt < f || cnt > ROWS_ROOM); ++t) {
+        uint64_t next;
+        if (cnt < f) {
+            low = (uint64_t)cut + 1;
+            next = (uint64_t)cut + 1 + (uint64_t)(((float)(f - cnt) + spare) / (float)r.len * 4294967296.0f);
+        } else {
+            high = cut;
+            next = (uint64_t)((float)cut * (((float)f + spare) / (float)cnt));
+        }
+        if (t >= 4 || next < low || next >= high) next = low + (high - low) / 2;
+        if (low >= high) break;
+        cut = uni((uint32_t)next);
+        cnt = 0;
+        for (int j = 0; j < r.n_blocks; ++j) take_block<false, true>(load_row_block(r, j, lane), 256 * j + 4 * lane - r.skip, r.len - 4, lo, hi, cut, cand, cnt);
+        cnt = uni(cnt);
+    }
+    if (cnt < f || cnt > ROWS_ROOM) {
+        if (lane < f) cand[lane] = (uint32_t)r.from[r.skip + lane];
+        cnt = f;
+    }
+    *cut_io = cut;
+    return cnt;
+}
+
+// The f smallest keys of cand[0 .. cnt), 64 * (E - 1) < cnt <= 64 * E, none above `cut`, written to `out` in row order and marked.
+// Their bound is found bit by bit from the cut's leading bit down, one compare per step and the rest on the scalar
+// unit, until exactly f keys lie below it: 4 to 6 steps.  (Four rows at once, a row per sixteen lanes, took twice the vector
+// instructions of this: the steps are those of the slowest row, and counts over sixteen lanes are four additions each.)
+template <int E, int MARK>
+__device__ __forceinline__ void emit_row(const uint32_t *cand, int cnt, int f, uint32_t lo, uint32_t hi, uint32_t cut, int lane, int32_t *__restrict__ out, bool mark,
+                                         const ReachedOfBatch &reached_b)
+{
+    uint32_t u[E], k[E];
+    unsigned long long vm[E], m[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) u[e] = cand[64 * e + lane];      // (past cnt: what an earlier row left)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        vm[e] = m[e] = low_lanes(cnt - 64 * e);
+        k[e] = key32(lo, hi, u[e]);
+    }
+    if (cnt > f) {
+        uint32_t from = 0, bit = 1u << (31 - __clz((int)(cut | 1u)));      // the f-th smallest key lies in [from, from + 2 * bit)
+        int c;
+        do {
+            const uint32_t t = from | bit;
+            c = 0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) { m[e] = ballot64(k[e] < t) & vm[e]; c += __popcll(m[e]); }
+            if (c < f) from = t;
+            bit >>= 1;
+        } while (c != f && bit != 0u);
+        if (c != f) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) m[e] = ballot64(k[e] <= from) & vm[e];
+        }
+    }
+    int first = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int at = places(m[e], first);
+        if (my_bit(m[e]) && at < f) {                            // (at < f but for repeated IDs)
+            out[at] = (int32_t)u[e];
+            if (MARK != MARK_NONE && mark) mark_reached<MARK>(reached_b, u[e]);
+        }
+        first += __popcll(m[e]);
+    }
+}
+
+template <int MARK>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sample_rows_kernel(HopArgs a)
+{
+    __shared__ uint32_t cand[ROWS_ROOM];
+    __shared__ ShortRec short_recs[64];
+    const int lane = threadIdx.x;
+    const int f = (int)a.fanout;
+    // Tiles first, dealt out in turn; in each round XCD x takes a contiguous eighth of the round's jobs (see sample_kernel).
+    int64_t k = blockIdx.x;
+    if (a.tile_order && (gridDim.x & 7u) == 0) k = (int64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    int64_t w = 0, tile_begin = 0; int tile_len = 0; uint64_t tile_state = 0;
+    if (k < a.n_tiles) { w = a.tile_order ? a.tile_order[k] : k; tile_begin = a.tile.begin[w]; tile_len = a.tile.len[w]; tile_state = a.tile.state[w]; }
+    for (;;) {
+        // a tile (one row, the first lane's), or the next group of nodes, a lane each
+        const bool is_tile = k < a.n_tiles;
+        int64_t rb_lane = 0;
+        int deg_lane = 0;
+        uint32_t b_lane = 0;
+        uint64_t S_lane = 0;
+        int64_t out_lane = 0;
+        int32_t *const out_base = is_tile ? a.tile_out : a.samp_nbr;
+        if (is_tile) {
+            rb_lane = tile_begin; deg_lane = lane == 0 ? tile_len : 0; S_lane = tile_state; out_lane = w * f;
+            k += gridDim.x;
+            if (k < a.n_tiles) { w = a.tile_order ? a.tile_order[k] : k; tile_begin = a.tile.begin[w]; tile_len = a.tile.len[w]; tile_state = a.tile.state[w]; }
+        } else {
+            const int64_t g = grab_work(a.next_work, lane);
+            if (g >= a.n_units) break;
+            const bool full = g < a.n_full_groups;               // 64 nodes, or 16 of the launch's last nodes
+            const int64_t i_lane = (full ? g << 6 : (a.n_full_groups << 6) + ((g - a.n_full_groups) << 4)) + lane;
+            const bool in = (full || lane < 16) && i_lane < a.n_frontier;
+            if (in) {
+                rb_lane = a.rec.row_begin[i_lane];
+                deg_lane = a.rec.deg[i_lane];
+                b_lane = a.rec.batch[i_lane];
+                S_lane = a.rec.state[i_lane];
+                out_lane = a.samp_off[i_lane];
+            }
+            // A row of at most TINY_ROW IDs that is no longer than the fan-out is its own sample: its node's lane copies
+            // and marks it, 64 rows at a time, four IDs of each in flight.
+            const bool tiny = deg_lane > 0 && deg_lane <= f && deg_lane <= TINY_ROW;
+            if (ballot64(tiny) != 0ull) {
+                const int32_t *row = a.indices + rb_lane;
+                int32_t *out = a.samp_nbr + out_lane;
+                const ReachedOfBatch reached_b = reached_of<MARK>(a.reached, b_lane);
+                for (int j0 = 0; ballot64(tiny && j0 < deg_lane) != 0ull; j0 += 4) {
+                    int32_t u[4] = {0, 0, 0, 0};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (tiny && j0 + q < deg_lane) u[q] = row[j0 + q];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (tiny && j0 + q < deg_lane) { out[j0 + q] = u[q]; mark_reached<MARK>(reached_b, (uint32_t)u[q]); }
+                }
+            }
+            const bool mine = !tiny && deg_lane > 0 && deg_lane <= SHORT_ROW;
+            const int count = __popcll(ballot64(mine));
+            if (count != 0) {
+                const int at = short_row_slot(mine, deg_lane, lane);
+                wave_lds_order();
+                if (mine) short_recs[at] = ShortRec{rb_lane, out_lane, S_lane, deg_lane, b_lane};
+                wave_lds_order();
+                sample_short_rows<MARK>(short_recs, count, a.indices, f, a.samp_nbr, a.reached, lane);
+            }
+        }
+        unsigned long long todo = ballot64(deg_lane > SHORT_ROW && (is_tile || deg_lane <= BIG_ROW));
+        if (todo == 0ull) continue;
+        // the guessed cut of this lane's row; a row that fits the candidates' room and would lose little is taken whole
+        uint32_t cut_lane = 0xFFFFFFFFu;
+        {
+            const float lambda = (is_tile ? safely_guessed_candidates(f) : guessed_candidates(f)) * a.guess_scale;
+            if (deg_lane > ROWS_ROOM || lambda * 2.0f <= (float)deg_lane) cut_lane = guessed_cut_of(fminf(lambda / (float)deg_lane, 0.99f));
+        }
+        // where the wave is: chunk j of the row of lane l
+        struct Cursor { StreamedRow r; int l, j; uint32_t lo, hi, cut; };
+        auto first_chunk_of = [&](int l) {
+            const int64_t rb = bcast64(rb_lane, l);
+            Cursor c;
+            c.l = l;
+            c.j = 0;
+            c.r.len = __builtin_amdgcn_readlane(deg_lane, l);
+            c.r.from = a.indices + rb;
+            c.r.skip = c.r.len > MID_ROW && (rb >> 5) != 0 ? (int)(((uintptr_t)c.r.from >> 2) & 31u) : 0;      // (no fewer than 32 IDs in front of the row)
+            c.r.from -= c.r.skip;
+            c.r.n_blocks = (c.r.skip + c.r.len + 255) >> 8;
+            c.lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)S_lane, l);
+            c.hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(S_lane >> 32), l);
+            c.cut = (uint32_t)__builtin_amdgcn_readlane((int)cut_lane, l);
+            return c;
+        };
+        auto next_lane = [&]() {
+            const int l = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1);
+            todo &= todo - 1ull;
+            return l;
+        };
+        auto load_chunk = [&](const Cursor &c, u32x4 (&to)[ROWS_CHUNK]) {
+#pragma unroll
+            for (int e = 0; e < ROWS_CHUNK; ++e) to[e] = load_row_block(c.r, c.j + e, lane);
+        };
+        Cursor at = first_chunk_of(next_lane()), ahead = at;     // the chunk that is looked through, and the one that is loaded
+        int cnt = 0;
+        // One chunk, held in `now`, while the next one is loaded into `then`; false: it was the last.
+        auto step = [&](u32x4 (&now)[ROWS_CHUNK], u32x4 (&then)[ROWS_CHUNK]) {
+            const bool last = at.j + ROWS_CHUNK >= at.r.n_blocks;      // of its row
+            bool more = true;
+            ahead.j += ROWS_CHUNK;
+            if (last) {
+                more = todo != 0ull;
+                if (more) ahead = first_chunk_of(next_lane());
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this chunk is here, and only then the next is asked for (behind the last one, the end of its row again)
+            load_chunk(ahead, then);
+            if (at.j > 0 && !last) {
+#pragma unroll
+                for (int q = 0; q < ROWS_CHUNK; ++q) take_block<true, false>(now[q], 0, 0, at.lo, at.hi, at.cut, cand, cnt);
+            } else {
+#pragma unroll
+                for (int q = 0; q < ROWS_CHUNK; ++q)
+                    if (q == 0 || at.j + q < at.r.n_blocks)
+                        take_block<true, true>(now[q], 256 * (at.j + q) + 4 * lane - at.r.skip, at.r.len - 4, at.lo, at.hi, at.cut, cand, cnt);
+            }
+            at.j += ROWS_CHUNK;
+            if (last) {
+                uint32_t cut = at.cut;
+                int n = cnt;
+                wave_lds_order();
+                if (n < f || n > ROWS_ROOM) {
+                    n = uni(retry_row(at.r, f, at.lo, at.hi, n, &cut, lane, cand));
+                    cut = uni(cut);
+                    wave_lds_order();
+                }
+                n = uni(n);
+                int32_t *out = out_base + bcast64(out_lane, at.l);
+                const ReachedOfBatch reached_b = reached_of<MARK>(a.reached, MARK == MARK_NONE ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)b_lane, at.l));
+                const uint32_t lo = at.lo, hi = at.hi;
+                at = ahead;
+                cnt = 0;
+                if (n <= 64) emit_row<1, MARK>(cand, n, f, lo, hi, cut, lane, out, !is_tile, reached_b);
+                else emit_row<2, MARK>(cand, n, f, lo, hi, cut, lane, out, !is_tile, reached_b);
+                wave_lds_order();
+            }
+            return more;
+        };
+        u32x4 x[ROWS_CHUNK], y[ROWS_CHUNK];
+        load_chunk(at, x);
+        while (step(x, y) && step(y, x)) {}
     }
 }
 
@@ -1420,19 +1771,18 @@ constexpr uint32_t HUB_BATCHES = 16;
 
 // Every workgroup of the sampling launch must be resident from the start (tiles are dealt out by workgroup index), so
 // the grid is what the chip holds of this kernel, or the amount of work if that is less.
-template <int CAP, int MARK>
+typedef void (*HopKernel)(HopArgs);
+template <HopKernel SAMPLE, HopKernel MERGE>
 static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, bool fine_tail, bool fine_if_few, hipStream_t st)
 {
     HopArgs a = args;
-    static std::atomic<int> asked[2] = {{0}, {0}};      // the same answer every time; asked once (schedules may be built from several threads)
-    const int which = a.min_deg > 0 ? 1 : 0;
-    int per_cu = asked[which].load(std::memory_order_relaxed);
+    static std::atomic<int> asked{0};                   // the same answer every time; asked once (schedules may be built from several threads)
+    int per_cu = asked.load(std::memory_order_relaxed);
     if (per_cu == 0) {
         int v = 0;
-        if (which) RG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, sample_kernel<CAP, MARK, true>, 64, 0));
-        else RG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, sample_kernel<CAP, MARK, false>, 64, 0));
+        RG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, SAMPLE, 64, 0));
         per_cu = v > 0 ? v : 1;
-        asked[which].store(per_cu, std::memory_order_relaxed);
+        asked.store(per_cu, std::memory_order_relaxed);
     }
     // Groups of 64 nodes, except that with fine_tail the last 128 nodes per resident wave (and always what is left of
     // the frontier after the last whole group) are handed out 16 at a time.
@@ -1443,9 +1793,8 @@ static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, 
     a.n_units = a.n_full_groups + (a.n_frontier - a.n_full_groups * 64 + 15) / 16;
     const int64_t n_work = a.n_tiles + a.n_units;
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_work, resident));
-    if (which) hipLaunchKernelGGL((sample_kernel<CAP, MARK, true>), dim3(grid), dim3(64), 0, st, a);
-    else hipLaunchKernelGGL((sample_kernel<CAP, MARK, false>), dim3(grid), dim3(64), 0, st, a);
-    if (a.n_tiles > 0) hipLaunchKernelGGL((sample_merge_kernel<CAP, MARK>), dim3(merge_grid), dim3(64), 0, st, a);
+    hipLaunchKernelGGL(SAMPLE, dim3(grid), dim3(64), 0, st, a);
+    if (a.n_tiles > 0) hipLaunchKernelGGL(MERGE, dim3(merge_grid), dim3(64), 0, st, a);
     return RG_OK;
 }
 
@@ -1757,7 +2106,8 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         int merge_span = 64;                              // tiles per look of a merging wave: 64 if that still occupies the chip's waves
         while (merge_span > 1 && n_tiles / merge_span < (int64_t)n_cu * 32) merge_span >>= 1;
         const unsigned merge_grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_tiles + merge_span - 1) / merge_span, (int64_t)n_cu * 64));
-        HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_rows ? SHORT_ROW : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work};
+        HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_rows ? SHORT_ROW : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work, 1.0f};
+        if (const char *scale = getenv("RAPIDGNN_GUESS_SCALE")) a.guess_scale = std::min(std::max((float)atof(scale), 1e-3f), 1e3f);      // same results either way; for tests
         ScopedTimer tm(KG_SAMPLER, st);
         if (hub_jobs) {
             const char *range = getenv("RAPIDGNN_HUB_RANGE");                         // same results either way; for tests
@@ -1774,17 +2124,23 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         const bool fine_tail = ids_here >= 1024ull * rows_here;
         // a frontier that does not give every resident wave a group of 64 (the seed hop) is split finer from rows of 256 IDs on
         const bool fine_if_few = ids_here >= 256ull * rows_here;
+#define RG_LAUNCH(...) RG_TRY((launch_hop<__VA_ARGS__>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)))
 #define RG_HOP(CAP)                                                                                                   \
     do {                                                                                                              \
-        if (inline_marks) RG_TRY((launch_hop<CAP, MARK_BITS>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));      \
-        else RG_TRY((launch_hop<CAP, MARK_NONE>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)));                   \
+        if (inline_marks && short_rows) RG_LAUNCH(sample_kernel<CAP, MARK_BITS, true>, sample_merge_kernel<CAP, MARK_BITS>);  \
+        else if (inline_marks) RG_LAUNCH(sample_kernel<CAP, MARK_BITS, false>, sample_merge_kernel<CAP, MARK_BITS>);   \
+        else if (short_rows) RG_LAUNCH(sample_kernel<CAP, MARK_NONE, true>, sample_merge_kernel<CAP, MARK_NONE>);      \
+        else RG_LAUNCH(sample_kernel<CAP, MARK_NONE, false>, sample_merge_kernel<CAP, MARK_NONE>);                     \
     } while (0)
-        if (need <= 128) RG_HOP(128);
-        else if (need <= 256) RG_HOP(256);
+        if (fanout <= (uint32_t)ROWS_FANOUT) {
+            if (inline_marks) RG_LAUNCH(sample_rows_kernel<MARK_BITS>, sample_merge_kernel<128, MARK_BITS>);
+            else RG_LAUNCH(sample_rows_kernel<MARK_NONE>, sample_merge_kernel<128, MARK_NONE>);
+        } else if (need <= 256) RG_HOP(256);
         else if (need <= 512) RG_HOP(512);
         else if (need <= 1024) RG_HOP(1024);
         else RG_HOP(2048);
 #undef RG_HOP
+#undef RG_LAUNCH
         RG_HIP(hipGetLastError());
         if (!inline_marks) RG_TRY(launch_mark_pass(cur, beta, reached, n_cu, st));
     }

@@ -1,0 +1,68 @@
+"""GPU parity of the sampling of rows above 64 IDs at fan-outs up to 64, where a row is streamed against a guessed cut:
+row lengths around the blocks' and chunks' ends, row starts at every distance from a 128-byte boundary (and at the start of
+the array), first cuts that let through too few, too many and the usual number of candidates -- against the oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [65, 66, 67, 68, 96, 97, 127, 128, 129, 130, 191, 192, 193, 254, 255, 256, 257, 258, 260, 285, 287, 288, 289, 511, 512, 513, 515, 543, 544, 767, 768, 769,
+           1023, 1024, 1025, 1056, 1300, 2047, 2049, 4099]
+
+
+@pytest.fixture(scope="module")
+def rg():
+    from paper_2509_05207_amd import binding
+    binding.lib()
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return binding
+
+
+@pytest.fixture(scope="module")
+def graph():
+    rng = np.random.default_rng(9)
+    n = 4800
+    deg = np.where(rng.random(n) < 0.25, rng.integers(0, 65, size=n), rng.choice(LENGTHS, size=n))
+    rows = [np.sort(rng.choice(n, size=int(d), replace=False)).astype(np.int32) for d in deg]
+    indptr = np.zeros(n + 1, np.int64)
+    indptr[1:] = np.cumsum(deg)
+    return n, indptr, np.concatenate(rows), rng.permutation(n)[:1500].astype(np.int32)
+
+
+@pytest.mark.parametrize("shift", [0, 1, 30])
+@pytest.mark.parametrize("scale", [None, "0.05", "0.6", "30"])
+@pytest.mark.parametrize("fanout", [(1, 2), (5, 16), (17, 32), (33, 48), (63, 64)])
+def test_rows_against_a_guessed_cut(rg, orc, graph, fanout, scale, shift, monkeypatch):
+    n, indptr, indices, train = graph
+    if scale is not None:
+        monkeypatch.setenv("RAPIDGNN_GUESS_SCALE", scale)
+    o = orc.Schedule(indptr, indices, train, 200, list(fanout), 3, 1, 2, n_threads=8)
+    dx = torch.zeros(indices.size + shift, dtype=torch.int32, device="cuda")[shift:]          # rows at every distance from a boundary
+    dx.copy_(torch.from_numpy(indices))
+    g = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), dx, torch.from_numpy(train).cuda(), 200, list(fanout), 3, 1, 2)
+    for hop in range(o.L + 1):
+        ids, off = o.frontier(hop)
+        gids, _, goff = rg.rg_schedule_frontier(g, hop)
+        assert np.array_equal(goff, off) and np.array_equal(gids.cpu().numpy(), ids), f"frontier {hop}"
+    for hop in range(o.L):
+        so, nb = o.samples(hop)
+        gso, gnb = rg.rg_schedule_samples(g, hop)
+        assert np.array_equal(gso.cpu().numpy(), so) and np.array_equal(gnb.cpu().numpy(), nb), f"samples {hop}"
+
+
+def test_tiles_against_other_cuts(rg, orc, monkeypatch):
+    """The pieces of rows above 16,384 IDs, when the first cut misses."""
+    rng = np.random.default_rng(10)
+    n = 60_000
+    deg = np.full(n, 3)
+    deg[:6] = [16385, 20000, 40000, 59999, 16384, 30011]
+    indptr = np.zeros(n + 1, np.int64)
+    indptr[1:] = np.cumsum(deg)
+    indices = np.concatenate([np.sort(rng.choice(n, size=int(d), replace=False)).astype(np.int32) for d in deg])
+    train = np.arange(40, dtype=np.int32)
+    o = orc.Schedule(indptr, indices, train, 10, [40], 0, 0, 0, n_threads=8)
+    for scale in ("0.1", "1", "10"):
+        monkeypatch.setenv("RAPIDGNN_GUESS_SCALE", scale)
+        g = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), 10, [40], 0, 0, 0)
+        assert np.array_equal(rg.rg_schedule_samples(g, 0)[1].cpu().numpy(), o.samples(0)[1]), scale
