@@ -849,6 +849,7 @@ struct ShortRec {
     uint64_t state;
     int32_t deg;
     uint32_t batch;
+    int32_t lane;         // whose row it is
 };
 
 template <int R> __device__ __forceinline__ uint32_t rotate16(uint32_t x)      // the value R lanes away within the lane's row of sixteen
@@ -856,15 +857,18 @@ template <int R> __device__ __forceinline__ uint32_t rotate16(uint32_t x)      /
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + R, 0xF, 0xF, false);
 }
 
-// The number of keys of the lane's row of sixteen lanes (one key per lane) that are smaller than this lane's.
-__device__ __forceinline__ int count_smaller16(uint32_t k)
+// cnt += the keys among a row of sixteen lanes' `theirs`, this lane's own left out, that are smaller than this lane's `mine`: each of the
+// fifteen others comes by as the row is rotated, a subtraction takes it in and leaves the answer in the carry, and the carry is added.
+// (Two instructions per key; the compiler's own are three and a wait for each rotation.)  The wait in front is for `theirs`,
+// which may have just been written: the hardware does not hold a row rotation back for it.
+__device__ __forceinline__ void add_smaller16(uint32_t theirs, uint32_t mine, uint32_t &cnt)
 {
-    int cnt = 0;
-#define RG_ROT(R) cnt += rotate16<R>(k) < k ? 1 : 0;
-    RG_ROT(1) RG_ROT(2) RG_ROT(3) RG_ROT(4) RG_ROT(5) RG_ROT(6) RG_ROT(7) RG_ROT(8)
-    RG_ROT(9) RG_ROT(10) RG_ROT(11) RG_ROT(12) RG_ROT(13) RG_ROT(14) RG_ROT(15)
+    uint32_t scrap;
+#define RG_ROT(R) "v_sub_co_u32_dpp %0, vcc, %2, %3 row_ror:" #R " row_mask:0xf bank_mask:0xf\n\tv_addc_co_u32_e32 %1, vcc, 0, %1, vcc\n\t"
+    asm("s_nop 1\n\t" RG_ROT(1) RG_ROT(2) RG_ROT(3) RG_ROT(4) RG_ROT(5) RG_ROT(6) RG_ROT(7) RG_ROT(8)
+        RG_ROT(9) RG_ROT(10) RG_ROT(11) RG_ROT(12) RG_ROT(13) RG_ROT(14) RG_ROT(15)
+        : "=&v"(scrap), "+v"(cnt) : "v"(theirs), "v"(mine) : "vcc");
 #undef RG_ROT
-    return cnt;
 }
 
 // The sum of x over the lane's row of sixteen lanes, in all of them.
@@ -893,10 +897,9 @@ __device__ __forceinline__ uint32_t last_of16(uint32_t x) { return (uint32_t)__b
 
 // Four rows' IDs, one row per sixteen lanes: lane l16 of a row holds IDs l16, l16 + 16, ... in u[0 .. E), n of them in the
 // row (same in its lanes).  The min(n, f) with the smallest keys go to `out` in order and are marked.  All 64 lanes call it.
-// One ID per lane is decided by rank (see count_smaller16); more by halving the range of key values until exactly f keys
-// lie below, all four rows side by side and in vector instructions alone: with counts taken from lane masks on the scalar
-// unit instead, that unit, which a compute unit's four SIMDs share, was busier than the vector units (84 % against 79 % of its issue
-// slots, 22 M rows of 340 IDs on average at fan-out 5).
+// One or two IDs per lane are decided by rank; more by halving the range of key values until exactly f keys
+// lie below, all four rows side by side and in vector instructions alone: counts taken from lane masks are scalar work, and that
+// unit is as busy as the vector units (see sample_rows_kernel).
 template <int E, int MARK>
 __device__ __forceinline__ void emit_rows(const uint32_t (&u)[E], int n, int f, uint32_t lo, uint32_t hi, int l16, int32_t *__restrict__ out,
                                           const ReachedOfBatch &reached_b)
@@ -909,9 +912,17 @@ __device__ __forceinline__ void emit_rows(const uint32_t (&u)[E], int n, int f, 
         uint32_t k[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) k[e] = sel[e] ? key32(lo, hi, u[e]) : 0xFFFFFFFFu;       // (a missing key's stand-in is below nothing)
-        if (E == 1) {
-            const int smaller = count_smaller16(k[0]);
-            if (search) sel[0] = sel[0] && smaller < f;
+        if (E <= 2) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                uint32_t smaller = 0;
+#pragma unroll
+                for (int q = 0; q < E; ++q) {
+                    add_smaller16(k[q], k[e], smaller);
+                    if (q != e) smaller += k[q] < k[e] ? 1u : 0u;
+                }
+                if (search) sel[e] = sel[e] && smaller < (uint32_t)f;
+            }
         } else {
             uint32_t from = 0, to = 0xFFFFFFFFu, t = to >> 1;     // fewer than f keys lie below `from`, at least f at or below `to`
             for (int step = 0; step < 34; ++step) {              // (distinct keys are told apart in 32 steps; repeated IDs of a damaged row never)
@@ -967,7 +978,7 @@ __device__ __forceinline__ void sample_short_rows(const ShortRec *recs, int coun
     // this lane's row of the round, and its IDs (0 where the row has none)
     auto fetch = [&](int it, ShortRec &r, uint32_t (&u)[4]) {
         const int slot = it * 4 + sg;
-        r = slot < count ? recs[slot] : ShortRec{0, 0, 0, 0, 0};
+        r = slot < count ? recs[slot] : ShortRec{};
         const int32_t *row = indices + r.row_begin;
 #pragma unroll
         for (int e = 0; e < 4; ++e) u[e] = l16 + 16 * e < r.deg ? (uint32_t)row[l16 + 16 * e] : 0u;
@@ -990,11 +1001,12 @@ __device__ __forceinline__ void sample_short_rows(const ShortRec *recs, int coun
     }
 }
 
-// Where a lane's short row goes in the list: shortest rows first, by the number of IDs per lane ((deg - 1) / 16), lane
-// order within a kind.  mine: this lane has a row of 1 .. SHORT_ROW IDs.  All 64 lanes call it.
+// Where a lane's row goes in the list of a group's rows that are sampled four at a time: shortest rows first, by the number of
+// IDs per lane ((deg - 1) >> SHIFT, below 4), lane order within a kind.  mine: this lane has such a row.  All 64 lanes call it.
+template <int SHIFT>
 __device__ __forceinline__ int short_row_slot(bool mine, int deg, int lane)
 {
-    const int kind = mine ? (deg - 1) >> 4 : -1;
+    const int kind = mine ? (deg - 1) >> SHIFT : -1;
     int at = 0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -1166,9 +1178,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CAP <= 
             const bool mine = in && !tiny && deg_lane > 0 && deg_lane <= SHORT_ROW;
             const int count = __popcll(ballot64(mine));
             if (count != 0) {
-                const int at = short_row_slot(mine, deg_lane, lane);
+                const int at = short_row_slot<4>(mine, deg_lane, lane);
                 __syncthreads();
-                if (mine) short_recs[at] = ShortRec{rb_lane, out_lane, (uint64_t)S_lane, deg_lane, b_lane};
+                if (mine) short_recs[at] = ShortRec{rb_lane, out_lane, (uint64_t)S_lane, deg_lane, b_lane, lane};
                 __syncthreads();
                 sample_short_rows<MARK>(short_recs, count, a.indices, f, a.samp_nbr, a.reached, lane);
             }
@@ -1375,10 +1387,81 @@ __device__ __forceinline__ void emit_row(const uint32_t *cand, int cnt, int f, u
     }
 }
 
+// Four rows of 65 .. MID_ROW IDs, sixteen lanes each (they are listed shortest first, so those of a round are of a kind).  A lane
+// takes four consecutive IDs of every 64; what passes the guessed cut goes to the row's list (`mine`), in order, from where
+// emit_rows takes it.  Returns the lanes (of the group) whose rows let too few or too many through: they are streamed like longer rows.
+// NQ: how many times 64 IDs the round's longest row has.
+// A row on its own spends more on its set-up and its cut, on the scalar unit above all, than on its keys: 2.45 M nodes, 5.8 M such rows,
+// fan-outs 15, 10, 5, some 230 instructions a row against 110 so, the launches 7.7 -> 7.3 ms; 50, 50 1.60 -> 1.45.
+constexpr int MID_STRIDE = ROWS_ROOM + 16;       // (sixteen banks further on for the next row)
+template <int NQ, int MARK>
+__device__ __forceinline__ unsigned long long sample_mid_round(const ShortRec &r, bool active, const int32_t *__restrict__ indices, int f, float lambda,
+                                                               int32_t *__restrict__ samp_nbr, const ReachedMaps &reached, int l16, uint32_t *mine)
+{
+    const uint32_t lo = (uint32_t)r.state, hi = (uint32_t)(r.state >> 32);
+    const char *row = reinterpret_cast<const char *>(indices + r.row_begin);
+    u32x4 u[NQ];
+    int first[NQ];                                               // from which of a lane's four IDs on they count
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int p = 64 * q + 4 * l16, at = min(p, r.deg - 4);
+        first[q] = active ? p - at : 4;
+        u[q] = *reinterpret_cast<const u32x4_dword_aligned *>(row + 4u * (uint32_t)at);
+    }
+    const uint32_t cut = guessed_cut_of(fminf(lambda / (float)r.deg, 0.99f));
+    bool sel[NQ][4];
+    uint32_t x = 0;                                              // how many of each four, in a byte each
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const uint32_t id[4] = {u[q].x, u[q].y, u[q].z, u[q].w};
+        uint32_t c = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sel[q][e] = key32_open(lo, hi, id[e]) <= cut && first[q] <= e;
+            c += sel[q][e] ? 1u : 0u;
+        }
+        x |= c << (8 * q);
+    }
+    const uint32_t incl = prefix16(x), all = last_of16(incl), place = incl - x + all * 0x01010100u;
+    const int n = (int)((all * 0x01010101u) >> 24);
+    const bool fits = n >= f && n <= ROWS_ROOM;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const uint32_t id[4] = {u[q].x, u[q].y, u[q].z, u[q].w};
+        uint32_t *to = mine + ((place >> (8 * q)) & 0xFFu);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (sel[q][e] && fits) *to++ = id[e];
+    }
+    wave_lds_order();
+    const int take = fits && active ? n : 0;
+    const ReachedOfBatch reached_b = reached_of<MARK>(reached, r.batch);
+    int32_t *out = samp_nbr + r.out;
+#define RG_EMIT(E)                                                                                                    \
+    do {                                                                                                              \
+        uint32_t v[E];                                                                                                \
+        _Pragma("unroll") for (int e = 0; e < E; ++e) v[e] = mine[l16 + 16 * e];                                      \
+        emit_rows<E, MARK>(v, take, f, lo, hi, l16, out, reached_b);                                                  \
+    } while (0)
+    if (ballot64(take > 64) != 0ull) RG_EMIT(8);
+    else if (ballot64(take > 32) != 0ull) RG_EMIT(4);
+    else if (ballot64(take > 16) != 0ull) RG_EMIT(2);
+    else RG_EMIT(1);
+#undef RG_EMIT
+    wave_lds_order();
+    unsigned long long again = 0ull, failed = ballot64(active && !fits && l16 == 0);
+    while (failed != 0ull) {
+        const int l = __builtin_amdgcn_readfirstlane(__ffsll((long long)failed) - 1);
+        failed &= failed - 1ull;
+        again |= 1ull << __builtin_amdgcn_readlane(r.lane, l);
+    }
+    return again;
+}
+
 template <int MARK>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sample_rows_kernel(HopArgs a)
 {
-    __shared__ uint32_t cand[ROWS_ROOM];
+    __shared__ uint32_t cand[4 * MID_STRIDE];                    // one streamed row's candidates, or those of four rows
     __shared__ ShortRec short_recs[64];
     const int lane = threadIdx.x;
     const int f = (int)a.fanout;
@@ -1433,14 +1516,31 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sa
             const bool mine = !tiny && deg_lane > 0 && deg_lane <= SHORT_ROW;
             const int count = __popcll(ballot64(mine));
             if (count != 0) {
-                const int at = short_row_slot(mine, deg_lane, lane);
+                const int at = short_row_slot<4>(mine, deg_lane, lane);
                 wave_lds_order();
-                if (mine) short_recs[at] = ShortRec{rb_lane, out_lane, S_lane, deg_lane, b_lane};
+                if (mine) short_recs[at] = ShortRec{rb_lane, out_lane, S_lane, deg_lane, b_lane, lane};
                 wave_lds_order();
                 sample_short_rows<MARK>(short_recs, count, a.indices, f, a.samp_nbr, a.reached, lane);
             }
         }
-        unsigned long long todo = ballot64(deg_lane > SHORT_ROW && (is_tile || deg_lane <= BIG_ROW));
+        unsigned long long todo = ballot64(deg_lane > MID_ROW && (is_tile || deg_lane <= BIG_ROW));      // rows that the whole wave streams
+        const bool mid = deg_lane > SHORT_ROW && deg_lane <= MID_ROW;
+        if (const int count = __popcll(ballot64(mid))) {
+            const int at = short_row_slot<6>(mid, deg_lane, lane);
+            wave_lds_order();
+            if (mid) short_recs[at] = ShortRec{rb_lane, out_lane, S_lane, deg_lane, b_lane, lane};
+            wave_lds_order();
+            const float lambda = guessed_candidates(f) * a.guess_scale;
+            const int l16 = lane & 15, sg = lane >> 4;
+            for (int k0 = 0; k0 < count; k0 += 4) {
+                const ShortRec r = short_recs[min(k0 + sg, count - 1)];
+                const bool active = k0 + sg < count;
+                uint32_t *mine = cand + sg * MID_STRIDE;
+                if (ballot64(r.deg > 192) != 0ull) todo |= sample_mid_round<4, MARK>(r, active, a.indices, f, lambda, a.samp_nbr, a.reached, l16, mine);
+                else if (ballot64(r.deg > 128) != 0ull) todo |= sample_mid_round<3, MARK>(r, active, a.indices, f, lambda, a.samp_nbr, a.reached, l16, mine);
+                else todo |= sample_mid_round<2, MARK>(r, active, a.indices, f, lambda, a.samp_nbr, a.reached, l16, mine);
+            }
+        }
         if (todo == 0ull) continue;
         // the guessed cut of this lane's row; a row that fits the candidates' room and would lose little is taken whole
         uint32_t cut_lane = 0xFFFFFFFFu;
