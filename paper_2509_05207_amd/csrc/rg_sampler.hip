@@ -68,7 +68,10 @@ constexpr int TILE_PIECE = 65536;        // ... in near-equal pieces of at most 
                                          // sampled among the tile jobs, where the batches that share it meet in the caches.  Measured on the five
                                          // workloads: pieces of 16,384 cost 8 % more sampling time on the largest graph, pieces of 131,072 7 %;
                                          // tiling from 8,192 IDs on is 3 % slower there and 3 % faster on large_sparse.)
-__device__ __host__ __forceinline__ int64_t tiles_of(int64_t deg) { return deg > BIG_ROW ? (deg + TILE_PIECE - 1) / TILE_PIECE : 0; }
+// Where a frontier is too small to fill the chip, a piece is what its launch waits for, at one memory latency per kilobyte: pieces of
+// SMALL_PIECE there.
+constexpr int SMALL_PIECE = 16384;
+__device__ __host__ __forceinline__ int64_t tiles_of(int64_t deg, int64_t piece) { return deg > BIG_ROW ? (deg + piece - 1) / piece : 0; }
 
 // Per frontier node, by position: where its row starts, its degree, its batch and its stream.
 struct NodeRecs {
@@ -134,6 +137,27 @@ __device__ __forceinline__ bool add_hub_row(const HubTable &h, uint32_t v, int64
     return false;
 }
 
+// A frontier's new IDs ascend, so the like places of all batches hold about the same nodes: taken one after the other (unit u:
+// round u / n_batches of batch u mod n_batches), what they read of a graph that many batches cover is still in the caches.
+// Small batches would leave many units unfilled, batches of very different sizes leave many empty, and where the frontiers together
+// have less than half as many entries as the graph has nodes there is little to share: those go by frontier position (n_batches = 0).
+// By position / by place: 233,000 nodes, 147 batches of 80,000, fan-out 10: the sampling launches 3.06 / 2.84 ms; 2.45 M nodes, 196 of 110,000, 7.17 / 6.94, and the
+// records of its nodes (random 128-byte lines of indptr) 448 / 308 us; 147 of 14,000, records 82 / 52 us; 111 M nodes, 147 of 5,800, 1.45 / 1.49 ms.
+struct ByPlace {
+    const int64_t *batch_off;                   // dev
+    uint32_t n_batches;
+    int64_t longest;                            // nodes of the largest batch
+};
+constexpr int PLACE_NODES = 1024;               // nodes per batch, on average, from which on
+static ByPlace by_place(const HopData &cur, uint32_t beta, int64_t n_nodes)
+{
+    ByPlace p{cur.off_dev, beta, 0};
+    for (uint32_t b = 0; b < beta; ++b) p.longest = std::max(p.longest, cur.off_host[b + 1] - cur.off_host[b]);
+    const int64_t n = cur.off_host[beta];
+    if (n < (int64_t)beta * PLACE_NODES || 2 * n < n_nodes || p.longest * beta > 2 * n || n >= (int64_t)1 << 30) p.n_batches = 0;
+    return p;
+}
+
 // Also adds up, over the frontier, what the hop will read of the adjacency: [0] the sum of the degrees (in IDs),
 // [1] the part of it in rows of up to BIG_ROW IDs (the rows that are not sampled as tiles), [2] the number of rows of
 // 1 .. SHORT_ROW IDs and [3] the IDs in them; of flagged hub rows, [4] how many and [5] how many tiles they make.  The
@@ -153,9 +177,9 @@ constexpr int SHORT_ROW = 64;            // rows of up to this many IDs are samp
 constexpr int NODE_THREADS = 256;
 constexpr int NODE_PER_THREAD = 4;
 constexpr int NODE_CHUNK = NODE_THREADS * NODE_PER_THREAD;
-constexpr uint32_t COUNT_BITS = 12;      // samples: at most RG_MAX_FANOUT; tiles: at most 2^31 / TILE_PIECE = 2^15
+constexpr uint32_t COUNT_BITS = 12;      // samples: at most RG_MAX_FANOUT; tiles: at most 2^31 / SMALL_PIECE = 2^17
 constexpr uint32_t HUB_FLAG = 1u << 31;
-static_assert(RG_MAX_FANOUT < (1u << COUNT_BITS) && (((uint64_t)1 << 31) / TILE_PIECE) < (1u << (31 - COUNT_BITS)), "");
+static_assert(RG_MAX_FANOUT < (1u << COUNT_BITS) && (((uint64_t)1 << 31) / SMALL_PIECE) < (1u << (31 - COUNT_BITS)), "");
 __device__ __forceinline__ uint32_t samples_of(uint32_t count) { return count & ((1u << COUNT_BITS) - 1u); }
 // The tile jobs of a node's row among those of the rows asked for.
 enum { TILES_OF_ROWS = 1, TILES_OF_HUB_ROWS = 2 };
@@ -167,14 +191,21 @@ __device__ __forceinline__ uint32_t tiles_in(uint32_t count, int which)
 template <bool HUBS>
 __global__ void __launch_bounds__(NODE_THREADS) node_records_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ frontier, int64_t n,
                                                                     const int64_t *__restrict__ batch_off, uint32_t n_batches, const uint64_t *__restrict__ batch_seed,
-                                                                    uint32_t hop, uint32_t fanout, NodeRecs r, uint32_t *__restrict__ count,
+                                                                    uint32_t hop, uint32_t fanout, int64_t tile_piece, NodeRecs r, uint32_t *__restrict__ count,
                                                                     unsigned long long *__restrict__ chunk_sum, uint32_t *__restrict__ chunk_hub /* HUBS */, int64_t n_nodes,
-                                                                    unsigned long long *__restrict__ total, HubTable hubs)
+                                                                    unsigned long long *__restrict__ total, HubTable hubs, int by_place)
 {
+    // by_place: the workgroup's chunk is one of those that begin in batch (blockIdx mod n_batches), see ByPlace
+    int64_t chunk = blockIdx.x;
+    if (by_place) {
+        const uint32_t round = blockIdx.x / n_batches, b = blockIdx.x - round * n_batches;
+        chunk = batch_off[b] / NODE_CHUNK + round;
+        if (chunk >= (b + 1 < n_batches ? batch_off[b + 1] / NODE_CHUNK : (n + NODE_CHUNK - 1) / NODE_CHUNK)) return;
+    }
     constexpr int SUMS = HUBS ? DEG_SUMS : DEG_SUMS - 2;
     __shared__ unsigned long long part[SUMS + 1][NODE_THREADS / 64];
     unsigned long long acc[SUMS + 1] = {};       // see above; and the chunk's sums
-    const int64_t base = (int64_t)blockIdx.x * NODE_CHUNK;
+    const int64_t base = chunk * NODE_CHUNK;
     int32_t v[NODE_PER_THREAD];
     int64_t b0[NODE_PER_THREAD], deg[NODE_PER_THREAD];
 #pragma unroll
@@ -207,7 +238,7 @@ __global__ void __launch_bounds__(NODE_THREADS) node_records_kernel(const int64_
         r.batch[i] = b;
         r.state[i] = combine(stream, (uint64_t)(uint32_t)v[k]);
         const uint32_t samples = (uint32_t)(d < (int64_t)fanout ? d : (int64_t)fanout);
-        const uint32_t tiles = (uint32_t)tiles_of(d);
+        const uint32_t tiles = (uint32_t)tiles_of(d, tile_piece);
         const bool hub = HUBS && d >= hubs.min_deg && add_hub_row(hubs, (uint32_t)v[k], b0[k], d, n_nodes);
         count[i] = samples | tiles << COUNT_BITS | (hub ? HUB_FLAG : 0u);
         acc[0] += (unsigned long long)d;
@@ -224,8 +255,8 @@ __global__ void __launch_bounds__(NODE_THREADS) node_records_kernel(const int64_
     __syncthreads();
     if (threadIdx.x <= SUMS) {
         const unsigned long long a = part[threadIdx.x][0] + part[threadIdx.x][1] + part[threadIdx.x][2] + part[threadIdx.x][3];
-        if (HUBS && threadIdx.x == 5) chunk_hub[blockIdx.x] = (uint32_t)a;
-        if (threadIdx.x == SUMS) chunk_sum[blockIdx.x] = a;
+        if (HUBS && threadIdx.x == 5) chunk_hub[chunk] = (uint32_t)a;
+        if (threadIdx.x == SUMS) chunk_sum[chunk] = a;
         else if (a) atomicAdd(total + SUMS * (blockIdx.x % DEG_SUM_SLOTS) + threadIdx.x, a);
     }
 }
@@ -1043,13 +1074,13 @@ __global__ void __launch_bounds__(NODE_THREADS) tile_nodes_kernel(const uint32_t
         for (uint32_t t = 0; t < tiles[k]; ++t, ++j) { r.node[j] = first + k; r.t[j] = (int32_t)t; }
 }
 // One thread per tile job.
-__global__ void tile_records_kernel(const int64_t *__restrict__ row_begin, const int32_t *__restrict__ deg, const uint64_t *__restrict__ state, int64_t n_tiles, TileRecs r)
+__global__ void tile_records_kernel(const int64_t *__restrict__ row_begin, const int32_t *__restrict__ deg, const uint64_t *__restrict__ state, int64_t n_tiles, int64_t tile_piece, TileRecs r)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n_tiles) return;
     const int64_t i = r.node[j], t = r.t[j];
     const int64_t d = deg[i];
-    const int64_t T = tiles_of(d);
+    const int64_t T = tiles_of(d, tile_piece);
     const int64_t first_pos = t * d / T, last_pos = (t + 1) * d / T;
     r.begin[j] = row_begin[i] + first_pos;
     r.len[j] = (int32_t)(last_pos - first_pos);
@@ -1083,7 +1114,10 @@ __global__ void tile_bucket_place_kernel(const int64_t *__restrict__ begin, int6
 struct HopArgs {
     const int32_t *indices;
     const int32_t *frontier; int64_t n_frontier;
-    int64_t n_full_groups, n_units;                                    // set by launch_hop: see there
+    int64_t n_full_groups, n_units;                                    // set by launch_hop: see there ...
+    int tail_shift; int64_t n_own;                                     // ... as are these, for sample_rows_kernel: nodes of a unit behind the full groups (their logarithm), units that belong to a workgroup
+    ByPlace place; int64_t n_full_rounds;                              // (rounds of full groups, where units go by place)
+    int64_t tile_piece;                                                // tiles_of
     int min_deg;                                                       // rows of up to this many IDs are not sampled one per wave but four at a time, a group's short rows first (sample_kernel<.., true>); 0: none are
     NodeRecs rec;
     uint32_t fanout;
@@ -1468,6 +1502,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sa
     // Tiles first, dealt out in turn; in each round XCD x takes a contiguous eighth of the round's jobs (see sample_kernel).
     int64_t k = blockIdx.x;
     if (a.tile_order && (gridDim.x & 7u) == 0) k = (int64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    int64_t own_unit = k >= a.n_tiles ? k - a.n_tiles : -1;
     int64_t w = 0, tile_begin = 0; int tile_len = 0; uint64_t tile_state = 0;
     if (k < a.n_tiles) { w = a.tile_order ? a.tile_order[k] : k; tile_begin = a.tile.begin[w]; tile_len = a.tile.len[w]; tile_state = a.tile.state[w]; }
     for (;;) {
@@ -1484,11 +1519,25 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sa
             k += gridDim.x;
             if (k < a.n_tiles) { w = a.tile_order ? a.tile_order[k] : k; tile_begin = a.tile.begin[w]; tile_len = a.tile.len[w]; tile_state = a.tile.state[w]; }
         } else {
-            const int64_t g = grab_work(a.next_work, lane);
+            // Workgroups without a tile have their first unit of nodes by index, the others come through the counter (7,168 waves that
+            // ask it at once wait 25 us for their turns, which is a small launch's whole time).
+            int64_t g = own_unit;
+            own_unit = -1;
+            if (g < 0) {
+                if (a.n_own >= a.n_units) break;
+                g = a.n_own + grab_work(a.next_work, lane);
+            }
             if (g >= a.n_units) break;
-            const bool full = g < a.n_full_groups;               // 64 nodes, or 16 of the launch's last nodes
-            const int64_t i_lane = (full ? g << 6 : (a.n_full_groups << 6) + ((g - a.n_full_groups) << 4)) + lane;
-            const bool in = (full || lane < 16) && i_lane < a.n_frontier;
+            const bool full = g < a.n_full_groups;               // 64 nodes, or fewer of the launch's last nodes
+            // its nodes: in frontier order, or the like places of all batches one after the other
+            int64_t i0 = full ? g << 6 : (a.n_full_groups << 6) + ((g - a.n_full_groups) << a.tail_shift), i_end = a.n_frontier;
+            if (a.place.n_batches) {
+                const uint32_t at = (uint32_t)(full ? g : g - a.n_full_groups), round = at / a.place.n_batches, b = at - round * a.place.n_batches;
+                i0 = a.place.batch_off[b] + (full ? (int64_t)round << 6 : (a.n_full_rounds << 6) + ((int64_t)round << a.tail_shift));
+                i_end = a.place.batch_off[b + 1];
+            }
+            const int64_t i_lane = i0 + lane;
+            const bool in = (full || lane < 1 << a.tail_shift) && i_lane < i_end;
             if (in) {
                 rb_lane = a.rec.row_begin[i_lane];
                 deg_lane = a.rec.deg[i_lane];
@@ -1647,7 +1696,7 @@ __global__ void __launch_bounds__(64) sample_merge_kernel(HopArgs a)
             firsts &= firsts - 1ull;
             const int64_t i = bcast64(i_lane, l);
             const int64_t w = base + l;
-            const int64_t T = tiles_of(a.rec.deg[i]);
+            const int64_t T = tiles_of(a.rec.deg[i], a.tile_piece);
             const uint32_t b = a.rec.batch[i];
             const uint64_t S = a.rec.state[i];
             const int32_t *row = a.tile_out + w * f;
@@ -1869,10 +1918,13 @@ constexpr int HUB_TILES_PER_CU = 24;
 // some 10 us a hop.
 constexpr uint32_t HUB_BATCHES = 16;
 
+// Nodes per compute unit from which on a frontier gives every resident wave a group of 64.
+constexpr int SMALL_FRONTIER = 28 * 64;
+
 // Every workgroup of the sampling launch must be resident from the start (tiles are dealt out by workgroup index), so
 // the grid is what the chip holds of this kernel, or the amount of work if that is less.
 typedef void (*HopKernel)(HopArgs);
-template <HopKernel SAMPLE, HopKernel MERGE>
+template <bool ROWS, HopKernel SAMPLE, HopKernel MERGE>
 static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, bool fine_tail, bool fine_if_few, hipStream_t st)
 {
     HopArgs a = args;
@@ -1887,12 +1939,31 @@ static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, 
     // Groups of 64 nodes, except that with fine_tail the last 128 nodes per resident wave (and always what is left of
     // the frontier after the last whole group) are handed out 16 at a time.
     const int64_t resident = (int64_t)n_cu * per_cu;
+    const bool few = a.n_frontier < resident * 64;               // fewer groups of 64 than waves
     int64_t tail_nodes = fine_tail ? std::min<int64_t>(a.n_frontier, resident * 128) : 0;
-    if (fine_if_few && a.n_frontier < resident * 64) tail_nodes = a.n_frontier;       // fewer groups of 64 than waves: sixteens throughout
-    a.n_full_groups = (a.n_frontier - tail_nodes) / 64;
-    a.n_units = a.n_full_groups + (a.n_frontier - a.n_full_groups * 64 + 15) / 16;
+    a.tail_shift = 4;
+    if (ROWS) {
+        // A frontier that leaves waves without a group of 64 is split so that all waves that it can occupy have one unit, of as few nodes as that
+        // takes (four at least: rows up to MID_ROW IDs are sampled four at a time), or twice as fine where rows are long work.
+        if (few) {
+            int shift = 2;
+            while (shift < 6 && (a.n_frontier >> shift) > resident) shift += 2;
+            if (fine_if_few && shift > 2) shift -= 2;
+            if (shift < 6) { a.tail_shift = shift; tail_nodes = a.n_frontier; }
+        }
+    } else if (fine_if_few && few) tail_nodes = a.n_frontier;    // sixteens throughout
+    if (ROWS && a.place.n_batches) {
+        const int64_t n_batches = a.place.n_batches, longest = a.place.longest;
+        a.n_full_rounds = std::max<int64_t>(0, longest - (tail_nodes + n_batches - 1) / n_batches) / 64;
+        a.n_full_groups = a.n_full_rounds * n_batches;
+        a.n_units = a.n_full_groups + (((longest - a.n_full_rounds * 64 - 1) >> a.tail_shift) + 1) * n_batches;
+    } else {
+        a.n_full_groups = (a.n_frontier - tail_nodes) / 64;
+        a.n_units = a.n_full_groups + (((a.n_frontier - a.n_full_groups * 64 - 1) >> a.tail_shift) + 1);
+    }
     const int64_t n_work = a.n_tiles + a.n_units;
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_work, resident));
+    a.n_own = std::max<int64_t>(0, (int64_t)grid - a.n_tiles);
     hipLaunchKernelGGL(SAMPLE, dim3(grid), dim3(64), 0, st, a);
     if (a.n_tiles > 0) hipLaunchKernelGGL(MERGE, dim3(merge_grid), dim3(64), 0, st, a);
     return RG_OK;
@@ -1905,14 +1976,21 @@ constexpr int POS_THREADS = 256;
 template <int MARK>
 __global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int32_t *__restrict__ indices, NodeRecs rec, int64_t n_cur, uint32_t f,
                                                                        const int64_t *__restrict__ samp_off, int32_t *__restrict__ samp_nbr,
-                                                                       ReachedMaps reached)
+                                                                       ReachedMaps reached, ByPlace place, int64_t n_units)
 {
     const uint32_t per_round = f >= POS_THREADS ? 1u : POS_THREADS / f;       // nodes per workgroup round
     const uint32_t sub = f >= POS_THREADS ? 0u : threadIdx.x / f;              // this lane's node within the round
     const uint32_t t0 = f >= POS_THREADS ? threadIdx.x : threadIdx.x - sub * f;
     const uint32_t step = f >= POS_THREADS ? POS_THREADS : f;                  // a lane's next draw of the same node
     if (sub >= per_round) return;
-    for (int64_t i = (int64_t)blockIdx.x * per_round + sub; i < n_cur; i += (int64_t)gridDim.x * per_round) {
+    for (int64_t unit = blockIdx.x; unit < n_units; unit += gridDim.x) {
+        int64_t i = unit * per_round + sub, i_end = n_cur;
+        if (place.n_batches) {
+            const uint32_t round = (uint32_t)unit / place.n_batches, b = (uint32_t)unit - round * place.n_batches;
+            i = place.batch_off[b] + (int64_t)round * per_round + sub;
+            i_end = place.batch_off[b + 1];
+        }
+        if (i >= i_end) continue;
         const uint32_t deg = (uint32_t)rec.deg[i];
         const uint32_t cnt = deg < f ? deg : f;
         if (t0 >= cnt) continue;
@@ -1935,15 +2013,15 @@ __global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int
 // hold bits: nothing scattered leaves the compute unit.  Marked one by one from the sampling kernels, the memory system takes 25 G
 // atomic ORs or 88 G byte stores a second and the kernels carry the address arithmetic.  233 k nodes, 29 M samples: 0.05 ms; 2.45 M nodes, 167 M samples:
 // 0.43, and the launches that marked bytes themselves 3.9 -> 2.2 ms; 146 M samples in three hops: 0.32, launches that marked
-// bits 10.6 -> 9.6.
+// bits 10.6 -> 9.6.  A lane reads four IDs at a time: one at a time, twice as many loads of a quarter the size in flight, 424 us instead of 327 and 328 instead of 293.
 // The pieces of a batch run on one XCD (workgroup g runs on XCD g mod 8) at about the same time and share the reads; the
 // batches left over from whole eights are dealt out over all XCDs, or one batch would have an eighth of the chip.
 constexpr int MARK_THREADS = 1024;
-constexpr int MARK_WORDS = 32768;                        // 128 KB of LDS, 1,048,576 IDs: every piece reads all samples of its batch, so few large ones (of 64 KB: 0.54 ms for the 167 M below, so 0.43)
+constexpr int MARK_WORDS = 38400;                        // a piece's words at most: 150 KB of LDS, 1,228,800 IDs
 constexpr int MARK_XCDS = 8;
-constexpr int MARK_IN_FLIGHT = 8;
+constexpr int MARK_IN_FLIGHT = 4;                        // loads of four IDs
 constexpr uint64_t MARK_SPARSE = 512, MARK_MANY = 1 << 21, MARK_CROWD = 64;      // see marks_want_a_pass
-constexpr uint64_t MARK_PASS = 320 << 10, MARK_ROUND = 240 << 10;
+constexpr uint64_t MARK_PASS = 320 << 10, MARK_ROUND = 240 << 10, MARK_FULL = 32768;
 constexpr int64_t MARK_PART = 1 << 18;                   // samples per part, at least, where there are too few pieces to fill the chip
 
 __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *__restrict__ samp_nbr, const int64_t *__restrict__ samp_off, const int64_t *__restrict__ batch_off,
@@ -1967,14 +2045,19 @@ __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *
     const int64_t first = samp_off[batch_off[b]], n = samp_off[batch_off[b + 1]] - first;
     const int64_t lo = first + n * part / parts, hi = first + n * (part + 1) / parts;
     const uint32_t id0 = piece * piece_words * 32u, n_ids = piece_words * 32u;
-    for (int64_t j0 = lo + threadIdx.x; j0 < hi; j0 += MARK_IN_FLIGHT * MARK_THREADS) {
-        uint32_t u[MARK_IN_FLIGHT];
+    auto mark = [&](uint32_t id) {
+        const uint32_t u = id - id0;
+        if (u < n_ids) atomicOr(&bits[u >> 5], 1u << (u & 31));
+    };
+    const int64_t whole_end = lo + (hi - lo) / 4 * 4;            // (vectors need no more than the alignment of an ID)
+    for (int64_t j0 = lo + 4 * threadIdx.x; j0 < whole_end; j0 += 4 * MARK_IN_FLIGHT * MARK_THREADS) {
+        u32x4 u[MARK_IN_FLIGHT];
 #pragma unroll
-        for (int q = 0; q < MARK_IN_FLIGHT; ++q) u[q] = (uint32_t)samp_nbr[min(j0 + q * MARK_THREADS, hi - 1)] - id0;      // (past the end: the last sample again)
+        for (int q = 0; q < MARK_IN_FLIGHT; ++q) u[q] = *reinterpret_cast<const u32x4_dword_aligned *>(samp_nbr + min(j0 + q * 4 * MARK_THREADS, whole_end - 4));      // (past the end: the last ones again)
 #pragma unroll
-        for (int q = 0; q < MARK_IN_FLIGHT; ++q)
-            if (u[q] < n_ids) atomicOr(&bits[u[q] >> 5], 1u << (u[q] & 31));
+        for (int q = 0; q < MARK_IN_FLIGHT; ++q) { mark(u[q].x); mark(u[q].y); mark(u[q].z); mark(u[q].w); }
     }
+    if (whole_end + threadIdx.x < hi) mark((uint32_t)samp_nbr[whole_end + threadIdx.x]);
     __syncthreads();
     // a thread per group of eight words: written where it holds bits (the map is clear otherwise), its flag set
     const uint64_t word0 = (uint64_t)piece * piece_words;
@@ -1997,7 +2080,16 @@ __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *
     }
 }
 
-static uint32_t mark_piece_words(const ReachedMaps &m) { return (uint32_t)std::min<uint64_t>(MARK_WORDS, m.words_per_batch); }      // (both multiples of eight)
+// Every piece reads all samples of its batch, so the pieces are as few as LDS allows, of equal size; one more where that
+// costs no further round of workgroups, since a workgroup then has fewer bits to set (2.45 M nodes in two pieces / three: 147 batches of
+// 1.1 M samples in 294 or 441 workgroups on 256 compute units 345 / 327 us, 196 batches of 0.7 M in 392 or 588 233 / 293).
+static uint32_t mark_pieces(const ReachedMaps &m, uint32_t beta, int n_cu)
+{
+    const uint64_t least = (m.words_per_batch + MARK_WORDS - 1) / MARK_WORDS, cus = (uint64_t)n_cu;
+    const auto rounds = [&](uint64_t pieces) { return (pieces * beta + cus - 1) / cus; };
+    return (uint32_t)(least > 1 && rounds(least + 1) == rounds(least) ? least + 1 : least);
+}
+static uint32_t mark_piece_words(const ReachedMaps &m, uint32_t pieces) { return (uint32_t)(((m.words_per_batch + pieces - 1) / pieces + 7) / 8 * 8); }
 
 // By a pass or by the sampling kernels themselves.  The pass clears and looks through the words of every batch's bitmap, some
 // 6 us per 128 KB of LDS and compute unit, and 8 us for itself, more where a few workgroups have all the samples; an atomic OR
@@ -2012,18 +2104,18 @@ static uint32_t mark_piece_words(const ReachedMaps &m) { return (uint32_t)std::m
 //    and MARK_ROUND per round of full workgroups (113 batches on 76,000 nodes, 115,000 and 1 M samples, 393 / 384 us).
 static bool marks_want_a_pass(const ReachedMaps &m, uint32_t beta, uint64_t n_marks, int n_cu)
 {
-    const uint64_t words = m.words_per_batch * (uint64_t)beta, piece_words = mark_piece_words(m);
+    const uint64_t words = m.words_per_batch * (uint64_t)beta;
     if (n_marks * MARK_SPARSE < words * 32) return false;
     if (n_marks >= MARK_MANY || n_marks >= words * MARK_CROWD) return true;
-    const uint64_t units = (m.words_per_batch + piece_words - 1) / piece_words * beta, cus = (uint64_t)n_cu;
-    return units * 4 >= cus && n_marks >= MARK_PASS + MARK_ROUND * ((units + cus - 1) / cus) * piece_words / MARK_WORDS;
+    const uint32_t pieces = mark_pieces(m, beta, n_cu);
+    const uint64_t units = (uint64_t)pieces * beta, cus = (uint64_t)n_cu;
+    return units * 4 >= cus && n_marks >= MARK_PASS + MARK_ROUND * ((units + cus - 1) / cus) * mark_piece_words(m, pieces) / MARK_FULL;
 }
 
 static rg_status launch_mark_pass(const HopData &cur, uint32_t beta, const ReachedMaps &m, int n_cu, hipStream_t st)
 {
     if (cur.n_samples == 0) return RG_OK;
-    const uint32_t piece_words = mark_piece_words(m);
-    const uint32_t pieces = (uint32_t)((m.words_per_batch + piece_words - 1) / piece_words);
+    const uint32_t pieces = mark_pieces(m, beta, n_cu), piece_words = mark_piece_words(m, pieces);
     // a few batches of many samples are read in parts, whose bits are ORed into the map
     const uint64_t units = (uint64_t)pieces * beta;
     const uint32_t parts = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(cur.n_samples / beta / MARK_PART, n_cu / (int64_t)units));
@@ -2047,6 +2139,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
 {
     const int64_t n_cur = cur.off_host[beta];
     const int64_t n_chunks = (n_cur + NODE_CHUNK - 1) / NODE_CHUNK;
+    const ByPlace place = by_place(cur, beta, g->n_nodes);
     // Hub rows (see hub_sample_kernel): where the table of a row is shared by the batches of an epoch -- behind the seeds,
     // which hold a node once.
     HubTable hubs{INT32_MAX, nullptr, nullptr, nullptr, nullptr};
@@ -2058,6 +2151,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
             hubs.min_deg = std::max((int32_t)std::min(line, 2147483647.0), BIG_ROW + 1);
     }
     const bool look_for_hubs = *looked_for_hubs = hubs.min_deg != INT32_MAX;
+    const int64_t tile_piece = fanout <= (uint32_t)ROWS_FANOUT && (hop == 0 || beta < HUB_BATCHES) && !look_for_hubs && n_cur < (int64_t)n_cu * SMALL_FRONTIER ? SMALL_PIECE : TILE_PIECE;
     uint32_t *count = nullptr, *chunk_hub = nullptr;
     unsigned long long *chunk_sum = nullptr;
     int64_t *samp_base = nullptr, *tile_base = nullptr;
@@ -2088,12 +2182,14 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     {
         ScopedTimer tm(KG_OFFSETS, st);
         const dim3 grid((unsigned)n_chunks), block(NODE_THREADS);
+        // (the chunks that begin in a batch, at most one more than fit it)
+        const dim3 record_grid(place.n_batches ? (unsigned)((place.longest / NODE_CHUNK + 2) * beta) : (unsigned)n_chunks);
         if (look_for_hubs)
-            hipLaunchKernelGGL(node_records_kernel<true>, grid, block, 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta, batch_seed, hop, fanout, rec, count, chunk_sum,
-                               chunk_hub, (int64_t)g->n_nodes, sum_deg_dev, hubs);
+            hipLaunchKernelGGL(node_records_kernel<true>, record_grid, block, 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta, batch_seed, hop, fanout, tile_piece, rec, count, chunk_sum,
+                               chunk_hub, (int64_t)g->n_nodes, sum_deg_dev, hubs, place.n_batches ? 1 : 0);
         else
-            hipLaunchKernelGGL(node_records_kernel<false>, grid, block, 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta, batch_seed, hop, fanout, rec, count, chunk_sum,
-                               chunk_hub, (int64_t)g->n_nodes, sum_deg_dev, hubs);
+            hipLaunchKernelGGL(node_records_kernel<false>, record_grid, block, 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta, batch_seed, hop, fanout, tile_piece, rec, count, chunk_sum,
+                               chunk_hub, (int64_t)g->n_nodes, sum_deg_dev, hubs, place.n_batches ? 1 : 0);
         hipLaunchKernelGGL(scan_chunks_kernel, dim3(1), dim3(CHUNK_SCAN_THREADS), 0, st, chunk_sum, (const uint32_t *)nullptr, n_chunks, samp_base, tile_base, cur.samp_off + n_cur);
         hipLaunchKernelGGL(sample_offsets_kernel, grid, block, 0, st, count, n_cur, samp_base, cur.samp_off);
         RG_HIP(hipGetLastError());
@@ -2119,8 +2215,9 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         if (fanout > 0 && n_cur > 0) {
             ScopedTimer tm(KG_SAMPLER, st);
             const int64_t per_round = fanout >= (uint32_t)POS_THREADS ? 1 : POS_THREADS / fanout;
-            const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_cur + per_round - 1) / per_round, (int64_t)n_cu * 64));
-#define RG_POSITIONS(M) hipLaunchKernelGGL(sample_positions_kernel<M>, dim3(grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, cur.samp_off, cur.samp_nbr, reached)
+            const int64_t n_units = place.n_batches ? (place.longest + per_round - 1) / per_round * beta : (n_cur + per_round - 1) / per_round;
+            const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_units, (int64_t)n_cu * 64));
+#define RG_POSITIONS(M) hipLaunchKernelGGL(sample_positions_kernel<M>, dim3(grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, cur.samp_off, cur.samp_nbr, reached, place, n_units)
             if (inline_marks) RG_POSITIONS(MARK_BITS);
             else RG_POSITIONS(MARK_NONE);
 #undef RG_POSITIONS
@@ -2169,7 +2266,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     if (n_tiles > 0) {
         ScopedTimer tm(KG_OFFSETS, st);
         hipLaunchKernelGGL(tile_nodes_kernel, dim3((unsigned)n_chunks), dim3(NODE_THREADS), 0, st, count, n_cur, tile_base, hub_jobs ? TILES_OF_ROWS : TILES_OF_ROWS | TILES_OF_HUB_ROWS, tile);
-        hipLaunchKernelGGL(tile_records_kernel, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, st, rec.row_begin, rec.deg, rec.state, n_tiles, tile);
+        hipLaunchKernelGGL(tile_records_kernel, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, st, rec.row_begin, rec.deg, rec.state, n_tiles, tile_piece, tile);
     }
     int32_t *tile_order = nullptr;
     bool group_tiles = n_tiles >= (int64_t)n_cu * 64 && n_tiles <= 0x7FFFFFFF;     // fewer jobs than two rounds of the resident waves: nothing to bring together
@@ -2206,7 +2303,20 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         int merge_span = 64;                              // tiles per look of a merging wave: 64 if that still occupies the chip's waves
         while (merge_span > 1 && n_tiles / merge_span < (int64_t)n_cu * 32) merge_span >>= 1;
         const unsigned merge_grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_tiles + merge_span - 1) / merge_span, (int64_t)n_cu * 64));
-        HopArgs a{g->indices, cur.ids, n_cur, 0, 0, short_rows ? SHORT_ROW : 0, rec, fanout, cur.samp_off, cur.samp_nbr, tile, n_tiles, tile_out, merge_span, tile_order, reached, next_work, 1.0f};
+        HopArgs a{};
+        a.indices = g->indices;
+        a.frontier = cur.ids; a.n_frontier = n_cur;
+        a.min_deg = short_rows ? SHORT_ROW : 0;
+        a.rec = rec;
+        a.fanout = fanout;
+        a.samp_off = cur.samp_off; a.samp_nbr = cur.samp_nbr;
+        a.tile = tile; a.n_tiles = n_tiles; a.tile_out = tile_out; a.tile_piece = tile_piece;
+        a.merge_span = merge_span;
+        a.tile_order = tile_order;
+        a.reached = reached;
+        a.next_work = next_work;
+        a.guess_scale = 1.0f;
+        a.place = place;
         if (const char *scale = getenv("RAPIDGNN_GUESS_SCALE")) a.guess_scale = std::min(std::max((float)atof(scale), 1e-3f), 1e3f);      // same results either way; for tests
         ScopedTimer tm(KG_SAMPLER, st);
         if (hub_jobs) {
@@ -2227,14 +2337,14 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
 #define RG_LAUNCH(...) RG_TRY((launch_hop<__VA_ARGS__>(a, n_cu, merge_grid, fine_tail, fine_if_few, st)))
 #define RG_HOP(CAP)                                                                                                   \
     do {                                                                                                              \
-        if (inline_marks && short_rows) RG_LAUNCH(sample_kernel<CAP, MARK_BITS, true>, sample_merge_kernel<CAP, MARK_BITS>);  \
-        else if (inline_marks) RG_LAUNCH(sample_kernel<CAP, MARK_BITS, false>, sample_merge_kernel<CAP, MARK_BITS>);   \
-        else if (short_rows) RG_LAUNCH(sample_kernel<CAP, MARK_NONE, true>, sample_merge_kernel<CAP, MARK_NONE>);      \
-        else RG_LAUNCH(sample_kernel<CAP, MARK_NONE, false>, sample_merge_kernel<CAP, MARK_NONE>);                     \
+        if (inline_marks && short_rows) RG_LAUNCH(false, sample_kernel<CAP, MARK_BITS, true>, sample_merge_kernel<CAP, MARK_BITS>);  \
+        else if (inline_marks) RG_LAUNCH(false, sample_kernel<CAP, MARK_BITS, false>, sample_merge_kernel<CAP, MARK_BITS>);   \
+        else if (short_rows) RG_LAUNCH(false, sample_kernel<CAP, MARK_NONE, true>, sample_merge_kernel<CAP, MARK_NONE>);      \
+        else RG_LAUNCH(false, sample_kernel<CAP, MARK_NONE, false>, sample_merge_kernel<CAP, MARK_NONE>);                     \
     } while (0)
         if (fanout <= (uint32_t)ROWS_FANOUT) {
-            if (inline_marks) RG_LAUNCH(sample_rows_kernel<MARK_BITS>, sample_merge_kernel<128, MARK_BITS>);
-            else RG_LAUNCH(sample_rows_kernel<MARK_NONE>, sample_merge_kernel<128, MARK_NONE>);
+            if (inline_marks) RG_LAUNCH(true, sample_rows_kernel<MARK_BITS>, sample_merge_kernel<128, MARK_BITS>);
+            else RG_LAUNCH(true, sample_rows_kernel<MARK_NONE>, sample_merge_kernel<128, MARK_NONE>);
         } else if (need <= 256) RG_HOP(256);
         else if (need <= 512) RG_HOP(512);
         else if (need <= 1024) RG_HOP(1024);
