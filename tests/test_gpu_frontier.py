@@ -56,3 +56,23 @@ def test_marks_in_pieces_and_parts(rg, orc, n, n_train, batch, mark_pass, monkey
     ids, off = o.frontier(1)
     gids, _, goff = rg.rg_schedule_frontier(s, 1)
     assert np.array_equal(goff, off) and np.array_equal(gids.cpu().numpy(), ids)
+
+
+@pytest.mark.parametrize("n", [40, 2047, 2048, 2049, 4100])
+@pytest.mark.parametrize("beta", [1, 7, 9, 64, 65, 255, 256, 300])
+def test_frequencies_from_the_bitmaps(rg, n, beta):
+    """The epoch's frequencies as column sums of the batches' bitmaps: batches fewer than the waves that share them out, as many as
+    a round takes and more, up to and past what eight planes count; nodes up to, at and past a workgroup's; some nodes in
+    every batch (the hubs that every row ends with)."""
+    rng = np.random.default_rng(n + beta)
+    deg, hubs = min(n // 2, 60), 3
+    rows = np.sort(np.stack([np.concatenate([rng.permutation(n - hubs)[:deg], np.arange(n - hubs, n)]) for _ in range(n)]), axis=1).astype(np.int32)
+    indptr = torch.arange(0, n * (deg + hubs) + 1, deg + hubs, dtype=torch.int64, device="cuda")
+    per_batch = max(1, min(n // beta, 40))
+    train = torch.from_numpy(rng.permutation(n)[: per_batch * beta].astype(np.int32)).cuda()
+    s = rg.rg_build_schedule(indptr, torch.from_numpy(rows.ravel()).cuda(), train, per_batch, [64, 64], 3, 0, 0)
+    ids = rg.rg_schedule_frontier(s, 2)[0].cpu().numpy()
+    feat = rg.make_features(torch.zeros(n, dtype=torch.uint8, device="cuda"), torch.arange(n, dtype=torch.int32, device="cuda"),
+                            torch.zeros((1, 4), dtype=torch.int32, device="cuda"), torch.zeros((n, 4), dtype=torch.int32, device="cuda"), 16)
+    cache = rg.rg_build_cache([s], feat, n // 3)
+    assert np.array_equal(rg.rg_cache_view(cache, n)["freq"].cpu().numpy().view(np.uint32), np.bincount(ids, minlength=n).astype(np.uint32))
