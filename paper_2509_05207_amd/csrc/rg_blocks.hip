@@ -12,7 +12,8 @@
 //
 // Bound by the scattered reads of the tables.  All workgroups of a batch run on one XCD (workgroup g runs on XCD g mod
 // 8), so that a batch's table is in one L2 and not read by all eight, and a thread keeps four edges in flight: 233 k nodes, 147
-// batches, 29 M edges: positions and edges 616 us, 302 so.
+// batches, 29 M edges: positions and edges 616 us, 302 so.  With up to 128 workgroups per batch instead of 32, so that an XCD is at two
+// batches at a time and their tables (0.9 MB each) stay in its 4 MB of L2, and four positions in flight too: 265.
 #include "rg_internal.h"
 
 #include <algorithm>
@@ -20,55 +21,67 @@
 namespace rg {
 
 constexpr int BLK_THREADS = 256;
-constexpr int BLK_PER_BATCH = 32;       // workgroups per batch; each walks its share with a stride
+constexpr int BLK_PER_BATCH = 128;      // workgroups per batch at most; each walks its share with a stride
 constexpr int BLK_IN_FLIGHT = 4;
 constexpr int BLK_XCDS = 8;
 
 // Workgroup g's batch within a group of batches, and its number among the batch's workgroups: batches go round the XCDs.
-__device__ __forceinline__ uint32_t batch_of_workgroup(uint32_t g, uint32_t *part)
+__device__ __forceinline__ uint32_t batch_of_workgroup(uint32_t g, uint32_t per_batch, uint32_t *part)
 {
     const uint32_t r = g / BLK_XCDS;
-    *part = r % BLK_PER_BATCH;
-    return r / BLK_PER_BATCH * BLK_XCDS + g % BLK_XCDS;
+    *part = r % per_batch;
+    return r / per_batch * BLK_XCDS + g % BLK_XCDS;
 }
-static unsigned workgroups_for(uint32_t n_batches) { return (n_batches + BLK_XCDS - 1) / BLK_XCDS * BLK_XCDS * BLK_PER_BATCH; }
+static unsigned workgroups_for(uint32_t n_batches, uint32_t per_batch) { return (n_batches + BLK_XCDS - 1) / BLK_XCDS * BLK_XCDS * per_batch; }
+// Workgroups of a batch: one round of its threads for an average batch's entries, up to half of what an XCD holds, so that
+// two batches' tables are in its L2 and not eight.
+static uint32_t workgroups_per_batch(int64_t n, uint32_t beta)
+{
+    const int64_t each = n / beta / (BLK_THREADS * BLK_IN_FLIGHT) + 1;
+    return (uint32_t)std::min<int64_t>(each, BLK_PER_BATCH);
+}
 
 // table[k][U_{L,b}[j]] = j for batch b = b_lo + k
 __global__ void __launch_bounds__(BLK_THREADS) block_positions_kernel(const int32_t *__restrict__ ids, const int64_t *__restrict__ off, uint32_t b_lo, uint32_t n_batches,
-                                                                      int64_t n_nodes, int32_t *__restrict__ table)
+                                                                      uint32_t per_batch, int64_t n_nodes, int32_t *__restrict__ table)
 {
     uint32_t part;
-    const uint32_t k = batch_of_workgroup(blockIdx.x, &part);
+    const uint32_t k = batch_of_workgroup(blockIdx.x, per_batch, &part);
     if (k >= n_batches) return;
     const int64_t u0 = off[b_lo + k], n = off[b_lo + k + 1] - u0;
     int32_t *t = table + (uint64_t)k * (uint64_t)n_nodes;
-    for (int64_t j = (int64_t)part * BLK_THREADS + threadIdx.x; j < n; j += (int64_t)BLK_PER_BATCH * BLK_THREADS) {
-        const uint32_t v = (uint32_t)ids[u0 + j];
-        if (v < (uint64_t)n_nodes) t[v] = (int32_t)j;
+    const int64_t step = (int64_t)per_batch * BLK_THREADS;
+    for (int64_t j0 = (int64_t)part * BLK_THREADS + threadIdx.x; j0 < n; j0 += BLK_IN_FLIGHT * step) {
+        uint32_t v[BLK_IN_FLIGHT];
+#pragma unroll
+        for (int q = 0; q < BLK_IN_FLIGHT; ++q) v[q] = (uint32_t)ids[u0 + min(j0 + q * step, n - 1)];              // (past the end: the last ID again, not written)
+#pragma unroll
+        for (int q = 0; q < BLK_IN_FLIGHT; ++q)
+            if (j0 + q * step < n && v[q] < (uint64_t)n_nodes) t[v[q]] = (int32_t)(j0 + q * step);
     }
 }
 
 // src_pos[e] = table[k][samp_nbr[e]] for the samples of batch b = b_lo + k
 __global__ void __launch_bounds__(BLK_THREADS) block_relabel_kernel(const int32_t *__restrict__ samp_nbr, const int64_t *__restrict__ samp_off,
-                                                                    const int64_t *__restrict__ off, uint32_t b_lo, uint32_t n_batches, int64_t n_nodes,
+                                                                    const int64_t *__restrict__ off, uint32_t b_lo, uint32_t n_batches, uint32_t per_batch, int64_t n_nodes,
                                                                     const int32_t *__restrict__ table, int32_t *__restrict__ src_pos)
 {
     uint32_t part;
-    const uint32_t k = batch_of_workgroup(blockIdx.x, &part);
+    const uint32_t k = batch_of_workgroup(blockIdx.x, per_batch, &part);
     if (k >= n_batches) return;
     const int64_t first = samp_off[off[b_lo + k]], end = samp_off[off[b_lo + k + 1]];
     const int32_t *t = table + (uint64_t)k * (uint64_t)n_nodes;
-    constexpr int64_t STEP = (int64_t)BLK_PER_BATCH * BLK_THREADS;
-    for (int64_t e0 = first + (int64_t)part * BLK_THREADS + threadIdx.x; e0 < end; e0 += BLK_IN_FLIGHT * STEP) {
+    const int64_t step = (int64_t)per_batch * BLK_THREADS;
+    for (int64_t e0 = first + (int64_t)part * BLK_THREADS + threadIdx.x; e0 < end; e0 += BLK_IN_FLIGHT * step) {
         uint32_t u[BLK_IN_FLIGHT];
         int32_t p[BLK_IN_FLIGHT];
 #pragma unroll
-        for (int q = 0; q < BLK_IN_FLIGHT; ++q) u[q] = (uint32_t)samp_nbr[min(e0 + q * STEP, end - 1)];          // (past the end: the last edge again, not written)
+        for (int q = 0; q < BLK_IN_FLIGHT; ++q) u[q] = (uint32_t)samp_nbr[min(e0 + q * step, end - 1)];          // (past the end: the last edge again, not written)
 #pragma unroll
         for (int q = 0; q < BLK_IN_FLIGHT; ++q) p[q] = u[q] < (uint64_t)n_nodes ? t[u[q]] : -1;
 #pragma unroll
         for (int q = 0; q < BLK_IN_FLIGHT; ++q)
-            if (e0 + q * STEP < end) __builtin_nontemporal_store(p[q], src_pos + e0 + q * STEP);
+            if (e0 + q * step < end) __builtin_nontemporal_store(p[q], src_pos + e0 + q * step);
     }
 }
 
@@ -95,12 +108,14 @@ rg_status rg_schedule_build_blocks(rg_schedule *s, uint64_t workspace_limit_byte
     for (uint32_t b_lo = 0; b_lo < s->n_batches && s->L > 0; b_lo += group) {
         const uint32_t nb = std::min(group, s->n_batches - b_lo);
         ScopedTimer tm(KG_BLOCKS, st);
-        hipLaunchKernelGGL(block_positions_kernel, dim3(workgroups_for(nb)), dim3(BLK_THREADS), 0, st, all.ids, all.off_dev, b_lo, nb, s->n_nodes, table);
+        const uint32_t per_batch = workgroups_per_batch(all.off_host[s->n_batches], s->n_batches);
+        hipLaunchKernelGGL(block_positions_kernel, dim3(workgroups_for(nb, per_batch)), dim3(BLK_THREADS), 0, st, all.ids, all.off_dev, b_lo, nb, per_batch, s->n_nodes, table);
         for (uint32_t l = 0; l < s->L; ++l) {
             const HopData &h = s->hop[l];
+            const uint32_t per_batch = workgroups_per_batch(h.n_samples, s->n_batches);
             if (h.n_samples > 0)
-                hipLaunchKernelGGL(block_relabel_kernel, dim3(workgroups_for(nb)), dim3(BLK_THREADS), 0, st, h.samp_nbr, h.samp_off, h.off_dev, b_lo, nb, s->n_nodes,
-                                   table, h.src_pos);
+                hipLaunchKernelGGL(block_relabel_kernel, dim3(workgroups_for(nb, per_batch)), dim3(BLK_THREADS), 0, st, h.samp_nbr, h.samp_off, h.off_dev, b_lo, nb, per_batch,
+                                   s->n_nodes, table, h.src_pos);
         }
     }
     RG_HIP(hipGetLastError());
