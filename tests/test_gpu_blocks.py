@@ -57,3 +57,25 @@ def test_positions_sampler_in_every_marking(rg, orc, mark_pass, fanout, monkeypa
         assert np.array_equal(rg.rg_schedule_frontier(s, hop)[0].cpu().numpy(), o.frontier(hop)[0]), hop
     for hop in range(2):
         assert np.array_equal(rg.rg_schedule_samples(s, hop)[1].cpu().numpy(), o.samples(hop)[1]), hop
+
+
+@pytest.mark.parametrize("batch,n_batches,rest", [(64, 3, 0), (65, 3, 2), (8200, 2, 1), (9000, 9, 8999), (120_000, 1, 0), (500, 17, 499)])
+def test_blocks_of_batches_of_every_size(rg, batch, n_batches, rest):
+    """From one workgroup per batch (1,024 edges on average) to the most there are (128) and several rounds of them; a last batch
+    much smaller than the average; every edge's place against the input nodes themselves."""
+    n, deg = 150_000, 20
+    g = torch.Generator("cuda").manual_seed(batch)
+    steps = torch.randint(0, n // deg, (n, deg), device="cuda", generator=g, dtype=torch.int32)
+    indices = (steps + torch.arange(deg, device="cuda", dtype=torch.int32) * (n // deg)).reshape(-1).contiguous()
+    indptr = torch.arange(0, n * deg + 1, deg, device="cuda", dtype=torch.int64)
+    train = torch.randperm(n, device="cuda", generator=g)[: batch * n_batches - rest].to(torch.int32)
+    s = rg.rg_build_schedule(indptr, indices, train, batch, [16, 3], 1, 0, 0)
+    rg.rg_schedule_build_blocks(s)
+    ids, _, off = rg.rg_schedule_frontier(s, 2)
+    for hop in range(2):
+        _, _, at = rg.rg_schedule_frontier(s, hop)
+        samp_off, nbr = rg.rg_schedule_samples(s, hop)
+        src = rg.rg_schedule_block(s, hop).to(torch.int64)
+        ends = samp_off[torch.from_numpy(np.asarray(at)).to("cuda")]
+        first = torch.from_numpy(np.asarray(off[:-1])).to("cuda")
+        assert torch.equal(ids[src + torch.repeat_interleave(first, ends[1:] - ends[:-1])], nbr), hop
