@@ -604,13 +604,20 @@ rg_status scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, Arena &tmp
 
 // ---------------------------------------------------------------- graph validation
 // Bound by reading indptr and indices once.  Where indptr ascends from 0 -- every graph but a damaged one -- the rows
-// lie back to back, and the violations are counted without looking at rows at all: over the flat array, every ID out of
-// range and every ID not above the one in front of it, less the latter at the starts of rows, which the pass over
-// indptr counts.  A wave per row, which is what finds the violations of any indptr (validate_rows, now run only where
+// lie back to back, and the violations are counted over the flat array: every ID out of range and every ID not above the one
+// in front of it, less the latter at the starts of rows.  A wave per row, which is what finds the violations of any indptr (validate_rows, now run only where
 // the rows are out of order), spends its time on 2.45 M rows' dependent loads: a graph of 122 M edges 4.4 ms, the two
 // streaming passes together 0.1 (0.5 GB).
+// The starts of the rows are scattered reads of lines that the flat pass reads too, so a wave of that pass looks at those among
+// the IDs it has just read (found in indptr, which is known to ascend by then), while they are in a cache: 2.45 M rows,
+// 122 M edges, starts with the pass over indptr 43 + 90 us, so 6 + 110.  (Per 64 KB and workgroup, behind a barrier: 6 + 129.)
+// Many rows to few IDs take the wave many turns, and small graphs feel its search for its first row: there the starts stay with
+// the pass over indptr (starts there / behind the IDs: 50 M nodes, 2 IDs each 238 / 292 us, 7 in one of 100 134 / 534; 8,000 nodes, 8 each 32.8 / 34.6).
 constexpr int VAL_THREADS = 256;
 constexpr int VAL_SLOTS = 16;                  // each count is kept in this many copies, summed by the host (adds to one address queue up)
+constexpr int64_t VAL_ROW_IDS = 16;            // IDs per row, on average, from which on a wave looks at the starts among its IDs ...
+constexpr int64_t VAL_MANY_IDS = 1 << 24;      // ... where there are so many
+__device__ __forceinline__ bool starts_with_the_ids(int64_t n_nodes, int64_t n) { return n >= VAL_ROW_IDS * n_nodes && n >= VAL_MANY_IDS; }
 enum { VAL_ROWS = 0, VAL_FLAT = 1, VAL_STARTS = 2, VAL_GENERAL = 3, VAL_COUNTS = 4 };
 
 __device__ __forceinline__ void add_block_count(unsigned long long x, unsigned long long *counts, int which)
@@ -627,10 +634,11 @@ __device__ __forceinline__ void add_block_count(unsigned long long x, unsigned l
 }
 
 // Rows that decrease (and an indptr that does not start at 0), and the non-empty rows whose first ID is in range but not
-// above the ID in front of it in the flat array.
+// above the ID in front of it in the flat array, where the flat pass does not look at those.
 __global__ void __launch_bounds__(VAL_THREADS) validate_indptr(int64_t n_nodes, const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                unsigned long long *__restrict__ counts)
 {
+    const bool look_at_starts = !starts_with_the_ids(n_nodes, indptr[n_nodes]);
     unsigned long long bad = 0, starts = 0;
     const int64_t step = (int64_t)gridDim.x * VAL_THREADS;
     for (int64_t v0 = (int64_t)blockIdx.x * VAL_THREADS + threadIdx.x; v0 < n_nodes; v0 += 4 * step) {
@@ -644,7 +652,7 @@ __global__ void __launch_bounds__(VAL_THREADS) validate_indptr(int64_t n_nodes, 
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const bool look = b[k] > 0 && b[k] < e[k];
+            const bool look = look_at_starts && b[k] > 0 && b[k] < e[k];
             here[k] = look ? indices[b[k]] : -1;
             front[k] = look ? indices[b[k] - 1] : -1;
         }
@@ -665,8 +673,25 @@ __device__ __forceinline__ bool any_row_bad(const unsigned long long *counts)
     return x != 0;
 }
 
-// The flat array: 16-byte loads from the first aligned ID on, four in flight per lane; the IDs in front of it and after
-// the last whole vector by the first workgroup.
+// The first v with indptr[v] >= x, by a wave that looks at 64 places at a time (x the same in all lanes, 0 <= x <=
+// indptr[n_nodes]; indptr ascends from 0).
+__device__ __forceinline__ int64_t first_row_from(const int64_t *__restrict__ indptr, int64_t n_nodes, int64_t x, int lane)
+{
+    int64_t lo = 0, hi = n_nodes;                // the answer lies in [lo, hi]
+    while (lo < hi) {
+        const int64_t step = (hi - lo + 63) / 64, at = lo + lane * step;
+        const int k = __popcll(__ballot(at < hi && indptr[min(at, hi)] < x));      // the first k places lie in front of it
+        if (k == 0) return lo;
+        hi = min(lo + k * step, hi);
+        lo += (k - 1) * step + 1;
+    }
+    return lo;
+}
+
+// The flat array, a contiguous part of it per wave: 16-byte loads from the first aligned ID on, four in flight per lane; the IDs
+// in front of the first whole vector and after the last by the first workgroup.  Behind each 4 KB so read come the non-empty rows
+// that start in them: those whose first ID is in range but not above the ID in front of it.
+constexpr int64_t VAL_ROUND = 4 * 64;            // vectors that a wave reads at once
 __global__ void __launch_bounds__(VAL_THREADS) validate_flat(int64_t n_nodes, const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                              unsigned long long *__restrict__ counts)
 {
@@ -674,34 +699,53 @@ __global__ void __launch_bounds__(VAL_THREADS) validate_flat(int64_t n_nodes, co
     const int64_t n = indptr[n_nodes];
     const uint32_t limit = (uint32_t)n_nodes;
     auto wrong = [&](int32_t front, int32_t u) { return ((uint32_t)u >= limit || front >= u) ? 1u : 0u; };
-    unsigned long long bad = 0;
+    unsigned long long bad = 0, starts = 0;
     int64_t head = (int64_t)((16 - ((uintptr_t)indices & 15)) & 15) / 4;
     if (head > n) head = n;
     const int64_t n_vec = (n - head) >> 2;
     const int4 *vec = reinterpret_cast<const int4 *>(indices + head);
     const int lane = threadIdx.x & 63;
-    const int64_t step = (int64_t)gridDim.x * VAL_THREADS;
-    for (int64_t i0 = (int64_t)blockIdx.x * VAL_THREADS + threadIdx.x; i0 - lane < n_vec; i0 += 4 * step) {      // (wave-uniform trip count: the lanes exchange IDs)
+    const int64_t n_waves = (int64_t)gridDim.x * (VAL_THREADS / 64), wave = (int64_t)blockIdx.x * (VAL_THREADS / 64) + (threadIdx.x >> 6);
+    const int64_t part = ((n_vec + n_waves - 1) / n_waves + VAL_ROUND - 1) / VAL_ROUND * VAL_ROUND;
+    const int64_t i_end = min((wave + 1) * part, n_vec);
+    const bool look_at_starts = starts_with_the_ids(n_nodes, n);
+    int64_t v = look_at_starts && wave > 0 && wave * part < n_vec ? first_row_from(indptr, n_nodes, head + 4 * wave * part, lane) : 0;
+    for (int64_t i_lo = wave * part; i_lo < i_end || (wave == 0 && i_lo == 0); i_lo += VAL_ROUND) {      // (fewer IDs than make a vector have their rows, too)
         int4 x[4];
         int32_t front[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int64_t i = i0 + k * step;
-            x[k] = i < n_vec ? vec[i] : make_int4(0, 0, 0, 0);
-            front[k] = lane == 0 && i < n_vec && head + 4 * i > 0 ? indices[head + 4 * i - 1] : -1;
+            const int64_t i = i_lo + k * 64 + lane;
+            x[k] = i < i_end ? vec[i] : make_int4(0, 0, 0, 0);
+            front[k] = lane == 0 && i < i_end && head + 4 * i > 0 ? indices[head + 4 * i - 1] : -1;
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int32_t left = __shfl_up(x[k].w, 1, 64);
             const int32_t f = lane == 0 ? front[k] : left;
-            if (i0 + k * step < n_vec) bad += wrong(f, x[k].x) + wrong(x[k].x, x[k].y) + wrong(x[k].y, x[k].z) + wrong(x[k].z, x[k].w);
+            if (i_lo + k * 64 + lane < i_end) bad += wrong(f, x[k].x) + wrong(x[k].x, x[k].y) + wrong(x[k].y, x[k].z) + wrong(x[k].z, x[k].w);
         }
+        if (!look_at_starts) continue;
+        const int64_t id_end = i_lo + VAL_ROUND >= n_vec ? n : head + 4 * (i_lo + VAL_ROUND);       // (a part that is not the last is whole rounds)
+        int c;
+        do {
+            const int64_t b = indptr[min(v + lane, n_nodes)], e = indptr[min(v + lane + 1, n_nodes)];
+            const bool in = v + lane < n_nodes && b < id_end;        // (the first c lanes: indptr ascends)
+            const bool look = in && b > 0 && b < e;
+            const int32_t here = look ? indices[b] : -1, before = look ? indices[b - 1] : -1;
+            if (here >= 0 && here < n_nodes && before >= here) ++starts;
+            c = __popcll(__ballot(in));
+            v += c;
+            // (sixty-four empty rows, one behind the other: on to the row that the next ID is in)
+            if (c == 64 && __shfl(b, 0, 64) == __shfl(e, 63, 64)) v = first_row_from(indptr, n_nodes, __shfl(b, 0, 64) + 1, lane) - 1;
+        } while (c == 64);
     }
     if (blockIdx.x == 0 && threadIdx.x < 8) {
         const int64_t j = threadIdx.x < 4 ? (int64_t)threadIdx.x : head + 4 * n_vec + threadIdx.x - 4;
         if (threadIdx.x < 4 ? j < head : j < n) bad += wrong(j > 0 ? indices[j - 1] : -1, indices[j]);
     }
     add_block_count(bad, counts, VAL_FLAT);
+    add_block_count(starts, counts, VAL_STARTS);
 }
 
 // Any indptr: one wave per row, grid-stride; nothing to do where validate_indptr found no row that decreases.  With more

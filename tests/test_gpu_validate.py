@@ -64,3 +64,25 @@ def test_rows_out_of_order_are_counted_row_by_row(rg, n):
         for k, x in damage.items():
             bad[k] = x
         check(rg, bad, indices, 0)
+
+
+@pytest.mark.parametrize("edges", [2_100_003, 34_000_001])
+@pytest.mark.parametrize("rows", [40, 300_000])
+def test_violations_over_many_waves(rg, edges, rows):
+    """Waves of one round of 1,024 IDs and of several; rows that span many waves (a row, or empty ones, beginning on the edges
+    between two) and rows that are many to a round; damage at the starts of rows, where it may be none, and inside."""
+    rng = np.random.default_rng(edges + rows)
+    indptr = np.sort(np.concatenate([[0, 0, edges], rng.integers(0, edges + 1, size=rows), np.arange(1, edges, edges // 64 // 1024 * 1024), np.arange(1, edges, edges // 64 // 1024 * 1024)])).astype(np.int64)
+    n = indptr.size - 1
+    first = np.zeros(edges + 1, bool)
+    first[indptr[:-1]] = True
+    first = first[:edges]
+    at = np.arange(edges)
+    indices = ((at - np.maximum.accumulate(np.where(first, at, 0))) % n).astype(np.int32)      # falls back to 0 within rows of more than n IDs too
+    hit = rng.integers(0, edges, size=1000)
+    indices[hit] = rng.choice(np.array([-1, n, 0, n - 1, 2**31 - 1]), size=hit.size)
+    bad = (indices < 0) | (indices >= n)
+    bad[1:] |= ~first[1:] & (indices[:-1] >= indices[1:])
+    pad = torch.zeros(edges + 3, dtype=torch.int32, device="cuda")
+    pad[3:] = torch.from_numpy(indices).cuda()
+    assert rg.rg_graph_validate(torch.from_numpy(indptr).cuda(), pad[3:]) == int(bad.sum())
