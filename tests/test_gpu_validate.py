@@ -72,7 +72,7 @@ def test_violations_over_many_waves(rg, edges, rows):
     """Waves of one round of 1,024 IDs and of several; rows that span many waves (a row, or empty ones, beginning on the edges
     between two) and rows that are many to a round; damage at the starts of rows, where it may be none, and inside."""
     rng = np.random.default_rng(edges + rows)
-    indptr = np.sort(np.concatenate([[0, 0, edges], rng.integers(0, edges + 1, size=rows), np.arange(1, edges, edges // 64 // 1024 * 1024), np.arange(1, edges, edges // 64 // 1024 * 1024)])).astype(np.int64)
+    indptr = np.sort(np.concatenate([[0, 0, edges], [edges // 3] * 200, rng.integers(0, edges + 1, size=rows), np.arange(1, edges, edges // 64 // 1024 * 1024), np.arange(1, edges, edges // 64 // 1024 * 1024)])).astype(np.int64)
     n = indptr.size - 1
     first = np.zeros(edges + 1, bool)
     first[indptr[:-1]] = True
