@@ -409,7 +409,7 @@ def measure(rg, name, args, full):
                                f"see pcie_inclusive), {G} batch(es) per gather launch",
                    "n_batches": n_batches, "sampled_edges_per_epoch": sampled_edges, "gathered_rows_per_epoch": rows_per_epoch,
                    "K_eff": int(k_eff)},
-        "sampler": {"kernel": "sample_kernel", "edges_per_s_kernel": sampled_edges / (samp_ms * 1e-3) if samp_ms else None, "GBps": samp_gbps,
+        "sampler": {"kernel": "sample_rows_kernel", "edges_per_s_kernel": sampled_edges / (samp_ms * 1e-3) if samp_ms else None, "GBps": samp_gbps,
                     "frac_hbm": samp_frac, "ms_per_step": samp_ms, "launches_per_step": samp_launches,
                     "algorithmic_bytes_per_step": samp_bytes, "row_entries_of_frontiers": sum(h["sum_deg"] for h in hops),
                     "row_entries_of_distinct_nodes": sum(h["distinct"] for h in hops)},
