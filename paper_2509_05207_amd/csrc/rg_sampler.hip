@@ -890,12 +890,13 @@ template <int R> __device__ __forceinline__ uint32_t rotate16(uint32_t x)      /
 
 // cnt += the keys among a row of sixteen lanes' `theirs`, this lane's own left out, that are smaller than this lane's `mine`: each of the
 // fifteen others comes by as the row is rotated, a subtraction takes it in and leaves the answer in the carry, and the carry is added.
-// (Two instructions per key; the compiler's own are three and a wait for each rotation.)  The wait in front is for `theirs`,
-// which may have just been written: the hardware does not hold a row rotation back for it.
+// (Two instructions per key; the compiler's own are three.)  The waits are those that the hardware leaves to the program and the
+// compiler puts into its own code, but not into this text: two states from the write of `theirs` to its rotation, two from a
+// carry's write to its read.
 __device__ __forceinline__ void add_smaller16(uint32_t theirs, uint32_t mine, uint32_t &cnt)
 {
     uint32_t scrap;
-#define RG_ROT(R) "v_sub_co_u32_dpp %0, vcc, %2, %3 row_ror:" #R " row_mask:0xf bank_mask:0xf\n\tv_addc_co_u32_e32 %1, vcc, 0, %1, vcc\n\t"
+#define RG_ROT(R) "v_sub_co_u32_dpp %0, vcc, %2, %3 row_ror:" #R " row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\tv_addc_co_u32_e32 %1, vcc, 0, %1, vcc\n\t"
     asm("s_nop 1\n\t" RG_ROT(1) RG_ROT(2) RG_ROT(3) RG_ROT(4) RG_ROT(5) RG_ROT(6) RG_ROT(7) RG_ROT(8)
         RG_ROT(9) RG_ROT(10) RG_ROT(11) RG_ROT(12) RG_ROT(13) RG_ROT(14) RG_ROT(15)
         : "=&v"(scrap), "+v"(cnt) : "v"(theirs), "v"(mine) : "vcc");
