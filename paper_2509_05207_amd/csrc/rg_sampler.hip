@@ -892,14 +892,14 @@ template <int R> __device__ __forceinline__ uint32_t rotate16(uint32_t x)      /
 // fifteen others comes by as the row is rotated, a subtraction takes it in and leaves the answer in the carry, and the carry is added.
 // (Two instructions per key; the compiler's own are three.)  The waits are those that the hardware leaves to the program and the
 // compiler puts into its own code, but not into this text: two states from the write of `theirs` to its rotation, two from a
-// carry's write to its read.
+// carry's write to its read.  cnt is written before the inputs are read for the last time, so it may share a register with neither.
 __device__ __forceinline__ void add_smaller16(uint32_t theirs, uint32_t mine, uint32_t &cnt)
 {
     uint32_t scrap;
 #define RG_ROT(R) "v_sub_co_u32_dpp %0, vcc, %2, %3 row_ror:" #R " row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\tv_addc_co_u32_e32 %1, vcc, 0, %1, vcc\n\t"
     asm("s_nop 1\n\t" RG_ROT(1) RG_ROT(2) RG_ROT(3) RG_ROT(4) RG_ROT(5) RG_ROT(6) RG_ROT(7) RG_ROT(8)
         RG_ROT(9) RG_ROT(10) RG_ROT(11) RG_ROT(12) RG_ROT(13) RG_ROT(14) RG_ROT(15)
-        : "=&v"(scrap), "+v"(cnt) : "v"(theirs), "v"(mine) : "vcc");
+        : "=&v"(scrap), "+&v"(cnt) : "v"(theirs), "v"(mine) : "vcc");
 #undef RG_ROT
 }
 

@@ -69,3 +69,16 @@ def test_wait_states(where, lines, operands):
         since[ops[0]] = 0
         if "_co_" in name:
             since["vcc"] = 0
+
+
+@pytest.mark.parametrize("where,lines,operands", [s for s in STATEMENTS if s[1]], ids=lambda x: x if isinstance(x, str) else "")
+def test_early_clobbers(where, lines, operands):
+    """An output that is written before the last line that reads an input has a register of its own (&): without it a read-write operand may
+    share one with an input that the compiler knows to be equal."""
+    outputs = [c for c in operands[0]] if operands else []
+    inputs = [f"%{len(outputs) + k}" for k in range(len(operands[1]) if len(operands) > 1 else 0)]
+    reads = [n for n, line in enumerate(lines) if any(re.search(re.escape(i) + r"\b", line) for i in inputs)]
+    for k, constraint in enumerate(outputs):
+        writes = [n for n, line in enumerate(lines) if re.match(rf"\w+ %{k}\b", line)]
+        if writes and reads and writes[0] < reads[-1]:
+            assert "&" in constraint, f"{where}: operand {k} is {constraint!r}"
