@@ -1311,6 +1311,7 @@ __device__ __forceinline__ uint64_t key_state(uint32_t hi) { return (uint64_t)hi
 __device__ __forceinline__ uint32_t hi_of(uint64_t c) { return (uint32_t)(c >> 32); }
 __device__ __forceinline__ uint32_t key32_after_mad(uint64_t y)
 {
+    asm("" : "+v"(y));                                           // (the whole sum is wanted, or it would be narrowed to a product and an addition again)
     uint32_t x = (uint32_t)y;
     x ^= x >> 15;
     return x * HB32;
@@ -1320,18 +1321,14 @@ __device__ __forceinline__ uint32_t key32_open_of_row(uint32_t lo, uint64_t c, u
 {
     uint32_t x = (u ^ lo) * HG32;
     x ^= x >> 16;
-    uint64_t y;
-    asm("v_mad_u64_u32 %0, vcc, %1, %2, %3" : "=v"(y) : "v"(x), "v"(ha32), "s"(c) : "vcc");
-    return key32_after_mad(y);
+    return key32_after_mad((uint64_t)x * ha32 + c);
 }
 // c a lane's own
 __device__ __forceinline__ uint32_t key32_open_of_lane(uint32_t lo, uint64_t c, uint32_t u)
 {
     uint32_t x = (u ^ lo) * HG32;
     x ^= x >> 16;
-    uint64_t y;
-    asm("v_mad_u64_u32 %0, vcc, %1, %2, %3" : "=v"(y) : "v"(x), "s"(HA32), "v"(c) : "vcc");
-    return key32_after_mad(y);
+    return key32_after_mad((uint64_t)x * HA32 + c);
 }
 
 // Appends the IDs of a block whose key is not above `cut` to cand[cnt ..), in row order, unless they do not fit; cnt counts on

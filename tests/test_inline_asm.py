@@ -82,3 +82,11 @@ def test_early_clobbers(where, lines, operands):
         writes = [n for n, line in enumerate(lines) if re.match(rf"\w+ %{k}\b", line)]
         if writes and reads and writes[0] < reads[-1]:
             assert "&" in constraint, f"{where}: operand {k} is {constraint!r}"
+
+
+@pytest.mark.parametrize("where,lines,operands", [s for s in STATEMENTS if s[1]], ids=lambda x: x if isinstance(x, str) else "")
+def test_scalar_operands_may_be_fresh(where, lines, operands):
+    """A scalar register that a vector instruction has just written (a lane read, a reload of a spilled scalar) is to be waited for by who
+    reads it in a vector instruction: an asm statement that takes one starts with the two states."""
+    takes = any(c.lstrip("+=&") in ("s", "sgpr") for c in sum(operands[1:2], []))
+    assert not takes or re.match(r"s_nop [1-9]", lines[0]), where
