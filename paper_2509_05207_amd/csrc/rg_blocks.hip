@@ -13,7 +13,7 @@
 // Bound by the scattered reads of the tables.  All workgroups of a batch run on one XCD (workgroup g runs on XCD g mod
 // 8), so that a batch's table is in one L2 and not read by all eight, and a thread keeps four edges in flight: 233 k nodes, 147
 // batches, 29 M edges: positions and edges 616 us, 302 so.  With up to 128 workgroups per batch instead of 32, so that an XCD is at two
-// batches at a time and their tables (0.9 MB each) stay in its 4 MB of L2, and four positions in flight too: 265.
+// batches at a time and their tables (0.9 MB each) stay in its 4 MB of L2, and four positions in flight too: 252.
 #include "rg_internal.h"
 
 #include <algorithm>
@@ -33,12 +33,17 @@ __device__ __forceinline__ uint32_t batch_of_workgroup(uint32_t g, uint32_t per_
     return r / per_batch * BLK_XCDS + g % BLK_XCDS;
 }
 static unsigned workgroups_for(uint32_t n_batches, uint32_t per_batch) { return (n_batches + BLK_XCDS - 1) / BLK_XCDS * BLK_XCDS * per_batch; }
-// Workgroups of a batch: one round of its threads for an average batch's entries, up to half of what an XCD holds, so that
-// two batches' tables are in its L2 and not eight.
-static uint32_t workgroups_per_batch(int64_t n, uint32_t beta)
+// Workgroups of a batch, of nb that a launch holds: one round of its threads for an average batch's entries, up to half of what
+// an XCD holds, so that two batches' tables are in its L2 and not eight.  A launch of few batches (the workspace holds nine tables of
+// 111 M nodes) or of small ones would leave the chip idle with that, and there each access is a wait for memory: as many as fill
+// the chip, down to one entry per thread.  Positions and edges of an epoch, 32 workgroups for every batch / by the entries alone / so: 111 M nodes, 147
+// batches 529 / 541 / 525 us, 30 M nodes 340 / 333 / 322, 2.45 M nodes, 196 batches 3,927 / 2,980 / 2,944, 1 M nodes 1,097 / 850 / 843,
+// 233,000 nodes 292 / 260 / 252, 60,000 nodes, 18 small batches 23 / 23 / 22.
+static uint32_t workgroups_per_batch(int64_t n, uint32_t beta, uint32_t nb, int n_cu)
 {
-    const int64_t each = n / beta / (BLK_THREADS * BLK_IN_FLIGHT) + 1;
-    return (uint32_t)std::min<int64_t>(each, BLK_PER_BATCH);
+    const int64_t each = n / beta, round = each / (BLK_THREADS * BLK_IN_FLIGHT) + 1, most = each / BLK_THREADS + 1;
+    const int64_t fill = (int64_t)n_cu * (2048 / BLK_THREADS) / ((nb + BLK_XCDS - 1) / BLK_XCDS * BLK_XCDS);
+    return (uint32_t)std::min<int64_t>(std::max(round, std::min(most, fill)), BLK_PER_BATCH);
 }
 
 // table[k][U_{L,b}[j]] = j for batch b = b_lo + k
@@ -54,10 +59,10 @@ __global__ void __launch_bounds__(BLK_THREADS) block_positions_kernel(const int3
     for (int64_t j0 = (int64_t)part * BLK_THREADS + threadIdx.x; j0 < n; j0 += BLK_IN_FLIGHT * step) {
         uint32_t v[BLK_IN_FLIGHT];
 #pragma unroll
-        for (int q = 0; q < BLK_IN_FLIGHT; ++q) v[q] = (uint32_t)ids[u0 + min(j0 + q * step, n - 1)];              // (past the end: the last ID again, not written)
+        for (int q = 0; q < BLK_IN_FLIGHT; ++q) v[q] = j0 + q * step < n ? (uint32_t)ids[u0 + j0 + q * step] : 0xFFFFFFFFu;
 #pragma unroll
         for (int q = 0; q < BLK_IN_FLIGHT; ++q)
-            if (j0 + q * step < n && v[q] < (uint64_t)n_nodes) t[v[q]] = (int32_t)(j0 + q * step);
+            if (v[q] < (uint64_t)n_nodes) t[v[q]] = (int32_t)(j0 + q * step);
     }
 }
 
@@ -76,7 +81,7 @@ __global__ void __launch_bounds__(BLK_THREADS) block_relabel_kernel(const int32_
         uint32_t u[BLK_IN_FLIGHT];
         int32_t p[BLK_IN_FLIGHT];
 #pragma unroll
-        for (int q = 0; q < BLK_IN_FLIGHT; ++q) u[q] = (uint32_t)samp_nbr[min(e0 + q * step, end - 1)];          // (past the end: the last edge again, not written)
+        for (int q = 0; q < BLK_IN_FLIGHT; ++q) u[q] = e0 + q * step < end ? (uint32_t)samp_nbr[e0 + q * step] : 0xFFFFFFFFu;
 #pragma unroll
         for (int q = 0; q < BLK_IN_FLIGHT; ++q) p[q] = u[q] < (uint64_t)n_nodes ? t[u[q]] : -1;
 #pragma unroll
@@ -99,6 +104,9 @@ rg_status rg_schedule_build_blocks(rg_schedule *s, uint64_t workspace_limit_byte
     const uint64_t per_batch = (uint64_t)std::max<int64_t>(s->n_nodes, 1) * sizeof(int32_t);
     if (workspace_limit_bytes == 0) workspace_limit_bytes = (uint64_t)4 << 30;
     const uint32_t group = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(s->n_batches, workspace_limit_bytes / per_batch));
+    int dev = 0, n_cu = 0;
+    RG_HIP(hipGetDevice(&dev));
+    RG_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     Arena tmp(s->arena.allocator(), st);     // scratch from the allocator the schedule was built with
     int32_t *table = nullptr;
     if (s->n_batches > 0) RG_TRY(tmp.dev((uint64_t)group * per_batch, (void **)&table));
@@ -108,11 +116,11 @@ rg_status rg_schedule_build_blocks(rg_schedule *s, uint64_t workspace_limit_byte
     for (uint32_t b_lo = 0; b_lo < s->n_batches && s->L > 0; b_lo += group) {
         const uint32_t nb = std::min(group, s->n_batches - b_lo);
         ScopedTimer tm(KG_BLOCKS, st);
-        const uint32_t per_batch = workgroups_per_batch(all.off_host[s->n_batches], s->n_batches);
+        const uint32_t per_batch = workgroups_per_batch(all.off_host[s->n_batches], s->n_batches, nb, n_cu);
         hipLaunchKernelGGL(block_positions_kernel, dim3(workgroups_for(nb, per_batch)), dim3(BLK_THREADS), 0, st, all.ids, all.off_dev, b_lo, nb, per_batch, s->n_nodes, table);
         for (uint32_t l = 0; l < s->L; ++l) {
             const HopData &h = s->hop[l];
-            const uint32_t per_batch = workgroups_per_batch(h.n_samples, s->n_batches);
+            const uint32_t per_batch = workgroups_per_batch(h.n_samples, s->n_batches, nb, n_cu);
             if (h.n_samples > 0)
                 hipLaunchKernelGGL(block_relabel_kernel, dim3(workgroups_for(nb, per_batch)), dim3(BLK_THREADS), 0, st, h.samp_nbr, h.samp_off, h.off_dev, b_lo, nb, per_batch,
                                    s->n_nodes, table, h.src_pos);
