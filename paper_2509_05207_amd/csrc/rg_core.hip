@@ -613,11 +613,14 @@ rg_status scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, Arena &tmp
 // 122 M edges, starts with the pass over indptr 43 + 90 us, so 6 + 110.  (Per 64 KB and workgroup, behind a barrier: 6 + 129.)
 // Many rows to few IDs take the wave many turns, and small graphs feel its search for its first row: there the starts stay with
 // the pass over indptr (starts there / behind the IDs: 50 M nodes, 2 IDs each 238 / 292 us, 7 in one of 100 134 / 534; 8,000 nodes, 8 each 32.8 / 34.6).
+// So do, in any graph, those of 64 consecutive rows (from a multiple of 64 on) with few IDs together: however the rows are spread, a wave has
+// no more than one block of 64 to look at for every 1,024 IDs it reads, and few steps between two of them.
 constexpr int VAL_THREADS = 256;
 constexpr int VAL_SLOTS = 16;                  // each count is kept in this many copies, summed by the host (adds to one address queue up)
 constexpr int64_t VAL_ROW_IDS = 16;            // IDs per row, on average, from which on a wave looks at the starts among its IDs ...
 constexpr int64_t VAL_MANY_IDS = 1 << 24;      // ... where there are so many
 __device__ __forceinline__ bool starts_with_the_ids(int64_t n_nodes, int64_t n) { return n >= VAL_ROW_IDS * n_nodes && n >= VAL_MANY_IDS; }
+__device__ __forceinline__ bool long_block(int64_t start, int64_t end) { return end - start >= VAL_ROW_IDS * 64; }
 enum { VAL_ROWS = 0, VAL_FLAT = 1, VAL_STARTS = 2, VAL_GENERAL = 3, VAL_COUNTS = 4 };
 
 __device__ __forceinline__ void add_block_count(unsigned long long x, unsigned long long *counts, int which)
@@ -634,25 +637,28 @@ __device__ __forceinline__ void add_block_count(unsigned long long x, unsigned l
 }
 
 // Rows that decrease (and an indptr that does not start at 0), and the non-empty rows whose first ID is in range but not
-// above the ID in front of it in the flat array, where the flat pass does not look at those.
+// above the ID in front of it in the flat array, where the flat pass does not look at those.  A wave has 64 consecutive rows at a time.
 __global__ void __launch_bounds__(VAL_THREADS) validate_indptr(int64_t n_nodes, const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                                unsigned long long *__restrict__ counts)
 {
-    const bool look_at_starts = !starts_with_the_ids(n_nodes, indptr[n_nodes]);
+    const int64_t n = indptr[n_nodes];
+    const bool flat_looks = starts_with_the_ids(n_nodes, n);
     unsigned long long bad = 0, starts = 0;
+    const int lane = threadIdx.x & 63;
     const int64_t step = (int64_t)gridDim.x * VAL_THREADS;
-    for (int64_t v0 = (int64_t)blockIdx.x * VAL_THREADS + threadIdx.x; v0 < n_nodes; v0 += 4 * step) {
+    for (int64_t v0 = (int64_t)blockIdx.x * VAL_THREADS + threadIdx.x; v0 - lane < n_nodes; v0 += 4 * step) {
         int64_t b[4], e[4];
         int32_t here[4], front[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int64_t v = v0 + k * step;
-            b[k] = v < n_nodes ? indptr[v] : 0;
-            e[k] = v < n_nodes ? indptr[v + 1] : 0;
+            b[k] = v < n_nodes ? indptr[v] : n;
+            e[k] = v < n_nodes ? indptr[v + 1] : n;
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const bool look = look_at_starts && b[k] > 0 && b[k] < e[k];
+            const bool mine = !flat_looks || !long_block(__shfl(b[k], 0, 64), __shfl(e[k], 63, 64));
+            const bool look = mine && b[k] > 0 && b[k] < e[k];
             here[k] = look ? indices[b[k]] : -1;
             front[k] = look ? indices[b[k] - 1] : -1;
         }
@@ -688,9 +694,36 @@ __device__ __forceinline__ int64_t first_row_from(const int64_t *__restrict__ in
     return lo;
 }
 
-// The flat array, a contiguous part of it per wave: 16-byte loads from the first aligned ID on, four in flight per lane; the IDs
-// in front of the first whole vector and after the last by the first workgroup.  Behind each 4 KB so read come the non-empty rows
-// that start in them: those whose first ID is in range but not above the ID in front of it.
+// The first long block of 64 rows from block k on, or no block of those that start in front of id_stop; *start: where it starts (INT64_MAX: there is
+// none).  By a wave, 64 blocks at a time; where those hold few IDs together, 64 groups of 64 blocks at a time, and so on (a group that holds
+// few IDs has no long block; the first that may have one is looked into).
+__device__ __forceinline__ int64_t next_long_block(const int64_t *__restrict__ indptr, int64_t n_nodes, int64_t k, int64_t id_stop, int lane, int64_t *start)
+{
+    int64_t group = 1;                           // blocks per lane
+    while (64 * k < n_nodes) {
+        const int64_t s = indptr[min(64 * (k + lane * group), n_nodes)], e = indptr[min(64 * (k + (lane + 1) * group), n_nodes)];
+        const int64_t first = __shfl(s, 0, 64);
+        if (first >= id_stop) break;
+        const unsigned long long m = __ballot(long_block(s, e));
+        if (m != 0ull) {
+            const int l = __ffsll((long long)m) - 1;
+            k += l * group;
+            *start = __shfl(s, l, 64);
+            if (group == 1) return k;
+            group /= 64;
+        } else {
+            k += 64 * group;
+            if (!long_block(first, __shfl(e, 63, 64)) && 64 * k < n_nodes) group *= 64;      // (at most three times: the rows are fewer than 2^31)
+        }
+    }
+    *start = INT64_MAX;
+    return k;
+}
+
+// The flat array, 4 KB at a time per wave: 16-byte loads from the first aligned ID on, four in flight per lane; the IDs
+// in front of the first whole vector and after the last by the first workgroup.  Where rows are looked at too, a wave has a contiguous
+// part, and behind each 4 KB come the rows of the long blocks that start in them: the non-empty ones whose first ID is in range but not above
+// the ID in front of it.  Elsewhere the waves read side by side (50 M nodes, 2 IDs each, parts / side by side 236 / 231 us).
 constexpr int64_t VAL_ROUND = 4 * 64;            // vectors that a wave reads at once
 __global__ void __launch_bounds__(VAL_THREADS) validate_flat(int64_t n_nodes, const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                              unsigned long long *__restrict__ counts)
@@ -707,10 +740,16 @@ __global__ void __launch_bounds__(VAL_THREADS) validate_flat(int64_t n_nodes, co
     const int lane = threadIdx.x & 63;
     const int64_t n_waves = (int64_t)gridDim.x * (VAL_THREADS / 64), wave = (int64_t)blockIdx.x * (VAL_THREADS / 64) + (threadIdx.x >> 6);
     const int64_t part = ((n_vec + n_waves - 1) / n_waves + VAL_ROUND - 1) / VAL_ROUND * VAL_ROUND;
-    const int64_t i_end = min((wave + 1) * part, n_vec);
     const bool look_at_starts = starts_with_the_ids(n_nodes, n);
-    int64_t v = look_at_starts && wave > 0 && wave * part < n_vec ? first_row_from(indptr, n_nodes, head + 4 * wave * part, lane) : 0;
-    for (int64_t i_lo = wave * part; i_lo < i_end || (wave == 0 && i_lo == 0); i_lo += VAL_ROUND) {      // (fewer IDs than make a vector have their rows, too)
+    const int64_t i_first = wave * (look_at_starts ? part : VAL_ROUND), i_step = look_at_starts ? VAL_ROUND : n_waves * VAL_ROUND;
+    const int64_t i_end = look_at_starts ? min((wave + 1) * part, n_vec) : n_vec;
+    const int64_t part_end = (wave + 1) * part >= n_vec ? n : head + 4 * (wave + 1) * part;
+    int64_t block = 0, start = 0;                // the next block of 64 rows, and where it starts
+    if (look_at_starts && wave > 0 && wave * part < n_vec) {
+        block = (first_row_from(indptr, n_nodes, head + 4 * wave * part, lane) + 63) / 64;
+        start = 64 * block < n_nodes ? indptr[64 * block] : INT64_MAX;
+    }
+    for (int64_t i_lo = i_first; i_lo < i_end; i_lo += i_step) {
         int4 x[4];
         int32_t front[4];
 #pragma unroll
@@ -727,25 +766,23 @@ __global__ void __launch_bounds__(VAL_THREADS) validate_flat(int64_t n_nodes, co
         }
         if (!look_at_starts) continue;
         const int64_t id_end = i_lo + VAL_ROUND >= n_vec ? n : head + 4 * (i_lo + VAL_ROUND);       // (a part that is not the last is whole rounds)
-        int c;
-        do {
-            const int64_t b = indptr[min(v + lane, n_nodes)], e = indptr[min(v + lane + 1, n_nodes)];
-            const bool in = v + lane < n_nodes && b < id_end;        // (the first c lanes: indptr ascends)
-            const bool look = in && b > 0 && b < e;
-            const int32_t here = look ? indices[b] : -1, before = look ? indices[b - 1] : -1;
-            if (here >= 0 && here < n_nodes && before >= here) ++starts;
-            c = __popcll(__ballot(in));
-            v += c;
-            // (sixty-four empty rows, one behind the other: on to the row that the next ID is in)
-            if (c == 64 && __shfl(b, 0, 64) == __shfl(e, 63, 64)) v = first_row_from(indptr, n_nodes, __shfl(b, 0, 64) + 1, lane) - 1;
-        } while (c == 64);
+        while (start < id_end) {
+            const int64_t v = 64 * block + lane, b = indptr[min(v, n_nodes)], e = indptr[min(v + 1, n_nodes)], end = __shfl(e, 63, 64);
+            ++block;
+            if (long_block(start, end)) {
+                const bool look = b > 0 && b < e;
+                const int32_t here = look ? indices[b] : -1, before = look ? indices[b - 1] : -1;
+                if (here >= 0 && here < n_nodes && before >= here) ++starts;
+                start = 64 * block < n_nodes ? end : INT64_MAX;
+            } else block = next_long_block(indptr, n_nodes, block, part_end, lane, &start);
+        }
     }
     if (blockIdx.x == 0 && threadIdx.x < 8) {
         const int64_t j = threadIdx.x < 4 ? (int64_t)threadIdx.x : head + 4 * n_vec + threadIdx.x - 4;
         if (threadIdx.x < 4 ? j < head : j < n) bad += wrong(j > 0 ? indices[j - 1] : -1, indices[j]);
     }
     add_block_count(bad, counts, VAL_FLAT);
-    add_block_count(starts, counts, VAL_STARTS);
+    if (look_at_starts) add_block_count(starts, counts, VAL_STARTS);
 }
 
 // Any indptr: one wave per row, grid-stride; nothing to do where validate_indptr found no row that decreases.  With more

@@ -86,3 +86,37 @@ def test_violations_over_many_waves(rg, edges, rows):
     pad = torch.zeros(edges + 3, dtype=torch.int32, device="cuda")
     pad[3:] = torch.from_numpy(indices).cuda()
     assert rg.rg_graph_validate(torch.from_numpy(indptr).cuda(), pad[3:]) == int(bad.sum())
+
+
+@pytest.mark.parametrize("light", ["one each", "one in 64", "one in 64, elsewhere", "none", "sixteen each", "every third block", "mixed"])
+@pytest.mark.parametrize("heavy_first", [True, False])
+def test_violations_where_few_rows_hold_most_ids(rg, light, heavy_first):
+    """Graphs whose rows hold 16 IDs and more on average, most of them in a few rows: blocks of 64 rows with few IDs together, in runs of
+    every kind, next to blocks with many; repeated IDs on the starts of rows, where they are no fault, and behind them, where they are."""
+    rng = np.random.default_rng(len(light))
+    rows, heavy = 400_000, 24
+    deg = {"one each": lambda: np.ones(rows, np.int64),
+           "one in 64": lambda: (np.arange(rows) % 64 == 0).astype(np.int64),
+           "one in 64, elsewhere": lambda: (np.arange(rows) % 64 == 37).astype(np.int64) * rng.integers(1, 40, size=rows),
+           "none": lambda: np.zeros(rows, np.int64),
+           "sixteen each": lambda: np.full(rows, 16) - (rng.random(rows) < 0.004),              # blocks of 1,024 IDs and of fewer
+           "every third block": lambda: np.where(np.arange(rows) // 64 % 3 == 0, 60, 1),
+           "mixed": lambda: np.repeat(rng.choice([0, 1, 15, 16, 17, 200], size=rows // 500), 500)}[light]()
+    big = np.full(heavy, 800_001)
+    deg = np.concatenate([big, deg] if heavy_first else [deg[: rows // 2], big[::2], deg[rows // 2:], big[1::2]])
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    n, edges = indptr.size - 1, int(indptr[-1])
+    assert edges >= 16 * n and edges >= 1 << 24
+    first = np.zeros(edges + 1, bool)
+    first[indptr[:-1]] = True
+    first = first[:edges]
+    at = np.arange(edges)
+    indices = ((at - np.maximum.accumulate(np.where(first, at, 0))) % n).astype(np.int32)
+    hit = rng.integers(0, edges, size=5000)
+    indices[hit] = rng.choice(np.array([-1, n, 0, n - 1, 2**31 - 1]), size=hit.size)
+    bad = (indices < 0) | (indices >= n)
+    bad[1:] |= ~first[1:] & (indices[:-1] >= indices[1:])
+    for phase in (0, 3):
+        pad = torch.zeros(edges + phase, dtype=torch.int32, device="cuda")
+        pad[phase:] = torch.from_numpy(indices).cuda()
+        assert rg.rg_graph_validate(torch.from_numpy(indptr).cuda(), pad[phase:]) == int(bad.sum())
