@@ -1279,7 +1279,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CAP <= 
 // read its last 16 bytes instead, and only the IDs that no other lane has count.  Blocks come in chunks of ROWS_CHUNK; while one is
 // looked through the next one of the row, or the first one of the next row, is on its way.
 constexpr int ROWS_FANOUT = 64;
-constexpr int ROWS_ROOM = 128;           // candidates of one row
+constexpr int ROWS_ROOM = 128;           // candidates of one row of four
+constexpr int STREAM_ROOM = 192;         // of a row that the whole wave streams: the safe guess lets 104 through at a fan-out of 64, and one tile in 100 more than 128
+                                         // (2,000 tiles of 60,000 IDs, fan-out 60: 204 us with room for 128, where some are streamed twice, 105 so)
 constexpr int ROWS_CHUNK = 2;
 constexpr int MID_ROW = 256;
 
@@ -1353,7 +1355,7 @@ __device__ __forceinline__ void take_block(const u32x4 &blk, int p, int last_fou
     if (__builtin_expect(((m[0] & m[1]) | (m01 & m[2]) | (m012 & m[3])) == 0ull, 1)) {      // no lane holds two candidates: lane order is row order
         const int before = cnt;
         cnt += __popcll(any);
-        if (cnt <= ROWS_ROOM) {
+        if (cnt <= STREAM_ROOM) {
             uint32_t v = my_bit(m[2]) ? u[2] : u[3];
             v = my_bit(m[1]) ? u[1] : v;
             v = my_bit(m[0]) ? u[0] : v;
@@ -1364,7 +1366,7 @@ __device__ __forceinline__ void take_block(const u32x4 &blk, int p, int last_fou
     } else {
         const int before = cnt;
         cnt += __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]);
-        if (cnt <= ROWS_ROOM) {
+        if (cnt <= STREAM_ROOM) {
             int at = places(m[3], places(m[2], places(m[1], places(m[0], before))));
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -1374,7 +1376,7 @@ __device__ __forceinline__ void take_block(const u32x4 &blk, int p, int last_fou
     }
 }
 
-// The row again, with finished keys, until between f and ROWS_ROOM IDs pass: the cut is moved by what the count says is missing
+// The row again, with finished keys, until between f and STREAM_ROOM IDs pass: the cut is moved by what the count says is missing
 // or too much, inside what the tries so far leave.  Returns how many, and the cut.  (Only a row that repeats IDs can have no
 // such cut; its first f IDs stand for it then.)
 __device__ __forceinline__ int retry_row(const StreamedRow &r, int f, uint32_t lo, uint64_t c, int cnt, uint32_t *cut_io, int lane, uint32_t *cand)
@@ -1382,7 +1384,7 @@ __device__ __forceinline__ int retry_row(const StreamedRow &r, int f, uint32_t l
     uint32_t cut = *cut_io;
     uint64_t low = 0, high = (uint64_t)1 << 32;                  // cuts below `low` let too few through, from `high` on too many
     const float spare = 2.0f * __fsqrt_rn((float)f) + 4.0f;
-    for (int t = 0; t < 48 && (cnt < f || cnt > ROWS_ROOM); ++t) {
+    for (int t = 0; t < 48 && (cnt < f || cnt > STREAM_ROOM); ++t) {
         uint64_t next;
         if (cnt < f) {
             low = (uint64_t)cut + 1;
@@ -1398,7 +1400,7 @@ __device__ __forceinline__ int retry_row(const StreamedRow &r, int f, uint32_t l
         for (int j = 0; j < r.n_blocks; ++j) take_block<false, true>(load_row_block(r, j, lane), 256 * j + 4 * lane - r.skip, r.len - 4, lo, c, 0u, cut, cand, cnt);
         cnt = uni(cnt);
     }
-    if (cnt < f || cnt > ROWS_ROOM) {
+    if (cnt < f || cnt > STREAM_ROOM) {
         if (lane < f) cand[lane] = (uint32_t)r.from[r.skip + lane];
         cnt = f;
     }
@@ -1527,6 +1529,7 @@ template <int MARK>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sample_rows_kernel(HopArgs a)
 {
     __shared__ uint32_t cand[4 * MID_STRIDE];                    // one streamed row's candidates, or those of four rows
+    static_assert(STREAM_ROOM <= 4 * MID_STRIDE && STREAM_ROOM % 64 == 0, "");
     __shared__ ShortRec short_recs[64];
     const int lane = threadIdx.x;
     const int f = (int)a.fanout;
@@ -1628,7 +1631,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sa
         uint32_t cut_lane = 0xFFFFFFFFu;
         {
             const float lambda = (is_tile ? safely_guessed_candidates(f) : guessed_candidates(f)) * a.guess_scale;
-            if (deg_lane > ROWS_ROOM || lambda * 2.0f <= (float)deg_lane) cut_lane = guessed_cut_of(fminf(lambda / (float)deg_lane, 0.99f));
+            if (deg_lane > STREAM_ROOM || lambda * 2.0f <= (float)deg_lane) cut_lane = guessed_cut_of(fminf(lambda / (float)deg_lane, 0.99f));
         }
         // where the wave is: chunk j of the row of lane l
         struct Cursor { StreamedRow r; int l, j; uint32_t lo, cut; uint64_t key; };
@@ -1683,7 +1686,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sa
                 uint32_t cut = at.cut;
                 int n = cnt;
                 wave_lds_order();
-                if (n < f || n > ROWS_ROOM) {
+                if (n < f || n > STREAM_ROOM) {
                     n = uni(retry_row(at.r, f, at.lo, at.key, n, &cut, lane, cand));
                     cut = uni(cut);
                     wave_lds_order();
@@ -1695,7 +1698,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sa
                 at = ahead;
                 cnt = 0;
                 if (n <= 64) emit_row<1, MARK>(cand, n, f, lo, hi, cut, lane, out, !is_tile, reached_b);
-                else emit_row<2, MARK>(cand, n, f, lo, hi, cut, lane, out, !is_tile, reached_b);
+                else if (n <= 128) emit_row<2, MARK>(cand, n, f, lo, hi, cut, lane, out, !is_tile, reached_b);
+                else emit_row<3, MARK>(cand, n, f, lo, hi, cut, lane, out, !is_tile, reached_b);
                 wave_lds_order();
             }
             return more;

@@ -51,8 +51,10 @@ def test_rows_against_a_guessed_cut(rg, orc, graph, fanout, scale, shift, monkey
         assert np.array_equal(gso.cpu().numpy(), so) and np.array_equal(gnb.cpu().numpy(), nb), f"samples {hop}"
 
 
-def test_tiles_against_other_cuts(rg, orc, monkeypatch):
-    """The pieces of rows above 16,384 IDs, when the first cut misses."""
+@pytest.mark.parametrize("fanout,scales", [(40, ("0.1", "1", "10")), (64, ("0.6", "1", "1.5", "1.8", "3"))])
+def test_tiles_against_other_cuts(rg, orc, fanout, scales, monkeypatch):
+    """The pieces of rows above 16,384 IDs, when the first cut misses; lists of one to three candidates per lane and longer ones (the safe
+    guess lets 104 through at a fan-out of 64)."""
     rng = np.random.default_rng(10)
     n = 60_000
     deg = np.full(n, 3)
@@ -61,8 +63,8 @@ def test_tiles_against_other_cuts(rg, orc, monkeypatch):
     indptr[1:] = np.cumsum(deg)
     indices = np.concatenate([np.sort(rng.choice(n, size=int(d), replace=False)).astype(np.int32) for d in deg])
     train = np.arange(40, dtype=np.int32)
-    o = orc.Schedule(indptr, indices, train, 10, [40], 0, 0, 0, n_threads=8)
-    for scale in ("0.1", "1", "10"):
+    o = orc.Schedule(indptr, indices, train, 10, [fanout], 0, 0, 0, n_threads=8)
+    for scale in scales:
         monkeypatch.setenv("RAPIDGNN_GUESS_SCALE", scale)
-        g = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), 10, [40], 0, 0, 0)
+        g = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), 10, [fanout], 0, 0, 0)
         assert np.array_equal(rg.rg_schedule_samples(g, 0)[1].cpu().numpy(), o.samples(0)[1]), scale
