@@ -1116,7 +1116,7 @@ struct HopArgs {
     const int32_t *indices;
     const int32_t *frontier; int64_t n_frontier;
     int64_t n_full_groups, n_units;                                    // set by launch_hop: see there ...
-    int tail_shift; int64_t n_own;                                     // ... as are these, for sample_rows_kernel: nodes of a unit behind the full groups (their logarithm), units that belong to a workgroup
+    int tail_shift; int64_t n_own, first_own;                          // ... as are these, for sample_rows_kernel: nodes of a unit behind the full groups (their logarithm), units that belong to a workgroup, and the first one's
     ByPlace place; int64_t n_full_rounds;                              // (rounds of full groups, where units go by place)
     int64_t tile_piece;                                                // tiles_of
     int min_deg;                                                       // rows of up to this many IDs are not sampled one per wave but four at a time, a group's short rows first (sample_kernel<.., true>); 0: none are
@@ -1538,7 +1538,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sa
     // Tiles first, dealt out in turn; in each round XCD x takes a contiguous eighth of the round's jobs (see sample_kernel).
     int64_t k = blockIdx.x;
     if (a.tile_order && (gridDim.x & 7u) == 0) k = (int64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    int64_t own_unit = k >= a.n_tiles ? k - a.n_tiles : -1;
+    int64_t own_unit = k - a.first_own + (k < a.first_own ? gridDim.x : 0);
+    if (own_unit >= a.n_own) own_unit = -1;
     int64_t w = 0, tile_begin = 0; int tile_len = 0; uint64_t tile_state = 0;
     if (k < a.n_tiles) { w = a.tile_order ? a.tile_order[k] : k; tile_begin = a.tile.begin[w]; tile_len = a.tile.len[w]; tile_state = a.tile.state[w]; }
     for (;;) {
@@ -1555,8 +1556,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sa
             k += gridDim.x;
             if (k < a.n_tiles) { w = a.tile_order ? a.tile_order[k] : k; tile_begin = a.tile.begin[w]; tile_len = a.tile.len[w]; tile_state = a.tile.state[w]; }
         } else {
-            // Workgroups without a tile have their first unit of nodes by index, the others come through the counter (7,168 waves that
-            // ask it at once wait 25 us for their turns, which is a small launch's whole time).
+            // Workgroups without a tile have their first unit of nodes by index, and where there is no more than one unit for each all
+            // have; the others come through the counter (7,168 waves that ask it at once wait 25 us for their turns, which is a small launch's
+            // whole time, and longer if they all come from a tile: 6,000 rows of 20,000 IDs, fan-out 10, by the counter / by index 167 / 106 us).
             int64_t g = own_unit;
             own_unit = -1;
             if (g < 0) {
@@ -2000,7 +2002,8 @@ static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, 
     }
     const int64_t n_work = a.n_tiles + a.n_units;
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_work, resident));
-    a.n_own = std::max<int64_t>(0, (int64_t)grid - a.n_tiles);
+    a.n_own = a.n_units <= (int64_t)grid ? a.n_units : std::max<int64_t>(0, (int64_t)grid - a.n_tiles);
+    a.first_own = a.n_tiles % grid;                              // (waves without a tile, or without one more, come first)
     hipLaunchKernelGGL(SAMPLE, dim3(grid), dim3(64), 0, st, a);
     if (a.n_tiles > 0) hipLaunchKernelGGL(MERGE, dim3(merge_grid), dim3(64), 0, st, a);
     return RG_OK;

@@ -68,3 +68,30 @@ def test_tiles_against_other_cuts(rg, orc, fanout, scales, monkeypatch):
         monkeypatch.setenv("RAPIDGNN_GUESS_SCALE", scale)
         g = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), 10, [fanout], 0, 0, 0)
         assert np.array_equal(rg.rg_schedule_samples(g, 0)[1].cpu().numpy(), o.samples(0)[1]), scale
+
+
+def test_more_pieces_than_waves_and_few_nodes(rg, orc):
+    """A second hop whose frontiers, 20 times the same 400 rows above 16,384 IDs, make more pieces than the chip runs waves (28 per compute
+    unit) but no more units of nodes: every wave has a piece, or two, and a unit of its own behind them."""
+    n, deg, hubs, seeds = 36_000, 17_500, 400, 600
+    rng = np.random.default_rng(2)
+    hub_ids = np.sort(rng.choice(n, size=hubs, replace=False)).astype(np.int32)
+    train = rng.choice(np.setdiff1d(np.arange(n), hub_ids), size=seeds, replace=False).astype(np.int32)
+    degs = rng.integers(0, 30, size=n)
+    degs[hub_ids] = deg
+    degs[train] = hubs
+    indptr = np.concatenate([[0], np.cumsum(degs)]).astype(np.int64)
+    is_hub, is_seed = np.zeros(n, bool), np.zeros(n, bool)
+    is_hub[hub_ids], is_seed[train] = True, True
+    rows = [2 * np.arange(deg) + rng.integers(0, 2, size=deg) if is_hub[v] else hub_ids if is_seed[v] else np.sort(rng.choice(n, size=degs[v], replace=False)) for v in range(n)]
+    indices = np.concatenate(rows).astype(np.int32)
+    o = orc.Schedule(indptr, indices, train, 30, [60, 9], 1, 0, 0, n_threads=8)
+    nodes, off = o.frontier(1)
+    waves = 28 * torch.cuda.get_device_properties(0).multi_processor_count
+    assert is_hub[nodes].sum() > waves >= nodes.size // 4
+    s = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), 30, [60, 9], 1, 0, 0)
+    for hop in range(2):
+        so, nb = o.samples(hop)
+        gso, gnb = rg.rg_schedule_samples(s, hop)
+        assert np.array_equal(gso.cpu().numpy(), so) and np.array_equal(gnb.cpu().numpy(), nb), hop
+    assert np.array_equal(rg.rg_schedule_frontier(s, 2)[0].cpu().numpy(), o.frontier(2)[0])
