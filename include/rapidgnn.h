@@ -98,7 +98,10 @@ typedef struct rg_cache rg_cache;
  *   a            allocator or NULL
  *   out          receives the handle
  * Scratch, for the duration of the call: two bitmaps of n_batches * n_nodes bits
- * (the IDs a batch has seen, and the IDs a hop reaches).
+ * (the IDs a batch has seen, and the IDs a hop reaches); and per hop 28 bytes per
+ * frontier node and 4 * fanout + 32 bytes per piece of the rows above 16,384 IDs
+ * (65,536 IDs a piece; at fan-outs up to 64 16,384 IDs in a first hop, or with
+ * fewer than 16 batches, where the larger ones are at most six per compute unit).
  * Environment: RAPIDGNN_SPARSE_FRONTIER=1 / 0 forces / forbids the frontier
  * passes tuned for graphs of 10^7 nodes and more (default: chosen from
  * n_nodes; the sampling kernels then mark what they reach themselves);

@@ -68,9 +68,13 @@ constexpr int TILE_PIECE = 65536;        // ... in near-equal pieces of at most 
                                          // sampled among the tile jobs, where the batches that share it meet in the caches.  Measured on the five
                                          // workloads: pieces of 16,384 cost 8 % more sampling time on the largest graph, pieces of 131,072 7 %;
                                          // tiling from 8,192 IDs on is 3 % slower there and 3 % faster on large_sparse.)
-// Where a frontier is too small to fill the chip, a piece is what its launch waits for, at one memory latency per kilobyte: pieces of
-// SMALL_PIECE there.
+// Where a hop's long rows are too few to fill the chip, a piece is what its launch waits for, at one memory latency per kilobyte: pieces of
+// SMALL_PIECE there, that is where pieces of TILE_PIECE are no more than FEW_TILES per compute unit.  More of them fill it as they are, and four times as
+// many no longer fit into the waves that run at once.  Sampling of one hop's rows in pieces of 16,384 / of 65,536, by how many rows, each one piece of the
+// larger: rows of 60,000 IDs, fan-out 10 500 30 / 50 us, 1,000 50 / 58, 1,500 90 / 96, 2,000 123 / 109, 3,000 165 / 149, 8,000 407 / 383; fan-out 60
+// 1,000 54 / 60, 2,000 128 / 116; rows of 34,000, fan-out 25 1,000 35 / 38, 2,000 62 / 57; rows of 20,000, fan-out 10 1,000 26 / 28, 2,000 40 / 35.
 constexpr int SMALL_PIECE = 16384;
+constexpr int FEW_TILES = 6;
 __device__ __host__ __forceinline__ int64_t tiles_of(int64_t deg, int64_t piece) { return deg > BIG_ROW ? (deg + piece - 1) / piece : 0; }
 
 // Per frontier node, by position: where its row starts, its degree, its batch and its stream.
@@ -160,8 +164,8 @@ static ByPlace by_place(const HopData &cur, uint32_t beta, int64_t n_nodes)
 
 // Also adds up, over the frontier, what the hop will read of the adjacency: [0] the sum of the degrees (in IDs),
 // [1] the part of it in rows of up to BIG_ROW IDs (the rows that are not sampled as tiles), [2] the number of rows of
-// 1 .. SHORT_ROW IDs and [3] the IDs in them; of flagged hub rows, [4] how many and [5] how many tiles they make.  The
-// sums (the first four where no hub rows are looked for) are spread over DEG_SUM_SLOTS sets of counters, total[number of
+// 1 .. SHORT_ROW IDs and [3] the IDs in them; of flagged hub rows, [4] how many and [5] how many tiles they make, or, where none are looked
+// for, [4] how many tiles all rows make in pieces of TILE_PIECE.  The sums (the first five where no hub rows are looked for) are spread over DEG_SUM_SLOTS sets of counters, total[number of
 // sums * slot + k], which the host adds up: thousands of workgroups adding to one address would queue up behind each other.
 constexpr int DEG_SUM_SLOTS = 64;
 constexpr int DEG_SUMS = 6;
@@ -202,7 +206,7 @@ __global__ void __launch_bounds__(NODE_THREADS) node_records_kernel(const int64_
         chunk = batch_off[b] / NODE_CHUNK + round;
         if (chunk >= (b + 1 < n_batches ? batch_off[b + 1] / NODE_CHUNK : (n + NODE_CHUNK - 1) / NODE_CHUNK)) return;
     }
-    constexpr int SUMS = HUBS ? DEG_SUMS : DEG_SUMS - 2;
+    constexpr int SUMS = HUBS ? DEG_SUMS : DEG_SUMS - 1;
     __shared__ unsigned long long part[SUMS + 1][NODE_THREADS / 64];
     unsigned long long acc[SUMS + 1] = {};       // see above; and the chunk's sums
     const int64_t base = chunk * NODE_CHUNK;
@@ -244,7 +248,8 @@ __global__ void __launch_bounds__(NODE_THREADS) node_records_kernel(const int64_
         acc[0] += (unsigned long long)d;
         if (d <= (int64_t)BIG_ROW) acc[1] += (unsigned long long)d;
         if (d > 0 && d <= (int64_t)SHORT_ROW) { acc[2] += 1; acc[3] += (unsigned long long)d; }
-        if (HUBS && hub) { acc[4 % SUMS] += 1; acc[5 % SUMS] += tiles; }
+        if (HUBS && hub) { acc[4] += 1; acc[5 % SUMS] += tiles; }
+        if (!HUBS) acc[4] += (unsigned long long)tiles_of(d, TILE_PIECE);
         acc[SUMS] += (unsigned long long)samples | (unsigned long long)(hub ? 0u : tiles) << 32;
     }
 #pragma unroll
@@ -2211,7 +2216,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
             hubs.min_deg = std::max((int32_t)std::min(line, 2147483647.0), BIG_ROW + 1);
     }
     const bool look_for_hubs = *looked_for_hubs = hubs.min_deg != INT32_MAX;
-    const int64_t tile_piece = fanout <= (uint32_t)ROWS_FANOUT && (hop == 0 || beta < HUB_BATCHES) && !look_for_hubs && n_cur < (int64_t)n_cu * SMALL_FRONTIER ? SMALL_PIECE : TILE_PIECE;
+    int64_t tile_piece = fanout <= (uint32_t)ROWS_FANOUT && (hop == 0 || beta < HUB_BATCHES) && !look_for_hubs && n_cur < (int64_t)n_cu * SMALL_FRONTIER ? SMALL_PIECE : TILE_PIECE;
     uint32_t *count = nullptr, *chunk_hub = nullptr;
     unsigned long long *chunk_sum = nullptr;
     int64_t *samp_base = nullptr, *tile_base = nullptr;
@@ -2227,7 +2232,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     RG_TRY(keep.dev_n<int64_t>((uint64_t)n_cur + 1, &cur.samp_off));
     unsigned long long sums[DEG_SUMS] = {}, *sum_deg_dev = nullptr;       // see node_records_kernel
     unsigned long long sum_parts[DEG_SUMS * DEG_SUM_SLOTS];
-    const int n_sums = look_for_hubs ? DEG_SUMS : DEG_SUMS - 2;
+    const int n_sums = look_for_hubs ? DEG_SUMS : DEG_SUMS - 1;
     const size_t sum_bytes = (size_t)n_sums * DEG_SUM_SLOTS * sizeof(unsigned long long);
     const size_t hub_cleared = look_for_hubs ? sizeof(HubCounts) + HUB_SLOTS * sizeof(uint32_t) : 0;      // behind the sums, cleared with them
     RG_TRY(tmp.dev(sum_bytes + hub_cleared, (void **)&sum_deg_dev));
@@ -2239,9 +2244,8 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         hubs.list = reinterpret_cast<int32_t *>(hubs.rows + HUB_SLOTS);
         RG_TRY(tmp.dev_n<uint32_t>((uint64_t)n_chunks, &chunk_hub));
     }
-    {
-        ScopedTimer tm(KG_OFFSETS, st);
-        const dim3 grid((unsigned)n_chunks), block(NODE_THREADS);
+    const dim3 grid((unsigned)n_chunks), block(NODE_THREADS);
+    auto launch_records = [&] {
         // (the chunks that begin in a batch, at most one more than fit it)
         const dim3 record_grid(place.n_batches ? (unsigned)((place.longest / NODE_CHUNK + 2) * beta) : (unsigned)n_chunks);
         if (look_for_hubs)
@@ -2251,6 +2255,10 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
             hipLaunchKernelGGL(node_records_kernel<false>, record_grid, block, 0, st, g->indptr, cur.ids, n_cur, cur.off_dev, beta, batch_seed, hop, fanout, tile_piece, rec, count, chunk_sum,
                                chunk_hub, (int64_t)g->n_nodes, sum_deg_dev, hubs, place.n_batches ? 1 : 0);
         hipLaunchKernelGGL(scan_chunks_kernel, dim3(1), dim3(CHUNK_SCAN_THREADS), 0, st, chunk_sum, (const uint32_t *)nullptr, n_chunks, samp_base, tile_base, cur.samp_off + n_cur);
+    };
+    {
+        ScopedTimer tm(KG_OFFSETS, st);
+        launch_records();
         hipLaunchKernelGGL(sample_offsets_kernel, grid, block, 0, st, count, n_cur, samp_base, cur.samp_off);
         RG_HIP(hipGetLastError());
     }
@@ -2288,9 +2296,15 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         }
         return RG_OK;
     }
+    if (tile_piece == SMALL_PIECE && sums[4] > (uint64_t)FEW_TILES * n_cu) {      // not so few after all: the same records, the rows in larger pieces
+        tile_piece = TILE_PIECE;
+        n_tiles = (int64_t)sums[4];
+        ScopedTimer tm(KG_OFFSETS, st);
+        launch_records();
+    }
     // The hub rows: as jobs of hub_sample_kernel where that saves more than it costs, the tables and jobs find memory and the
     // rows turn out to be in order; else as tile jobs like the other long rows.
-    const uint64_t n_hub_jobs = sums[4], n_hub_tiles = sums[5];
+    const uint64_t n_hub_jobs = look_for_hubs ? sums[4] : 0, n_hub_tiles = sums[5];
     HubBucket *buckets = nullptr;
     HubJob *jobs = nullptr;
     bool hub_jobs = n_hub_jobs > 0 && n_hub_jobs <= 0x7FFFFFFFull && (forced_line || n_hub_tiles >= (uint64_t)HUB_TILES_PER_CU * n_cu) &&

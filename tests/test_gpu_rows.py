@@ -70,6 +70,27 @@ def test_tiles_against_other_cuts(rg, orc, fanout, scales, monkeypatch):
         assert np.array_equal(rg.rg_schedule_samples(g, 0)[1].cpu().numpy(), o.samples(0)[1]), scale
 
 
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("deg", [16_385, 33_000])
+def test_pieces_of_few_and_of_many_long_rows(rg, orc, deg, more):
+    """A first hop's rows above 16,384 IDs go in small pieces up to six large ones per compute unit, in large ones beyond: on the line and past it."""
+    rows = 6 * torch.cuda.get_device_properties(0).multi_processor_count + more
+    n, small = 2 * deg, 50
+    rng = np.random.default_rng(deg)
+    long_rows = 2 * np.arange(deg, dtype=np.int32) + rng.integers(0, 2, size=(rows, deg), dtype=np.int32)
+    short_rows = np.sort(rng.integers(0, n // 8, size=(small, 8), dtype=np.int32) + np.arange(8, dtype=np.int32) * (n // 8), axis=1)
+    indptr = np.concatenate([np.arange(rows + 1, dtype=np.int64) * deg, rows * deg + 8 * np.arange(1, small + 1), np.full(n - rows - small, rows * deg + 8 * small)])
+    indices = np.concatenate([long_rows.ravel(), short_rows.ravel()])
+    train = rng.permutation(rows + small).astype(np.int32)
+    batch = -(-train.size // 20)
+    o = orc.Schedule(indptr, indices, train, batch, [7], 1, 0, 0, n_threads=8)
+    s = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), batch, [7], 1, 0, 0)
+    so, nb = o.samples(0)
+    gso, gnb = rg.rg_schedule_samples(s, 0)
+    assert np.array_equal(gso.cpu().numpy(), so) and np.array_equal(gnb.cpu().numpy(), nb)
+    assert np.array_equal(rg.rg_schedule_frontier(s, 1)[0].cpu().numpy(), o.frontier(1)[0])
+
+
 def test_more_pieces_than_waves_and_few_nodes(rg, orc):
     """A second hop whose frontiers, 20 times the same 400 rows above 16,384 IDs, make more pieces than the chip runs waves (28 per compute
     unit) but no more units of nodes: every wave has a piece, or two, and a unit of its own behind them."""
