@@ -1530,8 +1530,12 @@ __device__ __forceinline__ unsigned long long sample_mid_round(const ShortRec &r
     return again;
 }
 
+// Six waves per SIMD, 80 registers: eleven or twelve of them spill, to 40 or 52 bytes of scratch per lane, reloaded once per row or round of rows.  At
+// seven waves (72 registers, up to 20 spilled) what a row costs besides its keys is slower, at five nothing spills but fewer waves wait together:
+// sampling launches and mark pass at seven / six / five waves, 233,000 nodes 2,807 / 2,786 / 2,781 us, 2.45 M nodes, 15, 10, 5 7,077 / 7,039 / 7,036, 50, 50
+// 1,745 / 1,720 / 1,778, 111 M nodes 1,885 / 1,884 / 1,915; one hop of 200,000 rows of 100 IDs, fan-out 60 123 / 115; 16,000 rows of 20,000 IDs, fan-out 10 272 / 255.
 template <int MARK>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sample_rows_kernel(HopArgs a)
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) sample_rows_kernel(HopArgs a)
 {
     __shared__ uint32_t cand[4 * MID_STRIDE];                    // one streamed row's candidates, or those of four rows
     static_assert(STREAM_ROOM <= 4 * MID_STRIDE && STREAM_ROOM % 64 == 0, "");
@@ -1562,7 +1566,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) sa
             if (k < a.n_tiles) { w = a.tile_order ? a.tile_order[k] : k; tile_begin = a.tile.begin[w]; tile_len = a.tile.len[w]; tile_state = a.tile.state[w]; }
         } else {
             // Workgroups without a tile have their first unit of nodes by index, and where there is no more than one unit for each all
-            // have; the others come through the counter (7,168 waves that ask it at once wait 25 us for their turns, which is a small launch's
+            // have; the others come through the counter (thousands of waves that ask it at once wait 25 us for their turns, which is a small launch's
             // whole time, and longer if they all come from a tile: 6,000 rows of 20,000 IDs, fan-out 10, by the counter / by index 167 / 106 us).
             int64_t g = own_unit;
             own_unit = -1;
@@ -1963,7 +1967,7 @@ constexpr int HUB_TILES_PER_CU = 24;
 constexpr uint32_t HUB_BATCHES = 16;
 
 // Nodes per compute unit from which on a frontier gives every resident wave a group of 64.
-constexpr int SMALL_FRONTIER = 28 * 64;
+constexpr int SMALL_FRONTIER = 24 * 64;
 
 // Every workgroup of the sampling launch must be resident from the start (tiles are dealt out by workgroup index), so
 // the grid is what the chip holds of this kernel, or the amount of work if that is less.

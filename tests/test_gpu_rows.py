@@ -92,8 +92,8 @@ def test_pieces_of_few_and_of_many_long_rows(rg, orc, deg, more):
 
 
 def test_more_pieces_than_waves_and_few_nodes(rg, orc):
-    """A second hop whose frontiers, 20 times the same 400 rows above 16,384 IDs, make more pieces than the chip runs waves (28 per compute
-    unit) but no more units of nodes: every wave has a piece, or two, and a unit of its own behind them."""
+    """A second hop whose frontiers, 20 times the same 400 rows above 16,384 IDs, make more pieces than the chip runs waves (no more than 28
+    per compute unit) but no more units of nodes: every wave has a piece, or two, and a unit of its own behind them."""
     n, deg, hubs, seeds = 36_000, 17_500, 400, 600
     rng = np.random.default_rng(2)
     hub_ids = np.sort(rng.choice(n, size=hubs, replace=False)).astype(np.int32)
