@@ -620,6 +620,11 @@ constexpr int VAL_SLOTS = 16;                  // each count is kept in this man
 constexpr int64_t VAL_ROW_IDS = 16;            // IDs per row, on average, from which on a wave looks at the starts among its IDs ...
 constexpr int64_t VAL_MANY_IDS = 1 << 24;      // ... where there are so many
 __device__ __forceinline__ bool starts_with_the_ids(int64_t n_nodes, int64_t n) { return n >= VAL_ROW_IDS * n_nodes && n >= VAL_MANY_IDS; }
+__device__ __forceinline__ int64_t from_lane(int64_t x, int lane)      // (lane the same in the whole wave)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), lane);
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
 __device__ __forceinline__ bool long_block(int64_t start, int64_t end) { return end - start >= VAL_ROW_IDS * 64; }
 enum { VAL_ROWS = 0, VAL_FLAT = 1, VAL_STARTS = 2, VAL_GENERAL = 3, VAL_COUNTS = 4 };
 
@@ -657,7 +662,7 @@ __global__ void __launch_bounds__(VAL_THREADS) validate_indptr(int64_t n_nodes, 
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const bool mine = !flat_looks || !long_block(__shfl(b[k], 0, 64), __shfl(e[k], 63, 64));
+            const bool mine = !flat_looks || !long_block(from_lane(b[k], 0), from_lane(e[k], 63));
             const bool look = mine && b[k] > 0 && b[k] < e[k];
             here[k] = look ? indices[b[k]] : -1;
             front[k] = look ? indices[b[k] - 1] : -1;
@@ -702,18 +707,18 @@ __device__ __forceinline__ int64_t next_long_block(const int64_t *__restrict__ i
     int64_t group = 1;                           // blocks per lane
     while (64 * k < n_nodes) {
         const int64_t s = indptr[min(64 * (k + lane * group), n_nodes)], e = indptr[min(64 * (k + (lane + 1) * group), n_nodes)];
-        const int64_t first = __shfl(s, 0, 64);
+        const int64_t first = from_lane(s, 0);
         if (first >= id_stop) break;
         const unsigned long long m = __ballot(long_block(s, e));
         if (m != 0ull) {
-            const int l = __ffsll((long long)m) - 1;
+            const int l = __builtin_amdgcn_readfirstlane(__ffsll((long long)m) - 1);
             k += l * group;
-            *start = __shfl(s, l, 64);
+            *start = from_lane(s, l);
             if (group == 1) return k;
             group /= 64;
         } else {
             k += 64 * group;
-            if (!long_block(first, __shfl(e, 63, 64)) && 64 * k < n_nodes) group *= 64;      // (at most three times: the rows are fewer than 2^31)
+            if (!long_block(first, from_lane(e, 63)) && 64 * k < n_nodes) group *= 64;      // (at most three times: the rows are fewer than 2^31)
         }
     }
     *start = INT64_MAX;
@@ -767,7 +772,7 @@ __global__ void __launch_bounds__(VAL_THREADS) validate_flat(int64_t n_nodes, co
         if (!look_at_starts) continue;
         const int64_t id_end = i_lo + VAL_ROUND >= n_vec ? n : head + 4 * (i_lo + VAL_ROUND);       // (a part that is not the last is whole rounds)
         while (start < id_end) {
-            const int64_t v = 64 * block + lane, b = indptr[min(v, n_nodes)], e = indptr[min(v + 1, n_nodes)], end = __shfl(e, 63, 64);
+            const int64_t v = 64 * block + lane, b = indptr[min(v, n_nodes)], e = indptr[min(v + 1, n_nodes)], end = from_lane(e, 63);
             ++block;
             if (long_block(start, end)) {
                 const bool look = b > 0 && b < e;
