@@ -1121,10 +1121,10 @@ struct HopArgs {
     const int32_t *indices;
     const int32_t *frontier; int64_t n_frontier;
     int64_t n_full_groups, n_units;                                    // set by launch_hop: see there ...
-    int tail_shift; int64_t n_own, first_own;                          // ... as are these, for sample_rows_kernel: nodes of a unit behind the full groups (their logarithm), units that belong to a workgroup, and the first one's
+    int tail_shift; int64_t n_own, first_own;                          // ... as are these, for sample_rows_kernel: nodes of a unit behind the full groups (their logarithm), units that go by index, and the first one's workgroup
     ByPlace place; int64_t n_full_rounds;                              // (rounds of full groups, where units go by place)
     int64_t tile_piece;                                                // tiles_of
-    int min_deg;                                                       // rows of up to this many IDs are not sampled one per wave but four at a time, a group's short rows first (sample_kernel<.., true>); 0: none are
+    int min_deg;                                                       // rows of up to this many IDs are not copied one per wave but four at a time, a group's short rows first (sample_kernel<.., true>); 0: none are
     NodeRecs rec;
     uint32_t fanout;
     const int64_t *samp_off; int32_t *samp_nbr;
@@ -1565,11 +1565,12 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) sa
             k += gridDim.x;
             if (k < a.n_tiles) { w = a.tile_order ? a.tile_order[k] : k; tile_begin = a.tile.begin[w]; tile_len = a.tile.len[w]; tile_state = a.tile.state[w]; }
         } else {
-            // Workgroups without a tile have their first unit of nodes by index, and where there is no more than one unit for each all
-            // have; the others come through the counter (thousands of waves that ask it at once wait 25 us for their turns, which is a small launch's
-            // whole time, and longer if they all come from a tile: 6,000 rows of 20,000 IDs, fan-out 10, by the counter / by index 167 / 106 us).
+            // Workgroups without a tile have their first unit of nodes by index, and where a frontier is small all units go by index, a wave every
+            // grid's one; the others come through the counter.  It answers one wave every 4 to 8 ns: thousands that ask at once wait 25 us for their turns,
+            // which is a small launch's whole time, more where they all come from a tile (6,000 rows of 20,000 IDs, fan-out 10, by the counter / by index
+            // 167 / 106 us), and more where the units are small (13 batches of 7,500 nodes, 450 IDs each, in units of four: 384 / 160 us for two hops).
             int64_t g = own_unit;
-            own_unit = -1;
+            own_unit = g >= 0 && g + gridDim.x < a.n_own ? g + gridDim.x : -1;
             if (g < 0) {
                 if (a.n_own >= a.n_units) break;
                 g = a.n_own + grab_work(a.next_work, lane);
@@ -1992,7 +1993,7 @@ static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, 
     a.tail_shift = 4;
     if (ROWS) {
         // A frontier that leaves waves without a group of 64 is split so that all waves that it can occupy have one unit, of as few nodes as that
-        // takes (four at least: rows up to MID_ROW IDs are sampled four at a time), or twice as fine where rows are long work.
+        // takes (four at least: rows up to MID_ROW IDs are sampled four at a time), or four times as fine where rows are long work.
         if (few) {
             int shift = 2;
             while (shift < 6 && (a.n_frontier >> shift) > resident) shift += 2;
@@ -2011,7 +2012,7 @@ static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, 
     }
     const int64_t n_work = a.n_tiles + a.n_units;
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_work, resident));
-    a.n_own = a.n_units <= (int64_t)grid ? a.n_units : std::max<int64_t>(0, (int64_t)grid - a.n_tiles);
+    a.n_own = few ? a.n_units : std::max<int64_t>(0, (int64_t)grid - a.n_tiles);
     a.first_own = a.n_tiles % grid;                              // (waves without a tile, or without one more, come first)
     hipLaunchKernelGGL(SAMPLE, dim3(grid), dim3(64), 0, st, a);
     if (a.n_tiles > 0) hipLaunchKernelGGL(MERGE, dim3(merge_grid), dim3(64), 0, st, a);

@@ -116,3 +116,18 @@ def test_more_pieces_than_waves_and_few_nodes(rg, orc):
         gso, gnb = rg.rg_schedule_samples(s, hop)
         assert np.array_equal(gso.cpu().numpy(), so) and np.array_equal(gnb.cpu().numpy(), nb), hop
     assert np.array_equal(rg.rg_schedule_frontier(s, 2)[0].cpu().numpy(), o.frontier(2)[0])
+
+
+@pytest.mark.parametrize("batch,rest", [(1000, 0), (2000, 0), (2000, 1999), (40_000, 1)])
+def test_small_frontiers_of_more_units_than_waves(rg, orc, batch, rest):
+    """40,000 nodes of 300 IDs each, in units of four: more units than waves run at once, each wave's by index; in frontier order, and by the batches'
+    like places with a last batch of one node."""
+    n, deg = 40_000, 300
+    rng = np.random.default_rng(4)
+    indices = (rng.integers(0, n // deg, size=(n, deg), dtype=np.int32) + np.arange(deg, dtype=np.int32) * (n // deg)).ravel()
+    indptr = np.arange(0, n * deg + 1, deg, dtype=np.int64)
+    train = rng.permutation(n)[: n - rest].astype(np.int32)
+    o = orc.Schedule(indptr, indices, train, batch, [6], 1, 0, 0, n_threads=8)
+    s = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), batch, [6], 1, 0, 0)
+    assert np.array_equal(rg.rg_schedule_samples(s, 0)[1].cpu().numpy(), o.samples(0)[1])
+    assert np.array_equal(rg.rg_schedule_frontier(s, 1)[0].cpu().numpy(), o.frontier(1)[0])
