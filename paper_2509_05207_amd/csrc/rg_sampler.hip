@@ -2108,9 +2108,10 @@ __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *
 #pragma unroll
         for (int q = 0; q < MARK_IN_FLIGHT; ++q) to[q] = *reinterpret_cast<const u32x4_dword_aligned *>(samp_nbr + min(j0 + q * 4 * MARK_THREADS, whole_end - 4));      // (past the end: the last ones again)
     };
-    auto mark_all = [&](const u32x4 (&u)[MARK_IN_FLIGHT]) {
+    auto mark_all = [&](int64_t j0, const u32x4 (&u)[MARK_IN_FLIGHT]) {
 #pragma unroll
-        for (int q = 0; q < MARK_IN_FLIGHT; ++q) { mark(u[q].x); mark(u[q].y); mark(u[q].z); mark(u[q].w); }
+        for (int q = 0; q < MARK_IN_FLIGHT; ++q)
+            if (j0 + q * 4 * MARK_THREADS < whole_end) { mark(u[q].x); mark(u[q].y); mark(u[q].z); mark(u[q].w); }      // (thousands of threads' marks on the last ones' words would queue up: 98 batches of 41,000 samples 14.5 us, so 8.3)
     };
     constexpr int64_t ROUND = 4 * MARK_IN_FLIGHT * MARK_THREADS;
     if (whole_end > lo) {
@@ -2119,11 +2120,11 @@ __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *
         load(j0, x);
         while (j0 < whole_end) {
             load(j0 + ROUND, y);
-            mark_all(x);
+            mark_all(j0, x);
             j0 += ROUND;
             if (j0 >= whole_end) break;
             load(j0 + ROUND, x);
-            mark_all(y);
+            mark_all(j0, y);
             j0 += ROUND;
         }
     }
