@@ -473,8 +473,9 @@ __device__ __forceinline__ void emit_candidates(const uint32_t *buf, int cnt, in
 }
 
 // Row of f < len <= 64 * E IDs held in registers (u[e] of lane l is row[e * 64 + l]),
-// sampled and written to out in row order.  buf: scratch of at least 64 entries (used when E > 1).
-template <int E, int MARK>
+// sampled and written to out in row order.  buf: scratch of at least 64 entries (used when GUESS).  GUESS: a fan-out at which 64
+// candidates may do (merged tiles of fan-outs up to 64; at larger ones the guess lets more than 64 through as a rule).
+template <int E, int MARK, bool GUESS>
 __device__ __forceinline__ void sample_registers(const uint32_t (&u)[E], int len, int f, uint32_t lo, uint32_t hi, int lane, uint32_t *buf,
                                                  int32_t *__restrict__ out, const ReachedOfBatch &reached_b)
 {
@@ -486,11 +487,11 @@ __device__ __forceinline__ void sample_registers(const uint32_t (&u)[E], int len
         vm[e] = low_lanes(len - e * 64);
         k[e] = key32_open(lo, hi, u[e]);
     }
-    if (E > 1) {
+    if (GUESS && E > 1) {
         // As for long rows, a cut guessed from the key distribution first.  If between f and 64 IDs pass, they are
         // listed one per lane and the threshold is searched among those alone, from the guessed cut's leading bit down.
         const float lambda = guessed_candidates(f);
-        if (uni(lambda * 2.0f <= (float)len && lambda <= 56.0f)) {          // (a larger fan-out lets more than 64 through as a rule)
+        if (uni(lambda * 2.0f <= (float)len && lambda <= 56.0f)) {
             const uint32_t guessed = uni(guessed_cut_of(lambda / (float)len));
             unsigned long long m[E];
             int total = 0;
@@ -860,10 +861,10 @@ __device__ __forceinline__ void sample_row(const int32_t *__restrict__ row, int 
 {
     if (len <= 64) {
         const uint32_t u[1] = {first};
-        sample_registers<1, MARK>(u, len, f, lo, hi, lane, buf, out, reached_b);
+        sample_registers<1, MARK, false>(u, len, f, lo, hi, lane, buf, out, reached_b);
     } else if (len <= 256) {
         const uint32_t u[4] = {first, ahead.x, ahead.y, ahead.z};
-        sample_registers<4, MARK>(u, len, f, lo, hi, lane, buf, out, reached_b);
+        sample_registers<4, MARK, CAP <= 128>(u, len, f, lo, hi, lane, buf, out, reached_b);
     } else {
         sample_long_row<CAP, MARK>(row, len, first, f, lo, hi, lane, buf, ahead, out, reached_b);
     }
@@ -874,12 +875,8 @@ __device__ __forceinline__ void sample_row(const int32_t *__restrict__ row, int 
 // instructions, and the next row's load cannot start much earlier than this row's ends.  Here a wave takes 64
 // consecutive frontier nodes, lists the ones with 1 .. SHORT_ROW neighbours -- shortest first, so that rows of a
 // round are of a kind -- and samples four of them at once, one per row of sixteen lanes (lane l of a row holds IDs
-// l, l + 16, l + 32, l + 48 of it), with the next four rows' IDs already on their way.  The f smallest keys of a
-// row: for rows of up to 16 IDs (one key per lane) by rank -- every key is compared with every other key of its row as
-// the register rotates through the sixteen lanes (DPP row rotation, no LDS), and the IDs whose key has fewer than f
-// smaller keys are the sample; for longer rows by the same bisection on the key value as everywhere else, the four
-// rows searching side by side, each lane counting its own row's sixteen bits of every lane mask.  Output positions
-// come from the lane masks, in row order, as in the other kernels.
+// l, l + 16, l + 32, l + 48 of it), with the next four rows' IDs already on their way.  How the f smallest keys are found
+// and put in order: emit_rows.  At fan-outs above 64 such rows are their own samples and are copied.
 struct ShortRec {
     int64_t row_begin, out;
     uint64_t state;
@@ -1005,8 +1002,9 @@ __device__ __forceinline__ void emit_rows(const uint32_t (&u)[E], int n, int f, 
     }
 }
 
-// The listed short rows (recs[0 .. count), shortest first; LDS) sampled four per round.  All 64 lanes call it.
-template <int MARK>
+// The listed short rows (recs[0 .. count), shortest first; LDS) sampled four per round.  All 64 lanes call it.  COPY: none is longer
+// than the fan-out.
+template <int MARK, bool COPY>
 __device__ __forceinline__ void sample_short_rows(const ShortRec *recs, int count, const int32_t *__restrict__ indices, int f,
                                                   int32_t *__restrict__ samp_nbr, const ReachedMaps &reached, int lane)
 {
@@ -1029,7 +1027,11 @@ __device__ __forceinline__ void sample_short_rows(const ShortRec *recs, int coun
         int32_t *out = samp_nbr + r.out;
         const uint32_t lo = (uint32_t)r.state, hi = (uint32_t)(r.state >> 32);
         const uint32_t u1[1] = {u[0]}, u2[2] = {u[0], u[1]};
-        if (ballot64(r.deg > 32) != 0ull) emit_rows<4, MARK>(u, r.deg, f, lo, hi, l16, out, reached_b);
+        if (COPY) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (l16 + 16 * e < r.deg) { out[l16 + 16 * e] = (int32_t)u[e]; mark_reached<MARK>(reached_b, u[e]); }
+        } else if (ballot64(r.deg > 32) != 0ull) emit_rows<4, MARK>(u, r.deg, f, lo, hi, l16, out, reached_b);
         else if (ballot64(r.deg > 16) != 0ull) emit_rows<2, MARK>(u2, r.deg, f, lo, hi, l16, out, reached_b);
         else emit_rows<1, MARK>(u1, r.deg, f, lo, hi, l16, out, reached_b);
         r = r_next;
@@ -1148,7 +1150,7 @@ __device__ __forceinline__ int64_t grab_work(unsigned long long *counter, int la
 
 // The work of a hop: n_tiles tiles of long rows (done first, so the longest-running work starts first) and the groups
 // of 64 consecutive frontier nodes.
-// SHORT_INLINE: each group's rows of up to SHORT_ROW IDs are sampled four at a time before its other rows (an
+// Fan-outs above 64.  SHORT_INLINE: each group's rows of up to SHORT_ROW IDs are copied four at a time before its other rows (an
 // instantiation of its own: the code costs the streaming loop a few registers).
 template <int CAP, int MARK, bool SHORT_INLINE>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CAP <= 256 ? 7 : 1))) sample_kernel(HopArgs a)
@@ -1222,7 +1224,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CAP <= 
                 __syncthreads();
                 if (mine) short_recs[at] = ShortRec{rb_lane, out_lane, (uint64_t)S_lane, deg_lane, b_lane, lane};
                 __syncthreads();
-                sample_short_rows<MARK>(short_recs, count, a.indices, f, a.samp_nbr, a.reached, lane);
+                sample_short_rows<MARK, true>(short_recs, count, a.indices, f, a.samp_nbr, a.reached, lane);
             }
         }
         unsigned long long todo = ballot64(deg_lane > a.min_deg && deg_lane <= BIG_ROW);
@@ -1275,8 +1277,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CAP <= 
 // Per block of 256 IDs, everything a row costs included (233,000 nodes, rows of 13 blocks, fan-outs 25, 10): 57 vector and 59 scalar
 // instructions before, 49 and 36 so; the launches 3.65 -> 3.1 ms (2.45 M nodes: 15, 10, 5 9.6 -> 7.7, 50, 50 2.09 -> 1.6).
 //
-// A row's IDs are streamed once against a guessed cut (a key and its compare are nine vector
-// instructions per ID), what passes, a few dozen IDs, is listed in LDS in row order, and the f smallest keys of the list are
+// A row's IDs are streamed once against a guessed cut (a key and its compare are eight vector
+// instructions per ID, see key32_open_of_row), what passes, a few dozen IDs, is listed in LDS in row order, and the f smallest keys of the list are
 // the sample.  If fewer than f IDs pass, or more than fit, the row is streamed again with another cut (retry_row).
 //
 // A row is read in blocks of 256 IDs, 16 bytes per lane.  Rows above MID_ROW IDs are read from the last 128-byte boundary in
@@ -1617,7 +1619,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) sa
                 wave_lds_order();
                 if (mine) short_recs[at] = ShortRec{rb_lane, out_lane, S_lane, deg_lane, b_lane, lane};
                 wave_lds_order();
-                sample_short_rows<MARK>(short_recs, count, a.indices, f, a.samp_nbr, a.reached, lane);
+                sample_short_rows<MARK, false>(short_recs, count, a.indices, f, a.samp_nbr, a.reached, lane);
             }
         }
         unsigned long long todo = ballot64(deg_lane > MID_ROW && (is_tile || deg_lane <= BIG_ROW));      // rows that the whole wave streams
@@ -2373,8 +2375,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     }
 
     if (fanout > 0 && n_cur > 0) {
-        // Rows of up to SHORT_ROW IDs are sampled four at a time wherever a frontier has any (in a kernel of their own instead:
-        // 2.45 M nodes, fan-outs 15,10,5 10.2 ms against 9.6, fan-outs 50,50 2.20 against 2.10).  Same samples either way;
+        // Rows of up to SHORT_ROW IDs are taken four at a time wherever a frontier has any.  Same samples either way; at fan-outs above 64
         // RAPIDGNN_SHORT_ROWS = 0 forces one row per wave.
         bool short_rows = sums[2] != 0;
         if (const char *force = getenv("RAPIDGNN_SHORT_ROWS")) short_rows = force[0] != '0';
