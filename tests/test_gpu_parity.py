@@ -554,24 +554,44 @@ def test_few_listed_nodes_plan_without_the_route_table(case, rg, orc):
         assert st == orc.batch_stats(o, b, w.is_local.numpy(), slot)
 
 
-def test_rows_that_overflow_the_candidate_buffer_under_the_guessed_cut(rg, orc):
-    """Under the guessed cut a long row is expected to yield a few dozen candidates.  Rows built from IDs whose keys
-    (under the node's own state) lie below that cut by the hundred overflow the candidate buffer instead: at the very
-    first block, in the middle of the row, in its last blocks only, and by accumulation one past the buffer's size,
-    so the fast block loop is left at each of its three steps and the general path prunes and goes on."""
-    n, f, deg = 200000, 10, 1200
+def keys_of(orc, state, n):
+    """key32 of every ID below n under a node's state, as the oracle has it (spot-checked)."""
+    x = np.arange(n, dtype=np.uint32) ^ np.uint32(state & 0xFFFFFFFF)
+    x = x * np.uint32(0x9E3779B9)
+    x ^= x >> np.uint32(16)
+    x = (x + np.uint32(state >> 32)) * np.uint32(0x6A09E667)
+    x ^= x >> np.uint32(15)
+    x = x * np.uint32(0xBB67AE85)
+    x ^= x >> np.uint32(16)
+    for u in (0, 1, n // 3, n - 1):
+        assert int(x[u]) == orc.key32(state, u)
+    return x.astype(np.uint64)
+
+
+def guessed_cut(f, deg):
+    """The cut that a row of `deg` IDs (no more than 16,384) is first streamed against: f + 3 sqrt(f) + 3 of its keys lie below on average."""
+    lam = np.float32(f) + np.float32(3) * np.sqrt(np.float32(f)) + np.float32(3)
+    return int(lam / np.float32(deg) * np.float32(4294967296.0)) | 0xFFFF
+
+
+@pytest.mark.parametrize("f,room", [(10, 192), (64, 192), (70, 256), (190, 256)])
+def test_rows_that_overflow_the_candidate_buffer_under_the_guessed_cut(rg, orc, f, room):
+    """Under the guessed cut a long row is expected to yield few more candidates than the fan-out.  Rows built from IDs whose
+    keys (under the node's own state) lie below that cut by the hundred overflow the candidates' room instead: at the very
+    first block, in the middle of the row, in its last blocks only, and by accumulation up to the room's size and one past it.
+    At fan-outs up to 64 such a row is streamed again with a lower cut; above, the block loop is left at each of its three
+    steps and the general path prunes and goes on."""
+    n, deg = 200000, 1200
     s0, wk, ep = 5, 0, 1
     hs = orc.hop_state(orc.batch_seed(s0, wk, ep, 0), 0)
-    lam = f + 4.0 * np.sqrt(np.float32(f)) + 8.0
-    cut = int(np.float32(lam) / np.float32(deg) * np.float32(4294967296.0))
+    cut = guessed_cut(f, deg)
     # (seed, number of low keys, ID range the low-key IDs come from)
-    plans = [(17, deg, (0, n)), (1234, 200, (150000, n)), (50001, 300, (80000, 120000)), (77777, 129, (0, n)), (99999, 128, (0, n)),
-             (31, 600, (0, 60000))]
+    plans = [(17, deg, (0, n)), (1234, room + 72, (150000, n)), (50001, room + 100, (80000, 120000)), (77777, room + 1, (0, n)), (99999, room, (0, n)),
+             (31, room + 250, (0, 60000)), (40404, 129, (0, n)), (60606, 128, (0, n))]
     rng = np.random.default_rng(5)
     rows = [np.unique(rng.integers(0, n, 4)).astype(np.int32) for _ in range(n)]
     for v, n_low, (a, b) in plans:
-        S = orc.node_state(hs, v)
-        keys = np.array([orc.key32(S, u) for u in range(n)], dtype=np.uint64)
+        keys = keys_of(orc, orc.node_state(hs, v), n)
         cand = np.arange(n)
         cand = cand[cand != v]
         low = cand[(keys[cand] < cut // 2) & (cand >= a) & (cand < b)]
@@ -589,29 +609,28 @@ def test_rows_that_overflow_the_candidate_buffer_under_the_guessed_cut(rg, orc):
     g = rg.rg_build_schedule(dp, dx, dt, 100, [f], s0, wk, ep)
     o = orc.Schedule(indptr, indices, train, 100, [f], s0, wk, ep)
     assert_schedules_equal(rg, g, o)
-    # the rows are what they were built to be: far more keys below the guessed cut than the buffer holds
+    # the rows are what they were built to be: as many keys below the guessed cut as planned
     for v, n_low, _ in plans:
         S = orc.node_state(hs, v)
         assert sum(orc.key32(S, int(u)) <= cut for u in rows[v]) == n_low
 
 
-@pytest.mark.parametrize("deg", [1500, 200])
-def test_rows_built_to_defeat_the_guessed_cut(rg, orc, deg):
-    """Long rows (and rows of 65-256 IDs, which are held in registers) are first taken with a cut guessed from the
+@pytest.mark.parametrize("deg,f", [(1500, 10), (200, 10), (1500, 64), (200, 64), (1500, 70), (200, 70), (1500, 190)])
+def test_rows_built_to_defeat_the_guessed_cut(rg, orc, deg, f):
+    """Rows above 256 IDs, and at fan-outs up to 64 those of 65-256 too, are first taken with a cut guessed from the
     key distribution.  Rows made of IDs whose keys (under the node's own state) all lie above that cut, or with exactly
-    f - 1, f and f + 1 keys below it, force the fallback to the exact procedure and both sides of its trigger."""
-    n, f = 20000, 10
+    f - 1, f and f + 1 keys below it, force a second pass over the row (against another cut; at fan-outs above 64 by the
+    exact procedure) and both sides of its trigger."""
+    n = 20000
     s0, wk, ep = 21, 0, 3
     specials = [11, 222, 3333, 4444, 5555]               # seeds, all in batch 0 (one batch)
-    below = [0, f - 1, f, f + 1, 100]                    # keys below the guessed cut in each special row (100: more than a wave holds)
+    below = [0, f - 1, f, f + 1, max(100, f + 60)]       # keys below the guessed cut in each special row (the last: more than a wave holds)
     hs = orc.hop_state(orc.batch_seed(s0, wk, ep, 0), 0)
-    lam = f + 4.0 * np.sqrt(np.float32(f)) + 8.0
-    cut = int(np.float32(lam) / np.float32(deg) * np.float32(4294967296.0))
+    cut = guessed_cut(f, deg)
     rng = np.random.default_rng(77)
     rows = [np.unique(rng.integers(0, n, 6)).astype(np.int32) for _ in range(n)]
     for v, nb in zip(specials, below):
-        S = orc.node_state(hs, v)
-        keys = np.array([orc.key32(S, u) for u in range(n)], dtype=np.uint64)
+        keys = keys_of(orc, orc.node_state(hs, v), n)
         cand = np.arange(n)
         cand = cand[cand != v]
         lo_ids = cand[keys[cand] < cut // 2]             # safely below the cut

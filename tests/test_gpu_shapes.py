@@ -56,16 +56,18 @@ SHAPES = [
     (900, [(64, 64, 1), (65, 65, 1), (256, 256, 1), (257, 257, 1), (63, 63, 1), (255, 255, 1)], (9, 7), 33, 400),   # the class boundaries
     (3000, [(1, 16, 2), (17, 32, 2), (33, 48, 2), (49, 64, 2), (0, 0, 1)], (15, 40, 64), 97, 1500),                 # short rows only: every count of IDs per lane, fan-outs around them
     (1500, [(15, 17, 1), (31, 33, 1), (47, 49, 1), (63, 65, 1)], (16, 1, 63), 64, 1500),                            # the sixteen-lane boundaries
+    (3000, [(0, 0, 1), (1, 8, 2), (9, 16, 2), (17, 32, 2), (33, 48, 2), (49, 64, 2), (65, 300, 1)], (100, 65), 97, 1400),   # short rows at fan-outs above 64
 ]
+FORMS = [("keys", "auto"), ("keys", "marked_by_the_pass"), ("keys", "marked_as_sampled"), ("keys", "one_row_per_wave"),
+         ("positions", "marked_by_the_pass"), ("positions", "marked_as_sampled")]
 
 
-@pytest.mark.parametrize("shape", range(len(SHAPES)))
-@pytest.mark.parametrize("sampler,form", [("keys", "auto"), ("keys", "marked_by_the_pass"), ("keys", "marked_as_sampled"), ("keys", "one_row_per_wave"),
-                                          ("positions", "marked_by_the_pass"), ("positions", "marked_as_sampled")])
+# one row per wave: the short rows of a hop with a fan-out above 64 (at smaller ones they always go four at a time)
+@pytest.mark.parametrize("shape,sampler,form", [(k, s, f) for s, f in FORMS for k in range(len(SHAPES)) if f != "one_row_per_wave" or max(SHAPES[k][2]) > 64])
 def test_random_shape(rg, orc, shape, sampler, form, monkeypatch):
     if form.startswith("marked"):                        # how the reached-ID maps are written, forced (chosen per hop otherwise)
         monkeypatch.setenv("RAPIDGNN_MARK_PASS", "1" if form == "marked_by_the_pass" else "0")
-    if form == "one_row_per_wave":                       # without sampling four short rows at a time
+    if form == "one_row_per_wave":                       # without copying four short rows at a time
         monkeypatch.setenv("RAPIDGNN_SHORT_ROWS", "0")
     n, classes, fanout, batch, n_train = SHAPES[shape]
     rng = np.random.default_rng(4000 + shape)
