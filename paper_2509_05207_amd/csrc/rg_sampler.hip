@@ -1950,9 +1950,9 @@ __global__ void __launch_bounds__(HUB_THREADS) hub_sample_kernel(HubArgs a)
 
 // From which length on a row is sampled from the keys' side: twice the length at which its key values cost what its IDs
 // would.  A value costs about 1.6 times what an ID does (twice the arithmetic, no read), and the share of values that are
-// IDs one more scattered read each.  At the even length nothing is won and a few jobs do not fill the chip: 15 M nodes,
-// 176 batches, sampled from 520,000 IDs on (the even length) 770 us for the schedule, 699 without.  On the
-// graph above (even length 450,000), sampling altogether: from 350,000 2.2 ms, 450,000 2.09, 600,000 2.12, 800,000 2.20, none 4.5.
+// IDs one more scattered read each.  Near the even length nothing is won and a few jobs do not fill the chip.  Schedules by where the line
+// lies, in even lengths, 0.75 / 1 / 1.4 / 2 / 2.8 / no hub rows: 111 M nodes, 147 batches 3,171 / 2,749 / 2,775 / 2,828 / 2,919 / 3,516 us, 60 M
+// 2,316 / 2,199 / 2,178 / 2,196 / 2,248 / 2,359, 30 M 1,933 / 1,854 / 1,865 / 1,839 / 1,859 / 1,831, 15 M, 177 batches 1,340 / 1,119 / 1,114 / 971 / 974 / 945.
 static double hub_line(int64_t n_nodes, uint32_t fanout)
 {
     const double f = (double)fanout, lambda = f + 3.0 * std::sqrt(f) + 3.0;
@@ -1961,9 +1961,9 @@ static double hub_line(int64_t n_nodes, uint32_t fanout)
 }
 
 // How many tile jobs the hub rows must make, per compute unit, to be worth their tables: clearing and building those and a
-// wait for the rows' order cost 70 to 130 us (2 to 28 M distinct IDs), a tile job 17 ns.  Shares of 15 to 100 M nodes,
-// schedule with hub jobs against without: 387 to 3,480 tiles 31 to 129 us slower, 4,215 14 faster, 5,600 87, 6,525 40,
-// 7,654 67, 10,578 96, 21,835 289, 68,334 1,040.
+// wait for the rows' order cost 70 to 130 us (2 to 28 M distinct IDs), a tile job 17 ns.  Schedules with hub jobs / with tile jobs / by
+// this line: 111 M nodes, 147 batches 2,828 / 3,516 / 2,812 us, 20 batches of 512 585 / 626 / 580, 40 of 1,024 1,022 / 993 / 1,000; 60 M, 147 2,196 / 2,359 / 2,176,
+// 30 of 2,048 865 / 856 / 860; 30 M 1,839 / 1,831 / 1,831; 15 M, 176 of 163 614 / 598 / 604.
 constexpr int HUB_TILES_PER_CU = 24;
 // Epochs of fewer batches seldom hold so many (the 100 M nodes, 15 batches of 2,048 seeds: 6,525), and looking for them costs
 // some 10 us a hop.
@@ -2167,14 +2167,14 @@ static uint32_t mark_piece_words(const ReachedMaps &m, uint32_t pieces) { return
 // By a pass or by the sampling kernels themselves.  The pass clears and looks through the words of every batch's bitmap, some
 // 6 us per 128 KB of LDS and compute unit, and 8 us for itself, more where a few workgroups have all the samples; an atomic OR
 // costs 25 to 40 ps where little hides it, next to nothing while rows are read, and more where many meet on a word.  So the pass
-//  - from one sample per MARK_SPARSE IDs of bitmap on: 2.45 M nodes, one hop, fan-out 30, marked by the kernels / by the
-//    pass: keys sampler one per 2,848 445 / 525 us, 1,424 1,076 / 1,094, 712 810 / 787, 356 587 / 539 (positions sampler
-//    958 / 1,077, 702 / 778, 498 / 541; two hops, one per 148 in the second, 997 / 920);
-//  - there, from MARK_MANY samples on, or MARK_CROWD per word (sampling of one batch, fan-outs 50,50, 2.45 M nodes, 512 seeds
-//    (1 M samples in the second hop) 185 / 230 us, 4,096 seeds 407 / 344, 15,000 seeds 934 / 583; 30,000 nodes, 4,096 seeds
-//    154 / 106; ten batches on 40,000 nodes, 1.2 M samples, 91 per word, 287 / 280);
+// (schedules, marked by the kernels / by the pass)
+//  - from one sample per MARK_SPARSE IDs of bitmap on: 2.45 M nodes, one hop, 1.6 M samples, keys sampler one per 2,816 685 / 758 us, 1,432
+//    616 / 604, 710 449 / 426, 355 347 / 319; positions sampler, whose scattered reads leave marks more to hide behind, 710 417 / 450, 355 318 / 337, 177 282 / 297;
+//  - there, from MARK_MANY samples on, or MARK_CROWD per word (one batch, fan-outs 50, 50, 2.45 M nodes, 0.5 M samples in the second hop
+//    289 / 310, 1.0 M 321 / 317, 1.8 M 387 / 348, 3.3 M 508 / 393, 9.8 M 1,067 / 531; 30,000 nodes, one batch, 237 per word 329 / 263; ten batches on
+//    40,000 nodes, 15 per word 243 / 247, 26 267 / 268, 46 300 / 297, 77 328 / 317);
 //  - and where its workgroups are a quarter of the compute units and more, from as many samples on as cost what it does: MARK_PASS
-//    and MARK_ROUND per round of full workgroups (113 batches on 76,000 nodes, 115,000 and 1 M samples, 393 / 384 us).
+//    and MARK_ROUND per round of full workgroups (113 batches on 76,000 nodes, 0.5 M samples 324 / 324, 1.0 M 372 / 369, 1.8 M 422 / 418, 3.3 M 495 / 479).
 static bool marks_want_a_pass(const ReachedMaps &m, uint32_t beta, uint64_t n_marks, int n_cu)
 {
     const uint64_t words = m.words_per_batch * (uint64_t)beta;
