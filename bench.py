@@ -312,6 +312,10 @@ def device_copy_gbps(n_bytes=1 << 30, reps=5):
     return 2.0 * n_bytes * reps / (e0.elapsed_time(e1) * 1e-3) / 1e9
 
 
+# the kernels that the two rates are named after; their counted traffic is stored under "<workload>:<kernel>"
+SAMPLER_KERNEL, GATHER_KERNEL = "sample_rows_kernel", "gather_rows_kernel"
+
+
 def stored_traffic(workload, kernel):
     """HBM bytes per step of `kernel` on `workload` as counted by separate rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of
     this script (profiles/measured_traffic.json; the profiles/*_traffic.md files give the commands and the calibration).
@@ -409,11 +413,11 @@ def measure(rg, name, args, full):
                                f"see pcie_inclusive), {G} batch(es) per gather launch",
                    "n_batches": n_batches, "sampled_edges_per_epoch": sampled_edges, "gathered_rows_per_epoch": rows_per_epoch,
                    "K_eff": int(k_eff)},
-        "sampler": {"kernel": "sample_rows_kernel", "edges_per_s_kernel": sampled_edges / (samp_ms * 1e-3) if samp_ms else None, "GBps": samp_gbps,
+        "sampler": {"kernel": SAMPLER_KERNEL, "edges_per_s_kernel": sampled_edges / (samp_ms * 1e-3) if samp_ms else None, "GBps": samp_gbps,
                     "frac_hbm": samp_frac, "ms_per_step": samp_ms, "launches_per_step": samp_launches,
                     "algorithmic_bytes_per_step": samp_bytes, "row_entries_of_frontiers": sum(h["sum_deg"] for h in hops),
                     "row_entries_of_distinct_nodes": sum(h["distinct"] for h in hops)},
-        "gather": {"kernel": "gather_rows_kernel", "GBps": gath_gbps, "frac_hbm": gath_frac, "ms_per_step": gath_ms,
+        "gather": {"kernel": GATHER_KERNEL, "GBps": gath_gbps, "frac_hbm": gath_frac, "ms_per_step": gath_ms,
                    "launches_per_step": gath_launches, "algorithmic_bytes_per_step": gath_bytes,
                    "delivered_GBps": rows_per_epoch * W.row_bytes / (gath_ms * 1e-3) / 1e9 if gath_ms else None},
         "kernel_ms_per_step": {k: v["ms"] / steps for k, v in prof.items()},
@@ -437,6 +441,9 @@ def measure(rg, name, args, full):
                 traffic=None, launches_per_step=launches, avg_launch_ms=g["ms_per_step"] / launches,
                 algorithmic_bytes_per_launch=g["algorithmic_bytes_per_step"] / launches,
                 algorithmic_bytes_per_step=g["algorithmic_bytes_per_step"], dominant_group_by_time=dominant)
+    roof["frac_of"] = "algorithmic bytes"
+    if "traffic_per_step" not in g:
+        roof["traffic_source"] = f"none stored for {g['kernel']} on {cfg.name}"
     if "traffic_per_step" in g:
         roof["traffic"] = g["traffic_per_step"] / launches                      # per launch, like `achieved`
         roof["traffic_per_step"] = g["traffic_per_step"]
@@ -451,6 +458,7 @@ def measure(rg, name, args, full):
         roof["algorithmic_GBps"], roof["algorithmic_frac"] = g["GBps"], g["frac_hbm"]
         if "traffic_per_step" in g:
             roof["achieved"], roof["frac"] = group_rate(g["ms_per_step"], g["traffic_per_step"])
+            roof["frac_of"] = "bytes that moved"
     copy_gbps = device_copy_gbps()
     roof["device_copy_GBps"] = copy_gbps                       # a 1 GiB device-to-device copy on this machine, read + write
     roof["algorithmic_GBps_over_device_copy"] = g["GBps"] / copy_gbps

@@ -3,6 +3,8 @@ import os
 import subprocess
 import sys
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -24,3 +26,14 @@ def test_measured_traffic_table_is_well_formed():
         assert rec["hbm_bytes_per_step"] > 0
         assert abs(rec["fetch_bytes_per_step"] + rec["write_bytes_per_step"] - rec["hbm_bytes_per_step"]) <= 0.01 * rec["hbm_bytes_per_step"]
         assert os.path.exists(os.path.join(ROOT, rec["source"]))
+
+
+@pytest.mark.parametrize("workload", ["medium", "large_sparse", "fanout_stress", "partition_share"])
+def test_traffic_is_stored_for_the_kernels_that_the_benchmark_names(workload):
+    sys.path.insert(0, ROOT)
+    import bench
+    for kernel in (bench.SAMPLER_KERNEL, bench.GATHER_KERNEL):
+        rec = bench.stored_traffic(workload, kernel)
+        assert rec and rec["hbm_bytes_per_step"] > 0, kernel
+        with open(os.path.join(ROOT, rec["source"])) as fh:
+            assert f"rg::{kernel}<" in fh.read()                      # the table that it comes from is of that kernel
