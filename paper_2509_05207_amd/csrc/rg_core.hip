@@ -610,7 +610,7 @@ rg_status scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, Arena &tmp
 // streaming passes together 0.1 (0.5 GB).
 // The starts of the rows are scattered reads of lines that the flat pass reads too, so a wave of that pass looks at those among
 // the IDs it has just read (found in indptr, which is known to ascend by then), while they are in a cache: 2.45 M rows,
-// 122 M edges, starts with the pass over indptr 43 + 90 us, so 6 + 110.  (Per 64 KB and workgroup, behind a barrier: 6 + 129.)
+// 122 M edges, starts with the pass over indptr 43 + 90 us, so 9 + 107.  (Per 64 KB and workgroup, behind a barrier: 6 + 129.)
 // Many rows to few IDs take the wave many turns, and small graphs feel its search for its first row: there the starts stay with
 // the pass over indptr (starts there / behind the IDs: 50 M nodes, 2 IDs each 238 / 292 us, 7 in one of 100 134 / 534; 8,000 nodes, 8 each 32.8 / 34.6).
 // So do, in any graph, those of 64 consecutive rows (from a multiple of 64 on) with few IDs together: however the rows are spread, a wave has

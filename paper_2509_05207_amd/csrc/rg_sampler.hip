@@ -43,7 +43,8 @@
 //    row's sample: the f smallest keys of the row are among the f smallest of
 //    each tile.  This bounds the work of one wave whatever the degree skew.
 //    Tiles are dealt out by workgroup index and done before the groups of
-//    nodes, which the waves then take from a counter as they become free.
+//    nodes, which the waves then take from a counter as they become free (small
+//    frontiers at fan-outs up to 64: by index too).
 //  - the very longest rows, where a hop holds many of them, are not read but
 //    sampled from the keys' side (hub_sample_kernel).
 //
@@ -2066,8 +2067,8 @@ __global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int
 // Bound by reading the samples once per piece of the bitmap.  A workgroup puts MARK_WORDS words of one batch's bitmap
 // together in LDS from all of the batch's samples, or a part of them, and writes them and the flags of the groups that
 // hold bits: nothing scattered leaves the compute unit.  Marked one by one from the sampling kernels, the memory system takes 25 G
-// atomic ORs or 88 G byte stores a second and the kernels carry the address arithmetic.  233 k nodes, 29 M samples: 0.05 ms; 2.45 M nodes, 167 M samples:
-// 0.43, and the launches that marked bytes themselves 3.9 -> 2.2 ms; 146 M samples in three hops: 0.32, launches that marked
+// atomic ORs or 88 G byte stores a second and the kernels carry the address arithmetic.  233 k nodes, 29 M samples: 0.04 ms; 2.45 M nodes, 167 M samples:
+// 0.30, and the launches that marked bytes themselves 3.9 -> 2.2 ms; 146 M samples in three hops: 0.20, launches that marked
 // bits 10.6 -> 9.6.  A lane reads four IDs at a time: one at a time, twice as many loads of a quarter the size in flight, 424 us instead of 327 and 328 instead of 293.
 // The pieces of a batch run on one XCD (workgroup g runs on XCD g mod 8) at about the same time and share the reads; the
 // batches left over from whole eights are dealt out over all XCDs, or one batch would have an eighth of the chip.
