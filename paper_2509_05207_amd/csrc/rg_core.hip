@@ -614,18 +614,22 @@ rg_status scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, Arena &tmp
 // Many rows to few IDs take the wave many turns, and small graphs feel its search for its first row: there the starts stay with
 // the pass over indptr (starts there / behind the IDs: 50 M nodes, 2 IDs each 238 / 292 us, 7 in one of 100 134 / 534; 8,000 nodes, 8 each 32.8 / 34.6).
 // So do, in any graph, those of 64 consecutive rows (from a multiple of 64 on) with few IDs together: however the rows are spread, a wave has
-// no more than one block of 64 to look at for every 1,024 IDs it reads, and few steps between two of them.
+// no more than three blocks of 64 to look at for every 1,024 IDs it reads, and few steps between two of them.  Where the line lies (all starts with the
+// pass over indptr / behind the IDs / blocks from 256, 384, 512, 1,024 IDs on behind the IDs): a few rows with most IDs and the others with some 5 to 20, 2.4 M nodes,
+// 45 M IDs 83 / 79 / 78, 80, 88, 96 us, 70 M 104 / 98 / 97, 98, 98, 112; 2.45 M rows sorted by length 157 / 156 / 168, 160, 156, 152; 7 M nodes, 100
+// rows of 1.2 M IDs, then one ID in each 148 / 302 / 156 at any, in every 64th 143 / 10,070 / 146 at any.
 constexpr int VAL_THREADS = 256;
 constexpr int VAL_SLOTS = 16;                  // each count is kept in this many copies, summed by the host (adds to one address queue up)
 constexpr int64_t VAL_ROW_IDS = 16;            // IDs per row, on average, from which on a wave looks at the starts among its IDs ...
-constexpr int64_t VAL_MANY_IDS = 1 << 24;      // ... where there are so many
+constexpr int64_t VAL_MANY_IDS = 1 << 24;      // ... where there are so many,
+constexpr int64_t VAL_BLOCK_IDS = 384;         // in blocks of 64 rows that hold so many
 __device__ __forceinline__ bool starts_with_the_ids(int64_t n_nodes, int64_t n) { return n >= VAL_ROW_IDS * n_nodes && n >= VAL_MANY_IDS; }
 __device__ __forceinline__ int64_t from_lane(int64_t x, int lane)      // (lane the same in the whole wave)
 {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), lane);
     return (int64_t)((uint64_t)hi << 32 | lo);
 }
-__device__ __forceinline__ bool long_block(int64_t start, int64_t end) { return end - start >= VAL_ROW_IDS * 64; }
+__device__ __forceinline__ bool long_block(int64_t start, int64_t end) { return end - start >= VAL_BLOCK_IDS; }
 enum { VAL_ROWS = 0, VAL_FLAT = 1, VAL_STARTS = 2, VAL_GENERAL = 3, VAL_COUNTS = 4 };
 
 __device__ __forceinline__ void add_block_count(unsigned long long x, unsigned long long *counts, int which)

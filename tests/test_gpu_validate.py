@@ -88,7 +88,7 @@ def test_violations_over_many_waves(rg, edges, rows):
     assert rg.rg_graph_validate(torch.from_numpy(indptr).cuda(), pad[3:]) == int(bad.sum())
 
 
-@pytest.mark.parametrize("light", ["one each", "one in 64", "one in 64, elsewhere", "none", "sixteen each", "every third block", "mixed"])
+@pytest.mark.parametrize("light", ["one each", "one in 64", "one in 64, elsewhere", "none", "six each", "sixteen each", "every third block", "mixed"])
 @pytest.mark.parametrize("heavy_first", [True, False])
 def test_violations_where_few_rows_hold_most_ids(rg, light, heavy_first):
     """Graphs whose rows hold 16 IDs and more on average, most of them in a few rows: blocks of 64 rows with few IDs together, in runs of
@@ -99,9 +99,10 @@ def test_violations_where_few_rows_hold_most_ids(rg, light, heavy_first):
            "one in 64": lambda: (np.arange(rows) % 64 == 0).astype(np.int64),
            "one in 64, elsewhere": lambda: (np.arange(rows) % 64 == 37).astype(np.int64) * rng.integers(1, 40, size=rows),
            "none": lambda: np.zeros(rows, np.int64),
-           "sixteen each": lambda: np.full(rows, 16) - (rng.random(rows) < 0.004),              # blocks of 1,024 IDs and of fewer
+           "six each": lambda: np.full(rows, 6) - (rng.random(rows) < 0.008),                   # blocks of 384 IDs and of fewer
+           "sixteen each": lambda: np.full(rows, 16),
            "every third block": lambda: np.where(np.arange(rows) // 64 % 3 == 0, 60, 1),
-           "mixed": lambda: np.repeat(rng.choice([0, 1, 15, 16, 17, 200], size=rows // 500), 500)}[light]()
+           "mixed": lambda: np.repeat(rng.choice([0, 1, 5, 6, 7, 16, 200], size=rows // 500), 500)}[light]()
     big = np.full(heavy, 800_001)
     deg = np.concatenate([big, deg] if heavy_first else [deg[: rows // 2], big[::2], deg[rows // 2:], big[1::2]])
     indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
