@@ -2156,12 +2156,13 @@ __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *
 
 // Every piece reads all samples of its batch, so the pieces are as few as LDS allows, of equal size; one more where that
 // costs no further round of workgroups, since a workgroup then has fewer bits to set (2.45 M nodes in two pieces / three: 147 batches of
-// 1.1 M samples in 294 or 441 workgroups on 256 compute units 345 / 327 us, 196 batches of 0.7 M in 392 or 588 233 / 293).
+// 1.1 M samples in 294 or 441 workgroups on 256 compute units 345 / 327 us, 196 batches of 0.7 M in 392 or 588 233 / 293).  So are those of a bitmap of
+// more than MARK_FULL words that would fit one piece (1.1 M nodes, 75 batches of 0.6 M samples in one piece, two parts / in two pieces 160 / 72 us).
 static uint32_t mark_pieces(const ReachedMaps &m, uint32_t beta, int n_cu)
 {
     const uint64_t least = (m.words_per_batch + MARK_WORDS - 1) / MARK_WORDS, cus = (uint64_t)n_cu;
     const auto rounds = [&](uint64_t pieces) { return (pieces * beta + cus - 1) / cus; };
-    return (uint32_t)(least > 1 && rounds(least + 1) == rounds(least) ? least + 1 : least);
+    return (uint32_t)(m.words_per_batch > MARK_FULL && rounds(least + 1) == rounds(least) ? least + 1 : least);
 }
 static uint32_t mark_piece_words(const ReachedMaps &m, uint32_t pieces) { return (uint32_t)(((m.words_per_batch + pieces - 1) / pieces + 7) / 8 * 8); }
 

@@ -38,11 +38,11 @@ def test_new_ids_of_every_density(rg, orc, n, share, mark_pass, monkeypatch):
         assert np.array_equal(goff, off) and np.array_equal(gids.cpu().numpy(), ids), hop
 
 
-@pytest.mark.parametrize("n", [1_048_575, 1_048_577, 2_200_000])
+@pytest.mark.parametrize("n", [1_048_575, 1_048_577, 1_228_800, 1_228_801, 2_200_000])
 @pytest.mark.parametrize("n_train,batch", [(40_000, 40_000), (41_000, 20_480), (300, 20), (360, 20), (180, 20)])
 @pytest.mark.parametrize("mark_pass", ["1", "0"])
 def test_marks_in_pieces_and_parts(rg, orc, n, n_train, batch, mark_pass, monkeypatch):
-    """Bitmaps of one to three pieces of 1,048,576 IDs; batches whose samples are marked in several parts, and in one; one,
+    """Bitmaps on both sides of the 1,048,576 IDs from which on they go in two pieces and of the 1,228,800 that fit one, and of three pieces; batches whose samples are marked in several parts, and in one; one,
     two, fifteen, eighteen and nine batches, of which the pass sends whole eights to an XCD each."""
     monkeypatch.setenv("RAPIDGNN_MARK_PASS", mark_pass)
     rng = np.random.default_rng(n + n_train)
