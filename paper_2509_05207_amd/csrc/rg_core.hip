@@ -748,9 +748,9 @@ __global__ void __launch_bounds__(VAL_THREADS) validate_flat(int64_t n_nodes, co
     const int4 *vec = reinterpret_cast<const int4 *>(indices + head);
     const int lane = threadIdx.x & 63;
     const int64_t n_waves = (int64_t)gridDim.x * (VAL_THREADS / 64), wave = (int64_t)blockIdx.x * (VAL_THREADS / 64) + (threadIdx.x >> 6);
-    const int64_t part = ((n_vec + n_waves - 1) / n_waves + VAL_ROUND - 1) / VAL_ROUND * VAL_ROUND;
     const bool look_at_starts = starts_with_the_ids(n_nodes, n);
-    const int64_t i_first = wave * (look_at_starts ? part : VAL_ROUND), i_step = look_at_starts ? VAL_ROUND : n_waves * VAL_ROUND;
+    const int64_t part = look_at_starts ? ((n_vec + n_waves - 1) / n_waves + VAL_ROUND - 1) / VAL_ROUND * VAL_ROUND : VAL_ROUND;      // (a division in 64 bits is a microsecond of a small check)
+    const int64_t i_first = wave * part, i_step = look_at_starts ? VAL_ROUND : n_waves * VAL_ROUND;
     const int64_t i_end = look_at_starts ? min((wave + 1) * part, n_vec) : n_vec;
     const int64_t part_end = (wave + 1) * part >= n_vec ? n : head + 4 * (wave + 1) * part;
     int64_t block = 0, start = 0;                // the next block of 64 rows, and where it starts
