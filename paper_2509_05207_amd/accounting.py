@@ -19,8 +19,8 @@ def batches_per_epoch(n_train: int, batch_size: int) -> int:
 
 def gather_traffic_bytes(n_rows: int, row_bytes: int) -> int:
     """Algorithmic bytes of one feature-block gather: every row read once and
-    written once, one 4-byte node ID and one 8-byte routing entry per row."""
-    return n_rows * (2 * row_bytes + 4 + 8)
+    written once, one 4-byte node ID and one 4-byte routing code per row."""
+    return n_rows * (2 * row_bytes + 4 + 4)
 
 
 def gather_group(n_batches: int, rows_per_epoch: int, stride_bytes: int) -> int:

@@ -4,6 +4,7 @@
 #include "rg_device.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rg {
 
@@ -365,9 +366,9 @@ template <bool ALIGNED8, typename F>
 __global__ void __launch_bounds__(TOPK_THREADS) select_emit_kernel(const F *__restrict__ freq, const uint8_t *__restrict__ is_local, int64_t n,
                                                                    const SelectState *__restrict__ stp, const uint64_t *__restrict__ block_base,
                                                                    const uint64_t *__restrict__ tile_base, int32_t *__restrict__ cache_ids, SlotRec *__restrict__ slot_pairs,
-                                                                   const int32_t *__restrict__ row_of, int64_t *__restrict__ fill_entries)
+                                                                   const int32_t *__restrict__ row_of, uint32_t *__restrict__ fill_codes)
 {
-    // fill_entries[slot]: where VectorPull finds the row of the node in that slot (a8), written here while the node is at hand
+    // fill_codes[slot]: where VectorPull finds the row of the node in that slot (a8), written here while the node is at hand
     __shared__ uint64_t lds[TOPK_THREADS / 64];
     __shared__ uint16_t lists[TOPK_THREADS / 64][64 * SEL_PER_THREAD];
     const SelectState st = *stp;
@@ -414,7 +415,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) select_emit_kernel(const F *__re
     for (int j = lane; j < n_listed; j += 64) {
         const int64_t v = wave_first + list[j];
         cache_ids[wave_slot0 + j] = (int32_t)v;
-        fill_entries[wave_slot0 + j] = make_entry(TAG_REMOTE, row_of[v]);
+        fill_codes[wave_slot0 + j] = make_code(false, false, (uint32_t)row_of[v]);
     }
     // the slot map's record for 32 node IDs (see slot_lookup): bits from four lanes, the rank from the first of them
     uint32_t word = mine << (8 * (lane & 3)), lword = local8 << (8 * (lane & 3));
@@ -443,7 +444,7 @@ __device__ __forceinline__ uint32_t batch_of_pos(const int64_t *__restrict__ off
     return lo;
 }
 
-// Where a request for v's feature row is served from: (tag << 62) | row.  One record of the slot map says whether v
+// Where a request for v's feature row is served from.  One record of the slot map says whether v
 // is local and whether (and where) it is cached; row_of is read for the others only, and not even for those where the
 // tables hold the nodes' rows in the order of their IDs: row_of is then a rank, which the record gives too.
 struct RouteSources {
@@ -479,7 +480,7 @@ __global__ void row_ranks_kernel(SlotRec *recs, int64_t n, const int64_t *__rest
     if (__ballot(differs) != 0ull && (threadIdx.x & 63) == 0) *not_ranks = 1u;
 }
 
-// entry[j] = where ids[j] is served from, for every listed input node, which of them are misses (one
+// route[j] = where ids[j] is served from, for every listed input node, which of them are misses (one
 // bit each, in position order: a wave's ballot is the 64-bit word of its 64 consecutive positions), how many misses each tile
 // of PLAN_TILE positions holds and how many local rows each PLAN_GROUP of them.  Nothing is added up per batch here: the tiles of a batch run at the
 // same time, and two adds per tile to the batch's counters queued up behind each other (an epoch of 80 M input nodes in
@@ -493,7 +494,10 @@ constexpr int PLAN_TILE_WORDS = PLAN_TILE / 64;          // bit words per tile
 constexpr int PLAN_GROUP = 2 * PLAN_THREADS;             // positions to a count of local rows
 constexpr int PLAN_TILE_GROUPS = PLAN_TILE / PLAN_GROUP;
 
-__global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__restrict__ ids, int64_t n, RouteSources rs, int64_t *__restrict__ entry,
+// A route is a code or, where codes have met a row they cannot hold (*no_codes = 1; see make_code), an entry.
+template <typename ROUTE>
+__global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__restrict__ ids, int64_t n, RouteSources rs, uint32_t last_remote, ROUTE *__restrict__ route,
+                                                            uint32_t *__restrict__ no_codes,
                                                             unsigned long long *__restrict__ miss_bits /* [tiles * PLAN_TILE_WORDS] */,
                                                             int32_t *__restrict__ tile_miss /* [tiles] */, uint16_t *__restrict__ group_local /* [tiles * PLAN_TILE_GROUPS] */)
 {
@@ -519,17 +523,22 @@ __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__res
         } else row[k] = rs.row_of[v[k]];
     }
     int n_local[PLAN_TILE_GROUPS] = {}, n_miss = 0;        // of the wave
+    bool no_code = false;
 #pragma unroll
     for (int k = 0; k < PLAN_PER_THREAD; ++k) {
         const int64_t j = tile0 + (int64_t)k * PLAN_THREADS + threadIdx.x;
         const uint32_t bit = 1u << (v[k] & 31);
         const bool local = (rec[k].z & bit) != 0, cached = !local && (rec[k].x & bit) != 0;
-        if (j < n) __builtin_nontemporal_store(make_entry(local ? TAG_LOCAL : cached ? TAG_CACHE : TAG_REMOTE, row[k]), entry + j);
+        if constexpr (sizeof(ROUTE) == 4) {
+            no_code |= !fits_code(local, cached, (uint32_t)row[k], last_remote);      // (past the end: the last ID's answer again)
+            if (j < n) __builtin_nontemporal_store(make_code(local, cached, (uint32_t)row[k]), route + j);
+        } else if (j < n) __builtin_nontemporal_store(make_entry(local ? TAG_LOCAL : cached ? TAG_CACHE : TAG_REMOTE, row[k]), route + j);
         const unsigned long long ml = __ballot(j < n && local), mm = __ballot(j < n && !local && !cached);
         if (lane == 0) miss_bits[(uint64_t)blockIdx.x * PLAN_TILE_WORDS + k * (PLAN_THREADS / 64) + wave] = mm;
         n_local[k / 2] += __popcll(ml);
         n_miss += __popcll(mm);
     }
+    if (__ballot(no_code) != 0ull && lane == 0) *no_codes = 1u;
     if (lane == 0) {
         red[0][wave] = n_miss;
 #pragma unroll
@@ -559,12 +568,15 @@ __device__ __forceinline__ int64_t lane_bits_between(const unsigned long long *_
 
 // One workgroup per batch (and one for the end).  miss_off[b] = misses in front of batch b's first position: those of the
 // tiles in front of its tile (tile_scan) and of the positions in front of it inside the tile; n_local[b] = its local
-// rows: those of the whole groups between its ends, and the entries in front of and behind them.  Bound by its dependent
+// rows: those of the whole groups between its ends, and the routes in front of and behind them.  Bound by its dependent
 // reads, of which there are two: the batch's ends, then everything else at once (a plan of 500,000 entries in 145 batches 5.2 us; with
 // whole tiles counted and the entries of the end tiles read, 10.0).
+__device__ __forceinline__ int is_local_route(int64_t e) { return entry_tag(e) == TAG_LOCAL ? 1 : 0; }
+__device__ __forceinline__ int is_local_route(uint32_t c) { return c < CODE_NOT_LOCAL ? 1 : 0; }
 constexpr int COUNT_THREADS = 256;
 constexpr int COUNT_IN_FLIGHT = PLAN_GROUP / COUNT_THREADS;
-__global__ void __launch_bounds__(COUNT_THREADS) batch_counts_kernel(const unsigned long long *__restrict__ miss_bits, const int64_t *__restrict__ entry,
+template <typename ROUTE>
+__global__ void __launch_bounds__(COUNT_THREADS) batch_counts_kernel(const unsigned long long *__restrict__ miss_bits, const ROUTE *__restrict__ route,
                                                                      const int64_t *__restrict__ tile_scan, const uint16_t *__restrict__ group_local, int64_t n, int64_t n_tiles,
                                                                      const int64_t *__restrict__ batch_off, uint32_t n_batches, int64_t *__restrict__ miss_off,
                                                                      int64_t *__restrict__ n_local)
@@ -575,18 +587,20 @@ __global__ void __launch_bounds__(COUNT_THREADS) batch_counts_kernel(const unsig
     const int64_t lo = batch_off[b], hi = batch_off[min(b + 1, n_batches)];      // (the end: no positions)
     const int64_t g_lo = (lo + PLAN_GROUP - 1) / PLAN_GROUP, g_hi = hi / PLAN_GROUP;      // whole groups [g_lo, g_hi), if any
     const int64_t front_end = g_lo <= g_hi ? g_lo * PLAN_GROUP : hi, back = g_lo <= g_hi ? g_hi * PLAN_GROUP : hi;
-    int64_t e[2 * COUNT_IN_FLIGHT], local = 0;
+    const ROUTE not_local = (ROUTE)~(ROUTE)0;                                             // (as an entry and as a code)
+    ROUTE e[2 * COUNT_IN_FLIGHT];
+    int64_t local = 0;
 #pragma unroll
     for (int k = 0; k < COUNT_IN_FLIGHT; ++k) {
         const int64_t j = lo + k * COUNT_THREADS + threadIdx.x, i = back + k * COUNT_THREADS + threadIdx.x;
-        e[2 * k] = j < front_end ? entry[j] : make_entry(TAG_REMOTE, 0);
-        e[2 * k + 1] = i < hi ? entry[i] : make_entry(TAG_REMOTE, 0);
+        e[2 * k] = j < front_end ? route[j] : not_local;
+        e[2 * k + 1] = i < hi ? route[i] : not_local;
     }
     for (int64_t g = g_lo + threadIdx.x; g < g_hi; g += COUNT_THREADS) local += group_local[g];
     int64_t before = lo < n && wave == 0 ? lane_bits_between(miss_bits, lo / PLAN_TILE * PLAN_TILE, lo, lane) : 0;
     const int64_t scan_here = tile_scan[lo < n ? lo / PLAN_TILE : n_tiles];
 #pragma unroll
-    for (int k = 0; k < 2 * COUNT_IN_FLIGHT; ++k) local += entry_tag(e[k]) == TAG_LOCAL ? 1 : 0;
+    for (int k = 0; k < 2 * COUNT_IN_FLIGHT; ++k) local += is_local_route(e[k]);
     for (int o = 32; o > 0; o >>= 1) { before += __shfl_down(before, o, 64); local += __shfl_down(local, o, 64); }
     if (lane == 0) part[wave] = local;
     __syncthreads();
@@ -627,9 +641,9 @@ __global__ void __launch_bounds__(256) miss_list_kernel(const unsigned long long
     }
 }
 
-// Routing entries, miss lists and counts of one schedule.  What the
+// Routes, miss lists and counts of one schedule.  What the
 // plan keeps lives in `keep`; scratch in `tmp`.
-// Whether row_of is ranks (see RouteSources): asked once, in the entries of the first plan that has room for it before they are
+// Whether row_of is ranks (see RouteSources): asked once, in the codes of the first plan that has room for it before they are
 // written, so that it takes no memory of its own.
 struct RankCheck {
     SlotRec *recs;
@@ -650,7 +664,8 @@ static rg_status check_row_ranks(const RankCheck &c, const int32_t *row_of, void
     return RG_OK;
 }
 
-rg_status build_plan(const rg_schedule *s, RouteSources &rs, RankCheck &check, Arena &keep, Arena &tmp, hipStream_t st, Plan *plan)
+// no_codes: dev, 0 until a plan of this build has met a row that codes cannot hold; *codes: none has as far as the host knows
+rg_status build_plan(const rg_schedule *s, RouteSources &rs, RankCheck &check, uint64_t k_eff, uint32_t *no_codes, bool *codes, Arena &keep, Arena &tmp, hipStream_t st, Plan *plan)
 {
     const uint32_t beta = s->n_batches;
     const HopData &h = s->hop[s->L];
@@ -658,7 +673,8 @@ rg_status build_plan(const rg_schedule *s, RouteSources &rs, RankCheck &check, A
     plan->schedule_uid = s->uid;
     plan->miss_off.assign((size_t)beta + 1, 0);
     plan->stats.assign(beta, rg_gather_stats{0, 0, 0, 0});
-    RG_TRY(keep.dev_n<int64_t>((uint64_t)n, &plan->entry));
+    if (*codes) RG_TRY(keep.dev_n<uint32_t>((uint64_t)n, &plan->code));
+    else RG_TRY(keep.dev_n<int64_t>((uint64_t)n, &plan->entry));
     if (beta == 0) { RG_TRY(keep.dev_n<int32_t>(0, &plan->miss_rows)); return RG_OK; }
 
     const int64_t n_tiles = (n + PLAN_TILE - 1) / PLAN_TILE, n_words = n_tiles * PLAN_TILE_WORDS;
@@ -674,22 +690,40 @@ rg_status build_plan(const rg_schedule *s, RouteSources &rs, RankCheck &check, A
     RG_TRY(tmp.dev_n<int64_t>((uint64_t)beta, &n_local_dev));
     {
         ScopedTimer tm(KG_PLAN, st);
-        if (check.pending && (uint64_t)n * sizeof(int64_t) >= (uint64_t)((check.n_nodes + 31) / 32 + 1) * (sizeof(int64_t) + sizeof(int32_t))) {
-            RG_TRY(check_row_ranks(check, rs.row_of, plan->entry, tmp, st));
+        if (check.pending && *codes && (uint64_t)n * sizeof(uint32_t) >= (uint64_t)((check.n_nodes + 31) / 32 + 1) * (sizeof(int64_t) + sizeof(int32_t))) {
+            RG_TRY(check_row_ranks(check, rs.row_of, plan->code, tmp, st));
             rs.not_ranks = check.not_ranks;
             check.pending = false;
         }
-        if (n > 0)
-            hipLaunchKernelGGL(plan_kernel, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, plan->entry, miss_bits, tile_miss, group_local);
-        RG_TRY(scan_i32_to_i64(tile_miss, tile_scan, n_tiles, tmp, st));
-        hipLaunchKernelGGL(batch_counts_kernel, dim3(beta + 1), dim3(COUNT_THREADS), 0, st, miss_bits, plan->entry, tile_scan, group_local, n, n_tiles, h.off_dev, beta, miss_off_dev, n_local_dev);
     }
     std::vector<int64_t> n_local(beta);
-    {
+    const uint32_t last_remote = last_remote_code(k_eff);
+    auto route_and_count = [&](auto *route) -> rg_status {
+        using ROUTE = std::remove_pointer_t<decltype(route)>;
+        uint32_t no_codes_host = 0;
+        {
+            ScopedTimer tm(KG_PLAN, st);
+            if (n > 0)
+                hipLaunchKernelGGL(plan_kernel<ROUTE>, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, last_remote, route, no_codes, miss_bits, tile_miss, group_local);
+            RG_TRY(scan_i32_to_i64(tile_miss, tile_scan, n_tiles, tmp, st));
+            hipLaunchKernelGGL(batch_counts_kernel<ROUTE>, dim3(beta + 1), dim3(COUNT_THREADS), 0, st, miss_bits, route, tile_scan, group_local, n, n_tiles, h.off_dev, beta, miss_off_dev, n_local_dev);
+        }
         Readback rb(st);
         RG_TRY(rb.add(plan->miss_off.data(), miss_off_dev, ((size_t)beta + 1) * sizeof(int64_t)));
         RG_TRY(rb.add(n_local.data(), n_local_dev, (size_t)beta * sizeof(int64_t)));
+        RG_TRY(rb.add(&no_codes_host, no_codes, sizeof(no_codes_host)));
         RG_TRY(rb.wait());
+        if (sizeof(ROUTE) == sizeof(uint32_t) && no_codes_host != 0) *codes = false;
+        return RG_OK;
+    };
+    if (*codes) RG_TRY(route_and_count(plan->code));
+    if (!*codes) {                            // entries, where this plan or one before it has met a row out of the codes' reach
+        if (plan->code) {
+            keep.free_one(plan->code);        // (the host has waited for what wrote them)
+            plan->code = nullptr;
+            RG_TRY(keep.dev_n<int64_t>((uint64_t)n, &plan->entry));
+        }
+        RG_TRY(route_and_count(plan->entry));
     }
     const int64_t n_miss = plan->miss_off[beta];
     RG_TRY(keep.dev_n<int32_t>((uint64_t)n_miss, &plan->miss_rows));
@@ -799,10 +833,13 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
     // ---- a7: TopHot
     SelectState *stp = nullptr;
     unsigned long long *bins = nullptr;
-    RG_TRY(tmp.dev_n<SelectState>(1, &stp));
-    RG_TRY(tmp.dev_n<unsigned long long>((uint64_t)BIN_COPIES * DIGIT_BINS, &bins));
-    RG_HIP(hipMemsetAsync(stp, 0, sizeof(SelectState), st));
-    RG_HIP(hipMemsetAsync(bins, 0, (size_t)BIN_COPIES * DIGIT_BINS * sizeof(unsigned long long), st));
+    // cleared together: the state of the selection, what the plans report of their codes, the digit's bins
+    struct SelectScratch { SelectState state; uint32_t no_codes, pad; unsigned long long bins[BIN_COPIES * DIGIT_BINS]; };
+    SelectScratch *sel = nullptr;
+    RG_TRY(tmp.dev_n<SelectScratch>(1, &sel));
+    RG_HIP(hipMemsetAsync(sel, 0, sizeof(SelectScratch), st));
+    stp = &sel->state;
+    bins = sel->bins;
     int bits = 1;
     while (bits < 32 && (max_freq >> bits) != 0) ++bits;
     const int passes = (bits + DIGIT_BITS - 1) / DIGIT_BITS;
@@ -844,20 +881,20 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
     }
     c->K_eff = hs.k_eff;
     RG_TRY(c->arena.dev_n<int32_t>(c->K_eff, &c->cache_ids));
-    int64_t *fill_entries = nullptr;
-    RG_TRY(tmp.dev_n<int64_t>(c->K_eff ? c->K_eff : 1, &fill_entries));
+    uint32_t *fill_codes = nullptr;
+    RG_TRY(tmp.dev_n<uint32_t>(c->K_eff ? c->K_eff : 1, &fill_codes));
     RG_TRY(c->arena.dev_n<SlotRec>((uint64_t)std::max<int64_t>(sel_blocks, 1) * (SEL_TILE / 32), &c->slot_pairs));      // whole tiles: every thread of the select pass writes its share
     if (sel_blocks > 0) {
         ScopedTimer tm(KG_TOPK, st);
         const dim3 sg((unsigned)sel_blocks), sb(TOPK_THREADS);
         if (narrow && local8)
-            hipLaunchKernelGGL((select_emit_kernel<true, uint8_t>), sg, sb, 0, st, c->freq8, f->is_local, n, stp, block_tot, tile_tot, c->cache_ids, c->slot_pairs, f->row_of, fill_entries);
+            hipLaunchKernelGGL((select_emit_kernel<true, uint8_t>), sg, sb, 0, st, c->freq8, f->is_local, n, stp, block_tot, tile_tot, c->cache_ids, c->slot_pairs, f->row_of, fill_codes);
         else if (narrow)
-            hipLaunchKernelGGL((select_emit_kernel<false, uint8_t>), sg, sb, 0, st, c->freq8, f->is_local, n, stp, block_tot, tile_tot, c->cache_ids, c->slot_pairs, f->row_of, fill_entries);
+            hipLaunchKernelGGL((select_emit_kernel<false, uint8_t>), sg, sb, 0, st, c->freq8, f->is_local, n, stp, block_tot, tile_tot, c->cache_ids, c->slot_pairs, f->row_of, fill_codes);
         else if (local8)
-            hipLaunchKernelGGL((select_emit_kernel<true, uint32_t>), sg, sb, 0, st, c->freq, f->is_local, n, stp, block_tot, tile_tot, c->cache_ids, c->slot_pairs, f->row_of, fill_entries);
+            hipLaunchKernelGGL((select_emit_kernel<true, uint32_t>), sg, sb, 0, st, c->freq, f->is_local, n, stp, block_tot, tile_tot, c->cache_ids, c->slot_pairs, f->row_of, fill_codes);
         else
-            hipLaunchKernelGGL((select_emit_kernel<false, uint32_t>), sg, sb, 0, st, c->freq, f->is_local, n, stp, block_tot, tile_tot, c->cache_ids, c->slot_pairs, f->row_of, fill_entries);
+            hipLaunchKernelGGL((select_emit_kernel<false, uint32_t>), sg, sb, 0, st, c->freq, f->is_local, n, stp, block_tot, tile_tot, c->cache_ids, c->slot_pairs, f->row_of, fill_codes);
     }
     RG_HIP(hipGetLastError());
 
@@ -878,7 +915,7 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
         forked.side = side;
         RowSources src{(const uint8_t *)f->local_rows, f->local_stride, (const uint8_t *)c->rows, c->stride,
                        (const uint8_t *)f->remote_rows, f->remote_stride};
-        RG_TRY(launch_gather(fill_entries, (int64_t)c->K_eff, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)c->rows, c->stride, side, KG_FILL));
+        RG_TRY(launch_gather(Routes{nullptr, fill_codes, last_remote_code(0)}, (int64_t)c->K_eff, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)c->rows, c->stride, side, KG_FILL));
         RG_HIP(hipEventRecord(c->ev_join, side));
     }
 
@@ -890,7 +927,9 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
     bool look_for_ranks = n_inputs >= RANK_INPUTS_PER_NODE * n && n_inputs >= RANK_INPUTS;
     if (const char *force = getenv("RAPIDGNN_ROW_RANKS")) look_for_ranks = force[0] == '1';      // same results either way; for tests and tuning
     RankCheck check{c->slot_pairs, n, reinterpret_cast<uint32_t *>(bins), look_for_ranks && n > 0};       // (the digits have been chosen)
-    for (uint32_t e = 0; e < n_epochs; ++e) RG_TRY(build_plan(epochs[e], rs, check, c->arena, tmp, st, &c->plans[e]));
+    bool codes = true;
+    if (const char *force = getenv("RAPIDGNN_PLAN_CODES")) codes = force[0] != '0';      // same results either way; for tests
+    for (uint32_t e = 0; e < n_epochs; ++e) RG_TRY(build_plan(epochs[e], rs, check, c->K_eff, &sel->no_codes, &codes, c->arena, tmp, st, &c->plans[e]));
     if (forked.side) RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));
     RG_HIP(hipStreamSynchronize(st));
     if (forked.side) { RG_HIP(hipStreamSynchronize(forked.side)); forked.side = nullptr; }

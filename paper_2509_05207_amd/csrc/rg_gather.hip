@@ -5,7 +5,7 @@
 // row and run on into the next row: no lane idles whatever the row width.
 // Each thread keeps CHUNKS_IN_FLIGHT independent loads outstanding before it
 // stores (stores are non-temporal: the block is consumed by a later kernel,
-// not by this one).  The source of a row comes from its 8-byte routing entry:
+// not by this one).  The source of a row comes from its routing entry or code:
 // local table, cache table or remote table.
 //
 // The miss set is copied by the same kernel over the batch's miss list.  When
@@ -59,8 +59,16 @@ constexpr int CHUNKS_IN_FLIGHT = 8;
 // row is the vector that ENDS at the row's end and overlaps its predecessor (both write the same bytes there), so
 // that no lane leaves the vector path.  TAILPIECE = true (row widths that are no multiple of 4, or below VEC): the
 // last piece is copied in 8/4/2/1-byte parts.
-template <int VEC, int A, bool TAILPIECE>
-__global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const int64_t *__restrict__ entries, int64_t n_rows,
+// Where a row comes from, out of a routing entry or a routing code.
+__device__ __forceinline__ void decode_route(int64_t e, uint32_t, uint32_t &tag, uint64_t &row) { tag = (uint32_t)entry_tag(e); row = (uint64_t)entry_row(e); }
+__device__ __forceinline__ void decode_route(uint32_t c, uint32_t last_remote, uint32_t &tag, uint64_t &row)
+{
+    tag = c < CODE_NOT_LOCAL ? (uint32_t)TAG_LOCAL : c > last_remote ? (uint32_t)TAG_CACHE : (uint32_t)TAG_REMOTE;
+    row = c > last_remote ? ~c : c & ~CODE_NOT_LOCAL;
+}
+
+template <int VEC, int A, bool TAILPIECE, typename ROUTE>
+__global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const ROUTE *__restrict__ routes, uint32_t last_remote, int64_t n_rows,
                                                                      const int32_t *__restrict__ list, int64_t n_list, int mode,
                                                                      RowSources src, uint32_t row_bytes,
                                                                      uint8_t *__restrict__ out, uint64_t out_stride, int chunks)
@@ -94,12 +102,13 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const int64
             sp[k] = nullptr; dp[k] = nullptr;
             if (k < chunks && idx < total) {
                 const int64_t r = list ? (int64_t)list[w] : (int64_t)w;
-                const int64_t e = entries[r];
-                const int64_t tag = entry_tag(e), row = entry_row(e);
+                uint32_t tag;
+                uint64_t row;
+                decode_route(routes[r], last_remote, tag, row);
                 if (!(mode == 0 && tag == TAG_REMOTE)) {
-                    const uint8_t *base = tag == TAG_LOCAL ? src.local_rows + (uint64_t)row * src.local_stride
-                                        : tag == TAG_CACHE ? src.cache_rows + (uint64_t)row * src.cache_stride
-                                                           : src.remote_rows + (uint64_t)row * src.remote_stride;
+                    const uint8_t *base = tag == TAG_LOCAL ? src.local_rows + row * src.local_stride
+                                        : tag == TAG_CACHE ? src.cache_rows + row * src.cache_stride
+                                                           : src.remote_rows + row * src.remote_stride;
                     const uint32_t o = c < cpr ? c * VEC : last_off;
                     sp[k] = base + o;
                     dp[k] = out + (uint64_t)r * out_stride + o;
@@ -120,6 +129,12 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const int64
     }
 }
 
+// The routes of a plan's input nodes from position `at` on.
+static Routes plan_routes(const Plan &p, const rg_cache *c, int64_t at)
+{
+    return p.code ? Routes{nullptr, p.code + at, last_remote_code(c->K_eff)} : Routes{p.entry + at, nullptr, 0};
+}
+
 static int common_alignment(const RowSources &s, const uint8_t *out, uint64_t out_stride)
 {
     uint64_t bits = (uint64_t)(uintptr_t)s.local_rows | s.local_stride | (uint64_t)(uintptr_t)s.cache_rows | s.cache_stride |
@@ -130,7 +145,7 @@ static int common_alignment(const RowSources &s, const uint8_t *out, uint64_t ou
     return 1;
 }
 
-rg_status launch_gather(const int64_t *entries, int64_t n_rows, const int32_t *list, int64_t n_list, int mode, const RowSources &src,
+rg_status launch_gather(const Routes &routes, int64_t n_rows, const int32_t *list, int64_t n_list, int mode, const RowSources &src,
                         uint32_t row_bytes, uint8_t *out, uint64_t out_stride, hipStream_t st, int group)
 {
     const int64_t n_work = list ? n_list : n_rows;
@@ -155,14 +170,15 @@ rg_status launch_gather(const int64_t *entries, int64_t n_rows, const int32_t *l
     const uint64_t per_block = (uint64_t)GATHER_THREADS * chunks;
     const uint64_t blocks = std::max<uint64_t>(1, std::min<uint64_t>((total + per_block - 1) / per_block, (uint64_t)n_cu * 32));
     ScopedTimer tm(group, st);
+#define RG_GATHER_ROWS(V, AL, TAIL, ROUTE, FROM)                                                                                              \
+    hipLaunchKernelGGL((gather_rows_kernel<V, AL, TAIL, ROUTE>), dim3((unsigned)blocks), dim3(GATHER_THREADS), 0, st, FROM, routes.last_remote,  \
+                       n_rows, list, n_list, mode, src, row_bytes, out, out_stride, chunks)
 #define RG_GATHER_LAUNCH(V, AL)                                                                                                               \
     do {                                                                                                                                      \
-        if (tailpiece)                                                                                                                        \
-            hipLaunchKernelGGL((gather_rows_kernel<V, AL, true>), dim3((unsigned)blocks), dim3(GATHER_THREADS), 0, st, entries, n_rows, list,   \
-                               n_list, mode, src, row_bytes, out, out_stride, chunks);                                                        \
-        else                                                                                                                                  \
-            hipLaunchKernelGGL((gather_rows_kernel<V, AL, false>), dim3((unsigned)blocks), dim3(GATHER_THREADS), 0, st, entries, n_rows, list,  \
-                               n_list, mode, src, row_bytes, out, out_stride, chunks);                                                        \
+        if (tailpiece && routes.entry) RG_GATHER_ROWS(V, AL, true, int64_t, routes.entry);                                                    \
+        else if (tailpiece) RG_GATHER_ROWS(V, AL, true, uint32_t, routes.code);                                                               \
+        else if (routes.entry) RG_GATHER_ROWS(V, AL, false, int64_t, routes.entry);                                                           \
+        else RG_GATHER_ROWS(V, AL, false, uint32_t, routes.code);                                                                             \
     } while (0)
     switch (align) {
     case 16: RG_GATHER_LAUNCH(16, 16); break;
@@ -171,6 +187,7 @@ rg_status launch_gather(const int64_t *entries, int64_t n_rows, const int32_t *l
     default: RG_GATHER_LAUNCH(1, 1); break;
     }
 #undef RG_GATHER_LAUNCH
+#undef RG_GATHER_ROWS
     RG_HIP(hipGetLastError());
     return RG_OK;
 }
@@ -324,7 +341,7 @@ extern "C" rg_status rg_gather_batch_noalloc(const rg_schedule *s, const rg_cach
     if (m > 0) {
         launch_route(h.ids + off, m, f, c ? c->slot_pairs : nullptr, entry, stats ? counts : nullptr, st);
         RG_HIP(hipGetLastError());
-        RG_TRY(launch_gather(entry, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, -1));      // (group -1: no event timers, they are created on demand)
+        RG_TRY(launch_gather(Routes{entry, nullptr, 0}, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, -1));      // (group -1: no event timers, they are created on demand)
     }
     RG_HIP(hipGetLastError());
     if (stats) {
@@ -368,21 +385,21 @@ extern "C" rg_status rg_gather_batch(const rg_schedule *s, const rg_cache *c, co
 
     if (plan) {
         const int64_t n_miss = plan->miss_off[batch + 1] - plan->miss_off[batch];
-        const int64_t *entries = plan->entry + off;
+        const Routes routes = plan_routes(*plan, c, off);
         const bool remote_in_hbm = n_miss > 0 && (f->remote_rows == c->remote_rows_seen ? c->remote_is_device : is_device_memory(f->remote_rows));
         if (n_miss == 0 || remote_in_hbm) {
             // every source is HBM: one launch copies the whole block
-            RG_TRY(launch_gather(entries, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+            RG_TRY(launch_gather(routes, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
         } else if (side != st) {
             RG_HIP(hipEventRecord(c->ev_fork, st));            // earlier work on `stream` may still use `out`
             RG_HIP(hipStreamWaitEvent(side, c->ev_fork, 0));
-            RG_TRY(launch_gather(entries, m, plan->miss_rows + plan->miss_off[batch], n_miss, 1, src, f->row_bytes, (uint8_t *)out, out_stride, side, KG_MISS));
+            RG_TRY(launch_gather(routes, m, plan->miss_rows + plan->miss_off[batch], n_miss, 1, src, f->row_bytes, (uint8_t *)out, out_stride, side, KG_MISS));
             RG_HIP(hipEventRecord(c->ev_join, side));
-            RG_TRY(launch_gather(entries, m, nullptr, 0, 0, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+            RG_TRY(launch_gather(routes, m, nullptr, 0, 0, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
             RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));
         } else {
-            RG_TRY(launch_gather(entries, m, nullptr, 0, 0, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
-            RG_TRY(launch_gather(entries, m, plan->miss_rows + plan->miss_off[batch], n_miss, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_MISS));
+            RG_TRY(launch_gather(routes, m, nullptr, 0, 0, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+            RG_TRY(launch_gather(routes, m, plan->miss_rows + plan->miss_off[batch], n_miss, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_MISS));
         }
         s->uses.note(st);                                      // the launches above read the schedule's and the cache's arrays after this call returns
         c->uses.note(st);
@@ -405,7 +422,7 @@ extern "C" rg_status rg_gather_batch(const rg_schedule *s, const rg_cache *c, co
             launch_route(h.ids + off, m, f, c ? c->slot_pairs : nullptr, entry, counts, st);
         }
         RG_HIP(hipGetLastError());
-        RG_TRY(launch_gather(entry, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+        RG_TRY(launch_gather(Routes{entry, nullptr, 0}, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
     }
     if (stats) RG_HIP(hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, st));
     RG_HIP(hipStreamSynchronize(st));
@@ -460,23 +477,23 @@ extern "C" rg_status rg_gather_batches(const rg_schedule *s, const rg_cache *c, 
     hipStream_t side = side_stream ? as_stream(side_stream) : st;
     RowSources src{(const uint8_t *)f->local_rows, f->local_stride, (const uint8_t *)c->rows, c->stride, (const uint8_t *)f->remote_rows, f->remote_stride};
     const int64_t n_miss = plan->miss_off[first_batch + n_batches] - plan->miss_off[first_batch];
-    const int64_t *entries = plan->entry + off0;
+    const Routes routes = plan_routes(*plan, c, off0);
     const bool remote_in_hbm = n_miss > 0 && (f->remote_rows == c->remote_rows_seen ? c->remote_is_device : is_device_memory(f->remote_rows));
     if (n_miss == 0 || remote_in_hbm) {
-        RG_TRY(launch_gather(entries, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+        RG_TRY(launch_gather(routes, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
     } else {
         // rows with HBM sources in one launch; every batch's miss list (row indices within its own block) in a launch of its own
         if (side != st) {
             RG_HIP(hipEventRecord(c->ev_fork, st));
             RG_HIP(hipStreamWaitEvent(side, c->ev_fork, 0));
         }
-        RG_TRY(launch_gather(entries, m, nullptr, 0, 0, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+        RG_TRY(launch_gather(routes, m, nullptr, 0, 0, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
         for (uint32_t k = 0; k < n_batches; ++k) {
             const uint32_t b = first_batch + k;
             const int64_t nm = plan->miss_off[b + 1] - plan->miss_off[b];
             if (nm == 0) continue;
             const int64_t at = h.off_host[b] - off0, mb = h.off_host[b + 1] - h.off_host[b];
-            RG_TRY(launch_gather(plan->entry + h.off_host[b], mb, plan->miss_rows + plan->miss_off[b], nm, 1, src, f->row_bytes,
+            RG_TRY(launch_gather(plan_routes(*plan, c, h.off_host[b]), mb, plan->miss_rows + plan->miss_off[b], nm, 1, src, f->row_bytes,
                                  (uint8_t *)out + (uint64_t)at * out_stride, out_stride, side, KG_MISS));
         }
         if (side != st) {

@@ -79,3 +79,52 @@ def test_rows_whatever_order_the_tables_are_in(rg, n, order, look, monkeypatch):
         rg.rg_gather_batches(s, cache, feat, 0, s.n_batches, out)
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy(), np.stack([ids, ids * 3, ids ^ 5, -ids], axis=1))
+
+
+@pytest.mark.parametrize("codes", ["1", "0"])
+@pytest.mark.parametrize("K,at", [(0, None), (50, None), (0, 0), (50, 0), (50, 1), (700, 0), (700, 1)])
+@pytest.mark.parametrize("place", ["hbm", "pinned"])
+def test_rows_at_the_end_of_what_a_code_holds(rg, codes, K, at, place, monkeypatch):
+    """Plans of codes and of entries.  A remote table of one-byte rows, two billion of them: the last row that a code holds beside K
+    slots (at = 0) and the first that none does (at = 1) are some node's, in the second epoch's plan alone; batches of one epoch
+    are served from its plan whatever the other's is made of.  at = None: every row small."""
+    if place == "pinned" and at is not None:
+        pytest.skip("two billion rows in HBM alone")
+    monkeypatch.setenv("RAPIDGNN_PLAN_CODES", codes)
+    n, far_node, d = 5000, 4321, "cuda"
+    rng = np.random.default_rng(K)
+    indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
+    others = np.setdiff1d(np.arange(n), [far_node]).astype(np.int32)
+    # the far node is listed in one batch, the others below it in every epoch: it is the last candidate of a tie and never cached
+    trains = [others, np.append(others, np.int32(far_node))]
+    scheds = [rg.rg_build_schedule(indptr, indices, torch.from_numpy(rng.permutation(t)).to(d), 333, [], 5, 0, e) for e, t in enumerate(trains)]
+    is_local = (np.arange(n) % 3 == 0).astype(np.uint8)
+    is_local[far_node] = 0
+    row_of = np.where(is_local, np.cumsum(is_local) - 1, np.cumsum(1 - is_local) - 1).astype(np.int32)
+    value = rng.integers(0, 256, size=n).astype(np.uint8)
+    if at is not None:
+        row_of[far_node] = 2**31 - 1 - K + at if K or at == 0 else 2**31 - 1
+    local = np.zeros(n, np.uint8)
+    local[row_of[is_local == 1]] = value[is_local == 1]
+    remote = torch.zeros(2**31 if at is not None else n, dtype=torch.uint8, device=d if place == "hbm" else "cpu")
+    if place == "pinned":
+        remote = remote.pin_memory()
+    far = np.flatnonzero(is_local == 0)
+    remote[torch.from_numpy(row_of[far].astype(np.int64)).to(remote.device)] = torch.from_numpy(value[far]).to(remote.device)
+    feat = rg.make_features(torch.from_numpy(is_local).to(d), torch.from_numpy(row_of).to(d), torch.from_numpy(local).to(d), remote, 1)
+    cache = rg.rg_build_cache(scheds, feat, K)
+    cached = np.zeros(n, bool)
+    cached[rg.rg_cache_view(cache, n)["cache_ids"].cpu().numpy()] = True
+    assert cached.sum() == K and not cached[far_node]
+    for s in scheds:
+        ids, _, off = rg.rg_schedule_frontier(s, 0)
+        ids = ids.cpu().numpy()
+        want = []
+        for b in range(s.n_batches):
+            v = ids[off[b]:off[b + 1]]
+            loc, hit = int(is_local[v].sum()), int((cached[v] & (is_local[v] == 0)).sum())
+            want.append(dict(n_rows=v.size, n_local=loc, n_hit=hit, n_miss=v.size - loc - hit))
+        out = torch.zeros((ids.size, 1), dtype=torch.uint8, device=d)
+        assert rg.rg_gather_batches(s, cache, feat, 0, s.n_batches, out) == want
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy()[:, 0], value[ids])
