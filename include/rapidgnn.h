@@ -216,8 +216,8 @@ typedef struct rg_features {
  * id ascending); pulls their rows from the remote table into a device table
  * (VectorPull; slot j holds the j-th smallest cached id); and prepares, for
  * every batch of every given epoch, the routing of each input node (local
- * table / cache slot / remote miss), the miss list M_i^e and the batch's
- * counts.
+ * table / cache slot / remote miss), which says what M_i^e is, and the
+ * batch's counts.
  *
  *   epochs    host array of n_epochs >= 1 schedule handles over the same n_nodes
  *   f         feature storage (borrowed for the life of the cache)

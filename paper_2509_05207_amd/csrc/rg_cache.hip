@@ -434,16 +434,6 @@ __global__ void widen_slots_kernel(const SlotRec *__restrict__ pairs, int64_t n,
 }
 
 // ---------------------------------------------------------------- a5/a9: routing plan
-__device__ __forceinline__ uint32_t batch_of_pos(const int64_t *__restrict__ off, uint32_t n_batches, int64_t i)
-{
-    uint32_t lo = 0, hi = n_batches;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (off[mid] <= i) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
 // Where a request for v's feature row is served from.  One record of the slot map says whether v
 // is local and whether (and where) it is cached; row_of is read for the others only, and not even for those where the
 // tables hold the nodes' rows in the order of their IDs: row_of is then a rank, which the record gives too.
@@ -480,36 +470,45 @@ __global__ void row_ranks_kernel(SlotRec *recs, int64_t n, const int64_t *__rest
     if (__ballot(differs) != 0ull && (threadIdx.x & 63) == 0) *not_ranks = 1u;
 }
 
-// route[j] = where ids[j] is served from, for every listed input node, which of them are misses (one
-// bit each, in position order: a wave's ballot is the 64-bit word of its 64 consecutive positions), how many misses each tile
-// of PLAN_TILE positions holds and how many local rows each PLAN_GROUP of them.  Nothing is added up per batch here: the tiles of a batch run at the
+// route[j] = where ids[j] is served from, for every listed input node, and how many local rows and misses each PLAN_GROUP of
+// them holds (misses in the upper half of the word).  Nothing is added up per batch here: the tiles of a batch run at the
 // same time, and two adds per tile to the batch's counters queued up behind each other (an epoch of 80 M input nodes in
-// 196 batches: 712 us with the adds, 494 with tiles of 1,024 positions without them, 441 so; 111 M nodes, 4.2 M input
-// nodes: 253 -> 122).  The kernel waits for its dependent reads (ID, slot-map record, row), so each kind
-// is asked for by all of a thread's positions before the first answer is used.
+// 196 batches: 712 us with the adds, 494 without them).  The kernel waits for its dependent reads (ID, slot-map record, row), so
+// each kind is asked for by all of a thread's positions before the first answer is used; a thread's positions come in fours, which
+// are one load of IDs and one store of codes.
+// A route is a code or, where codes have met a row they cannot hold (*no_codes = 1; see make_code), an entry.
 constexpr int PLAN_THREADS = 256;
-constexpr int PLAN_PER_THREAD = 8;
+constexpr int PLAN_QUADS = 2;
+constexpr int PLAN_PER_THREAD = 4 * PLAN_QUADS;
 constexpr int PLAN_TILE = PLAN_THREADS * PLAN_PER_THREAD;
-constexpr int PLAN_TILE_WORDS = PLAN_TILE / 64;          // bit words per tile
-constexpr int PLAN_GROUP = 2 * PLAN_THREADS;             // positions to a count of local rows
+constexpr int PLAN_GROUP = 2 * PLAN_THREADS;             // positions to a word of counts: a quad of two waves
 constexpr int PLAN_TILE_GROUPS = PLAN_TILE / PLAN_GROUP;
 
-// A route is a code or, where codes have met a row they cannot hold (*no_codes = 1; see make_code), an entry.
 template <typename ROUTE>
 __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__restrict__ ids, int64_t n, RouteSources rs, uint32_t last_remote, ROUTE *__restrict__ route,
-                                                            uint32_t *__restrict__ no_codes,
-                                                            unsigned long long *__restrict__ miss_bits /* [tiles * PLAN_TILE_WORDS] */,
-                                                            int32_t *__restrict__ tile_miss /* [tiles] */, uint16_t *__restrict__ group_local /* [tiles * PLAN_TILE_GROUPS] */)
+                                                            uint32_t *__restrict__ no_codes, uint32_t *__restrict__ group_counts /* [tiles * PLAN_TILE_GROUPS] */)
 {
-    __shared__ int red[1 + PLAN_TILE_GROUPS][PLAN_THREADS / 64];
-    const int64_t tile0 = (int64_t)blockIdx.x * PLAN_TILE;
+    static_assert(PLAN_GROUP == 4 * 64 * 2 && PLAN_THREADS == 4 * 64, "two waves' quads are a group");
+    typedef uint32_t id4 __attribute__((ext_vector_type(4), aligned(4)));              // (an allocator of the caller's may align less than sixteen bytes)
+    typedef ROUTE route4 __attribute__((ext_vector_type(4), aligned(sizeof(ROUTE))));
+    __shared__ uint32_t red[PLAN_QUADS][PLAN_THREADS / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool ranks = rs.not_ranks && *rs.not_ranks == 0u;
+    const int64_t j0 = (int64_t)blockIdx.x * PLAN_TILE + 4 * (int64_t)threadIdx.x;      // of the first quad; the next one 4 * PLAN_THREADS on
     uint32_t v[PLAN_PER_THREAD];
     SlotRec rec[PLAN_PER_THREAD];
     int32_t row[PLAN_PER_THREAD];
 #pragma unroll
-    for (int k = 0; k < PLAN_PER_THREAD; ++k) v[k] = (uint32_t)ids[min(tile0 + (int64_t)k * PLAN_THREADS + threadIdx.x, n - 1)];      // (past the end: the last ID again, not used)
+    for (int q = 0; q < PLAN_QUADS; ++q) {
+        const int64_t j = j0 + q * 4 * PLAN_THREADS;
+        if (j + 4 <= n) {
+            const id4 x = *reinterpret_cast<const id4 *>(ids + j);
+            v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[4 * q + k] = (uint32_t)ids[min(j + k, n - 1)];      // (past the end: the last ID again, not used)
+        }
+    }
 #pragma unroll
     for (int k = 0; k < PLAN_PER_THREAD; ++k) rec[k] = rs.slot_pairs[v[k] >> 5];
 #pragma unroll
@@ -522,127 +521,81 @@ __global__ void __launch_bounds__(PLAN_THREADS) plan_kernel(const int32_t *__res
             row[k] = (int32_t)((rec[k].z & bit) ? local : v[k] - local);
         } else row[k] = rs.row_of[v[k]];
     }
-    int n_local[PLAN_TILE_GROUPS] = {}, n_miss = 0;        // of the wave
     bool no_code = false;
 #pragma unroll
-    for (int k = 0; k < PLAN_PER_THREAD; ++k) {
-        const int64_t j = tile0 + (int64_t)k * PLAN_THREADS + threadIdx.x;
-        const uint32_t bit = 1u << (v[k] & 31);
-        const bool local = (rec[k].z & bit) != 0, cached = !local && (rec[k].x & bit) != 0;
-        if constexpr (sizeof(ROUTE) == 4) {
-            no_code |= !fits_code(local, cached, (uint32_t)row[k], last_remote);      // (past the end: the last ID's answer again)
-            if (j < n) __builtin_nontemporal_store(make_code(local, cached, (uint32_t)row[k]), route + j);
-        } else if (j < n) __builtin_nontemporal_store(make_entry(local ? TAG_LOCAL : cached ? TAG_CACHE : TAG_REMOTE, row[k]), route + j);
-        const unsigned long long ml = __ballot(j < n && local), mm = __ballot(j < n && !local && !cached);
-        if (lane == 0) miss_bits[(uint64_t)blockIdx.x * PLAN_TILE_WORDS + k * (PLAN_THREADS / 64) + wave] = mm;
-        n_local[k / 2] += __popcll(ml);
-        n_miss += __popcll(mm);
+    for (int q = 0; q < PLAN_QUADS; ++q) {
+        const int64_t j = j0 + q * 4 * PLAN_THREADS;
+        route4 r;
+        uint32_t counts = 0;                               // of the wave's quad
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const SlotRec &here = rec[4 * q + k];
+            const uint32_t bit = 1u << (v[4 * q + k] & 31), at = (uint32_t)row[4 * q + k];
+            const bool local = (here.z & bit) != 0, cached = !local && (here.x & bit) != 0;
+            if constexpr (sizeof(ROUTE) == 4) {
+                no_code |= !fits_code(local, cached, at, last_remote);      // (past the end: the last ID's answer again)
+                r[k] = make_code(local, cached, at);
+            } else r[k] = make_entry(local ? TAG_LOCAL : cached ? TAG_CACHE : TAG_REMOTE, row[4 * q + k]);
+            counts += (uint32_t)__popcll(__ballot(j + k < n && local)) + ((uint32_t)__popcll(__ballot(j + k < n && !local && !cached)) << 16);
+        }
+        if (j + 4 <= n) __builtin_nontemporal_store(r, reinterpret_cast<route4 *>(route + j));
+        else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (j + k < n) route[j + k] = r[k];
+        }
+        if (lane == 0) red[q][wave] = counts;
     }
     if (__ballot(no_code) != 0ull && lane == 0) *no_codes = 1u;
-    if (lane == 0) {
-        red[0][wave] = n_miss;
-#pragma unroll
-        for (int q = 0; q < PLAN_TILE_GROUPS; ++q) red[1 + q][wave] = n_local[q];
-    }
     __syncthreads();
-    if (threadIdx.x <= PLAN_TILE_GROUPS) {
-        int c = 0;
-        for (int w = 0; w < PLAN_THREADS / 64; ++w) c += red[threadIdx.x][w];
-        if (threadIdx.x == 0) tile_miss[blockIdx.x] = c;
-        else group_local[(uint64_t)blockIdx.x * PLAN_TILE_GROUPS + threadIdx.x - 1] = (uint16_t)c;
+    if (threadIdx.x < PLAN_TILE_GROUPS) {
+        const int q = threadIdx.x / 2, w = threadIdx.x % 2 * 2;
+        group_counts[(uint64_t)blockIdx.x * PLAN_TILE_GROUPS + threadIdx.x] = red[q][w] + red[q][w + 1];
     }
 }
 
-// Set bits among positions [lo, hi), counted by a wave (the sum is the lanes' together).
-__device__ __forceinline__ int64_t lane_bits_between(const unsigned long long *__restrict__ bits, int64_t lo, int64_t hi, int lane)
-{
-    int64_t cnt = 0;
-    for (int64_t w = (lo >> 6) + lane; (w << 6) < hi; w += 64) {
-        unsigned long long m = bits[w];
-        if ((w << 6) < lo) m &= ~0ull << (lo & 63);
-        if (hi - (w << 6) < 64) m &= (1ull << (hi & 63)) - 1ull;
-        cnt += __popcll(m);
-    }
-    return cnt;
-}
+// What a route adds to a word of counts.
+__device__ __forceinline__ uint32_t counts_of_route(int64_t e, uint32_t) { return entry_tag(e) == TAG_LOCAL ? 1u : entry_tag(e) == TAG_REMOTE ? 1u << 16 : 0u; }
+__device__ __forceinline__ uint32_t counts_of_route(uint32_t c, uint32_t last_remote) { return c < CODE_NOT_LOCAL ? 1u : c <= last_remote ? 1u << 16 : 0u; }
 
-// One workgroup per batch (and one for the end).  miss_off[b] = misses in front of batch b's first position: those of the
-// tiles in front of its tile (tile_scan) and of the positions in front of it inside the tile; n_local[b] = its local
-// rows: those of the whole groups between its ends, and the routes in front of and behind them.  Bound by its dependent
-// reads, of which there are two: the batch's ends, then everything else at once (a plan of 500,000 entries in 145 batches 5.2 us; with
-// whole tiles counted and the entries of the end tiles read, 10.0).
-__device__ __forceinline__ int is_local_route(int64_t e) { return entry_tag(e) == TAG_LOCAL ? 1 : 0; }
-__device__ __forceinline__ int is_local_route(uint32_t c) { return c < CODE_NOT_LOCAL ? 1 : 0; }
+// One workgroup per batch: its local rows and misses, those of the whole groups between its ends and of the routes in front of
+// and behind them.  Bound by its dependent reads, of which there are two: the batch's ends, then everything else at once (a
+// plan of 500,000 input nodes in 145 batches 5 us; with whole tiles counted and the entries of the end tiles read, 10.0).
 constexpr int COUNT_THREADS = 256;
 constexpr int COUNT_IN_FLIGHT = PLAN_GROUP / COUNT_THREADS;
 template <typename ROUTE>
-__global__ void __launch_bounds__(COUNT_THREADS) batch_counts_kernel(const unsigned long long *__restrict__ miss_bits, const ROUTE *__restrict__ route,
-                                                                     const int64_t *__restrict__ tile_scan, const uint16_t *__restrict__ group_local, int64_t n, int64_t n_tiles,
-                                                                     const int64_t *__restrict__ batch_off, uint32_t n_batches, int64_t *__restrict__ miss_off,
-                                                                     int64_t *__restrict__ n_local)
+__global__ void __launch_bounds__(COUNT_THREADS) batch_counts_kernel(const ROUTE *__restrict__ route, uint32_t last_remote, const uint32_t *__restrict__ group_counts,
+                                                                     const int64_t *__restrict__ batch_off, uint32_t n_batches, int64_t *__restrict__ counts /* [2 * batches]: local rows, then misses */)
 {
-    __shared__ int64_t part[COUNT_THREADS / 64];
+    __shared__ int64_t part[2][COUNT_THREADS / 64];
     const uint32_t b = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t lo = batch_off[b], hi = batch_off[min(b + 1, n_batches)];      // (the end: no positions)
+    const int64_t lo = batch_off[b], hi = batch_off[b + 1];
     const int64_t g_lo = (lo + PLAN_GROUP - 1) / PLAN_GROUP, g_hi = hi / PLAN_GROUP;      // whole groups [g_lo, g_hi), if any
     const int64_t front_end = g_lo <= g_hi ? g_lo * PLAN_GROUP : hi, back = g_lo <= g_hi ? g_hi * PLAN_GROUP : hi;
-    const ROUTE not_local = (ROUTE)~(ROUTE)0;                                             // (as an entry and as a code)
-    ROUTE e[2 * COUNT_IN_FLIGHT];
-    int64_t local = 0;
+    uint32_t ends = 0;
 #pragma unroll
     for (int k = 0; k < COUNT_IN_FLIGHT; ++k) {
         const int64_t j = lo + k * COUNT_THREADS + threadIdx.x, i = back + k * COUNT_THREADS + threadIdx.x;
-        e[2 * k] = j < front_end ? route[j] : not_local;
-        e[2 * k + 1] = i < hi ? route[i] : not_local;
+        if (j < front_end) ends += counts_of_route(route[j], last_remote);
+        if (i < hi) ends += counts_of_route(route[i], last_remote);
     }
-    for (int64_t g = g_lo + threadIdx.x; g < g_hi; g += COUNT_THREADS) local += group_local[g];
-    int64_t before = lo < n && wave == 0 ? lane_bits_between(miss_bits, lo / PLAN_TILE * PLAN_TILE, lo, lane) : 0;
-    const int64_t scan_here = tile_scan[lo < n ? lo / PLAN_TILE : n_tiles];
-#pragma unroll
-    for (int k = 0; k < 2 * COUNT_IN_FLIGHT; ++k) local += is_local_route(e[k]);
-    for (int o = 32; o > 0; o >>= 1) { before += __shfl_down(before, o, 64); local += __shfl_down(local, o, 64); }
-    if (lane == 0) part[wave] = local;
+    int64_t local = ends & 0xFFFFu, miss = ends >> 16;
+    for (int64_t g = g_lo + threadIdx.x; g < g_hi; g += COUNT_THREADS) {
+        const uint32_t c = group_counts[g];
+        local += c & 0xFFFFu;
+        miss += c >> 16;
+    }
+    for (int o = 32; o > 0; o >>= 1) { local += __shfl_down(local, o, 64); miss += __shfl_down(miss, o, 64); }
+    if (lane == 0) { part[0][wave] = local; part[1][wave] = miss; }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        miss_off[b] = scan_here + before;
-        if (b < n_batches) n_local[b] = part[0] + part[1] + part[2] + part[3];
+    if (threadIdx.x < 2) {
+        int64_t c = 0;
+        for (int w = 0; w < COUNT_THREADS / 64; ++w) c += part[threadIdx.x][w];
+        counts[(uint64_t)threadIdx.x * n_batches + b] = c;
     }
 }
 
-// miss_rows[rank of the miss] = its position within its batch, for every miss.  A workgroup takes one tile: every
-// wave reads the tile's PLAN_TILE_WORDS words of miss bits (one per lane), scans their bit counts, and writes the
-// misses of every fourth word.
-__global__ void __launch_bounds__(256) miss_list_kernel(const unsigned long long *__restrict__ miss_bits, const int64_t *__restrict__ tile_scan,
-                                                        const int64_t *__restrict__ batch_off, uint32_t n_batches, int32_t *__restrict__ miss_rows)
-{
-    static_assert(PLAN_TILE_WORDS <= 64 && PLAN_TILE_WORDS % 4 == 0, "a lane per word; four waves share the words");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t tile = blockIdx.x;
-    const unsigned long long mine = lane < PLAN_TILE_WORDS ? miss_bits[tile * PLAN_TILE_WORDS + lane] : 0ull;
-    if (__ballot(mine != 0ull) == 0ull) return;                  // no miss in the tile
-    int incl = __popcll(mine);
-    for (int d = 1; d < PLAN_TILE_WORDS; d <<= 1) {
-        const int y = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += y;
-    }
-    const int before_word = incl - __popcll(mine);               // misses of the tile in front of this lane's word
-    const int64_t tile0 = tile * PLAN_TILE, tile_base = tile_scan[tile];
-    // almost every tile lies inside one batch: its first position's batch then serves all of its positions
-    const uint32_t b_first = batch_of_pos(batch_off, n_batches, tile0);
-    const int64_t start_first = batch_off[b_first], end_first = batch_off[b_first + 1];
-    for (int w = wave; w < PLAN_TILE_WORDS; w += 4) {
-        const unsigned long long m = __shfl(mine, w, 64);
-        const int before = __shfl(before_word, w, 64);
-        if (!((m >> lane) & 1ull)) continue;
-        const int64_t j = tile0 + 64 * w + lane;
-        const int64_t start = j < end_first ? start_first : batch_off[batch_of_pos(batch_off, n_batches, j)];
-        miss_rows[tile_base + before + __popcll(m & ((1ull << lane) - 1ull))] = (int32_t)(j - start);
-    }
-}
-
-// Routes, miss lists and counts of one schedule.  What the
-// plan keeps lives in `keep`; scratch in `tmp`.
 // Whether row_of is ranks (see RouteSources): asked once, in the codes of the first plan that has room for it before they are
 // written, so that it takes no memory of its own.
 struct RankCheck {
@@ -664,82 +617,79 @@ static rg_status check_row_ranks(const RankCheck &c, const int32_t *row_of, void
     return RG_OK;
 }
 
-// no_codes: dev, 0 until a plan of this build has met a row that codes cannot hold; *codes: none has as far as the host knows
-rg_status build_plan(const rg_schedule *s, RouteSources &rs, RankCheck &check, uint64_t k_eff, uint32_t *no_codes, bool *codes, Arena &keep, Arena &tmp, hipStream_t st, Plan *plan)
+// The plans of all epochs: routes, and counts per batch, which the host waits for once, behind the last epoch's.  What a plan
+// keeps lives in `keep`; scratch in `tmp`.  no_codes: dev, 0; *codes: whether routes are codes, false on return if
+// a row turned out to be out of their reach.
+static rg_status launch_plans(const rg_schedule *const *epochs, RouteSources &rs, RankCheck &check, uint64_t k_eff, uint32_t *no_codes, bool *codes, Arena &keep, Arena &tmp,
+                              hipStream_t st, std::vector<Plan> &plans)
 {
-    const uint32_t beta = s->n_batches;
-    const HopData &h = s->hop[s->L];
-    const int64_t n = beta ? h.off_host[beta] : 0;
-    plan->schedule_uid = s->uid;
-    plan->miss_off.assign((size_t)beta + 1, 0);
-    plan->stats.assign(beta, rg_gather_stats{0, 0, 0, 0});
-    if (*codes) RG_TRY(keep.dev_n<uint32_t>((uint64_t)n, &plan->code));
-    else RG_TRY(keep.dev_n<int64_t>((uint64_t)n, &plan->entry));
-    if (beta == 0) { RG_TRY(keep.dev_n<int32_t>(0, &plan->miss_rows)); return RG_OK; }
-
-    const int64_t n_tiles = (n + PLAN_TILE - 1) / PLAN_TILE, n_words = n_tiles * PLAN_TILE_WORDS;
-    unsigned long long *miss_bits = nullptr;
-    int32_t *tile_miss = nullptr;
-    uint16_t *group_local = nullptr;
-    int64_t *tile_scan = nullptr, *miss_off_dev = nullptr, *n_local_dev = nullptr;
-    RG_TRY(tmp.dev_n<unsigned long long>((uint64_t)std::max<int64_t>(n_words, 1), &miss_bits));
-    RG_TRY(tmp.dev_n<int32_t>((uint64_t)std::max<int64_t>(n_tiles, 1), &tile_miss));
-    RG_TRY(tmp.dev_n<uint16_t>((uint64_t)std::max<int64_t>(n_tiles, 1) * PLAN_TILE_GROUPS, &group_local));
-    RG_TRY(tmp.dev_n<int64_t>((uint64_t)n_tiles + 1, &tile_scan));
-    RG_TRY(tmp.dev_n<int64_t>((uint64_t)beta + 1, &miss_off_dev));
-    RG_TRY(tmp.dev_n<int64_t>((uint64_t)beta, &n_local_dev));
-    {
+    const uint32_t last_remote = last_remote_code(k_eff);
+    std::vector<std::vector<int64_t>> counts(plans.size());
+    uint32_t no_codes_host = 0;
+    Readback rb(st);
+    for (size_t e = 0; e < plans.size(); ++e) {
+        const rg_schedule *s = epochs[e];
+        Plan &plan = plans[e];
+        const uint32_t beta = s->n_batches;
+        const HopData &h = s->hop[s->L];
+        const int64_t n = beta ? h.off_host[beta] : 0, n_tiles = (n + PLAN_TILE - 1) / PLAN_TILE;
+        if (*codes) RG_TRY(keep.dev_n<uint32_t>((uint64_t)n, &plan.code));
+        else RG_TRY(keep.dev_n<int64_t>((uint64_t)n, &plan.entry));
+        counts[e].assign(2 * (size_t)beta, 0);
+        if (n == 0) continue;
+        uint32_t *group_counts = nullptr;
+        int64_t *counts_dev = nullptr;
+        RG_TRY(tmp.dev_n<uint32_t>((uint64_t)n_tiles * PLAN_TILE_GROUPS, &group_counts));
+        RG_TRY(tmp.dev_n<int64_t>(2 * (uint64_t)beta, &counts_dev));
         ScopedTimer tm(KG_PLAN, st);
         if (check.pending && *codes && (uint64_t)n * sizeof(uint32_t) >= (uint64_t)((check.n_nodes + 31) / 32 + 1) * (sizeof(int64_t) + sizeof(int32_t))) {
-            RG_TRY(check_row_ranks(check, rs.row_of, plan->code, tmp, st));
+            RG_TRY(check_row_ranks(check, rs.row_of, plan.code, tmp, st));
             rs.not_ranks = check.not_ranks;
             check.pending = false;
         }
+        auto launch = [&](auto *route) {
+            using ROUTE = std::remove_pointer_t<decltype(route)>;
+            hipLaunchKernelGGL(plan_kernel<ROUTE>, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, last_remote, route, no_codes, group_counts);
+            hipLaunchKernelGGL(batch_counts_kernel<ROUTE>, dim3(beta), dim3(COUNT_THREADS), 0, st, route, last_remote, group_counts, h.off_dev, beta, counts_dev);
+        };
+        if (*codes) launch(plan.code);
+        else launch(plan.entry);
+        RG_HIP(hipGetLastError());
+        RG_TRY(rb.add(counts[e].data(), counts_dev, counts[e].size() * sizeof(int64_t)));
     }
-    std::vector<int64_t> n_local(beta);
-    const uint32_t last_remote = last_remote_code(k_eff);
-    auto route_and_count = [&](auto *route) -> rg_status {
-        using ROUTE = std::remove_pointer_t<decltype(route)>;
-        uint32_t no_codes_host = 0;
-        {
-            ScopedTimer tm(KG_PLAN, st);
-            if (n > 0)
-                hipLaunchKernelGGL(plan_kernel<ROUTE>, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, last_remote, route, no_codes, miss_bits, tile_miss, group_local);
-            RG_TRY(scan_i32_to_i64(tile_miss, tile_scan, n_tiles, tmp, st));
-            hipLaunchKernelGGL(batch_counts_kernel<ROUTE>, dim3(beta + 1), dim3(COUNT_THREADS), 0, st, miss_bits, route, tile_scan, group_local, n, n_tiles, h.off_dev, beta, miss_off_dev, n_local_dev);
+    RG_TRY(rb.add(&no_codes_host, no_codes, sizeof(no_codes_host)));
+    RG_TRY(rb.wait());
+    if (no_codes_host != 0) *codes = false;
+    for (size_t e = 0; e < plans.size(); ++e) {
+        const rg_schedule *s = epochs[e];
+        Plan &plan = plans[e];
+        const HopData &h = s->hop[s->L];
+        const uint32_t beta = s->n_batches;
+        plan.schedule_uid = s->uid;
+        plan.miss_off.assign((size_t)beta + 1, 0);
+        plan.stats.assign(beta, rg_gather_stats{0, 0, 0, 0});
+        for (uint32_t b = 0; b < beta; ++b) {
+            rg_gather_stats &g = plan.stats[b];
+            g.n_rows = (uint64_t)(h.off_host[b + 1] - h.off_host[b]);
+            g.n_local = (uint64_t)counts[e][b];
+            g.n_miss = (uint64_t)counts[e][(size_t)beta + b];
+            g.n_hit = g.n_rows - g.n_local - g.n_miss;
+            plan.miss_off[b + 1] = plan.miss_off[b] + (int64_t)g.n_miss;
         }
-        Readback rb(st);
-        RG_TRY(rb.add(plan->miss_off.data(), miss_off_dev, ((size_t)beta + 1) * sizeof(int64_t)));
-        RG_TRY(rb.add(n_local.data(), n_local_dev, (size_t)beta * sizeof(int64_t)));
-        RG_TRY(rb.add(&no_codes_host, no_codes, sizeof(no_codes_host)));
-        RG_TRY(rb.wait());
-        if (sizeof(ROUTE) == sizeof(uint32_t) && no_codes_host != 0) *codes = false;
-        return RG_OK;
-    };
-    if (*codes) RG_TRY(route_and_count(plan->code));
-    if (!*codes) {                            // entries, where this plan or one before it has met a row out of the codes' reach
-        if (plan->code) {
-            keep.free_one(plan->code);        // (the host has waited for what wrote them)
-            plan->code = nullptr;
-            RG_TRY(keep.dev_n<int64_t>((uint64_t)n, &plan->entry));
-        }
-        RG_TRY(route_and_count(plan->entry));
-    }
-    const int64_t n_miss = plan->miss_off[beta];
-    RG_TRY(keep.dev_n<int32_t>((uint64_t)n_miss, &plan->miss_rows));
-    if (n_miss > 0) {
-        ScopedTimer tm(KG_PLAN, st);
-        hipLaunchKernelGGL(miss_list_kernel, dim3((unsigned)n_tiles), dim3(256), 0, st, miss_bits, tile_scan, h.off_dev, beta, plan->miss_rows);
-    }
-    RG_HIP(hipGetLastError());
-    for (uint32_t b = 0; b < beta; ++b) {
-        rg_gather_stats &g = plan->stats[b];
-        g.n_rows = (uint64_t)(h.off_host[b + 1] - h.off_host[b]);
-        g.n_local = (uint64_t)n_local[b];
-        g.n_miss = (uint64_t)(plan->miss_off[b + 1] - plan->miss_off[b]);
-        g.n_hit = g.n_rows - g.n_local - g.n_miss;
     }
     return RG_OK;                 // (the caller waits for the stream before `tmp` goes back)
+}
+
+static rg_status build_plans(const rg_schedule *const *epochs, RouteSources &rs, RankCheck &check, uint64_t k_eff, uint32_t *no_codes, Arena &keep, Arena &tmp,
+                             hipStream_t st, std::vector<Plan> &plans)
+{
+    bool codes = true;
+    if (const char *force = getenv("RAPIDGNN_PLAN_CODES")) codes = force[0] != '0';      // same results either way; for tests
+    const bool tried = codes;
+    RG_TRY(launch_plans(epochs, rs, check, k_eff, no_codes, &codes, keep, tmp, st, plans));
+    if (codes || !tried) return RG_OK;
+    for (Plan &p : plans) { keep.free_one(p.code); p.code = nullptr; }          // (the host has waited for what wrote them)
+    return launch_plans(epochs, rs, check, k_eff, no_codes, &codes, keep, tmp, st, plans);
 }
 
 // The tally as uint32_t[n_nodes] for rg_cache_view: the array itself, or -- where the build counted in bytes -- a
@@ -915,11 +865,11 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
         forked.side = side;
         RowSources src{(const uint8_t *)f->local_rows, f->local_stride, (const uint8_t *)c->rows, c->stride,
                        (const uint8_t *)f->remote_rows, f->remote_stride};
-        RG_TRY(launch_gather(Routes{nullptr, fill_codes, last_remote_code(0)}, (int64_t)c->K_eff, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)c->rows, c->stride, side, KG_FILL));
+        RG_TRY(launch_gather(Routes{nullptr, fill_codes, last_remote_code(0)}, (int64_t)c->K_eff, ROWS_ALL, src, f->row_bytes, (uint8_t *)c->rows, c->stride, side, KG_FILL));
         RG_HIP(hipEventRecord(c->ev_join, side));
     }
 
-    // ---- a5/a9: plans, miss lists and counts for every batch of every epoch
+    // ---- a5/a9: plans and counts for every batch of every epoch
     c->plans.resize(n_epochs);
     RouteSources rs{f->row_of, c->slot_pairs, nullptr};
     int64_t n_inputs = 0;
@@ -927,9 +877,7 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
     bool look_for_ranks = n_inputs >= RANK_INPUTS_PER_NODE * n && n_inputs >= RANK_INPUTS;
     if (const char *force = getenv("RAPIDGNN_ROW_RANKS")) look_for_ranks = force[0] == '1';      // same results either way; for tests and tuning
     RankCheck check{c->slot_pairs, n, reinterpret_cast<uint32_t *>(bins), look_for_ranks && n > 0};       // (the digits have been chosen)
-    bool codes = true;
-    if (const char *force = getenv("RAPIDGNN_PLAN_CODES")) codes = force[0] != '0';      // same results either way; for tests
-    for (uint32_t e = 0; e < n_epochs; ++e) RG_TRY(build_plan(epochs[e], rs, check, c->K_eff, &sel->no_codes, &codes, c->arena, tmp, st, &c->plans[e]));
+    RG_TRY(build_plans(epochs, rs, check, c->K_eff, &sel->no_codes, c->arena, tmp, st, c->plans));
     if (forked.side) RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));
     RG_HIP(hipStreamSynchronize(st));
     if (forked.side) { RG_HIP(hipStreamSynchronize(forked.side)); forked.side = nullptr; }

@@ -8,12 +8,14 @@
 // not by this one).  The source of a row comes from its routing entry or code:
 // local table, cache table or remote table.
 //
-// The miss set is copied by the same kernel over the batch's miss list.  When
-// the remote table is pinned host memory (mapped into the device's address
-// space) that launch goes to the side stream and its loads cross the host
-// link -- SyncPull without host-side packing or staging.  When the remote
-// table is device memory, one launch on the main stream copies every row.
+// When the remote table is pinned host memory (mapped into the device's address
+// space) the miss set is copied by a launch of its own, on the side stream: a
+// wave finds the misses among a run of rows and copies those, and its loads
+// cross the host link -- SyncPull without host-side packing or staging, and
+// without a list of the misses.  When the remote table is device memory, one
+// launch on the main stream copies every row.
 #include "rg_internal.h"
+#include "rg_device.h"
 
 #include <algorithm>
 #include <mutex>
@@ -68,8 +70,7 @@ __device__ __forceinline__ void decode_route(uint32_t c, uint32_t last_remote, u
 }
 
 template <int VEC, int A, bool TAILPIECE, typename ROUTE>
-__global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const ROUTE *__restrict__ routes, uint32_t last_remote, int64_t n_rows,
-                                                                     const int32_t *__restrict__ list, int64_t n_list, int mode,
+__global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const ROUTE *__restrict__ routes, uint32_t last_remote, int64_t n_rows, int skip_remote,
                                                                      RowSources src, uint32_t row_bytes,
                                                                      uint8_t *__restrict__ out, uint64_t out_stride, int chunks)
 {
@@ -78,11 +79,10 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const ROUTE
     const uint32_t cpr = row_bytes / VEC, tail = row_bytes % VEC;
     const uint32_t cpt = cpr + (tail ? 1u : 0u);                  // pieces per row: full vectors, then the last piece
     const uint32_t last_off = TAILPIECE ? cpr * VEC : row_bytes - VEC;     // where the piece after the full vectors starts
-    const uint64_t n_work = (uint64_t)(list ? n_list : n_rows);
-    const uint64_t total = n_work * cpt;
+    const uint64_t total = (uint64_t)n_rows * cpt;
     // A workgroup takes GATHER_THREADS * chunks consecutive pieces per round (chunks <= CHUNKS_IN_FLIGHT, fewer for
     // a block of rows too small to fill the chip otherwise): one contiguous span of the output, 32 KB with 16-byte
-    // pieces.  Within a round the flat index -> (work item, piece) pair is advanced by GATHER_THREADS without
+    // pieces.  Within a round the flat index -> (row, piece) pair is advanced by GATHER_THREADS without
     // dividing again.
     const uint32_t ROUND = GATHER_THREADS * (uint32_t)chunks;
     const uint32_t dq = GATHER_THREADS / cpt;
@@ -101,17 +101,16 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const ROUTE
             kind[k] = 0;
             sp[k] = nullptr; dp[k] = nullptr;
             if (k < chunks && idx < total) {
-                const int64_t r = list ? (int64_t)list[w] : (int64_t)w;
                 uint32_t tag;
                 uint64_t row;
-                decode_route(routes[r], last_remote, tag, row);
-                if (!(mode == 0 && tag == TAG_REMOTE)) {
+                decode_route(routes[w], last_remote, tag, row);
+                if (!(skip_remote && tag == TAG_REMOTE)) {
                     const uint8_t *base = tag == TAG_LOCAL ? src.local_rows + row * src.local_stride
                                         : tag == TAG_CACHE ? src.cache_rows + row * src.cache_stride
                                                            : src.remote_rows + row * src.remote_stride;
                     const uint32_t o = c < cpr ? c * VEC : last_off;
                     sp[k] = base + o;
-                    dp[k] = out + (uint64_t)r * out_stride + o;
+                    dp[k] = out + w * out_stride + o;
                     kind[k] = (!TAILPIECE || c < cpr) ? 1 : 2;
                     if (kind[k] == 1) v[k] = *reinterpret_cast<const P *>(sp[k]);
                 }
@@ -125,6 +124,65 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const ROUTE
         for (int k = 0; k < CHUNKS_IN_FLIGHT; ++k) {
             if (kind[k] == 1) __builtin_nontemporal_store(v[k], reinterpret_cast<P *>(dp[k]));
             else if (TAILPIECE && kind[k] == 2) copy_tail<VEC, A>(sp[k], dp[k], tail);
+        }
+    }
+}
+
+// The remote rows alone.  A wave takes per_wave consecutive rows (a power of two up to 64) per round, one route a lane, lists the
+// remote ones in LDS and copies those as the kernel above copies all: flat pieces, one per lane, CHUNKS_IN_FLIGHT under way.  Bound by
+// the host link.  (A list of the misses made with every plan took 79 us per 80 M input nodes, and a wait for its length.)
+template <int VEC, int A, bool TAILPIECE, typename ROUTE>
+__global__ void __launch_bounds__(GATHER_THREADS) gather_remote_kernel(const ROUTE *__restrict__ routes, uint32_t last_remote, int64_t n_rows, int per_wave,
+                                                                       RowSources src, uint32_t row_bytes, uint8_t *__restrict__ out, uint64_t out_stride)
+{
+    using T = typename VecT<VEC>::type;
+    using P = typename PieceT<VEC, A>::type;
+    struct Miss { uint64_t src_row, out_row; };
+    __shared__ Miss lists[GATHER_THREADS / 64][64];
+    const uint32_t cpr = row_bytes / VEC, tail = row_bytes % VEC;
+    const uint32_t cpt = cpr + (tail ? 1u : 0u);
+    const uint32_t last_off = TAILPIECE ? cpr * VEC : row_bytes - VEC;
+    const uint32_t dq = 64 / cpt, dr = 64 - dq * cpt;
+    const int lane = threadIdx.x & 63;
+    Miss *mine = lists[threadIdx.x >> 6];
+    const int64_t n_waves = (int64_t)gridDim.x * (GATHER_THREADS / 64), wave = (int64_t)blockIdx.x * (GATHER_THREADS / 64) + (threadIdx.x >> 6);
+    for (int64_t first = wave * per_wave; first < n_rows; first += n_waves * per_wave) {
+        uint32_t tag = (uint32_t)TAG_LOCAL;
+        uint64_t row = 0;
+        if (lane < per_wave && first + lane < n_rows) decode_route(routes[first + lane], last_remote, tag, row);
+        const bool miss = tag == (uint32_t)TAG_REMOTE;
+        const unsigned long long all = __ballot(miss);
+        wave_lds_order();                                          // the last round's list has been read
+        if (miss) mine[__popcll(all & ((1ull << lane) - 1ull))] = Miss{row, (uint64_t)(first + lane)};
+        wave_lds_order();
+        const uint64_t total = (uint64_t)__popcll(all) * cpt;      // (64 rows of up to 2^32 bytes)
+        uint32_t m = (uint32_t)lane / cpt, c = (uint32_t)lane - m * cpt;
+        for (uint64_t idx = lane; idx < total;) {
+            T v[CHUNKS_IN_FLIGHT];
+            const uint8_t *sp[CHUNKS_IN_FLIGHT];
+            uint8_t *dp[CHUNKS_IN_FLIGHT];
+            int kind[CHUNKS_IN_FLIGHT];                            // 0 nothing, 1 full vector, 2 last piece in parts
+#pragma unroll
+            for (int k = 0; k < CHUNKS_IN_FLIGHT; ++k) {
+                kind[k] = 0;
+                sp[k] = nullptr; dp[k] = nullptr;
+                if (idx < total) {
+                    const uint32_t o = c < cpr ? c * VEC : last_off;
+                    sp[k] = src.remote_rows + mine[m].src_row * src.remote_stride + o;
+                    dp[k] = out + mine[m].out_row * out_stride + o;
+                    kind[k] = (!TAILPIECE || c < cpr) ? 1 : 2;
+                    if (kind[k] == 1) v[k] = *reinterpret_cast<const P *>(sp[k]);
+                }
+                idx += 64;
+                m += dq;
+                c += dr;
+                if (c >= cpt) { c -= cpt; ++m; }
+            }
+#pragma unroll
+            for (int k = 0; k < CHUNKS_IN_FLIGHT; ++k) {
+                if (kind[k] == 1) __builtin_nontemporal_store(v[k], reinterpret_cast<P *>(dp[k]));
+                else if (TAILPIECE && kind[k] == 2) copy_tail<VEC, A>(sp[k], dp[k], tail);
+            }
         }
     }
 }
@@ -145,11 +203,10 @@ static int common_alignment(const RowSources &s, const uint8_t *out, uint64_t ou
     return 1;
 }
 
-rg_status launch_gather(const Routes &routes, int64_t n_rows, const int32_t *list, int64_t n_list, int mode, const RowSources &src,
-                        uint32_t row_bytes, uint8_t *out, uint64_t out_stride, hipStream_t st, int group)
+rg_status launch_gather(const Routes &routes, int64_t n_rows, RowsWanted wanted, const RowSources &src, uint32_t row_bytes, uint8_t *out, uint64_t out_stride,
+                        hipStream_t st, int group)
 {
-    const int64_t n_work = list ? n_list : n_rows;
-    if (n_work <= 0) return RG_OK;
+    if (n_rows <= 0) return RG_OK;
     int align = common_alignment(src, out, out_stride);
     const int vec = align >= 4 ? 16 : 1;                        // dword-aligned rows take 16-byte vectors, anything else goes byte by byte
     const uint32_t tail = row_bytes % (uint32_t)vec;
@@ -163,16 +220,29 @@ rg_status launch_gather(const Routes &routes, int64_t n_rows, const int32_t *lis
     RG_HIP(hipGetDevice(&dev));
     RG_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     // pieces per thread and round: as many as stay in flight, fewer when that would leave compute units without a workgroup
-    const uint64_t total = (uint64_t)n_work * cpt;
+    const uint64_t total = (uint64_t)n_rows * cpt;
     const uint64_t want_blocks = (uint64_t)n_cu * 8;
     int chunks = CHUNKS_IN_FLIGHT;
     while (chunks > 1 && (total + (uint64_t)GATHER_THREADS * chunks - 1) / ((uint64_t)GATHER_THREADS * chunks) < want_blocks) --chunks;
     const uint64_t per_block = (uint64_t)GATHER_THREADS * chunks;
     const uint64_t blocks = std::max<uint64_t>(1, std::min<uint64_t>((total + per_block - 1) / per_block, (uint64_t)n_cu * 32));
+    const int skip_remote = wanted == ROWS_NOT_REMOTE ? 1 : 0;
+    // rows per wave of the remote rows' kernel: two pieces a lane, or a single row, fewer rows where that leaves compute units without waves (rows of
+    // 2,408 bytes, 1,971 us at one row a wave and the link's rate, 1,979 at 32; a list of the misses 1,974)
+    int per_wave = 1;
+    while (per_wave < 64 && per_wave * cpt < 128 && n_rows / (2 * per_wave) >= (int64_t)n_cu * 8) per_wave <<= 1;
+    const int64_t per_remote_block = per_wave * (GATHER_THREADS / 64);
+    const unsigned remote_blocks = (unsigned)std::min<int64_t>((n_rows + per_remote_block - 1) / per_remote_block, (int64_t)n_cu * 32);
     ScopedTimer tm(group, st);
 #define RG_GATHER_ROWS(V, AL, TAIL, ROUTE, FROM)                                                                                              \
-    hipLaunchKernelGGL((gather_rows_kernel<V, AL, TAIL, ROUTE>), dim3((unsigned)blocks), dim3(GATHER_THREADS), 0, st, FROM, routes.last_remote,  \
-                       n_rows, list, n_list, mode, src, row_bytes, out, out_stride, chunks)
+    do {                                                                                                                                      \
+        if (wanted == ROWS_REMOTE)                                                                                                            \
+            hipLaunchKernelGGL((gather_remote_kernel<V, AL, TAIL, ROUTE>), dim3(remote_blocks), dim3(GATHER_THREADS), 0, st, FROM,            \
+                               routes.last_remote, n_rows, per_wave, src, row_bytes, out, out_stride);                                        \
+        else                                                                                                                                  \
+            hipLaunchKernelGGL((gather_rows_kernel<V, AL, TAIL, ROUTE>), dim3((unsigned)blocks), dim3(GATHER_THREADS), 0, st, FROM,           \
+                               routes.last_remote, n_rows, skip_remote, src, row_bytes, out, out_stride, chunks);                             \
+    } while (0)
 #define RG_GATHER_LAUNCH(V, AL)                                                                                                               \
     do {                                                                                                                                      \
         if (tailpiece && routes.entry) RG_GATHER_ROWS(V, AL, true, int64_t, routes.entry);                                                    \
@@ -341,7 +411,7 @@ extern "C" rg_status rg_gather_batch_noalloc(const rg_schedule *s, const rg_cach
     if (m > 0) {
         launch_route(h.ids + off, m, f, c ? c->slot_pairs : nullptr, entry, stats ? counts : nullptr, st);
         RG_HIP(hipGetLastError());
-        RG_TRY(launch_gather(Routes{entry, nullptr, 0}, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, -1));      // (group -1: no event timers, they are created on demand)
+        RG_TRY(launch_gather(Routes{entry, nullptr, 0}, m, ROWS_ALL, src, f->row_bytes, (uint8_t *)out, out_stride, st, -1));      // (group -1: no event timers, they are created on demand)
     }
     RG_HIP(hipGetLastError());
     if (stats) {
@@ -389,17 +459,17 @@ extern "C" rg_status rg_gather_batch(const rg_schedule *s, const rg_cache *c, co
         const bool remote_in_hbm = n_miss > 0 && (f->remote_rows == c->remote_rows_seen ? c->remote_is_device : is_device_memory(f->remote_rows));
         if (n_miss == 0 || remote_in_hbm) {
             // every source is HBM: one launch copies the whole block
-            RG_TRY(launch_gather(routes, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+            RG_TRY(launch_gather(routes, m, ROWS_ALL, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
         } else if (side != st) {
             RG_HIP(hipEventRecord(c->ev_fork, st));            // earlier work on `stream` may still use `out`
             RG_HIP(hipStreamWaitEvent(side, c->ev_fork, 0));
-            RG_TRY(launch_gather(routes, m, plan->miss_rows + plan->miss_off[batch], n_miss, 1, src, f->row_bytes, (uint8_t *)out, out_stride, side, KG_MISS));
+            RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, side, KG_MISS));
             RG_HIP(hipEventRecord(c->ev_join, side));
-            RG_TRY(launch_gather(routes, m, nullptr, 0, 0, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+            RG_TRY(launch_gather(routes, m, ROWS_NOT_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
             RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));
         } else {
-            RG_TRY(launch_gather(routes, m, nullptr, 0, 0, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
-            RG_TRY(launch_gather(routes, m, plan->miss_rows + plan->miss_off[batch], n_miss, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_MISS));
+            RG_TRY(launch_gather(routes, m, ROWS_NOT_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+            RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_MISS));
         }
         s->uses.note(st);                                      // the launches above read the schedule's and the cache's arrays after this call returns
         c->uses.note(st);
@@ -422,7 +492,7 @@ extern "C" rg_status rg_gather_batch(const rg_schedule *s, const rg_cache *c, co
             launch_route(h.ids + off, m, f, c ? c->slot_pairs : nullptr, entry, counts, st);
         }
         RG_HIP(hipGetLastError());
-        RG_TRY(launch_gather(Routes{entry, nullptr, 0}, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+        RG_TRY(launch_gather(Routes{entry, nullptr, 0}, m, ROWS_ALL, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
     }
     if (stats) RG_HIP(hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, st));
     RG_HIP(hipStreamSynchronize(st));
@@ -480,22 +550,15 @@ extern "C" rg_status rg_gather_batches(const rg_schedule *s, const rg_cache *c, 
     const Routes routes = plan_routes(*plan, c, off0);
     const bool remote_in_hbm = n_miss > 0 && (f->remote_rows == c->remote_rows_seen ? c->remote_is_device : is_device_memory(f->remote_rows));
     if (n_miss == 0 || remote_in_hbm) {
-        RG_TRY(launch_gather(routes, m, nullptr, 0, 1, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+        RG_TRY(launch_gather(routes, m, ROWS_ALL, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
     } else {
-        // rows with HBM sources in one launch; every batch's miss list (row indices within its own block) in a launch of its own
+        // rows with HBM sources in one launch, the misses in another
         if (side != st) {
             RG_HIP(hipEventRecord(c->ev_fork, st));
             RG_HIP(hipStreamWaitEvent(side, c->ev_fork, 0));
         }
-        RG_TRY(launch_gather(routes, m, nullptr, 0, 0, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
-        for (uint32_t k = 0; k < n_batches; ++k) {
-            const uint32_t b = first_batch + k;
-            const int64_t nm = plan->miss_off[b + 1] - plan->miss_off[b];
-            if (nm == 0) continue;
-            const int64_t at = h.off_host[b] - off0, mb = h.off_host[b + 1] - h.off_host[b];
-            RG_TRY(launch_gather(plan_routes(*plan, c, h.off_host[b]), mb, plan->miss_rows + plan->miss_off[b], nm, 1, src, f->row_bytes,
-                                 (uint8_t *)out + (uint64_t)at * out_stride, out_stride, side, KG_MISS));
-        }
+        RG_TRY(launch_gather(routes, m, ROWS_NOT_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
+        RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, side, KG_MISS));
         if (side != st) {
             RG_HIP(hipEventRecord(c->ev_join, side));
             RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));

@@ -143,8 +143,7 @@ struct Plan {
     uint64_t schedule_uid = 0;
     uint32_t *code = nullptr;            // dev, [|U_L| total]: routing codes (see below) ...
     int64_t *entry = nullptr;            // ... or, where a row is out of their reach, routing entries: one of the two is set
-    int32_t *miss_rows = nullptr;        // dev, output-row index of every miss, batches concatenated
-    std::vector<int64_t> miss_off;       // host, [beta + 1]
+    std::vector<int64_t> miss_off;       // host, [beta + 1]: misses in front of each batch
     std::vector<rg_gather_stats> stats;  // host, [beta]
 };
 
@@ -228,10 +227,9 @@ struct RowSources {
     const uint8_t *cache_rows; uint64_t cache_stride;
     const uint8_t *remote_rows; uint64_t remote_stride;
 };
-// mode 0: copy rows whose tag is local or cache (skip misses); mode 1: copy every row;
-// list != nullptr: only the rows list[0..n_list) (used for the miss set).
-rg_status launch_gather(const Routes &routes, int64_t n_rows, const int32_t *list, int64_t n_list, int mode,
-                        const RowSources &src, uint32_t row_bytes, uint8_t *out, uint64_t out_stride,
+// Copies the rows [0, n_rows) of `out`: all of them, those that are not remote, or the remote ones alone.
+enum RowsWanted { ROWS_ALL, ROWS_NOT_REMOTE, ROWS_REMOTE };
+rg_status launch_gather(const Routes &routes, int64_t n_rows, RowsWanted wanted, const RowSources &src, uint32_t row_bytes, uint8_t *out, uint64_t out_stride,
                         hipStream_t st, int group);
 
 // A few small values read back from the device behind one stream synchronisation.  They travel through a pinned

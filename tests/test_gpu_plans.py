@@ -27,7 +27,7 @@ def test_counts_and_rows_of_every_batch(rg, n_train, batch, K):
     is_local = (rng.random(n) < 0.25).astype(np.uint8)
     row_of = np.where(is_local, np.cumsum(is_local) - 1, np.cumsum(1 - is_local) - 1).astype(np.int32)
     table = rng.integers(0, 2**31, size=(n, 4)).astype(np.int32)
-    remote = torch.from_numpy(table[is_local == 0]).pin_memory()          # misses go through the miss lists
+    remote = torch.from_numpy(table[is_local == 0]).pin_memory()          # misses are copied by a launch of their own
     feat = rg.make_features(torch.from_numpy(is_local).to(d), torch.from_numpy(row_of).to(d), torch.from_numpy(table[is_local == 1]).to(d), remote, 16)
     cache = rg.rg_build_cache(scheds, feat, K)
     cached = np.zeros(n, bool)
@@ -128,3 +128,38 @@ def test_rows_at_the_end_of_what_a_code_holds(rg, codes, K, at, place, monkeypat
         assert rg.rg_gather_batches(s, cache, feat, 0, s.n_batches, out) == want
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy()[:, 0], value[ids])
+
+
+@pytest.mark.parametrize("row_bytes", [1, 3, 16, 30, 100, 2408, 4100])
+@pytest.mark.parametrize("n,missing", [(1, 1.0), (63, 0.5), (65, 0.0), (5000, 0.01), (5000, 0.5), (40_000, 1.0), (600_000, 0.3)])
+def test_misses_of_a_pinned_table(rg, n, missing, row_bytes):
+    """The launch that finds a batch's misses and copies them: one row to a wave and many, rows of one piece and of several rounds of a
+    wave's pieces, vectors, overlapping last vectors and odd tails; a block per batch and one for all."""
+    if n * row_bytes > 64 << 20:
+        pytest.skip("wide rows at the smaller counts")
+    d = "cuda"
+    rng = np.random.default_rng(n + row_bytes)
+    indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
+    s = rg.rg_build_schedule(indptr, indices, torch.arange(n, dtype=torch.int32, device=d), max(1, n - n // 3), [], 5, 0, 0)
+    is_local = (rng.random(n) >= missing).astype(np.uint8)
+    row_of = np.where(is_local, np.cumsum(is_local) - 1, np.cumsum(1 - is_local) - 1).astype(np.int32)
+    stride = (row_bytes + 15) // 16 * 16 if row_bytes % 4 == 0 else row_bytes
+    table = rng.integers(0, 256, size=(n, stride)).astype(np.uint8)
+    local = torch.from_numpy(np.concatenate([table[is_local == 1], table[:1]])).to(d)
+    remote = torch.from_numpy(np.concatenate([table[is_local == 0], table[:1]])).pin_memory()
+    feat = rg.make_features(torch.from_numpy(is_local).to(d), torch.from_numpy(row_of).to(d), local, remote, row_bytes)
+    cache = rg.rg_build_cache([s], feat, int(0.2 * n))
+    ids, _, off = rg.rg_schedule_frontier(s, 0)
+    ids = ids.cpu().numpy()
+    side = torch.cuda.Stream()
+    for whole in (True, False):
+        out = torch.full((n, stride), 7, dtype=torch.uint8, device=d)
+        if whole:
+            rg.rg_gather_batches(s, cache, feat, 0, s.n_batches, out, side_stream=side)
+        else:
+            for b in range(s.n_batches):
+                rg.rg_gather_batch(s, cache, feat, b, out[off[b]:], out_stride=stride)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert np.array_equal(got[:, :row_bytes], table[ids][:, :row_bytes])
+        assert (got[:, row_bytes:] == 7).all()
