@@ -144,8 +144,9 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_remote_kernel(const ROU
     const uint32_t last_off = TAILPIECE ? cpr * VEC : row_bytes - VEC;
     const uint32_t dq = 64 / cpt, dr = 64 - dq * cpt;
     const int lane = threadIdx.x & 63;
-    Miss *mine = lists[threadIdx.x >> 6];
-    const int64_t n_waves = (int64_t)gridDim.x * (GATHER_THREADS / 64), wave = (int64_t)blockIdx.x * (GATHER_THREADS / 64) + (threadIdx.x >> 6);
+    const int wave_here = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);        // (a scalar: the rounds are the wave's)
+    Miss *mine = lists[wave_here];
+    const int64_t n_waves = (int64_t)gridDim.x * (GATHER_THREADS / 64), wave = (int64_t)blockIdx.x * (GATHER_THREADS / 64) + wave_here;
     for (int64_t first = wave * per_wave; first < n_rows; first += n_waves * per_wave) {
         uint32_t tag = (uint32_t)TAG_LOCAL;
         uint64_t row = 0;

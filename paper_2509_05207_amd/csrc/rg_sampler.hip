@@ -2022,43 +2022,139 @@ static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, 
     return RG_OK;
 }
 
-// The O(f) sampler: one lane per sampled edge.  A node with deg <= f copies its row; otherwise lane t reads the
-// row at its drawn position (rg_device.h) and nothing else of the row.  Lanes of a workgroup are dealt to
-// (node, draw) pairs: 256 / f nodes per round when f < 256, one node per round otherwise.
-// BY_PLACE (see ByPlace): an instantiation of its own, since the look at every unit's batch costs the other (111 M nodes, fan-outs 15, 10 362 us
-// without, 382 with it; 50, 3 289 and 315).
+// The O(f) sampler.  A node with deg <= f copies its row; otherwise draw t reads the row at its drawn position (rg_device.h) and
+// nothing else of the row.
+//
+// Bound by the walks of the drawn positions, some 110 vector instructions a step, and by the lines of the rows' IDs.  A walk takes 1.4 steps on
+// average, but the longest of 64 takes four to six, which is what a lane per draw waits for.  So a wave takes a unit of nodes, up to
+// POS_DRAWS draws, lists the draws that walk and deals them out to its lanes as they come free; positions are kept in LDS, and
+// the rows read at all of them afterwards (233,000 nodes, 147 batches, fan-outs 25, 10, 29 M draws: a lane per draw / so 452 / 343 us).
+// BY_PLACE (see ByPlace): an instantiation of its own, since the look at every unit's batch costs the other (with a lane per draw: 111 M nodes, fan-outs
+// 15, 10 362 us without, 382 with it; 50, 3 289 and 315).
 constexpr int POS_THREADS = 256;
+constexpr int POS_WAVES = POS_THREADS / 64;
+constexpr int POS_DRAWS = 256;           // positions of a wave in LDS (the launch of 25 M draws with 64 / 128 / 256 / 384 / 512: 468 / 346 / 292 / 318 / 328 us)
+constexpr int POS_LEAST = 64;            // draws per unit, at least, where there are few (see sample_hop)
+constexpr int POS_IN_FLIGHT = 4;
+struct PosNode {
+    uint64_t state;
+    int64_t row_begin, out;
+    uint32_t deg, batch;
+};
 template <int MARK, bool BY_PLACE>
-__global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int32_t *__restrict__ indices, NodeRecs rec, int64_t n_cur, uint32_t f,
+__global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int32_t *__restrict__ indices, NodeRecs rec, int64_t n_cur, uint32_t f, uint32_t unit_nodes,
                                                                        const int64_t *__restrict__ samp_off, int32_t *__restrict__ samp_nbr,
                                                                        ReachedMaps reached, ByPlace place, int64_t n_units)
 {
-    const uint32_t per_round = f >= POS_THREADS ? 1u : POS_THREADS / f;       // nodes per workgroup round
-    const uint32_t sub = f >= POS_THREADS ? 0u : threadIdx.x / f;              // this lane's node within the round
-    const uint32_t t0 = f >= POS_THREADS ? threadIdx.x : threadIdx.x - sub * f;
-    const uint32_t step = f >= POS_THREADS ? POS_THREADS : f;                  // a lane's next draw of the same node
-    if (sub >= per_round) return;
-    const int64_t first = (int64_t)blockIdx.x * (BY_PLACE ? 1 : per_round) + (BY_PLACE ? 0 : sub), end = BY_PLACE ? n_units : n_cur;
-    const int64_t stride = (int64_t)gridDim.x * (BY_PLACE ? 1 : per_round);
-    for (int64_t at = first; at < end; at += stride) {                         // units, or this lane's nodes
-        int64_t i = at;
+    __shared__ PosNode all_nodes[POS_WAVES][64];
+    __shared__ uint32_t all_pos[POS_WAVES][POS_DRAWS];
+    __shared__ uint16_t all_walks[POS_WAVES][POS_DRAWS];
+    constexpr uint32_t NO_DRAW = 0xFFFFFFFFu;                                  // (no position: rows are shorter than 2^31)
+    const int lane = threadIdx.x & 63;
+    const int wave = uni((int)threadIdx.x >> 6);
+    PosNode *nodes = all_nodes[wave];
+    uint32_t *pos = all_pos[wave];
+    uint16_t *walks = all_walks[wave];
+    const float per_node = 1.0f / (float)f;
+    // draw d of the unit: node d / f, and its draw number (exact: where a unit has several nodes, d + 1/2 below 2^8 is 1/256 of a node or more away from any edge)
+    auto node_of = [&](uint32_t d) { return unit_nodes == 1 ? 0u : (uint32_t)(((float)d + 0.5f) * per_node); };
+    for (int64_t at = (int64_t)blockIdx.x * POS_WAVES + wave; at < n_units; at += (int64_t)gridDim.x * POS_WAVES) {
+        int64_t i0 = at * unit_nodes, i_end = n_cur;
         if (BY_PLACE) {
             const uint32_t round = (uint32_t)at / place.n_batches, b = (uint32_t)at - round * place.n_batches;
-            i = place.batch_off[b] + (int64_t)round * per_round + sub;
-            if (i >= place.batch_off[b + 1]) continue;
+            i0 = place.batch_off[b] + (int64_t)round * unit_nodes;
+            i_end = place.batch_off[b + 1];
         }
-        const uint32_t deg = (uint32_t)rec.deg[i];
-        const uint32_t cnt = deg < f ? deg : f;
-        if (t0 >= cnt) continue;
-        const int32_t *row = indices + rec.row_begin[i];
-        const uint64_t S = rec.state[i];
-        int32_t *out = samp_nbr + samp_off[i];
-        const ReachedOfBatch reached_b = reached_of<MARK>(reached, rec.batch[i]);
-        for (uint32_t t = t0; t < cnt; t += step) {
-            const uint32_t p = deg <= f ? t : draw_position(deg, t, S);
-            const int32_t u = row[p];
-            out[t] = u;
-            mark_reached<MARK>(reached_b, (uint32_t)u);
+        if (i0 >= i_end) continue;
+        const uint32_t n_nodes = (uint32_t)min((int64_t)unit_nodes, i_end - i0), n_draws = n_nodes * f;
+        wave_lds_order();                                                      // the last unit's have been read
+        uint32_t my_deg = 0;
+        if ((uint32_t)lane < n_nodes) {
+            const int64_t i = i0 + lane;
+            my_deg = (uint32_t)rec.deg[i];
+            nodes[lane] = PosNode{rec.state[i], rec.row_begin[i], samp_off[i], my_deg, rec.batch[i]};
+        }
+        const bool selects = my_deg > f && my_deg <= DRAW_SELECT;
+        wave_lds_order();
+        for (uint32_t d0 = 0; d0 < n_draws; d0 += POS_DRAWS) {
+            const uint32_t n = uni(min((uint32_t)POS_DRAWS, n_draws - d0));
+            uint32_t n_walks = 0;
+            for (uint32_t q0 = 0; q0 < n; q0 += 64) {
+                const uint32_t j = q0 + lane;
+                bool walk = false;
+                if (j < n) {
+                    const uint32_t k = node_of(d0 + j), t = d0 + j - k * f, deg = nodes[k].deg;
+                    walk = deg > f && deg > DRAW_SELECT;
+                    if (!walk) pos[j] = deg > f ? draw32(nodes[k].state, t) : t < deg ? t : NO_DRAW;
+                }
+                const unsigned long long m = ballot64(walk);
+                if (walk) walks[n_walks + lanes_below(m, lane)] = (uint16_t)j;
+                n_walks = uni(n_walks + (uint32_t)__popcll(m));
+            }
+            wave_lds_order();
+            // Rows selected from: the draws of a node follow from one another, so a node's lane goes through them, the random words at hand (a lane
+            // per draw that repeated all draws before its own / so, schedules of 2.45 M nodes, fan-outs 15, 10, 5 3,440 / 2,478 us, 50, 50 4,352 / 3,099).
+            if (selects) {
+                uint64_t free_slots = low_lanes((int)my_deg);
+                for (uint32_t t = 0; t < f; ++t) {                             // (a unit of such rows is one round: f < DRAW_SELECT)
+                    const uint32_t p = nth_set_bit(free_slots, __umulhi(pos[lane * f + t], my_deg - t));
+                    free_slots &= ~(1ull << p);
+                    pos[lane * f + t] = p;
+                }
+            }
+            // One step of every lane's walk; lanes whose walk has ended take the next ones of the list.  All lanes go round together until the last
+            // walk has ended: the counts are the wave's, in scalar registers, and the barrier at the loop's end is its one way back (with a way back
+            // for lanes that walk on, the compiler made a loop of its own of it, in which they went round without the others).
+            uint32_t next = 64, left = n_walks, j = 0, deg = 0, n_bits = 0, x = 0;
+            uint64_t S = 0;
+            auto take = [&](uint32_t w) {
+                j = walks[w];
+                const uint32_t k = node_of(d0 + j);
+                x = d0 + j - k * f;
+                deg = nodes[k].deg;
+                S = nodes[k].state;
+                n_bits = 32u - (uint32_t)__clz((int)(deg - 1u));
+            };
+            bool on = (uint32_t)lane < n_walks;
+            if (on) take((uint32_t)lane);
+            while (left != 0u) {
+                bool ended = false;
+                if (on) {
+                    x = feistel(x, n_bits, S);
+                    ended = x < deg;
+                    if (ended) pos[j] = x;
+                }
+                const unsigned long long m = ballot64(ended);
+                const uint32_t w = next + (uint32_t)lanes_below(m, lane);
+                const uint32_t n_ended = (uint32_t)__popcll(m);
+                next = uni(next + n_ended);
+                left = uni(left - n_ended);
+                if (ended) {
+                    on = w < n_walks;
+                    if (on) take(w);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            wave_lds_order();
+            for (uint32_t q0 = 0; q0 < n; q0 += 64 * POS_IN_FLIGHT) {
+                int32_t u[POS_IN_FLIGHT];
+                uint32_t k[POS_IN_FLIGHT], p[POS_IN_FLIGHT];
+#pragma unroll
+                for (int q = 0; q < POS_IN_FLIGHT; ++q) {
+                    const uint32_t jq = q0 + 64 * q + lane;
+                    p[q] = jq < n ? pos[jq] : NO_DRAW;
+                    k[q] = jq < n ? node_of(d0 + jq) : 0u;
+                    if (p[q] != NO_DRAW) u[q] = indices[nodes[k[q]].row_begin + p[q]];
+                }
+#pragma unroll
+                for (int q = 0; q < POS_IN_FLIGHT; ++q)
+                    if (p[q] != NO_DRAW) {
+                        const uint32_t d = d0 + q0 + 64 * q + lane;
+                        samp_nbr[nodes[k[q]].out + (d - k[q] * f)] = u[q];
+                        mark_reached<MARK>(reached_of<MARK>(reached, nodes[k[q]].batch), (uint32_t)u[q]);
+                    }
+            }
+            wave_lds_order();                                                  // the positions have been read
         }
     }
 }
@@ -2292,10 +2388,15 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     if (sampler == RG_SAMPLER_POSITIONS) {
         if (fanout > 0 && n_cur > 0) {
             ScopedTimer tm(KG_SAMPLER, st);
-            const int64_t per_round = fanout >= (uint32_t)POS_THREADS ? 1 : POS_THREADS / fanout;
-            const int64_t n_units = place.n_batches ? (place.longest + per_round - 1) / per_round * beta : (n_cur + per_round - 1) / per_round;
-            const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_units, (int64_t)n_cu * 64));
-#define RG_POSITIONS(M, P) hipLaunchKernelGGL((sample_positions_kernel<M, P>), dim3(grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, cur.samp_off, cur.samp_nbr, reached, place, n_units)
+            // as many draws to a unit as a wave has room for, or as few as give every wave that the chip holds a unit
+            const int64_t waves = (int64_t)n_cu * 32;
+            int64_t draws = POS_DRAWS;
+            while (draws > POS_LEAST && n_cur * fanout < draws * waves) draws /= 2;
+            const uint32_t unit_nodes = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(64, draws / fanout));
+            const int64_t n_units = place.n_batches ? (place.longest + unit_nodes - 1) / unit_nodes * beta : (n_cur + unit_nodes - 1) / unit_nodes;
+            // (a wave per unit: waves that walk over the units by turns drift apart, and with them what they read: 312 us)
+            const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_units + POS_WAVES - 1) / POS_WAVES, 0x7FFFFFFF));
+#define RG_POSITIONS(M, P) hipLaunchKernelGGL((sample_positions_kernel<M, P>), dim3(grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, unit_nodes, cur.samp_off, cur.samp_nbr, reached, place, n_units)
             if (inline_marks && place.n_batches) RG_POSITIONS(MARK_BITS, true);
             else if (inline_marks) RG_POSITIONS(MARK_BITS, false);
             else if (place.n_batches) RG_POSITIONS(MARK_NONE, true);

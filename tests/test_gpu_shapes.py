@@ -135,3 +135,23 @@ def test_rows_of_several_tiles(rg, orc, group_tiles, mark_pass, monkeypatch):
         so, nb = o.samples(hop)
         gso, gnb = rg.rg_schedule_samples(g, hop)
         assert np.array_equal(gso.cpu().numpy(), so) and np.array_equal(gnb.cpu().numpy(), nb), f"samples {hop}"
+
+
+@pytest.mark.parametrize("fanouts", [(300, 3), (512, 2), (513,), (1024, 1), (256, 7), (8, 9), (1, 2, 3), (64, 17), (1984,)])
+def test_walks_dealt_out_to_lanes(fanouts, rg, orc):
+    """The O(f) sampler's units: one node's draws in one and several rounds of its room for positions, several nodes' and as many as a wave has
+    lanes, more walks than lanes and fewer; rows around the fan-out, of up to 64 IDs, and just above powers of two, whose walks are long."""
+    rng = np.random.default_rng(sum(fanouts))
+    classes = [(0, 3, 1), (60, 64, 1), (65, 65, 1), (129, 130, 2), (257, 260, 2), (513, 530, 2), (1025, 1100, 1), (2049, 2100, 1)]
+    indptr, indices = random_graph(rng, 2500, classes)
+    train = rng.permutation(2500)[:700].astype(np.int32)
+    o = orc.Schedule(indptr, indices, train, 200, list(fanouts), 11, 2, 3, n_threads=8, sampler="positions")
+    d = "cuda"
+    g = rg.rg_build_schedule_with(torch.from_numpy(indptr).to(d), torch.from_numpy(indices).to(d), torch.from_numpy(train).to(d), 200, list(fanouts), 11, 2, 3,
+                                  sampler=rg.RG_SAMPLER_POSITIONS)
+    for hop in range(o.L + 1):
+        assert np.array_equal(rg.rg_schedule_frontier(g, hop)[0].cpu().numpy(), o.frontier(hop)[0])
+    for hop in range(o.L):
+        so, nbr = rg.rg_schedule_samples(g, hop)
+        oso, onbr = o.samples(hop)
+        assert np.array_equal(so.cpu().numpy(), oso) and np.array_equal(nbr.cpu().numpy(), onbr)
