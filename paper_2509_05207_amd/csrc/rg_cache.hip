@@ -27,12 +27,12 @@ __global__ void tally_kernel(const int32_t *__restrict__ ids, int64_t n, F *__re
     }
 }
 
-// freq += the frequencies an epoch's schedule already holds (computed from its bitmaps when it was built)
-template <typename F>
+// freq += the frequencies an epoch's schedule already holds (computed from its bitmaps when it was built); FIRST: freq holds nothing yet
+template <typename F, bool FIRST>
 __global__ void add_epoch_freq_kernel(const uint32_t *__restrict__ epoch_freq, int64_t n, F *__restrict__ freq)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) freq[i] = (F)(freq[i] + epoch_freq[i]);
+    if (i < n) freq[i] = (F)((FIRST ? 0u : (uint32_t)freq[i]) + epoch_freq[i]);
 }
 
 // The uint8_t tally as the uint32_t array the cache's view hands out (made when first asked for).
@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) select_scan_tiles(uint64_t *__re
         if (i0 + k < n_blocks) block_tot[i0 + k] = run;
         run += x[k];
     }
-    if (threadIdx.x == 0) tile_tot[blockIdx.x] = tot;
+    if (threadIdx.x == 0) tile_tot[blockIdx.x] = gridDim.x > 1 ? tot : 0;      // (a single tile has nothing in front: no second level)
 }
 
 // One workgroup; a thread takes eight consecutive totals per round.
@@ -760,7 +760,7 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
     void *tally = nullptr;
     RG_TRY(c->arena.dev(tally_bytes ? tally_bytes : 16, &tally));
     if (narrow) c->freq8 = (uint8_t *)tally; else c->freq = (uint32_t *)tally;
-    RG_HIP(hipMemsetAsync(tally, 0, tally_bytes, st));
+    bool counted = false;                                // the tally holds counts (or zeros)
     for (uint32_t e = 0; e < n_epochs; ++e) {
         const rg_schedule *s = epochs[e];
         if (s->n_batches == 0) continue;
@@ -770,14 +770,20 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
         ScopedTimer tm(KG_HIST, st);
         if (s->epoch_freq) {
             const dim3 grid((unsigned)((n + 255) / 256));
-            if (narrow) hipLaunchKernelGGL(add_epoch_freq_kernel<uint8_t>, grid, dim3(256), 0, st, s->epoch_freq, n, c->freq8);
-            else hipLaunchKernelGGL(add_epoch_freq_kernel<uint32_t>, grid, dim3(256), 0, st, s->epoch_freq, n, c->freq);
+            if (narrow && counted) hipLaunchKernelGGL((add_epoch_freq_kernel<uint8_t, false>), grid, dim3(256), 0, st, s->epoch_freq, n, c->freq8);
+            else if (narrow) hipLaunchKernelGGL((add_epoch_freq_kernel<uint8_t, true>), grid, dim3(256), 0, st, s->epoch_freq, n, c->freq8);
+            else if (counted) hipLaunchKernelGGL((add_epoch_freq_kernel<uint32_t, false>), grid, dim3(256), 0, st, s->epoch_freq, n, c->freq);
+            else hipLaunchKernelGGL((add_epoch_freq_kernel<uint32_t, true>), grid, dim3(256), 0, st, s->epoch_freq, n, c->freq);
+            counted = true;
             continue;
         }
+        if (!counted) RG_HIP(hipMemsetAsync(tally, 0, tally_bytes, st));
+        counted = true;
         const unsigned grid = (unsigned)std::min<int64_t>((m + 255) / 256, (int64_t)n_cu * 32);
         if (narrow) hipLaunchKernelGGL(tally_kernel<uint8_t>, dim3(grid), dim3(256), 0, st, h.ids, m, c->freq8);
         else hipLaunchKernelGGL(tally_kernel<uint32_t>, dim3(grid), dim3(256), 0, st, h.ids, m, c->freq);
     }
+    if (!counted) RG_HIP(hipMemsetAsync(tally, 0, tally_bytes, st));
     RG_HIP(hipGetLastError());
 
     // ---- a7: TopHot
@@ -820,7 +826,7 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
             else if (local8) hipLaunchKernelGGL((select_block_totals<true, uint32_t>), sg, sb, 0, st, c->freq, f->is_local, n, stp, block_tot);
             else hipLaunchKernelGGL((select_block_totals<false, uint32_t>), sg, sb, 0, st, c->freq, f->is_local, n, stp, block_tot);
             hipLaunchKernelGGL(select_scan_tiles, dim3((unsigned)sel_tiles), dim3(TOPK_THREADS), 0, st, block_tot, sel_blocks, tile_tot);
-            hipLaunchKernelGGL(select_scan_totals, dim3(1), dim3(TOPK_THREADS), 0, st, tile_tot, sel_tiles);
+            if (sel_tiles > 1) hipLaunchKernelGGL(select_scan_totals, dim3(1), dim3(TOPK_THREADS), 0, st, tile_tot, sel_tiles);
         }
     }
     SelectState hs;

@@ -2341,8 +2341,10 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     const int n_sums = look_for_hubs ? DEG_SUMS : DEG_SUMS - 1;
     const size_t sum_bytes = (size_t)n_sums * DEG_SUM_SLOTS * sizeof(unsigned long long);
     const size_t hub_cleared = look_for_hubs ? sizeof(HubCounts) + HUB_SLOTS * sizeof(uint32_t) : 0;      // behind the sums, cleared with them
-    RG_TRY(tmp.dev(sum_bytes + hub_cleared, (void **)&sum_deg_dev));
-    RG_HIP(hipMemsetAsync(sum_deg_dev, 0, sum_bytes + hub_cleared, st));
+    unsigned long long *next_work = nullptr;                              // the sampling launch's work counter, cleared with them too (sixteen bytes in front)
+    RG_TRY(tmp.dev(2 * sizeof(unsigned long long) + sum_bytes + hub_cleared, (void **)&next_work));
+    RG_HIP(hipMemsetAsync(next_work, 0, 2 * sizeof(unsigned long long) + sum_bytes + hub_cleared, st));
+    sum_deg_dev = next_work + 2;
     if (look_for_hubs) {
         hubs.counts = reinterpret_cast<HubCounts *>(sum_deg_dev + DEG_SUMS * DEG_SUM_SLOTS);
         hubs.keys = reinterpret_cast<uint32_t *>(hubs.counts + 1);
@@ -2483,9 +2485,6 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
         bool short_rows = sums[2] != 0;
         if (const char *force = getenv("RAPIDGNN_SHORT_ROWS")) short_rows = force[0] != '0';
         const uint32_t need = fanout + 64;
-        unsigned long long *next_work = nullptr;
-        RG_TRY(tmp.dev_n<unsigned long long>(1, &next_work));
-        RG_HIP(hipMemsetAsync(next_work, 0, sizeof(unsigned long long), st));
         int merge_span = 64;                              // tiles per look of a merging wave: 64 if that still occupies the chip's waves
         while (merge_span > 1 && n_tiles / merge_span < (int64_t)n_cu * 32) merge_span >>= 1;
         const unsigned merge_grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_tiles + merge_span - 1) / merge_span, (int64_t)n_cu * 64));

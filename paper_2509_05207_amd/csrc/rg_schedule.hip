@@ -30,10 +30,12 @@ static uint64_t worker_stream(uint64_t s0, uint32_t worker) { return combine(mix
 static uint64_t epoch_stream(uint64_t s0, uint32_t worker, uint32_t epoch) { return combine(worker_stream(s0, worker), epoch); }
 static uint64_t shuffle_stream(uint64_t s0, uint32_t worker, uint32_t epoch) { return combine(worker_stream(s0, worker), ((uint64_t)1 << 32) + epoch); }
 
-__global__ void batch_seeds_kernel(uint64_t epoch_state, uint32_t n_batches, uint64_t *__restrict__ seeds)
+// The batches' states, and where each begins among the seeds (off[n_batches]: where the last one ends).
+__global__ void batch_seeds_kernel(uint64_t epoch_state, uint32_t n_batches, uint64_t batch_size, uint64_t T, uint64_t *__restrict__ seeds, int64_t *__restrict__ off)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n_batches) seeds[i] = combine(epoch_state, i);
+    if (i <= n_batches) off[i] = (int64_t)min((uint64_t)i * batch_size, T);
 }
 
 // Shuffle: train position t gets key combine(P_e, t); the epoch's order is ascending (key, t).
@@ -87,9 +89,20 @@ __global__ void shuffle_scatter_kernel(uint64_t P, uint64_t T, uint32_t bucket_b
 constexpr int RANK_THREADS = 256;
 constexpr int RANK_TILE = 1024;      // entries of a bucket in LDS at a time (16 KB)
 
-// One workgroup per bucket: seeds[first + rank(x)] = train[x.pos] for every entry x of the bucket.
+// Where the seeds are marked: the `seen` bitmaps (words NULL: no hops, no marks).
+struct SeedMarks {
+    uint32_t *seen;               // paired: the first group's `seen` half of the paired records (see paired_word)
+    uint8_t *seen_flags;          // NULL in the large-graph form: see clear_listed_seen_kernel
+    uint64_t words_per_batch;
+    int64_t n_nodes;
+    uint32_t batch_size;
+    int paired;
+};
+
+// One workgroup per bucket: seeds[first + rank(x)] = train[x.pos] for every entry x of the bucket, and marks it as its batch's.
+// (The marks as a launch of their own: 7 us of 230,000 seeds, 19 on 111 M nodes.)
 __global__ void __launch_bounds__(RANK_THREADS) shuffle_rank_kernel(const KeyPos *__restrict__ kp, const int64_t *__restrict__ bucket_off,
-                                                                    const int32_t *__restrict__ train, int32_t *__restrict__ seeds)
+                                                                    const int32_t *__restrict__ train, int32_t *__restrict__ seeds, SeedMarks marks)
 {
     __shared__ KeyPos tile[RANK_TILE];
     const int64_t first = bucket_off[blockIdx.x], n = bucket_off[blockIdx.x + 1] - first;
@@ -97,6 +110,7 @@ __global__ void __launch_bounds__(RANK_THREADS) shuffle_rank_kernel(const KeyPos
         const int64_t e = e0 + threadIdx.x;
         const bool have = e < n;
         KeyPos mine = have ? kp[first + e] : KeyPos{0, 0};
+        const uint32_t v = have ? (uint32_t)train[mine.pos] : 0u;
         int64_t rank = 0;
         for (int64_t j0 = 0; j0 < n; j0 += RANK_TILE) {
             const int m = (int)(n - j0 < RANK_TILE ? n - j0 : RANK_TILE);
@@ -106,21 +120,15 @@ __global__ void __launch_bounds__(RANK_THREADS) shuffle_rank_kernel(const KeyPos
             if (have)
                 for (int j = 0; j < m; ++j) rank += kp_less(tile[j], mine) ? 1 : 0;
         }
-        if (have) seeds[first + rank] = train[mine.pos];
+        if (!have) continue;
+        const uint64_t t = (uint64_t)(first + rank);
+        seeds[t] = (int32_t)v;
+        if (marks.seen && (int64_t)v < marks.n_nodes) {                // (a build with other values is refused as soon as the host has read shuffle_count_kernel's count)
+            const uint64_t word = (t / marks.batch_size) * marks.words_per_batch + (v >> 5);
+            atomicOr(&marks.seen[marks.paired ? paired_word(word) : word], 1u << (v & 31));
+            if (marks.seen_flags) marks.seen_flags[word >> 3] = 1;
+        }
     }
-}
-
-// paired: `seen` points at the first group's `seen` half of the paired records (see paired_word)
-__global__ void mark_seeds_kernel(const int32_t *__restrict__ seeds, uint64_t T, uint32_t batch_size, uint32_t *__restrict__ seen,
-                                  uint8_t *__restrict__ seen_flags, uint64_t words_per_batch, int64_t n_nodes, int paired)
-{
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    const uint32_t v = (uint32_t)seeds[t];
-    if ((int64_t)v >= n_nodes) return;          // (refused by the host as soon as it has read shuffle_count_kernel's count)
-    const uint64_t word = (t / batch_size) * words_per_batch + (v >> 5);
-    atomicOr(&seen[paired ? paired_word(word) : word], 1u << (v & 31));
-    if (seen_flags) seen_flags[word >> 3] = 1;          // (NULL in the large-graph form: see clear_listed_seen_kernel)
 }
 
 // ---------------------------------------------------------------- a6 (first half): freq(v) of the epoch as column sums
@@ -136,13 +144,16 @@ constexpr int FREQ_PLANES = 16;          // counts up to 65,535 batches
 constexpr int FREQ_SLICES = 8;
 constexpr int FREQ_IN_FLIGHT = 8;
 constexpr int FREQ_WORDS = 64;           // positions of a workgroup, one per lane
+// It is the last to read the bitmaps, and leaves them and their flags clear for the next build (a fill each, 2 to 10 us, before).
 template <int PLANES>
-__global__ void __launch_bounds__(FREQ_SLICES * FREQ_WORDS) epoch_freq_kernel(const uint32_t *__restrict__ seen, uint64_t words_per_batch, uint32_t n_batches, int64_t n_nodes,
-                                                                             uint32_t *__restrict__ freq)
+__global__ void __launch_bounds__(FREQ_SLICES * FREQ_WORDS) epoch_freq_kernel(uint32_t *__restrict__ seen, uint8_t *__restrict__ seen_flags, uint64_t words_per_batch, uint32_t n_batches,
+                                                                             int64_t n_nodes, uint32_t *__restrict__ freq)
 {
     __shared__ uint32_t sums[FREQ_SLICES / 2][PLANES][FREQ_WORDS];
     const uint32_t lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
-    const uint32_t *from = seen + (uint64_t)blockIdx.x * FREQ_WORDS + lane;
+    uint32_t *from = seen + (uint64_t)blockIdx.x * FREQ_WORDS + lane;
+    static_assert(FREQ_WORDS == 8 * sizeof(uint64_t), "a workgroup's flags of a batch are one word of eight");
+    uint64_t *flags = reinterpret_cast<uint64_t *>(seen_flags) + blockIdx.x;               // (words_per_batch is a multiple of 64)
     uint32_t plane[PLANES];
 #pragma unroll
     for (int k = 0; k < PLANES; ++k) plane[k] = 0;
@@ -152,6 +163,12 @@ __global__ void __launch_bounds__(FREQ_SLICES * FREQ_WORDS) epoch_freq_kernel(co
         for (int q = 0; q < FREQ_IN_FLIGHT; ++q) {
             const uint32_t b = b0 + q * FREQ_SLICES;
             word[q] = b < n_batches ? from[(uint64_t)b * words_per_batch] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < FREQ_IN_FLIGHT; ++q) {
+            const uint32_t b = b0 + q * FREQ_SLICES;
+            if (word[q] != 0u) from[(uint64_t)b * words_per_batch] = 0u;
+            if (b < n_batches && lane == 0) flags[(uint64_t)b * (words_per_batch / FREQ_WORDS)] = 0ull;
         }
 #pragma unroll
         for (int q = 0; q < FREQ_IN_FLIGHT; ++q) {
@@ -621,7 +638,6 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
     // ---- a1: batch seeds
     uint64_t *batch_seed = nullptr;
     RG_TRY(tmp.dev_n<uint64_t>(beta ? beta : 1, &batch_seed));
-    if (beta) hipLaunchKernelGGL(batch_seeds_kernel, dim3((beta + 255) / 256), dim3(256), 0, st, epoch_stream(s0, worker, epoch), beta, batch_seed);
 
     // ---- a2: shuffle and cut into batches
     HopData &h0 = s->hop[0];
@@ -629,7 +645,7 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
     RG_TRY(s->arena.dev_n<int64_t>((uint64_t)beta + 1, &h0.off_dev));
     h0.off_host.resize((size_t)beta + 1);
     for (uint32_t b = 0; b <= beta; ++b) h0.off_host[b] = (int64_t)std::min<uint64_t>((uint64_t)b * B, T);
-    RG_HIP(hipMemcpyAsync(h0.off_dev, h0.off_host.data(), ((size_t)beta + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(batch_seeds_kernel, dim3(beta / 256 + 1), dim3(256), 0, st, epoch_stream(s0, worker, epoch), beta, (uint64_t)B, T, batch_seed, h0.off_dev);
     // cleared together: the count of bad train nodes, the bit per node of the check, the shuffle's bucket counts
     uint32_t bucket_bits = 0;                  // about a hundred positions per bucket, a power of two of buckets
     while (bucket_bits < 20 && ((uint64_t)128 << bucket_bits) < T) ++bucket_bits;
@@ -645,6 +661,47 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
         set_error("rg_build_schedule: %llu of the %llu train nodes are outside [0, n_nodes) or repeated", n_bad_host, (unsigned long long)T);
         return RG_EINVAL;
     };
+    // ---- bitmaps (n_nodes bits per batch, rounded up to whole 8-word groups)
+    const uint64_t wpb = (((uint64_t)g->n_nodes + 31) / 32 + FRS_WORDS_PER_THREAD - 1) / FRS_WORDS_PER_THREAD * FRS_WORDS_PER_THREAD;
+    bool sparse_maps = wpb >= ((uint64_t)1 << 18);                           // 8.4 M nodes and up: a batch leaves most groups untouched
+    if (const char *force = getenv("RAPIDGNN_SPARSE_FRONTIER")) sparse_maps = force[0] == '1';   // same results either way; for tests and tuning
+    const uint32_t chunk_words = sparse_maps ? FRS_CHUNK_WORDS : FR_CHUNK_WORDS;
+    const uint32_t chunks = (uint32_t)((wpb + chunk_words - 1) / chunk_words);
+    // The maps come from the pool of all-zero blocks and go back to it: every hop's frontier pass clears what the hop
+    // marked in `reached` and its flags, and `seen` is cleared at the end group by group (seen_flags says which), so a
+    // build clears what it touched, not n_batches * n_nodes bits (2 GB a map on a graph of 10^8 nodes).
+    uint32_t *seen = nullptr, *reached_words = nullptr;
+    uint8_t *reached_flags = nullptr;                  // one byte per group of 256 IDs of `reached`
+    uint8_t *seen_flags = nullptr;                     // the same for `seen`: groups that hold any bit
+    const uint64_t n_groups = wpb / FR_WORDS_PER_THREAD * beta;          // (a multiple of eight: wpb is a multiple of 64)
+    uint32_t *paired = nullptr;                        // the large-graph form: both maps in one array of records (see paired_word)
+    if (L > 0 && beta > 0) {
+        if (sparse_maps) {
+            RG_TRY(tmp.dev_zeroed(2 * wpb * beta * sizeof(uint32_t), (void **)&paired, st));
+            reached_words = paired;
+            seen = paired + FR_WORDS_PER_THREAD;
+        } else {
+            RG_TRY(tmp.dev_zeroed(wpb * beta * sizeof(uint32_t), (void **)&seen, st));
+            RG_TRY(tmp.dev_zeroed(wpb * beta * sizeof(uint32_t), (void **)&reached_words, st));
+        }
+        RG_TRY(tmp.dev_zeroed(n_groups, (void **)&reached_flags, st));
+        if (!sparse_maps) RG_TRY(tmp.dev_zeroed(n_groups, (void **)&seen_flags, st));
+        if (const char *check = getenv("RAPIDGNN_CHECK_ZERO_MAPS"); check && check[0] == '1') {
+            // for tests: the maps, wherever they came from, really hold nothing but zeros (the pool of all-zero blocks keeps its promise)
+            unsigned long long *n_dev = nullptr, n_host = 0;
+            RG_TRY(tmp.dev_n<unsigned long long>(1, &n_dev));
+            RG_HIP(hipMemsetAsync(n_dev, 0, sizeof(unsigned long long), st));
+            const struct { const void *p; uint64_t bytes; } parts[4] = {{paired ? nullptr : seen, paired ? 0 : wpb * beta * 4}, {reached_words, wpb * beta * (paired ? 8u : 4u)},
+                                                                        {reached_flags, n_groups}, {seen_flags, seen_flags ? n_groups : 0}};
+            for (const auto &part : parts)
+                if (part.bytes)
+                    hipLaunchKernelGGL(count_nonzero_kernel, dim3(1024), dim3(256), 0, st, (const unsigned long long *)part.p, part.bytes / 8, n_dev);
+            Readback rb(st);
+            RG_TRY(rb.add(&n_host, n_dev, sizeof(n_host)));
+            RG_TRY(rb.wait());
+            if (n_host != 0) { set_error("rg_build_schedule: %llu words of the per-batch maps are not zero at the start of the build", n_host); return RG_EHIP; }
+        }
+    }
     if (T > 0) {
         KeyPos *kp = nullptr;
         int32_t *place = h0.ids;               // (the seeds are written by the last of the three kernels, the places read by the one before)
@@ -658,7 +715,8 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
             hipLaunchKernelGGL(shuffle_count_kernel, dim3(blocks), dim3(256), 0, st, P, T, bucket_bits, bucket_cnt, place, train, (int64_t)g->n_nodes, once, n_bad_train);
             RG_TRY(scan_i32_to_i64(bucket_cnt, bucket_off, (int64_t)n_buckets, tmp, st));
             hipLaunchKernelGGL(shuffle_scatter_kernel, dim3(blocks), dim3(256), 0, st, P, T, bucket_bits, bucket_off, place, kp);
-            hipLaunchKernelGGL(shuffle_rank_kernel, dim3((unsigned)n_buckets), dim3(RANK_THREADS), 0, st, kp, bucket_off, train, h0.ids);
+            hipLaunchKernelGGL(shuffle_rank_kernel, dim3((unsigned)n_buckets), dim3(RANK_THREADS), 0, st, kp, bucket_off, train, h0.ids,
+                               SeedMarks{seen, seen_flags, wpb, (int64_t)g->n_nodes, B, sparse_maps ? 1 : 0});
         }
         RG_HIP(hipGetLastError());
     }
@@ -682,50 +740,7 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
         return refuse_bad_train();
     }
 
-    // ---- bitmaps (n_nodes bits per batch, rounded up to whole 8-word groups)
-    const uint64_t wpb = (((uint64_t)g->n_nodes + 31) / 32 + FRS_WORDS_PER_THREAD - 1) / FRS_WORDS_PER_THREAD * FRS_WORDS_PER_THREAD;
-    bool sparse_maps = wpb >= ((uint64_t)1 << 18);                           // 8.4 M nodes and up: a batch leaves most groups untouched
-    if (const char *force = getenv("RAPIDGNN_SPARSE_FRONTIER")) sparse_maps = force[0] == '1';   // same results either way; for tests and tuning
-    const uint32_t chunk_words = sparse_maps ? FRS_CHUNK_WORDS : FR_CHUNK_WORDS;
-    const uint32_t chunks = (uint32_t)((wpb + chunk_words - 1) / chunk_words);
-    // The maps come from the pool of all-zero blocks and go back to it: every hop's frontier pass clears what the hop
-    // marked in `reached` and its flags, and `seen` is cleared at the end group by group (seen_flags says which), so a
-    // build clears what it touched, not n_batches * n_nodes bits (2 GB a map on a graph of 10^8 nodes).
-    uint32_t *seen = nullptr, *reached_words = nullptr;
-    uint8_t *reached_flags = nullptr;                  // one byte per group of 256 IDs of `reached`
-    uint8_t *seen_flags = nullptr;                     // the same for `seen`: groups that hold any bit
-    const uint64_t n_groups = wpb / FR_WORDS_PER_THREAD * beta;          // (a multiple of eight: wpb is a multiple of 64)
-    uint32_t *paired = nullptr;                        // the large-graph form: both maps in one array of records (see paired_word)
-    if (sparse_maps) {
-        RG_TRY(tmp.dev_zeroed(2 * wpb * beta * sizeof(uint32_t), (void **)&paired, st));
-        reached_words = paired;
-        seen = paired + FR_WORDS_PER_THREAD;
-    } else {
-        RG_TRY(tmp.dev_zeroed(wpb * beta * sizeof(uint32_t), (void **)&seen, st));
-        RG_TRY(tmp.dev_zeroed(wpb * beta * sizeof(uint32_t), (void **)&reached_words, st));
-    }
-    RG_TRY(tmp.dev_zeroed(n_groups, (void **)&reached_flags, st));
-    if (!sparse_maps) RG_TRY(tmp.dev_zeroed(n_groups, (void **)&seen_flags, st));
-    if (const char *check = getenv("RAPIDGNN_CHECK_ZERO_MAPS"); check && check[0] == '1') {
-        // for tests: the maps, wherever they came from, really hold nothing but zeros (the pool of all-zero blocks keeps its promise)
-        unsigned long long *n_dev = nullptr, n_host = 0;
-        RG_TRY(tmp.dev_n<unsigned long long>(1, &n_dev));
-        RG_HIP(hipMemsetAsync(n_dev, 0, sizeof(unsigned long long), st));
-        const struct { const void *p; uint64_t bytes; } parts[4] = {{paired ? nullptr : seen, paired ? 0 : wpb * beta * 4}, {reached_words, wpb * beta * (paired ? 8u : 4u)},
-                                                                    {reached_flags, n_groups}, {seen_flags, seen_flags ? n_groups : 0}};
-        for (const auto &part : parts)
-            if (part.bytes)
-                hipLaunchKernelGGL(count_nonzero_kernel, dim3(1024), dim3(256), 0, st, (const unsigned long long *)part.p, part.bytes / 8, n_dev);
-        Readback rb(st);
-        RG_TRY(rb.add(&n_host, n_dev, sizeof(n_host)));
-        RG_TRY(rb.wait());
-        if (n_host != 0) { set_error("rg_build_schedule: %llu words of the per-batch maps are not zero at the start of the build", n_host); return RG_EHIP; }
-    }
     const ReachedMaps reached{reached_words, reached_flags, wpb, paired != nullptr};
-    {
-        ScopedTimer tm(KG_FRONTIER, st);
-        hipLaunchKernelGGL(mark_seeds_kernel, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, st, h0.ids, T, B, seen, seen_flags, wpb, (int64_t)g->n_nodes, sparse_maps ? 1 : 0);
-    }
     int32_t *fresh_cnt = nullptr;
     int64_t *fresh_scan = nullptr;
     const uint64_t n_cells = (uint64_t)beta * chunks;
@@ -790,16 +805,18 @@ static rg_status build_schedule_impl(const rg_graph *g, const int32_t *train, ui
         }
         RG_HIP(hipGetLastError());
     }
+    bool seen_clear = false;
     // a6, first half: where the bitmaps are smaller than the lists of input nodes, the epoch's frequencies come from them
     if (!sparse_maps && beta < (1u << FREQ_PLANES) && wpb * (uint64_t)beta <= (uint64_t)s->hop[L].off_host[beta]) {
         RG_TRY(s->arena.dev_n<uint32_t>((uint64_t)g->n_nodes, &s->epoch_freq));
         ScopedTimer tm(KG_HIST, st);
         const dim3 grid((unsigned)(wpb / FREQ_WORDS)), block(FREQ_SLICES * FREQ_WORDS);
-        if (beta < 1u << 8) hipLaunchKernelGGL(epoch_freq_kernel<8>, grid, block, 0, st, seen, wpb, beta, (int64_t)g->n_nodes, s->epoch_freq);
-        else hipLaunchKernelGGL(epoch_freq_kernel<FREQ_PLANES>, grid, block, 0, st, seen, wpb, beta, (int64_t)g->n_nodes, s->epoch_freq);
+        if (beta < 1u << 8) hipLaunchKernelGGL(epoch_freq_kernel<8>, grid, block, 0, st, seen, seen_flags, wpb, beta, (int64_t)g->n_nodes, s->epoch_freq);
+        else hipLaunchKernelGGL(epoch_freq_kernel<FREQ_PLANES>, grid, block, 0, st, seen, seen_flags, wpb, beta, (int64_t)g->n_nodes, s->epoch_freq);
         RG_HIP(hipGetLastError());
+        seen_clear = true;
     }
-    {
+    if (!seen_clear) {
         // `seen` back to all-zero.  Clearing the flagged groups alone costs about eight times as much per group as a
         // fill costs per group of the whole map (scattered 32-byte stores against a streaming fill), and a group is
         // flagged by at least one input node: the fill wins unless fewer than an eighth of the groups can be flagged.
