@@ -79,3 +79,20 @@ def test_blocks_of_batches_of_every_size(rg, batch, n_batches, rest):
         ends = samp_off[torch.from_numpy(np.asarray(at)).to("cuda")]
         first = torch.from_numpy(np.asarray(off[:-1])).to("cuda")
         assert torch.equal(ids[src + torch.repeat_interleave(first, ends[1:] - ends[:-1])], nbr), hop
+
+
+@pytest.mark.parametrize("force", ["1", "0"])
+@pytest.mark.parametrize("n,batch,fanout", [(33, 5, [3]), (64, 64, [2, 2]), (65, 7, [4, 4]), (2047, 300, [5, 1, 3]), (2049, 1, [40, 2]), (4100, 4100, [3, 3, 3, 3]),
+                                            (60_000, 900, [6, 5]), (150_000, 2000, [4, 2, 2])])
+def test_blocks_by_ranks_and_by_tables(rg, orc, n, batch, fanout, force, monkeypatch):
+    """Positions from bitmaps in LDS and from tables: graphs around whole words and pairs of words, one to five bitmaps, batches of one seed and
+    of all nodes, one batch shared out among all workgroups and many."""
+    monkeypatch.setenv("RAPIDGNN_BLOCK_RANKS", force)
+    rng = np.random.default_rng(n)
+    indptr, indices = graph(rng, n, 12)
+    train = rng.permutation(n)[: max(batch, min(n, 3 * batch + 1))].astype(np.int32)
+    o = orc.Schedule(indptr, indices, train, batch, fanout, 1, 0, 0)
+    s = rg.rg_build_schedule(torch.from_numpy(indptr).cuda(), torch.from_numpy(indices).cuda(), torch.from_numpy(train).cuda(), batch, fanout, 1, 0, 0)
+    rg.rg_schedule_build_blocks(s)
+    for hop in range(len(fanout)):
+        assert np.array_equal(rg.rg_schedule_block(s, hop).cpu().numpy(), o.block(hop)), hop
