@@ -347,23 +347,42 @@ void Arena::release_all()
 }
 
 // ---------------------------------------------------------------- last uses, retired handles
-UseLog::~UseLog()
+static std::atomic<uint64_t> g_next_log_id{1};
+UseLog::UseLog() : id_(g_next_log_id.fetch_add(1)) {}
+UseLog::Event::~Event()
 {
-    for (Use &u : uses_) (void)hipEventDestroy(u.ev);
+    if (ev) (void)hipEventDestroy(ev);
 }
 
-void UseLog::note(hipStream_t st)
+void UseLog::note(UseLog &a, UseLog &b, hipStream_t st)
 {
-    std::lock_guard<std::mutex> lk(mu_);
-    for (Use &u : uses_)
-        if (u.st == st) {
-            if (hipEventRecord(u.ev, st) != hipSuccess) { (void)hipGetLastError(); lost_ = true; }
+    std::scoped_lock lk(a.mu_, b.mu_);
+    for (Use &u : a.uses_)
+        if (u.st == st && u.partner == b.id_) {
+            if (hipEventRecord(u.at->ev, st) != hipSuccess) { (void)hipGetLastError(); a.lost_ = b.lost_ = true; }
             return;
         }
-    hipEvent_t ev = nullptr;
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); lost_ = true; return; }
-    if (hipEventRecord(ev, st) != hipSuccess) { (void)hipGetLastError(); (void)hipEventDestroy(ev); lost_ = true; return; }
-    uses_.push_back({st, ev});
+    // the pair's first use on this stream.  What has completed needs no event any more, so that a schedule served from cache after cache does not collect them
+    // (not while the stream is captured, when events are not asked).
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
+    if (capture == hipStreamCaptureStatusNone) { a.forget_completed(); b.forget_completed(); }
+    auto at = std::make_shared<Event>();
+    if (hipEventCreateWithFlags(&at->ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); at->ev = nullptr; a.lost_ = b.lost_ = true; return; }
+    if (hipEventRecord(at->ev, st) != hipSuccess) { (void)hipGetLastError(); a.lost_ = b.lost_ = true; return; }
+    a.uses_.push_back({st, b.id_, at});
+    b.uses_.push_back({st, a.id_, at});
+}
+
+void UseLog::forget_completed()
+{
+    size_t kept = 0;
+    for (Use &u : uses_) {
+        // (an event that others hold too may be recorded again by them: it is kept until they let go of it or it is found here by the pair's next use)
+        const bool done = u.at.use_count() == 1 && hipEventQuery(u.at->ev) == hipSuccess;
+        if (!done) { (void)hipGetLastError(); if (&uses_[kept] != &u) uses_[kept] = std::move(u); ++kept; }
+    }
+    uses_.resize(kept);
 }
 
 bool UseLog::idle()
@@ -371,7 +390,7 @@ bool UseLog::idle()
     std::lock_guard<std::mutex> lk(mu_);
     if (lost_) return false;
     for (Use &u : uses_) {
-        const hipError_t e = hipEventQuery(u.ev);
+        const hipError_t e = hipEventQuery(u.at->ev);
         if (e == hipErrorNotReady) return false;
         if (e != hipSuccess) { (void)hipGetLastError(); return false; }
     }
@@ -383,7 +402,21 @@ void UseLog::wait()
     std::lock_guard<std::mutex> lk(mu_);
     if (lost_) { (void)hipDeviceSynchronize(); lost_ = false; return; }
     for (Use &u : uses_)
-        if (hipEventSynchronize(u.ev) != hipSuccess) { (void)hipGetLastError(); (void)hipDeviceSynchronize(); return; }
+        if (hipEventSynchronize(u.at->ev) != hipSuccess) { (void)hipGetLastError(); (void)hipDeviceSynchronize(); return; }
+}
+
+rg_status compute_units(int *n_cu)
+{
+    static std::atomic<int> known[64];                   // per device; 0: not asked yet
+    int dev = 0;
+    RG_HIP(hipGetDevice(&dev));
+    int n = dev >= 0 && dev < 64 ? known[dev].load(std::memory_order_relaxed) : 0;
+    if (n == 0) {
+        RG_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+        if (dev >= 0 && dev < 64) known[dev].store(n, std::memory_order_relaxed);
+    }
+    *n_cu = n;
+    return RG_OK;
 }
 
 namespace {

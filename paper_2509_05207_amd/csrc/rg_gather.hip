@@ -62,10 +62,10 @@ constexpr int CHUNKS_IN_FLIGHT = 8;
 // that no lane leaves the vector path.  TAILPIECE = true (row widths that are no multiple of 4, or below VEC): the
 // last piece is copied in 8/4/2/1-byte parts.
 // Where a row comes from, out of a routing entry or a routing code.
-__device__ __forceinline__ void decode_route(int64_t e, uint32_t, uint32_t &tag, uint64_t &row) { tag = (uint32_t)entry_tag(e); row = (uint64_t)entry_row(e); }
-__device__ __forceinline__ void decode_route(uint32_t c, uint32_t last_remote, uint32_t &tag, uint64_t &row)
+__device__ __forceinline__ void decode_route(int64_t e, uint32_t, int64_t &tag, uint64_t &row) { tag = entry_tag(e); row = (uint64_t)entry_row(e); }
+__device__ __forceinline__ void decode_route(uint32_t c, uint32_t last_remote, int64_t &tag, uint64_t &row)
 {
-    tag = c < CODE_NOT_LOCAL ? (uint32_t)TAG_LOCAL : c > last_remote ? (uint32_t)TAG_CACHE : (uint32_t)TAG_REMOTE;
+    tag = c < CODE_NOT_LOCAL ? TAG_LOCAL : c > last_remote ? TAG_CACHE : TAG_REMOTE;
     row = c > last_remote ? ~c : c & ~CODE_NOT_LOCAL;
 }
 
@@ -101,9 +101,9 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const ROUTE
             kind[k] = 0;
             sp[k] = nullptr; dp[k] = nullptr;
             if (k < chunks && idx < total) {
-                uint32_t tag;
+                int64_t tag;
                 uint64_t row;
-                decode_route(routes[w], last_remote, tag, row);
+                decode_route(routes[(int64_t)w], last_remote, tag, row);
                 if (!(skip_remote && tag == TAG_REMOTE)) {
                     const uint8_t *base = tag == TAG_LOCAL ? src.local_rows + row * src.local_stride
                                         : tag == TAG_CACHE ? src.cache_rows + row * src.cache_stride
@@ -148,10 +148,10 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_remote_kernel(const ROU
     Miss *mine = lists[wave_here];
     const int64_t n_waves = (int64_t)gridDim.x * (GATHER_THREADS / 64), wave = (int64_t)blockIdx.x * (GATHER_THREADS / 64) + wave_here;
     for (int64_t first = wave * per_wave; first < n_rows; first += n_waves * per_wave) {
-        uint32_t tag = (uint32_t)TAG_LOCAL;
+        int64_t tag = TAG_LOCAL;
         uint64_t row = 0;
         if (lane < per_wave && first + lane < n_rows) decode_route(routes[first + lane], last_remote, tag, row);
-        const bool miss = tag == (uint32_t)TAG_REMOTE;
+        const bool miss = tag == TAG_REMOTE;
         const unsigned long long all = __ballot(miss);
         wave_lds_order();                                          // the last round's list has been read
         if (miss) mine[__popcll(all & ((1ull << lane) - 1ull))] = Miss{row, (uint64_t)(first + lane)};
@@ -217,9 +217,8 @@ rg_status launch_gather(const Routes &routes, int64_t n_rows, RowsWanted wanted,
     const bool tailpiece = tail != 0 && !overlap_last;
     if (overlap_last) align = std::min(align, (row_bytes % 8 == 0) ? 8 : 4);
     const uint64_t cpt = row_bytes / (uint32_t)vec + (tail ? 1 : 0);
-    int dev = 0, n_cu = 256;
-    RG_HIP(hipGetDevice(&dev));
-    RG_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+    int n_cu = 256;
+    RG_TRY(compute_units(&n_cu));
     // pieces per thread and round: as many as stay in flight, fewer when that would leave compute units without a workgroup
     const uint64_t total = (uint64_t)n_rows * cpt;
     const uint64_t want_blocks = (uint64_t)n_cu * 8;
@@ -472,8 +471,7 @@ extern "C" rg_status rg_gather_batch(const rg_schedule *s, const rg_cache *c, co
             RG_TRY(launch_gather(routes, m, ROWS_NOT_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
             RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_MISS));
         }
-        s->uses.note(st);                                      // the launches above read the schedule's and the cache's arrays after this call returns
-        c->uses.note(st);
+        UseLog::note(s->uses, c->uses, st);                    // the launches above read the schedule's and the cache's arrays after this call returns
         if (stats) *stats = plan->stats[batch];
         return RG_OK;
     }
@@ -565,8 +563,7 @@ extern "C" rg_status rg_gather_batches(const rg_schedule *s, const rg_cache *c, 
             RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));
         }
     }
-    s->uses.note(st);
-    c->uses.note(st);
+    UseLog::note(s->uses, c->uses, st);
     if (stats)
         for (uint32_t k = 0; k < n_batches; ++k) stats[k] = plan->stats[first_batch + k];
     return RG_OK;

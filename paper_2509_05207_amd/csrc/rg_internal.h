@@ -6,6 +6,7 @@
 #include <stdint.h>
 #include <stddef.h>
 #include <atomic>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -80,20 +81,26 @@ class Arena {
 
 // ---------------------------------------------------------------- last uses of a handle
 // A gather served from a prepared plan returns while its kernels still read the schedule and the cache.  Each such
-// call records, per stream, an event behind its last launch; a destroy call then knows exactly what it has to wait
-// for (that handle's own readers), not for the whole device.
+// call records, per pair of handles and stream, an event behind its last launch, which both handles keep; a destroy call then
+// knows exactly what it has to wait for (that handle's own readers), not for the whole device.  (Recording an event is a
+// microsecond or two of a call of ten: one for each handle 12.2 us, so 10.0, a batch of 64 seeds.)
 class UseLog {
   public:
-    UseLog() = default;
-    ~UseLog();
+    UseLog();
     UseLog(const UseLog &) = delete;
     UseLog &operator=(const UseLog &) = delete;
-    void note(hipStream_t st);      // work just enqueued on st reads the handle
+    static void note(UseLog &a, UseLog &b, hipStream_t st);      // work just enqueued on st reads both handles
     bool idle();                    // every noted use has completed
     void wait();                    // blocks until idle
   private:
-    struct Use { hipStream_t st; hipEvent_t ev; };
+    struct Event {
+        hipEvent_t ev = nullptr;
+        ~Event();
+    };
+    struct Use { hipStream_t st; uint64_t partner; std::shared_ptr<Event> at; };
+    void forget_completed();        // (mu_ held)
     std::mutex mu_;
+    const uint64_t id_;             // never given to another handle's log
     std::vector<Use> uses_;
     bool lost_ = false;             // an event could not be created or recorded: only a device-wide wait is safe
 };
@@ -268,6 +275,9 @@ rg_status helper_stream(hipStream_t *out);
 // Where a cache build on this thread reports the bytes of its table as soon as the table is allocated (NULL: nowhere).
 // The double-buffered cache sets it on its build thread so that the memory bound counts a C_sec under construction.
 extern thread_local std::atomic<uint64_t> *tls_table_bytes_sink;
+
+// The current device's compute units (asked of the runtime once per device).
+rg_status compute_units(int *n_cu);
 
 // True when p is device memory on the current device (false for pinned host memory).
 bool is_device_memory(const void *p);

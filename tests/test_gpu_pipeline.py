@@ -438,3 +438,42 @@ def test_damaged_schedule_files_are_refused(case, rg, tmp_path):
         rg.rg_schedule_save(case.gsched, tmp_path / "no_such_dir" / "x")
     assert e.value.status == rg.RG_EIO
     rg.rg_schedule_load(path)                                  # and the good file still loads
+
+
+def test_handles_that_share_their_last_uses(rg):
+    """One schedule served from cache after cache and two schedules from one, on two streams by turns, the handles let go while the gathers are
+    in flight, schedule first and cache first: the blocks are those of a call by itself."""
+    from paper_2509_05207_amd import synth
+    w = synth.make_workload("small", device="cuda", feature_device="cuda", remote_device="cuda")
+    cfg = w.cfg
+    feat = rg.make_features(w.is_local, w.row_of, w.local_rows, w.remote_rows, w.row_bytes)
+    build = lambda e: rg.rg_build_schedule(w.indptr, w.indices, w.train, cfg.batch_size, cfg.fanout, cfg.s0, cfg.worker, e)
+    want = {}
+    for e in (0, 1):
+        s = build(e)
+        off = rg.rg_schedule_frontier(s, s.L)[2]
+        out = torch.zeros((int(off[-1]), w.stride_bytes), dtype=torch.uint8, device="cuda")
+        rg.rg_gather_batches(s, rg.rg_build_cache([s], feat, 0), feat, 0, s.n_batches, out)
+        torch.cuda.synchronize()
+        want[e] = out[:, : w.row_bytes].clone()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for cache_first in (False, True):
+        kept = build(0)
+        for k in range(6):
+            other = build(1)
+            cache = rg.rg_build_cache([kept, other], feat, 50 * k)
+            outs = []
+            for n, (e, s) in enumerate([(0, kept), (1, other), (0, kept), (1, other)]):
+                out = torch.zeros((want[e].shape[0], w.stride_bytes), dtype=torch.uint8, device="cuda")
+                torch.cuda.synchronize()
+                for _ in range(3):
+                    rg.rg_gather_batches(s, cache, feat, 0, s.n_batches, out, stream=streams[(n + k) % 2])
+                outs.append((e, out))
+            if cache_first:
+                del cache, other, s
+            else:
+                del s, other, cache
+            build(k)                                             # takes and clears blocks from the pool
+            torch.cuda.synchronize()
+            for e, out in outs:
+                assert torch.equal(out[:, : w.row_bytes], want[e])
