@@ -625,8 +625,8 @@ static rg_status launch_plans(const rg_schedule *const *epochs, RouteSources &rs
 {
     const uint32_t last_remote = last_remote_code(k_eff);
     std::vector<std::vector<int64_t>> counts(plans.size());
+    std::vector<int64_t *> counts_of(plans.size(), nullptr);      // dev
     uint32_t no_codes_host = 0;
-    Readback rb(st);
     for (size_t e = 0; e < plans.size(); ++e) {
         const rg_schedule *s = epochs[e];
         Plan &plan = plans[e];
@@ -638,9 +638,8 @@ static rg_status launch_plans(const rg_schedule *const *epochs, RouteSources &rs
         counts[e].assign(2 * (size_t)beta, 0);
         if (n == 0) continue;
         uint32_t *group_counts = nullptr;
-        int64_t *counts_dev = nullptr;
         RG_TRY(tmp.dev_n<uint32_t>((uint64_t)n_tiles * PLAN_TILE_GROUPS, &group_counts));
-        RG_TRY(tmp.dev_n<int64_t>(2 * (uint64_t)beta, &counts_dev));
+        RG_TRY(tmp.dev_n<int64_t>(2 * (uint64_t)beta, &counts_of[e]));
         ScopedTimer tm(KG_PLAN, st);
         if (check.pending && *codes && (uint64_t)n * sizeof(uint32_t) >= (uint64_t)((check.n_nodes + 31) / 32 + 1) * (sizeof(int64_t) + sizeof(int32_t))) {
             RG_TRY(check_row_ranks(check, rs.row_of, plan.code, tmp, st));
@@ -650,13 +649,15 @@ static rg_status launch_plans(const rg_schedule *const *epochs, RouteSources &rs
         auto launch = [&](auto *route) {
             using ROUTE = std::remove_pointer_t<decltype(route)>;
             hipLaunchKernelGGL(plan_kernel<ROUTE>, dim3((unsigned)n_tiles), dim3(PLAN_THREADS), 0, st, h.ids, n, rs, last_remote, route, no_codes, group_counts);
-            hipLaunchKernelGGL(batch_counts_kernel<ROUTE>, dim3(beta), dim3(COUNT_THREADS), 0, st, route, last_remote, group_counts, h.off_dev, beta, counts_dev);
+            hipLaunchKernelGGL(batch_counts_kernel<ROUTE>, dim3(beta), dim3(COUNT_THREADS), 0, st, route, last_remote, group_counts, h.off_dev, beta, counts_of[e]);
         };
         if (*codes) launch(plan.code);
         else launch(plan.entry);
         RG_HIP(hipGetLastError());
-        RG_TRY(rb.add(counts[e].data(), counts_dev, counts[e].size() * sizeof(int64_t)));
     }
+    Readback rb(st);                                              // (from here on nothing leaves between a copy asked for and the wait)
+    for (size_t e = 0; e < plans.size(); ++e)
+        if (counts_of[e]) RG_TRY(rb.add(counts[e].data(), counts_of[e], counts[e].size() * sizeof(int64_t)));
     RG_TRY(rb.add(&no_codes_host, no_codes, sizeof(no_codes_host)));
     RG_TRY(rb.wait());
     if (no_codes_host != 0) *codes = false;
