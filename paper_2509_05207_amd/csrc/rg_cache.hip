@@ -116,14 +116,62 @@ __global__ void __launch_bounds__(TOPK_THREADS) digit_histogram_kernel(const uin
         if (h[k]) atomicAdd(&mine[k], (unsigned long long)h[k]);
 }
 
-// The same for the uint8_t tally: one digit, so no prefix to match.  A wave takes SEL_TILE consecutive nodes at a time and also leaves their number of
-// candidates, which is the select passes' total of those nodes wherever all candidates are taken (111 M nodes: a pass of 58 us that need
-// not be).  WIDE (is_local 16-byte aligned; the tally always is): a lane takes sixteen consecutive nodes per load of either array, and visits only the
+// The same for the uint8_t tally: one digit, so no prefix to match.  WIDE (is_local 16-byte aligned; the tally always
+// is): a lane takes sixteen consecutive nodes per round, one 16-byte load of each array, and visits only the
 // bytes that are candidates (non-zero count, not local).
 __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t w) { return (w | ((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu)) & 0x80808080u; }   // bit 7 of every non-zero byte
 
 template <bool WIDE>
 __global__ void __launch_bounds__(TOPK_THREADS) digit_histogram8_kernel(const uint8_t *__restrict__ freq, const uint8_t *__restrict__ is_local, int64_t n,
+                                                                        const SelectState *__restrict__ stp, unsigned long long *__restrict__ bins)
+{
+    __shared__ unsigned int h[DIGIT_BINS];
+    for (int k = threadIdx.x; k < DIGIT_BINS; k += TOPK_THREADS) h[k] = 0;
+    __syncthreads();
+    if (stp->take_all) return;
+    int64_t done = 0;
+    if (WIDE) {
+        auto count_word = [&](uint32_t fw, uint32_t lw) {
+            uint32_t cand = nonzero_bytes(fw) & ~nonzero_bytes(lw);
+            while (cand) {
+                const int top = __ffs((int)cand) - 1;              // bit 7 of the candidate's byte
+                cand &= cand - 1;
+                atomicAdd(&h[(fw >> (top - 7)) & 0xFFu], 1u);
+            }
+        };
+        auto count16 = [&](const uint4 fv, const uint4 lv) {
+            if ((fv.x | fv.y | fv.z | fv.w) == 0u) return;
+            count_word(fv.x, lv.x); count_word(fv.y, lv.y); count_word(fv.z, lv.z); count_word(fv.w, lv.w);
+        };
+        const int64_t n16 = n >> 4;
+        const int64_t span = (n16 + gridDim.x - 1) / gridDim.x;
+        const int64_t q_end = min(n16, (int64_t)(blockIdx.x + 1) * span);
+        int64_t q = (int64_t)blockIdx.x * span + threadIdx.x;
+        for (; q + TOPK_THREADS < q_end; q += 2 * TOPK_THREADS) {
+            const uint4 f0 = reinterpret_cast<const uint4 *>(freq)[q], f1 = reinterpret_cast<const uint4 *>(freq)[q + TOPK_THREADS];
+            const uint4 l0 = reinterpret_cast<const uint4 *>(is_local)[q], l1 = reinterpret_cast<const uint4 *>(is_local)[q + TOPK_THREADS];
+            count16(f0, l0); count16(f1, l1);
+        }
+        for (; q < q_end; q += TOPK_THREADS) count16(reinterpret_cast<const uint4 *>(freq)[q], reinterpret_cast<const uint4 *>(is_local)[q]);
+        done = n16 << 4;
+    }
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t v = done + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+        const uint32_t fv = freq[v];
+        if (fv != 0 && !is_local[v]) atomicAdd(&h[fv], 1u);
+    }
+    __syncthreads();
+    unsigned long long *mine = bins + (size_t)(blockIdx.x % BIN_COPIES) * DIGIT_BINS;
+    for (int k = threadIdx.x; k < DIGIT_BINS; k += TOPK_THREADS)
+        if (h[k]) atomicAdd(&mine[k], (unsigned long long)h[k]);
+}
+
+// The same by waves that take SEL_TILE consecutive nodes at a time and also leave their number of candidates, which is the select passes' total
+// of those nodes wherever all candidates are taken (111 M nodes: a pass of 58 us that need not be).  From CANDIDATES_NODES on: a graph of fewer
+// tiles leaves waves idle (10,000 nodes: 4.1 us by the kernel above, 9.9 so, and 3 to spare).
+constexpr int64_t CANDIDATES_NODES = 1 << 23;
+template <bool WIDE>
+__global__ void __launch_bounds__(TOPK_THREADS) candidates_histogram8_kernel(const uint8_t *__restrict__ freq, const uint8_t *__restrict__ is_local, int64_t n,
                                                                         unsigned long long *__restrict__ bins, uint64_t *__restrict__ block_tot)
 {
     __shared__ unsigned int h[DIGIT_BINS];
@@ -318,7 +366,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) select_block_totals(const F *__r
 {
     __shared__ uint64_t lds[TOPK_THREADS / 64];
     const SelectState st = *stp;
-    if (candidates_known && st.take_all) return;               // (digit_histogram8_kernel has left the totals)
+    if (candidates_known && st.take_all) return;               // (candidates_histogram8_kernel has left the totals)
     const int64_t n_blocks = (n + SEL_TILE - 1) / SEL_TILE;
     for (int64_t block = blockIdx.x; block < n_blocks; block += gridDim.x) {
         const int64_t first = block * SEL_TILE + (int64_t)threadIdx.x * SEL_PER_THREAD;
@@ -813,6 +861,8 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
     int bits = 1;
     while (bits < 32 && (max_freq >> bits) != 0) ++bits;
     const int passes = (bits + DIGIT_BITS - 1) / DIGIT_BITS;
+    bool candidates_known = narrow && n >= CANDIDATES_NODES;
+    if (const char *force = getenv("RAPIDGNN_COUNT_CANDIDATES")) candidates_known = narrow && force[0] == '1';      // same results either way; for tests and tuning
     const bool local4 = ((uintptr_t)f->is_local & 3) == 0, local8 = ((uintptr_t)f->is_local & 7) == 0,      // the caller's array: wide loads only if it allows them
                local16 = ((uintptr_t)f->is_local & 15) == 0;
     const int64_t sel_blocks = (n + SEL_TILE - 1) / SEL_TILE;
@@ -827,18 +877,20 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
         for (int p = 0; p < passes; ++p) {
             const int shift = (passes - 1 - p) * DIGIT_BITS;
             if (narrow) {
-                if (local16) hipLaunchKernelGGL(digit_histogram8_kernel<true>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, bins, block_tot);
-                else hipLaunchKernelGGL(digit_histogram8_kernel<false>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, bins, block_tot);
+                if (candidates_known && local16) hipLaunchKernelGGL(candidates_histogram8_kernel<true>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, bins, block_tot);
+                else if (candidates_known) hipLaunchKernelGGL(candidates_histogram8_kernel<false>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, bins, block_tot);
+                else if (local16) hipLaunchKernelGGL(digit_histogram8_kernel<true>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, stp, bins);
+                else hipLaunchKernelGGL(digit_histogram8_kernel<false>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, stp, bins);
             } else if (local4) hipLaunchKernelGGL(digit_histogram_kernel<true>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq, f->is_local, n, stp, shift, bins);
             else hipLaunchKernelGGL(digit_histogram_kernel<false>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq, f->is_local, n, stp, shift, bins);
             hipLaunchKernelGGL(choose_digit_kernel, dim3(1), dim3(DIGIT_BINS), 0, st, stp, bins, shift, p == 0 ? 1 : 0, K);
         }
         if (sel_blocks > 0) {
             const dim3 tg((unsigned)std::min<int64_t>(sel_blocks, (int64_t)n_cu * 32)), sb(TOPK_THREADS);
-            if (narrow && local8) hipLaunchKernelGGL((select_block_totals<true, uint8_t>), tg, sb, 0, st, c->freq8, f->is_local, n, stp, narrow ? 1 : 0, block_tot);
-            else if (narrow) hipLaunchKernelGGL((select_block_totals<false, uint8_t>), tg, sb, 0, st, c->freq8, f->is_local, n, stp, narrow ? 1 : 0, block_tot);
-            else if (local8) hipLaunchKernelGGL((select_block_totals<true, uint32_t>), tg, sb, 0, st, c->freq, f->is_local, n, stp, narrow ? 1 : 0, block_tot);
-            else hipLaunchKernelGGL((select_block_totals<false, uint32_t>), tg, sb, 0, st, c->freq, f->is_local, n, stp, narrow ? 1 : 0, block_tot);
+            if (narrow && local8) hipLaunchKernelGGL((select_block_totals<true, uint8_t>), tg, sb, 0, st, c->freq8, f->is_local, n, stp, candidates_known ? 1 : 0, block_tot);
+            else if (narrow) hipLaunchKernelGGL((select_block_totals<false, uint8_t>), tg, sb, 0, st, c->freq8, f->is_local, n, stp, candidates_known ? 1 : 0, block_tot);
+            else if (local8) hipLaunchKernelGGL((select_block_totals<true, uint32_t>), tg, sb, 0, st, c->freq, f->is_local, n, stp, candidates_known ? 1 : 0, block_tot);
+            else hipLaunchKernelGGL((select_block_totals<false, uint32_t>), tg, sb, 0, st, c->freq, f->is_local, n, stp, candidates_known ? 1 : 0, block_tot);
             hipLaunchKernelGGL(select_scan_tiles, dim3((unsigned)sel_tiles), dim3(TOPK_THREADS), 0, st, block_tot, sel_blocks, tile_tot);
             if (sel_tiles > 1) hipLaunchKernelGGL(select_scan_totals, dim3(1), dim3(TOPK_THREADS), 0, st, tile_tot, sel_tiles);
         }

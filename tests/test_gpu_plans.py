@@ -163,3 +163,27 @@ def test_misses_of_a_pinned_table(rg, n, missing, row_bytes):
         got = out.cpu().numpy()
         assert np.array_equal(got[:, :row_bytes], table[ids][:, :row_bytes])
         assert (got[:, row_bytes:] == 7).all()
+
+
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 50_000])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_candidates_counted_by_the_histogram(rg, n, shift, monkeypatch):
+    """The histogram that leaves the candidates of every 2,048 nodes, and the one that does not: caches that hold all candidates, one less, and none, with
+    is_local at an aligned address and not."""
+    d = "cuda"
+    rng = np.random.default_rng(n)
+    indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
+    scheds = [rg.rg_build_schedule(indptr, indices, torch.from_numpy(rng.permutation(n)[: max(1, n * k // 4)].astype(np.int32)).to(d), max(1, n // 5), [], 5, 0, k) for k in (1, 2, 4)]
+    is_local = np.zeros(n + shift, np.uint8)
+    is_local[shift:] = rng.random(n) < 0.3
+    local = torch.from_numpy(is_local).to(d)[shift:]
+    feat = rg.make_features(local, torch.arange(n, dtype=torch.int32, device=d), torch.zeros((n, 4), device=d), torch.zeros((n, 4), device=d), 16)
+    freq = np.zeros(n, np.int64)
+    for s in scheds:
+        np.add.at(freq, rg.rg_schedule_frontier(s, 0)[0].cpu().numpy(), 1)
+    cand = np.flatnonzero((freq > 0) & (is_local[shift:] == 0))
+    for K in sorted({0, max(0, cand.size - 1), cand.size, n + 5}):
+        want = np.sort(cand[np.lexsort((cand, -freq[cand]))[:K]])
+        for force in ("1", "0"):
+            monkeypatch.setenv("RAPIDGNN_COUNT_CANDIDATES", force)
+            assert np.array_equal(rg.rg_cache_view(rg.rg_build_cache(scheds, feat, K), n)["cache_ids"].cpu().numpy(), want)
