@@ -53,6 +53,7 @@
 // the bitmaps, else by the sampling waves as they write them.
 #include "rg_internal.h"
 #include "rg_device.h"
+#include "rg_launch.h"
 
 #include <algorithm>
 #include <atomic>
@@ -2031,10 +2032,6 @@ static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, 
 // the rows read at all of them afterwards (233,000 nodes, 147 batches, fan-outs 25, 10, 29 M draws: a lane per draw / so 452 / 343 us).
 // BY_PLACE (see ByPlace): an instantiation of its own, since the look at every unit's batch costs the other (with a lane per draw: 111 M nodes, fan-outs
 // 15, 10 362 us without, 382 with it; 50, 3 289 and 315).
-constexpr int POS_THREADS = 256;
-constexpr int POS_WAVES = POS_THREADS / 64;
-constexpr int POS_DRAWS = 256;           // positions of a wave in LDS (the launch of 25 M draws with 64 / 128 / 256 / 384 / 512: 468 / 346 / 292 / 318 / 328 us)
-constexpr int POS_LEAST = 64;            // draws per unit, at least, where there are few (see sample_hop)
 constexpr int POS_IN_FLIGHT = 4;
 struct PosNode {
     uint64_t state;
@@ -2390,15 +2387,8 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     if (sampler == RG_SAMPLER_POSITIONS) {
         if (fanout > 0 && n_cur > 0) {
             ScopedTimer tm(KG_SAMPLER, st);
-            // as many draws to a unit as a wave has room for, or as few as give every wave that the chip holds a unit
-            const int64_t waves = (int64_t)n_cu * 32;
-            int64_t draws = POS_DRAWS;
-            while (draws > POS_LEAST && n_cur * fanout < draws * waves) draws /= 2;
-            const uint32_t unit_nodes = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(64, draws / fanout));
-            const int64_t n_units = place.n_batches ? (place.longest + unit_nodes - 1) / unit_nodes * beta : (n_cur + unit_nodes - 1) / unit_nodes;
-            // (a wave per unit: waves that walk over the units by turns drift apart, and with them what they read: 312 us)
-            const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_units + POS_WAVES - 1) / POS_WAVES, 0x7FFFFFFF));
-#define RG_POSITIONS(M, P) hipLaunchKernelGGL((sample_positions_kernel<M, P>), dim3(grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, unit_nodes, cur.samp_off, cur.samp_nbr, reached, place, n_units)
+            const PositionUnits units = position_units(n_cur, fanout, place.n_batches != 0, place.longest, beta, n_cu);
+#define RG_POSITIONS(M, P) hipLaunchKernelGGL((sample_positions_kernel<M, P>), dim3(units.grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, units.nodes, cur.samp_off, cur.samp_nbr, reached, place, units.n)
             if (inline_marks && place.n_batches) RG_POSITIONS(MARK_BITS, true);
             else if (inline_marks) RG_POSITIONS(MARK_BITS, false);
             else if (place.n_batches) RG_POSITIONS(MARK_NONE, true);

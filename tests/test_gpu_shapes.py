@@ -155,3 +155,15 @@ def test_walks_dealt_out_to_lanes(fanouts, rg, orc):
         so, nbr = rg.rg_schedule_samples(g, hop)
         oso, onbr = o.samples(hop)
         assert np.array_equal(so.cpu().numpy(), oso) and np.array_equal(nbr.cpu().numpy(), onbr)
+
+
+def test_more_units_of_one_node_than_a_launch_has_waves(rg):
+    """A hop of more frontier nodes, each a unit of its own at this fan-out, than one launch may have waves: some waves take two."""
+    n, d = 2**26 + 5, "cuda"
+    g = torch.Generator(device=d).manual_seed(3)
+    indices = torch.randint(0, n, (n,), generator=g, device=d, dtype=torch.int32)                # rows of one ID
+    s = rg.rg_build_schedule_with(torch.arange(n + 1, dtype=torch.int64, device=d), indices, torch.arange(n, dtype=torch.int32, device=d), n, [129], 1, 0, 0,
+                                  sampler=rg.RG_SAMPLER_POSITIONS)
+    off, nbr = rg.rg_schedule_samples(s, 0)
+    assert torch.equal(off, torch.arange(n + 1, dtype=torch.int64, device=d))
+    assert torch.equal(nbr, indices[rg.rg_schedule_frontier(s, 0)[0].long()])

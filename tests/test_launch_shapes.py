@@ -1,0 +1,50 @@
+"""Launch shapes computed on the host, compiled by themselves: what a launch may have at most, and that its units cover the work."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_05207_amd", "csrc")
+DRIVER = r"""
+#include "rg_launch.h"
+#include <cstdio>
+#include <cstring>
+int main()
+{
+    char what[32];
+    long long a[6];
+    while (scanf("%31s %lld %lld %lld %lld %lld %lld", what, a, a + 1, a + 2, a + 3, a + 4, a + 5) == 7) {
+        if (!strcmp(what, "positions")) {
+            const rg::PositionUnits u = rg::position_units(a[0], (uint32_t)a[1], a[2] != 0, a[3], (uint32_t)a[4], (int)a[5]);
+            printf("%u %lld %u\n", u.nodes, (long long)u.n, u.grid);
+        }
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    d = tmp_path_factory.mktemp("shapes")
+    (d / "driver.cpp").write_text(DRIVER)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, "-o", str(d / "driver"), str(d / "driver.cpp")])
+
+    def ask(what, *args):
+        line = " ".join([what] + [str(int(x)) for x in args] + ["0"] * (6 - len(args)))
+        return [int(x) for x in subprocess.run([str(d / "driver")], input=line + "\n", capture_output=True, text=True, check=True).stdout.split()]
+    return ask
+
+
+@pytest.mark.parametrize("fanout", [1, 3, 25, 50, 64, 85, 86, 128, 129, 256, 1984])
+@pytest.mark.parametrize("n_cur", [1, 64, 40_000, 2**26, 2**27 + 1, 2**30 - 1, 2**31 - 1, 80 * 10**9])
+@pytest.mark.parametrize("beta", [0, 1, 147, 65_535])
+def test_units_of_the_position_sampler(shapes, n_cur, fanout, beta):
+    """beta > 0: batches of equal length by place, which frontiers of up to 2^30 nodes go by."""
+    if beta and n_cur >= 2**30:
+        pytest.skip("by position")
+    longest = -(-n_cur // max(beta, 1))
+    nodes, n_units, grid = shapes("positions", n_cur, fanout, beta > 0, longest, beta, 256)
+    assert 1 <= nodes <= 64 and (nodes == 1 or nodes * fanout <= 256)
+    assert n_units == (-(-longest // nodes) * beta if beta else -(-n_cur // nodes))
+    assert 1 <= grid and grid * 256 < 2**32                      # what a launch may have
+    assert grid * 4 >= min(n_units, 2**26 - 4)                   # a wave per unit, as far as that goes
