@@ -362,25 +362,29 @@ void UseLog::note(UseLog &a, UseLog &b, hipStream_t st)
             if (hipEventRecord(u.at->ev, st) != hipSuccess) { (void)hipGetLastError(); a.lost_ = b.lost_ = true; }
             return;
         }
-    // the pair's first use on this stream.  What has completed needs no event any more, so that a schedule served from cache after cache does not collect them
-    // (not while the stream is captured, when events are not asked).
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusActive; }
-    if (capture == hipStreamCaptureStatusNone) { a.forget_completed(); b.forget_completed(); }
-    auto at = std::make_shared<Event>();
-    if (hipEventCreateWithFlags(&at->ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); at->ev = nullptr; a.lost_ = b.lost_ = true; return; }
+    // The pair's first use on this stream.  An event whose other holder has let go of it is recorded again, here behind what it stood for, so that a
+    // schedule served from cache after cache does not collect events.  (Not found by asking which have completed: hipEventQuery ends a global
+    // capture that is under way on any other stream.)
+    std::shared_ptr<Event> at;
+    a.take_unshared(st, &at);
+    b.take_unshared(st, &at);
+    if (!at) at = std::make_shared<Event>();
+    if (!at->ev && hipEventCreateWithFlags(&at->ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); at->ev = nullptr; a.lost_ = b.lost_ = true; return; }
     if (hipEventRecord(at->ev, st) != hipSuccess) { (void)hipGetLastError(); a.lost_ = b.lost_ = true; return; }
     a.uses_.push_back({st, b.id_, at});
     b.uses_.push_back({st, a.id_, at});
 }
 
-void UseLog::forget_completed()
+void UseLog::take_unshared(hipStream_t st, std::shared_ptr<Event> *first)
 {
     size_t kept = 0;
     for (Use &u : uses_) {
-        // (an event that others hold too may be recorded again by them: it is kept until they let go of it or it is found here by the pair's next use)
-        const bool done = u.at.use_count() == 1 && hipEventQuery(u.at->ev) == hipSuccess;
-        if (!done) { (void)hipGetLastError(); if (&uses_[kept] != &u) uses_[kept] = std::move(u); ++kept; }
+        if (u.st == st && u.at.use_count() == 1) {
+            if (!*first) *first = std::move(u.at);
+        } else {
+            if (&uses_[kept] != &u) uses_[kept] = std::move(u);
+            ++kept;
+        }
     }
     uses_.resize(kept);
 }

@@ -98,7 +98,7 @@ class UseLog {
         ~Event();
     };
     struct Use { hipStream_t st; uint64_t partner; std::shared_ptr<Event> at; };
-    void forget_completed();        // (mu_ held)
+    void take_unshared(hipStream_t st, std::shared_ptr<Event> *first);      // leaves out the uses on st that nobody shares any more; the event of one of them in *first, if that is empty  (mu_ held)
     std::mutex mu_;
     const uint64_t id_;             // never given to another handle's log
     std::vector<Use> uses_;

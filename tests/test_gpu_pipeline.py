@@ -477,3 +477,36 @@ def test_handles_that_share_their_last_uses(rg):
             torch.cuda.synchronize()
             for e, out in outs:
                 assert torch.equal(out[:, : w.row_bytes], want[e])
+
+
+def test_gathers_beside_a_capture(rg):
+    """A gather whose schedule was served by a cache that is gone, from another cache and on another stream than the one that is being captured:
+    the capture lives on, and both do what they would have done alone."""
+    n, d = 5000, "cuda"
+    indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
+    s = rg.rg_build_schedule(indptr, indices, torch.arange(n, dtype=torch.int32, device=d), 500, [], 1, 0, 0)
+    is_local = (torch.arange(n, device=d) % 3 == 0).to(torch.uint8)
+    table = torch.arange(4 * n, dtype=torch.int32, device=d).view(n, 4)
+    feat = rg.make_features(is_local, torch.arange(n, dtype=torch.int32, device=d), table, table, 16)
+    want = table[rg.rg_schedule_frontier(s, 0)[0][:500].long()]
+    gathers, captured = torch.cuda.Stream(), torch.cuda.Stream()
+    out, x = torch.zeros((500, 4), dtype=torch.int32, device=d), torch.zeros(8, device=d)
+    torch.cuda.synchronize()
+    for replays in (1, 2, 3):
+        gone, cache = rg.rg_build_cache([s], feat, 100), rg.rg_build_cache([s], feat, 100)
+        rg.rg_gather_batch(s, gone, feat, 0, out, stream=gathers)
+        torch.cuda.synchronize()
+        del gone
+        graph = torch.cuda.CUDAGraph()
+        out.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=captured, capture_error_mode="global"):
+            x.add_(1)
+            rg.rg_gather_batch(s, cache, feat, 0, out, stream=gathers)
+            x.add_(1)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        for _ in range(replays):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert bool((x == replays * (replays + 1)).all())
