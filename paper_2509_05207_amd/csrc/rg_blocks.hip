@@ -192,11 +192,15 @@ __global__ void __launch_bounds__(RANK_BLOCK) block_ranks_kernel(RankArgs a, uin
             for (int q = 0; q < BLK_IN_FLIGHT; ++q) {
                 const int64_t e = e0 + q * RANK_BLOCK;
                 if (e >= hi) continue;
-                int32_t p = -1;                      // (of an ID that the batch does not list: a schedule never has one)
+                int32_t p = -1;                      // (of an ID that the batch does not list, which only a file may have)
                 if (word[q] != 0u) {
                     const uint32_t r = rank(set[q], u[q], word[q]);
                     p = (int32_t)(set[q] == 0u ? seed_at[r] : at[q] + r);
-                }
+                } else if (u[q] < (uint64_t)a.n_nodes)
+                    for (uint32_t s = l + 2; s < n_sets; ++s) {      // (only a file's samples may lie in what a later hop adds)
+                        const uint32_t x = bits[s * n_words + (u[q] >> 5)];
+                        if ((x >> (u[q] & 31)) & 1u) p = (int32_t)(ends[s - 1] + rank(s, u[q], x));
+                    }
                 __builtin_nontemporal_store(p, a.src_pos[l] + e);
             }
         }
@@ -241,7 +245,7 @@ rg_status rg_schedule_build_blocks(rg_schedule *s, uint64_t workspace_limit_byte
     int32_t *table = nullptr;
     const uint64_t n_words = ((uint64_t)s->n_nodes + 63) / 64 * 2;
     size_t lds_bytes = 0;
-    const bool by_ranks = s->n_batches > 0 && s->L > 0 && ranks_pay(s, n_words, n_cu, &lds_bytes);
+    const bool by_ranks = s->n_batches > 0 && s->L > 0 && s->ids_ascend && ranks_pay(s, n_words, n_cu, &lds_bytes);
     if (s->n_batches > 0 && !by_ranks) RG_TRY(tmp.dev((uint64_t)group * per_batch, (void **)&table));
     for (uint32_t l = 0; l < s->L; ++l)           // every allocation before the first launch: no early return with kernels in flight
         if (!s->hop[l].src_pos) RG_TRY(s->arena.dev_n<int32_t>((uint64_t)s->hop[l].n_samples, &s->hop[l].src_pos));

@@ -139,6 +139,7 @@ struct rg_schedule {
     uint64_t uid = 0;                // identity for plan lookup (pointers can be reused)
     std::vector<rg::HopData> hop;    // L + 1 entries
     bool blocks_built = false;
+    bool ids_ascend = true;          // in every batch each hop's new IDs ascend, as the builds leave them (files may hold others: see rg_store.hip)
     uint32_t *epoch_freq = nullptr;  // dev, [n_nodes]: in how many of the epoch's input sets each node is, or NULL (then the lists are tallied)
     mutable rg::UseLog uses;         // gathers in flight that read this schedule
     explicit rg_schedule(const rg_allocator *a) : arena(a) {}

@@ -7,7 +7,8 @@
 //   for hop 0..L-1: samp_off i64[|U_hop| + 1],    samp_nbr i32[samp_off[|U_hop|]]   (after that hop's ids)
 // Device arrays go through a pinned staging buffer in pieces, so neither side needs the whole schedule in host
 // memory.  A loaded file is checked before anything on the device depends on it: offsets monotone and consistent,
-// every ID inside [0, n_nodes).
+// every ID inside [0, n_nodes).  A batch's U_L is its seeds and then each hop's new IDs, which rg_schedule_save leaves in ascending
+// order; a file with another order is read too, and noted, since computation blocks can be made by ranks only where they ascend.
 #include "rg_internal.h"
 
 #include <algorithm>
@@ -155,8 +156,33 @@ static rg_status load_range(const char *path, uint32_t first_batch, uint32_t n_b
     RG_TRY(tmp.pinned(STAGE_BYTES, &stage));
 
     auto ids_in_range = [n_nodes](int32_t *p, uint64_t n, uint64_t) -> rg_status {
-        for (uint64_t i = 0; i < n; ++i)
+        bool outside = false;
+        for (uint64_t i = 0; i < n; ++i) outside |= (uint32_t)p[i] >= (uint32_t)n_nodes;      // (no way out of the loop: several IDs at a time)
+        for (uint64_t i = 0; i < n && outside; ++i)
             if (p[i] < 0 || (int64_t)p[i] >= n_nodes) { set_error("rg_schedule_load: node ID %d outside [0, %lld)", p[i], (long long)n_nodes); return RG_EIO; }
+        return RG_OK;
+    };
+    // The last hop's pieces are looked through for the order of each hop's new IDs: `at` runs over the parts (batch, hop) of U_L.
+    struct { uint32_t batch = 0, hop = 0; int64_t end = 0; int32_t last = -1; bool seeds = false; } at;      // batch, hop: of the next part
+    auto inputs_in_range = [&](int32_t *p, uint64_t n, uint64_t first) -> rg_status {
+        RG_TRY(ids_in_range(p, n, first));
+        for (uint64_t i = 0; i < n && s->ids_ascend;) {
+            while (at.end <= (int64_t)(first + i)) {             // the next part that is not empty begins here
+                const std::vector<int64_t> &of_hop = s->hop[at.hop].off_host, &of_last = s->hop[L].off_host;
+                at.end = of_last[at.batch] + of_hop[at.batch + 1] - of_hop[at.batch];
+                at.seeds = at.hop == 0;                          // (in the order of the shuffle)
+                at.last = -1;
+                if (at.hop < L) ++at.hop;
+                else { at.hop = 0; ++at.batch; }
+            }
+            const uint64_t stop = std::min<uint64_t>(n, (uint64_t)at.end - first);
+            if (at.seeds) { i = stop; continue; }
+            bool ascend = p[i] > at.last;
+            for (uint64_t j = i + 1; j < stop; ++j) ascend &= p[j] > p[j - 1];
+            s->ids_ascend = ascend;
+            at.last = p[stop - 1];
+            i = stop;
+        }
         return RG_OK;
     };
     std::vector<int64_t> off((size_t)nb + 1), prev_off;
@@ -186,7 +212,8 @@ static rg_status load_range(const char *path, uint32_t first_batch, uint32_t n_b
         RG_HIP(hipStreamSynchronize(st));
         RG_TRY(s->arena.dev_n<int32_t>(m, &h.ids));
         RG_TRY(seek_to(cur + first * sizeof(int32_t)));
-        RG_TRY((file_to_device<int32_t>(file.f, h.ids, m, stage, st, ids_in_range)));
+        if (l < L) RG_TRY((file_to_device<int32_t>(file.f, h.ids, m, stage, st, ids_in_range)));
+        else RG_TRY((file_to_device<int32_t>(file.f, h.ids, m, stage, st, inputs_in_range)));
         cur += n * sizeof(int32_t);
         if (l < L) {
             if (!section_fits(n + 1, sizeof(int64_t))) { set_error("rg_schedule_load: file is truncated (sample offsets of hop %u)", l); return RG_EIO; }

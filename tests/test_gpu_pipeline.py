@@ -510,3 +510,64 @@ def test_gathers_beside_a_capture(rg):
             graph.replay()
         torch.cuda.synchronize()
         assert bool((x == replays * (replays + 1)).all())
+
+
+@pytest.mark.parametrize("force", ["1", "0"])
+@pytest.mark.parametrize("batches", [None, (0, 3), (2, 3), (4, 1)])
+@pytest.mark.parametrize("change", ["none", "last hop", "one batch", "both hops", "equal", "later hop"])
+def test_blocks_of_schedules_from_files(rg, change, batches, force, tmp_path, monkeypatch):
+    """Computation blocks of loaded schedules and ranges, by ranks wherever that is right: files as they are saved, with the new IDs of hops in another order
+    (in all batches, in the last batch alone), with an ID twice, and with samples that only a later hop lists.  Every position leads to the sample's ID."""
+    monkeypatch.setenv("RAPIDGNN_BLOCK_RANKS", force)
+    n, d = 3000, "cuda"
+    rng = np.random.default_rng(7)
+    indptr = torch.arange(n + 1, dtype=torch.int64) * 12
+    indices = torch.from_numpy(rng.integers(0, n, size=12 * n).astype(np.int32))
+    train = torch.from_numpy(rng.permutation(n)[:250].astype(np.int32))
+    s = rg.rg_build_schedule(indptr.to(d), indices.to(d), train.to(d), 50, [4, 3], 1, 0, 0)
+    path = tmp_path / "s"
+    rg.rg_schedule_save(s, path)
+    raw, beta = bytearray(path.read_bytes()), s.n_batches
+    at, ids, off, nbr_at = 32, [], [], []
+    for hop in range(3):                                         # the file's arrays, in place
+        off.append(np.frombuffer(raw, np.int64, beta + 1, at)); at += 8 * (beta + 1)
+        m = int(off[hop][-1])
+        ids.append(np.frombuffer(raw, np.int32, m, at)); at += 4 * m
+        if hop < 2:
+            so = np.frombuffer(raw, np.int64, m + 1, at); at += 8 * (m + 1)
+            nbr_at.append((so, np.frombuffer(raw, np.int32, int(so[-1]), at))); at += 4 * int(so[-1])
+    assert at == len(raw)
+    size = [np.diff(o) for o in off]
+    for b in range(beta):
+        if change == "one batch" and b != beta - 1:
+            continue
+        lo = off[2][b] + size[1][b]
+        if change in ("last hop", "one batch"):
+            ids[2][lo:off[2][b + 1]] = ids[2][lo:off[2][b + 1]][::-1].copy()
+        if change == "both hops":
+            for hop in (1, 2):
+                part = ids[hop][off[hop][b] + size[0][b]:off[hop][b] + size[1][b]]
+                part[:] = np.roll(part, 3)
+        if change == "equal":                                    # the ID behind the first is the first again: the one that was there is listed no more
+            old = int(ids[2][lo + 1])
+            ids[2][lo + 1] = ids[2][lo]
+            so, nbr = nbr_at[1]
+            mine = nbr[so[off[1][b]]:so[off[1][b + 1]]]
+            mine[mine == old] = ids[2][lo]
+        if change == "later hop":
+            so, nbr = nbr_at[0]
+            nbr[so[off[0][b]]:so[off[0][b + 1]]][::5] = ids[2][lo + 2]
+    path.write_bytes(raw)
+    first, count = batches if batches else (0, beta)
+    t = rg.rg_schedule_load_range(path, first, count) if batches else rg.rg_schedule_load(path)
+    rg.rg_schedule_build_blocks(t)
+    u_last, _, u_off = rg.rg_schedule_frontier(t, 2)
+    u_last = u_last.cpu().numpy()
+    for hop in range(2):
+        so, nbr = (x.cpu().numpy() for x in rg.rg_schedule_samples(t, hop))
+        src, f_off = rg.rg_schedule_block(t, hop).cpu().numpy(), rg.rg_schedule_frontier(t, hop)[2]
+        for b in range(count):
+            e = slice(so[f_off[b]], so[f_off[b + 1]])
+            where = src[e]
+            assert where.min() >= 0 and where.max() < u_off[b + 1] - u_off[b]
+            assert np.array_equal(u_last[u_off[b]:u_off[b + 1]][where], nbr[e])
