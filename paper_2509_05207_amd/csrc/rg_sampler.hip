@@ -2063,7 +2063,7 @@ __global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int
             i_end = place.batch_off[b + 1];
         }
         if (i0 >= i_end) continue;
-        const uint32_t n_nodes = (uint32_t)min((int64_t)unit_nodes, i_end - i0), n_draws = n_nodes * f;
+        const uint32_t n_nodes = (uint32_t)min((int64_t)unit_nodes, i_end - i0);
         wave_lds_order();                                                      // the last unit's have been read
         uint32_t my_deg = 0;
         if ((uint32_t)lane < n_nodes) {
@@ -2073,6 +2073,9 @@ __global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int
         }
         const bool selects = my_deg > f && my_deg <= DRAW_SELECT;
         wave_lds_order();
+        // (A node that is a unit by itself has rounds for what it draws, not for all of f: 100,000 rows of five IDs, fan-out 1,984, a schedule 344 us
+        // with rounds for f, so 186, with a lane per draw 197.)
+        const uint32_t n_draws = unit_nodes == 1 ? uni(min(f, nodes[0].deg)) : n_nodes * f;
         for (uint32_t d0 = 0; d0 < n_draws; d0 += POS_DRAWS) {
             const uint32_t n = uni(min((uint32_t)POS_DRAWS, n_draws - d0));
             uint32_t n_walks = 0;
