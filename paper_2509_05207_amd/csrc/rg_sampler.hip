@@ -2085,7 +2085,7 @@ __global__ void __launch_bounds__(POS_THREADS) sample_positions_kernel(const int
                 if (j < n) {
                     const uint32_t k = node_of(d0 + j), t = d0 + j - k * f, deg = nodes[k].deg;
                     walk = deg > f && deg > DRAW_SELECT;
-                    if (!walk) pos[j] = deg > f ? draw32(nodes[k].state, t) : t < deg ? t : NO_DRAW;
+                    pos[j] = walk ? NO_DRAW : deg > f ? draw32(nodes[k].state, t) : t < deg ? t : NO_DRAW;      // (a walk's until it has ended: nothing is read where a loop failed to end one)
                 }
                 const unsigned long long m = ballot64(walk);
                 if (walk) walks[n_walks + lanes_below(m, lane)] = (uint16_t)j;
