@@ -112,7 +112,7 @@ static size_t rank_lds_bytes(uint32_t L, uint64_t n_words, uint64_t most_seeds) 
 
 __global__ void __launch_bounds__(RANK_BLOCK) block_ranks_kernel(RankArgs a, uint32_t parts)
 {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];      // (read in pairs; whatever stands in front of it)
     __shared__ uint32_t ends[RG_MAX_HOPS + 1];       // where hop h's IDs end in the batch's U_L
     __shared__ uint32_t wave_sum[RANK_BLOCK / 64];
     const uint32_t n_sets = a.L + 1, n_words = a.n_words, n_pairs = n_words / 2;

@@ -2179,7 +2179,7 @@ constexpr int64_t MARK_PART = 1 << 18;                   // samples per part, at
 __global__ void __launch_bounds__(MARK_THREADS) mark_pass_kernel(const int32_t *__restrict__ samp_nbr, const int64_t *__restrict__ samp_off, const int64_t *__restrict__ batch_off,
                                                                  uint32_t n_batches, uint32_t pieces, uint32_t parts, uint32_t piece_words, ReachedMaps m)
 {
-    extern __shared__ uint32_t bits[];                   // [piece_words]
+    extern __shared__ __align__(16) uint32_t bits[];     // [piece_words], read in fours
     const uint32_t per_batch = pieces * parts, whole = n_batches / MARK_XCDS * MARK_XCDS, rest = n_batches - whole;
     uint32_t b, at;                                      // the batch, and which of its workgroups
     if (blockIdx.x < whole * per_batch) {

@@ -90,3 +90,14 @@ def test_scalar_operands_may_be_fresh(where, lines, operands):
     reads it in a vector instruction: an asm statement that takes one starts with the two states."""
     takes = any(c.lstrip("+=&") in ("s", "sgpr") for c in sum(operands[1:2], []))
     assert not takes or re.match(r"s_nop [1-9]", lines[0]), where
+
+
+def test_dynamic_lds_is_aligned_for_vectors():
+    """LDS sized at the launch begins behind a kernel's static LDS, wherever that ends, unless its declaration asks for more: kernels read it in vectors."""
+    found = 0
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.hip"))):
+        for line in open(path).read().split("\n"):
+            if "extern __shared__" in line:
+                found += 1
+                assert "__align__(16)" in line, f"{os.path.basename(path)}: {line.strip()}"
+    assert found >= 2
