@@ -15,6 +15,7 @@
 // batches, 29 M edges: positions and edges 616 us, 302 so.  With up to 128 workgroups per batch instead of 32, so that an XCD is at two
 // batches at a time and their tables (0.9 MB each) stay in its 4 MB of L2, and four positions in flight too: 252.
 #include "rg_internal.h"
+#include "rg_launch.h"
 
 #include <algorithm>
 
@@ -207,10 +208,7 @@ __global__ void __launch_bounds__(RANK_BLOCK) block_ranks_kernel(RankArgs a, uin
     }
 }
 
-// By ranks where they fit LDS, where the batches are so many that each has few workgroups to make bitmaps for, and where a batch has samples
-// enough to pay for clearing and counting them, some 18 us a round of workgroups at 233,000 nodes (by tables / by ranks: 233,000 nodes, 147 batches of
-// 199,000 samples 250 / 176 us, 31,000 95 / 60, 7,700 53 / 42; 500 of 3,400 74 / 58; 2,000 of 1,400 137 / 163, of 300 50 / 157; 100 batches of 200,000 179 / 120, 64
-// 123 / 94, 64 of 7,700 35 / 37; 40 of 200,000 86 / 83, 40 of 31,000 42 / 44, 20 of 200,000 62 / 73, one 32 / 64; 30,000 nodes, 64 of 6,000 31 / 26).
+// By ranks where they fit LDS and where that is the faster (see blocks_by_ranks).
 static bool ranks_pay(const rg_schedule *s, uint64_t n_words, int n_cu, size_t *lds_bytes)
 {
     uint64_t most_seeds = 0, edges = 0;
@@ -220,8 +218,7 @@ static bool ranks_pay(const rg_schedule *s, uint64_t n_words, int n_cu, size_t *
     *lds_bytes = rank_lds_bytes(s->L, n_words, most_seeds);
     if (*lds_bytes > RANK_LDS) return false;
     if (const char *force = getenv("RAPIDGNN_BLOCK_RANKS")) return force[0] == '1';      // same results either way; for tests and tuning
-    const uint64_t beta = s->n_batches, cus = (uint64_t)n_cu, nodes_per_edge = beta * 2 >= cus ? 64 : 16;
-    return beta * 4 >= cus && edges * nodes_per_edge >= (uint64_t)s->n_nodes * beta;
+    return blocks_by_ranks((uint64_t)s->n_nodes, s->L, s->n_batches, edges, n_cu);
 }
 
 }  // namespace rg

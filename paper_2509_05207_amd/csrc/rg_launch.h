@@ -33,4 +33,23 @@ inline PositionUnits position_units(int64_t n_cur, uint32_t fanout, bool by_plac
     return PositionUnits{(uint32_t)nodes, n, grid_for((n + POS_WAVES - 1) / POS_WAVES, POS_THREADS)};
 }
 
+// ---------------------------------------------------------------- computation blocks
+// By ranks (block_ranks_kernel) rather than by tables of positions: where the batches are so many that each has few workgroups to make bitmaps for, and where a
+// batch has samples enough to pay for clearing and counting them, some 18 us a round of workgroups at 233,000 nodes (edges: samples of all hops and batches).
+// By tables / by ranks, us: 233,000 nodes, 147 batches of 199,000 samples 250 / 176, 31,000 95 / 60, 7,700 53 / 42; 500 of 3,400 74 / 58; 2,000 of 1,400 137 / 163,
+// of 300 50 / 157; 100 batches of 200,000 179 / 120, 64 123 / 94, 64 of 7,700 35 / 37; 40 of 200,000 86 / 83, 40 of 31,000 42 / 44, 20 of 200,000 62 / 73, one 32 / 64;
+// 30,000 nodes, 64 of 6,000 31 / 26.  Two to eight hops on 20,000 to 160,000 nodes, 64 to 700 batches: 0.34 to 1.05 of the tables' time.
+// Behind the first round of workgroups a batch costs 17 ns (two hops) to 28 (four), while the tables of small graphs stay in the L2s, so that there the batch
+// has to have the more samples the smaller the graph: 1,000 batches, three hops, 8,000 nodes, 1,000 samples 40 / 45, 2,000 48 / 46; 32,000 nodes, 500
+// 40 / 44, 1,000 54 / 46; one hop, 16,000 nodes, 320 27 / 31, 640 34 / 33; 4,000 batches, 8,000 nodes, 1,000 samples 89 / 127, 32,000 nodes 161 / 129;
+// 500 batches, two hops, 16,000 nodes, 256 26 / 28, 1,100 33 / 29.
+constexpr uint64_t RANK_NODE_SAMPLES = 6000000;          // nodes times samples per batch and bitmap, from which on
+inline bool blocks_by_ranks(uint64_t n_nodes, uint32_t L, uint64_t beta, uint64_t edges, int n_cu)
+{
+    const uint64_t cus = (uint64_t)n_cu, nodes_per_edge = beta * 2 >= cus ? 64 : 16;
+    if (beta * 4 < cus || edges * nodes_per_edge < n_nodes * beta) return false;
+    const uint64_t least = beta <= cus ? 0 : beta <= 2 * cus ? RANK_NODE_SAMPLES / 4 : RANK_NODE_SAMPLES;
+    return edges * n_nodes >= least * (L + 1) * beta;
+}
+
 }  // namespace rg

@@ -18,6 +18,7 @@ int main()
             const rg::PositionUnits u = rg::position_units(a[0], (uint32_t)a[1], a[2] != 0, a[3], (uint32_t)a[4], (int)a[5]);
             printf("%u %lld %u\n", u.nodes, (long long)u.n, u.grid);
         }
+        if (!strcmp(what, "ranks")) printf("%d\n", rg::blocks_by_ranks(a[0], (uint32_t)a[1], a[2], a[3], (int)a[4]) ? 1 : 0);
     }
 }
 """
@@ -48,3 +49,26 @@ def test_units_of_the_position_sampler(shapes, n_cur, fanout, beta):
     assert n_units == (-(-longest // nodes) * beta if beta else -(-n_cur // nodes))
     assert 1 <= grid and grid * 256 < 2**32                      # what a launch may have
     assert grid * 4 >= min(n_units, 2**26 - 4)                   # a wave per unit, as far as that goes
+
+
+@pytest.mark.parametrize("n,hops,batches,per_batch,by_ranks", [
+    # measured, us by tables / by ranks
+    (233_000, 2, 147, 199_000, True),       # 250 / 176
+    (233_000, 2, 2_000, 1_400, False),      # 137 / 163
+    (233_000, 2, 1, 199_000, False),        # 32 / 64
+    (160_000, 3, 700, 3_750, True),         # 111 / 81
+    (80_000, 8, 64, 613_000, True),         # 273 / 201
+    (64_000, 4, 4_000, 2_000, True),        # 460 / 169
+    (32_000, 3, 1_000, 500, False),         # 40 / 44
+    (32_000, 3, 1_000, 1_000, True),        # 54 / 46
+    (20_000, 1, 700, 320, False),           # 25 / 30
+    (20_000, 3, 700, 1_860, True),          # 51 / 44
+    (16_000, 2, 500, 256, False),           # 26 / 28
+    (16_000, 2, 500, 1_114, True),          # 33 / 29
+    (16_000, 3, 1_000, 552, False),         # 41 / 49
+    (8_000, 3, 4_000, 1_003, False),        # 89 / 127
+    (4_000, 2, 1_000, 140, False),          # 27 / 36
+    (4_000, 3, 1_000, 138, False),          # 30 / 42
+])
+def test_blocks_by_ranks_where_they_are_faster(shapes, n, hops, batches, per_batch, by_ranks):
+    assert shapes("ranks", n, hops, batches, batches * per_batch, 256) == [int(by_ranks)]
