@@ -131,8 +131,9 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const ROUTE
 // The remote rows alone.  A wave takes per_wave consecutive rows (a power of two up to 64) per round, one route a lane, lists the
 // remote ones in LDS and copies those as the kernel above copies all: flat pieces, one per lane, CHUNKS_IN_FLIGHT under way.  Bound by
 // the host link.  (A list of the misses made with every plan took 79 us per 80 M input nodes, and a wait for its length.)
+// parts > 1 (then per_wave is 1): a row's pieces are shared out among that many waves.
 template <int VEC, int A, bool TAILPIECE, typename ROUTE>
-__global__ void __launch_bounds__(GATHER_THREADS) gather_remote_kernel(const ROUTE *__restrict__ routes, uint32_t last_remote, int64_t n_rows, int per_wave,
+__global__ void __launch_bounds__(GATHER_THREADS) gather_remote_kernel(const ROUTE *__restrict__ routes, uint32_t last_remote, int64_t n_rows, int per_wave, uint32_t parts,
                                                                        RowSources src, uint32_t row_bytes, uint8_t *__restrict__ out, uint64_t out_stride)
 {
     using T = typename VecT<VEC>::type;
@@ -147,7 +148,9 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_remote_kernel(const ROU
     const int wave_here = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);        // (a scalar: the rounds are the wave's)
     Miss *mine = lists[wave_here];
     const int64_t n_waves = (int64_t)gridDim.x * (GATHER_THREADS / 64), wave = (int64_t)blockIdx.x * (GATHER_THREADS / 64) + wave_here;
-    for (int64_t first = wave * per_wave; first < n_rows; first += n_waves * per_wave) {
+    for (int64_t unit = wave; unit * per_wave < n_rows * parts; unit += n_waves) {
+        const int64_t first = parts == 1 ? unit * per_wave : unit / parts;
+        const uint32_t part = parts == 1 ? 0u : (uint32_t)(unit - first * parts);
         int64_t tag = TAG_LOCAL;
         uint64_t row = 0;
         if (lane < per_wave && first + lane < n_rows) decode_route(routes[first + lane], last_remote, tag, row);
@@ -156,9 +159,11 @@ __global__ void __launch_bounds__(GATHER_THREADS) gather_remote_kernel(const ROU
         wave_lds_order();                                          // the last round's list has been read
         if (miss) mine[__popcll(all & ((1ull << lane) - 1ull))] = Miss{row, (uint64_t)(first + lane)};
         wave_lds_order();
-        const uint64_t total = (uint64_t)__popcll(all) * cpt;      // (64 rows of up to 2^32 bytes)
+        const uint64_t pieces = (uint64_t)__popcll(all) * cpt;     // (64 rows of up to 2^32 bytes)
+        const uint64_t begin = parts == 1 ? 0u : pieces * part / parts, total = parts == 1 ? pieces : pieces * (part + 1) / parts;
         uint32_t m = (uint32_t)lane / cpt, c = (uint32_t)lane - m * cpt;
-        for (uint64_t idx = lane; idx < total;) {
+        if (parts != 1) { m = 0; c = (uint32_t)begin + lane; }
+        for (uint64_t idx = begin + lane; idx < total;) {
             T v[CHUNKS_IN_FLIGHT];
             const uint8_t *sp[CHUNKS_IN_FLIGHT];
             uint8_t *dp[CHUNKS_IN_FLIGHT];
@@ -205,7 +210,7 @@ static int common_alignment(const RowSources &s, const uint8_t *out, uint64_t ou
 }
 
 rg_status launch_gather(const Routes &routes, int64_t n_rows, RowsWanted wanted, const RowSources &src, uint32_t row_bytes, uint8_t *out, uint64_t out_stride,
-                        hipStream_t st, int group)
+                        hipStream_t st, int group, int64_t n_remote)
 {
     if (n_rows <= 0) return RG_OK;
     int align = common_alignment(src, out, out_stride);
@@ -231,14 +236,25 @@ rg_status launch_gather(const Routes &routes, int64_t n_rows, RowsWanted wanted,
     // 2,408 bytes, 1,971 us at one row a wave and the link's rate, 1,979 at 32; a list of the misses 1,974)
     int per_wave = 1;
     while (per_wave < 64 && per_wave * cpt < 128 && n_rows / (2 * per_wave) >= (int64_t)n_cu * 8) per_wave <<= 1;
-    const int64_t per_remote_block = per_wave * (GATHER_THREADS / 64);
-    const unsigned remote_blocks = (unsigned)std::min<int64_t>((n_rows + per_remote_block - 1) / per_remote_block, (int64_t)n_cu * 32);
+    // Few misses of wide rows: a row's pieces are shared out among waves, a round of them (8 KB) or more each (8 rows of 1 MB 419 us with a wave a row, 163 so,
+    // 174 with a list of the misses; one 352 / 32 / 39; with parts for 512 waves, not 64, 64 rows of 64 KB 104 us for 88).
+    int64_t parts = 1;
+    if (per_wave == 1)
+        while (n_remote * parts < 64 && cpt >= (uint64_t)parts * 2 * 64 * CHUNKS_IN_FLIGHT && n_rows * parts <= (int64_t)n_cu * 64) parts *= 2;
+    // Where all rows would be asked for at once and half of them and more are misses, the link is at its best with some hundred waves' loads on it; fewer misses
+    // need more waves to find them, and more rows take further rounds (a list of misses / all waves / LINK_WAVES: 1,000 rows of 16 KB, misses alone 316 / 338 / 306
+    // us; 3,000 of 4 KB 243 / 275 / 229; 30,000 of 400 bytes 308 / 313 / 285, half of them misses 166 / 167 / 159; 20,000 of 2,408 bytes, half 480 / 470 / 483, a
+    // twentieth 79 / 71 / 85; 100,000, misses alone, on a stream beside 4,540 / 4,520 / 4,680).
+    constexpr int64_t LINK_WAVES = 256, waves_here = GATHER_THREADS / 64;
+    const int64_t n_units = (n_rows * parts + per_wave - 1) / per_wave, all_waves = (int64_t)n_cu * 32 * waves_here;
+    const int64_t n_waves = std::min(n_units, n_units <= all_waves && n_remote * 2 >= n_rows ? LINK_WAVES : all_waves);
+    const unsigned remote_blocks = (unsigned)((n_waves + waves_here - 1) / waves_here);
     ScopedTimer tm(group, st);
 #define RG_GATHER_ROWS(V, AL, TAIL, ROUTE, FROM)                                                                                              \
     do {                                                                                                                                      \
         if (wanted == ROWS_REMOTE)                                                                                                            \
             hipLaunchKernelGGL((gather_remote_kernel<V, AL, TAIL, ROUTE>), dim3(remote_blocks), dim3(GATHER_THREADS), 0, st, FROM,            \
-                               routes.last_remote, n_rows, per_wave, src, row_bytes, out, out_stride);                                        \
+                               routes.last_remote, n_rows, per_wave, (uint32_t)parts, src, row_bytes, out, out_stride);                       \
         else                                                                                                                                  \
             hipLaunchKernelGGL((gather_rows_kernel<V, AL, TAIL, ROUTE>), dim3((unsigned)blocks), dim3(GATHER_THREADS), 0, st, FROM,           \
                                routes.last_remote, n_rows, skip_remote, src, row_bytes, out, out_stride, chunks);                             \
@@ -463,13 +479,13 @@ extern "C" rg_status rg_gather_batch(const rg_schedule *s, const rg_cache *c, co
         } else if (side != st) {
             RG_HIP(hipEventRecord(c->ev_fork, st));            // earlier work on `stream` may still use `out`
             RG_HIP(hipStreamWaitEvent(side, c->ev_fork, 0));
-            RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, side, KG_MISS));
+            RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, side, KG_MISS, n_miss));
             RG_HIP(hipEventRecord(c->ev_join, side));
             RG_TRY(launch_gather(routes, m, ROWS_NOT_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
             RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));
         } else {
             RG_TRY(launch_gather(routes, m, ROWS_NOT_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
-            RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_MISS));
+            RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_MISS, n_miss));
         }
         UseLog::note(s->uses, c->uses, st);                    // the launches above read the schedule's and the cache's arrays after this call returns
         if (stats) *stats = plan->stats[batch];
@@ -557,7 +573,7 @@ extern "C" rg_status rg_gather_batches(const rg_schedule *s, const rg_cache *c, 
             RG_HIP(hipStreamWaitEvent(side, c->ev_fork, 0));
         }
         RG_TRY(launch_gather(routes, m, ROWS_NOT_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, st, KG_GATHER));
-        RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, side, KG_MISS));
+        RG_TRY(launch_gather(routes, m, ROWS_REMOTE, src, f->row_bytes, (uint8_t *)out, out_stride, side, KG_MISS, n_miss));
         if (side != st) {
             RG_HIP(hipEventRecord(c->ev_join, side));
             RG_HIP(hipStreamWaitEvent(st, c->ev_join, 0));

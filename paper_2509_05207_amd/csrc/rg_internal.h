@@ -235,10 +235,10 @@ struct RowSources {
     const uint8_t *cache_rows; uint64_t cache_stride;
     const uint8_t *remote_rows; uint64_t remote_stride;
 };
-// Copies the rows [0, n_rows) of `out`: all of them, those that are not remote, or the remote ones alone.
+// Copies the rows [0, n_rows) of `out`: all of them, those that are not remote, or the remote ones alone (n_remote of them).
 enum RowsWanted { ROWS_ALL, ROWS_NOT_REMOTE, ROWS_REMOTE };
 rg_status launch_gather(const Routes &routes, int64_t n_rows, RowsWanted wanted, const RowSources &src, uint32_t row_bytes, uint8_t *out, uint64_t out_stride,
-                        hipStream_t st, int group);
+                        hipStream_t st, int group, int64_t n_remote = 0);
 
 // A few small values read back from the device behind one stream synchronisation.  They travel through a pinned
 // staging block (kept in a pool for the life of the process): a copy into pageable memory costs the runtime

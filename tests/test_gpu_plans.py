@@ -165,6 +165,34 @@ def test_misses_of_a_pinned_table(rg, n, missing, row_bytes):
         assert (got[:, row_bytes:] == 7).all()
 
 
+@pytest.mark.parametrize("row_bytes", [16383, 16384, 16400, 30_002, 100_004, (1 << 20) + 4])
+@pytest.mark.parametrize("n,missing", [(1, 1.0), (7, 1.0), (40, 0.5), (600, 0.01)])
+def test_few_misses_of_wide_rows(rg, n, missing, row_bytes):
+    """Rows whose pieces are shared out among waves: one part and many, widths that the parts do not divide, vectors, overlapping last vectors and odd tails."""
+    if n * row_bytes > 64 << 20:
+        pytest.skip("wide rows at the smaller counts")
+    d = "cuda"
+    rng = np.random.default_rng(n + row_bytes)
+    indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
+    s = rg.rg_build_schedule(indptr, indices, torch.arange(n, dtype=torch.int32, device=d), n, [], 5, 0, 0)
+    is_local = np.ones(n, np.uint8)
+    is_local[rng.permutation(n)[: max(1, int(n * missing))]] = 0
+    row_of = np.where(is_local, np.cumsum(is_local) - 1, np.cumsum(1 - is_local) - 1).astype(np.int32)
+    table = rng.integers(0, 256, size=(n, row_bytes + 5)).astype(np.uint8)
+    for pad in (0, 4):                                           # strides of the tables and of the block
+        rows = np.ascontiguousarray(table[:, : row_bytes + pad])
+        local = torch.from_numpy(np.concatenate([rows[is_local == 1], rows[:1]])).to(d)
+        remote = torch.from_numpy(np.concatenate([rows[is_local == 0], rows[:1]])).pin_memory()
+        feat = rg.make_features(torch.from_numpy(is_local).to(d), torch.from_numpy(row_of).to(d), local, remote, row_bytes)
+        cache = rg.rg_build_cache([s], feat, 0)
+        out = torch.full((n, row_bytes + pad), 7, dtype=torch.uint8, device=d)
+        rg.rg_gather_batch(s, cache, feat, 0, out, out_stride=row_bytes + pad)
+        torch.cuda.synchronize()
+        got, ids = out.cpu().numpy(), rg.rg_schedule_frontier(s, 0)[0].cpu().numpy()
+        assert np.array_equal(got[:, :row_bytes], rows[ids][:, :row_bytes])
+        assert (got[:, row_bytes:] == 7).all()
+
+
 @pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 50_000])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_candidates_counted_by_the_histogram(rg, n, shift, monkeypatch):
