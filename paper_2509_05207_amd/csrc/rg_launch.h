@@ -23,12 +23,18 @@ struct PositionUnits {
 // As many draws to a unit as a wave has room for, or as few as give every wave that the chip holds a unit.  by_place: the units of each of beta batches
 // are counted as those of the longest (see ByPlace).  A wave per unit: waves that walk over the units by turns drift apart, and with them what they read (292
 // us, so 312); only where a launch cannot have that many waves do they.
-inline PositionUnits position_units(int64_t n_cur, uint32_t fanout, bool by_place, int64_t longest, uint32_t beta, int n_cu)
+// scattered: the waves mark their n_samples in maps of 8.4 M IDs and more.  Every mark is then a line of its own, which the launch waits for, and fewer draws to a
+// unit pay up to POS_SCATTERED rounds of waves, as long as a unit has POS_SAMPLES of the samples (15 M nodes, rows of 30 IDs, units of 256 / 128 / 64 draws, us: 150,000 nodes of fan-out 16
+// 130 / 119 / 115, 30 212 / 198 / 189; 1,000,000 of 4 198 / 187 / 179, of 10 397 / 388 / 388, of 23 871 / 872 / 917; rows of 100, 150,000 of 50 339 / 315 / 309; 60 M nodes, rows of 8 IDs,
+// 1,000,000 of 10 440 / 417 / 401, of 50 406 / 403 / 482).
+constexpr int64_t POS_SCATTERED = 16, POS_SAMPLES = 32;
+inline PositionUnits position_units(int64_t n_cur, int64_t n_samples, uint32_t fanout, bool by_place, int64_t longest, uint32_t beta, int n_cu, bool scattered)
 {
-    const int64_t waves = (int64_t)n_cu * 32;
+    const int64_t waves = (int64_t)n_cu * 32, all = n_cur * (int64_t)fanout;
+    const auto nodes_of = [&](int64_t draws) { return std::max<int64_t>(1, std::min<int64_t>(64, draws / fanout)); };
     int64_t draws = POS_DRAWS;
-    while (draws > POS_LEAST && n_cur * fanout < draws * waves) draws /= 2;
-    const int64_t nodes = std::max<int64_t>(1, std::min<int64_t>(64, draws / fanout));
+    while (draws > POS_LEAST && (all < draws * waves || (scattered && all < draws * waves * POS_SCATTERED && nodes_of(draws / 2) * n_samples >= POS_SAMPLES * n_cur))) draws /= 2;
+    const int64_t nodes = nodes_of(draws);
     const int64_t n = by_place ? (longest + nodes - 1) / nodes * beta : (n_cur + nodes - 1) / nodes;
     return PositionUnits{(uint32_t)nodes, n, grid_for((n + POS_WAVES - 1) / POS_WAVES, POS_THREADS)};
 }

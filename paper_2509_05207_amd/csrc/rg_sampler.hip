@@ -2390,7 +2390,7 @@ rg_status sample_hop(const rg_graph *g, HopData &cur, uint32_t beta, const uint6
     if (sampler == RG_SAMPLER_POSITIONS) {
         if (fanout > 0 && n_cur > 0) {
             ScopedTimer tm(KG_SAMPLER, st);
-            const PositionUnits units = position_units(n_cur, fanout, place.n_batches != 0, place.longest, beta, n_cu);
+            const PositionUnits units = position_units(n_cur, cur.n_samples, fanout, place.n_batches != 0, place.longest, beta, n_cu, reached.paired);
 #define RG_POSITIONS(M, P) hipLaunchKernelGGL((sample_positions_kernel<M, P>), dim3(units.grid), dim3(POS_THREADS), 0, st, g->indices, rec, n_cur, fanout, units.nodes, cur.samp_off, cur.samp_nbr, reached, place, units.n)
             if (inline_marks && place.n_batches) RG_POSITIONS(MARK_BITS, true);
             else if (inline_marks) RG_POSITIONS(MARK_BITS, false);

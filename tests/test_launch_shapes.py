@@ -12,10 +12,10 @@ DRIVER = r"""
 int main()
 {
     char what[32];
-    long long a[6];
-    while (scanf("%31s %lld %lld %lld %lld %lld %lld", what, a, a + 1, a + 2, a + 3, a + 4, a + 5) == 7) {
+    long long a[8];
+    while (scanf("%31s %lld %lld %lld %lld %lld %lld %lld %lld", what, a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6, a + 7) == 9) {
         if (!strcmp(what, "positions")) {
-            const rg::PositionUnits u = rg::position_units(a[0], (uint32_t)a[1], a[2] != 0, a[3], (uint32_t)a[4], (int)a[5]);
+            const rg::PositionUnits u = rg::position_units(a[0], a[1], (uint32_t)a[2], a[3] != 0, a[4], (uint32_t)a[5], (int)a[6], a[7] != 0);
             printf("%u %lld %u\n", u.nodes, (long long)u.n, u.grid);
         }
         if (!strcmp(what, "ranks")) printf("%d\n", rg::blocks_by_ranks(a[0], (uint32_t)a[1], a[2], a[3], (int)a[4]) ? 1 : 0);
@@ -31,24 +31,40 @@ def shapes(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, "-o", str(d / "driver"), str(d / "driver.cpp")])
 
     def ask(what, *args):
-        line = " ".join([what] + [str(int(x)) for x in args] + ["0"] * (6 - len(args)))
+        line = " ".join([what] + [str(int(x)) for x in args] + ["0"] * (8 - len(args)))
         return [int(x) for x in subprocess.run([str(d / "driver")], input=line + "\n", capture_output=True, text=True, check=True).stdout.split()]
     return ask
 
 
 @pytest.mark.parametrize("fanout", [1, 3, 25, 50, 64, 85, 86, 128, 129, 256, 1984])
+@pytest.mark.parametrize("scattered", [False, True])
 @pytest.mark.parametrize("n_cur", [1, 64, 40_000, 2**26, 2**27 + 1, 2**30 - 1, 2**31 - 1, 80 * 10**9])
 @pytest.mark.parametrize("beta", [0, 1, 147, 65_535])
-def test_units_of_the_position_sampler(shapes, n_cur, fanout, beta):
+def test_units_of_the_position_sampler(shapes, n_cur, fanout, beta, scattered):
     """beta > 0: batches of equal length by place, which frontiers of up to 2^30 nodes go by."""
     if beta and n_cur >= 2**30:
         pytest.skip("by position")
     longest = -(-n_cur // max(beta, 1))
-    nodes, n_units, grid = shapes("positions", n_cur, fanout, beta > 0, longest, beta, 256)
+    nodes, n_units, grid = shapes("positions", n_cur, n_cur * min(fanout, 40), fanout, beta > 0, longest, beta, 256, scattered)
     assert 1 <= nodes <= 64 and (nodes == 1 or nodes * fanout <= 256)
     assert n_units == (-(-longest // nodes) * beta if beta else -(-n_cur // nodes))
     assert 1 <= grid and grid * 256 < 2**32                      # what a launch may have
     assert grid * 4 >= min(n_units, 2**26 - 4)                   # a wave per unit, as far as that goes
+
+
+@pytest.mark.parametrize("n_cur,row,fanout,scattered,nodes", [
+    # measured, us with 64 / 128 / 256 draws to a unit
+    (3_700_000, 500, 10, False, 25),     # 468 / 346 / 292, the walks
+    (150_000, 30, 16, True, 4),          # 115 / 119 / 130, marks all over a map of 15 M IDs
+    (150_000, 30, 30, True, 2),          # 189 / 198 / 212
+    (150_000, 100, 50, True, 1),         # 309 / 315 / 339
+    (1_000_000, 30, 4, True, 16),        # 179 / 187 / 198
+    (1_000_000, 30, 23, True, 5),        # 917 / 872 / 871
+    (1_000_000, 8, 10, True, 6),         # 401 / 417 / 440
+    (1_000_000, 8, 50, True, 5),         # 482 / 403 / 406
+])
+def test_units_by_what_bounds_them(shapes, n_cur, row, fanout, scattered, nodes):
+    assert shapes("positions", n_cur, n_cur * min(row, fanout), fanout, 0, 0, 0, 256, scattered)[0] == nodes
 
 
 @pytest.mark.parametrize("n,hops,batches,per_batch,by_ranks", [
