@@ -121,102 +121,76 @@ __global__ void __launch_bounds__(TOPK_THREADS) digit_histogram_kernel(const uin
 // bytes that are candidates (non-zero count, not local).
 __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t w) { return (w | ((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu)) & 0x80808080u; }   // bit 7 of every non-zero byte
 
-template <bool WIDE>
-__global__ void __launch_bounds__(TOPK_THREADS) digit_histogram8_kernel(const uint8_t *__restrict__ freq, const uint8_t *__restrict__ is_local, int64_t n,
-                                                                        const SelectState *__restrict__ stp, unsigned long long *__restrict__ bins)
+// The candidates among four and among sixteen consecutive nodes into the histogram h (LDS); how many they are.
+__device__ __forceinline__ int count_word(unsigned int *h, uint32_t fw, uint32_t lw)
 {
-    __shared__ unsigned int h[DIGIT_BINS];
-    for (int k = threadIdx.x; k < DIGIT_BINS; k += TOPK_THREADS) h[k] = 0;
-    __syncthreads();
-    if (stp->take_all) return;
-    int64_t done = 0;
-    if (WIDE) {
-        auto count_word = [&](uint32_t fw, uint32_t lw) {
-            uint32_t cand = nonzero_bytes(fw) & ~nonzero_bytes(lw);
-            while (cand) {
-                const int top = __ffs((int)cand) - 1;              // bit 7 of the candidate's byte
-                cand &= cand - 1;
-                atomicAdd(&h[(fw >> (top - 7)) & 0xFFu], 1u);
-            }
-        };
-        auto count16 = [&](const uint4 fv, const uint4 lv) {
-            if ((fv.x | fv.y | fv.z | fv.w) == 0u) return;
-            count_word(fv.x, lv.x); count_word(fv.y, lv.y); count_word(fv.z, lv.z); count_word(fv.w, lv.w);
-        };
-        const int64_t n16 = n >> 4;
-        const int64_t span = (n16 + gridDim.x - 1) / gridDim.x;
-        const int64_t q_end = min(n16, (int64_t)(blockIdx.x + 1) * span);
-        int64_t q = (int64_t)blockIdx.x * span + threadIdx.x;
-        for (; q + TOPK_THREADS < q_end; q += 2 * TOPK_THREADS) {
-            const uint4 f0 = reinterpret_cast<const uint4 *>(freq)[q], f1 = reinterpret_cast<const uint4 *>(freq)[q + TOPK_THREADS];
-            const uint4 l0 = reinterpret_cast<const uint4 *>(is_local)[q], l1 = reinterpret_cast<const uint4 *>(is_local)[q + TOPK_THREADS];
-            count16(f0, l0); count16(f1, l1);
-        }
-        for (; q < q_end; q += TOPK_THREADS) count16(reinterpret_cast<const uint4 *>(freq)[q], reinterpret_cast<const uint4 *>(is_local)[q]);
-        done = n16 << 4;
+    uint32_t cand = nonzero_bytes(fw) & ~nonzero_bytes(lw);
+    const int n_here = __popc(cand);
+    while (cand) {
+        const int top = __ffs((int)cand) - 1;                  // bit 7 of the candidate's byte
+        cand &= cand - 1;
+        atomicAdd(&h[(fw >> (top - 7)) & 0xFFu], 1u);
     }
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t v = done + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-        const uint32_t fv = freq[v];
-        if (fv != 0 && !is_local[v]) atomicAdd(&h[fv], 1u);
-    }
-    __syncthreads();
-    unsigned long long *mine = bins + (size_t)(blockIdx.x % BIN_COPIES) * DIGIT_BINS;
-    for (int k = threadIdx.x; k < DIGIT_BINS; k += TOPK_THREADS)
-        if (h[k]) atomicAdd(&mine[k], (unsigned long long)h[k]);
+    return n_here;
+}
+__device__ __forceinline__ int count16(unsigned int *h, const uint4 fv, const uint4 lv)
+{
+    if ((fv.x | fv.y | fv.z | fv.w) == 0u) return 0;          // most nodes are never listed
+    return count_word(h, fv.x, lv.x) + count_word(h, fv.y, lv.y) + count_word(h, fv.z, lv.z) + count_word(h, fv.w, lv.w);
 }
 
-// The same by waves that take SEL_TILE consecutive nodes at a time and also leave their number of candidates, which is the select passes' total
-// of those nodes wherever all candidates are taken (111 M nodes: a pass of 58 us that need not be).  From CANDIDATES_NODES on: a graph of fewer
-// tiles leaves waves idle (10,000 nodes: 4.1 us by the kernel above, 9.9 so, and 3 to spare).
-constexpr int64_t CANDIDATES_NODES = 1 << 23;
+// A wave takes SEL_TILE consecutive nodes at a time and also leaves their number of candidates, which is the select passes' total of those nodes wherever all
+// candidates are taken (111 M nodes: a pass of 58 us that need not be).  In the last tile a lane has sixteen nodes to a load as far as they go, then
+// one (one after the other from its start: 10 M nodes, the selection 46 us -> 52).
 template <bool WIDE>
-__global__ void __launch_bounds__(TOPK_THREADS) candidates_histogram8_kernel(const uint8_t *__restrict__ freq, const uint8_t *__restrict__ is_local, int64_t n,
+__global__ void __launch_bounds__(TOPK_THREADS) digit_histogram8_kernel(const uint8_t *__restrict__ freq, const uint8_t *__restrict__ is_local, int64_t n,
                                                                         unsigned long long *__restrict__ bins, uint64_t *__restrict__ block_tot)
 {
     __shared__ unsigned int h[DIGIT_BINS];
     for (int k = threadIdx.x; k < DIGIT_BINS; k += TOPK_THREADS) h[k] = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    auto count_word = [&](uint32_t fw, uint32_t lw) {
-        uint32_t cand = nonzero_bytes(fw) & ~nonzero_bytes(lw);
-        const int n_here = __popc(cand);
-        while (cand) {
-            const int top = __ffs((int)cand) - 1;              // bit 7 of the candidate's byte
-            cand &= cand - 1;
-            atomicAdd(&h[(fw >> (top - 7)) & 0xFFu], 1u);
-        }
-        return n_here;
-    };
-    auto count16 = [&](const uint4 fv, const uint4 lv) {
-        if ((fv.x | fv.y | fv.z | fv.w) == 0u) return 0;      // most nodes are never listed
-        return count_word(fv.x, lv.x) + count_word(fv.y, lv.y) + count_word(fv.z, lv.z) + count_word(fv.w, lv.w);
-    };
-    constexpr int LOADS = SEL_TILE / (64 * 16);
+    constexpr int LOADS = SEL_TILE / (64 * 16), IN_FLIGHT = 8;
     static_assert(SEL_TILE == LOADS * 64 * 16, "a wave's loads are a tile");
-    // a wave's tiles are consecutive
-    const int64_t n_tiles = (n + SEL_TILE - 1) / SEL_TILE, n_waves = (int64_t)gridDim.x * (TOPK_THREADS / 64);
-    const int64_t per_wave = (n_tiles + n_waves - 1) / n_waves, wave = (int64_t)blockIdx.x * (TOPK_THREADS / 64) + (threadIdx.x >> 6);
-    const int64_t t_end = min(n_tiles, (wave + 1) * per_wave);
-    for (int64_t t = wave * per_wave; t < t_end; ++t) {
+    auto count_tile = [&](int64_t t, auto is_whole) {
+        constexpr bool WHOLE = decltype(is_whole)::value;
+        const int64_t first = t * SEL_TILE, left = n - first;
         int here = 0;
-        if (WIDE && (t + 1) * SEL_TILE <= n) {
-            const uint4 *fq = reinterpret_cast<const uint4 *>(freq + t * SEL_TILE), *lq = reinterpret_cast<const uint4 *>(is_local + t * SEL_TILE);
+        if constexpr (WIDE) {
+            const uint4 *fq = reinterpret_cast<const uint4 *>(freq + first), *lq = reinterpret_cast<const uint4 *>(is_local + first);
             uint4 f[LOADS], l[LOADS];
 #pragma unroll
-            for (int k = 0; k < LOADS; ++k) { f[k] = fq[k * 64 + lane]; l[k] = lq[k * 64 + lane]; }
+            for (int k = 0; k < LOADS; ++k) {
+                if (!WHOLE) f[k] = l[k] = make_uint4(0u, 0u, 0u, 0u);
+                if (WHOLE || (k * 64 + lane + 1) * 16 <= left) { f[k] = fq[k * 64 + lane]; l[k] = lq[k * 64 + lane]; }
+            }
 #pragma unroll
-            for (int k = 0; k < LOADS; ++k) here += count16(f[k], l[k]);
+            for (int k = 0; k < LOADS; ++k) here += count16(h, f[k], l[k]);
+            if (!WHOLE && lane < (left & 15)) {
+                const int64_t v = n - (left & 15) + lane;
+                if (freq[v] != 0 && !is_local[v]) { atomicAdd(&h[freq[v]], 1u); ++here; }
+            }
         } else {
-            const int64_t end = min(n, (t + 1) * SEL_TILE);
-            for (int64_t v = t * SEL_TILE + lane; v < end; v += 64) {
-                const uint32_t fv = freq[v];
-                if (fv != 0 && !is_local[v]) { atomicAdd(&h[fv], 1u); ++here; }
+            for (int64_t j = lane; j < (WHOLE ? SEL_TILE : left); j += 64 * IN_FLIGHT) {
+                uint8_t f[IN_FLIGHT], l[IN_FLIGHT];
+#pragma unroll
+                for (int k = 0; k < IN_FLIGHT; ++k) f[k] = WHOLE || j + 64 * k < left ? freq[first + j + 64 * k] : 0;
+#pragma unroll
+                for (int k = 0; k < IN_FLIGHT; ++k) l[k] = f[k] != 0 ? is_local[first + j + 64 * k] : 1;
+#pragma unroll
+                for (int k = 0; k < IN_FLIGHT; ++k)
+                    if (!l[k]) { atomicAdd(&h[f[k]], 1u); ++here; }
             }
         }
         for (int o = 32; o > 0; o >>= 1) here += __shfl_down(here, o, 64);
         if (lane == 0) block_tot[t] = (uint64_t)here << 32;
-    }
+    };
+    // a wave's tiles are consecutive; the last one of all may be a part
+    const int64_t n_whole = n / SEL_TILE, n_tiles = (n + SEL_TILE - 1) / SEL_TILE, n_waves = (int64_t)gridDim.x * (TOPK_THREADS / 64);
+    const int64_t per_wave = (n_tiles + n_waves - 1) / n_waves, wave = (int64_t)blockIdx.x * (TOPK_THREADS / 64) + (threadIdx.x >> 6);
+    const int64_t t_end = min(n_whole, (wave + 1) * per_wave);
+    for (int64_t t = wave * per_wave; t < t_end; ++t) count_tile(t, std::true_type{});
+    if (n_whole < n_tiles && wave == n_whole / per_wave) count_tile(n_whole, std::false_type{});
     __syncthreads();
     unsigned long long *mine = bins + (size_t)(blockIdx.x % BIN_COPIES) * DIGIT_BINS;
     for (int k = threadIdx.x; k < DIGIT_BINS; k += TOPK_THREADS)
@@ -362,11 +336,11 @@ __device__ __forceinline__ uint64_t block_exclusive_scan_u64(uint64_t x, uint64_
 
 template <bool ALIGNED8, typename F>
 __global__ void __launch_bounds__(TOPK_THREADS) select_block_totals(const F *__restrict__ freq, const uint8_t *__restrict__ is_local, int64_t n,
-                                                                    const SelectState *__restrict__ stp, int candidates_known, uint64_t *__restrict__ block_tot)
+                                                                    const SelectState *__restrict__ stp, uint64_t *__restrict__ block_tot)
 {
     __shared__ uint64_t lds[TOPK_THREADS / 64];
     const SelectState st = *stp;
-    if (candidates_known && st.take_all) return;               // (candidates_histogram8_kernel has left the totals)
+    if (sizeof(F) == 1 && st.take_all) return;                 // (digit_histogram8_kernel has left the totals)
     const int64_t n_blocks = (n + SEL_TILE - 1) / SEL_TILE;
     for (int64_t block = blockIdx.x; block < n_blocks; block += gridDim.x) {
         const int64_t first = block * SEL_TILE + (int64_t)threadIdx.x * SEL_PER_THREAD;
@@ -861,8 +835,6 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
     int bits = 1;
     while (bits < 32 && (max_freq >> bits) != 0) ++bits;
     const int passes = (bits + DIGIT_BITS - 1) / DIGIT_BITS;
-    bool candidates_known = narrow && n >= CANDIDATES_NODES;
-    if (const char *force = getenv("RAPIDGNN_COUNT_CANDIDATES")) candidates_known = narrow && force[0] == '1';      // same results either way; for tests and tuning
     const bool local4 = ((uintptr_t)f->is_local & 3) == 0, local8 = ((uintptr_t)f->is_local & 7) == 0,      // the caller's array: wide loads only if it allows them
                local16 = ((uintptr_t)f->is_local & 15) == 0;
     const int64_t sel_blocks = (n + SEL_TILE - 1) / SEL_TILE;
@@ -877,20 +849,18 @@ static rg_status build_cache_impl(const rg_schedule *const *epochs, uint32_t n_e
         for (int p = 0; p < passes; ++p) {
             const int shift = (passes - 1 - p) * DIGIT_BITS;
             if (narrow) {
-                if (candidates_known && local16) hipLaunchKernelGGL(candidates_histogram8_kernel<true>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, bins, block_tot);
-                else if (candidates_known) hipLaunchKernelGGL(candidates_histogram8_kernel<false>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, bins, block_tot);
-                else if (local16) hipLaunchKernelGGL(digit_histogram8_kernel<true>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, stp, bins);
-                else hipLaunchKernelGGL(digit_histogram8_kernel<false>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, stp, bins);
+                if (local16) hipLaunchKernelGGL(digit_histogram8_kernel<true>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, bins, block_tot);
+                else hipLaunchKernelGGL(digit_histogram8_kernel<false>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq8, f->is_local, n, bins, block_tot);
             } else if (local4) hipLaunchKernelGGL(digit_histogram_kernel<true>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq, f->is_local, n, stp, shift, bins);
             else hipLaunchKernelGGL(digit_histogram_kernel<false>, dim3(grid), dim3(TOPK_THREADS), 0, st, c->freq, f->is_local, n, stp, shift, bins);
             hipLaunchKernelGGL(choose_digit_kernel, dim3(1), dim3(DIGIT_BINS), 0, st, stp, bins, shift, p == 0 ? 1 : 0, K);
         }
         if (sel_blocks > 0) {
             const dim3 tg((unsigned)std::min<int64_t>(sel_blocks, (int64_t)n_cu * 32)), sb(TOPK_THREADS);
-            if (narrow && local8) hipLaunchKernelGGL((select_block_totals<true, uint8_t>), tg, sb, 0, st, c->freq8, f->is_local, n, stp, candidates_known ? 1 : 0, block_tot);
-            else if (narrow) hipLaunchKernelGGL((select_block_totals<false, uint8_t>), tg, sb, 0, st, c->freq8, f->is_local, n, stp, candidates_known ? 1 : 0, block_tot);
-            else if (local8) hipLaunchKernelGGL((select_block_totals<true, uint32_t>), tg, sb, 0, st, c->freq, f->is_local, n, stp, candidates_known ? 1 : 0, block_tot);
-            else hipLaunchKernelGGL((select_block_totals<false, uint32_t>), tg, sb, 0, st, c->freq, f->is_local, n, stp, candidates_known ? 1 : 0, block_tot);
+            if (narrow && local8) hipLaunchKernelGGL((select_block_totals<true, uint8_t>), tg, sb, 0, st, c->freq8, f->is_local, n, stp, block_tot);
+            else if (narrow) hipLaunchKernelGGL((select_block_totals<false, uint8_t>), tg, sb, 0, st, c->freq8, f->is_local, n, stp, block_tot);
+            else if (local8) hipLaunchKernelGGL((select_block_totals<true, uint32_t>), tg, sb, 0, st, c->freq, f->is_local, n, stp, block_tot);
+            else hipLaunchKernelGGL((select_block_totals<false, uint32_t>), tg, sb, 0, st, c->freq, f->is_local, n, stp, block_tot);
             hipLaunchKernelGGL(select_scan_tiles, dim3((unsigned)sel_tiles), dim3(TOPK_THREADS), 0, st, block_tot, sel_blocks, tile_tot);
             if (sel_tiles > 1) hipLaunchKernelGGL(select_scan_totals, dim3(1), dim3(TOPK_THREADS), 0, st, tile_tot, sel_tiles);
         }

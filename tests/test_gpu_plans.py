@@ -193,11 +193,11 @@ def test_few_misses_of_wide_rows(rg, n, missing, row_bytes):
         assert (got[:, row_bytes:] == 7).all()
 
 
-@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 50_000])
+@pytest.mark.parametrize("n", [1, 15, 16, 1039, 2047, 2048, 2049, 2064, 50_000])
 @pytest.mark.parametrize("shift", [0, 1])
-def test_candidates_counted_by_the_histogram(rg, n, shift, monkeypatch):
-    """The histogram that leaves the candidates of every 2,048 nodes, and the one that does not: caches that hold all candidates, one less, and none, with
-    is_local at an aligned address and not."""
+def test_candidates_counted_by_the_histogram(rg, n, shift):
+    """The byte histogram leaves the candidates of every 2,048 nodes: caches that hold all candidates, one less, and none, with is_local at an aligned address
+    and not, and last tiles of one node, of sixteen and of parts of both."""
     d = "cuda"
     rng = np.random.default_rng(n)
     indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
@@ -212,6 +212,4 @@ def test_candidates_counted_by_the_histogram(rg, n, shift, monkeypatch):
     cand = np.flatnonzero((freq > 0) & (is_local[shift:] == 0))
     for K in sorted({0, max(0, cand.size - 1), cand.size, n + 5}):
         want = np.sort(cand[np.lexsort((cand, -freq[cand]))[:K]])
-        for force in ("1", "0"):
-            monkeypatch.setenv("RAPIDGNN_COUNT_CANDIDATES", force)
-            assert np.array_equal(rg.rg_cache_view(rg.rg_build_cache(scheds, feat, K), n)["cache_ids"].cpu().numpy(), want)
+        assert np.array_equal(rg.rg_cache_view(rg.rg_build_cache(scheds, feat, K), n)["cache_ids"].cpu().numpy(), want)
