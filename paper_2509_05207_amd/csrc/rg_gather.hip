@@ -16,6 +16,7 @@
 // launch on the main stream copies every row.
 #include "rg_internal.h"
 #include "rg_device.h"
+#include "rg_launch.h"
 
 #include <algorithm>
 #include <mutex>
@@ -55,12 +56,7 @@ __device__ __forceinline__ void copy_tail(const uint8_t *src, uint8_t *dst, uint
 }
 
 constexpr int GATHER_THREADS = 256;
-constexpr int CHUNKS_IN_FLIGHT = 8;
 
-// TAILPIECE = false: every piece is a full vector.  Either row_bytes is a multiple of VEC, or the last piece of a
-// row is the vector that ENDS at the row's end and overlaps its predecessor (both write the same bytes there), so
-// that no lane leaves the vector path.  TAILPIECE = true (row widths that are no multiple of 4, or below VEC): the
-// last piece is copied in 8/4/2/1-byte parts.
 // Where a row comes from, out of a routing entry or a routing code.
 __device__ __forceinline__ void decode_route(int64_t e, uint32_t, int64_t &tag, uint64_t &row) { tag = entry_tag(e); row = (uint64_t)entry_row(e); }
 __device__ __forceinline__ void decode_route(uint32_t c, uint32_t last_remote, int64_t &tag, uint64_t &row)
@@ -69,6 +65,10 @@ __device__ __forceinline__ void decode_route(uint32_t c, uint32_t last_remote, i
     row = c > last_remote ? ~c : c & ~CODE_NOT_LOCAL;
 }
 
+// TAILPIECE = false: every piece is a full vector.  Either row_bytes is a multiple of VEC, or the last piece of a
+// row is the vector that ENDS at the row's end and overlaps its predecessor (both write the same bytes there), so
+// that no lane leaves the vector path.  TAILPIECE = true (row widths that are no multiple of 4, or below VEC): the
+// last piece is copied in 8/4/2/1-byte parts.
 template <int VEC, int A, bool TAILPIECE, typename ROUTE>
 __global__ void __launch_bounds__(GATHER_THREADS) gather_rows_kernel(const ROUTE *__restrict__ routes, uint32_t last_remote, int64_t n_rows, int skip_remote,
                                                                      RowSources src, uint32_t row_bytes,
@@ -232,29 +232,14 @@ rg_status launch_gather(const Routes &routes, int64_t n_rows, RowsWanted wanted,
     const uint64_t per_block = (uint64_t)GATHER_THREADS * chunks;
     const uint64_t blocks = std::max<uint64_t>(1, std::min<uint64_t>((total + per_block - 1) / per_block, (uint64_t)n_cu * 32));
     const int skip_remote = wanted == ROWS_NOT_REMOTE ? 1 : 0;
-    // rows per wave of the remote rows' kernel: two pieces a lane, or a single row, fewer rows where that leaves compute units without waves (rows of
-    // 2,408 bytes, 1,971 us at one row a wave and the link's rate, 1,979 at 32; a list of the misses 1,974)
-    int per_wave = 1;
-    while (per_wave < 64 && per_wave * cpt < 128 && n_rows / (2 * per_wave) >= (int64_t)n_cu * 8) per_wave <<= 1;
-    // Few misses of wide rows: a row's pieces are shared out among waves, a round of them (8 KB) or more each (8 rows of 1 MB 419 us with a wave a row, 163 so,
-    // 174 with a list of the misses; one 352 / 32 / 39; with parts for 512 waves, not 64, 64 rows of 64 KB 104 us for 88).
-    int64_t parts = 1;
-    if (per_wave == 1)
-        while (n_remote * parts < 64 && cpt >= (uint64_t)parts * 2 * 64 * CHUNKS_IN_FLIGHT && n_rows * parts <= (int64_t)n_cu * 64) parts *= 2;
-    // Where all rows would be asked for at once and half of them and more are misses, the link is at its best with some hundred waves' loads on it; fewer misses
-    // need more waves to find them, and more rows take further rounds (a list of misses / all waves / LINK_WAVES: 1,000 rows of 16 KB, misses alone 316 / 338 / 306
-    // us; 3,000 of 4 KB 243 / 275 / 229; 30,000 of 400 bytes 308 / 313 / 285, half of them misses 166 / 167 / 159; 20,000 of 2,408 bytes, half 480 / 470 / 483, a
-    // twentieth 79 / 71 / 85; 100,000, misses alone, on a stream beside 4,540 / 4,520 / 4,680).
-    constexpr int64_t LINK_WAVES = 256, waves_here = GATHER_THREADS / 64;
-    const int64_t n_units = (n_rows * parts + per_wave - 1) / per_wave, all_waves = (int64_t)n_cu * 32 * waves_here;
-    const int64_t n_waves = std::min(n_units, n_units <= all_waves && n_remote * 2 >= n_rows ? LINK_WAVES : all_waves);
-    const unsigned remote_blocks = (unsigned)((n_waves + waves_here - 1) / waves_here);
+    const RemoteShape remote = remote_shape(n_rows, n_remote, cpt, vec, n_cu);
+    const unsigned remote_blocks = (unsigned)((remote.waves + GATHER_THREADS / 64 - 1) / (GATHER_THREADS / 64));
     ScopedTimer tm(group, st);
 #define RG_GATHER_ROWS(V, AL, TAIL, ROUTE, FROM)                                                                                              \
     do {                                                                                                                                      \
         if (wanted == ROWS_REMOTE)                                                                                                            \
             hipLaunchKernelGGL((gather_remote_kernel<V, AL, TAIL, ROUTE>), dim3(remote_blocks), dim3(GATHER_THREADS), 0, st, FROM,            \
-                               routes.last_remote, n_rows, per_wave, (uint32_t)parts, src, row_bytes, out, out_stride);                       \
+                               routes.last_remote, n_rows, remote.per_wave, (uint32_t)remote.parts, src, row_bytes, out, out_stride);         \
         else                                                                                                                                  \
             hipLaunchKernelGGL((gather_rows_kernel<V, AL, TAIL, ROUTE>), dim3((unsigned)blocks), dim3(GATHER_THREADS), 0, st, FROM,           \
                                routes.last_remote, n_rows, skip_remote, src, row_bytes, out, out_stride, chunks);                             \

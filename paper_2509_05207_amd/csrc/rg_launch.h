@@ -39,6 +39,38 @@ inline PositionUnits position_units(int64_t n_cur, int64_t n_samples, uint32_t f
     return PositionUnits{(uint32_t)nodes, n, grid_for((n + POS_WAVES - 1) / POS_WAVES, POS_THREADS)};
 }
 
+// ---------------------------------------------------------------- remote rows out of pinned memory (gather_remote_kernel)
+constexpr int CHUNKS_IN_FLIGHT = 8;      // loads a lane has under way (of both gather kernels)
+constexpr int64_t LINK_BYTES = 2 << 20;
+struct RemoteShape {
+    int per_wave;                        // consecutive rows of a wave's round
+    int64_t parts;                       // waves to a row (then per_wave is 1)
+    int64_t waves;
+};
+// n_remote of n_rows rows are remote, pieces to a row, vec bytes to a piece.
+inline RemoteShape remote_shape(int64_t n_rows, int64_t n_remote, uint64_t pieces, int vec, int n_cu)
+{
+    // Two pieces a lane, or a single row, fewer rows where that leaves compute units without waves (rows of 2,408 bytes, 1,971 us at one row a wave
+    // and the link's rate, 1,979 at 32; a list of the misses 1,974).
+    RemoteShape r{1, 1, 0};
+    while (r.per_wave < 64 && r.per_wave * pieces < 128 && n_rows / (2 * r.per_wave) >= (int64_t)n_cu * 8) r.per_wave <<= 1;
+    // Few misses of wide rows: a row's pieces are shared out among waves, a round of them (8 KB) or more each (8 rows of 1 MB 440 us with a wave a row, 171 so,
+    // 181 with a list of the misses; one 352 / 32 / 39; with parts for 512 waves, not 64, 64 rows of 64 KB 104 us for 88).
+    if (r.per_wave == 1)
+        while (n_remote * r.parts < 64 && pieces >= (uint64_t)r.parts * 2 * 64 * CHUNKS_IN_FLIGHT && n_rows * r.parts <= (int64_t)n_cu * 64) r.parts *= 2;
+    // Where all rows would be asked for at once the link is at its best with LINK_BYTES on it, so that the more of its pieces a wave has under way, the fewer
+    // waves (a list of misses / all waves / so, us: 1,000 rows of 16 KB, misses alone 326 / 346 / 313; 3,000 of 4 KB 250 / 285 / 244, half of them misses 144 / 160 / 137,
+    // a fifth 79 / 70 / 71; 30,000 of 400 bytes 312 / 324 / 300; 20,000 of 2,408 930 / 930 / 922). Where pieces are single bytes fewer waves are slower
+    // (20,000 rows of 1,202 bytes, half of them misses 381 / 357 / 390); more rows than the chip holds waves take further rounds anyway.
+    const int64_t n_units = (n_rows * r.parts + r.per_wave - 1) / r.per_wave, all_waves = (int64_t)n_cu * 128;
+    r.waves = std::min(n_units, all_waves);
+    if (vec == 16 && n_units <= all_waves) {
+        const double under_way = (double)r.per_wave * (double)pieces / (double)r.parts * (double)n_remote / (double)n_rows;
+        r.waves = std::min(r.waves, (int64_t)((double)LINK_BYTES / (16.0 * std::min(64.0 * CHUNKS_IN_FLIGHT, std::max(1.0, under_way)))));
+    }
+    return r;
+}
+
 // ---------------------------------------------------------------- computation blocks
 // By ranks (block_ranks_kernel) rather than by tables of positions: where the batches are so many that each has few workgroups to make bitmaps for, and where a
 // batch has samples enough to pay for clearing and counting them, some 18 us a round of workgroups at 233,000 nodes (edges: samples of all hops and batches).

@@ -18,6 +18,10 @@ int main()
             const rg::PositionUnits u = rg::position_units(a[0], a[1], (uint32_t)a[2], a[3] != 0, a[4], (uint32_t)a[5], (int)a[6], a[7] != 0);
             printf("%u %lld %u\n", u.nodes, (long long)u.n, u.grid);
         }
+        if (!strcmp(what, "remote")) {
+            const rg::RemoteShape r = rg::remote_shape(a[0], a[1], a[2], (int)a[3], (int)a[4]);
+            printf("%d %lld %lld\n", r.per_wave, (long long)r.parts, (long long)r.waves);
+        }
         if (!strcmp(what, "ranks")) printf("%d\n", rg::blocks_by_ranks(a[0], (uint32_t)a[1], a[2], a[3], (int)a[4]) ? 1 : 0);
     }
 }
@@ -88,3 +92,35 @@ def test_units_by_what_bounds_them(shapes, n_cur, row, fanout, scattered, nodes)
 ])
 def test_blocks_by_ranks_where_they_are_faster(shapes, n, hops, batches, per_batch, by_ranks):
     assert shapes("ranks", n, hops, batches, batches * per_batch, 256) == [int(by_ranks)]
+
+
+@pytest.mark.parametrize("rows,misses,row_bytes,vec,least,most", [
+    # waves; measured, us with 256 / 512 to 1,024 / all of them, a wave to 64 rows and fewer
+    (1_000, 1_000, 16_384, 16, 256, 256),            # 315 / - / 346
+    (3_000, 3_000, 4_096, 16, 400, 700),             # 240 / 244 / 285
+    (3_000, 600, 4_096, 16, 2_000, 3_000),           # a fifth: 79 / - / 70
+    (30_000, 30_000, 400, 16, 500, 1_000),           # 294 / 300 / 324
+    (20_000, 20_000, 1_202, 1, 20_000, 20_000),      # 1,643 / - / 641
+    (20_000, 10_000, 1_202, 1, 20_000, 20_000),      # 1,045 / - / 357
+    (2_000, 2_000, 16, 16, 2_000, 2_000),            # 38 / - / 24
+    (5_000, 5_000, 17, 1, 1_250, 5_000),             # 48 / - / 32
+    (8, 8, 1 << 20, 16, 64, 64),                     # (shared out in parts)
+    (100_000, 100_000, 2_408, 16, 32_768, 32_768),
+])
+def test_waves_that_ask_the_link(shapes, rows, misses, row_bytes, vec, least, most):
+    pieces = -(-row_bytes // vec)
+    per_wave, parts, waves = shapes("remote", rows, misses, pieces, vec, 256)
+    assert least <= waves <= most
+
+
+@pytest.mark.parametrize("rows", [1, 7, 64, 2_047, 4_096, 100_000, 2**31 - 1])
+@pytest.mark.parametrize("pieces", [1, 2, 63, 64, 128, 1_024, 65_537, 2**28, 2**32 - 1])
+@pytest.mark.parametrize("one_in", [1, 2, 30])
+@pytest.mark.parametrize("vec", [1, 16])
+def test_remote_rows_have_waves(shapes, rows, pieces, one_in, vec):
+    per_wave, parts, waves = shapes("remote", rows, max(1, rows // one_in), pieces, vec, 256)
+    assert 1 <= per_wave <= 64 and parts >= 1 and (per_wave == 1 or parts == 1)
+    assert 1 <= waves <= 32_768
+    assert rows * parts < 2**40                                  # the kernel counts units in 64 bits
+    if parts > 1:
+        assert pieces // parts >= 512                            # a part is a round of pieces
