@@ -55,9 +55,13 @@ inline RemoteShape remote_shape(int64_t n_rows, int64_t n_remote, uint64_t piece
     RemoteShape r{1, 1, 0};
     while (r.per_wave < 64 && r.per_wave * pieces < 128 && n_rows / (2 * r.per_wave) >= (int64_t)n_cu * 8) r.per_wave <<= 1;
     // Few misses of wide rows: a row's pieces are shared out among waves, a round of them (8 KB) or more each (8 rows of 1 MB 440 us with a wave a row, 171 so,
-    // 181 with a list of the misses; one 352 / 32 / 39; with parts for 512 waves, not 64, 64 rows of 64 KB 104 us for 88).
+    // 181 with a list of the misses; one 352 / 32 / 39; with parts for 512 waves, not 64, 64 rows of 64 KB 104 us for 88).  Where pieces are single bytes a
+    // round has little under way, and more waves of two pieces a lane are the better (500 rows of 9,602 bytes, half of them misses, a wave a row / so / a list 189 / 89 / 93 us;
+    // 300 of 3,001, misses alone 76 / 45 / 56; 3,000 of 1,202, a tenth 48 / 37 / 43).
+    const uint64_t least = vec == 16 ? 64 * CHUNKS_IN_FLIGHT : 128;
+    const int64_t busy = vec == 16 ? 64 : (int64_t)n_cu * 64;
     if (r.per_wave == 1)
-        while (n_remote * r.parts < 64 && pieces >= (uint64_t)r.parts * 2 * 64 * CHUNKS_IN_FLIGHT && n_rows * r.parts <= (int64_t)n_cu * 64) r.parts *= 2;
+        while (n_remote * r.parts < busy && pieces >= (uint64_t)r.parts * 2 * least && n_rows * r.parts <= (int64_t)n_cu * 64) r.parts *= 2;
     // Where all rows would be asked for at once the link is at its best with LINK_BYTES on it, so that the more of its pieces a wave has under way, the fewer
     // waves (a list of misses / all waves / so, us: 1,000 rows of 16 KB, misses alone 326 / 346 / 313; 3,000 of 4 KB 250 / 285 / 244, half of them misses 144 / 160 / 137,
     // a fifth 79 / 70 / 71; 30,000 of 400 bytes 312 / 324 / 300; 20,000 of 2,408 930 / 930 / 922). Where pieces are single bytes fewer waves are slower

@@ -165,7 +165,7 @@ def test_misses_of_a_pinned_table(rg, n, missing, row_bytes):
         assert (got[:, row_bytes:] == 7).all()
 
 
-@pytest.mark.parametrize("row_bytes", [16383, 16384, 16400, 30_002, 100_004, (1 << 20) + 4])
+@pytest.mark.parametrize("row_bytes", [255, 257, 1202, 16383, 16384, 16400, 30_002, 100_004, (1 << 20) + 4])
 @pytest.mark.parametrize("n,missing", [(1, 1.0), (7, 1.0), (40, 0.5), (600, 0.01)])
 def test_few_misses_of_wide_rows(rg, n, missing, row_bytes):
     """Rows whose pieces are shared out among waves: one part and many, widths that the parts do not divide, vectors, overlapping last vectors and odd tails."""
