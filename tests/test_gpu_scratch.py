@@ -27,10 +27,12 @@ def test_scratch_of_the_shuffle(rg):
 
 
 @pytest.mark.parametrize("look", ["1", "0"])
-def test_scratch_of_a_plan(rg, look, monkeypatch):
-    """Beside its entries (8 bytes a position) and its list of misses (4 a miss), a plan takes a bit per position and 20 bytes per
-    2,048 of them while it is made; looking whether row_of is ranks takes nothing (1/64 of the 4 M positions are 0.06 MB)."""
+@pytest.mark.parametrize("codes", ["1", "0"])
+def test_scratch_of_a_plan(rg, look, codes, monkeypatch):
+    """Beside its codes (4 bytes a position; 8 where they have to be entries) a plan takes 4 bytes per 512 positions while it is made; looking whether
+    row_of is ranks takes nothing.  The selection's scratch is 8 bytes per 2,048 nodes and 0.13 MB."""
     monkeypatch.setenv("RAPIDGNN_ROW_RANKS", look)
+    monkeypatch.setenv("RAPIDGNN_PLAN_CODES", codes)
     rng = np.random.default_rng(1)
     n, d = 4_000_000, "cuda"
     indptr, indices = torch.zeros(n + 1, dtype=torch.int64, device=d), torch.zeros(0, dtype=torch.int32, device=d)
@@ -41,7 +43,7 @@ def test_scratch_of_a_plan(rg, look, monkeypatch):
     feat = rg.make_features(torch.from_numpy(is_local).to(d), torch.from_numpy(row_of).to(d), table, table, 16)
     a = RecordingAllocator(rg)
     c = rg.rg_build_cache([s], feat, 0, allocator=a.struct)
-    n_miss = int((is_local == 0).sum())
-    assert a.live < 8 * n + 4 * n_miss + n + n // 2 + (1 << 18)              # entries, misses; the tally's byte and the slot map's half per node
-    assert a.peak - a.live < n // 8 + n // 64 + (1 << 18)
+    route = 4 if codes == "1" else 8
+    assert a.live < route * n + n + n // 2 + (1 << 18)                       # routes; the tally's byte and the slot map's half per node
+    assert a.peak - a.live < n // 128 + n // 256 + (1 << 18)
     del c
