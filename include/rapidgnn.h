@@ -180,7 +180,8 @@ rg_status rg_schedule_samples(const rg_schedule *s, uint32_t hop, const int64_t 
  * request, not stored).  A file is checked while it is read -- magic, header
  * ranges, offsets monotone and consistent between hops, every node ID inside
  * [0, n_nodes), exact length -- and refused with RG_EIO otherwise; nothing
- * is written through `out` then. */
+ * is written through `out` then.  rg_schedule_save leaves each hop's new IDs of a
+ * batch in ascending order; files with another order are read too. */
 rg_status rg_schedule_save(const rg_schedule *s, const char *path, void *stream);
 rg_status rg_schedule_load(const char *path, const rg_allocator *a, void *stream, rg_schedule **out);
 
@@ -231,7 +232,8 @@ typedef struct rg_features {
  * RAPIDGNN_ROW_RANKS=1 / 0 makes the plans look whether row_of numbers the local
  * and the remote nodes in the order of their IDs, in which case they need not read
  * it, / not look (default: from 2^24 listed input nodes on, if they are eight per
- * node of the graph).  Same results either way.  The fill of the table runs on a stream the library
+ * node of the graph); RAPIDGNN_PLAN_CODES=0 keeps the routing in 8 bytes per input
+ * node instead of 4, as a remote row of 2^31 - K_eff and more does by itself.  Same results either way.  The fill of the table runs on a stream the library
  * owns, beside the routing work on `stream`; the call returns after both.
  */
 rg_status rg_build_cache(const rg_schedule *const *epochs, uint32_t n_epochs, const rg_features *f,
@@ -348,7 +350,12 @@ void rg_trim_memory(void);
  * block (rg_gather_batch) are in source order of the outermost block.
  *   workspace_limit_bytes  device scratch for position tables, 4 * n_nodes
  *                          bytes per batch processed together; 0 = 4 GiB.
- *                          At least one batch's table is always allocated.
+ *                          At least one batch's table is allocated, except where
+ *                          no tables are needed: small graphs with many batches,
+ *                          whose positions are ranks (6 (L + 1) bytes per 32 nodes,
+ *                          and 4 per seed of the largest batch, fit 150 KB).
+ * Environment: RAPIDGNN_BLOCK_RANKS=1 / 0 takes ranks wherever they fit / never
+ * (default: where they are the faster).  Same results either way.
  * Waits for `stream`.  A second call is a no-op.  rg_schedule_block returns
  * RG_EINVAL before the blocks are built, RG_ERANGE for hop >= L.
  *   src_pos_dev  dev int32 [n_samples of the hop], owned by the schedule */

@@ -149,6 +149,8 @@ __device__ __forceinline__ bool add_hub_row(const HubTable &h, uint32_t v, int64
 // have less than half as many entries as the graph has nodes there is little to share: those go by frontier position (n_batches = 0).
 // By position / by place: 233,000 nodes, 147 batches of 80,000, fan-out 10: the sampling launches 3.06 / 2.84 ms; 2.45 M nodes, 196 of 110,000, 7.17 / 6.94, and the
 // records of its nodes (random 128-byte lines of indptr) 448 / 308 us; 147 of 14,000, records 82 / 52 us; 111 M nodes, 147 of 5,800, 1.45 / 1.49 ms.
+// The positions sampler alike: 233,000 nodes, 147 batches of 25,000, fan-out 10, 649 / 535 us; 2.45 M nodes, 196 of 170,000, fan-out 5, 1,956 / 1,465; 15 M nodes, 147 of
+// 16,000 1,075 / 1,501; but rows that are copied whole (2.45 M nodes, 196 of 51,000, fan-out 50 of 50 IDs) 2,007 / 2,353.
 struct ByPlace {
     const int64_t *batch_off;                   // dev
     uint32_t n_batches;
@@ -2030,8 +2032,8 @@ static rg_status launch_hop(const HopArgs &args, int n_cu, unsigned merge_grid, 
 // average, but the longest of 64 takes four to six, which is what a lane per draw waits for.  So a wave takes a unit of nodes, up to
 // POS_DRAWS draws, lists the draws that walk and deals them out to its lanes as they come free; positions are kept in LDS, and
 // the rows read at all of them afterwards (233,000 nodes, 147 batches, fan-outs 25, 10, 29 M draws: a lane per draw / so 452 / 343 us).
-// BY_PLACE (see ByPlace): an instantiation of its own, since the look at every unit's batch costs the other (with a lane per draw: 111 M nodes, fan-outs
-// 15, 10 362 us without, 382 with it; 50, 3 289 and 315).
+// BY_PLACE (see ByPlace): an instantiation of its own (one kernel that looks whether units go by place, units by position: sampling 10 M nodes, fan-out 50, rows of 50,
+// 2,007 / 2,019 us; 3.7 M, fan-out 10, 649 / 651).
 constexpr int POS_IN_FLIGHT = 4;
 struct PosNode {
     uint64_t state;
@@ -2267,7 +2269,8 @@ static uint32_t mark_piece_words(const ReachedMaps &m, uint32_t pieces) { return
 // costs 25 to 40 ps where little hides it, next to nothing while rows are read, and more where many meet on a word.  So the pass
 // (schedules, marked by the kernels / by the pass)
 //  - from one sample per MARK_SPARSE IDs of bitmap on: 2.45 M nodes, one hop, 1.6 M samples, keys sampler one per 2,816 685 / 758 us, 1,432
-//    616 / 604, 710 449 / 426, 355 347 / 319; positions sampler, whose scattered reads leave marks more to hide behind, 710 417 / 450, 355 318 / 337, 177 282 / 297;
+//    616 / 604, 710 449 / 426, 355 347 / 319; the positions sampler, whose launch is shorter, is faster by the pass at one per 1,531 already (524 / 503, 766 389 / 371,
+//    383 311 / 277), and with fewer samples than MARK_MANY (1.6 M in 16 batches 236 / 203): the lines are the keys sampler's;
 //  - there, from MARK_MANY samples on, or MARK_CROWD per word (one batch, fan-outs 50, 50, 2.45 M nodes, 0.5 M samples in the second hop
 //    289 / 310, 1.0 M 321 / 317, 1.8 M 387 / 348, 3.3 M 508 / 393, 9.8 M 1,067 / 531; 30,000 nodes, one batch, 237 per word 329 / 263; ten batches on
 //    40,000 nodes, 15 per word 243 / 247, 26 267 / 268, 46 300 / 297, 77 328 / 317);
