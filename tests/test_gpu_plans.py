@@ -179,7 +179,7 @@ def test_few_misses_of_wide_rows(rg, n, missing, row_bytes):
     is_local[rng.permutation(n)[: max(1, int(n * missing))]] = 0
     row_of = np.where(is_local, np.cumsum(is_local) - 1, np.cumsum(1 - is_local) - 1).astype(np.int32)
     table = rng.integers(0, 256, size=(n, row_bytes + 5)).astype(np.uint8)
-    for pad in (0, 4):                                           # strides of the tables and of the block
+    for pad in sorted({0, 4, -row_bytes % 4}):                   # strides of the tables and of the block; the last: vectors whatever the width
         rows = np.ascontiguousarray(table[:, : row_bytes + pad])
         local = torch.from_numpy(np.concatenate([rows[is_local == 1], rows[:1]])).to(d)
         remote = torch.from_numpy(np.concatenate([rows[is_local == 0], rows[:1]])).pin_memory()
